@@ -33,7 +33,7 @@ inline tl_status from_hip(hipError_t e) { return e == hipSuccess ? TL_OK : TL_ER
 // Most activation rows one launch of the 1.6-bit weight-streaming kernel takes.
 constexpr int64_t kGemvMaxM = 4096;
 
-// Small-M kernel (blocks of 16 or 32 activation rows that each stream W) or LDS-tiled MFMA
+// Small-M kernel (blocks of 16 or 32 activation rows that each stream W) or tiled matrix-core
 // kernel, when both can run the shape: whichever the cost models below make cheaper.  They are
 // fits to measurements (us; W in MB of packed weights):
 //  * small-M, blocks of 32 rows, one pass over K: 4 + blocks x (0.31 + 0.2 W)
@@ -43,11 +43,7 @@ constexpr int64_t kGemvMaxM = 4096;
 //  * small-M, blocks of 16 rows: 3.8 + blocks x W x (0.17 while W stays in the L2 caches, 0.21
 //    beyond), at least 0.3 per block; when K needs several passes 1 + 3 passes + blocks x 0.175 W
 //    (11008 -> 4096: 2 blocks 13.7 us, 16 blocks 44.2 us)
-//  * MFMA, 128 x 128 tiles (at most one per CU): 7 + K/64 x (0.43 + 0.09 (tiles - 128)/128 beyond 128
-//    tiles) with two sets of waves per tile (K % 128 == 0), else 4 + K/64 x (0.53 + 0.04 tiles/256)
-//  * MFMA, 128 x 256 tiles: (5 + K/64 x 0.86) x f(tiles/256), f(r) = 1 up to one tile per CU, then
-//    max(r, 0.82 ceil(r)): a round that is not full costs most of a full one
-//    (4096 -> 14336: 336 tiles 98 us, 448 tiles 107 us, 896 tiles 219 us).
+//  * tiled matrix-core kernel: mfma_time (tl_tile_2bit.hip)
 inline bool prefer_small_m(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 16) return true;
@@ -71,28 +67,11 @@ inline bool prefer_small_m(int64_t M, int64_t N, int64_t K)
         const double per_block = per_mb * w_mb > 0.3 ? per_mb * w_mb : 0.3;
         t_small = 3.8 + double((M + 15) / 16) * per_block;
     }
-    const double steps = double(K / 64);
-    const double row_blocks = double((M + 127) / 128);
-    const double wide = row_blocks * double((N + 255) / 256);
-    double t_mfma;
-    if (wide <= 128.0) {                                   // 128 x 128 tiles, at most one per CU
-        const double tiles = row_blocks * double((N + 127) / 128);
-        if (K % 128 == 0)                                  // two sets of waves per tile
-            t_mfma = 7.0 + steps * (0.43 + 0.09 * (tiles > 128.0 ? (tiles - 128.0) / 128.0 : 0.0));
-        else
-            t_mfma = 4.0 + steps * (0.53 + 0.04 * tiles / 256.0);
-    } else {                                               // 128 x 256 tiles, in rounds of 256
-        const double r = wide / 256.0;
-        const double rounds = double(int64_t(r) + (r > double(int64_t(r)) ? 1 : 0));
-        const double f = r <= 1.0 ? 1.0 : (r > 0.82 * rounds ? r : 0.82 * rounds);
-        t_mfma = (5.0 + steps * 0.86) * f;
-    }
-    // The constants above were fitted on one machine, and machines differ by several percent
-    // (the same library: 18.3 and 19.6 us for the same launch).  Near the crossover the two kernels
-    // are within that spread of each other, so a band rather than the bare comparison decides:
-    // beyond 16 rows the tiled kernel takes the shape unless the model puts the small-M kernel
-    // ahead by more than 5 %.
-    return 1.05 * t_small < t_mfma;
+    // The constants are fits on one machine, and machines differ by several percent (the same library:
+    // 18.3 and 19.6 us for the same launch).  Near the crossover the two kernels are within that spread of each
+    // other, so a band rather than the bare comparison decides: beyond 16 rows the small-M kernel keeps a shape unless
+    // the model puts the tiled kernel ahead by more than 7 %.
+    return t_small < 1.07 * tl::mfma_time(M, N, K);
 }
 
 }  // namespace
@@ -118,7 +97,7 @@ tl_status tl_unpack_dev(tl_format fmt, const void* packed, int64_t N, int64_t K,
 tl_path tl_ternary_gemm_which(int64_t M, int64_t N, int64_t K)
 {
     if (!tl::dims_ok(M, N, K)) return TL_PATH_AUTO;
-    if (tl::gemv_supports(M, N, K) && (tl::prefer_small_m(M, N, K) || !tl::mfma_supports(M, N, K))) return TL_PATH_GEMV;
+    if (tl::gemv_supports(M, N, K) && (!tl::mfma_supports(M, N, K) || tl::prefer_small_m(M, N, K))) return TL_PATH_GEMV;
     if (tl::mfma_supports(M, N, K)) return TL_PATH_MFMA;
     return TL_PATH_GENERIC;
 }

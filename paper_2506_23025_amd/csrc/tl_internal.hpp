@@ -102,8 +102,10 @@ struct Gemm3Desc {
 bool gemv3_groups(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStream_t s);
 
-// LDS-tiled MFMA prefill kernel (2-bit).  Needs K % 64 == 0.
+// Tiled matrix-core kernel for many activation rows (2-bit).  Needs K % 64 == 0.
 bool mfma_supports(int64_t M, int64_t N, int64_t K);
+// what it is expected to take (us), with the tile shape it would choose
+double mfma_time(int64_t M, int64_t N, int64_t K);
 hipError_t launch_mfma(const __half* x, const uint32_t* Wp, float gamma, __half* y,
                        int64_t M, int64_t N, int64_t K, hipStream_t s);
 

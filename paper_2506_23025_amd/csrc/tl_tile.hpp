@@ -1,0 +1,786 @@
+// The tiled matrix-core kernel for many activation rows: Y = X (gamma What)^T of App. B with the
+// packed forms of Sec. 3 decoded to fp16 in registers right before the matrix instruction that
+// consumes them.  One kernel for every packed form (2-bit words, 2-bit words with group scales,
+// both 1.6-bit byte codes) and every K; what differs is how a step's weights get into LDS.
+//
+// A workgroup of 8 waves owns a BM x BN tile of Y.  K is walked in steps of KS = 32 NP; the waves form
+// WK sets that share the NP 32-k blocks of a step out among them, and WM x WN waves per set, each with
+// FM x FN fragments of v_mfma_f32_16x16x32_f16.
+//
+//  * What bounds it: at full size the chip's power.  A loop of nothing but the matrix instruction on this data gives
+//    1.85 (32x32x16, W as the row operand), 2.0 (32x32x16, X as the row operand) and 2.3 PFLOP/s (16x16x32), so
+//    the 16x16x32 form is used; without the X fragment reads the kernel is 20 % faster, without the decode 6 %.
+//    Small tiles are bound by instruction issue (11 vector operations of decode per FM matrix instructions) and by
+//    the start and end of a launch (5 to 6 us of it in a 20 us call).
+//  * X goes to LDS as it lies in memory, by LDS-DMA (global_load_lds_dwordx4: no registers, no
+//    vector instructions), ST steps ahead.  16-byte pieces of a row are swizzled by row on the way
+//    in so that the fragment reads are free of bank conflicts.
+//  * W stays packed in LDS: a 2-bit word holds 16 codes of one column, 1/8 of the bytes of fp16.  A lane
+//    (column i, k quarter g) needs half a word as pairs of neighbours: with t = w >> 2, one byte permute of
+//    (w, t) puts code 2q at bit 4q and code 2q + 1 at bit 4q + 16.  `& mask | 0x64006400` makes an fp16
+//    pair (1024 + 16^q c), one packed fma turns it into (c - 1) exactly: 11 vector operations per 8 weights
+//    and lane, and a decoded operand feeds FM matrix instructions.
+//  * 1.6-bit forms are transcoded to 2-bit words once per workgroup and step: a thread looks up the
+//    8 bytes of a column's 40 weights in a 256-entry table of 10-bit entries and writes 80 bits of
+//    codes to LDS two steps before they are used.  A step is then 160 k or a multiple.
+//  * Group scales (one per 16 k, or per set and step, and column) travel with the step by LDS-DMA
+//    and multiply the decoded operand: s (c - 1) is exact in fp16.
+//  * One barrier per step, and it stands before the last block's matrix instructions, whose
+//    operands are in registers by then; the transfers of the step ST further on are spread between the matrix
+//    instructions (all of them right behind the barrier: 385k instead of 361k clocks for two tiles of
+//    256 x 256 x 4096).
+//  * The W fragments are the 16-row operand, so a lane ends up with four consecutive columns of a row of Y;
+//    they are turned through LDS and stored in 16-byte pieces.
+//
+// Measured, 4096 -> 14336, M = 2048 (256 x 256 tiles): 172 to 184 us (1.31 to 1.40 PFLOP/s) on four machines where the
+// kernel before (128 x 256 tiles of 32x32x16, X through registers) took 207 to 216.
+#pragma once
+#include "tl_internal.hpp"
+
+#include <atomic>
+#include <type_traits>
+
+namespace tl {
+
+enum TileFmt { kTile2Bit = 0, kTileGs = 1, kTile1p6 = 2 };
+
+struct TileParams {
+    const __half* x;
+    const unsigned char* W;      // packed rows
+    const __half* scales;        // kTileGs: [ceil(K / group)][N]
+    __half* y;
+    float gamma;
+    int M, N, K;
+    int row_bytes;               // bytes per packed row
+    int group16;                 // kTileGs: 16-k blocks per group
+    int fx;                      // kTile1p6: fixed-point byte code
+    int tiles_m, tiles_n;
+};
+
+// RAGGED: K is not a multiple of 64 (2-bit) or 8 (1.6-bit): rows of X and W start anywhere, X goes
+// through registers (masked past K) and 2-bit words are fetched one by one.
+// UNIT: blocks per scale unit (kTileGs): NB, or 1 when groups are shorter than a set's part of a step.
+template <int FMT_, bool RAGGED_, int FM_, int FN_, int WM_, int WN_, int WK_, int NP_, int ST_, int UNIT_ = 1>
+struct TileCfg {
+    static constexpr int FMT = FMT_, FM = FM_, FN = FN_, WM = WM_, WN = WN_, WK = WK_, NP = NP_;
+    static constexpr bool RAGGED = RAGGED_;
+    static constexpr int ST = RAGGED ? 2 : ST_;
+    static constexpr int NB = (NP + WK - 1) / WK;                 // blocks of a set (sets past NP % WK have one less)
+    static constexpr int BM = 16 * FM * WM, BN = 16 * FN * WN;
+    static constexpr int KS = 32 * NP;
+    static constexpr int P = KS / 8;                              // 16-byte pieces per X row and step
+    static constexpr int XD = (BM * P + 511) / 512;               // pieces per thread and step
+    static constexpr int XST = XD * 8192;                         // bytes of an X stage (surplus pieces land in its padding)
+    static constexpr bool CODES = FMT == kTile1p6;                // W goes through the transcoder
+    static constexpr int CH = KS / 80;                            // 1.6-bit: 16-byte chunks per column and step
+    static constexpr int WST = CODES ? BN * CH * 16 : BN * KS / 4;   // bytes of a W stage (raw bytes or words)
+    static constexpr int WSLOTS = CODES ? 2 : ST;
+    static constexpr int WL = WST / 16 / 8;                       // lanes per wave in the W transfer (16 bytes each)
+    static constexpr int WD = (RAGGED && !CODES) ? WST / 4 / 512 : 1;   // W transfers per wave and step
+    static constexpr int CST = CODES ? BN * KS / 4 : 0;           // a slot of transcoded words, [word][column]
+    static constexpr bool PARTIAL = RAGGED || CODES || KS > 64;   // the last step may reach past K
+    static constexpr int UNIT = UNIT_;
+    static constexpr int NU = FMT == kTileGs ? 2 * NP / UNIT : 0; // scale rows per step
+    static constexpr int SD = (NU * BN + 511) / 512;              // scale transfers per wave and step
+    static constexpr int SST = SD * 2048;
+    static constexpr int OFF_W = ST * XST;
+    static constexpr int OFF_S = OFF_W + WSLOTS * WST;
+    static constexpr int OFF_C = OFF_S + ST * SST;
+    static constexpr int OFF_T = OFF_C + 2 * CST;
+    static constexpr int RING = OFF_T + (CODES ? 1024 : 0);
+    static constexpr int RED = WK > 1 ? 4 * FM * FN * 1024 : 0;   // half of the waves hand over their sums
+    static constexpr int OUT = 8 * 16 * (FN * 32 + 16);           // 16 rows of every wave's tile as fp16
+    static constexpr int LDS = RING > RED ? (RING > OUT ? RING : OUT) : (RED > OUT ? RED : OUT);
+    static constexpr int OCC = LDS <= 80 * 1024 ? 4 : 2;          // waves per SIMD: two workgroups per CU where LDS holds them
+    static_assert(WM * WN * WK == 8, "8 waves");
+    static_assert(LDS <= 160 * 1024, "tile does not fit");
+    static_assert(FN == 2 || FN == 4, "rolling decode: a fragment is decoded while the others are multiplied");
+    static_assert((CODES ? KS % 80 == 0 : KS % 64 == 0) && WL <= 64 && WD >= 1, "step");
+    static_assert(UNIT == 1 || (UNIT == 2 * NB && NP % WK == 0), "scale unit: 16 k, or a set's part of a step");
+};
+
+namespace tile {
+
+template <int N>
+__device__ __forceinline__ void wait_vm()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+
+// LDS writes and reads of this wave done, then the workgroup's barrier; global transfers stay in flight
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
+}
+
+// The transfers are written out by hand (LDS base in M0, lane l lands at base + 16 l or + 4 l): a transfer
+// the compiler knows of makes it drain the memory pipeline before every later LDS access.  Every
+// wait for them is an explicit wait_vm.
+__device__ __forceinline__ void dma16(uint32_t voff, const void* sbase, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+// the same for the lanes of `mask` only (all lanes are active around it)
+__device__ __forceinline__ void dma16_lanes(uint32_t voff, const void* sbase, uint32_t lds, unsigned long long mask)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+                 : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)), "s"(mask) : "memory");
+}
+__device__ __forceinline__ void dma4(uint32_t voff, const void* sbase, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+__device__ __forceinline__ void dma2(uint32_t voff, const void* sbase, uint32_t lds)   // zero-extended to a dword
+{
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_ushort %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+
+__device__ __forceinline__ uint32_t pkfma(uint32_t a, uint32_t b, uint32_t c)
+{
+    const f16x2 r = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b),
+                                              __builtin_bit_cast(f16x2, c));
+    return __builtin_bit_cast(uint32_t, r);
+}
+
+// half of a packed word (8 codes, in order) -> fp16 c - 1; sel: the byte selector of this lane's half
+__device__ __forceinline__ u32x4 decode8(uint32_t w, uint32_t sel, uint32_t k1024)
+{
+    const uint32_t u = __builtin_amdgcn_perm(w >> 2, w, sel);
+    const uint32_t v = u >> 8;
+    u32x4 o;
+    o[0] = pkfma((u & 0x00030003u) | k1024, 0x3C003C00u, 0xE401E401u);     // 1024 + c
+    o[1] = pkfma((u & 0x00300030u) | k1024, 0x2C002C00u, 0xD410D410u);     // 1024 + 16 c
+    o[2] = pkfma((v & 0x00030003u) | k1024, 0x3C003C00u, 0xE401E401u);
+    o[3] = pkfma((v & 0x00300030u) | k1024, 0x2C002C00u, 0xD410D410u);
+    return o;
+}
+
+// Piece q of row r of an X stage lies at 16-byte slot r P + slot.  A fragment read takes 4 neighbouring pieces of
+// 16 rows; the slots put one piece of 16 consecutive rows into different bank quads.
+template <int P>
+__device__ __forceinline__ int slot_of(int row, int q)
+{
+    if constexpr (P == 8) return q ^ ((row >> 1) & 7);
+    else if constexpr (P == 20) { const int s = q + ((row >> 2) & 3); return s >= 20 ? s - 20 : s; }
+    else if constexpr (P == 40) { const int s = q + ((row >> 1) & 7); return s >= 40 ? s - 40 : s; }
+    else return q ^ (row & 15);                           // P = 16, 32
+}
+template <int P>
+__device__ __forceinline__ int piece_of(int row, int slot)
+{
+    if constexpr (P == 8) return slot ^ ((row >> 1) & 7);
+    else if constexpr (P == 20) { const int s = slot - ((row >> 2) & 3); return s < 0 ? s + 20 : s; }
+    else if constexpr (P == 40) { const int s = slot - ((row >> 1) & 7); return s < 0 ? s + 40 : s; }
+    else return slot ^ (row & 15);
+}
+
+}  // namespace tile
+
+template <class C>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(C::OCC, C::OCC)))
+tile_kernel(TileParams p)
+{
+    using namespace tile;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr int FM = C::FM, FN = C::FN, NB = C::NB, WK = C::WK, NP = C::NP, KS = C::KS, P = C::P, BN = C::BN, BM = C::BM, ST = C::ST;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int set = wave / (C::WM * C::WN);
+    const int wm = (wave / C::WN) % C::WM, wn = wave % C::WN;
+    const uint32_t lds0 = uint32_t(uintptr_t((const __attribute__((address_space(3))) unsigned char*)lds));
+
+    // Tile order: workgroup ids go round the 8 XCDs, each with an L2 of its own.  An XCD takes a
+    // contiguous piece of an order that walks the grid in bands of 4 row blocks, column by column, so the
+    // workgroups resident on it share row blocks of X four columns at a time and columns of W.
+    int tm, tn;
+    {
+        const int total = p.tiles_m * p.tiles_n;
+        const int xcd = int(blockIdx.x) & 7, q = int(blockIdx.x) >> 3;
+        const int rem = total & 7;
+        const int lin = xcd * (total >> 3) + (xcd < rem ? xcd : rem) + q;
+        const int per_band = 4 * p.tiles_n;
+        const int band = lin / per_band, r = lin - band * per_band;
+        const int height = p.tiles_m - 4 * band < 4 ? p.tiles_m - 4 * band : 4;
+        tn = r / height;
+        tm = 4 * band + (r - tn * height);
+    }
+    const int m_base = tm * BM, n_base = tn * BN;
+    const int K = p.K;
+    const int nblk = (K + 31) >> 5;                       // 32-k blocks
+    const int steps = (nblk + NP - 1) / NP;
+    // the set's blocks of a step: NB of them, or one less, from block0 on
+    constexpr int kFullSets = NP % WK == 0 ? WK : NP % WK;
+    const bool short_set = kFullSets < WK && set >= kFullSets;
+    const int block0 = set * NB - (kFullSets < WK && set > kFullSets ? set - kFullSets : 0);
+
+    // ---- X transfers ------------------------------------------------------------------------------
+    const unsigned char* const xtile = reinterpret_cast<const unsigned char*>(p.x + size_t(m_base) * K);
+    uint32_t xoff[C::XD];                                 // row start within the tile, bytes
+    const int mlast = p.M - 1 - m_base;
+#pragma unroll
+    for (int d = 0; d < C::XD; ++d) {
+        const int lin = (d * 8 + wave) * 64 + lane;
+        const int row = lin / P;
+        xoff[d] = uint32_t(row < mlast ? row : mlast) * uint32_t(K) * 2u;   // rows past M repeat the last one, never stored
+        if constexpr (!C::RAGGED) xoff[d] += uint32_t(piece_of<P>(row, lin - row * P)) * 16u;
+    }
+    // the piece of transfer d, worked out again where it is needed (not kept in a register)
+    auto piece = [&](int d) {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int lin = (d * 8 + wave) * 64 + l;
+        const int row = lin / P;
+        return uint32_t(piece_of<P>(row, lin - row * P));
+    };
+    typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+    u32x4 xreg[C::RAGGED ? C::XD : 1];
+    // DMA form, step s into stage st = s mod ST.  Pieces past K read the row's first piece: their weights are zero, and
+    // a NaN there stays within its own row.
+    auto issue_x = [&](int s, int st, int d, auto inside) {
+        const uint32_t dst = lds0 + uint32_t(st) * C::XST + uint32_t(wave) * 1024u + uint32_t(d) * 8192u;
+        if (!C::PARTIAL || decltype(inside)::value || (s + 1) * KS <= K) {
+            dma16(xoff[d], xtile + size_t(s) * (KS * 2), dst);
+        } else {
+            const uint32_t q = piece(d), k = uint32_t(s) * KS + q * 8u;
+            dma16(k < uint32_t(K) ? xoff[d] + uint32_t(s) * (KS * 2) : xoff[d] - q * 16u, xtile, dst);
+        }
+    };
+    // register form (rows start at any even byte)
+    auto load_x = [&](int s) {
+#pragma unroll
+        for (int d = 0; d < (C::RAGGED ? C::XD : 0); ++d) {
+            const uint32_t k = uint32_t(s) * KS + piece(d) * 8u;
+            typedef const __attribute__((address_space(1))) unsigned char* gb;
+            gb src = (gb)(xtile + size_t(xoff[d]) + size_t(k) * 2);
+            u32x4 v = u32x4{0u, 0u, 0u, 0u};
+            if (k + 8 <= uint32_t(K)) {
+                v = *(const __attribute__((address_space(1))) u32x4_any*)src;
+            } else if (k < uint32_t(K)) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (k + e < uint32_t(K))
+                        v[e >> 1] |= uint32_t(*(const __attribute__((address_space(1))) uint16_t*)(src + 2 * e)) << (16 * (e & 1));
+            }
+            xreg[d] = v;
+        }
+    };
+    auto store_x = [&](int s) {
+#pragma unroll
+        for (int d = 0; d < (C::RAGGED ? C::XD : 0); ++d)
+            *reinterpret_cast<u32x4*>(lds + (s % ST) * C::XST + (d * 8 + wave) * 1024 + lane * 16) = xreg[d];
+    };
+
+    // ---- W transfers --------------------------------------------------------------------------------
+    const unsigned char* const wtile = p.W + size_t(n_base) * size_t(p.row_bytes);
+    const int nlast = p.N - 1 - n_base;
+    constexpr int PW = C::CODES ? C::CH : KS / 64;           // 16-byte pieces per column and step
+    uint32_t woff[C::WD], wpc = 0;
+    if constexpr (C::RAGGED && !C::CODES) {
+#pragma unroll
+        for (int d = 0; d < C::WD; ++d) {
+            const int lin = (d * 8 + wave) * 64 + lane;   // word: column lin / (KS / 16)
+            const int col = lin / (KS / 16);
+            wpc = uint32_t(lin - col * (KS / 16));        // the same for every d: 512 is a multiple of KS / 16
+            woff[d] = uint32_t(col < nlast ? col : nlast) * uint32_t(p.row_bytes);
+        }
+    } else {
+        const int lin = wave * C::WL + lane;
+        const int col = lin / PW;
+        wpc = uint32_t(lin - col * PW);
+        woff[0] = uint32_t(col < nlast ? col : nlast) * uint32_t(p.row_bytes);
+    }
+    auto issue_w = [&](int s, int st, auto inside) {
+        const uint32_t base = lds0 + C::OFF_W + uint32_t(C::CODES ? s & 1 : st) * C::WST;
+        if constexpr (C::RAGGED && !C::CODES) {
+            uint32_t o = (uint32_t(s) * (KS / 16) + wpc) * 4u;
+            if (o >= uint32_t(p.row_bytes)) o = 0;        // past the row: fetched, never used
+#pragma unroll
+            for (int d = 0; d < C::WD; ++d) dma4(woff[d] + o, wtile, base + uint32_t(d * 8 + wave) * 256u);
+        } else {
+            const uint32_t dst = base + uint32_t(wave) * (C::WL * 16);
+            constexpr unsigned long long lanes = C::WL == 64 ? ~0ull : (1ull << (C::WL & 63)) - 1;
+            const unsigned char* src = wtile + size_t(s) * (PW * 16);
+            uint32_t o = woff[0] + wpc * 16u;
+            if constexpr (C::PARTIAL && !decltype(inside)::value) {
+                if ((uint32_t(s) * PW + wpc) * 16u >= uint32_t(p.row_bytes)) o = woff[0];   // past the row: fetched, never used
+            }
+            if constexpr (C::WL == 64) dma16(o, src, dst);
+            else dma16_lanes(o, src, dst, lanes);
+        }
+    };
+
+    // ---- scale transfers ------------------------------------------------------------------------------
+    auto issue_s = [&](int s, int st, int d) {
+        const int first = (d * 8 + wave) * 64;            // BN is a multiple of 64: one scale row per transfer
+        int unit = first / BN;
+        const int col = first - unit * BN + lane;
+        if (unit >= C::NU) unit = C::NU - 1;              // surplus waves write padding
+        int blk = s * (KS / 16) + unit * C::UNIT;
+        if (blk * 16 >= K) blk = (K - 1) >> 4;
+        const size_t g = size_t(blk / p.group16);
+        dma2(uint32_t(col < nlast ? col : nlast) * 2u, p.scales + g * size_t(p.N) + n_base,
+             lds0 + C::OFF_S + uint32_t(st) * C::SST + uint32_t(first) * 4u);
+    };
+    // Transfer d of a step's D: the weights, the scales, then X (the order matters for the 1.6-bit forms: their
+    // bytes are waited for one step before X).
+    constexpr int D = 1 + C::SD + C::XD;
+    auto issue = [&](int s, int st, auto dt, auto inside) {
+        constexpr int d = decltype(dt)::value;
+        if constexpr (d == 0) issue_w(s, st, inside);
+        else if constexpr (d <= C::SD) issue_s(s, st, d - 1);
+        else issue_x(s, st, d - 1 - C::SD, inside);
+    };
+
+    // ---- 1.6-bit bytes -> 2-bit words: 8 bytes (40 weights) per thread -----------------------------------
+    const int nbytes = (K + 4) / 5;
+    uint32_t* const table = reinterpret_cast<uint32_t*>(lds + C::OFF_T);
+    auto transcode = [&](int s, auto inside) {
+        if constexpr (C::CODES) {
+#pragma unroll
+            for (int i0 = 0; i0 < BN * C::CH * 2; i0 += 512) {
+                __builtin_amdgcn_sched_barrier(0);        // one round's look-ups in registers at a time
+                const int w0 = i0 + wave * 64;            // column, then chunk and half (BN is a multiple of 64)
+                if (BN * C::CH * 2 - i0 >= 512 || w0 < BN * C::CH * 2) {
+                    const int part = w0 / BN, col = w0 - part * BN + lane;
+                    const int ch = part >> 1, half = part & 1;
+                    const u32x2 raw = *reinterpret_cast<const u32x2*>(lds + C::OFF_W + (s & 1) * C::WST + (col * C::CH + ch) * 16 + half * 8);
+                    uint32_t e[8];
+#pragma unroll
+                    for (int b = 0; b < 8; ++b) e[b] = table[(raw[b >> 2] >> (8 * (b & 3))) & 255u];
+                    if (!decltype(inside)::value && (s + 1) * (C::CH * 16) > nbytes) {   // bytes past the row count as weight 0
+                        const int b0 = (s * C::CH + ch) * 16 + half * 8;
+#pragma unroll
+                        for (int b = 0; b < 8; ++b)
+                            if (b0 + b >= nbytes) e[b] = 0x155u;
+                    }
+                    const uint32_t d0 = e[0] | (e[1] << 10) | (e[2] << 20) | (e[3] << 30);
+                    const uint32_t d1 = (e[3] >> 2) | (e[4] << 8) | (e[5] << 18) | (e[6] << 28);
+                    const uint32_t d2 = (e[6] >> 4) | (e[7] << 6);       // 16 bits
+                    uint32_t* const c = reinterpret_cast<uint32_t*>(lds + C::OFF_C + (s & 1) * C::CST) + (ch * 5) * BN + col;
+                    uint16_t* const mid = reinterpret_cast<uint16_t*>(c + 2 * BN);
+                    if (half == 0) {
+                        c[0] = d0;
+                        c[BN] = d1;
+                        mid[0] = uint16_t(d2);
+                    } else {                              // 80 bits from bit 80 on
+                        mid[1] = uint16_t(d0);
+                        c[3 * BN] = (d0 >> 16) | (d1 << 16);
+                        c[4 * BN] = (d1 >> 16) | (d2 << 16);
+                    }
+                }
+            }
+        }
+    };
+
+    // ---- fragments ---------------------------------------------------------------------------------------
+    const int fi = lane & 15, fg = lane >> 4;             // row of X / column of W, k quarter of a block
+    const uint32_t sel = (fg & 1) ? 0x07060302u : 0x05040100u;
+    // in a vector register the compiler cannot see through: mask and merge are then one v_and_or_b32
+    uint32_t k1024;
+    asm volatile("v_mov_b32 %0, 0x64006400" : "=v"(k1024));
+    const int xrow = wm * 16 * FM + fi;                   // + 16 a: the swizzle depends on row % 16 alone
+    uint32_t xa[NB];                                      // fragment addresses within a stage, block ks
+#pragma unroll
+    for (int ks = 0; ks < NB; ++ks) {
+        const int blk = block0 + ks < NP ? block0 + ks : 0;
+        xa[ks] = uint32_t(xrow * P + slot_of<P>(xrow, blk * 4 + fg)) * 16u;
+    }
+    const int wcol = wn * 16 * FN + fi;                   // + 16 b
+    f16x8 xf[2][FM];
+    u32x4 wf[FN];
+    // The lane's packed word per fragment: of all blocks of a step, or (1.6-bit forms, three blocks: registers) of one block
+    constexpr int NCW = C::CODES ? 1 : NB;
+    uint32_t cw[FN][NCW];
+    uint32_t sc[FN][C::FMT == kTileGs && C::UNIT == 1 ? NB : 1];
+    constexpr int NS = C::FMT == kTileGs && C::UNIT == 1 ? NB : 1;
+    auto read_x = [&](auto par, int st, auto kst, auto from, auto to) {
+        constexpr int PAR = decltype(par)::value, ks = decltype(kst)::value;
+        const unsigned char* const b = lds + st * C::XST + xa[ks];
+#pragma unroll
+        for (int a = decltype(from)::value; a < decltype(to)::value; ++a)
+            xf[PAR][a] = *reinterpret_cast<const f16x8*>(b + a * (16 * P * 16));
+    };
+    auto read_w = [&](int s, int st, auto kst, auto inside) {
+        const int word0 = block0 * 2 + (fg >> 1);      // + 2 ks
+#pragma unroll
+        for (int b = 0; b < FN; ++b) {
+            const int col = wcol + 16 * b;
+            if constexpr (C::CODES) {
+                const uint32_t* const c = reinterpret_cast<const uint32_t*>(lds + C::OFF_C + (s & 1) * C::CST) + col;
+                cw[b][0] = c[(word0 + 2 * decltype(kst)::value) * BN];
+            } else {
+                const uint32_t* const c = reinterpret_cast<const uint32_t*>(lds + C::OFF_W + st * C::WST) + col * (KS / 16);
+#pragma unroll
+                for (int ks = 0; ks < NCW; ++ks) cw[b][ks] = c[word0 + 2 * ks];
+            }
+            if constexpr (C::PARTIAL && !C::CODES && !decltype(inside)::value) {
+                if ((s + 1) * NP > nblk) {                // blocks past K: weights 0
+#pragma unroll
+                    for (int ks = 0; ks < NCW; ++ks)
+                        if (s * NP + block0 + ks >= nblk) cw[b][ks] = 0x55555555u;
+                }
+            }
+            if constexpr (C::FMT == kTileGs) {
+                const uint32_t* const q = reinterpret_cast<const uint32_t*>(lds + C::OFF_S + st * C::SST) + col;
+#pragma unroll
+                for (int u = 0; u < NS; ++u) sc[b][u] = C::UNIT == 1 ? q[(word0 + 2 * u) * BN] : q[set * BN];
+            }
+        }
+    };
+    // one fragment (16 columns x 32 k): 11 vector operations
+    auto decode = [&](int b, uint32_t word, uint32_t scale) {
+        u32x4 o = decode8(word, sel, k1024);
+        if constexpr (C::FMT == kTileGs) {
+            const _Float16 s1 = __builtin_bit_cast(f16x2, scale)[0];
+            const f16x2 s2 = {s1, s1};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, uint32_t(o[q])) * s2);
+        }
+        wf[b] = o;
+    };
+
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::true_type Inside;                        // the step lies inside K
+    typedef std::false_type Any;
+    // The D transfers of a step are spread over its 2 FN NB slots (two per fragment's matrix instructions): all at
+    // once, they would hold up the waves at the CU's one address path (16 clocks per transfer) with
+    // nothing left in the matrix pipes.  Slots count from the barrier on: the first 2 FN belong to the last block
+    // of step s - ST, the others to the next step's blocks.
+    auto run = [&](auto nb) {
+    constexpr int NB = decltype(nb)::value;
+    constexpr int SLOTS = 2 * FN * NB;
+    typedef std::integral_constant<int, 0> IFirst;
+    typedef std::integral_constant<int, 2 * FN> IEarly;
+    typedef std::integral_constant<int, SLOTS> ISlots;
+    auto issue_slots = [&](int s, int st, auto from, auto to, auto inside) {
+        auto one = [&](auto dt) {
+            constexpr int d = decltype(dt)::value;
+            if constexpr (d < D) {
+                constexpr int slot = d * SLOTS / D;
+                if constexpr (slot >= decltype(from)::value && slot < decltype(to)::value) issue(s, st, dt, inside);
+            }
+        };
+        one(std::integral_constant<int, 0>{}); one(std::integral_constant<int, 1>{}); one(std::integral_constant<int, 2>{});
+        one(std::integral_constant<int, 3>{}); one(std::integral_constant<int, 4>{}); one(std::integral_constant<int, 5>{});
+        one(std::integral_constant<int, 6>{}); one(std::integral_constant<int, 7>{}); one(std::integral_constant<int, 8>{});
+    };
+    static_assert(D <= 9, "transfers per step");
+
+    // ---- prologue: the first steps are requested, step 0 (and for the 1.6-bit forms the words of step 1) complete
+    if constexpr (C::CODES) {
+        for (int b = tid; b < 256; b += 512) {
+            unsigned c[5];
+            if (p.fx) {
+                unsigned v = (unsigned(b) * 243u) >> 8;
+                for (int i = 4; i >= 0; --i) { c[i] = v % 3u; v /= 3u; }
+            } else {
+                unsigned v = b >= 243 ? b - 243 : b;
+                for (int i = 0; i < 5; ++i) { c[i] = v % 3u; v /= 3u; }
+            }
+            table[b] = c[0] | (c[1] << 2) | (c[2] << 4) | (c[3] << 6) | (c[4] << 8);
+        }
+        issue_w(0, 0, Any{});
+        if (steps > 1) issue_w(1, 1, Any{});
+        if constexpr (C::RAGGED) {
+            load_x(0); store_x(0);
+            if (steps > 1) { load_x(1); store_x(1); }
+            if (steps > 2) load_x(2);
+        } else {
+#pragma unroll
+            for (int d = 0; d < C::XD; ++d) {
+                issue_x(0, 0, d, Any{});
+                if (steps > 1) issue_x(1, 1, d, Any{});
+            }
+        }
+        wait_vm<0>();
+        lds_barrier();
+        transcode(0, Any{});
+        if (steps > 1) transcode(1, Any{});
+        lds_barrier();
+        if (steps > 2) {
+            if constexpr (C::RAGGED) issue_w(2, 0, Any{});
+            else issue_slots(2, 2, IFirst{}, IEarly{}, Any{});
+        }
+    } else if constexpr (C::RAGGED) {
+        issue_w(0, 0, Any{});
+        if (steps > 1) issue_w(1, 1, Any{});
+#pragma unroll
+        for (int d = 0; d < C::SD; ++d) {
+            issue_s(0, 0, d);
+            if (steps > 1) issue_s(1, 1, d);
+        }
+        load_x(0); store_x(0);
+        if (steps > 1) { load_x(1); store_x(1); }
+        if (steps > 2) load_x(2);
+        wait_vm<0>();
+        lds_barrier();
+    } else {
+#pragma unroll
+        for (int b = 0; b + 1 < ST; ++b)
+            if (b < steps) issue_slots(b, b, IFirst{}, ISlots{}, Any{});
+        if (steps > ST - 1) {
+            wait_vm<(ST - 2) * D>();
+            issue_slots(ST - 1, ST - 1, IFirst{}, IEarly{}, Any{});
+        } else {
+            wait_vm<0>();
+        }
+        lds_barrier();
+    }
+    typedef std::integral_constant<int, FM> IFM;
+    read_x(I0{}, 0, I0{}, I0{}, IFM{});
+    read_w(0, 0, I0{}, Any{});
+#pragma unroll
+    for (int b = 0; b + 1 < FN; ++b) decode(b, cw[b][0], sc[b][0]);
+
+    // The barrier of step s: behind it all reads of stage s are done and step s + 1 is in LDS.
+    auto turn = [&](int s, auto mode) {
+        if constexpr (C::RAGGED) {
+            wait_vm<0>();
+            lds_barrier();
+            if constexpr (C::CODES) {
+                if (s + 3 < steps) issue_w(s + 3, 0, Any{});
+            } else if (s + 2 < steps) {
+                issue_w(s + 2, s & 1, Any{});
+#pragma unroll
+                for (int d = 0; d < C::SD; ++d) issue_s(s + 2, s & 1, d);
+            }
+            if (s + 2 < steps) store_x(s + 2);
+            if (s + 3 < steps) load_x(s + 3);
+        } else if constexpr (C::CODES) {
+            // X of step s + 2 may still be on its way, its bytes may not
+            if (decltype(mode)::value < 2 || s + 2 < steps) wait_vm<C::XD>(); else wait_vm<0>();
+            lds_barrier();
+        } else {
+            // steps s + 2 .. s + ST - 1 may still be on their way, as far as there are any
+            if constexpr (decltype(mode)::value < 2) {
+                wait_vm<(ST - 2) * D>();
+            } else {
+                const int r = steps - 2 - s;
+                if (ST > 2 && r >= ST - 2) wait_vm<(ST - 2) * D>();
+                else if (ST > 3 && r >= ST - 3) wait_vm<(ST > 3 ? ST - 3 : 0) * D>();
+                else if (r >= 1) wait_vm<D>();
+                else wait_vm<0>();
+            }
+            lds_barrier();
+        }
+    };
+
+    // One step.  A block walks its FN weight fragments; while fragment b is multiplied with the FM fragments of X,
+    // the fragment before it is replaced by the next block's (fragment FN - 1 by its own block's), the next block's X is
+    // requested, and the transfers' slots come by.
+    // mode 0: the step requested next exists and lies inside K (no condition in the loop); 1: it exists; 2: there may
+    // be none (the last step reads ahead into whatever the ring holds and drops it).
+    // st: s mod ST.  An odd number of blocks swaps the two sets of X fragments from step to step: PAR0 is the set of
+    // the step's first block; with SWAP = false they are copied, and every step starts from set 0.
+    int st = 0, st_before = ST - 1;
+    auto step = [&](int s, auto par0, auto swap, auto mode) {
+        constexpr int MODE = decltype(mode)::value;
+        typedef std::integral_constant<bool, MODE == 0> In;
+        const int st_next = st + 1 == ST ? 0 : st + 1;
+        auto block = [&](auto kst) {
+            constexpr int ks = decltype(kst)::value;
+            constexpr int PAR = (decltype(par0)::value + ks) & 1;
+            constexpr bool END = ks + 1 == NB;
+            typedef std::integral_constant<int, PAR ^ 1> NextPar;
+            typedef std::integral_constant<int, (END ? 0 : ks + 1)> Next;
+            constexpr int nx = Next::value;
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t own = cw[FN - 1][NCW == 1 ? 0 : ks], own_sc = sc[FN - 1][NS == 1 ? 0 : ks];
+            if constexpr (END) turn(s, mode);
+            if constexpr (END || NCW == 1) read_w(END ? s + 1 : s, END ? st_next : st, Next{}, In{});
+            auto half = [&](auto bt, auto ht) {           // half of fragment b's matrix instructions
+                constexpr int b = decltype(bt)::value, h = decltype(ht)::value;
+                constexpr int from = h * FM / 2, to = (h + 1) * FM / 2;
+                if constexpr (b < 2) {                    // a quarter of the next block's X
+                    constexpr int i = 2 * b + h;
+                    read_x(NextPar{}, END ? st_next : st, Next{}, std::integral_constant<int, i * FM / 4>{}, std::integral_constant<int, (i + 1) * FM / 4>{});
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int a = from; a < to; ++a)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wf[b]), xf[PAR][a], acc[a][b], 0, 0, 0);
+                if constexpr (h == 1) {
+                    if constexpr (b == 0) decode(FN - 1, own, own_sc);
+                    else decode(b - 1, cw[b - 1][NCW == 1 ? 0 : nx], sc[b - 1][NS == 1 ? 0 : nx]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (!C::RAGGED) {
+                    constexpr int slot = (END ? 0 : 2 * FN * (ks + 1)) + 2 * b + h;
+                    const int t = END ? s + ST : s + ST - 1;
+                    if constexpr (MODE < 2 || !END || C::CODES)
+                        if (MODE < 2 || t < steps) issue_slots(t, END ? st : st_before, std::integral_constant<int, slot>{}, std::integral_constant<int, slot + 1>{}, In{});
+                }
+            };
+            auto fragment = [&](auto bt) { half(bt, std::integral_constant<int, 0>{}); half(bt, std::integral_constant<int, 1>{}); };
+            fragment(std::integral_constant<int, 0>{});
+            fragment(std::integral_constant<int, 1>{});
+            if constexpr (FN > 2) {
+                fragment(std::integral_constant<int, (FN > 2 ? 2 : 0)>{});
+                fragment(std::integral_constant<int, (FN > 2 ? 3 : 0)>{});
+            }
+            if constexpr (END) {
+                if constexpr (C::CODES) { if (MODE == 0 || s + 2 < steps) transcode(s + 2, In{}); }
+                if constexpr (PAR == 0 && !decltype(swap)::value) {
+#pragma unroll
+                    for (int a = 0; a < FM; ++a) xf[0][a] = xf[1][a];
+                }
+            }
+        };
+        block(std::integral_constant<int, 0>{});
+        if constexpr (NB > 1) block(std::integral_constant<int, (NB > 1 ? 1 : 0)>{});
+        if constexpr (NB > 2) block(std::integral_constant<int, (NB > 2 ? 2 : 0)>{});
+        static_assert(NB <= 3, "blocks per set and step");
+        st_before = st;
+        st = st_next;
+    };
+    typedef std::integral_constant<int, 1> I1;
+    typedef std::integral_constant<int, 2> I2;
+    constexpr bool kSwap = (NB & 1) && !C::CODES;
+    int s = 0;
+    if constexpr (!C::RAGGED) {
+        constexpr int ahead = C::CODES ? 3 : ST;
+        const int inside_steps = K / KS;
+        if constexpr (kSwap) {
+            for (; s + 1 + ahead < inside_steps; s += 2) {
+                step(s, I0{}, std::true_type{}, I0{});
+                step(s + 1, I1{}, std::true_type{}, I0{});
+            }
+        } else {
+            for (; s + ahead < inside_steps; ++s) step(s, I0{}, std::false_type{}, I0{});
+        }
+        if constexpr (!C::CODES)
+            for (; s + ahead < steps; ++s) step(s, I0{}, std::false_type{}, I1{});
+    }
+    for (; s < steps; ++s) step(s, I0{}, std::false_type{}, I2{});
+    };
+    if constexpr (kFullSets < WK) {
+        if (short_set) run(std::integral_constant<int, NB - 1>{});
+        else run(std::integral_constant<int, NB>{});
+    } else {
+        run(std::integral_constant<int, NB>{});
+    }
+
+    // ---- sums of the sets, halving: set h adds set h + half (fixed order) ------------------------------------
+    if constexpr (WK > 1) {
+        const int wr = wave % (C::WM * C::WN);
+#pragma unroll
+        for (int half = WK / 2; half >= 1; half >>= 1) {
+            lds_barrier();
+            if (set >= half && set < 2 * half) {
+                f32x4* const red = reinterpret_cast<f32x4*>(lds) + ((set - half) * (C::WM * C::WN) + wr) * (FM * FN * 64) + lane;
+#pragma unroll
+                for (int a = 0; a < FM; ++a)
+#pragma unroll
+                    for (int b = 0; b < FN; ++b) red[(a * FN + b) * 64] = acc[a][b];
+            }
+            lds_barrier();
+            if (set < half) {
+                const f32x4* const red = reinterpret_cast<const f32x4*>(lds) + (set * (C::WM * C::WN) + wr) * (FM * FN * 64) + lane;
+#pragma unroll
+                for (int a = 0; a < FM; ++a)
+#pragma unroll
+                    for (int b = 0; b < FN; ++b) acc[a][b] += red[(a * FN + b) * 64];
+            }
+        }
+        lds_barrier();
+        if (set != 0) return;
+    } else {
+        lds_barrier();
+    }
+
+    // ---- output: y[m][n] = fp16(gamma acc).  A lane holds row m = lane % 16 of a fragment and the columns
+    // 4 (lane / 16) + r: each strip of 16 rows is turned through the wave's own piece of LDS.
+    constexpr int OROW = FN * 32 + 16;
+    unsigned char* const ob = lds + wave * (16 * OROW);
+    const int n0 = n_base + wn * 16 * FN;
+#pragma unroll
+    for (int a = 0; a < FM; ++a) {
+        const int m0 = m_base + wm * 16 * FM + 16 * a;
+#pragma unroll
+        for (int b = 0; b < FN; ++b) {
+            const f16x2 lo = {(_Float16)(p.gamma * acc[a][b][0]), (_Float16)(p.gamma * acc[a][b][1])};
+            const f16x2 hi = {(_Float16)(p.gamma * acc[a][b][2]), (_Float16)(p.gamma * acc[a][b][3])};
+            *reinterpret_cast<u32x2*>(ob + fi * OROW + b * 32 + fg * 8) =
+                u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+        }
+        // a wave reads what it wrote itself: LDS operations of one wave execute in order
+        asm volatile("" : : : "memory");
+        if ((p.N & 7) == 0) {
+#pragma unroll
+            for (int i = 0; i < FN / 2; ++i) {            // 16 rows x 2 FN pieces of 8 columns
+                const int q = i * 64 + lane;
+                const int row = q / (2 * FN), pc = q - row * (2 * FN);
+                const u32x4 v = *reinterpret_cast<const u32x4*>(ob + row * OROW + pc * 16);
+                const int m = m0 + row, n = n0 + pc * 8;
+                if (m < p.M && n < p.N) *reinterpret_cast<u32x4*>(p.y + size_t(m) * p.N + n) = v;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4 * FN; ++i) {
+                const int q = i * 64 + lane;
+                const int row = q / (16 * FN), c = q - row * (16 * FN);
+                const uint16_t v = *reinterpret_cast<const uint16_t*>(ob + row * OROW + c * 2);
+                const int m = m0 + row, n = n0 + c;
+                if (m < p.M && n < p.N) *reinterpret_cast<uint16_t*>(p.y + size_t(m) * p.N + n) = v;
+            }
+        }
+        asm volatile("" : : : "memory");
+    }
+}
+
+// ---- host side ----------------------------------------------------------------------------------------------
+
+// The dynamic-LDS limit of an instance on the current device, raised once per device.
+template <class C>
+hipError_t tile_prepare()
+{
+    static std::atomic<bool> raised[kMaxDevices];
+    const int dev = device_slot();
+    if (dev >= 0 && raised[dev].load(std::memory_order_relaxed)) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_kernel<C>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+    if (e == hipSuccess && dev >= 0) raised[dev].store(true, std::memory_order_relaxed);
+    return e;
+}
+
+template <class C>
+hipError_t tile_launch(TileParams p, hipStream_t s)
+{
+    const hipError_t e = tile_prepare<C>();
+    if (e != hipSuccess) return e;
+    p.tiles_m = (p.M + C::BM - 1) / C::BM;
+    p.tiles_n = (p.N + C::BN - 1) / C::BN;
+    hipLaunchKernelGGL((tile_kernel<C>), dim3(unsigned(p.tiles_m) * unsigned(p.tiles_n)), dim3(512), C::LDS, s, p);
+    return hipGetLastError();
+}
+
+// What a tile shape costs (us, measured with K = 1024 and 4096 and one or two full rounds of workgroups): a round of
+// `slots` workgroups takes start + per_step x steps (a round of at most 256 workgroups per_step_alone, where two
+// share a CU), every launch kTileLaunch more; a last round that is not full costs 0.6 to 1 of a full one (384 and
+// 448 tiles of 256 x 256 on 256 CUs: 0.90 and 0.94 of 512).
+struct TileCost {
+    int bm, bn, ks, slots;
+    double start, per_step, per_step_alone;
+};
+constexpr double kTileLaunch = 2.0;
+
+inline double tile_time(const TileCost& c, int64_t M, int64_t N, int64_t K)
+{
+    const double tiles = double((M + c.bm - 1) / c.bm) * double((N + c.bn - 1) / c.bn);
+    const double steps = double((K + c.ks - 1) / c.ks);
+    const double full = double(int64_t(tiles / c.slots));
+    const double rest = tiles - full * c.slots;
+    double rounds = full;
+    if (rest > 0.0) rounds += full == 0.0 ? 1.0 : 0.6 + 0.4 * rest / c.slots;
+    const double step = tiles <= 256.0 ? c.per_step_alone : c.per_step;
+    return kTileLaunch + rounds * (c.start + steps * step);
+}
+
+}  // namespace tl

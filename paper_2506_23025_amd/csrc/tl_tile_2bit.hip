@@ -1,0 +1,86 @@
+// 2-bit words, one gamma, K a multiple of 64: instances of the tiled matrix-core kernel and the choice among them.
+#include "tl_tile.hpp"
+
+namespace tl {
+
+namespace {
+
+// waves x fragments -> tile; the larger the tile, the fewer bytes cross LDS and L2 per matrix instruction.
+typedef TileCfg<kTile2Bit, false, 8, 4, 2, 4, 1, 2, 4> T256x256;    // steps of 64
+typedef TileCfg<kTile2Bit, false, 8, 4, 1, 4, 2, 4, 4> T128x256;    // steps of 128 from here on: sets of waves share K
+typedef TileCfg<kTile2Bit, false, 8, 2, 1, 4, 2, 4, 4> T128x128;
+typedef TileCfg<kTile2Bit, false, 8, 2, 1, 2, 4, 4, 4> T128x64;
+typedef TileCfg<kTile2Bit, false, 4, 2, 1, 2, 4, 4, 4> T64x64;      // two workgroups per CU
+typedef TileCfg<kTile2Bit, false, 2, 2, 1, 2, 4, 4, 4> T32x64;      // two workgroups per CU
+
+constexpr int kShapes = 6;
+constexpr TileCost kCost[kShapes] = {
+    {256, 256, 64, 256, 5.7, 1.36, 1.36},
+    {128, 256, 128, 256, 7.0, 1.36, 1.36},
+    {128, 128, 128, 256, 4.0, 0.77, 0.77},
+    {128, 64, 128, 256, 4.2, 0.41, 0.41},
+    {64, 64, 128, 512, 3.0, 0.50, 0.24},
+    {32, 64, 128, 512, 2.5, 0.31, 0.19},
+};
+
+// Row offsets within a tile are 32-bit: tiles of 256 rows up to K = 2^22, of 128 up to 2^23.
+inline bool fits(const TileCost& c, int64_t K) { return int64_t(c.bm) * K <= int64_t(1) << 30; }
+
+int pick(int64_t M, int64_t N, int64_t K, double* us)
+{
+    int best = kShapes - 2;
+    double t_best = 1e300;
+    for (int i = 0; i < kShapes; ++i) {
+        if (!fits(kCost[i], K)) continue;
+        const double t = tile_time(kCost[i], M, N, K);
+        if (t < t_best) { t_best = t; best = i; }
+    }
+    if (us) *us = t_best;
+    return best;
+}
+
+}  // namespace
+
+bool mfma_supports(int64_t M, int64_t N, int64_t K)
+{
+    return M >= 1 && N >= 1 && K >= 64 && (K % 64) == 0 && K <= (int64_t(1) << 24) &&
+           M <= (int64_t(1) << 24) && N <= (int64_t(1) << 24);
+}
+
+double mfma_time(int64_t M, int64_t N, int64_t K)
+{
+    double us;
+    pick(M, N, K, &us);
+    return us;
+}
+
+hipError_t mfma_init()
+{
+    hipError_t e = tile_prepare<T256x256>();
+    if (e == hipSuccess) e = tile_prepare<T128x256>();
+    if (e == hipSuccess) e = tile_prepare<T128x128>();
+    if (e == hipSuccess) e = tile_prepare<T128x64>();
+    if (e == hipSuccess) e = tile_prepare<T64x64>();
+    if (e == hipSuccess) e = tile_prepare<T32x64>();
+    return e;
+}
+
+hipError_t launch_mfma(const __half* x, const uint32_t* Wp, float gamma, __half* y,
+                       int64_t M, int64_t N, int64_t K, hipStream_t s)
+{
+    TileParams p{};
+    p.x = x; p.W = reinterpret_cast<const unsigned char*>(Wp); p.y = y; p.gamma = gamma;
+    p.M = int(M); p.N = int(N); p.K = int(K);
+    p.row_bytes = int(K / 4);
+    p.group16 = 1;
+    switch (pick(M, N, K, nullptr)) {
+        case 0: return tile_launch<T256x256>(p, s);
+        case 1: return tile_launch<T128x256>(p, s);
+        case 2: return tile_launch<T128x128>(p, s);
+        case 3: return tile_launch<T128x64>(p, s);
+        case 4: return tile_launch<T64x64>(p, s);
+        default: return tile_launch<T32x64>(p, s);
+    }
+}
+
+}  // namespace tl

@@ -1,0 +1,40 @@
+"""The tiled matrix-core kernel at the edges of its tiles, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2506_23025_amd as tl
+import synth_inputs as si
+from parity import assert_close, dev_u32, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _sampled(N, seed, most=300):
+    """Columns to compare: all of a small matrix, else a sample with both ends and a tile edge."""
+    if N <= 1100:
+        return np.arange(N)
+    cols = np.sort(np.random.default_rng(seed).choice(N, most, replace=False))
+    cols[:2], cols[-2:] = (0, 255), (N - 2, N - 1)
+    return np.unique(cols)
+
+
+# The shapes take, by the library's cost model, tiles of 256 x 256 (rows and columns past the edge; 2, 3 and 1 steps
+# of K, fewer than the ring is deep), 128 x 256, 128 x 128, 128 x 64, 64 x 64 and 32 x 64, with an N that is a multiple
+# of 8 or not (16-byte or single stores) and a K whose last step is half empty (K % 128 = 64) where steps are 128.
+TILE_SHAPES = [
+    (1030, 8200, 128), (1030, 8201, 192), (2500, 2700, 64), (2048, 3000, 192), (300, 9000, 704), (515, 4099, 256),
+    (117, 14340, 4096), (700, 1500, 320), (640, 2500, 1152), (129, 1030, 1088), (65, 1030, 192), (17, 70, 64),
+]
+
+
+@pytest.mark.parametrize("M,N,K", TILE_SHAPES)
+def test_tile_2bit(M, N, K):
+    x, W, g = si.layer(31000 + M + N + K, M, N, K)
+    xd, wd = to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W))
+    yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+    tl.tl_ternary_gemm_path(xd, wd, si.gamma_bits(g), yd, M, N, K, path=tl.TL_PATH_MFMA)
+    y = yd.cpu().numpy().view(np.float16)
+    cols = _sampled(N, M)
+    assert np.isfinite(y).all()
+    assert_close(y[:, cols], oracle.gemm(x, np.ascontiguousarray(W[cols]), g), x, g, f"tile {M}x{N}x{K}")
