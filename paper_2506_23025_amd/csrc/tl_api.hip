@@ -184,6 +184,9 @@ tl_status gemm_1p6(const void* x, const void* Wpacked, uint16_t gamma_fp16_bits,
     const float gamma = tl::half_bits_to_float(gamma_fp16_bits);
     const int64_t stride = static_cast<int64_t>(tl_row_stride_bytes(TL_FMT_1P6BIT, K));
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (tl::tile3_preferred(M, N, K))
+        return tl::from_hip(tl::launch_tile3(static_cast<const __half*>(x), static_cast<const uint8_t*>(Wpacked), stride,
+                                             gamma, static_cast<__half*>(y), M, N, K, fx, s));
     if (tl::gemv3_supports(M < tl::kGemvMaxM ? M : tl::kGemvMaxM, N, K)) {
         // more rows than one launch takes: one launch per kGemvMaxM rows
         const __half* xh = static_cast<const __half*>(x);
@@ -249,7 +252,8 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
     }
     const bool fx = format == TL_FMT_1P6BIT_FX;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Jobs whose K fits one pass of the stream form share launches; the others go one by one.
+    // Jobs whose K fits one pass of the stream form share launches; the others, and those with so many rows that the
+    // tiled kernel is faster, go one by one.
     tl::Gemm3Desc fused[64];
     int nf = 0;
     auto flush = [&]() -> tl_status {
@@ -260,7 +264,7 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
     };
     for (int64_t i = 0; i < count; ++i) {
         const tl_gemm_job& j = jobs[i];
-        if (tl::gemv3_groups(j.M, j.N, j.K)) {
+        if (tl::gemv3_groups(j.M, j.N, j.K) && !tl::tile3_preferred(j.M, j.N, j.K)) {
             fused[nf++] = tl::Gemm3Desc{static_cast<const __half*>(j.x), static_cast<const uint8_t*>(j.Wpacked),
                                         static_cast<__half*>(j.y), tl::half_bits_to_float(j.gamma_fp16_bits),
                                         j.M, j.N, j.K, static_cast<int64_t>(tl_row_stride_bytes(TL_FMT_1P6BIT, j.K))};
@@ -315,6 +319,7 @@ tl_status tl_init(void)
     hipError_t e = tl::gemv_init();
     if (e == hipSuccess) e = tl::gemv3_init();
     if (e == hipSuccess) e = tl::mfma_init();
+    if (e == hipSuccess) e = tl::tile3_init();
     return tl::from_hip(e);
 }
 

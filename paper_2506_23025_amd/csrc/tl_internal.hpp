@@ -102,6 +102,12 @@ struct Gemm3Desc {
 bool gemv3_groups(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStream_t s);
 
+// Tiled matrix-core kernel for the 1.6-bit formats, and whether it is the faster one for a shape (never for M <= 16,
+// and only where K % 8 == 0).
+bool tile3_preferred(int64_t M, int64_t N, int64_t K);
+hipError_t launch_tile3(const __half* x, const uint8_t* Wp, int64_t stride, float gamma, __half* y,
+                        int64_t M, int64_t N, int64_t K, bool fx, hipStream_t s);
+
 // Tiled matrix-core kernel for many activation rows (2-bit).  Needs K % 64 == 0.
 bool mfma_supports(int64_t M, int64_t N, int64_t K);
 // what it is expected to take (us), with the tile shape it would choose
@@ -123,6 +129,7 @@ inline int device_slot()
 hipError_t gemv_init();
 hipError_t gemv3_init();
 hipError_t mfma_init();
+hipError_t tile3_init();
 
 // fp16 bits -> float on the host (exact).
 float half_bits_to_float(uint16_t h);

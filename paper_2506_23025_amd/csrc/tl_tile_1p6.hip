@@ -1,0 +1,85 @@
+// Both 1.6-bit byte codes: instances of the tiled matrix-core kernel and the choice among them.
+#include "tl_tile.hpp"
+
+namespace tl {
+
+namespace {
+
+// Steps of 160 k (two sets of waves take 3 and 2 of its five 32-k blocks) or 320 k (four sets: 3, 3, 2, 2).
+typedef TileCfg<kTile1p6, false, 8, 4, 1, 4, 2, 5, 3> T128x256;
+typedef TileCfg<kTile1p6, false, 8, 2, 1, 4, 2, 5, 3> T128x128;
+typedef TileCfg<kTile1p6, false, 4, 2, 1, 4, 2, 5, 3> T64x128;
+typedef TileCfg<kTile1p6, false, 4, 2, 1, 2, 4, 10, 3> T64x64;
+typedef TileCfg<kTile1p6, false, 2, 2, 1, 2, 4, 10, 3> T32x64;
+
+constexpr int kShapes = 5;
+constexpr TileCost kCost[kShapes] = {
+    {128, 256, 160, 256, 7.0, 2.10, 2.10},
+    {128, 128, 160, 256, 5.0, 1.11, 1.11},
+    {64, 128, 160, 256, 2.8, 0.78, 0.78},
+    {64, 64, 320, 256, 3.1, 0.84, 0.84},
+    {32, 64, 320, 256, 2.1, 0.70, 0.70},
+};
+
+int pick(int64_t M, int64_t N, int64_t K, double* us)
+{
+    int best = kShapes - 1;
+    double t_best = 1e300;
+    for (int i = 0; i < kShapes; ++i) {
+        if (int64_t(kCost[i].bm) * K > int64_t(1) << 30) continue;        // row offsets within a tile are 32-bit
+        const double t = tile_time(kCost[i], M, N, K);
+        if (t < t_best) { t_best = t; best = i; }
+    }
+    if (us) *us = t_best;
+    return best;
+}
+
+}  // namespace
+
+// Tiled kernel or weight-streaming kernel (gemv3), where both can run the shape (K % 8 == 0).  The weight-streaming
+// kernel decodes W once per 16 rows; its time (us, W in MB of packed bytes, b blocks of 16 rows): 5 + b (0.12 + 0.28 W)
+// while K is one pass (4096 -> 14336: b = 4 19.0, b = 32 114.6; 4096 -> 4096: b = 32 38.2); beyond, rounds of 256
+// 16-row tiles of W that take 10.4 us at K = 11008 (11008 -> 4096: b = 1 11.4, b = 2 21.6, b = 32 334).  The tiled kernel on the same: 4096 -> 14336 b = 32 57,
+// 11008 -> 4096 b = 32 62, 4096 -> 4096 b = 32 26.
+bool tile3_preferred(int64_t M, int64_t N, int64_t K)
+{
+    if (M <= 16 || K < 8 || K % 8 != 0 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
+    const double w_mb = double(N) * double((K + 4) / 5) / 1.0e6;
+    const double blocks = double((M + 15) / 16);
+    const double rounds = double(((M + 15) / 16 * ((N + 15) / 16) + 255) / 256);
+    const double t_stream = gemv3_groups(M < 4096 ? M : 4096, N, K) ? 5.0 + blocks * (0.12 + 0.28 * w_mb)
+                                                                    : 1.0 + rounds * 10.4 * double(K) / 11008.0;
+    double us;
+    pick(M, N, K, &us);
+    return 1.08 * us < t_stream;                          // a band: near the crossover the models are within that of each other
+}
+
+hipError_t tile3_init()
+{
+    hipError_t e = tile_prepare<T128x256>();
+    if (e == hipSuccess) e = tile_prepare<T128x128>();
+    if (e == hipSuccess) e = tile_prepare<T64x128>();
+    if (e == hipSuccess) e = tile_prepare<T64x64>();
+    if (e == hipSuccess) e = tile_prepare<T32x64>();
+    return e;
+}
+
+hipError_t launch_tile3(const __half* x, const uint8_t* Wp, int64_t stride, float gamma, __half* y,
+                        int64_t M, int64_t N, int64_t K, bool fx, hipStream_t s)
+{
+    TileParams p{};
+    p.x = x; p.W = Wp; p.y = y; p.gamma = gamma;
+    p.M = int(M); p.N = int(N); p.K = int(K);
+    p.row_bytes = int(stride);
+    p.group16 = 1;
+    p.fx = fx;
+    switch (pick(M, N, K, nullptr)) {
+        case 0: return tile_launch<T128x256>(p, s);
+        case 1: return tile_launch<T128x128>(p, s);
+        case 2: return tile_launch<T64x128>(p, s);
+        case 3: return tile_launch<T64x64>(p, s);
+        default: return tile_launch<T32x64>(p, s);
+    }
+}
+
+}  // namespace tl

@@ -38,3 +38,24 @@ def test_tile_2bit(M, N, K):
     cols = _sampled(N, M)
     assert np.isfinite(y).all()
     assert_close(y[:, cols], oracle.gemm(x, np.ascontiguousarray(W[cols]), g), x, g, f"tile {M}x{N}x{K}")
+
+
+# 1.6-bit codes: 128 x 256, 128 x 128, 64 x 128, 64 x 64 and 32 x 64; K inside one step, one byte into the next, ending
+# in a byte with 3 weights, in the first half of a 32-k block, and long; N with and without 16-byte stores.
+TILE3_SHAPES = [
+    (512, 14340, 4096), (2050, 2056, 1288), (500, 4100, 1600), (1030, 2050, 168), (500, 1030, 648), (700, 1100, 952),
+    (60, 4096, 11008), (500, 600, 328),
+]
+
+
+@pytest.mark.parametrize("fx", [False, True])
+@pytest.mark.parametrize("M,N,K", TILE3_SHAPES)
+def test_tile_1p6(M, N, K, fx):
+    x, W, g = si.layer(32000 + M + N + K, M, N, K)
+    Wp = tl.tl_pack_1p6bit_fx(W) if fx else tl.tl_pack_1p6bit(W)
+    yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+    (tl.tl_ternary_gemm_1p6_fx if fx else tl.tl_ternary_gemm_1p6)(to_dev(x.view(np.int16)), to_dev(Wp), si.gamma_bits(g), yd, M, N, K)
+    y = yd.cpu().numpy().view(np.float16)
+    cols = _sampled(N, M)
+    assert np.isfinite(y).all()
+    assert_close(y[:, cols], oracle.gemm(x, np.ascontiguousarray(W[cols]), g), x, g, f"tile 1.6 {M}x{N}x{K}")
