@@ -230,6 +230,8 @@ tl_status tl_ternary_gemm_gs(const void* x, const void* Wpacked, const void* sca
     const uint32_t* wp = static_cast<const uint32_t*>(Wpacked);
     const __half* sh = static_cast<const __half*>(scales);
     __half* yh = static_cast<__half*>(y);
+    if (tl::tile_gs_preferred(M, N, K, group))
+        return tl::from_hip(tl::launch_tile_gs(xh, wp, sh, group, yh, M, N, K, s));
     if (tl::gemv_gs_supports(M, N, K, group)) {
         const hipError_t e = tl::launch_gemv_gs(xh, wp, sh, group, yh, M, N, K, s);
         if (e != hipErrorInvalidValue) return tl::from_hip(e);
@@ -290,7 +292,8 @@ tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, 
         if (!tl::aligned16(j.x) || !tl::aligned16(j.Wpacked) || !tl::aligned16(j.scales) || !tl::aligned16(j.y)) return TL_ERR_ALIGN;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Jobs the weight-streaming kernel takes share launches; the others go one by one.
+    // Jobs the weight-streaming kernel takes share launches; the others, and those with so many rows that the tiled
+    // kernel is faster, go one by one.
     tl::GemmGsDesc fused[64];
     int nf = 0;
     auto flush = [&]() -> tl_status {
@@ -301,7 +304,7 @@ tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, 
     };
     for (int64_t i = 0; i < count; ++i) {
         const tl_gemm_gs_job& j = jobs[i];
-        if (tl::gemv_gs_supports(j.M, j.N, j.K, j.group)) {
+        if (tl::gemv_gs_supports(j.M, j.N, j.K, j.group) && !tl::tile_gs_preferred(j.M, j.N, j.K, j.group)) {
             fused[nf++] = tl::GemmGsDesc{static_cast<const __half*>(j.x), static_cast<const uint32_t*>(j.Wpacked),
                                          static_cast<const __half*>(j.scales), static_cast<__half*>(j.y),
                                          j.M, j.N, j.K, j.group};
@@ -320,6 +323,7 @@ tl_status tl_init(void)
     if (e == hipSuccess) e = tl::gemv3_init();
     if (e == hipSuccess) e = tl::mfma_init();
     if (e == hipSuccess) e = tl::tile3_init();
+    if (e == hipSuccess) e = tl::tile_gs_init();
     return tl::from_hip(e);
 }
 

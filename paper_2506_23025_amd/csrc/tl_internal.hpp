@@ -102,6 +102,11 @@ struct Gemm3Desc {
 bool gemv3_groups(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStream_t s);
 
+// Tiled matrix-core kernel for group scales, and whether it is the faster one for a shape (only where K % 64 == 0).
+bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group);
+hipError_t launch_tile_gs(const __half* x, const uint32_t* Wp, const __half* scales, int64_t group, __half* y,
+                          int64_t M, int64_t N, int64_t K, hipStream_t s);
+
 // Tiled matrix-core kernel for the 1.6-bit formats, and whether it is the faster one for a shape (never for M <= 16,
 // and only where K % 8 == 0).
 bool tile3_preferred(int64_t M, int64_t N, int64_t K);
@@ -130,6 +135,7 @@ hipError_t gemv_init();
 hipError_t gemv3_init();
 hipError_t mfma_init();
 hipError_t tile3_init();
+hipError_t tile_gs_init();
 
 // fp16 bits -> float on the host (exact).
 float half_bits_to_float(uint16_t h);

@@ -1,0 +1,103 @@
+// 2-bit words with group scales, K a multiple of 64: instances of the tiled matrix-core kernel and the choice among
+// them.
+#include "tl_tile.hpp"
+
+namespace tl {
+
+namespace {
+
+// Last parameter: 16-k blocks per scale that is fetched.  The large tiles fetch one scale per 64 k (groups that are
+// multiples of 64; a scale per 16 k would cost four transfers a step instead of one: 128 x 128, K = 4096, 256 tiles
+// 39.7 against 36.0 us), the small ones one per 16 k (no difference: their one transfer has room for them).
+typedef TileCfg<kTileGs, false, 8, 4, 2, 4, 1, 2, 3, 4> T256x256;
+typedef TileCfg<kTileGs, false, 8, 4, 1, 4, 2, 4, 3, 4> T128x256;
+typedef TileCfg<kTileGs, false, 8, 2, 1, 4, 2, 4, 4, 4> T128x128;
+typedef TileCfg<kTileGs, false, 8, 2, 1, 4, 2, 4, 3, 1> T128x128any;
+typedef TileCfg<kTileGs, false, 8, 2, 1, 2, 4, 4, 3, 1> T128x64any;
+typedef TileCfg<kTileGs, false, 4, 2, 1, 2, 4, 4, 4, 1> T64x64any;
+typedef TileCfg<kTileGs, false, 2, 2, 1, 2, 4, 4, 4, 1> T32x64any;
+
+constexpr int kShapes = 7, kFirstAny = 3;     // from kFirstAny on any group that is a multiple of 16
+constexpr TileCost kCost[kShapes] = {
+    {256, 256, 64, 256, 6.1, 1.57, 1.57},
+    {128, 256, 128, 256, 7.0, 1.63, 1.63},
+    {128, 128, 128, 256, 4.7, 0.92, 0.92},
+    {128, 128, 128, 256, 4.4, 1.04, 1.04},
+    {128, 64, 128, 256, 4.2, 0.54, 0.54},
+    {64, 64, 128, 512, 3.6, 0.63, 0.34},
+    {32, 64, 128, 512, 3.0, 0.46, 0.28},
+};
+
+int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
+{
+    int best = kShapes - 1;
+    double t_best = 1e300;
+    for (int i = group % 64 == 0 ? 0 : kFirstAny; i < kShapes; ++i) {
+        if (int64_t(kCost[i].bm) * K > int64_t(1) << 30) continue;        // row offsets within a tile are 32-bit
+        const double t = tile_time(kCost[i], M, N, K);
+        if (t < t_best) { t_best = t; best = i; }
+    }
+    if (us) *us = t_best;
+    return best;
+}
+
+}  // namespace
+
+// Tiled kernel or what would take the call without it (us; W in MB of packed words, b blocks of 16 rows):
+//  * the weight-streaming kernel, which decodes W once per 16 rows: 4.6 + 6 per pass over K beyond the first + b (0.1 +
+//    0.18 W), with groups that are odd multiples of 128 b (0.1 + 0.31 W) (4096 -> 14336, b = 32: 90 and 153; 4096 ->
+//    4096: 32.7 and 48.4; 11008 -> 4096: 91 and 141)
+//  * the plain kernel on the vector ALUs (other groups): 3 + K / 4096 (6.5 + 1.25 per row, up to 16) for every 512
+//    workgroups of 16 x 16 outputs (4096 -> 4096: M = 1 11.3, M = 4 14.6, M = 16 29.8, M = 37 45.8)
+bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    if (K < 64 || K % 64 != 0 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
+    const double w_mb = double(N) * double(K) / 4.0e6;
+    const double blocks = double((M + 15) / 16);
+    double other;
+    if (gemv_gs_supports(M, N, K, group)) {
+        if (M <= 16) return false;
+        const double passes = double((K + 4095) / 4096);
+        other = 4.6 + 6.0 * (passes - 1.0) + blocks * (0.1 + (group % 256 == 0 ? 0.18 : 0.31) * w_mb);
+    } else {
+        const double groups = blocks * double((N + 15) / 16) / 512.0;
+        other = 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
+    }
+    double us;
+    pick(M, N, K, group, &us);
+    return 1.08 * us < other;                              // a band: near the crossover the models are within that of each other
+}
+
+hipError_t tile_gs_init()
+{
+    hipError_t e = tile_prepare<T256x256>();
+    if (e == hipSuccess) e = tile_prepare<T128x256>();
+    if (e == hipSuccess) e = tile_prepare<T128x128>();
+    if (e == hipSuccess) e = tile_prepare<T128x128any>();
+    if (e == hipSuccess) e = tile_prepare<T128x64any>();
+    if (e == hipSuccess) e = tile_prepare<T64x64any>();
+    if (e == hipSuccess) e = tile_prepare<T32x64any>();
+    return e;
+}
+
+hipError_t launch_tile_gs(const __half* x, const uint32_t* Wp, const __half* scales, int64_t group, __half* y,
+                          int64_t M, int64_t N, int64_t K, hipStream_t s)
+{
+    TileParams p{};
+    p.x = x; p.W = reinterpret_cast<const unsigned char*>(Wp); p.scales = scales; p.y = y; p.gamma = 1.f;
+    p.M = int(M); p.N = int(N); p.K = int(K);
+    p.row_bytes = int(K / 4);
+    // a group longer than K is the one group there is
+    p.group16 = int((group < K ? group : K) / 16);
+    switch (pick(M, N, K, group, nullptr)) {
+        case 0: return tile_launch<T256x256>(p, s);
+        case 1: return tile_launch<T128x256>(p, s);
+        case 2: return tile_launch<T128x128>(p, s);
+        case 3: return tile_launch<T128x128any>(p, s);
+        case 4: return tile_launch<T128x64any>(p, s);
+        case 5: return tile_launch<T64x64any>(p, s);
+        default: return tile_launch<T32x64any>(p, s);
+    }
+}
+
+}  // namespace tl

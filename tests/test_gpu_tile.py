@@ -59,3 +59,25 @@ def test_tile_1p6(M, N, K, fx):
     cols = _sampled(N, M)
     assert np.isfinite(y).all()
     assert_close(y[:, cols], oracle.gemm(x, np.ascontiguousarray(W[cols]), g), x, g, f"tile 1.6 {M}x{N}x{K}")
+
+
+# Group scales: every tile shape; groups of 64 and more (one scale per 64 k), of 32, 48, 16 (one per 16 k), longer than K,
+# ending inside a step and inside a group; N with and without 16-byte stores.
+TILE_GS_SHAPES = [
+    (1030, 8200, 192, 64), (2048, 3000, 192, 128), (300, 9000, 704, 256), (300, 9001, 704, 48), (117, 14340, 4096, 32),
+    (640, 2500, 1152, 96), (129, 1030, 1088, 16), (40, 300, 1024, 128), (17, 70, 64, 4096), (16, 333, 4096, 64), (5, 40, 320, 64),
+]
+
+
+@pytest.mark.parametrize("M,N,K,group", TILE_GS_SHAPES)
+def test_tile_group_scales(M, N, K, group):
+    rng = np.random.default_rng(33000 + M + N + K)
+    x, W, _ = si.layer(33000 + M + N + K, M, N, K)
+    s = si.group_scales(rng, -(-K // group), N)
+    yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+    tl.tl_ternary_gemm_gs(to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), to_dev(s.view(np.int16)), group, yd, M, N, K)
+    y = yd.cpu().numpy().view(np.float16)
+    cols = _sampled(N, M)
+    assert np.isfinite(y).all()
+    ref = oracle.gemm_group_scales(x, np.ascontiguousarray(W[cols]), np.ascontiguousarray(s[:, cols]), group)
+    assert_close(y[:, cols], ref, x, 0.05, f"tile scales {M}x{N}x{K} group {group}")   # no scale is above 0.05
