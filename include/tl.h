@@ -151,8 +151,8 @@ tl_status tl_unpack_dev(tl_format fmt, const void* packed, int64_t N, int64_t K,
  * row); an infinity in row m makes that row NaN where the exact result would be +-infinity,
  * because the fast kernels compute sum (w + 1) x - sum x (Sec. 3.1 stores w + 1).
  * Any M, N, K >= 1 is accepted; the library picks the kernel from the shape
- * (small M: weight-streaming kernel; large M: LDS-tiled MFMA kernel; shapes the
- * fast kernels cannot take: the generic kernel).  Results are deterministic:
+ * (small M: weight-streaming kernel; large M: tiled matrix-core kernel; K that is no
+ * multiple of 64: the tiled kernel's form for such rows, or the generic kernel where that is faster).  Results are deterministic:
  * no atomics, fixed reduction order.  Behaviour on a 2-bit code 3 is memory-safe
  * but otherwise unspecified.
  */
@@ -170,7 +170,8 @@ tl_status tl_init(void);
 
 /*
  * The kernel tl_ternary_gemm (TL_PATH_AUTO) runs for a shape: TL_PATH_GEMV, TL_PATH_MFMA or
- * TL_PATH_GENERIC; TL_PATH_AUTO (0) if M, N or K is not a valid size.  A pure function of the
+ * TL_PATH_GENERIC (K no multiple of 64: the any-shape kernels, i.e. the generic kernel or the tiled
+ * kernel's form for odd K); TL_PATH_AUTO (0) if M, N or K is not a valid size.  A pure function of the
  * three numbers (host side, touches no GPU): the library's cost models of its two fast
  * kernels decide between them where both can run the shape.
  */
@@ -222,10 +223,11 @@ tl_status tl_ternary_gemm_1p6_fx(const void* x, const void* Wpacked, uint16_t ga
  * scales held in a separate buffer).  `scales` is a device pointer to fp16
  * [ceil(K / group)][N], 16-byte aligned; the last group may be short.  x, Wpacked (2-bit
  * format), y, stream, accumulation and rounding as for tl_ternary_gemm.  `group` must be a
- * multiple of 16 (TL_ERR_SHAPE otherwise).  K % 64 == 0 runs on the matrix cores: few activation
+ * multiple of 16 (TL_ERR_SHAPE otherwise).  K % 64 == 0: few activation
  * rows, group % 128 == 0 and N % 4 == 0 in the weight-streaming small-M kernel (M in blocks of 16
- * rows; multiples of 256 a little faster than odd multiples of 128), the rest in the tiled kernel;
- * other K, and one or two rows with other groups, in the generic kernel.
+ * rows; multiples of 256 a little faster than odd multiples of 128), the rest in the tiled kernel,
+ * except where so few rows make the generic kernel the faster one; other K likewise in the tiled or
+ * the generic kernel.
  * Nothing is allocated; the call is asynchronous on `stream`.
  */
 tl_status tl_ternary_gemm_gs(const void* x, const void* Wpacked, const void* scales, int64_t group,

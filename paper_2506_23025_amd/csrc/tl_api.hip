@@ -114,7 +114,12 @@ tl_status tl_ternary_gemm_path(const void* x, const void* Wpacked, uint16_t gamm
     const uint32_t* wp = static_cast<const uint32_t*>(Wpacked);
     __half* yh = static_cast<__half*>(y);
 
-    if (path == TL_PATH_AUTO) path = tl_ternary_gemm_which(M, N, K);
+    if (path == TL_PATH_AUTO) {
+        path = tl_ternary_gemm_which(M, N, K);
+        // shapes of the any-shape path: the tiled kernel's form for odd K where it is the faster one
+        if (path == TL_PATH_GENERIC && K % 64 != 0 && tl::tile_ragged_preferred(M, N, K))
+            return tl::from_hip(tl::launch_tile_ragged(xh, wp, gamma, yh, M, N, K, s));
+    }
     switch (path) {
         case TL_PATH_GENERIC:
             return tl::from_hip(tl::launch_gemm_generic(xh, wp, gamma, yh, M, N, K, s));

@@ -102,16 +102,20 @@ struct Gemm3Desc {
 bool gemv3_groups(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStream_t s);
 
-// Tiled matrix-core kernel for group scales, and whether it is the faster one for a shape (only where K % 64 == 0).
+// Tiled matrix-core kernel for group scales, and whether it is the faster one for a shape.
 bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group);
 hipError_t launch_tile_gs(const __half* x, const uint32_t* Wp, const __half* scales, int64_t group, __half* y,
                           int64_t M, int64_t N, int64_t K, hipStream_t s);
 
-// Tiled matrix-core kernel for the 1.6-bit formats, and whether it is the faster one for a shape (never for M <= 16,
-// and only where K % 8 == 0).
+// Tiled matrix-core kernel for the 1.6-bit formats, and whether it is the faster one for a shape.
 bool tile3_preferred(int64_t M, int64_t N, int64_t K);
 hipError_t launch_tile3(const __half* x, const uint8_t* Wp, int64_t stride, float gamma, __half* y,
                         int64_t M, int64_t N, int64_t K, bool fx, hipStream_t s);
+
+// Tiled matrix-core kernel for 2-bit words and a K that is no multiple of 64, and whether it beats the plain kernel.
+bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K);
+hipError_t launch_tile_ragged(const __half* x, const uint32_t* Wp, float gamma, __half* y,
+                              int64_t M, int64_t N, int64_t K, hipStream_t s);
 
 // Tiled matrix-core kernel for many activation rows (2-bit).  Needs K % 64 == 0.
 bool mfma_supports(int64_t M, int64_t N, int64_t K);

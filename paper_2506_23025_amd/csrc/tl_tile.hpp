@@ -57,7 +57,7 @@ struct TileParams {
     int tiles_m, tiles_n;
 };
 
-// RAGGED: K is not a multiple of 64 (2-bit) or 8 (1.6-bit): rows of X and W start anywhere, X goes
+// RAGGED: K (at least 8) is not a multiple of 64 (2-bit) or 8 (1.6-bit): rows of X and W start anywhere, X goes
 // through registers (masked past K) and 2-bit words are fetched one by one.
 // UNIT: blocks per scale unit (kTileGs): NB, or 1 when groups are shorter than a set's part of a step.
 template <int FMT_, bool RAGGED_, int FM_, int FN_, int WM_, int WN_, int WK_, int NP_, int ST_, int UNIT_ = 1>
@@ -76,9 +76,10 @@ struct TileCfg {
     static constexpr int WST = CODES ? BN * CH * 16 : BN * KS / 4;   // bytes of a W stage (raw bytes or words)
     static constexpr int WSLOTS = CODES ? 2 : ST;
     static constexpr int WL = WST / 16 / 8;                       // lanes per wave in the W transfer (16 bytes each)
-    static constexpr int WD = (RAGGED && !CODES) ? WST / 4 / 512 : 1;   // W transfers per wave and step
+    static constexpr int WD = RAGGED ? (CODES ? BN * CH * 2 / 512 : WST / 4 / 512) : 1;   // fetches per thread and step (RAGGED)
+    static constexpr int DEP = 4;                                 // RAGGED: steps of X and W on their way in registers
     static constexpr int CST = CODES ? BN * KS / 4 : 0;           // a slot of transcoded words, [word][column]
-    static constexpr bool PARTIAL = RAGGED || CODES || KS > 64;   // the last step may reach past K
+    static constexpr bool PARTIAL = CODES || KS > 64;   // the last step may reach past K
     static constexpr int UNIT = UNIT_;
     static constexpr int NU = FMT == kTileGs ? 2 * NP / UNIT : 0; // scale rows per step
     static constexpr int SD = (NU * BN + 511) / 512;              // scale transfers per wave and step
@@ -91,10 +92,12 @@ struct TileCfg {
     static constexpr int RED = WK > 1 ? 4 * FM * FN * 1024 : 0;   // half of the waves hand over their sums
     static constexpr int OUT = 8 * 16 * (FN * 32 + 16);           // 16 rows of every wave's tile as fp16
     static constexpr int LDS = RING > RED ? (RING > OUT ? RING : OUT) : (RED > OUT ? RED : OUT);
-    static constexpr int OCC = LDS <= 80 * 1024 ? 4 : 2;          // waves per SIMD: two workgroups per CU where LDS holds them
+    // waves per SIMD: two workgroups per CU where LDS and registers hold them
+    static constexpr int OCC = LDS <= 80 * 1024 && FM * FN <= (RAGGED ? (CODES ? 0 : 4) : 8) ? 4 : 2;
     static_assert(WM * WN * WK == 8, "8 waves");
     static_assert(LDS <= 160 * 1024, "tile does not fit");
     static_assert(FN == 2 || FN == 4, "rolling decode: a fragment is decoded while the others are multiplied");
+    static_assert(BN % 64 == 0 || FMT == kTile2Bit, "a wave fetches scales and bytes of one row of units or chunks");
     static_assert((CODES ? KS % 80 == 0 : KS % 64 == 0) && WL <= 64 && WD >= 1, "step");
     static_assert(UNIT == 1 || (UNIT == 2 * NB && NP % WK == 0), "scale unit: 16 k, or a set's part of a step");
 };
@@ -225,16 +228,14 @@ tile_kernel(TileParams p)
         xoff[d] = uint32_t(row < mlast ? row : mlast) * uint32_t(K) * 2u;   // rows past M repeat the last one, never stored
         if constexpr (!C::RAGGED) xoff[d] += uint32_t(piece_of<P>(row, lin - row * P)) * 16u;
     }
-    // the piece of transfer d, worked out again where it is needed (not kept in a register)
+    // the piece of transfer d (LDS-DMA form: worked out again where it is needed, not kept in a register)
     auto piece = [&](int d) {
         int l = lane;
-        asm volatile("" : "+v"(l));
+        if constexpr (!C::RAGGED) asm volatile("" : "+v"(l));
         const int lin = (d * 8 + wave) * 64 + l;
         const int row = lin / P;
         return uint32_t(piece_of<P>(row, lin - row * P));
     };
-    typedef u32x4 __attribute__((aligned(2))) u32x4_any;
-    u32x4 xreg[C::RAGGED ? C::XD : 1];
     // DMA form, step s into stage st = s mod ST.  Pieces past K read the row's first piece: their weights are zero, and
     // a NaN there stays within its own row.
     auto issue_x = [&](int s, int st, int d, auto inside) {
@@ -246,81 +247,60 @@ tile_kernel(TileParams p)
             dma16(k < uint32_t(K) ? xoff[d] + uint32_t(s) * (KS * 2) : xoff[d] - q * 16u, xtile, dst);
         }
     };
-    // register form (rows start at any even byte)
-    auto load_x = [&](int s) {
-#pragma unroll
-        for (int d = 0; d < (C::RAGGED ? C::XD : 0); ++d) {
-            const uint32_t k = uint32_t(s) * KS + piece(d) * 8u;
-            typedef const __attribute__((address_space(1))) unsigned char* gb;
-            gb src = (gb)(xtile + size_t(xoff[d]) + size_t(k) * 2);
-            u32x4 v = u32x4{0u, 0u, 0u, 0u};
-            if (k + 8 <= uint32_t(K)) {
-                v = *(const __attribute__((address_space(1))) u32x4_any*)src;
-            } else if (k < uint32_t(K)) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (k + e < uint32_t(K))
-                        v[e >> 1] |= uint32_t(*(const __attribute__((address_space(1))) uint16_t*)(src + 2 * e)) << (16 * (e & 1));
-            }
-            xreg[d] = v;
-        }
-    };
-    auto store_x = [&](int s) {
-#pragma unroll
-        for (int d = 0; d < (C::RAGGED ? C::XD : 0); ++d)
-            *reinterpret_cast<u32x4*>(lds + (s % ST) * C::XST + (d * 8 + wave) * 1024 + lane * 16) = xreg[d];
-    };
-
     // ---- W transfers --------------------------------------------------------------------------------
     const unsigned char* const wtile = p.W + size_t(n_base) * size_t(p.row_bytes);
     const int nlast = p.N - 1 - n_base;
     constexpr int PW = C::CODES ? C::CH : KS / 64;           // 16-byte pieces per column and step
-    uint32_t woff[C::WD], wpc = 0;
-    if constexpr (C::RAGGED && !C::CODES) {
-#pragma unroll
-        for (int d = 0; d < C::WD; ++d) {
-            const int lin = (d * 8 + wave) * 64 + lane;   // word: column lin / (KS / 16)
-            const int col = lin / (KS / 16);
-            wpc = uint32_t(lin - col * (KS / 16));        // the same for every d: 512 is a multiple of KS / 16
-            woff[d] = uint32_t(col < nlast ? col : nlast) * uint32_t(p.row_bytes);
-        }
-    } else {
+    uint32_t woff, wpc;
+    {
         const int lin = wave * C::WL + lane;
         const int col = lin / PW;
         wpc = uint32_t(lin - col * PW);
-        woff[0] = uint32_t(col < nlast ? col : nlast) * uint32_t(p.row_bytes);
+        woff = uint32_t(col < nlast ? col : nlast) * uint32_t(p.row_bytes);
     }
     auto issue_w = [&](int s, int st, auto inside) {
         const uint32_t base = lds0 + C::OFF_W + uint32_t(C::CODES ? s & 1 : st) * C::WST;
-        if constexpr (C::RAGGED && !C::CODES) {
-            uint32_t o = (uint32_t(s) * (KS / 16) + wpc) * 4u;
-            if (o >= uint32_t(p.row_bytes)) o = 0;        // past the row: fetched, never used
-#pragma unroll
-            for (int d = 0; d < C::WD; ++d) dma4(woff[d] + o, wtile, base + uint32_t(d * 8 + wave) * 256u);
-        } else {
-            const uint32_t dst = base + uint32_t(wave) * (C::WL * 16);
-            constexpr unsigned long long lanes = C::WL == 64 ? ~0ull : (1ull << (C::WL & 63)) - 1;
-            const unsigned char* src = wtile + size_t(s) * (PW * 16);
-            uint32_t o = woff[0] + wpc * 16u;
-            if constexpr (C::PARTIAL && !decltype(inside)::value) {
-                if ((uint32_t(s) * PW + wpc) * 16u >= uint32_t(p.row_bytes)) o = woff[0];   // past the row: fetched, never used
-            }
-            if constexpr (C::WL == 64) dma16(o, src, dst);
-            else dma16_lanes(o, src, dst, lanes);
+        const uint32_t dst = base + uint32_t(wave) * (C::WL * 16);
+        constexpr unsigned long long lanes = C::WL == 64 ? ~0ull : (1ull << (C::WL & 63)) - 1;
+        const unsigned char* src = wtile + size_t(s) * (PW * 16);
+        uint32_t o = woff + wpc * 16u;
+        if constexpr (C::PARTIAL && !decltype(inside)::value) {
+            if ((uint32_t(s) * PW + wpc) * 16u >= uint32_t(p.row_bytes)) o = woff;   // past the row: fetched, never used
         }
+        if constexpr (C::WL == 64) dma16(o, src, dst);
+        else dma16_lanes(o, src, dst, lanes);
     };
 
-    // ---- scale transfers ------------------------------------------------------------------------------
-    auto issue_s = [&](int s, int st, int d) {
-        const int first = (d * 8 + wave) * 64;            // BN is a multiple of 64: one scale row per transfer
-        int unit = first / BN;
-        const int col = first - unit * BN + lane;
-        if (unit >= C::NU) unit = C::NU - 1;              // surplus waves write padding
-        int blk = s * (KS / 16) + unit * C::UNIT;
-        if (blk * 16 >= K) blk = (K - 1) >> 4;
-        const size_t g = size_t(blk / p.group16);
-        dma2(uint32_t(col < nlast ? col : nlast) * 2u, p.scales + g * size_t(p.N) + n_base,
-             lds0 + C::OFF_S + uint32_t(st) * C::SST + uint32_t(first) * 4u);
+    // ---- scale transfers: transfer d of a wave fetches 64 columns of one scale row of the step.  The steps are asked for
+    // in order, so the row's group is carried along instead of divided out.
+    constexpr int SD1 = C::SD > 0 ? C::SD : 1;
+    int sgroup[SD1], sleft[SD1], sblk[SD1];               // group, 16-k blocks into it, 16-k block
+    const int group16 = C::FMT == kTileGs ? p.group16 : 1;
+    const int sgroups = (KS / 16) / group16, sblocks = (KS / 16) - sgroups * group16;
+    const int slast = ((K - 1) >> 4) / group16;
+#pragma unroll
+    for (int d = 0; d < C::SD; ++d) {
+        int unit = (d * 8 + wave) * 64 / BN;              // BN is a multiple of 64: one scale row per transfer
+        if (unit >= C::NU) unit = C::NU - 1;              // surplus waves fetch into padding
+        sblk[d] = unit * C::UNIT;
+        sgroup[d] = sblk[d] / group16;
+        sleft[d] = sblk[d] - sgroup[d] * group16;
+    }
+    // the row of transfer d for the next step that has not been asked for
+    auto scale_row = [&](int d) {
+        const __half* const r = p.scales + size_t(sblk[d] * 16 < K ? sgroup[d] : slast) * size_t(p.N) + n_base;
+        sblk[d] += KS / 16;
+        sgroup[d] += sgroups;
+        sleft[d] += sblocks;
+        if (sleft[d] >= group16) { sleft[d] -= group16; ++sgroup[d]; }
+        return r;
+    };
+    auto scale_col = [&](int d) {
+        const int col = (d * 8 + wave) * 64 % BN + lane;
+        return uint32_t(col < nlast ? col : nlast);
+    };
+    auto issue_s = [&](int st, int d) {
+        dma2(scale_col(d) * 2u, scale_row(d), lds0 + C::OFF_S + uint32_t(st) * C::SST + uint32_t(d * 8 + wave) * 256u);
     };
     // Transfer d of a step's D: the weights, the scales, then X (the order matters for the 1.6-bit forms: their
     // bytes are waited for one step before X).
@@ -328,48 +308,125 @@ tile_kernel(TileParams p)
     auto issue = [&](int s, int st, auto dt, auto inside) {
         constexpr int d = decltype(dt)::value;
         if constexpr (d == 0) issue_w(s, st, inside);
-        else if constexpr (d <= C::SD) issue_s(s, st, d - 1);
+        else if constexpr (d <= C::SD) issue_s(st, d - 1);
         else issue_x(s, st, d - 1 - C::SD, inside);
     };
 
     // ---- 1.6-bit bytes -> 2-bit words: 8 bytes (40 weights) per thread -----------------------------------
     const int nbytes = (K + 4) / 5;
     uint32_t* const table = reinterpret_cast<uint32_t*>(lds + C::OFF_T);
+    // round r of a step's: threads take a column's 8 bytes each (BN is a multiple of 64: chunk and half are a wave's)
+    constexpr int ROUNDS = C::CODES ? (BN * C::CH * 2 + 511) / 512 : 0;
+    auto transcode_one = [&](int s, int r, u32x2 raw, auto inside) {
+        const int w0 = r * 512 + wave * 64;
+        const int part = w0 / BN, col = w0 - part * BN + lane;
+        const int ch = part >> 1, half = part & 1;
+        uint32_t e[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) e[b] = table[(raw[b >> 2] >> (8 * (b & 3))) & 255u];
+        if (!decltype(inside)::value && (s + 1) * (C::CH * 16) > nbytes) {   // bytes past the row count as weight 0
+            const int b0 = (s * C::CH + ch) * 16 + half * 8;
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+                if (b0 + b >= nbytes) e[b] = 0x155u;
+        }
+        const uint32_t d0 = e[0] | (e[1] << 10) | (e[2] << 20) | (e[3] << 30);
+        const uint32_t d1 = (e[3] >> 2) | (e[4] << 8) | (e[5] << 18) | (e[6] << 28);
+        const uint32_t d2 = (e[6] >> 4) | (e[7] << 6);       // 16 bits
+        uint32_t* const c = reinterpret_cast<uint32_t*>(lds + C::OFF_C + (s & 1) * C::CST) + (ch * 5) * BN + col;
+        uint16_t* const mid = reinterpret_cast<uint16_t*>(c + 2 * BN);
+        if (half == 0) {
+            c[0] = d0;
+            c[BN] = d1;
+            mid[0] = uint16_t(d2);
+        } else {                              // 80 bits from bit 80 on
+            mid[1] = uint16_t(d0);
+            c[3 * BN] = (d0 >> 16) | (d1 << 16);
+            c[4 * BN] = (d1 >> 16) | (d2 << 16);
+        }
+    };
     auto transcode = [&](int s, auto inside) {
-        if constexpr (C::CODES) {
 #pragma unroll
-            for (int i0 = 0; i0 < BN * C::CH * 2; i0 += 512) {
-                __builtin_amdgcn_sched_barrier(0);        // one round's look-ups in registers at a time
-                const int w0 = i0 + wave * 64;            // column, then chunk and half (BN is a multiple of 64)
-                if (BN * C::CH * 2 - i0 >= 512 || w0 < BN * C::CH * 2) {
+        for (int r = 0; r < ROUNDS; ++r) {
+            __builtin_amdgcn_sched_barrier(0);            // one round's look-ups in registers at a time
+            const int w0 = r * 512 + wave * 64;
+            if (BN * C::CH * 2 - r * 512 >= 512 || w0 < BN * C::CH * 2) {
+                const int part = w0 / BN, col = w0 - part * BN + lane;
+                transcode_one(s, r, *reinterpret_cast<const u32x2*>(lds + C::OFF_W + (s & 1) * C::WST + (col * C::CH + (part >> 1)) * 16 + (part & 1) * 8), inside);
+            }
+        }
+    };
+
+    // ---- RAGGED: X, W and the scales of a step through registers, DEP steps ahead.  Rows start anywhere, so a thread fetches
+    // its 16 bytes of X from wherever they lie; a piece that reaches past K is fetched from the row's last 16
+    // bytes and shifted down, which leaves zeros past K (so whatever W holds there does not matter), and one that lies
+    // past K altogether is zero.  All fetches are unconditional: their steps and offsets are held inside the rows.
+    typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+    typedef const __attribute__((address_space(1))) unsigned char* gbytes;
+    constexpr int DEP = C::DEP;
+    u32x4 rx[C::RAGGED ? DEP : 1][C::XD];
+    uint32_t rw[C::RAGGED ? DEP : 1][C::WD * (C::CODES ? 2 : 1)];
+    uint16_t rs[C::RAGGED ? DEP : 1][SD1];
+    auto fetch = [&](int t, auto slot) {
+        if constexpr (C::RAGGED) {
+            constexpr int j = decltype(slot)::value;
+#pragma unroll
+            for (int d = 0; d < C::XD; ++d) {
+                uint32_t k = uint32_t(t) * KS + piece(d) * 8u;
+                k = k < uint32_t(K) - 8u ? k : uint32_t(K) - 8u;
+                rx[j][d] = *(const __attribute__((address_space(1))) u32x4_any*)((gbytes)xtile + xoff[d] + k * 2u);
+            }
+#pragma unroll
+            for (int d = 0; d < C::WD; ++d) {
+                if constexpr (C::CODES) {
+                    const int w0 = d * 512 + wave * 64;
                     const int part = w0 / BN, col = w0 - part * BN + lane;
-                    const int ch = part >> 1, half = part & 1;
-                    const u32x2 raw = *reinterpret_cast<const u32x2*>(lds + C::OFF_W + (s & 1) * C::WST + (col * C::CH + ch) * 16 + half * 8);
-                    uint32_t e[8];
-#pragma unroll
-                    for (int b = 0; b < 8; ++b) e[b] = table[(raw[b >> 2] >> (8 * (b & 3))) & 255u];
-                    if (!decltype(inside)::value && (s + 1) * (C::CH * 16) > nbytes) {   // bytes past the row count as weight 0
-                        const int b0 = (s * C::CH + ch) * 16 + half * 8;
-#pragma unroll
-                        for (int b = 0; b < 8; ++b)
-                            if (b0 + b >= nbytes) e[b] = 0x155u;
-                    }
-                    const uint32_t d0 = e[0] | (e[1] << 10) | (e[2] << 20) | (e[3] << 30);
-                    const uint32_t d1 = (e[3] >> 2) | (e[4] << 8) | (e[5] << 18) | (e[6] << 28);
-                    const uint32_t d2 = (e[6] >> 4) | (e[7] << 6);       // 16 bits
-                    uint32_t* const c = reinterpret_cast<uint32_t*>(lds + C::OFF_C + (s & 1) * C::CST) + (ch * 5) * BN + col;
-                    uint16_t* const mid = reinterpret_cast<uint16_t*>(c + 2 * BN);
-                    if (half == 0) {
-                        c[0] = d0;
-                        c[BN] = d1;
-                        mid[0] = uint16_t(d2);
-                    } else {                              // 80 bits from bit 80 on
-                        mid[1] = uint16_t(d0);
-                        c[3 * BN] = (d0 >> 16) | (d1 << 16);
-                        c[4 * BN] = (d1 >> 16) | (d2 << 16);
-                    }
+                    uint32_t o = (uint32_t(t) * C::CH + uint32_t(part >> 1)) * 16u + uint32_t(part & 1) * 8u;
+                    o = o < uint32_t(p.row_bytes) - 8u ? o : uint32_t(p.row_bytes) - 8u;
+                    const u32x2 v = *(const __attribute__((address_space(1))) u32x2*)((gbytes)wtile + uint32_t(col < nlast ? col : nlast) * uint32_t(p.row_bytes) + o);
+                    rw[j][2 * d] = v[0];
+                    rw[j][2 * d + 1] = v[1];
+                } else {
+                    const int lin = d * 512 + tid;        // word: column lin / (KS / 16)
+                    const int col = lin / (KS / 16);
+                    uint32_t o = (uint32_t(t) * (KS / 16) + uint32_t(lin - col * (KS / 16))) * 4u;
+                    o = o < uint32_t(p.row_bytes) - 4u ? o : uint32_t(p.row_bytes) - 4u;
+                    rw[j][d] = *(const __attribute__((address_space(1))) uint32_t*)((gbytes)wtile + uint32_t(col < nlast ? col : nlast) * uint32_t(p.row_bytes) + o);
                 }
             }
+#pragma unroll
+            for (int d = 0; d < C::SD; ++d)
+                rs[j][d] = *((const __attribute__((address_space(1))) uint16_t*)scale_row(d) + scale_col(d));
+        }
+    };
+    // step t from its registers into stage t & 1
+    auto put = [&](int t, auto slot) {
+        if constexpr (C::RAGGED) {
+            constexpr int j = decltype(slot)::value;
+            const bool tail = (t + 1) * KS > K;
+#pragma unroll
+            for (int d = 0; d < C::XD; ++d) {
+                u32x4 v = rx[j][d];
+                if (tail) {
+                    const int past = t * KS + int(piece(d)) * 8 + 8 - K;      // elements past K, 16 bits each
+                    const uint64_t lo = uint64_t(v[0]) | (uint64_t(v[1]) << 32), hi = uint64_t(v[2]) | (uint64_t(v[3]) << 32);
+                    const int n = 16 * (past > 0 ? past : 0);
+                    uint64_t a = lo, b = hi;
+                    if (n >= 128) { a = 0; b = 0; }
+                    else if (n >= 64) { a = hi >> (n - 64); b = 0; }
+                    else if (n > 0) { a = (lo >> n) | (hi << (64 - n)); b = hi >> n; }
+                    v = u32x4{uint32_t(a), uint32_t(a >> 32), uint32_t(b), uint32_t(b >> 32)};
+                }
+                *reinterpret_cast<u32x4*>(lds + (t & 1) * C::XST + (d * 8 + wave) * 1024 + lane * 16) = v;
+            }
+#pragma unroll
+            for (int d = 0; d < C::WD; ++d) {
+                if constexpr (C::CODES) transcode_one(t, d, u32x2{rw[j][2 * d], rw[j][2 * d + 1]}, std::true_type{});
+                else *reinterpret_cast<uint32_t*>(lds + C::OFF_W + (t & 1) * C::WST + (d * 512 + tid) * 4) = rw[j][d];
+            }
+#pragma unroll
+            for (int d = 0; d < C::SD; ++d)
+                *reinterpret_cast<uint32_t*>(lds + C::OFF_S + (t & 1) * C::SST + (d * 512 + tid) * 4) = rs[j][d];
         }
     };
 
@@ -447,6 +504,9 @@ tile_kernel(TileParams p)
         for (int b = 0; b < FN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    typedef std::integral_constant<int, 2> I2;
+    typedef std::integral_constant<int, 3> I3;
     typedef std::true_type Inside;                        // the step lies inside K
     typedef std::false_type Any;
     // The D transfers of a step are spread over its 2 FN NB slots (two per fragment's matrix instructions): all at
@@ -486,41 +546,28 @@ tile_kernel(TileParams p)
             }
             table[b] = c[0] | (c[1] << 2) | (c[2] << 4) | (c[3] << 6) | (c[4] << 8);
         }
+    }
+    if constexpr (C::RAGGED) {
+        static_assert(DEP == 4, "slots");
+        fetch(0, I0{}); fetch(1, I1{}); fetch(2, I2{}); fetch(3, I3{});
+        if constexpr (C::CODES) lds_barrier();            // the table
+        put(0, I0{}); fetch(4, I0{});
+        put(1, I1{}); fetch(5, I1{});
+        lds_barrier();
+    } else if constexpr (C::CODES) {
         issue_w(0, 0, Any{});
         if (steps > 1) issue_w(1, 1, Any{});
-        if constexpr (C::RAGGED) {
-            load_x(0); store_x(0);
-            if (steps > 1) { load_x(1); store_x(1); }
-            if (steps > 2) load_x(2);
-        } else {
 #pragma unroll
-            for (int d = 0; d < C::XD; ++d) {
-                issue_x(0, 0, d, Any{});
-                if (steps > 1) issue_x(1, 1, d, Any{});
-            }
+        for (int d = 0; d < C::XD; ++d) {
+            issue_x(0, 0, d, Any{});
+            if (steps > 1) issue_x(1, 1, d, Any{});
         }
         wait_vm<0>();
         lds_barrier();
         transcode(0, Any{});
         if (steps > 1) transcode(1, Any{});
         lds_barrier();
-        if (steps > 2) {
-            if constexpr (C::RAGGED) issue_w(2, 0, Any{});
-            else issue_slots(2, 2, IFirst{}, IEarly{}, Any{});
-        }
-    } else if constexpr (C::RAGGED) {
-        issue_w(0, 0, Any{});
-        if (steps > 1) issue_w(1, 1, Any{});
-#pragma unroll
-        for (int d = 0; d < C::SD; ++d) {
-            issue_s(0, 0, d);
-            if (steps > 1) issue_s(1, 1, d);
-        }
-        load_x(0); store_x(0);
-        if (steps > 1) { load_x(1); store_x(1); }
-        if (steps > 2) load_x(2);
-        wait_vm<0>();
-        lds_barrier();
+        if (steps > 2) issue_slots(2, 2, IFirst{}, IEarly{}, Any{});
     } else {
 #pragma unroll
         for (int b = 0; b + 1 < ST; ++b)
@@ -542,17 +589,7 @@ tile_kernel(TileParams p)
     // The barrier of step s: behind it all reads of stage s are done and step s + 1 is in LDS.
     auto turn = [&](int s, auto mode) {
         if constexpr (C::RAGGED) {
-            wait_vm<0>();
             lds_barrier();
-            if constexpr (C::CODES) {
-                if (s + 3 < steps) issue_w(s + 3, 0, Any{});
-            } else if (s + 2 < steps) {
-                issue_w(s + 2, s & 1, Any{});
-#pragma unroll
-                for (int d = 0; d < C::SD; ++d) issue_s(s + 2, s & 1, d);
-            }
-            if (s + 2 < steps) store_x(s + 2);
-            if (s + 3 < steps) load_x(s + 3);
         } else if constexpr (C::CODES) {
             // X of step s + 2 may still be on its way, its bytes may not
             if (decltype(mode)::value < 2 || s + 2 < steps) wait_vm<C::XD>(); else wait_vm<0>();
@@ -580,7 +617,7 @@ tile_kernel(TileParams p)
     // st: s mod ST.  An odd number of blocks swaps the two sets of X fragments from step to step: PAR0 is the set of
     // the step's first block; with SWAP = false they are copied, and every step starts from set 0.
     int st = 0, st_before = ST - 1;
-    auto step = [&](int s, auto par0, auto swap, auto mode) {
+    auto step = [&](int s, auto par0, auto swap, auto mode, auto slot) {
         constexpr int MODE = decltype(mode)::value;
         typedef std::integral_constant<bool, MODE == 0> In;
         const int st_next = st + 1 == ST ? 0 : st + 1;
@@ -626,7 +663,10 @@ tile_kernel(TileParams p)
                 fragment(std::integral_constant<int, (FN > 2 ? 3 : 0)>{});
             }
             if constexpr (END) {
-                if constexpr (C::CODES) { if (MODE == 0 || s + 2 < steps) transcode(s + 2, In{}); }
+                if constexpr (C::RAGGED) {                // slot: (s + 2) mod DEP
+                    put(s + 2, slot);
+                    fetch(s + 2 + DEP, slot);
+                } else if constexpr (C::CODES) { if (MODE == 0 || s + 2 < steps) transcode(s + 2, In{}); }
                 if constexpr (PAR == 0 && !decltype(swap)::value) {
 #pragma unroll
                     for (int a = 0; a < FM; ++a) xf[0][a] = xf[1][a];
@@ -640,25 +680,36 @@ tile_kernel(TileParams p)
         st_before = st;
         st = st_next;
     };
-    typedef std::integral_constant<int, 1> I1;
-    typedef std::integral_constant<int, 2> I2;
     constexpr bool kSwap = (NB & 1) && !C::CODES;
+    typedef std::integral_constant<int, kSwap ? 1 : 0> IOdd;
+    typedef std::integral_constant<bool, kSwap> Swap;
     int s = 0;
-    if constexpr (!C::RAGGED) {
+    if constexpr (C::RAGGED) {
+        for (;;) {
+            step(s, I0{}, Swap{}, I2{}, I2{});
+            if (++s >= steps) break;
+            step(s, IOdd{}, Swap{}, I2{}, I3{});
+            if (++s >= steps) break;
+            step(s, I0{}, Swap{}, I2{}, I0{});
+            if (++s >= steps) break;
+            step(s, IOdd{}, Swap{}, I2{}, I1{});
+            if (++s >= steps) break;
+        }
+    } else {
         constexpr int ahead = C::CODES ? 3 : ST;
         const int inside_steps = K / KS;
         if constexpr (kSwap) {
             for (; s + 1 + ahead < inside_steps; s += 2) {
-                step(s, I0{}, std::true_type{}, I0{});
-                step(s + 1, I1{}, std::true_type{}, I0{});
+                step(s, I0{}, Swap{}, I0{}, I0{});
+                step(s + 1, I1{}, Swap{}, I0{}, I0{});
             }
         } else {
-            for (; s + ahead < inside_steps; ++s) step(s, I0{}, std::false_type{}, I0{});
+            for (; s + ahead < inside_steps; ++s) step(s, I0{}, std::false_type{}, I0{}, I0{});
         }
         if constexpr (!C::CODES)
-            for (; s + ahead < steps; ++s) step(s, I0{}, std::false_type{}, I1{});
+            for (; s + ahead < steps; ++s) step(s, I0{}, std::false_type{}, I1{}, I0{});
+        for (; s < steps; ++s) step(s, I0{}, std::false_type{}, I2{}, I0{});
     }
-    for (; s < steps; ++s) step(s, I0{}, std::false_type{}, I2{});
     };
     if constexpr (kFullSets < WK) {
         if (short_set) run(std::integral_constant<int, NB - 1>{});

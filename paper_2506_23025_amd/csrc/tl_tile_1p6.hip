@@ -21,13 +21,28 @@ constexpr TileCost kCost[kShapes] = {
     {32, 64, 320, 256, 2.1, 0.70, 0.70},
 };
 
+// K that is no multiple of 8
+typedef TileCfg<kTile1p6, true, 4, 2, 1, 4, 2, 5, 2> R64x128;
+typedef TileCfg<kTile1p6, true, 2, 2, 1, 4, 2, 5, 2> R32x128;
+typedef TileCfg<kTile1p6, true, 1, 2, 1, 2, 4, 10, 2> R16x64;
+
+constexpr int kRagged = 3;
+constexpr TileCost kRaggedCost[kRagged] = {
+    {64, 128, 160, 256, 5.4, 0.96, 0.96},
+    {32, 128, 160, 256, 3.7, 0.70, 0.70},
+    {16, 64, 320, 256, 3.5, 0.63, 0.63},
+};
+
 int pick(int64_t M, int64_t N, int64_t K, double* us)
 {
-    int best = kShapes - 1;
+    const bool ragged = K % 8 != 0;
+    const TileCost* const cost = ragged ? kRaggedCost : kCost;
+    const int count = ragged ? kRagged : kShapes;
+    int best = count - 1;
     double t_best = 1e300;
-    for (int i = 0; i < kShapes; ++i) {
-        if (int64_t(kCost[i].bm) * K > int64_t(1) << 30) continue;        // row offsets within a tile are 32-bit
-        const double t = tile_time(kCost[i], M, N, K);
+    for (int i = 0; i < count; ++i) {
+        if (int64_t(cost[i].bm) * K > int64_t(1) << 30) continue;         // row offsets within a tile are 32-bit
+        const double t = tile_time(cost[i], M, N, K);
         if (t < t_best) { t_best = t; best = i; }
     }
     if (us) *us = t_best;
@@ -36,21 +51,28 @@ int pick(int64_t M, int64_t N, int64_t K, double* us)
 
 }  // namespace
 
-// Tiled kernel or weight-streaming kernel (gemv3), where both can run the shape (K % 8 == 0).  The weight-streaming
+// Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel (gemv3): it
+// never loses up to 16 rows.  The weight-streaming
 // kernel decodes W once per 16 rows; its time (us, W in MB of packed bytes, b blocks of 16 rows): 5 + b (0.12 + 0.28 W)
 // while K is one pass (4096 -> 14336: b = 4 19.0, b = 32 114.6; 4096 -> 4096: b = 32 38.2); beyond, rounds of 256
 // 16-row tiles of W that take 10.4 us at K = 11008 (11008 -> 4096: b = 1 11.4, b = 2 21.6, b = 32 334).  The tiled kernel on the same: 4096 -> 14336 b = 32 57,
 // 11008 -> 4096 b = 32 62, 4096 -> 4096 b = 32 26.
+// Other K: the plain kernel on the vector ALUs, 3 + K / 4096 (7 + 7.5 per row, up to 4) for every 1024 workgroups of 4 x 4
+// outputs (4090 -> 4099: M = 1 17.8, M = 4 39, M = 16 159, M = 37 324; 1001 -> 1024: M = 1 6.8, M = 16 13).
 bool tile3_preferred(int64_t M, int64_t N, int64_t K)
 {
-    if (M <= 16 || K < 8 || K % 8 != 0 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
+    if ((M <= 16 && K % 8 == 0) || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
+    double us;
+    pick(M, N, K, &us);
+    if (K % 8 != 0) {
+        const double groups = double((M + 3) / 4) * double((N + 3) / 4) / 1024.0;
+        return us < 3.0 + double(K) / 4096.0 * (7.0 + 7.5 * double(M < 4 ? M : 4)) * (groups > 1.0 ? groups : 1.0);
+    }
     const double w_mb = double(N) * double((K + 4) / 5) / 1.0e6;
     const double blocks = double((M + 15) / 16);
     const double rounds = double(((M + 15) / 16 * ((N + 15) / 16) + 255) / 256);
     const double t_stream = gemv3_groups(M < 4096 ? M : 4096, N, K) ? 5.0 + blocks * (0.12 + 0.28 * w_mb)
                                                                     : 1.0 + rounds * 10.4 * double(K) / 11008.0;
-    double us;
-    pick(M, N, K, &us);
     return 1.08 * us < t_stream;                          // a band: near the crossover the models are within that of each other
 }
 
@@ -61,6 +83,9 @@ hipError_t tile3_init()
     if (e == hipSuccess) e = tile_prepare<T64x128>();
     if (e == hipSuccess) e = tile_prepare<T64x64>();
     if (e == hipSuccess) e = tile_prepare<T32x64>();
+    if (e == hipSuccess) e = tile_prepare<R64x128>();
+    if (e == hipSuccess) e = tile_prepare<R32x128>();
+    if (e == hipSuccess) e = tile_prepare<R16x64>();
     return e;
 }
 
@@ -73,7 +98,15 @@ hipError_t launch_tile3(const __half* x, const uint8_t* Wp, int64_t stride, floa
     p.row_bytes = int(stride);
     p.group16 = 1;
     p.fx = fx;
-    switch (pick(M, N, K, nullptr)) {
+    const int shape = pick(M, N, K, nullptr);
+    if (K % 8 != 0) {
+        switch (shape) {
+            case 0: return tile_launch<R64x128>(p, s);
+            case 1: return tile_launch<R32x128>(p, s);
+            default: return tile_launch<R16x64>(p, s);
+        }
+    }
+    switch (shape) {
         case 0: return tile_launch<T128x256>(p, s);
         case 1: return tile_launch<T128x128>(p, s);
         case 2: return tile_launch<T64x128>(p, s);

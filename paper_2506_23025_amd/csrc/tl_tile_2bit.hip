@@ -1,4 +1,4 @@
-// 2-bit words, one gamma, K a multiple of 64: instances of the tiled matrix-core kernel and the choice among them.
+// 2-bit words, one gamma: instances of the tiled matrix-core kernel and the choice among them.
 #include "tl_tile.hpp"
 
 namespace tl {
@@ -39,7 +39,63 @@ int pick(int64_t M, int64_t N, int64_t K, double* us)
     return best;
 }
 
+// K that is no multiple of 64
+typedef TileCfg<kTile2Bit, true, 8, 2, 1, 4, 2, 4, 2> R128x128;     // steps of 128
+typedef TileCfg<kTile2Bit, true, 4, 2, 1, 4, 2, 4, 2> R64x128;
+typedef TileCfg<kTile2Bit, true, 2, 2, 1, 2, 4, 4, 2> R32x64;       // two workgroups per CU
+typedef TileCfg<kTile2Bit, true, 1, 2, 1, 1, 8, 8, 2> R16x32;       // steps of 256, two workgroups per CU
+
+constexpr int kRagged = 4;
+constexpr TileCost kRaggedCost[kRagged] = {
+    {128, 128, 128, 256, 7.8, 1.10, 1.10},
+    {64, 128, 128, 256, 3.6, 0.60, 0.60},
+    {32, 64, 128, 512, 2.2, 0.45, 0.31},
+    {16, 32, 256, 512, 2.0, 0.46, 0.28},
+};
+
+int pick_ragged(int64_t M, int64_t N, int64_t K, double* us)
+{
+    int best = kRagged - 1;
+    double t_best = 1e300;
+    for (int i = 0; i < kRagged; ++i) {
+        if (!fits(kRaggedCost[i], K)) continue;
+        const double t = tile_time(kRaggedCost[i], M, N, K);
+        if (t < t_best) { t_best = t; best = i; }
+    }
+    if (us) *us = t_best;
+    return best;
+}
+
 }  // namespace
+
+// K that is no multiple of 64: tiled kernel or the plain kernel on the vector ALUs, which takes (us) 2.8 + K / 4096
+// (5.6 + 1.6 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (4090 -> 4099: M = 1 9.6, M = 4 13.0, M = 16
+// 32.3, M = 37 52.8; 1000 -> 1024: M = 1 4.4, M = 16 8.9).  The tiled kernel on the same: 7.8, 7.9, 8.1, 11.4; 4.6, 4.7.
+bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K)
+{
+    if (K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
+    const double groups = double((M + 15) / 16) * double((N + 15) / 16) / 512.0;
+    const double plain = 2.8 + double(K) / 4096.0 * (5.6 + 1.6 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
+    double us;
+    pick_ragged(M, N, K, &us);
+    return us < plain;
+}
+
+hipError_t launch_tile_ragged(const __half* x, const uint32_t* Wp, float gamma, __half* y,
+                              int64_t M, int64_t N, int64_t K, hipStream_t s)
+{
+    TileParams p{};
+    p.x = x; p.W = reinterpret_cast<const unsigned char*>(Wp); p.y = y; p.gamma = gamma;
+    p.M = int(M); p.N = int(N); p.K = int(K);
+    p.row_bytes = int((K + 15) / 16 * 4);
+    p.group16 = 1;
+    switch (pick_ragged(M, N, K, nullptr)) {
+        case 0: return tile_launch<R128x128>(p, s);
+        case 1: return tile_launch<R64x128>(p, s);
+        case 2: return tile_launch<R32x64>(p, s);
+        default: return tile_launch<R16x32>(p, s);
+    }
+}
 
 bool mfma_supports(int64_t M, int64_t N, int64_t K)
 {
@@ -62,6 +118,10 @@ hipError_t mfma_init()
     if (e == hipSuccess) e = tile_prepare<T128x64>();
     if (e == hipSuccess) e = tile_prepare<T64x64>();
     if (e == hipSuccess) e = tile_prepare<T32x64>();
+    if (e == hipSuccess) e = tile_prepare<R128x128>();
+    if (e == hipSuccess) e = tile_prepare<R64x128>();
+    if (e == hipSuccess) e = tile_prepare<R32x64>();
+    if (e == hipSuccess) e = tile_prepare<R16x32>();
     return e;
 }
 

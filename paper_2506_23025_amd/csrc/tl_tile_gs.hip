@@ -1,4 +1,4 @@
-// 2-bit words with group scales, K a multiple of 64: instances of the tiled matrix-core kernel and the choice among
+// 2-bit words with group scales: instances of the tiled matrix-core kernel and the choice among
 // them.
 #include "tl_tile.hpp"
 
@@ -28,13 +28,28 @@ constexpr TileCost kCost[kShapes] = {
     {32, 64, 128, 512, 3.0, 0.46, 0.28},
 };
 
+// K that is no multiple of 64
+typedef TileCfg<kTileGs, true, 4, 2, 1, 4, 2, 4, 2, 1> R64x128;
+typedef TileCfg<kTileGs, true, 2, 2, 1, 2, 4, 4, 2, 1> R32x64;      // two workgroups per CU
+typedef TileCfg<kTileGs, true, 1, 2, 1, 2, 4, 4, 2, 1> R16x64;      // two workgroups per CU
+
+constexpr int kRagged = 3;
+constexpr TileCost kRaggedCost[kRagged] = {
+    {64, 128, 128, 256, 4.2, 0.83, 0.83},
+    {32, 64, 128, 512, 2.8, 0.54, 0.38},
+    {16, 64, 128, 512, 2.5, 0.53, 0.36},
+};
+
 int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
 {
-    int best = kShapes - 1;
+    const bool ragged = K % 64 != 0;
+    const TileCost* const cost = ragged ? kRaggedCost : kCost;
+    const int count = ragged ? kRagged : kShapes;
+    int best = count - 1;
     double t_best = 1e300;
-    for (int i = group % 64 == 0 ? 0 : kFirstAny; i < kShapes; ++i) {
-        if (int64_t(kCost[i].bm) * K > int64_t(1) << 30) continue;        // row offsets within a tile are 32-bit
-        const double t = tile_time(kCost[i], M, N, K);
+    for (int i = ragged || group % 64 == 0 ? 0 : kFirstAny; i < count; ++i) {
+        if (int64_t(cost[i].bm) * K > int64_t(1) << 30) continue;         // row offsets within a tile are 32-bit
+        const double t = tile_time(cost[i], M, N, K);
         if (t < t_best) { t_best = t; best = i; }
     }
     if (us) *us = t_best;
@@ -51,21 +66,19 @@ int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
 //    workgroups of 16 x 16 outputs (4096 -> 4096: M = 1 11.3, M = 4 14.6, M = 16 29.8, M = 37 45.8)
 bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
 {
-    if (K < 64 || K % 64 != 0 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
-    const double w_mb = double(N) * double(K) / 4.0e6;
-    const double blocks = double((M + 15) / 16);
-    double other;
-    if (gemv_gs_supports(M, N, K, group)) {
-        if (M <= 16) return false;
-        const double passes = double((K + 4095) / 4096);
-        other = 4.6 + 6.0 * (passes - 1.0) + blocks * (0.1 + (group % 256 == 0 ? 0.18 : 0.31) * w_mb);
-    } else {
-        const double groups = blocks * double((N + 15) / 16) / 512.0;
-        other = 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
-    }
+    if (K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
     double us;
     pick(M, N, K, group, &us);
-    return 1.08 * us < other;                              // a band: near the crossover the models are within that of each other
+    const double blocks = double((M + 15) / 16);
+    if (gemv_gs_supports(M, N, K, group)) {
+        if (M <= 16) return false;
+        const double w_mb = double(N) * double(K) / 4.0e6;
+        const double passes = double((K + 4095) / 4096);
+        // a band: near the crossover the models are within that of each other
+        return 1.08 * us < 4.6 + 6.0 * (passes - 1.0) + blocks * (0.1 + (group % 256 == 0 ? 0.18 : 0.31) * w_mb);
+    }
+    const double groups = blocks * double((N + 15) / 16) / 512.0;
+    return us < 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
 }
 
 hipError_t tile_gs_init()
@@ -77,6 +90,9 @@ hipError_t tile_gs_init()
     if (e == hipSuccess) e = tile_prepare<T128x64any>();
     if (e == hipSuccess) e = tile_prepare<T64x64any>();
     if (e == hipSuccess) e = tile_prepare<T32x64any>();
+    if (e == hipSuccess) e = tile_prepare<R64x128>();
+    if (e == hipSuccess) e = tile_prepare<R32x64>();
+    if (e == hipSuccess) e = tile_prepare<R16x64>();
     return e;
 }
 
@@ -86,10 +102,18 @@ hipError_t launch_tile_gs(const __half* x, const uint32_t* Wp, const __half* sca
     TileParams p{};
     p.x = x; p.W = reinterpret_cast<const unsigned char*>(Wp); p.scales = scales; p.y = y; p.gamma = 1.f;
     p.M = int(M); p.N = int(N); p.K = int(K);
-    p.row_bytes = int(K / 4);
+    p.row_bytes = int((K + 15) / 16 * 4);
     // a group longer than K is the one group there is
-    p.group16 = int((group < K ? group : K) / 16);
-    switch (pick(M, N, K, group, nullptr)) {
+    p.group16 = int((group < K ? group : K + 15) / 16);
+    const int shape = pick(M, N, K, group, nullptr);
+    if (K % 64 != 0) {
+        switch (shape) {
+            case 0: return tile_launch<R64x128>(p, s);
+            case 1: return tile_launch<R32x64>(p, s);
+            default: return tile_launch<R16x64>(p, s);
+        }
+    }
+    switch (shape) {
         case 0: return tile_launch<T256x256>(p, s);
         case 1: return tile_launch<T128x256>(p, s);
         case 2: return tile_launch<T128x128>(p, s);

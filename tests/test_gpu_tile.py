@@ -81,3 +81,52 @@ def test_tile_group_scales(M, N, K, group):
     assert np.isfinite(y).all()
     ref = oracle.gemm_group_scales(x, np.ascontiguousarray(W[cols]), np.ascontiguousarray(s[:, cols]), group)
     assert_close(y[:, cols], ref, x, 0.05, f"tile scales {M}x{N}x{K} group {group}")   # no scale is above 0.05
+
+
+# K that fits no 16-byte piece: X rows at any even byte, W rows at any word; K of one piece (the smallest the form takes),
+# one short of and past a block, a piece, a step and the fetch depth; the four tile shapes; N = 1 and N odd.
+RAGGED_SHAPES = [
+    (1, 1, 9), (3, 40, 33), (16, 333, 1001), (16, 4099, 255), (37, 4099, 4090), (70, 257, 127), (40, 1030, 129), (200, 2050, 257),
+    (150, 8200, 641), (900, 2500, 1100), (1030, 4100, 383), (5, 64, 2044), (33, 130, 8190),
+]
+
+
+@pytest.mark.parametrize("M,N,K", RAGGED_SHAPES)
+def test_tile_odd_k(M, N, K):
+    x, W, g = si.layer(34000 + M + N + K, M, N, K)
+    cols = _sampled(N, M)
+    ref = oracle.gemm(x, np.ascontiguousarray(W[cols]), g)
+    xd, gb = to_dev(x.view(np.int16)), si.gamma_bits(g)
+    yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+
+    def check(what, ref, gamma):
+        y = yd.cpu().numpy().view(np.float16)
+        assert np.isfinite(y).all()
+        assert_close(y[:, cols], ref, x, gamma, f"odd K {what} {M}x{N}x{K}")
+        yd.fill_(-1)
+
+    tl.tl_ternary_gemm(xd, dev_u32(tl.tl_pack_2bit(W)), gb, yd, M, N, K)
+    check("2-bit", ref, g)
+    for fx in (False, True):
+        Wp = to_dev(tl.tl_pack_1p6bit_fx(W) if fx else tl.tl_pack_1p6bit(W))
+        (tl.tl_ternary_gemm_1p6_fx if fx else tl.tl_ternary_gemm_1p6)(xd, Wp, gb, yd, M, N, K)
+        check(f"1.6-bit fx={fx}", ref, g)
+    for group in (16, 144, 8192):
+        s = si.group_scales(np.random.default_rng(K + group), -(-K // group), N)
+        tl.tl_ternary_gemm_gs(xd, dev_u32(tl.tl_pack_2bit(W)), to_dev(s.view(np.int16)), group, yd, M, N, K)
+        sref = oracle.gemm_group_scales(x, np.ascontiguousarray(W[cols]), np.ascontiguousarray(s[:, cols]), group)
+        check(f"scales {group}", sref, 0.05)
+
+
+def test_tile_odd_k_keeps_rows_apart():
+    # a row of x with an infinity or a NaN next to rows without: the pieces that reach past K must not bring it in
+    M, N, K = 40, 200, 1003
+    x, W, g = si.layer(34900, M, N, K)
+    x[3, 0], x[7, K - 1], x[39, 5] = np.inf, np.nan, -np.inf
+    yd = to_dev(np.zeros((M, N), dtype=np.int16))
+    tl.tl_ternary_gemm(to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), si.gamma_bits(g), yd, M, N, K)
+    y = yd.cpu().numpy().view(np.float16)
+    clean = np.setdiff1d(np.arange(M), [3, 7, 39])
+    assert np.isfinite(y[clean]).all()
+    assert_close(y[clean], oracle.gemm(x[clean], W, g), x[clean], g, "rows beside a NaN")
+    assert np.isnan(y[7]).all()
