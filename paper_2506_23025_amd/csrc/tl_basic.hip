@@ -6,22 +6,6 @@ namespace tl {
 
 namespace {
 
-// ---- Sec. 3.1 decode: one thread per 32-bit word, 16 weights out -------------------
-__global__ void __launch_bounds__(256)
-unpack2_kernel(const uint32_t* __restrict__ packed, int64_t N, int64_t K, int64_t words,
-               int8_t* __restrict__ out)
-{
-    const int64_t gid = blockIdx.x * int64_t(256) + threadIdx.x;
-    if (gid >= N * words) return;
-    const int64_t n = gid / words;
-    const int64_t i = gid - n * words;
-    uint32_t word = packed[gid];
-    const int64_t base = 16 * i;
-    int8_t* dst = out + n * K + base;
-    const int len = (K - base < 16) ? int(K - base) : 16;
-    for (int j = 0; j < len; ++j, word >>= 2) dst[j] = int8_t(int(word & 3u) - 1);
-}
-
 // Digit i (0..4) of a 1.6-bit byte as w + 1.  Plain form: base-3 digits, least significant
 // first.  Fixed-point form (Sec. 3.2 with k = 5, p = 8): the byte is b = ceil(256 V / 243) for the
 // block value V = sum_j d_j 3^(4-j) < 243, so V = floor(243 b / 256) gives it back, and its base-3
@@ -48,22 +32,97 @@ __device__ __forceinline__ void digits5(unsigned v, bool fx, unsigned (&d)[5])
     }
 }
 
-// ---- base-3 byte decode: one thread per byte, up to 5 weights out ------------------
+// ---- device unpacking ------------------------------------------------------------
+// Bound by HBM: a quarter or a fifth of a byte read and one byte written per weight.  What matters is that the
+// output leaves in whole 16-byte pieces (a thread that stores its 16 or 5 weights byte by byte: 4096 x 14336
+// from 1.6-bit bytes 35.6 us; this kernel 12.0, 5.9 TB/s read and written).  The output is therefore walked as one flat array in 16-byte pieces aligned
+// in memory, whatever K and the address of W_out are: a thread finds the row and column its piece starts at, fetches
+// the 16 codes from there as one 32-bit word -- two packed words shifted together, or four bytes looked up in a
+// table of 10-bit code groups -- and spreads them to bytes.  Pieces that lie across the end of a row, or
+// of the array, go weight by weight.
+// FMT: 0 2-bit words, 1 plain base-3 bytes, 2 fixed-point bytes.
+constexpr int kUnpackPieces = 4;             // pieces per thread: their fetches are in flight together
+
+template <int FMT>
 __global__ void __launch_bounds__(256)
-unpack3_kernel(const uint8_t* __restrict__ packed, int64_t N, int64_t K, int64_t stride,
-               int64_t nbytes, int8_t* __restrict__ out, bool fx)
+unpack_kernel(const unsigned char* __restrict__ packed, int64_t K, int64_t stride, int64_t total, int head,
+              int8_t* __restrict__ out)
 {
-    const int64_t gid = blockIdx.x * int64_t(256) + threadIdx.x;
-    if (gid >= N * nbytes) return;
-    const int64_t n = gid / nbytes;
-    const int64_t b = gid - n * nbytes;
-    unsigned d[5];
-    digits5(packed[n * stride + b], fx, d);
-    const int64_t base = 5 * b;
-    int8_t* dst = out + n * K + base;
+    __shared__ uint32_t table[FMT == 0 ? 1 : 256];            // byte -> five 2-bit codes
+    if constexpr (FMT != 0) {
+        unsigned d[5];
+        digits5(threadIdx.x, FMT == 2, d);
+        table[threadIdx.x] = d[0] | (d[1] << 2) | (d[2] << 4) | (d[3] << 6) | (d[4] << 8);
+        __syncthreads();
+    }
+    // first weight of the block's first piece; the array's first piece may start before the array (head in 0..15)
+    const int64_t f0 = int64_t(blockIdx.x) * (256 * 16 * kUnpackPieces) - head;
+    const int64_t base = f0 > 0 ? f0 : 0;
+    const int64_t n0 = base / K;                               // uniform: once per block
+    const uint32_t k0 = uint32_t(base - n0 * K);
+    const uint32_t Ku = uint32_t(K);
+    int64_t row[kUnpackPieces];
+    uint32_t col[kUnpackPieces];
+    bool whole[kUnpackPieces];
+    uint32_t lo[kUnpackPieces], hi[kUnpackPieces];
 #pragma unroll
-    for (int i = 0; i < 5; ++i)
-        if (base + i < K) dst[i] = int8_t(int(d[i]) - 1);
+    for (int u = 0; u < kUnpackPieces; ++u) {
+        const int64_t f = f0 + (u * 256 + int(threadIdx.x)) * 16;
+        const int64_t g = f > 0 ? f : 0;
+        const uint32_t k = k0 + uint32_t(g - base);            // < 2^31 + 2^14
+        const uint32_t q = k / Ku;
+        row[u] = n0 + q;
+        col[u] = k - q * Ku;
+        whole[u] = f >= 0 && f + 16 <= total && col[u] + 16u <= Ku;
+        lo[u] = hi[u] = 0;
+        if (whole[u]) {
+            const unsigned char* const r = packed + row[u] * stride;
+            if constexpr (FMT == 0) {
+                const uint32_t* const w = reinterpret_cast<const uint32_t*>(r) + (col[u] >> 4);
+                lo[u] = w[0];
+                if (col[u] & 15u) hi[u] = w[1];                // the piece ends inside the row: there is a next word
+            } else {
+                typedef uint32_t __attribute__((aligned(1))) u32_any;
+                lo[u] = *reinterpret_cast<const u32_any*>(r + col[u] / 5u);      // the 4 bytes that hold weights col .. col + 15
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kUnpackPieces; ++u) {
+        const int64_t f = f0 + (u * 256 + int(threadIdx.x)) * 16;
+        if (whole[u]) {
+            uint64_t codes;
+            if constexpr (FMT == 0) {
+                codes = (uint64_t(lo[u]) | (uint64_t(hi[u]) << 32)) >> (2u * (col[u] & 15u));
+            } else {
+                codes = uint64_t(table[lo[u] & 255u]) | (uint64_t(table[(lo[u] >> 8) & 255u]) << 10) |
+                        (uint64_t(table[(lo[u] >> 16) & 255u]) << 20) | (uint64_t(table[lo[u] >> 24]) << 30);
+                codes >>= 2u * (col[u] % 5u);
+            }
+            const uint32_t c = uint32_t(codes);
+            u32x4 o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t b = (c >> (8 * j)) & 255u;
+                const uint32_t v = (b | (b << 6) | (b << 12) | (b << 18)) & 0x03030303u;     // one code per byte
+                o[j] = (v + 0x7f7f7f7fu) ^ 0x80808080u;                                      // code - 1, byte by byte
+            }
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(out + f));
+        } else {
+            int64_t n = row[u];
+            uint32_t k = col[u];
+            for (int e = 0; e < 16; ++e) {
+                const int64_t g = f + e;
+                if (g < 0 || g >= total) continue;
+                const unsigned char* const r = packed + n * stride;
+                uint32_t code;
+                if constexpr (FMT == 0) code = reinterpret_cast<const uint32_t*>(r)[k >> 4] >> (2u * (k & 15u));
+                else code = table[r[k / 5u]] >> (2u * (k % 5u));
+                out[g] = int8_t(int(code & 3u) - 1);
+                if (++k == Ku) { k = 0; ++n; }
+            }
+        }
+    }
 }
 
 __global__ void __launch_bounds__(256)
@@ -327,21 +386,29 @@ inline unsigned blocks_for(int64_t items, int per_block)
 
 }  // namespace
 
+namespace {
+
+template <int FMT>
+hipError_t launch_unpack(const void* packed, int64_t N, int64_t K, int64_t stride, int8_t* out, hipStream_t s)
+{
+    const int64_t total = N * K;
+    const int head = int(reinterpret_cast<uintptr_t>(out) & 15u);         // bytes of the first 16-byte piece before the array
+    hipLaunchKernelGGL(unpack_kernel<FMT>, dim3(blocks_for(total + head, 256 * 16 * kUnpackPieces)), dim3(256), 0, s,
+                       static_cast<const unsigned char*>(packed), K, stride, total, head, out);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_unpack2(const uint32_t* packed, int64_t N, int64_t K, int8_t* out, hipStream_t s)
 {
-    const int64_t words = (K + 15) / 16;
-    hipLaunchKernelGGL(unpack2_kernel, dim3(blocks_for(N * words, 256)), dim3(256), 0, s,
-                       packed, N, K, words, out);
-    return hipGetLastError();
+    return launch_unpack<0>(packed, N, K, (K + 15) / 16 * 4, out, s);
 }
 
 hipError_t launch_unpack3(const uint8_t* packed, int64_t N, int64_t K, int64_t stride, int8_t* out,
                           bool fx, hipStream_t s)
 {
-    const int64_t nbytes = (K + 4) / 5;
-    hipLaunchKernelGGL(unpack3_kernel, dim3(blocks_for(N * nbytes, 256)), dim3(256), 0, s,
-                       packed, N, K, stride, nbytes, out, fx);
-    return hipGetLastError();
+    return fx ? launch_unpack<2>(packed, N, K, stride, out, s) : launch_unpack<1>(packed, N, K, stride, out, s);
 }
 
 hipError_t launch_probe_copy(void* dst, const void* src, size_t bytes, hipStream_t s)
