@@ -131,10 +131,27 @@ def _ptr(t):
     return t.data_ptr()
 
 
+def _first_stream():
+    """The current stream by torch's public call, which also sets torch's device up.  The calls after
+    it ask for the same handle directly where this torch has the functions: 0.2 us instead of the 2.8 us that building a
+    Stream object takes, as long as the launch itself."""
+    global _raw_stream
+    import torch
+    handle = torch.cuda.current_stream().cuda_stream
+    device, raw = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if device is not None and raw is not None and raw(device()) == handle:
+        _raw_stream = (device, raw)
+    return handle
+
+
+_raw_stream = None      # once torch has a device: (current device, raw handle of its current stream)
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is not None:
+            return _raw_stream[1](_raw_stream[0]())
+        return _first_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -887,11 +887,37 @@ static_assert(sizeof(WgRec) == 64, "one record per 64-byte line");
 
 struct LeanBatch {
     WgRec rec[kLeanMaxGroups];
+    __device__ const WgRec& mine() const { return rec[blockIdx.x]; }
 };
 
-template <int T>
+// A launch of one job: 64 bytes of arguments instead of 16 KB.  The records cost nothing on the device but 1 us of
+// the host per launch (written, copied, copied again into the argument segment), which is a fifth of a small decode call:
+// 2048 -> 2048 at M = 1 called in a loop 5.3 us with them, 3.4 us without (that, and no bisection for a
+// single job in launch_stream).  Workgroup g works its own record out: `per` tiles, the first `plus` workgroups one more.
+struct LeanOne {
+    const unsigned char* W;       // packed row 0 of the matrix
+    const unsigned char* x;
+    __half* y;
+    float gamma;
+    int K, N;
+    int Mrem;
+    int per, plus;
+    __device__ WgRec mine() const
+    {
+        const int g = int(blockIdx.x);
+        WgRec r;
+        r.tile0 = g * per + (g < plus ? g : plus);
+        r.ntiles = per + (g < plus ? 1 : 0);
+        r.W = W + size_t(r.tile0) * (size_t(4) * size_t(K));          // 16 rows of K / 4 bytes
+        r.x = x; r.y = y; r.gamma = gamma;
+        r.K = K; r.N = N; r.Mrem = Mrem;
+        return r;
+    }
+};
+
+template <int T, class Args>
 __global__ void __launch_bounds__(512)
-gemv_lean_kernel(LeanBatch b)
+gemv_lean_kernel(Args b)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63;
@@ -901,7 +927,7 @@ gemv_lean_kernel(LeanBatch b)
     unsigned char* const my_lds = lds_raw + wave * kStride;
     typedef const __attribute__((address_space(1))) unsigned char* gbytes;
 
-    const WgRec& R = b.rec[blockIdx.x];
+    const auto& R = b.mine();
     const int K = R.K, N = R.N, rows = R.Mrem, ntiles = R.ntiles;
     const unsigned char* const Wrun = R.W;
     const uint32_t row_bytes = uint32_t(K) >> 2;
@@ -1104,9 +1130,9 @@ gemv_lean_kernel(LeanBatch b)
 constexpr int kLongMaxPasses = 4;
 constexpr int kLongWaveLds = kWaveLds + 2048;     // 16 KB of activation staging + one tile slice
 
-template <int T>
+template <int T, class Args>
 __global__ void __launch_bounds__(512)
-gemv_longk_kernel(LeanBatch b)
+gemv_longk_kernel(Args b)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63;
@@ -1116,7 +1142,7 @@ gemv_longk_kernel(LeanBatch b)
     unsigned char* const tile_buf = my_lds + kWaveLds;
     typedef const __attribute__((address_space(1))) unsigned char* gbytes;
 
-    const WgRec& R = b.rec[blockIdx.x];
+    const auto& R = b.mine();
     const int K = R.K, N = R.N, rows = R.Mrem, ntiles = R.ntiles;
     const int slices = (K + kSliceK - 1) / kSliceK;
     const int P = __builtin_amdgcn_readfirstlane((slices - wave + NW - 1) / NW);   // passes of this wave, >= 1
@@ -1401,21 +1427,49 @@ constexpr int kStreamWaves = 8;         // waves of a stream-form workgroup when
 constexpr int kStreamMaxPasses = 8;     // passes over K the stream form takes: K <= 32768
 constexpr int kStreamMaxRun = 32;       // tiles of a run whose sums fit the 32 KB of LDS left over
 
-using LeanFn = void (*)(LeanBatch);
+template <class Args>
+using LeanFn = void (*)(Args);
 
-LeanFn pick_lean(int T)
+template <class Args>
+LeanFn<Args> pick_lean(int T)
 {
     switch (T) {
-        case 1: return gemv_lean_kernel<1>;
-        case 2: return gemv_lean_kernel<2>;
-        default: return gemv_lean_kernel<3>;
+        case 1: return gemv_lean_kernel<1, Args>;
+        case 2: return gemv_lean_kernel<2, Args>;
+        default: return gemv_lean_kernel<3, Args>;
     }
+}
+
+template <class Args>
+hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, hipStream_t s)
+{
+    const LeanFn<Args> fn = pick_lean<Args>(T);
+    static bool lds_raised[kMaxDevices][4];
+    const int dev = device_slot();
+    if (dev < 0 || !lds_raised[dev][T]) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
+        if (e != hipSuccess) return e;
+        if (dev >= 0) lds_raised[dev][T] = true;
+    }
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(NW * 64), size_t(NW) * stream_wave_lds(T), s, args);
+    return hipGetLastError();
+}
+
+LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int K, int N, int rows, int tiles, int grid)
+{
+    return LeanOne{reinterpret_cast<const unsigned char*>(W), reinterpret_cast<const unsigned char*>(x), y, gamma, K, N, rows,
+                   tiles / grid, tiles % grid};
 }
 
 // Launch of the lean kernel: wg[j] workgroups for job j, each with a run of consecutive tiles
 // (the first tiles % wg[j] of them one tile longer), written out as one record per workgroup.
 hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, hipStream_t s)
 {
+    if (b.count == 1) {
+        const GemvJob& J = b.job[0];
+        return launch_lean_args(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0]), wg[0], NW, T, s);
+    }
     LeanBatch lb;
     int grid = 0;
     for (int j = 0; j < b.count; ++j) {
@@ -1434,22 +1488,29 @@ hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, hipStre
             r.pad[0] = r.pad[1] = r.pad[2] = r.pad[3] = 0;
         }
     }
-    LeanFn fn = pick_lean(T);
-    static bool lds_raised[kMaxDevices][4];
+    return launch_lean_args(lb, grid, NW, T, s);
+}
+
+template <class Args>
+LeanFn<Args> pick_longk(int T)
+{
+    return T == 1 ? gemv_longk_kernel<1, Args> : gemv_longk_kernel<2, Args>;
+}
+
+template <class Args>
+hipError_t launch_longk_args(const Args& args, int grid, int T, hipStream_t s)
+{
+    const LeanFn<Args> fn = pick_longk<Args>(T);
+    static bool lds_raised[kMaxDevices][3];
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][T]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
         if (e != hipSuccess) return e;
         if (dev >= 0) lds_raised[dev][T] = true;
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(NW * 64), size_t(NW) * stream_wave_lds(T), s, lb);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kStreamWaves * 64), size_t(kStreamWaves) * kLongWaveLds, s, args);
     return hipGetLastError();
-}
-
-LeanFn pick_longk(int T)
-{
-    return T == 1 ? gemv_longk_kernel<1> : gemv_longk_kernel<2>;
 }
 
 // Calls in which every GEMM has 4096 < K <= 16384 and N a multiple of 16, and which hold at most two
@@ -1470,6 +1531,11 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
     int64_t groups = 0;
     for (int i = 0; i < count; ++i) groups += ((jobs[i].M + 15) / 16) * ((jobs[i].N / 16 + T - 1) / T);
     if (groups > kLeanMaxGroups) return false;
+    if (count == 1 && jobs[0].M <= 16) {
+        const GemmDesc& d = jobs[0];
+        *err = launch_longk_args(one_job(d.W, d.x, d.y, d.gamma, int(d.K), int(d.N), int(d.M), int(d.N / 16), int(groups)), int(groups), T, s);
+        return true;
+    }
     LeanBatch lb;
     int grid = 0;
     for (int i = 0; i < count; ++i) {
@@ -1491,17 +1557,7 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
             }
         }
     }
-    LeanFn fn = pick_longk(T);
-    static bool lds_raised[kMaxDevices][3];
-    const int dev = device_slot();
-    if (dev < 0 || !lds_raised[dev][T]) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
-        if (e != hipSuccess) { *err = e; return true; }
-        if (dev >= 0) lds_raised[dev][T] = true;
-    }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kStreamWaves * 64), size_t(kStreamWaves) * kLongWaveLds, s, lb);
-    *err = hipGetLastError();
+    *err = launch_longk_args(lb, grid, T, s);
     return true;
 }
 
@@ -1540,7 +1596,8 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
                         pol.start_up_per_row * double(rows) + (passes(j) > 1 ? pol.pass_start : 0.0)};
     }
     int wg[kMaxJobs];
-    deal_workgroups(model, dj, b.count, G, wg);
+    if (b.count == 1) wg[0] = G;                           // all of them (G is at most the job's tiles)
+    else deal_workgroups(model, dj, b.count, G, wg);
     int run = 1;                                           // longest run of tiles of a workgroup
     for (int j = 0; j < b.count; ++j) {
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
@@ -1687,11 +1744,13 @@ hipError_t gemv_init()
         return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     };
     for (int T = 1; T <= 2; ++T) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_longk(T)), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_longk<LeanBatch>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
+        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_longk<LeanOne>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= 3; ++T) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean(T)), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanBatch>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
+        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanOne>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= kTMax; ++T)

@@ -1,0 +1,36 @@
+"""Single decode calls: the launch with one job's arguments, at the edges of its split into runs of tiles."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2506_23025_amd as tl
+import synth_inputs as si
+from parity import assert_close, dev_u32, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+# one tile; fewer, as many and one more than the workgroups of a K (256 / waves per group); runs of 1 to 3 and more with and
+# without longer ones; then long K: one and two tiles per workgroup, an odd number of tiles
+@pytest.mark.parametrize("M,N,K", [(1, 16, 4096), (1, 4080, 4096), (3, 4096, 4096), (16, 4112, 4096), (2, 8208, 4096), (1, 20496, 4096),
+                                   (1, 4096, 512), (5, 16400, 1024), (1, 16, 4160), (4, 4096, 4608), (1, 4112, 8192), (16, 8176, 4672)])
+def test_single_decode_call(M, N, K):
+    import torch
+    x, W, g = si.layer(35000 + M + N + K, M, N, K)
+    xd, wd, gb = to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), si.gamma_bits(g)
+    yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+    tl.tl_ternary_gemm(xd, wd, gb, yd, M, N, K)
+    y = yd.cpu().numpy().view(np.float16)
+    cols = np.unique(np.r_[0:16, N - 16:N, np.random.default_rng(N).choice(N, min(N, 200), replace=False)])
+    assert np.isfinite(y).all()
+    assert_close(y[:, cols], oracle.gemm(x, np.ascontiguousarray(W[cols]), g), x, g, f"single call {M}x{N}x{K}")
+    # the call goes to the stream that is current, also on a stream that is not the first one used
+    side = torch.cuda.Stream()
+    yd.fill_(-1)
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(2000000)
+        tl.tl_ternary_gemm(xd, wd, gb, yd, M, N, K)
+        on_side = yd.clone()                               # right behind it on the same stream
+    side.synchronize()
+    assert np.array_equal(on_side.cpu().numpy(), y.view(np.int16))
