@@ -17,8 +17,8 @@ constexpr TileCost kCost[kShapes] = {
     {128, 256, 160, 256, 7.0, 2.10, 2.10},
     {128, 128, 160, 256, 5.0, 1.11, 1.11},
     {64, 128, 160, 256, 2.8, 0.78, 0.78},
-    {64, 64, 320, 256, 3.1, 0.84, 0.84},
-    {32, 64, 320, 256, 2.1, 0.70, 0.70},
+    {64, 64, 320, 256, 2.7, 0.84, 0.84},
+    {32, 64, 320, 256, 1.9, 0.70, 0.70},
 };
 
 // K that is no multiple of 8
@@ -30,7 +30,7 @@ constexpr int kRagged = 3;
 constexpr TileCost kRaggedCost[kRagged] = {
     {64, 128, 160, 256, 5.4, 0.96, 0.96},
     {32, 128, 160, 256, 3.7, 0.70, 0.70},
-    {16, 64, 320, 256, 3.5, 0.63, 0.63},
+    {16, 64, 320, 256, 3.1, 0.63, 0.63},
 };
 
 int pick(int64_t M, int64_t N, int64_t K, double* us)

@@ -18,9 +18,9 @@ constexpr TileCost kCost[kShapes] = {
     {256, 256, 64, 256, 5.7, 1.36, 1.36},
     {128, 256, 128, 256, 7.0, 1.36, 1.36},
     {128, 128, 128, 256, 4.0, 0.77, 0.77},
-    {128, 64, 128, 256, 4.2, 0.41, 0.41},
-    {64, 64, 128, 512, 3.0, 0.50, 0.24},
-    {32, 64, 128, 512, 2.5, 0.31, 0.19},
+    {128, 64, 128, 256, 3.5, 0.41, 0.41},
+    {64, 64, 128, 512, 2.6, 0.50, 0.24},
+    {32, 64, 128, 512, 2.3, 0.31, 0.19},
 };
 
 // Row offsets within a tile are 32-bit: tiles of 256 rows up to K = 2^22, of 128 up to 2^23.
@@ -49,8 +49,8 @@ constexpr int kRagged = 4;
 constexpr TileCost kRaggedCost[kRagged] = {
     {128, 128, 128, 256, 7.8, 1.10, 1.10},
     {64, 128, 128, 256, 3.6, 0.60, 0.60},
-    {32, 64, 128, 512, 2.2, 0.45, 0.31},
-    {16, 32, 256, 512, 2.0, 0.46, 0.28},
+    {32, 64, 128, 512, 1.8, 0.45, 0.31},
+    {16, 32, 256, 512, 1.5, 0.46, 0.28},
 };
 
 int pick_ragged(int64_t M, int64_t N, int64_t K, double* us)
@@ -70,7 +70,7 @@ int pick_ragged(int64_t M, int64_t N, int64_t K, double* us)
 
 // K that is no multiple of 64: tiled kernel or the plain kernel on the vector ALUs, which takes (us) 2.8 + K / 4096
 // (5.6 + 1.6 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (4090 -> 4099: M = 1 9.6, M = 4 13.0, M = 16
-// 32.3, M = 37 52.8; 1000 -> 1024: M = 1 4.4, M = 16 8.9).  The tiled kernel on the same: 7.8, 7.9, 8.1, 11.4; 4.6, 4.7.
+// 32.3, M = 37 52.8; 1000 -> 1024: M = 1 4.4, M = 16 8.9).  The tiled kernel on the same: 7.4, 7.4, 7.7, 10.8; 4.4, 4.5.
 bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K)
 {
     if (K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;

@@ -23,9 +23,9 @@ constexpr TileCost kCost[kShapes] = {
     {128, 256, 128, 256, 7.0, 1.63, 1.63},
     {128, 128, 128, 256, 4.7, 0.92, 0.92},
     {128, 128, 128, 256, 4.4, 1.04, 1.04},
-    {128, 64, 128, 256, 4.2, 0.54, 0.54},
-    {64, 64, 128, 512, 3.6, 0.63, 0.34},
-    {32, 64, 128, 512, 3.0, 0.46, 0.28},
+    {128, 64, 128, 256, 3.5, 0.54, 0.54},
+    {64, 64, 128, 512, 3.2, 0.63, 0.34},
+    {32, 64, 128, 512, 2.8, 0.46, 0.28},
 };
 
 // K that is no multiple of 64
@@ -36,8 +36,8 @@ typedef TileCfg<kTileGs, true, 1, 2, 1, 2, 4, 4, 2, 1> R16x64;      // two workg
 constexpr int kRagged = 3;
 constexpr TileCost kRaggedCost[kRagged] = {
     {64, 128, 128, 256, 4.2, 0.83, 0.83},
-    {32, 64, 128, 512, 2.8, 0.54, 0.38},
-    {16, 64, 128, 512, 2.5, 0.53, 0.36},
+    {32, 64, 128, 512, 2.4, 0.54, 0.38},
+    {16, 64, 128, 512, 2.1, 0.53, 0.36},
 };
 
 int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
