@@ -38,8 +38,10 @@ __device__ __forceinline__ void digits5(unsigned v, bool fx, unsigned (&d)[5])
 // from 1.6-bit bytes 35.6 us; this kernel 12.0, 5.9 TB/s read and written).  The output is therefore walked as one flat array in 16-byte pieces aligned
 // in memory, whatever K and the address of W_out are: a thread finds the row and column its piece starts at, fetches
 // the 16 codes from there as one 32-bit word -- two packed words shifted together, or four bytes looked up in a
-// table of 10-bit code groups -- and spreads them to bytes.  Pieces that lie across the end of a row, or
-// of the array, go weight by weight.
+// table of 10-bit code groups -- and spreads them to bytes.  A piece across the end of a row puts two such words
+// together (weight by weight those few pieces held up their whole waves: K = 321, 12928 rows 17.6 us, byte stores 7.1,
+// this 4.1), and where rows are shorter than a piece as many as it takes; the pieces across the ends of the array go
+// weight by weight.
 // FMT: 0 2-bit words, 1 plain base-3 bytes, 2 fixed-point bytes.
 constexpr int kUnpackPieces = 4;             // pieces per thread: their fetches are in flight together
 
@@ -64,7 +66,30 @@ unpack_kernel(const unsigned char* __restrict__ packed, int64_t K, int64_t strid
     int64_t row[kUnpackPieces];
     uint32_t col[kUnpackPieces];
     bool whole[kUnpackPieces];
-    uint32_t lo[kUnpackPieces], hi[kUnpackPieces];
+    uint32_t lo[kUnpackPieces], hi[kUnpackPieces], nx[kUnpackPieces];
+    // the 16 codes from column k of a row on (fewer near its end): 2-bit word `lo` and, where they reach into it, the next; or
+    // the 4 bytes that hold them
+    auto fetch = [&](const unsigned char* r, uint32_t k, uint32_t& w0, uint32_t& w1) {
+        if constexpr (FMT == 0) {
+            const uint32_t* const w = reinterpret_cast<const uint32_t*>(r) + (k >> 4);
+            w0 = w[0];
+            if ((k & 15u) != 0 && (k & ~15u) + 16u < Ku) w1 = w[1];
+        } else {
+            typedef uint32_t __attribute__((aligned(1))) u32_any;
+            // held inside the row, whose padding the last bytes may take in
+            const uint32_t at = k / 5u, last = uint32_t(stride) - 4u, b = at < last ? at : last;
+            w0 = *reinterpret_cast<const u32_any*>(r + b) >> (8u * (at - b));
+        }
+    };
+    auto codes_of = [&](uint32_t w0, uint32_t w1, uint32_t k) {
+        if constexpr (FMT == 0) {
+            return uint32_t((uint64_t(w0) | (uint64_t(w1) << 32)) >> (2u * (k & 15u)));
+        } else {
+            const uint64_t c = uint64_t(table[w0 & 255u]) | (uint64_t(table[(w0 >> 8) & 255u]) << 10) |
+                               (uint64_t(table[(w0 >> 16) & 255u]) << 20) | (uint64_t(table[w0 >> 24]) << 30);
+            return uint32_t(c >> (2u * (k % 5u)));
+        }
+    };
 #pragma unroll
     for (int u = 0; u < kUnpackPieces; ++u) {
         const int64_t f = f0 + (u * 256 + int(threadIdx.x)) * 16;
@@ -73,33 +98,31 @@ unpack_kernel(const unsigned char* __restrict__ packed, int64_t K, int64_t strid
         const uint32_t q = k / Ku;
         row[u] = n0 + q;
         col[u] = k - q * Ku;
-        whole[u] = f >= 0 && f + 16 <= total && col[u] + 16u <= Ku;
-        lo[u] = hi[u] = 0;
+        whole[u] = f >= 0 && f + 16 <= total;
+        lo[u] = hi[u] = nx[u] = 0;
         if (whole[u]) {
             const unsigned char* const r = packed + row[u] * stride;
-            if constexpr (FMT == 0) {
-                const uint32_t* const w = reinterpret_cast<const uint32_t*>(r) + (col[u] >> 4);
-                lo[u] = w[0];
-                if (col[u] & 15u) hi[u] = w[1];                // the piece ends inside the row: there is a next word
-            } else {
-                typedef uint32_t __attribute__((aligned(1))) u32_any;
-                lo[u] = *reinterpret_cast<const u32_any*>(r + col[u] / 5u);      // the 4 bytes that hold weights col .. col + 15
-            }
+            uint32_t none = 0;
+            fetch(r, col[u], lo[u], hi[u]);
+            if (col[u] + 16u > Ku) fetch(r + stride, 0, nx[u], none);       // the piece goes on in the next row
         }
     }
 #pragma unroll
     for (int u = 0; u < kUnpackPieces; ++u) {
         const int64_t f = f0 + (u * 256 + int(threadIdx.x)) * 16;
         if (whole[u]) {
-            uint64_t codes;
-            if constexpr (FMT == 0) {
-                codes = (uint64_t(lo[u]) | (uint64_t(hi[u]) << 32)) >> (2u * (col[u] & 15u));
-            } else {
-                codes = uint64_t(table[lo[u] & 255u]) | (uint64_t(table[(lo[u] >> 8) & 255u]) << 10) |
-                        (uint64_t(table[(lo[u] >> 16) & 255u]) << 20) | (uint64_t(table[lo[u] >> 24]) << 30);
-                codes >>= 2u * (col[u] % 5u);
+            uint32_t c = codes_of(lo[u], hi[u], col[u]);
+            if (col[u] + 16u > Ku) {
+                uint32_t bits = 2u * (Ku - col[u]);                          // of this row's codes, 2 .. 30
+                c = (c & ((1u << bits) - 1u)) | (codes_of(nx[u], 0, 0) << bits);
+                const unsigned char* r = packed + (row[u] + 1) * stride;
+                while ((bits += 2u * Ku) < 32u) {                            // rows shorter than a piece
+                    uint32_t w0, none = 0;
+                    r += stride;
+                    fetch(r, 0, w0, none);
+                    c = (c & ((1u << bits) - 1u)) | (codes_of(w0, 0, 0) << bits);
+                }
             }
-            const uint32_t c = uint32_t(codes);
             u32x4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
