@@ -33,8 +33,9 @@
 //  * Four forms.  The stream form (gemv_stream_kernel: K up to 8 slices per pass) gives a wave
 //    one slice for the whole kernel and a workgroup a run of consecutive tiles of one job, so
 //    activations are staged once and only weights move afterwards.  The lean form
-//    (gemv_lean_kernel) is the stream form cut down to the decode shapes (one pass over K, one
-//    block of 16 rows, one gamma, N a multiple of 16) and is what those launches run.  The
+//    (gemv_lean_kernel) is the stream form cut down to the decode shapes (K the same number of
+//    slices in every job or, in a second copy, several passes over K; one block of 16 rows, one
+//    gamma, N a multiple of 16) and is what those launches run.  The
 //    long-K form (gemv_longk_kernel) takes lone calls with 4096 < K <= 16384 whose workgroups
 //    get one or two tiles each: a wave walks its up to four slices with the next one's data
 //    already in flight.  The general form (gemv_kernel) loops a wave over slices and a
@@ -855,9 +856,9 @@ gemv_stream_kernel(GemvBatch b)
 }
 
 // ------------------------------------------------------------------------------------------
-// Lean stream kernel: the stream form for launches in which every job takes one pass over K with
-// the same number of 512-weight slices (= waves per workgroup), one block of at most 16
-// activation rows, one gamma, and N a multiple of 16 -- the decode shapes.  What differs from
+// Lean stream kernel: the stream form for launches in which every job has as many 512-weight
+// slices as the workgroup has waves, or (PASSES) more, one block of at most 16 activation
+// rows, one gamma, and N a multiple of 16 -- the decode shapes.  What differs from
 // gemv_stream_kernel is the way in and the loop, not the arithmetic:
 //  * Every workgroup has a 64-byte record of its own in the kernel arguments (pointers of its job,
 //    first tile and length of its run), read with one scalar load at an address that depends on
@@ -915,7 +916,12 @@ struct LeanOne {
     }
 };
 
-template <int T, class Args>
+// PASSES: jobs may have K beyond the waves' slices (the down projection among the linears of a block).  Such a job's run is
+// streamed once per NW slices; between passes the sums of the run wait in LDS (1 KB per tile behind the waves' areas)
+// with the thread that owns the output quad.  The last item of a pass asks for the next pass's first weights; the
+// activations follow once every wave has left the sums of that item, which share LDS with them.  Waves past the last
+// slice of the last pass multiply zeros.
+template <int T, bool PASSES, class Args>
 __global__ void __launch_bounds__(512)
 gemv_lean_kernel(Args b)
 {
@@ -936,11 +942,13 @@ gemv_lean_kernel(Args b)
     const int lr = lane >> 3, lc = lane & 7;   // load mapping: row of the half tile, chunk of the slice
     const int mi = lane & 15, mg = lane >> 4;  // MFMA mapping: row / activation column, k group
 
-    // ---- activations of this wave's slice: LDS-DMA, swizzled (lane l fetches piece l ^ (r & 7) of row r)
-    {
+    const int slices = (K + kSliceK - 1) / kSliceK;
+    const int n_pass = PASSES ? (slices + NW - 1) / NW : 1;
+    // ---- activations of a slice: LDS-DMA, swizzled (lane l fetches piece l ^ (r & 7) of row r)
+    auto stage_x = [&](int slice) {
         const size_t row_stride = size_t(K) * 2;
-        gbytes src = (gbytes)(R.x + size_t(wave) * (kSliceK * 2));
-        if ((wave + 1) * kSliceK <= K) {                    // the whole slice lies inside K
+        gbytes src = (gbytes)(R.x + size_t(slice) * (kSliceK * 2));
+        if ((slice + 1) * kSliceK <= K) {                   // the whole slice lies inside K
             const uint32_t lane16 = uint32_t(lane) << 4;
 #pragma unroll 1
             for (int r = 0; r < rows; ++r) {
@@ -952,7 +960,7 @@ gemv_lean_kernel(Args b)
 #pragma unroll 1
             for (int r = 0; r < rows; ++r) {
                 const int kk = (lane ^ (r & 7)) << 3;      // first of this lane's 8 activations within the slice
-                if (wave * kSliceK + kk < K) {
+                if (slice * kSliceK + kk < K) {
                     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + uint32_t(kk) * 2u),
                                                      (__attribute__((address_space(3))) void*)(my_lds + r * 1024), 16, 0, 0);
                 } else {
@@ -961,12 +969,16 @@ gemv_lean_kernel(Args b)
                 src += row_stride;
             }
         }
-    }
+    };
+    stage_x(wave);
     // ---- weights: the lane's two 16-byte pieces of a tile, relative to the tile's first row
-    uint32_t chunk = uint32_t(wave) * 8u + uint32_t(lc);
-    if (chunk >= (uint32_t(K) >> 6)) chunk = 0;            // past K: multiplied by zero activations
-    const uint32_t voff0 = uint32_t(lr) * row_bytes + chunk * 16u;
-    const uint32_t voff1 = voff0 + 8u * row_bytes;
+    auto offset_of = [&](int slice) {
+        uint32_t chunk = uint32_t(slice) * 8u + uint32_t(lc);
+        if (chunk >= (uint32_t(K) >> 6)) chunk = 0;        // past K: multiplied by zero activations
+        return uint32_t(lr) * row_bytes + chunk * 16u;
+    };
+    uint32_t voff0 = offset_of(wave);
+    uint32_t voff1 = voff0 + 8u * row_bytes;
     // the run as a raw buffer (no stride, byte offsets, size = the run): base in scalar registers
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Wrun), 0, uint32_t(ntiles) * tile_bytes, 0x00020000);
     u32x4 wreg[T][2];
@@ -991,14 +1003,15 @@ gemv_lean_kernel(Args b)
 
     // ---- activations -> MFMA B operands (see gemv_stream_kernel) and the -sum(x) seed ----------
     uint32_t breg[2][4][8];
-    f32x4 nsx = f32x4{0.f, 0.f, 0.f, 0.f};
-    {
+    f32x4 nsx;
+    auto build = [&](bool active) {
+        nsx = f32x4{0.f, 0.f, 0.f, 0.f};
         int mr = 1;
         while (mr < rows) mr *= 2;
         const int xrow = mi & (mr - 1);
         const uint32_t xr_off = uint32_t(xrow) * 1024u + uint32_t(mg) * 128u;
         const uint32_t sw = uint32_t(xrow & 7);
-        const bool live = mi < rows;
+        const bool live = mi < rows && (!PASSES || active);
         const uint32_t sel_lo = live ? 0x05040100u : 0x0c0c0c0cu;
         const uint32_t sel_hi = live ? 0x07060302u : 0x0c0c0c0cu;
 #pragma unroll
@@ -1022,7 +1035,8 @@ gemv_lean_kernel(Args b)
                 const u32x4 bb = u32x4{breg[h][0][e], breg[h][1][e], breg[h][2][e], breg[h][3][e]};
                 nsx = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), nsx, 0, 0, 0);
             }
-    }
+    };
+    build(true);
 
     const uint32_t ww_off = uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
     const uint32_t wr_off0 = uint32_t(mi) * 128u + (uint32_t((mg) ^ (mi & 7)) << 4);
@@ -1036,9 +1050,11 @@ gemv_lean_kernel(Args b)
 
     // One item of NT tiles starting at tile `first` of the run.  REFILL: each tile's registers are
     // loaded again at once with the tile T further on.
-    auto item = [&](auto nt_tag, auto refill_tag, int first, int parity) {
+    // REFILL 2 (PASSES): with the first tiles of the next pass, to whose slice the offsets have been moved.
+    unsigned char* const ysum = lds_raw + NW * kStride;
+    auto item = [&](auto nt_tag, auto refill_tag, int first, int parity, bool first_pass, bool last_pass) {
         constexpr int NT = decltype(nt_tag)::value;
-        constexpr bool REFILL = decltype(refill_tag)::value;
+        constexpr int REFILL = decltype(refill_tag)::value;
         f32x4 part[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -1046,11 +1062,11 @@ gemv_lean_kernel(Args b)
             // Writing a tile to LDS and asking for the tile that takes its registers is a handful
             // of LDS, scalar and memory instructions; they run at raised priority so that they do
             // not queue behind the other wave's decode (measured: decode sweep 17.55 -> 17.2 us).
-            if constexpr (REFILL) __builtin_amdgcn_s_setprio(3);
+            if constexpr (REFILL != 0) __builtin_amdgcn_s_setprio(3);
             *reinterpret_cast<u32x4*>(reg_t + ww_off) = wreg[t][0];
             *reinterpret_cast<u32x4*>(reg_t + 1024 + ww_off) = wreg[t][1];
-            if constexpr (REFILL) {
-                issue_w(first + T + t, t);
+            if constexpr (REFILL != 0) {
+                issue_w(REFILL == 2 ? t : first + T + t, t);
                 __builtin_amdgcn_s_setprio(0);
                 // the requests leave here, as soon as the registers are free: left to itself the
                 // scheduler sinks all of an item's loads to its end, which costs two tiles of lead
@@ -1080,6 +1096,10 @@ gemv_lean_kernel(Args b)
             part[t] = __builtin_elementwise_fma(__builtin_elementwise_fma(acc[0], f32x4{4.f, 4.f, 4.f, 4.f}, acc[1]),
                                                 f32x4{4.f, 4.f, 4.f, 4.f}, acc[2]);
         }
+        if constexpr (REFILL == 2) {
+#pragma unroll
+            for (int t = NT; t < T; ++t) issue_w(t, t);
+        }
         // split-K: partial sums into this wave's set `parity`, one LDS-only barrier, fixed-order sum
         unsigned char* const red = my_lds + 4096 + parity * (T * 1024);
 #pragma unroll
@@ -1092,8 +1112,13 @@ gemv_lean_kernel(Args b)
             for (int w = 0; w < 8; ++w)
                 v[w] = (w < NW) ? reinterpret_cast<const f32x4*>(lds_raw + w * kStride + 4096 + parity * (T * 1024) + ot * 1024)[lane]
                                 : f32x4{0.f, 0.f, 0.f, 0.f};
-            const f32x4 s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-            if (mi < rows) {
+            f32x4 s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+            if constexpr (PASSES) {
+                f32x4* const keep = reinterpret_cast<f32x4*>(ysum + (first + ot) * 1024) + lane;
+                if (!first_pass) s += *keep;
+                if (!last_pass) *keep = s;
+            }
+            if (mi < rows && (!PASSES || last_pass)) {
                 const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
                 const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
                 *(__attribute__((address_space(1))) u32x2*)(yrow + (ycol + 16u * uint32_t(first + ot))) =
@@ -1103,13 +1128,43 @@ gemv_lean_kernel(Args b)
     };
 
     const int n_items = (ntiles + T - 1) / T;
-    int i = 0;
-    for (; i + 1 < n_items; ++i)
-        item(std::integral_constant<int, T>{}, std::true_type{}, i * T, i & 1);
-    const int rem = ntiles - i * T;                        // 1 .. T tiles are left
-    if (T == 1 || rem == 1) item(std::integral_constant<int, 1>{}, std::false_type{}, i * T, i & 1);
-    else if (T == 2 || rem == 2) item(std::integral_constant<int, (T >= 2 ? 2 : 1)>{}, std::false_type{}, i * T, i & 1);
-    else item(std::integral_constant<int, T>{}, std::false_type{}, i * T, i & 1);
+    typedef std::integral_constant<int, 0> None;
+    typedef std::integral_constant<int, 1> Refill;
+    typedef std::integral_constant<int, 2> NextPass;
+    typedef std::integral_constant<int, 1> N1;
+    typedef std::integral_constant<int, (T >= 2 ? 2 : 1)> N2;
+    typedef std::integral_constant<int, T> NT;
+    auto last_item = [&](auto refill, int i, bool first_pass, bool last_pass) {
+        const int rem = ntiles - i * T;                    // 1 .. T tiles are left
+        if (T == 1 || rem == 1) item(N1{}, refill, i * T, i & 1, first_pass, last_pass);
+        else if (T == 2 || rem == 2) item(N2{}, refill, i * T, i & 1, first_pass, last_pass);
+        else item(NT{}, refill, i * T, i & 1, first_pass, last_pass);
+    };
+    if constexpr (!PASSES) {
+        int i = 0;
+        for (; i + 1 < n_items; ++i) item(NT{}, Refill{}, i * T, i & 1, true, true);
+        last_item(None{}, i, true, true);
+    } else {
+        for (int pass = 0; pass < n_pass; ++pass) {
+            const bool first_pass = pass == 0, last_pass = pass + 1 == n_pass;
+            int i = 0;
+            for (; i + 1 < n_items; ++i) item(NT{}, Refill{}, i * T, i & 1, first_pass, last_pass);
+            if (last_pass) {
+                last_item(None{}, i, first_pass, true);
+            } else {
+                const int slice = (pass + 1) * NW + wave;
+                voff0 = offset_of(slice);
+                voff1 = voff0 + 8u * row_bytes;
+                last_item(NextPass{}, i, first_pass, false);
+                // the activations land where other waves may still be reading this item's sums
+                __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
+                __builtin_amdgcn_s_barrier();
+                if (slice < slices) stage_x(slice);
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
+                build(slice < slices);
+            }
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1430,29 +1485,32 @@ constexpr int kStreamMaxRun = 32;       // tiles of a run whose sums fit the 32 
 template <class Args>
 using LeanFn = void (*)(Args);
 
-template <class Args>
+template <class Args, bool PASSES>
 LeanFn<Args> pick_lean(int T)
 {
     switch (T) {
-        case 1: return gemv_lean_kernel<1, Args>;
-        case 2: return gemv_lean_kernel<2, Args>;
-        default: return gemv_lean_kernel<3, Args>;
+        case 1: return gemv_lean_kernel<1, PASSES, Args>;
+        case 2: return gemv_lean_kernel<2, PASSES, Args>;
+        default: return gemv_lean_kernel<3, PASSES, Args>;
     }
 }
 
-template <class Args>
-hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, hipStream_t s)
+constexpr int lean_lds(bool passes) { return 8 * stream_wave_lds(3) + (passes ? kStreamMaxRun * 1024 : 0); }
+
+// kept: tiles of the longest run of a job of several passes
+template <bool PASSES, class Args>
+hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept, hipStream_t s)
 {
-    const LeanFn<Args> fn = pick_lean<Args>(T);
+    const LeanFn<Args> fn = pick_lean<Args, PASSES>(T);
     static bool lds_raised[kMaxDevices][4];
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][T]) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(PASSES));
         if (e != hipSuccess) return e;
         if (dev >= 0) lds_raised[dev][T] = true;
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(NW * 64), size_t(NW) * stream_wave_lds(T), s, args);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(NW * 64), size_t(NW) * stream_wave_lds(T) + size_t(kept) * 1024, s, args);
     return hipGetLastError();
 }
 
@@ -1464,11 +1522,11 @@ LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int 
 
 // Launch of the lean kernel: wg[j] workgroups for job j, each with a run of consecutive tiles
 // (the first tiles % wg[j] of them one tile longer), written out as one record per workgroup.
-hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, hipStream_t s)
+hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, hipStream_t s)
 {
-    if (b.count == 1) {
+    if (b.count == 1 && kept == 0) {
         const GemvJob& J = b.job[0];
-        return launch_lean_args(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0]), wg[0], NW, T, s);
+        return launch_lean_args<false>(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0]), wg[0], NW, T, 0, s);
     }
     LeanBatch lb;
     int grid = 0;
@@ -1488,7 +1546,7 @@ hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, hipStre
             r.pad[0] = r.pad[1] = r.pad[2] = r.pad[3] = 0;
         }
     }
-    return launch_lean_args(lb, grid, NW, T, s);
+    return kept ? launch_lean_args<true>(lb, grid, NW, T, kept, s) : launch_lean_args<false>(lb, grid, NW, T, 0, s);
 }
 
 template <class Args>
@@ -1618,15 +1676,18 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
         if (T < 1) return hipErrorInvalidValue;
     }
     if (T < 1) T = 1;
-    // The lean kernel takes the launch when every job has the same number of slices (one per wave),
-    // N is a multiple of 16 throughout and the workgroups fit its record table.
-    bool lean = pol.lean && !multi_pass && nb == 1 && gs == 0 && T <= 3;
-    int total_groups = 0;
+    // The lean kernel takes the launch when every job has at least one slice per wave (more: several passes), N is a
+    // multiple of 16 throughout and the workgroups fit its record table.  (The linears of a block, K = 4096 three times
+    // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
+    bool lean = pol.lean && nb == 1 && gs == 0 && T <= 3;
+    int total_groups = 0, kept = 0;
     for (int j = 0; j < b.count; ++j) {
-        lean = lean && b.job[j].slices == NW && (b.job[j].N & 15) == 0;
+        lean = lean && b.job[j].slices >= NW && (b.job[j].N & 15) == 0;
         total_groups += wg[j];
+        const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
+        if (passes(j) > 1 && r > kept) kept = r;
     }
-    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, s);
+    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, s);
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;
     for (int j = 0; j < b.count; ++j) {
@@ -1749,8 +1810,9 @@ hipError_t gemv_init()
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= 3; ++T) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanBatch>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
-        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanOne>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * stream_wave_lds(3));
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanBatch, false>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(false));
+        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanBatch, true>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(true));
+        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanOne, false>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(false));
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= kTMax; ++T)
