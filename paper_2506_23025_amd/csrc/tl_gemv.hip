@@ -35,7 +35,7 @@
 //    activations are staged once and only weights move afterwards.  The lean form
 //    (gemv_lean_kernel) is the stream form cut down to the decode shapes (K the same number of
 //    slices in every job or, in a second copy, several passes over K; one block of 16 rows, one
-//    gamma, N a multiple of 16) and is what those launches run.  The
+//    gamma or scales of groups of 256s, N a multiple of 16) and is what those launches run.  The
 //    long-K form (gemv_longk_kernel) takes lone calls with 4096 < K <= 16384 whose workgroups
 //    get one or two tiles each: a wave walks its up to four slices with the next one's data
 //    already in flight.  The general form (gemv_kernel) loops a wave over slices and a
@@ -858,7 +858,7 @@ gemv_stream_kernel(GemvBatch b)
 // ------------------------------------------------------------------------------------------
 // Lean stream kernel: the stream form for launches in which every job has as many 512-weight
 // slices as the workgroup has waves, or (PASSES) more, one block of at most 16 activation
-// rows, one gamma, and N a multiple of 16 -- the decode shapes.  What differs from
+// rows, one gamma or (GS) scales for groups of 256s, and N a multiple of 16 -- the decode shapes.  What differs from
 // gemv_stream_kernel is the way in and the loop, not the arithmetic:
 //  * Every workgroup has a 64-byte record of its own in the kernel arguments (pointers of its job,
 //    first tile and length of its run), read with one scalar load at an address that depends on
@@ -882,7 +882,9 @@ struct WgRec {                    // 64 bytes; rec[blockIdx.x] is read with scal
     int K, N;
     int Mrem;                     // 1..16
     int tile0, ntiles;            // the run: tiles tile0 .. tile0 + ntiles - 1 of the job (ntiles >= 1)
-    int pad[4];
+    const unsigned char* sc;      // group scales [groups][N] fp16, and 1 / (scale units of 256 weights per group): unit u lies in
+    uint32_t group_inv;           // group (2 u group_inv) >> 32; see group_inverse
+    int pad;
 };
 static_assert(sizeof(WgRec) == 64, "one record per 64-byte line");
 
@@ -903,6 +905,8 @@ struct LeanOne {
     int K, N;
     int Mrem;
     int per, plus;
+    uint32_t group_inv;           // see WgRec
+    const unsigned char* sc;
     __device__ WgRec mine() const
     {
         const int g = int(blockIdx.x);
@@ -912,16 +916,22 @@ struct LeanOne {
         r.W = W + size_t(r.tile0) * (size_t(4) * size_t(K));          // 16 rows of K / 4 bytes
         r.x = x; r.y = y; r.gamma = gamma;
         r.K = K; r.N = N; r.Mrem = Mrem;
+        r.sc = sc; r.group_inv = group_inv;
         return r;
     }
 };
+static_assert(sizeof(LeanOne) == 64, "the arguments of a lone call");
 
 // PASSES: jobs may have K beyond the waves' slices (the down projection among the linears of a block).  Such a job's run is
 // streamed once per NW slices; between passes the sums of the run wait in LDS (1 KB per tile behind the waves' areas)
 // with the thread that owns the output quad.  The last item of a pass asks for the next pass's first weights; the
 // activations follow once every wave has left the sums of that item, which share LDS with them.  Waves past the last
 // slice of the last pass multiply zeros.
-template <int T, bool PASSES, class Args>
+// GS: group scales, groups of whole units of 256 weights (half a slice).  The halves of a tile are summed one after the
+// other in the same accumulators, each scaled by its group's scales of the lane's four output rows, which are
+// requested with the tile's weights.  Against the general form, groups of 256: block at M = 1 / 4 / 16 16.0 / 17.2 / 24.5 ->
+// 15.8 / 16.6 / 19.5 us, its jobs of one pass 11.7 / 12.3 / 13.7 -> 10.4 / 10.7 / 12.1, 4096 x 11008 alone 8.8 / 10.3 / 15.1 -> 7.7 / 8.2 / 10.9.
+template <int T, bool PASSES, bool GS, class Args>
 __global__ void __launch_bounds__(512)
 gemv_lean_kernel(Args b)
 {
@@ -971,6 +981,24 @@ gemv_lean_kernel(Args b)
         }
     };
     stage_x(wave);
+    constexpr int H = GS ? 2 : 1;
+    // GS: the job's scales from the run's first row as a raw buffer, the lane's rows in it, and the units' groups
+    const uint32_t last_unit = uint32_t(K - 1) >> 8;
+    auto group_of = [&](uint32_t u) {                      // a product: two divisions would stand before the first request
+        return uint32_t((uint64_t(2u * (u < last_unit ? u : last_unit)) * R.group_inv) >> 32);   // past K: the last one (its activations are zeros)
+    };
+    const __amdgpu_buffer_rsrc_t sres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char*>(R.sc) + size_t(R.tile0) * 32u, 0,
+        GS ? (group_of(last_unit) + 1u) * uint32_t(N) * 2u - uint32_t(R.tile0) * 32u : 0u, 0x00020000);
+    const uint32_t sc_lane = uint32_t(mg) * 8u;
+    uint32_t sc_unit[H] = {};
+    auto scales_of = [&](int slice) {
+        if constexpr (GS) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) sc_unit[h] = group_of(uint32_t(2 * slice + h)) * uint32_t(N) * 2u;
+        }
+    };
+    scales_of(wave);
     // ---- weights: the lane's two 16-byte pieces of a tile, relative to the tile's first row
     auto offset_of = [&](int slice) {
         uint32_t chunk = uint32_t(slice) * 8u + uint32_t(lc);
@@ -982,6 +1010,7 @@ gemv_lean_kernel(Args b)
     // the run as a raw buffer (no stride, byte offsets, size = the run): base in scalar registers
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Wrun), 0, uint32_t(ntiles) * tile_bytes, 0x00020000);
     u32x4 wreg[T][2];
+    u32x2 sreg[T][H];
     auto issue_w = [&](int idx, int t) {                   // idx: tile of the run; past the run: its last tile again
         const int c = idx < ntiles ? idx : ntiles - 1;
         // Buffer loads: descriptor and tile offset are scalar, the lane offset is a register that
@@ -991,6 +1020,11 @@ gemv_lean_kernel(Args b)
         const uint32_t so = uint32_t(c) * tile_bytes;
         wreg[t][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, voff0, so, 2));   // 2: nt
         wreg[t][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, voff1, so, 2));
+        if constexpr (GS) {
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+                sreg[t][h] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(sres, sc_lane, __builtin_amdgcn_readfirstlane(sc_unit[h] + uint32_t(c) * 32u), 0));
+        }
     };
     // in tile order, and kept so: the loop's wait counts are the worse of this order and its own
 #pragma unroll
@@ -998,14 +1032,15 @@ gemv_lean_kernel(Args b)
         issue_w(t, t);
         __builtin_amdgcn_sched_barrier(0);
     }
-    // the compiler does not track LDS-DMA: wait until only the 2T weight loads are outstanding
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * T));
+    // the compiler does not track LDS-DMA: wait until only the weight (and scale) loads are outstanding
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((GS ? 4 : 2) * T));
 
     // ---- activations -> MFMA B operands (see gemv_stream_kernel) and the -sum(x) seed ----------
     uint32_t breg[2][4][8];
-    f32x4 nsx;
+    f32x4 nsx[H];
     auto build = [&](bool active) {
-        nsx = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int h = 0; h < H; ++h) nsx[h] = f32x4{0.f, 0.f, 0.f, 0.f};
         int mr = 1;
         while (mr < rows) mr *= 2;
         const int xrow = mi & (mr - 1);
@@ -1033,7 +1068,7 @@ gemv_lean_kernel(Args b)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const u32x4 bb = u32x4{breg[h][0][e], breg[h][1][e], breg[h][2][e], breg[h][3][e]};
-                nsx = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), nsx, 0, 0, 0);
+                nsx[GS ? h : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), nsx[GS ? h : 0], 0, 0, 0);
             }
     };
     build(true);
@@ -1041,7 +1076,7 @@ gemv_lean_kernel(Args b)
     const uint32_t ww_off = uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
     const uint32_t wr_off0 = uint32_t(mi) * 128u + (uint32_t((mg) ^ (mi & 7)) << 4);
     const uint32_t wr_off1 = uint32_t(mi) * 128u + (uint32_t((4 + mg) ^ (mi & 7)) << 4);
-    const float gamma = R.gamma * 65536.f;               // times the 2^16 left in the partial sums
+    const float gamma = GS ? 65536.f : R.gamma * 65536.f;               // times the 2^16 left in the partial sums
     typedef __attribute__((address_space(1))) __half* gh_ptr;
     // the output quad this thread owns in an item's epilogue: tile t = threadIdx.x / 64 of the item
     const int ot = int(threadIdx.x) >> 6;
@@ -1052,6 +1087,7 @@ gemv_lean_kernel(Args b)
     // loaded again at once with the tile T further on.
     // REFILL 2 (PASSES): with the first tiles of the next pass, to whose slice the offsets have been moved.
     unsigned char* const ysum = lds_raw + NW * kStride;
+    bool idle = false;                                     // this wave has no slice in this pass
     auto item = [&](auto nt_tag, auto refill_tag, int first, int parity, bool first_pass, bool last_pass) {
         constexpr int NT = decltype(nt_tag)::value;
         constexpr int REFILL = decltype(refill_tag)::value;
@@ -1065,6 +1101,17 @@ gemv_lean_kernel(Args b)
             if constexpr (REFILL != 0) __builtin_amdgcn_s_setprio(3);
             *reinterpret_cast<u32x4*>(reg_t + ww_off) = wreg[t][0];
             *reinterpret_cast<u32x4*>(reg_t + 1024 + ww_off) = wreg[t][1];
+            u32x2 sc_cur[H];
+            if constexpr (GS) {
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    // This tile's scales are taken over here, before the refill replaces them: left to itself the compiler
+                    // copies those of all tiles at the head of the loop and waits for every request of the item there
+                    // (block at M = 4 17.0 -> 16.6 us).
+                    sc_cur[h] = sreg[t][h];
+                    asm volatile("" : "+v"(sc_cur[h]));
+                }
+            }
             if constexpr (REFILL != 0) {
                 issue_w(REFILL == 2 ? t : first + T + t, t);
                 __builtin_amdgcn_s_setprio(0);
@@ -1087,14 +1134,23 @@ gemv_lean_kernel(Args b)
                     const u32x4 a = sh[src] & mask;
                     const u32x4 bb = u32x4{breg[h][0][e], breg[h][1][e], breg[h][2][e], breg[h][3][e]};
                     // first product of an accumulator: class 0 starts from the -sum(x) seed, the others from zero
-                    const f32x4 c0 = (h == 0 && (e == 0 || e == 1 || e == 4)) ? (j == 0 ? nsx : f32x4{0.f, 0.f, 0.f, 0.f}) : acc[j];
+                    const f32x4 c0 = ((GS || h == 0) && (e == 0 || e == 1 || e == 4)) ? (j == 0 ? nsx[GS ? h : 0] : f32x4{0.f, 0.f, 0.f, 0.f}) : acc[j];
                     acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), c0, 0, 0, 0);
+                }
+                if constexpr (GS) {
+                    // register r of the accumulator is output row 4 (lane / 16) + r of the tile
+                    const f16x4 sh4 = __builtin_bit_cast(f16x4, sc_cur[h]);
+                    const f32x4 sc = {float(sh4[0]), float(sh4[1]), float(sh4[2]), float(sh4[3])};
+                    const f32x4 sum = __builtin_elementwise_fma(__builtin_elementwise_fma(acc[0], f32x4{4.f, 4.f, 4.f, 4.f}, acc[1]),
+                                                                f32x4{4.f, 4.f, 4.f, 4.f}, acc[2]);
+                    part[t] = h == 0 ? sc * sum : __builtin_elementwise_fma(sc, sum, part[t]);
                 }
             }
             // the three classes carry 2^-20, 2^-18 and 2^-16: two fused multiply-adds leave the sum at
             // 2^-16, and that power of two goes into the scale of the epilogue (exact, same roundings)
-            part[t] = __builtin_elementwise_fma(__builtin_elementwise_fma(acc[0], f32x4{4.f, 4.f, 4.f, 4.f}, acc[1]),
-                                                f32x4{4.f, 4.f, 4.f, 4.f}, acc[2]);
+            if constexpr (!GS)
+                part[t] = __builtin_elementwise_fma(__builtin_elementwise_fma(acc[0], f32x4{4.f, 4.f, 4.f, 4.f}, acc[1]),
+                                                    f32x4{4.f, 4.f, 4.f, 4.f}, acc[2]);
         }
         if constexpr (REFILL == 2) {
 #pragma unroll
@@ -1103,7 +1159,8 @@ gemv_lean_kernel(Args b)
         // split-K: partial sums into this wave's set `parity`, one LDS-only barrier, fixed-order sum
         unsigned char* const red = my_lds + 4096 + parity * (T * 1024);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) reinterpret_cast<f32x4*>(red + t * 1024)[lane] = part[t];
+        for (int t = 0; t < NT; ++t)                       // an idle wave's zeros may have met an infinite scale
+            reinterpret_cast<f32x4*>(red + t * 1024)[lane] = (GS && PASSES && idle) ? f32x4{0.f, 0.f, 0.f, 0.f} : part[t];
         __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
         __builtin_amdgcn_s_barrier();
         if (ot < NT) {
@@ -1155,13 +1212,15 @@ gemv_lean_kernel(Args b)
                 const int slice = (pass + 1) * NW + wave;
                 voff0 = offset_of(slice);
                 voff1 = voff0 + 8u * row_bytes;
+                scales_of(slice);
                 last_item(NextPass{}, i, first_pass, false);
                 // the activations land where other waves may still be reading this item's sums
                 __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
                 __builtin_amdgcn_s_barrier();
                 if (slice < slices) stage_x(slice);
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
-                build(slice < slices);
+                idle = slice >= slices;
+                build(!idle);
             }
         }
     }
@@ -1485,23 +1544,23 @@ constexpr int kStreamMaxRun = 32;       // tiles of a run whose sums fit the 32 
 template <class Args>
 using LeanFn = void (*)(Args);
 
-template <class Args, bool PASSES>
+template <class Args, bool PASSES, bool GS>
 LeanFn<Args> pick_lean(int T)
 {
     switch (T) {
-        case 1: return gemv_lean_kernel<1, PASSES, Args>;
-        case 2: return gemv_lean_kernel<2, PASSES, Args>;
-        default: return gemv_lean_kernel<3, PASSES, Args>;
+        case 1: return gemv_lean_kernel<1, PASSES, GS, Args>;
+        case 2: return gemv_lean_kernel<2, PASSES, GS, Args>;
+        default: return gemv_lean_kernel<3, PASSES, GS, Args>;
     }
 }
 
 constexpr int lean_lds(bool passes) { return 8 * stream_wave_lds(3) + (passes ? kStreamMaxRun * 1024 : 0); }
 
 // kept: tiles of the longest run of a job of several passes
-template <bool PASSES, class Args>
+template <bool PASSES, bool GS, class Args>
 hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept, hipStream_t s)
 {
-    const LeanFn<Args> fn = pick_lean<Args, PASSES>(T);
+    const LeanFn<Args> fn = pick_lean<Args, PASSES, GS>(T);
     static bool lds_raised[kMaxDevices][4];
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][T]) {
@@ -1514,19 +1573,39 @@ hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept,
     return hipGetLastError();
 }
 
-LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int K, int N, int rows, int tiles, int grid)
+template <class Args>
+hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept, bool gs, hipStream_t s)
+{
+    if (gs) return kept ? launch_lean_args<true, true>(args, grid, NW, T, kept, s) : launch_lean_args<false, true>(args, grid, NW, T, 0, s);
+    return kept ? launch_lean_args<true, false>(args, grid, NW, T, kept, s) : launch_lean_args<false, false>(args, grid, NW, T, 0, s);
+}
+
+// ceil(2^31 / units per group): u * inverse / 2^31 rounded down is u / hpg for every u and hpg up to 2^15 (the error of the
+// inverse, below 2^-31, times u stays below the 1 / hpg that is missing to the next whole number), and K holds at most
+// kStreamWaves kStreamMaxPasses slices.  A group longer than K is one group.
+uint32_t group_inverse(const GemvJob& J)
+{
+    if (J.scales == nullptr) return 0;
+    const int units = (J.K + 255) / 256;
+    const uint32_t hpg = uint32_t(J.hpg < units ? J.hpg : units);
+    return uint32_t(((uint64_t(1) << 31) + hpg - 1) / hpg);
+}
+static_assert(2 * kStreamWaves * kStreamMaxPasses <= 1 << 15, "group_inverse");
+
+LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int K, int N, int rows, int tiles, int grid,
+                const __half* scales = nullptr, uint32_t group_inv = 0)
 {
     return LeanOne{reinterpret_cast<const unsigned char*>(W), reinterpret_cast<const unsigned char*>(x), y, gamma, K, N, rows,
-                   tiles / grid, tiles % grid};
+                   tiles / grid, tiles % grid, group_inv, reinterpret_cast<const unsigned char*>(scales)};
 }
 
 // Launch of the lean kernel: wg[j] workgroups for job j, each with a run of consecutive tiles
 // (the first tiles % wg[j] of them one tile longer), written out as one record per workgroup.
-hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, hipStream_t s)
+hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, bool gs, hipStream_t s)
 {
-    if (b.count == 1 && kept == 0) {
+    if (b.count == 1) {
         const GemvJob& J = b.job[0];
-        return launch_lean_args<false>(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0]), wg[0], NW, T, 0, s);
+        return launch_lean_args(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0], J.scales, group_inverse(J)), wg[0], NW, T, kept, gs, s);
     }
     LeanBatch lb;
     int grid = 0;
@@ -1534,6 +1613,7 @@ hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kep
         const GemvJob& J = b.job[j];
         const int per = J.tiles / wg[j], plus = J.tiles % wg[j];
         const size_t tile_bytes = size_t(16) * (size_t(J.K) / 4);
+        const uint32_t inv = group_inverse(J);
         for (int g = 0; g < wg[j]; ++g) {
             WgRec& r = lb.rec[grid++];
             r.tile0 = g * per + (g < plus ? g : plus);
@@ -1543,10 +1623,11 @@ hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kep
             r.y = J.y;
             r.gamma = J.gamma;
             r.K = J.K; r.N = J.N; r.Mrem = J.Mrem;
-            r.pad[0] = r.pad[1] = r.pad[2] = r.pad[3] = 0;
+            r.sc = reinterpret_cast<const unsigned char*>(J.scales);
+            r.group_inv = inv; r.pad = 0;
         }
     }
-    return kept ? launch_lean_args<true>(lb, grid, NW, T, kept, s) : launch_lean_args<false>(lb, grid, NW, T, 0, s);
+    return launch_lean_args(lb, grid, NW, T, kept, gs, s);
 }
 
 template <class Args>
@@ -1611,7 +1692,7 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
                 r.gamma = d.gamma;
                 r.K = int(d.K); r.N = int(d.N);
                 r.Mrem = int(d.M - m0 < 16 ? d.M - m0 : 16);
-                r.pad[0] = r.pad[1] = r.pad[2] = r.pad[3] = 0;
+                r.sc = nullptr; r.group_inv = 0; r.pad = 0;
             }
         }
     }
@@ -1677,9 +1758,10 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     }
     if (T < 1) T = 1;
     // The lean kernel takes the launch when every job has at least one slice per wave (more: several passes), N is a
-    // multiple of 16 throughout and the workgroups fit its record table.  (The linears of a block, K = 4096 three times
+    // multiple of 16 throughout, scales if any for groups of whole 256s (units of 128 would need every product twice and the
+    // registers of twice the sums) and the workgroups fit its record table.  (The linears of a block, K = 4096 three times
     // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
-    bool lean = pol.lean && nb == 1 && gs == 0 && T <= 3;
+    bool lean = pol.lean && nb == 1 && gs != 4 && T <= 3;
     int total_groups = 0, kept = 0;
     for (int j = 0; j < b.count; ++j) {
         lean = lean && b.job[j].slices >= NW && (b.job[j].N & 15) == 0;
@@ -1687,7 +1769,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
         if (passes(j) > 1 && r > kept) kept = r;
     }
-    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, s);
+    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs != 0, s);
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;
     for (int j = 0; j < b.count; ++j) {
@@ -1810,9 +1892,19 @@ hipError_t gemv_init()
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= 3; ++T) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanBatch, false>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(false));
-        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanBatch, true>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(true));
-        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_lean<LeanOne, false>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(false));
+        hipError_t e = hipSuccess;
+        auto raise_lean = [&](auto gs_tag) {
+            constexpr bool GS = decltype(gs_tag)::value;
+            auto raise_one = [&](const void* fn, bool passes) {
+                if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(passes));
+            };
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS>(T)), true);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, false, GS>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, true, GS>(T)), true);
+        };
+        raise_lean(std::false_type{});
+        raise_lean(std::true_type{});
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= kTMax; ++T)

@@ -1,4 +1,4 @@
-"""Decode launches: single calls with one job's arguments, at the edges of their split into runs of tiles, and groups with long K."""
+"""Decode launches: single calls with one job's arguments, at the edges of their split into runs of tiles, and groups with long K and with group scales."""
 import numpy as np
 import pytest
 
@@ -54,3 +54,37 @@ def test_grouped_calls_with_long_k(M, sizes):
         y = yd.cpu().numpy().view(np.float16)
         assert np.isfinite(y).all()
         assert_close(y[:, cols], ref, x, g, f"long K in a group {M}x{N}x{K}")
+
+
+# scales per group of a multiple of 256 weights, N a multiple of 16: groups of half a slice, of one and one and a half slices, of all of K,
+# with and without several passes, alone and in a group; one to three tiles in the last item
+@pytest.mark.parametrize("M,sizes,group", [(4, [(4096, 4096)] * 2 + [(4096, 11008)], 256), (1, [(1040, 4096), (8208, 4672)], 768), (16, [(16400, 8192)], 512),
+                                           (5, [(16, 4096)], 4096), (3, [(4112, 1024), (12304, 1024)], 256), (2, [(2064, 4160)], 256)])
+def test_decode_with_group_scales(M, sizes, group):
+    jobs, want = [], []
+    for i, (N, K) in enumerate(sizes):
+        x, W, _ = si.layer(37000 + M + i + N + K, M, N, K)
+        sc = si.group_scales(np.random.default_rng(N + K), (K + group - 1) // group, N)
+        yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+        jobs.append((to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), to_dev(sc.view(np.int16)), group, yd, M, N, K))
+        cols = np.unique(np.r_[0:16, N - 16:N, np.random.default_rng(N).choice(N, min(N, 200), replace=False)])
+        want.append((yd, cols, oracle.gemm_packed2_group_scales(x, tl.tl_pack_2bit(np.ascontiguousarray(W[cols])),
+                                                                np.ascontiguousarray(sc[:, cols]), group, K), x, float(sc.max())))
+    tl.tl_ternary_gemm_gs_grouped(jobs)
+    for (yd, cols, ref, x, g), (N, K) in zip(want, sizes):
+        y = yd.cpu().numpy().view(np.float16)
+        assert np.isfinite(y).all()
+        assert_close(y[:, cols], ref, x, g, f"group scales {M}x{N}x{K} / {group}")
+
+
+def test_an_infinite_group_scale_stays_in_its_output():
+    # K of nine slices: waves without a slice in the second pass must not turn their zeros into NaN
+    M, N, K, group = 1, 2048, 4608, 4608
+    x, W, _ = si.layer(38001, M, N, K)
+    x, W[100] = np.abs(x), 1                               # every partial sum of the column is positive
+    sc = si.group_scales(np.random.default_rng(5), 1, N)
+    sc[0, 100] = np.inf
+    yd = to_dev(np.zeros((M, N), dtype=np.int16))
+    tl.tl_ternary_gemm_gs(to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), to_dev(sc.view(np.int16)), group, yd, M, N, K)
+    y = yd.cpu().numpy().view(np.float16)[0]
+    assert np.isinf(y[100]) and np.isfinite(np.delete(y, 100)).all()
