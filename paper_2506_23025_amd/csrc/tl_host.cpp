@@ -33,7 +33,7 @@ inline uint64_t not_digits(uint64_t d) { return (d & (kOnes * 0xFC)) | (d & (d >
 
 // `whole` packed words of 16 weights; returns nonzero if a value was no weight.  The 2-bit fields of eight bytes are drawn
 // together in three steps.  A copy for AVX2, four loads to an instruction, is taken where the CPU has it (4096 x 4096
-// on this code's build machine: one weight at a time 12.6 ms, eight 3.0 ms, with AVX2 1.6 ms).
+// on one core of a server: one weight at a time 12.6 ms, eight 3.0 ms, with AVX2 1.6 ms).
 inline __attribute__((always_inline)) uint64_t pack_words(const int8_t* row, uint32_t* dst, int64_t whole) {
     uint64_t off = 0;
     for (int64_t i = 0; i < whole; ++i) {
