@@ -402,10 +402,10 @@ def main():
         st = timed(lambda: launch_prefill(M), reps)
         us = per_unit(st, reps)[0]
         fl = 2.0 * M * pre_N * K
-        which = {tl.TL_PATH_GEMV: "small-M kernel", tl.TL_PATH_MFMA: "mfma_kernel",
+        which = {tl.TL_PATH_GEMV: "small-M kernel", tl.TL_PATH_MFMA: "tile_kernel",
                  tl.TL_PATH_GENERIC: "generic kernel"}[tl.tl_ternary_gemm_which(M, pre_N, K)]
-        us_auto = us if which == "mfma_kernel" else per_unit(timed(lambda: launch_prefill(M, tl.TL_PATH_AUTO), reps), reps)[0]
-        prefill.append(dict(layer=pre_name, M=M, N=pre_N, K=K, kernel="mfma_kernel", **us_row(st, reps),
+        us_auto = us if which == "tile_kernel" else per_unit(timed(lambda: launch_prefill(M, tl.TL_PATH_AUTO), reps), reps)[0]
+        prefill.append(dict(layer=pre_name, M=M, N=pre_N, K=K, kernel="tile_kernel", **us_row(st, reps),
                             TFLOPs=round(fl / us / 1e6, 1), mfma_frac=round(fl / us / 1e6 / MFMA_PEAK_TFLOPS, 4),
                             kernel_vs_mfma_probe=round(fl / us / 1e6 / mfma_probe["TFLOPs"], 4),
                             tl_ternary_gemm=dict(kernel=which, us=round(us_auto, 2), TFLOPs=round(fl / us_auto / 1e6, 1),

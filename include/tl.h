@@ -60,7 +60,7 @@ typedef enum tl_path {
     TL_PATH_AUTO = 0,
     TL_PATH_GENERIC = 1, /* plain VALU kernel, any M, N, K                        */
     TL_PATH_GEMV = 2,    /* weight-streaming small-M kernel: M <= 16 per pass     */
-    TL_PATH_MFMA = 3,    /* LDS-tiled fp16 MFMA prefill kernel                    */
+    TL_PATH_MFMA = 3,    /* tiled fp16 MFMA kernel for many rows                 */
     TL_PATH_INT_RANGE_ = 0x7fffffff /* not a path (see TL_FMT_INT_RANGE_)         */
 } tl_path;
 
