@@ -74,8 +74,10 @@ bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
         if (M <= 16) return false;
         const double w_mb = double(N) * double(K) / 4.0e6;
         const double passes = double((K + 4095) / 4096);
-        // a band: near the crossover the models are within that of each other
-        return 1.08 * us < 4.6 + 6.0 * (passes - 1.0) + blocks * (0.1 + (group % 256 == 0 ? 0.18 : 0.31) * w_mb);
+        // no band for the streaming kernel: measured at M = 32 to 256 over five layers, groups of 128 and 256, this line loses
+        // nothing, and a band of 8 % kept 4096 -> 14336 at M = 192 (groups of 256) at 39.4 us instead of 32.3, 11008 -> 4096
+        // at M = 64 (groups of 128) at 33.5 instead of 24.4
+        return us < 4.6 + 6.0 * (passes - 1.0) + blocks * (0.1 + (group % 256 == 0 ? 0.18 : 0.31) * w_mb);
     }
     const double groups = blocks * double((N + 15) / 16) / 512.0;
     return us < 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
