@@ -327,11 +327,16 @@ tile_kernel(TileParams p)
         uint32_t e[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) e[b] = table[(raw[b >> 2] >> (8 * (b & 3))) & 255u];
-        if (!decltype(inside)::value && (s + 1) * (C::CH * 16) > nbytes) {   // bytes past the row count as weight 0
+        if (!decltype(inside)::value && (s + 1) * (C::CH * 16) >= nbytes) {
+            // Bytes past the row count as weight 0, and so do the last byte's digits past K, whatever they are: X holds the
+            // row's first activations there and not zeros.
             const int b0 = (s * C::CH + ch) * 16 + half * 8;
+            const uint32_t keep = (1u << (2 * (K - (nbytes - 1) * 5))) - 1u;
 #pragma unroll
-            for (int b = 0; b < 8; ++b)
-                if (b0 + b >= nbytes) e[b] = 0x155u;
+            for (int b = 0; b < 8; ++b) {
+                const uint32_t m = b0 + b < nbytes - 1 ? ~0u : (b0 + b == nbytes - 1 ? keep : 0u);
+                e[b] = (e[b] & m) | (0x155u & ~m);
+            }
         }
         const uint32_t d0 = e[0] | (e[1] << 10) | (e[2] << 20) | (e[3] << 30);
         const uint32_t d1 = (e[3] >> 2) | (e[4] << 8) | (e[5] << 18) | (e[6] << 28);

@@ -130,3 +130,40 @@ def test_tile_odd_k_keeps_rows_apart():
     assert np.isfinite(y[clean]).all()
     assert_close(y[clean], oracle.gemm(x[clean], W, g), x[clean], g, "rows beside a NaN")
     assert np.isnan(y[7]).all()
+
+
+def _with_spare_digits(Wp, K, fx, digit):
+    """The packed rows with the digits past K of each row's last byte (the packers write 1) set to `digit`."""
+    nb, rem = -(-K // 5), K - 5 * (-(-K // 5) - 1)
+    P = Wp.copy()
+    last = P[:, nb - 1].astype(int)
+    if fx:                                                 # first weight: most significant digit
+        v = (last * 243 >> 8) // 3 ** (5 - rem) * 3 ** (5 - rem) + digit * ((3 ** (5 - rem) - 1) // 2)
+        last = (v * 256 + 242) // 243
+    else:                                                  # first weight: least significant digit
+        last = last % 3 ** rem + digit * ((3 ** 5 - 3 ** rem) // 2)
+    P[:, nb - 1] = last.astype(np.uint8)
+    return P
+
+
+# K of one to four weights in a row's last byte, that byte first, in the middle and last of what a step and a thread fetch; few rows,
+# which the streaming kernel takes, and many
+@pytest.mark.parametrize("fx", [False, True])
+@pytest.mark.parametrize("M,N,K", [(4, 600, 328), (500, 600, 328), (512, 4100, 4096), (60, 1030, 11008), (1030, 2050, 168), (700, 1100, 952),
+                                   (500, 1030, 104), (40, 70, 8)])
+def test_spare_digits_of_the_last_byte_do_not_count(M, N, K, fx):
+    x, W, g = si.layer(39000 + M + N + K, M, N, K)
+    Wp = tl.tl_pack_1p6bit_fx(W) if fx else tl.tl_pack_1p6bit(W)
+    xd, gb = to_dev(x.view(np.int16)), si.gamma_bits(g)
+
+    def product(packed):
+        yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+        (tl.tl_ternary_gemm_1p6_fx if fx else tl.tl_ternary_gemm_1p6)(xd, to_dev(packed), gb, yd, M, N, K)
+        return yd.cpu().numpy()
+
+    want = product(Wp)
+    for digit in (0, 2):
+        other = _with_spare_digits(Wp, K, fx, digit)
+        assert not np.array_equal(other, Wp)
+        assert np.array_equal(tl.tl_unpack(tl.TL_FMT_1P6BIT_FX if fx else tl.TL_FMT_1P6BIT, other, N, K), W)
+        assert np.array_equal(product(other), want), f"spare digits {digit}"
