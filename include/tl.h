@@ -223,7 +223,9 @@ tl_status tl_ternary_gemm_1p6_fx(const void* x, const void* Wpacked, uint16_t ga
  * scales held in a separate buffer).  `scales` is a device pointer to fp16
  * [ceil(K / group)][N], 16-byte aligned; the last group may be short.  x, Wpacked (2-bit
  * format), y, stream, accumulation and rounding as for tl_ternary_gemm.  `group` must be a
- * multiple of 16 (TL_ERR_SHAPE otherwise).  K % 64 == 0: few activation
+ * multiple of 16 (TL_ERR_SHAPE otherwise).  Scales are expected to be finite: an infinite one makes
+ * the outputs of its column infinite or NaN, a NaN makes them NaN, and neither shows in another column.
+ * K % 64 == 0: few activation
  * rows, group % 128 == 0 and N % 4 == 0 in the weight-streaming small-M kernel (M in blocks of 16
  * rows; multiples of 256 a little faster than odd multiples of 128), the rest in the tiled kernel,
  * except where so few rows make the generic kernel the faster one; other K likewise in the tiled or

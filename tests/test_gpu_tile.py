@@ -167,3 +167,35 @@ def test_spare_digits_of_the_last_byte_do_not_count(M, N, K, fx):
         assert not np.array_equal(other, Wp)
         assert np.array_equal(tl.tl_unpack(tl.TL_FMT_1P6BIT_FX if fx else tl.TL_FMT_1P6BIT, other, N, K), W)
         assert np.array_equal(product(other), want), f"spare digits {digit}"
+
+
+# An infinite scale makes the outputs of its column infinite, with the sign of scale times the group's sum, whatever the number of rows; a NaN
+# makes them NaN; the other columns do not notice.  Tiles that store 16 bytes, 8 bytes and single values, with sets of waves side
+# by side and not; K that ends inside a step.
+@pytest.mark.parametrize("M,N,K,group", [(4, 300, 1024, 128), (40, 300, 1024, 128), (1030, 8200, 192, 128), (1030, 8204, 192, 128), (2048, 3000, 192, 256),
+                                         (700, 9000, 704, 256), (300, 9004, 704, 128), (640, 2500, 1152, 384), (512, 4096, 1024, 128), (256, 4096, 512, 4096),
+                                         (129, 1030, 1088, 16)])
+def test_infinite_group_scales_with_many_rows(M, N, K, group):
+    rng = np.random.default_rng(39500 + M + N + K)
+    x, W, _ = si.layer(39500 + M + N + K, M, N, K)
+    x[:, :] = np.where(x == 0, np.float16(0.5), x)
+    s = si.group_scales(rng, -(-K // group), N)
+    last = s.shape[0] - 1
+    bad = {1: (0, np.inf), 64: (last, np.inf), 66: (last // 2, -np.inf), N - 1: (last, -np.inf), N - 30: (0, np.nan)}
+    for n, (gi, v) in bad.items():
+        s[gi, n] = v
+    yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+    tl.tl_ternary_gemm_gs(to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), to_dev(s.view(np.int16)), group, yd, M, N, K)
+    y = yd.cpu().numpy().view(np.float16)
+    for n, (gi, v) in bad.items():
+        k = slice(gi * group, min(K, (gi + 1) * group))
+        part = x[:, k].astype(np.float64) @ W[n, k].astype(np.float64)
+        if np.isnan(v):
+            assert np.isnan(y[:, n]).all()
+        else:
+            assert (part != 0).all()                       # none here: NaN
+            same = y[:, n].astype(np.float64) == np.sign(part) * v
+            assert same.all(), f"column {n}: rows {np.flatnonzero(~same)[:8]}"
+    cols = np.setdiff1d(_sampled(N, M), list(bad))
+    ref = oracle.gemm_group_scales(x, np.ascontiguousarray(W[cols]), np.ascontiguousarray(s[:, cols]), group)
+    assert_close(y[:, cols], ref, x, 0.05, f"beside infinite scales {M}x{N}x{K} group {group}")
