@@ -1,6 +1,7 @@
 // Device decode (byte-exact twin of the host decoders), the measurement probes (copy, read-only,
 // bare MFMA loop) and the generic VALU GEMMs that accept every shape.
 #include "tl_internal.hpp"
+#include "tl_unpack.hpp"
 
 namespace tl {
 
@@ -112,17 +113,12 @@ unpack_kernel(const unsigned char* __restrict__ packed, int64_t K, int64_t strid
         const int64_t f = f0 + (u * 256 + int(threadIdx.x)) * 16;
         if (whole[u]) {
             uint32_t c = codes_of(lo[u], hi[u], col[u]);
-            if (col[u] + 16u > Ku) {
-                uint32_t bits = 2u * (Ku - col[u]);                          // of this row's codes, 2 .. 30
-                c = (c & ((1u << bits) - 1u)) | (codes_of(nx[u], 0, 0) << bits);
-                const unsigned char* r = packed + (row[u] + 1) * stride;
-                while ((bits += 2u * Ku) < 32u) {                            // rows shorter than a piece
-                    uint32_t w0, none = 0;
-                    r += stride;
-                    fetch(r, 0, w0, none);
-                    c = (c & ((1u << bits) - 1u)) | (codes_of(w0, 0, 0) << bits);
-                }
-            }
+            if (col[u] + 16u > Ku)
+                c = join_rows(c, Ku - col[u], Ku, [&](int i) {
+                    uint32_t w0 = nx[u], none = 0;
+                    if (i > 1) fetch(packed + (row[u] + i) * stride, 0, w0, none);
+                    return codes_of(w0, 0, 0);
+                });
             u32x4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {

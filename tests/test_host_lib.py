@@ -256,6 +256,22 @@ def test_workgroup_allocator_invariants(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
 
 
+def test_unpacker_joins_rows_of_every_length(tmp_path):
+    # csrc/tl_unpack.hpp puts the pieces across a row's end together: right codes, no row asked for that the piece does not reach, for
+    # rows of 1 to 48 weights and of the 32 largest lengths (one more and 32 bits no longer hold a piece's end)
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++") or shutil.which("c++")
+    assert cxx, "no C++ compiler"
+    exe = str(tmp_path / "unpack_host")
+    cmd = [cxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "paper_2506_23025_amd", "csrc"),
+           os.path.join(ROOT, "tests", "c", "unpack_host.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
+
+
 def test_kernel_choice_is_a_pure_function_of_the_shape():
     # decode batch sizes stream the weights; the prefill sizes of the workloads use the tiled MFMA
     # kernel; shapes neither fast kernel takes fall back; invalid sizes give no path
