@@ -1582,12 +1582,11 @@ hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept,
 
 // ceil(2^31 / units per group): u * inverse / 2^31 rounded down is u / hpg for every u and hpg up to 2^15 (the error of the
 // inverse, below 2^-31, times u stays below the 1 / hpg that is missing to the next whole number), and K holds at most
-// kStreamWaves kStreamMaxPasses slices.  A group longer than K is one group.
+// kStreamWaves kStreamMaxPasses slices.  (J.hpg is at most the units of K, see launch_gemv_gs_jobs.)
 uint32_t group_inverse(const GemvJob& J)
 {
     if (J.scales == nullptr) return 0;
-    const int units = (J.K + 255) / 256;
-    const uint32_t hpg = uint32_t(J.hpg < units ? J.hpg : units);
+    const uint32_t hpg = uint32_t(J.hpg);
     return uint32_t(((uint64_t(1) << 31) + hpg - 1) / hpg);
 }
 static_assert(2 * kStreamWaves * kStreamMaxPasses <= 1 << 15, "group_inverse");
@@ -2013,7 +2012,7 @@ bool gemv_gs_supports(int64_t M, int64_t N, int64_t K, int64_t group)
 {
     const int64_t slices = (K + kSliceK - 1) / kSliceK;
     // (the kernel addresses the scales with 32-bit byte offsets)
-    if (((K + group - 1) / group) * N * 2 >= (int64_t(1) << 31)) return false;
+    if (((K - 1) / group + 1) * N * 2 >= (int64_t(1) << 31)) return false;
     return gemv_supports(M, N, K) && group >= 128 && group % 128 == 0 && N >= 4 && N % 4 == 0 &&
            slices <= kStreamWaves * kStreamMaxPasses &&
            (slices <= kStreamWaves || (N + 15) / 16 <= int64_t(256) * kStreamMaxRun);
@@ -2052,7 +2051,9 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
             const GemmGsDesc& d = jobs[i];
             if ((d.group % 256 == 0 ? 2 : 4) != units) continue;
             const int slices = int((d.K + kSliceK - 1) / kSliceK);
-            const int hpg = int(d.group / (kSliceK / units));
+            // units per group: a group longer than K is the one group there is (the quotient itself need not fit 32 bits)
+            const int64_t unit = kSliceK / units, all = (d.K + unit - 1) / unit;
+            const int hpg = int(d.group / unit < all ? d.group / unit : all);
             for (int64_t m0 = 0; m0 < d.M; m0 += 16) {
                 GemvJob j;
                 j.x = d.x + m0 * d.K;

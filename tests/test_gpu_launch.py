@@ -88,3 +88,23 @@ def test_an_infinite_group_scale_stays_in_its_output():
     tl.tl_ternary_gemm_gs(to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), to_dev(sc.view(np.int16)), group, yd, M, N, K)
     y = yd.cpu().numpy().view(np.float16)[0]
     assert np.isinf(y[100]) and np.isfinite(np.delete(y, 100)).all()
+
+
+# a group longer than K is the one group there is, however long: few rows (units of 256 and of 128 weights), many rows, odd K
+@pytest.mark.parametrize("M,N,K", [(1, 4096, 4096), (16, 48, 11008), (40, 1024, 512), (600, 1030, 1024), (3, 50, 100)])
+def test_groups_longer_than_k(M, N, K):
+    x, W, _ = si.layer(38100 + M + N + K, M, N, K)
+    xd, wd = to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W))
+    sd = to_dev(si.group_scales(np.random.default_rng(K), 1, N).view(np.int16))
+
+    def product(group):
+        yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+        tl.tl_ternary_gemm_gs(xd, wd, sd, group, yd, M, N, K)
+        return yd.cpu().numpy()
+
+    for step in (256, 128, 16):                            # multiples of 256, odd multiples of 128, of 16
+        first = (K // 256 + 1) * 256 + (step if step < 256 else 0)
+        want = product(first)
+        assert np.isfinite(want.view(np.float16)).all()
+        for base in (1 << 31, 1 << 40, (1 << 63) - 512):
+            assert np.array_equal(product(base + (step if step < 256 else 0)), want), f"group {base} + {step}"

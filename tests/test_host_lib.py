@@ -272,6 +272,34 @@ def test_unpacker_joins_rows_of_every_length(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
 
 
+def test_group_longer_than_any_row_does_not_end_the_process():
+    # A group is any multiple of 16 in 64 bits, and what cannot run is refused with a status.  In a process of its own, and only
+    # where there is no GPU: no memory stands behind the addresses.
+    import subprocess
+    import sys
+    code = """
+import sys
+import paper_2506_23025_amd as tl
+try:
+    tl.tl_init()
+    print("ok")
+    sys.exit(0)
+except tl.TlError:
+    pass
+for group in (2**31, 2**32, 2**40, 2**40 + 128, 2**62, 2**63 - 256, 2**63 - 128, 2**63 - 16):
+    for M, N, K in ((1, 4096, 4096), (4, 4096, 4096), (16, 48, 11008), (40, 4096, 4096), (3, 44, 128), (3, 50, 100)):
+        for call in (lambda: tl.tl_ternary_gemm_gs(1 << 20, 1 << 20, 1 << 20, group, 1 << 20, M, N, K, stream=0),
+                     lambda: tl.tl_ternary_gemm_gs_grouped([(1 << 20, 1 << 20, 1 << 20, group, 1 << 20, M, N, K)] * 2, stream=0)):
+            try:
+                call()
+            except tl.TlError as e:
+                assert e.status == tl.TL_ERR_HIP, (group, M, N, K, e)
+print("ok")
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr[-500:])
+
+
 def test_kernel_choice_is_a_pure_function_of_the_shape():
     # decode batch sizes stream the weights; the prefill sizes of the workloads use the tiled MFMA
     # kernel; shapes neither fast kernel takes fall back; invalid sizes give no path
