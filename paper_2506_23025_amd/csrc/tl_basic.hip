@@ -113,12 +113,14 @@ unpack_kernel(const unsigned char* __restrict__ packed, int64_t K, int64_t strid
         const int64_t f = f0 + (u * 256 + int(threadIdx.x)) * 16;
         if (whole[u]) {
             uint32_t c = codes_of(lo[u], hi[u], col[u]);
-            if (col[u] + 16u > Ku)
+            if (col[u] + 16u > Ku) {
+                const unsigned char* r = packed + (row[u] + 1) * stride;
                 c = join_rows(c, Ku - col[u], Ku, [&](int i) {
                     uint32_t w0 = nx[u], none = 0;
-                    if (i > 1) fetch(packed + (row[u] + i) * stride, 0, w0, none);
+                    if (i > 1) fetch(r += stride, 0, w0, none);
                     return codes_of(w0, 0, 0);
                 });
+            }
             u32x4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {

@@ -17,11 +17,10 @@ namespace tl {
 template <class Next>
 TL_UNPACK_FN uint32_t join_rows(uint32_t c, uint32_t left, uint32_t K, Next&& next)
 {
-    c = (c & ((1u << (2u * left)) - 1u)) | (next(1) << (2u * left));
-    if (K < 16u) {                        // rows shorter than a piece; twice a long row's K would not fit 32 bits
-        uint32_t have = left + K;
-        for (int i = 2; have < 16u; have += K, ++i) c = (c & ((1u << (2u * have)) - 1u)) | (next(i) << (2u * have));
-    }
+    uint32_t bits = 2u * left;
+    c = (c & ((1u << bits) - 1u)) | (next(1) << bits);
+    const uint32_t row = 2u * (K < 16u ? K : 16u);        // a row's bits, held at a piece's: twice a long row's K does not fit 32 bits
+    for (int i = 2; (bits += row) < 32u; ++i) c = (c & ((1u << bits) - 1u)) | (next(i) << bits);
     return c;
 }
 
