@@ -728,19 +728,24 @@ tile_kernel(TileParams p)
 
     // ---- group scales: columns with an infinite scale.  s (c - 1) makes a zero weight under it NaN, and terms of both signs too, where
     // s times the group's sum is an infinity (the streaming kernel, which takes few rows, scales sums).  A thread that was
-    // about to store a value that is not finite (`odd`, a packed sum of 0 times every value, is NaN then) looks through the
+    // about to store a value that is not finite (`odd`, the sum of 0 times every value, is NaN then) looks through the
     // scales of its columns and, where one is not finite, works its outputs out again from the groups of such scales.
     // (512 x 4096 x 4096, groups of 128: 23.8 us, with five such columns 181, with a row of NaN in X, where nothing is worked
     // out again, 29; looking at the outputs costs nothing that shows.)
     constexpr bool kRedo = C::FMT == kTileGs && !C::RAGGED;
-    f16x2 odd = {(_Float16)0.f, (_Float16)0.f};
-    auto look = [&](uint32_t pair) {
-        if constexpr (kRedo) odd = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, pair), f16x2{(_Float16)0.f, (_Float16)0.f}, odd);
+    float odd = 0.f;
+    auto look = [&](float value) {
+        if constexpr (kRedo) odd = fmaf(value, 0.f, odd);
+    };
+    auto look2 = [&](uint32_t pair) {
+        const f16x2 v = __builtin_bit_cast(f16x2, pair);
+        look(v[0]);
+        look(v[1]);
     };
     // columns n0 .. n0 + cols - 1, rows m0, m0 + step, ... (count of them)
     auto redo = [&](int n0, int cols, int m0, int step, int count) {
         if constexpr (kRedo) {
-            if (odd[0] == odd[0] && odd[1] == odd[1]) return;
+            if (odd == odd) return;
 #pragma unroll 1
             for (int n = n0; n < n0 + cols && n < p.N; ++n) {
                 const uint16_t* const sc = reinterpret_cast<const uint16_t*>(p.scales) + n;
@@ -807,12 +812,10 @@ tile_kernel(TileParams p)
             if (m >= p.M || n >= p.N) continue;
             __half* const dst = p.y + size_t(m) * p.N + n;
             const f32x4 s = v[0] * p.gamma;
-            const f16x2 lo = {(_Float16)s[0], (_Float16)s[1]}, hi = {(_Float16)s[2], (_Float16)s[3]};
-            const u32x2 quad = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-            look(quad[0]);
-            look(quad[1]);
+            look(s[0]); look(s[1]); look(s[2]); look(s[3]);
             if ((p.N & 3) == 0) {
-                *reinterpret_cast<u32x2*>(dst) = quad;
+                const f16x2 lo = {(_Float16)s[0], (_Float16)s[1]}, hi = {(_Float16)s[2], (_Float16)s[3]};
+                *reinterpret_cast<u32x2*>(dst) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -873,7 +876,7 @@ tile_kernel(TileParams p)
                 const int q = i * 64 + lane;
                 const int row = q / (2 * FN), pc = q - row * (2 * FN);
                 const u32x4 v = *reinterpret_cast<const u32x4*>(ob + row * OROW + pc * 16);
-                look(v[0]); look(v[1]); look(v[2]); look(v[3]);
+                look2(v[0]); look2(v[1]); look2(v[2]); look2(v[3]);
                 const int m = m0 + row, n = n0 + pc * 8;
                 if (m < p.M && n < p.N) *reinterpret_cast<u32x4*>(p.y + size_t(m) * p.N + n) = v;
             }
@@ -883,7 +886,7 @@ tile_kernel(TileParams p)
                 const int q = i * 64 + lane;
                 const int row = q / (16 * FN), c = q - row * (16 * FN);
                 const uint16_t v = *reinterpret_cast<const uint16_t*>(ob + row * OROW + c * 2);
-                look(v);
+                look2(v);
                 const int m = m0 + row, n = n0 + c;
                 if (m < p.M && n < p.N) *reinterpret_cast<uint16_t*>(p.y + size_t(m) * p.N + n) = v;
             }
