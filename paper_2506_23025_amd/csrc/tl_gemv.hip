@@ -1270,7 +1270,8 @@ gemv_longk_kernel(Args b)
     const uint32_t stage_addr = uint32_t(uintptr_t((const __attribute__((address_space(3))) unsigned char*)my_lds));
     auto dma16 = [&](gbytes src, uint32_t lds_base) {       // lane l: 16 bytes from src (per lane) to lds_base + 16 l
         const uint32_t base = __builtin_amdgcn_readfirstlane(lds_base);
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(base) : "memory");
+        // s_nop: the wait state that a transfer needs behind a scalar write of M0
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(base) : "memory");
     };
     auto stage_x = [&](int p) {
         const int sl = wave + NW * p;

@@ -121,10 +121,13 @@ __device__ __forceinline__ void lds_barrier()
 
 // The transfers are written out by hand (LDS base in M0, lane l lands at base + 16 l or + 4 l): a transfer
 // the compiler knows of makes it drain the memory pipeline before every later LDS access.  Every
-// wait for them is an explicit wait_vm.
+// wait for them is an explicit wait_vm.  gfx950 asks for one wait state between a scalar write of M0 and the transfer that
+// reads it; the compiler adds it for its own transfers and looks into no string, so it stands here (dma16_lanes has
+// the exec write in between).  Five more states would be due after a vector instruction that writes the base's scalar
+// registers; none does, and a test reads the built code for both.
 __device__ __forceinline__ void dma16(uint32_t voff, const void* sbase, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 // the same for the lanes of `mask` only (all lanes are active around it)
 __device__ __forceinline__ void dma16_lanes(uint32_t voff, const void* sbase, uint32_t lds, unsigned long long mask)
@@ -134,11 +137,11 @@ __device__ __forceinline__ void dma16_lanes(uint32_t voff, const void* sbase, ui
 }
 __device__ __forceinline__ void dma4(uint32_t voff, const void* sbase, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 __device__ __forceinline__ void dma2(uint32_t voff, const void* sbase, uint32_t lds)   // zero-extended to a dword
 {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_ushort %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_ushort %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 
 __device__ __forceinline__ uint32_t pkfma(uint32_t a, uint32_t b, uint32_t c)
