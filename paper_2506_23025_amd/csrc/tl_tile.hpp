@@ -35,6 +35,7 @@
 // Measured, 4096 -> 14336, M = 2048 (256 x 256 tiles): 172 to 184 us (1.31 to 1.40 PFLOP/s) on four machines where the
 // kernel before (128 x 256 tiles of 32x32x16, X through registers) took 207 to 216.
 #pragma once
+#include "tl_grid.hpp"
 #include "tl_internal.hpp"
 
 #include <atomic>
@@ -922,10 +923,19 @@ hipError_t tile_launch(TileParams p, hipStream_t s)
 {
     const hipError_t e = tile_prepare<C>();
     if (e != hipSuccess) return e;
-    p.tiles_m = (p.M + C::BM - 1) / C::BM;
     p.tiles_n = (p.N + C::BN - 1) / C::BN;
-    hipLaunchKernelGGL((tile_kernel<C>), dim3(unsigned(p.tiles_m) * unsigned(p.tiles_n)), dim3(512), C::LDS, s, p);
-    return hipGetLastError();
+    // one launch, but for outputs of 137 GB and more
+    const int64_t rows = tile_row_blocks(p.tiles_n) * C::BM;
+    for (int64_t m = 0, M = p.M; m < M; m += rows) {
+        p.M = int(M - m < rows ? M - m : rows);
+        p.tiles_m = (p.M + C::BM - 1) / C::BM;
+        hipLaunchKernelGGL((tile_kernel<C>), dim3(unsigned(p.tiles_m) * unsigned(p.tiles_n)), dim3(kTileThreads), C::LDS, s, p);
+        const hipError_t launched = hipGetLastError();
+        if (launched != hipSuccess) return launched;
+        p.x += int64_t(p.M) * p.K;
+        p.y += int64_t(p.M) * p.N;
+    }
+    return hipSuccess;
 }
 
 // What a tile shape costs (us, measured with K = 1024 and 4096 and one or two full rounds of workgroups): a round of

@@ -272,6 +272,21 @@ def test_unpacker_joins_rows_of_every_length(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
 
 
+def test_tiled_launches_hold_their_threads_in_32_bits(tmp_path):
+    # csrc/tl_grid.hpp: a grid of 2^32 threads and more is launched as what is left of the count modulo 2^32, and nobody says so
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++") or shutil.which("c++")
+    assert cxx, "no C++ compiler"
+    exe = str(tmp_path / "grid_host")
+    cmd = [cxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "paper_2506_23025_amd", "csrc"),
+           os.path.join(ROOT, "tests", "c", "grid_host.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
+
+
 def test_group_longer_than_any_row_does_not_end_the_process():
     # A group is any multiple of 16 in 64 bits, and what cannot run is refused with a status.  In a process of its own, and only
     # where there is no GPU: no memory stands behind the addresses.
