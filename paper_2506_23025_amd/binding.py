@@ -147,6 +147,15 @@ def _first_stream():
 _raw_stream = None      # once torch has a device: (current device, raw handle of its current stream)
 
 
+def _forget_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+# A forked child asks torch again, which refuses a device that its parent had set up.
+os.register_at_fork(after_in_child=_forget_stream)
+
+
 def _stream(stream):
     if stream is None:
         if _raw_stream is not None:

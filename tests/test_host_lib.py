@@ -329,3 +329,26 @@ def test_kernel_choice_is_a_pure_function_of_the_shape():
     # the model follows the measured crossovers (small-M kernel up to M = 768 at 4096 -> 14336)
     assert tl.tl_ternary_gemm_which(512, 14336, 4096) == tl.TL_PATH_GEMV
     assert tl.tl_ternary_gemm_which(1024, 4096, 11008) == tl.TL_PATH_MFMA
+
+
+def test_a_forked_child_asks_torch_for_its_stream_again():
+    # torch refuses the GPU in a child that was forked after it had set the device up; the functions kept for the calls after the
+    # first must not carry the child past that
+    import os
+    from paper_2506_23025_amd import binding
+    kept = binding._raw_stream
+    binding._raw_stream = (lambda: 0, lambda device: 1234)
+    try:
+        assert binding._stream(None) == 1234
+        r, w = os.pipe()
+        pid = os.fork()
+        if pid == 0:
+            os.write(w, b"kept" if binding._raw_stream is not None else b"gone")
+            os._exit(0)
+        os.waitpid(pid, 0)
+        assert os.read(r, 16) == b"gone"
+        assert binding._raw_stream is not None
+        os.close(r)
+        os.close(w)
+    finally:
+        binding._raw_stream = kept
