@@ -322,6 +322,21 @@ tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, 
     return flush();
 }
 
+// For the tests, which assert what they run; not part of the interface.  form: 0 2-bit words, 1 a 1.6-bit code, 2 group scales, 3 2-bit words on
+// TL_PATH_MFMA.  The tiled kernel's instance for a call of its own, or -1 where another kernel takes it.
+__attribute__((visibility("default"))) int tl_internal_tile_instance(int form, int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    switch (form) {
+        case 0:
+            if (tl_ternary_gemm_which(M, N, K) == TL_PATH_MFMA) return tl::mfma_shape(M, N, K);
+            return tl_ternary_gemm_which(M, N, K) == TL_PATH_GENERIC && K % 64 != 0 && tl::tile_ragged_preferred(M, N, K) ? tl::tile_ragged_shape(M, N, K) : -1;
+        case 1: return tl::tile3_preferred(M, N, K) ? tl::tile3_shape(M, N, K) : -1;
+        case 2: return tl::tile_gs_preferred(M, N, K, group) ? tl::tile_gs_shape(M, N, K, group) : -1;
+        case 3: return tl::mfma_supports(M, N, K) ? tl::mfma_shape(M, N, K) : -1;
+        default: return -1;
+    }
+}
+
 tl_status tl_init(void)
 {
     hipError_t e = tl::gemv_init();

@@ -124,6 +124,13 @@ double mfma_time(int64_t M, int64_t N, int64_t K);
 hipError_t launch_mfma(const __half* x, const uint32_t* Wp, float gamma, __half* y,
                        int64_t M, int64_t N, int64_t K, hipStream_t s);
 
+// The instance (its place in the table of its file) the tiled kernel would run a shape with; kRaggedShape more for the forms for odd K.
+constexpr int kRaggedShape = 100;
+int mfma_shape(int64_t M, int64_t N, int64_t K);
+int tile_ragged_shape(int64_t M, int64_t N, int64_t K);
+int tile3_shape(int64_t M, int64_t N, int64_t K);
+int tile_gs_shape(int64_t M, int64_t N, int64_t K, int64_t group);
+
 // Prepare every kernel instance on the current device (dynamic-LDS limits); idempotent.
 // Once-per-device flags (a function attribute holds for the device it was set on): index of the
 // current device, or -1 when it cannot be tracked, in which case the caller does the work again.

@@ -76,6 +76,8 @@ bool tile3_preferred(int64_t M, int64_t N, int64_t K)
     return 1.08 * us < t_stream;                          // a band: near the crossover the models are within that of each other
 }
 
+int tile3_shape(int64_t M, int64_t N, int64_t K) { return (K % 8 != 0 ? kRaggedShape : 0) + pick(M, N, K, nullptr); }
+
 hipError_t tile3_init()
 {
     hipError_t e = tile_prepare<T128x256>();

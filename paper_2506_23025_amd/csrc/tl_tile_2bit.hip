@@ -110,6 +110,9 @@ double mfma_time(int64_t M, int64_t N, int64_t K)
     return us;
 }
 
+int mfma_shape(int64_t M, int64_t N, int64_t K) { return pick(M, N, K, nullptr); }
+int tile_ragged_shape(int64_t M, int64_t N, int64_t K) { return kRaggedShape + pick_ragged(M, N, K, nullptr); }
+
 hipError_t mfma_init()
 {
     hipError_t e = tile_prepare<T256x256>();

@@ -83,6 +83,8 @@ bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
     return us < 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
 }
 
+int tile_gs_shape(int64_t M, int64_t N, int64_t K, int64_t group) { return (K % 64 != 0 ? kRaggedShape : 0) + pick(M, N, K, group, nullptr); }
+
 hipError_t tile_gs_init()
 {
     hipError_t e = tile_prepare<T256x256>();

@@ -5,7 +5,7 @@ import pytest
 import oracle
 import paper_2506_23025_amd as tl
 import synth_inputs as si
-from parity import assert_close, dev_u32, to_dev
+from parity import REL_TOL, assert_close, dev_u32, floors, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -61,11 +61,12 @@ def test_tile_1p6(M, N, K, fx):
     assert_close(y[:, cols], oracle.gemm(x, np.ascontiguousarray(W[cols]), g), x, g, f"tile 1.6 {M}x{N}x{K}")
 
 
-# Group scales: every tile shape; groups of 64 and more (one scale per 64 k), of 32, 48, 16 (one per 16 k), longer than K,
+# Group scales: every tile shape (and three calls so small that they go elsewhere); groups of 64 and more (one scale per 64 k), of 32, 48, 16 (one per 16 k), longer than K,
 # ending inside a step and inside a group; N with and without 16-byte stores.
 TILE_GS_SHAPES = [
     (1030, 8200, 192, 64), (2048, 3000, 192, 128), (300, 9000, 704, 256), (300, 9001, 704, 48), (117, 14340, 4096, 32),
     (640, 2500, 1152, 96), (129, 1030, 1088, 16), (40, 300, 1024, 128), (17, 70, 64, 4096), (16, 333, 4096, 64), (5, 40, 320, 64),
+    (300, 9004, 704, 128), (300, 2050, 1024, 64), (300, 4100, 320, 32),
 ]
 
 
@@ -84,10 +85,12 @@ def test_tile_group_scales(M, N, K, group):
 
 
 # K that fits no 16-byte piece: X rows at any even byte, W rows at any word; K of one piece (the smallest the form takes),
-# one short of and past a block, a piece, a step and the fetch depth; the four tile shapes; N = 1 and N odd.
+# one short of and past a block, a piece, a step and the fetch depth; every tile shape of the three forms (the smallest K and
+# the smallest matrices go to the plain kernels; the 1.6-bit form's smallest K below); N = 1 and N odd.
 RAGGED_SHAPES = [
     (1, 1, 9), (3, 40, 33), (16, 333, 1001), (16, 4099, 255), (37, 4099, 4090), (70, 257, 127), (40, 1030, 129), (200, 2050, 257),
     (150, 8200, 641), (900, 2500, 1100), (1030, 4100, 383), (5, 64, 2044), (33, 130, 8190),
+    (1024, 4096, 1001), (700, 2050, 127),
 ]
 
 
@@ -116,6 +119,22 @@ def test_tile_odd_k(M, N, K):
         tl.tl_ternary_gemm_gs(xd, dev_u32(tl.tl_pack_2bit(W)), to_dev(s.view(np.int16)), group, yd, M, N, K)
         sref = oracle.gemm_group_scales(x, np.ascontiguousarray(W[cols]), np.ascontiguousarray(s[:, cols]), group)
         check(f"scales {group}", sref, 0.05)
+
+
+# K of one piece: rows shorter than a step of X, a fetch of W and a 16-byte store, in the tiled kernel with 1.6-bit codes.  Outputs this small reach
+# fp16's subnormal range, where rounding alone is 2^-25 whatever the value.
+@pytest.mark.parametrize("K", [9, 15, 33])
+def test_tile_smallest_odd_k(K):
+    M, N = 2000, 2050
+    x, W, g = si.layer(34800 + K, M, N, K)
+    xd, gb = to_dev(x.view(np.int16)), si.gamma_bits(g)
+    ref = oracle.gemm(x, W, g)
+    for fx in (False, True):
+        yd = to_dev(np.full((M, N), -1, dtype=np.int16))
+        Wp = to_dev(tl.tl_pack_1p6bit_fx(W) if fx else tl.tl_pack_1p6bit(W))
+        (tl.tl_ternary_gemm_1p6_fx if fx else tl.tl_ternary_gemm_1p6)(xd, Wp, gb, yd, M, N, K)
+        y = yd.cpu().numpy().view(np.float16).astype(np.float64)
+        assert (np.abs(y - ref) <= REL_TOL * np.maximum(np.abs(ref), floors(x, g, K)) + 2.0 ** -25).all()
 
 
 def test_tile_odd_k_keeps_rows_apart():

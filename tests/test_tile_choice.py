@@ -1,0 +1,39 @@
+"""Which kernel the library's cost models send a call to: the GPU tests of the tiled kernel reach every instance of it (CPU, no launch)."""
+import ctypes
+
+import paper_2506_23025_amd as tl
+import test_gpu_tile as shapes
+
+_instance = tl.raw().tl_internal_tile_instance           # not in tl.h: for the tests alone
+_instance.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 4
+_instance.restype = ctypes.c_int
+
+TWO_BIT, ONE_POINT_SIX, SCALES, TWO_BIT_FORCED = range(4)
+RAGGED = 100                                               # first instance of the forms for odd K
+
+
+def instance(form, M, N, K, group=0):
+    """Place of the tiled kernel's instance in the table of its form, or -1 where another kernel takes the call."""
+    return _instance(form, M, N, K, group)
+
+
+def test_tile_shapes_reach_every_instance():
+    assert {instance(TWO_BIT_FORCED, *s) for s in shapes.TILE_SHAPES} == set(range(6))
+    assert {instance(ONE_POINT_SIX, *s) for s in shapes.TILE3_SHAPES} == set(range(5))
+    assert {instance(SCALES, *s) for s in shapes.TILE_GS_SHAPES} - {-1} == set(range(7))
+
+
+def test_odd_k_shapes_reach_every_instance():
+    assert {instance(TWO_BIT, *s) for s in shapes.RAGGED_SHAPES} - {-1} == {RAGGED + i for i in range(4)}
+    assert {instance(ONE_POINT_SIX, *s) for s in shapes.RAGGED_SHAPES} - {-1} == {RAGGED + i for i in range(3)}
+    assert all(instance(ONE_POINT_SIX, 2000, 2050, K) >= RAGGED for K in (9, 15, 33))
+    assert {instance(SCALES, *s, group) for s in shapes.RAGGED_SHAPES for group in (16, 144, 8192)} - {-1} == {RAGGED + i for i in range(3)}
+
+
+def test_shapes_beyond_the_form_are_left_to_others():
+    assert instance(TWO_BIT, 16, 4096, 4096) == -1         # few rows
+    assert instance(ONE_POINT_SIX, 16, 4096, 4096) == -1
+    assert instance(SCALES, 16, 4096, 4096, 128) == -1
+    for form in (TWO_BIT, ONE_POINT_SIX, SCALES):
+        assert instance(form, 1024, 4096, 7, 16) == -1     # K of less than a piece
+        assert instance(form, 1 << 25, 16, 100, 16) == -1  # rows past 2^24
