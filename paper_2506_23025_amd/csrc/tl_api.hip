@@ -67,6 +67,10 @@ inline bool prefer_small_m(int64_t M, int64_t N, int64_t K)
         const double per_block = per_mb * w_mb > 0.3 ? per_mb * w_mb : 0.3;
         t_small = 3.8 + double((M + 15) / 16) * per_block;
     }
+    // Short rows: what a block of rows costs beside its share of W (activations, outputs, the workgroups' starts) is not spread over as
+    // much of W.  M = 512, measured (and by the lines above): K = 512 N = 16384 29.7 (15.2), 8192 17.3 (13.4); K = 1024 N = 16384
+    // 26.1 (22.4), 4096 16.2 (13.4); 2048 -> 2048 16.6 (13.4); 4096 -> 4096 20.1 (22.4).
+    if (slices <= 4) t_small = 4.0 + (t_small - 4.0) * (slices == 1 ? 2.0 : 1.4);
     // The constants are fits on one machine, and machines differ by several percent (the same library:
     // 18.3 and 19.6 us for the same launch).  Near the crossover the two kernels are within that spread of each
     // other, so a band rather than the bare comparison decides: beyond 16 rows the small-M kernel keeps a shape unless

@@ -926,7 +926,8 @@ static_assert(sizeof(LeanOne) == 64, "the arguments of a lone call");
 // streamed once per NW slices; between passes the sums of the run wait in LDS (1 KB per tile behind the waves' areas)
 // with the thread that owns the output quad.  The last item of a pass asks for the next pass's first weights; the
 // activations follow once every wave has left the sums of that item, which share LDS with them.  Waves past the last
-// slice of the last pass multiply zeros.
+// slice take no part in the last pass but for the exchange (multiplying zeros instead, 7936 x 5248 at M = 18, two slices in the last of
+// two passes, took 12.5 us and the general form 11.1; now 11.3; 65 rows of 11648 x 4480 25.3, 23.6 and 22.3); GS multiplies zeros.
 // GS: group scales, groups of whole units of 256 weights (half a slice).  The halves of a tile are summed one after the
 // other in the same accumulators, each scaled by its group's scales of the lane's four output rows, which are
 // requested with the tile's weights.  Against the general form, groups of 256: block at M = 1 / 4 / 16 16.0 / 17.2 / 24.5 ->
@@ -1046,7 +1047,7 @@ gemv_lean_kernel(Args b)
         const int xrow = mi & (mr - 1);
         const uint32_t xr_off = uint32_t(xrow) * 1024u + uint32_t(mg) * 128u;
         const uint32_t sw = uint32_t(xrow & 7);
-        const bool live = mi < rows && (!PASSES || active);
+        const bool live = mi < rows && (!(PASSES && GS) || active);
         const uint32_t sel_lo = live ? 0x05040100u : 0x0c0c0c0cu;
         const uint32_t sel_hi = live ? 0x07060302u : 0x0c0c0c0cu;
 #pragma unroll
@@ -1087,11 +1088,16 @@ gemv_lean_kernel(Args b)
     // loaded again at once with the tile T further on.
     // REFILL 2 (PASSES): with the first tiles of the next pass, to whose slice the offsets have been moved.
     unsigned char* const ysum = lds_raw + NW * kStride;
-    bool idle = false;                                     // this wave has no slice in this pass
+    bool idle = false, next_live = true;                   // this wave has no slice in this pass, has one in the next
     auto item = [&](auto nt_tag, auto refill_tag, int first, int parity, bool first_pass, bool last_pass) {
         constexpr int NT = decltype(nt_tag)::value;
         constexpr int REFILL = decltype(refill_tag)::value;
         f32x4 part[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) part[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // A wave without a slice in the last pass only takes part in the exchange.  (GS: it multiplies zeros as well.  Left out there,
+        // the block at M = 4 takes 16.65 instead of 16.42 us, the branch's registers being spilled.)
+        if (!PASSES || GS || !idle) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             unsigned char* const reg_t = my_lds + (t & 1) * 2048;
@@ -1113,7 +1119,7 @@ gemv_lean_kernel(Args b)
                 }
             }
             if constexpr (REFILL != 0) {
-                issue_w(REFILL == 2 ? t : first + T + t, t);
+                if (REFILL == 1 || GS || next_live) issue_w(REFILL == 2 ? t : first + T + t, t);
                 __builtin_amdgcn_s_setprio(0);
                 // the requests leave here, as soon as the registers are free: left to itself the
                 // scheduler sinks all of an item's loads to its end, which costs two tiles of lead
@@ -1152,14 +1158,17 @@ gemv_lean_kernel(Args b)
                 part[t] = __builtin_elementwise_fma(__builtin_elementwise_fma(acc[0], f32x4{4.f, 4.f, 4.f, 4.f}, acc[1]),
                                                     f32x4{4.f, 4.f, 4.f, 4.f}, acc[2]);
         }
+        }
         if constexpr (REFILL == 2) {
+            if (GS || next_live) {
 #pragma unroll
-            for (int t = NT; t < T; ++t) issue_w(t, t);
+                for (int t = NT; t < T; ++t) issue_w(t, t);
+            }
         }
         // split-K: partial sums into this wave's set `parity`, one LDS-only barrier, fixed-order sum
         unsigned char* const red = my_lds + 4096 + parity * (T * 1024);
 #pragma unroll
-        for (int t = 0; t < NT; ++t)                       // an idle wave's zeros may have met an infinite scale
+        for (int t = 0; t < NT; ++t)                       // GS: an idle wave's zeros may have met an infinite scale
             reinterpret_cast<f32x4*>(red + t * 1024)[lane] = (GS && PASSES && idle) ? f32x4{0.f, 0.f, 0.f, 0.f} : part[t];
         __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
         __builtin_amdgcn_s_barrier();
@@ -1213,14 +1222,17 @@ gemv_lean_kernel(Args b)
                 voff0 = offset_of(slice);
                 voff1 = voff0 + 8u * row_bytes;
                 scales_of(slice);
+                next_live = slice < slices;
                 last_item(NextPass{}, i, first_pass, false);
                 // the activations land where other waves may still be reading this item's sums
                 __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
                 __builtin_amdgcn_s_barrier();
-                if (slice < slices) stage_x(slice);
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
-                idle = slice >= slices;
-                build(!idle);
+                idle = !next_live;
+                if (!idle) stage_x(slice);
+                if (GS || !idle) {
+                    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
+                    build(!idle);
+                }
             }
         }
     }
