@@ -1775,12 +1775,23 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
     bool lean = pol.lean && nb == 1 && gs != 4 && T <= 3;
     int total_groups = 0, kept = 0;
+    int64_t w_bytes = 0;                                   // packed words the launch streams
     for (int j = 0; j < b.count; ++j) {
         lean = lean && b.job[j].slices >= NW && (b.job[j].N & 15) == 0;
         total_groups += wg[j];
+        w_bytes += int64_t(b.job[j].tiles) * 4 * b.job[j].K;
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
         if (passes(j) > 1 && r > kept) kept = r;
+        // With scales the general form is ahead (M = 2, 5760 -> 5376 7.3 against 8.9 us, -> 11584 9.0 / 10.8; M = 4, 4224 -> 8960 9.1 / 10.6;
+        // M = 1, 12928 -> 6784 13.0 / 15.3) up to 4 rows, whose activations it asks for a pass ahead, on runs of more than a tile,
+        // where the last pass has work for half of the waves at most: it skips the others.  Beside that the lean form is (M = 2, 5504 ->
+        // 3200 6.9 / 5.9; M = 9, 12224 -> 4992 15.4 / 15.1; M = 1, 11008 -> 4096 8.8 / 7.7).
+        const int last = b.job[j].slices % NW;
+        if (gs != 0 && passes(j) > 1 && b.job[j].Mrem <= 4 && r > 1 && last != 0 && 2 * last <= NW) lean = false;
     }
+    // The table of records costs the host 0.7 us, which a launch with scales earns back from about 12 MB on (several blocks of rows of a
+    // layer, lean over general: below 1 MB 1.09, 2 to 12 MB 1.00 to 1.02, 12 to 16 MB 0.96, beyond 0.93 to 0.95).
+    if (gs != 0 && b.count > 1 && w_bytes < (int64_t(12) << 20)) lean = false;
     if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs != 0, s);
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;

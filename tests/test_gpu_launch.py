@@ -59,7 +59,9 @@ def test_grouped_calls_with_long_k(M, sizes):
 # scales per group of a multiple of 256 weights, N a multiple of 16: groups of half a slice, of one and one and a half slices, of all of K,
 # with and without several passes, alone and in a group; one to three tiles in the last item
 @pytest.mark.parametrize("M,sizes,group", [(4, [(4096, 4096)] * 2 + [(4096, 11008)], 256), (1, [(1040, 4096), (8208, 4672)], 768), (16, [(16400, 8192)], 512),
-                                           (5, [(16, 4096)], 4096), (3, [(4112, 1024), (12304, 1024)], 256), (2, [(2064, 4160)], 256)])
+                                           (5, [(16, 4096)], 4096), (3, [(4112, 1024), (12304, 1024)], 256), (2, [(2064, 4160)], 256),
+                                           # and large enough for the lean kernel as a group, with one pass and with two
+                                           (3, [(4112, 1024), (49168, 1024)], 256), (5, [(1040, 4096), (16400, 4672)], 768), (2, [(11584, 5760)], 256)])
 def test_decode_with_group_scales(M, sizes, group):
     jobs, want = [], []
     for i, (N, K) in enumerate(sizes):
