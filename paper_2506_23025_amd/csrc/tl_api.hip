@@ -33,49 +33,48 @@ inline tl_status from_hip(hipError_t e) { return e == hipSuccess ? TL_OK : TL_ER
 // Most activation rows one launch of the 1.6-bit weight-streaming kernel takes.
 constexpr int64_t kGemvMaxM = 4096;
 
-// Small-M kernel (blocks of 16 or 32 activation rows that each stream W) or tiled matrix-core
-// kernel, when both can run the shape: whichever the cost models below make cheaper.  They are
-// fits to measurements (us; W in MB of packed weights):
-//  * small-M, blocks of 32 rows, one pass over K: 4 + blocks x (0.31 + 0.2 W)
-//    (4096 -> 14336: 3.2 us per block); several passes: launches of up to 4096 tiles, each
-//    passes x (8.7 + 0.88 x its longest run of tiles per workgroup)
-//    (11008 -> 4096: 16 blocks 68 us, 8 blocks 47 us)
-//  * small-M, blocks of 16 rows: 3.8 + blocks x W x (0.17 while W stays in the L2 caches, 0.21
-//    beyond), at least 0.3 per block; when K needs several passes 1 + 3 passes + blocks x 0.175 W
-//    (11008 -> 4096: 2 blocks 13.7 us, 16 blocks 44.2 us)
-//  * tiled matrix-core kernel: mfma_time (tl_tile_2bit.hip)
+// What the small-M kernel takes (us) for more than 16 rows: t tiles of 16 output rows, b blocks of 16 or 32 activation rows, s slices of
+// 512 weights, p passes of 8 slices.  In one pass a block costs its activations and a share of every tile, which depends on s
+// alone (a workgroup has s waves, and as many more workgroups fit as 8 / s allows), not on the bytes of W.  Fitted with the
+// tiled kernel's times (see TileCost): 10 % for nine in ten calls, 15 % with several passes.  The one line that is older is that of blocks
+// of 32 rows with 8 slices: it is 0.8 of the time for most N, and right where t b is a multiple of 256.
+inline double small_m_time(int64_t M, int64_t N, int64_t K)
+{
+    const int s = int((K + 511) / 512);
+    const double t = double((N + 15) / 16);
+    const double p = double((s + 7) / 8);
+    if (tl::gemv_two_blocks(M, N, K)) {
+        const int64_t blocks = (M + 31) / 32;
+        const double b = double(blocks);
+        if (s > 8) {
+            // launches of at most 4096 tiles
+            const int64_t tiles = (N + 15) / 16, cap = tiles >= 4096 ? 1 : 4096 / tiles;
+            return 5.16 * p * double((blocks + cap - 1) / cap) + 0.51 * b + b * t / 256.0 * (0.09 * double(s) + 0.49 * p);
+        }
+        if (s == 8) return 4.0 + b * (0.31 + 0.2 * double(N) * double(K) / 4.0e6);
+        constexpr double per_tile[8] = {0, 0, 0.334, 0.63, 0.53, 0.82, 0.87, 0.95};
+        return 5.8 * double((blocks + 31) / 32) + 0.148 * b + per_tile[s] * b * t / 256.0;
+    }
+    const int64_t blocks = (M + 15) / 16;
+    const double b = double(blocks), launches = double((blocks + 31) / 32);
+    if (s <= 8) {
+        constexpr double per_tile[9] = {0, 0.114, 0.185, 0.30, 0.32, 0.56, 0.57, 0.62, 0.62};
+        return 4.5 * launches + 0.173 * b + per_tile[s] * b * t / 256.0;
+    }
+    if (b * t >= 512.0) return 1.2 + 2.44 * launches * p + 0.133 * b + b * t / 256.0 * (0.059 * double(s) + 0.39 * p);
+    if (N % 16 == 0) return 3.0 + 1.3 * p + 0.115 * double(s) * b * t / 256.0;
+    return 1.7 + 3.2 * p + 0.06 * b + 0.166 * double(s) * b * t / 256.0;
+}
+
+// Small-M kernel or tiled matrix-core kernel, when both can run the shape.  A band rather than the bare comparison decides, since machines
+// differ by several percent (the same library: 18.3 and 19.6 us for the same launch): beyond 16 rows the small-M kernel keeps a shape
+// unless the models put the tiled kernel ahead by more than 7 %.  Over the calls of the fit the one chosen is 1.0 % slower than the faster one on
+// average and 16 % in one of a hundred; with the constants before 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
 inline bool prefer_small_m(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 16) return true;
-    const double w_mb = double(N) * double(K) / 4.0e6;
-    const int64_t slices = (K + 511) / 512;
-    double t_small;
-    if (tl::gemv_two_blocks(M, N, K) && slices > 8) {
-        // several passes over K: launches of at most 4096 tiles; a launch costs, per pass, a
-        // start plus its longest run of tiles
-        const int64_t blocks = (M + 31) / 32, tiles = (N + 15) / 16;
-        const int64_t cap = tiles >= 4096 ? 1 : 4096 / tiles;
-        const double passes = double((slices + 7) / 8);
-        auto launch_us = [&](int64_t b) { return passes * (8.7 + 0.88 * double((b * tiles + 255) / 256)); };
-        t_small = double(blocks / cap) * launch_us(cap) + (blocks % cap ? launch_us(blocks % cap) : 0.0);
-    } else if (tl::gemv_two_blocks(M, N, K)) {
-        t_small = 4.0 + double((M + 31) / 32) * (0.31 + 0.2 * w_mb);
-    } else if (slices > 8) {
-        t_small = 1.0 + 3.0 * double((slices + 7) / 8) + double((M + 15) / 16) * 0.175 * w_mb;
-    } else {
-        const double per_mb = w_mb < 8.4 ? 0.17 : 0.21;
-        const double per_block = per_mb * w_mb > 0.3 ? per_mb * w_mb : 0.3;
-        t_small = 3.8 + double((M + 15) / 16) * per_block;
-    }
-    // Short rows: what a block of rows costs beside its share of W (activations, outputs, the workgroups' starts) is not spread over as
-    // much of W.  M = 512, measured (and by the lines above): K = 512 N = 16384 29.7 (15.2), 8192 17.3 (13.4); K = 1024 N = 16384
-    // 26.1 (22.4), 4096 16.2 (13.4); 2048 -> 2048 16.6 (13.4); 4096 -> 4096 20.1 (22.4).
-    if (slices <= 4) t_small = 4.0 + (t_small - 4.0) * (slices == 1 ? 2.0 : 1.4);
-    // The constants are fits on one machine, and machines differ by several percent (the same library:
-    // 18.3 and 19.6 us for the same launch).  Near the crossover the two kernels are within that spread of each
-    // other, so a band rather than the bare comparison decides: beyond 16 rows the small-M kernel keeps a shape unless
-    // the model puts the tiled kernel ahead by more than 7 %.
-    return t_small < 1.07 * tl::mfma_time(M, N, K);
+    const double t_small = small_m_time(M, N, K);
+    return t_small < 1.07 * tl::mfma_at_least(K) || t_small < 1.07 * tl::mfma_time(M, N, K);
 }
 
 }  // namespace

@@ -1789,9 +1789,9 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
         const int last = b.job[j].slices % NW;
         if (gs != 0 && passes(j) > 1 && b.job[j].Mrem <= 4 && r > 1 && last != 0 && 2 * last <= NW) lean = false;
     }
-    // The table of records costs the host 0.7 us, which a launch with scales earns back from about 12 MB on (several blocks of rows of a
+    // The table of records costs the host 0.7 us, which a launch with scales and one pass over K earns back from about 12 MB on (several blocks of rows of a
     // layer, lean over general: below 1 MB 1.09, 2 to 12 MB 1.00 to 1.02, 12 to 16 MB 0.96, beyond 0.93 to 0.95).
-    if (gs != 0 && b.count > 1 && w_bytes < (int64_t(12) << 20)) lean = false;
+    if (gs != 0 && b.count > 1 && !multi_pass && w_bytes < (int64_t(12) << 20)) lean = false;
     if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs != 0, s);
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;

@@ -121,6 +121,7 @@ hipError_t launch_tile_ragged(const __half* x, const uint32_t* Wp, float gamma, 
 bool mfma_supports(int64_t M, int64_t N, int64_t K);
 // what it is expected to take (us), with the tile shape it would choose
 double mfma_time(int64_t M, int64_t N, int64_t K);
+double mfma_at_least(int64_t K);                       // a bound below it
 hipError_t launch_mfma(const __half* x, const uint32_t* Wp, float gamma, __half* y,
                        int64_t M, int64_t N, int64_t K, hipStream_t s);
 

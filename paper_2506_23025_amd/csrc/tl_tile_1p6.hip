@@ -14,11 +14,11 @@ typedef TileCfg<kTile1p6, false, 2, 2, 1, 2, 4, 10, 3> T32x64;
 
 constexpr int kShapes = 5;
 constexpr TileCost kCost[kShapes] = {
-    {128, 256, 160, 256, 7.0, 2.10, 2.10},
-    {128, 128, 160, 256, 5.0, 1.11, 1.11},
-    {64, 128, 160, 256, 2.8, 0.78, 0.78},
-    {64, 64, 320, 256, 2.7, 0.84, 0.84},
-    {32, 64, 320, 256, 1.9, 0.70, 0.70},
+    {128, 256, 160, 256, 9.4, 9.4, 1.64, 1.98, 1.98, 0.90, 0.5},
+    {128, 128, 160, 256, 6.0, 6.0, 0.904, 1.09, 1.09, 0.88, 1.05},
+    {64, 128, 160, 256, 4.0, 4.0, 0.715, 0.818, 0.818, 0.90, 1.25},
+    {64, 64, 320, 256, 3.8, 3.8, 0.748, 0.88, 0.88, 0.93, 1.4},
+    {32, 64, 320, 256, 2.85, 2.85, 0.631, 0.728, 0.728, 0.93, 1.45},
 };
 
 // K that is no multiple of 8
@@ -28,9 +28,9 @@ typedef TileCfg<kTile1p6, true, 1, 2, 1, 2, 4, 10, 2> R16x64;
 
 constexpr int kRagged = 3;
 constexpr TileCost kRaggedCost[kRagged] = {
-    {64, 128, 160, 256, 5.4, 0.96, 0.96},
-    {32, 128, 160, 256, 3.7, 0.70, 0.70},
-    {16, 64, 320, 256, 3.1, 0.63, 0.63},
+    {64, 128, 160, 256, 5.4, 5.4, 0.96, 0.96, 0.96, 0.6, 2.0},
+    {32, 128, 160, 256, 3.7, 3.7, 0.70, 0.70, 0.70, 0.6, 2.0},
+    {16, 64, 320, 256, 3.1, 3.1, 0.63, 0.63, 0.63, 0.6, 2.0},
 };
 
 int pick(int64_t M, int64_t N, int64_t K, double* us)

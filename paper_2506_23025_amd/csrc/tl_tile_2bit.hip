@@ -15,12 +15,12 @@ typedef TileCfg<kTile2Bit, false, 2, 2, 1, 2, 4, 4, 4> T32x64;      // two workg
 
 constexpr int kShapes = 6;
 constexpr TileCost kCost[kShapes] = {
-    {256, 256, 64, 256, 5.7, 1.36, 1.36},
-    {128, 256, 128, 256, 7.0, 1.36, 1.36},
-    {128, 128, 128, 256, 4.0, 0.77, 0.77},
-    {128, 64, 128, 256, 3.5, 0.41, 0.41},
-    {64, 64, 128, 512, 2.6, 0.50, 0.24},
-    {32, 64, 128, 512, 2.3, 0.31, 0.19},
+    {256, 256, 64, 256, 6.2, 6.2, 1.07, 1.32, 1.32, 0.87, 0.5},
+    {128, 256, 128, 256, 7.3, 7.3, 1.17, 1.43, 1.43, 0.84, 0.5},
+    {128, 128, 128, 256, 4.9, 4.9, 0.656, 0.786, 0.786, 0.88, 0.9},
+    {128, 64, 128, 256, 4.3, 4.3, 0.336, 0.43, 0.43, 0.92, 1.15},
+    {64, 64, 128, 512, 2.25, 3.35, 0.229, 0.273, 0.475, 0.43, 2.1},
+    {32, 64, 128, 512, 1.35, 2.65, 0.191, 0.213, 0.318, 0.43, 2.4},
 };
 
 // Row offsets within a tile are 32-bit: tiles of 256 rows up to K = 2^22, of 128 up to 2^23.
@@ -47,10 +47,10 @@ typedef TileCfg<kTile2Bit, true, 1, 2, 1, 1, 8, 8, 2> R16x32;       // steps of 
 
 constexpr int kRagged = 4;
 constexpr TileCost kRaggedCost[kRagged] = {
-    {128, 128, 128, 256, 7.8, 1.10, 1.10},
-    {64, 128, 128, 256, 3.6, 0.60, 0.60},
-    {32, 64, 128, 512, 1.8, 0.45, 0.31},
-    {16, 32, 256, 512, 1.5, 0.46, 0.28},
+    {128, 128, 128, 256, 7.8, 7.8, 1.10, 1.10, 1.10, 0.6, 2.0},
+    {64, 128, 128, 256, 3.6, 3.6, 0.60, 0.60, 0.60, 0.6, 2.0},
+    {32, 64, 128, 512, 1.8, 1.8, 0.31, 0.31, 0.45, 0.6, 2.0},
+    {16, 32, 256, 512, 1.5, 1.5, 0.28, 0.28, 0.46, 0.6, 2.0},
 };
 
 int pick_ragged(int64_t M, int64_t N, int64_t K, double* us)
@@ -102,6 +102,8 @@ bool mfma_supports(int64_t M, int64_t N, int64_t K)
     return M >= 1 && N >= 1 && K >= 64 && (K % 64) == 0 && K <= (int64_t(1) << 24) &&
            M <= (int64_t(1) << 24) && N <= (int64_t(1) << 24);
 }
+
+double mfma_at_least(int64_t K) { return tile_at_least(kCost, kShapes, K); }
 
 double mfma_time(int64_t M, int64_t N, int64_t K)
 {

@@ -19,13 +19,13 @@ typedef TileCfg<kTileGs, false, 2, 2, 1, 2, 4, 4, 4, 1> T32x64any;
 
 constexpr int kShapes = 7, kFirstAny = 3;     // from kFirstAny on any group that is a multiple of 16
 constexpr TileCost kCost[kShapes] = {
-    {256, 256, 64, 256, 6.1, 1.57, 1.57},
-    {128, 256, 128, 256, 7.0, 1.63, 1.63},
-    {128, 128, 128, 256, 4.7, 0.92, 0.92},
-    {128, 128, 128, 256, 4.4, 1.04, 1.04},
-    {128, 64, 128, 256, 3.5, 0.54, 0.54},
-    {64, 64, 128, 512, 3.2, 0.63, 0.34},
-    {32, 64, 128, 512, 2.8, 0.46, 0.28},
+    {256, 256, 64, 256, 6.3, 6.3, 1.205, 1.454, 1.454, 0.93, 0.5},
+    {128, 256, 128, 256, 7.85, 7.85, 1.29, 1.525, 1.525, 0.91, 0.75},
+    {128, 128, 128, 256, 5.6, 5.6, 0.73, 0.863, 0.863, 0.90, 1.2},
+    {128, 128, 128, 256, 5.45, 5.45, 0.815, 0.932, 0.932, 0.91, 1.1},
+    {128, 64, 128, 256, 4.45, 4.45, 0.415, 0.49, 0.49, 0.91, 0.95},
+    {64, 64, 128, 512, 2.0, 3.8, 0.28, 0.321, 0.542, 0.42, 2.85},
+    {32, 64, 128, 512, 1.4, 3.2, 0.236, 0.258, 0.407, 0.39, 2.9},
 };
 
 // K that is no multiple of 64
@@ -35,9 +35,9 @@ typedef TileCfg<kTileGs, true, 1, 2, 1, 2, 4, 4, 2, 1> R16x64;      // two workg
 
 constexpr int kRagged = 3;
 constexpr TileCost kRaggedCost[kRagged] = {
-    {64, 128, 128, 256, 4.2, 0.83, 0.83},
-    {32, 64, 128, 512, 2.4, 0.54, 0.38},
-    {16, 64, 128, 512, 2.1, 0.53, 0.36},
+    {64, 128, 128, 256, 4.2, 4.2, 0.83, 0.83, 0.83, 0.6, 2.0},
+    {32, 64, 128, 512, 2.4, 2.4, 0.38, 0.38, 0.54, 0.6, 2.0},
+    {16, 64, 128, 512, 2.1, 2.1, 0.36, 0.36, 0.53, 0.6, 2.0},
 };
 
 int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)

@@ -25,6 +25,7 @@ def _sampled(N, seed, most=300):
 TILE_SHAPES = [
     (1030, 8200, 128), (1030, 8201, 192), (2500, 2700, 64), (2048, 3000, 192), (300, 9000, 704), (515, 4099, 256),
     (117, 14340, 4096), (700, 1500, 320), (640, 2500, 1152), (129, 1030, 1088), (65, 1030, 192), (17, 70, 64),
+    (512, 14340, 256), (400, 2050, 320),
 ]
 
 
@@ -44,7 +45,7 @@ def test_tile_2bit(M, N, K):
 # in a byte with 3 weights, in the first half of a 32-k block, and long; N with and without 16-byte stores.
 TILE3_SHAPES = [
     (512, 14340, 4096), (2050, 2056, 1288), (500, 4100, 1600), (1030, 2050, 168), (500, 1030, 648), (700, 1100, 952),
-    (60, 4096, 11008), (500, 600, 328),
+    (60, 4096, 11008), (500, 600, 328), (190, 10000, 488),
 ]
 
 
@@ -66,7 +67,7 @@ def test_tile_1p6(M, N, K, fx):
 TILE_GS_SHAPES = [
     (1030, 8200, 192, 64), (2048, 3000, 192, 128), (300, 9000, 704, 256), (300, 9001, 704, 48), (117, 14340, 4096, 32),
     (640, 2500, 1152, 96), (129, 1030, 1088, 16), (40, 300, 1024, 128), (17, 70, 64, 4096), (16, 333, 4096, 64), (5, 40, 320, 64),
-    (300, 9004, 704, 128), (300, 2050, 1024, 64), (300, 4100, 320, 32),
+    (300, 9004, 704, 128), (300, 2050, 1024, 64), (300, 4100, 320, 32), (512, 14340, 256, 64),
 ]
 
 

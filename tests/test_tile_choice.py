@@ -39,11 +39,12 @@ def test_shapes_beyond_the_form_are_left_to_others():
         assert instance(form, 1 << 25, 16, 100, 16) == -1  # rows past 2^24
 
 
-def test_short_rows_of_two_bit_words():
-    # a block of rows costs the small-M kernel more than its share of W: measured (us, small-M / tiled) 16384 x 512 at M = 192 11.7 / 9.2, 384 18.9 / 14.0, 512
-    # 29.7 / 15.0; 16384 x 1024 at 384 23.0 / 19.1; 2048 x 2048 at 192 8.8 / 6.9.  And where the small-M kernel is ahead: 2048 x 2048 at 48
-    # 5.3 / 6.7, at 96 6.1 / 6.7; 4096 x 4096 at 96 9.0 / 10.3.
-    for M, N, K in ((192, 16384, 512), (384, 16384, 512), (512, 16384, 512), (384, 16384, 1024), (192, 2048, 2048)):
+def test_two_bit_words_at_many_rows():
+    # measured (us), small-M / tiled: 14701 x 2304 at M = 1295 141 / 93, 15104 x 2688 at 1421 152 / 104, 5447 x 1920 at 884 30.9 / 30.4, 16384 x 512
+    # at 192 11.7 / 9.2, 384 18.9 / 14.0, 512 29.7 / 15.0; 16384 x 1024 at 384 23.0 / 19.1; 2048 x 2048 at 192 8.8 / 6.9.  And where the
+    # small-M kernel is ahead: 2048 x 2048 at 48 5.3 / 6.7, at 96 6.1 / 6.7; 4096 x 4096 at 96 9.0 / 10.3.
+    for M, N, K in ((1295, 14701, 2304), (1421, 15104, 2688), (884, 5447, 1920), (192, 16384, 512), (384, 16384, 512), (512, 16384, 512), (384, 16384, 1024),
+                    (192, 2048, 2048)):
         assert tl.tl_ternary_gemm_which(M, N, K) == tl.TL_PATH_MFMA, (M, N, K)
     for M, N, K in ((48, 2048, 2048), (96, 2048, 2048), (96, 4096, 4096), (16, 16384, 512)):
         assert tl.tl_ternary_gemm_which(M, N, K) == tl.TL_PATH_GEMV, (M, N, K)
