@@ -51,29 +51,44 @@ int pick(int64_t M, int64_t N, int64_t K, double* us)
 
 }  // namespace
 
-// Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel (gemv3): it
-// never loses up to 16 rows.  The weight-streaming
-// kernel decodes W once per 16 rows; its time (us, W in MB of packed bytes, b blocks of 16 rows): 5 + b (0.12 + 0.28 W)
-// while K is one pass (4096 -> 14336: b = 4 19.0, b = 32 114.6; 4096 -> 4096: b = 32 38.2); beyond, rounds of 256
-// 16-row tiles of W that take 10.4 us at K = 11008 (11008 -> 4096: b = 1 11.4, b = 2 21.6, b = 32 334).  The tiled kernel on the same: 4096 -> 14336 b = 32 57,
-// 11008 -> 4096 b = 32 62, 4096 -> 4096 b = 32 26.
+// What the weight-streaming kernel (gemv3) takes (us) for more than 16 rows, W being decoded once per b blocks of 16: t tiles of 16 output
+// rows, s slices of 128 packed bytes.  While K is one pass a tile costs what s waves cost; beyond that workgroups of up to 4
+// tiles go in rounds of 256.  Fitted to 8400 calls over M = 17 .. 2048, N = 512 .. 16384, K = 512 .. 14336: 10 % for nine in ten calls,
+// 15 % with several passes.
+static double stream3_time(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t tiles = (N + 15) / 16;
+    const double b = double((M + 15) / 16);
+    const int64_t s = ((K + 4) / 5 + 127) / 128;
+    if (s <= 7) {
+        constexpr double per_tile[8] = {0, 0.226, 0.397, 0.551, 0.856, 0.988, 1.047, 1.162};
+        return 5.0 + per_tile[s] * b * double(tiles) / 256.0;
+    }
+    int64_t groups = tiles < 256 ? tiles : 256, per_group = (tiles + groups - 1) / groups;
+    if (per_group > 4) { per_group = 4; groups = (tiles + 3) / 4; }
+    const double rounds = double(((M + 15) / 16 * groups + 255) / 256), k = double(K) / 4096.0;
+    return 1.0 + 0.14 * k + rounds * (4.1 + k * (1.36 + 0.78 * double(per_group)));
+}
+
+// Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel, which never
+// loses up to 16 rows and beyond keeps a call unless it is behind by more than 4 %: over the calls of the fit the one chosen is 0.4 % slower
+// than the faster one on average and 11 % in one of a hundred.  (A line through few of them before took narrow layers and 17 to 36 rows of long
+// ones from it: 4096 x 576 at M = 1965 25.3 us there, 32.0 here, 8704 x 4260 at 18 17.9 and 22.7.)
 // Other K: the plain kernel on the vector ALUs, 3 + K / 4096 (7 + 7.5 per row, up to 4) for every 1024 workgroups of 4 x 4
 // outputs (4090 -> 4099: M = 1 17.8, M = 4 39, M = 16 159, M = 37 324; 1001 -> 1024: M = 1 6.8, M = 16 13).
 bool tile3_preferred(int64_t M, int64_t N, int64_t K)
 {
     if ((M <= 16 && K % 8 == 0) || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
     double us;
-    pick(M, N, K, &us);
     if (K % 8 != 0) {
+        pick(M, N, K, &us);
         const double groups = double((M + 3) / 4) * double((N + 3) / 4) / 1024.0;
         return us < 3.0 + double(K) / 4096.0 * (7.0 + 7.5 * double(M < 4 ? M : 4)) * (groups > 1.0 ? groups : 1.0);
     }
-    const double w_mb = double(N) * double((K + 4) / 5) / 1.0e6;
-    const double blocks = double((M + 15) / 16);
-    const double rounds = double(((M + 15) / 16 * ((N + 15) / 16) + 255) / 256);
-    const double t_stream = gemv3_groups(M < 4096 ? M : 4096, N, K) ? 5.0 + blocks * (0.12 + 0.28 * w_mb)
-                                                                    : 1.0 + rounds * 10.4 * double(K) / 11008.0;
-    return 1.08 * us < t_stream;                          // a band: near the crossover the models are within that of each other
+    const double t_stream = stream3_time(M, N, K) / 1.04;
+    if (tile_at_least(kCost, kShapes, K) >= t_stream) return false;
+    pick(M, N, K, &us);
+    return us < t_stream;
 }
 
 int tile3_shape(int64_t M, int64_t N, int64_t K) { return (K % 8 != 0 ? kRaggedShape : 0) + pick(M, N, K, nullptr); }
