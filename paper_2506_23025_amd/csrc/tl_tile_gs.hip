@@ -58,28 +58,40 @@ int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
 
 }  // namespace
 
-// Tiled kernel or what would take the call without it (us; W in MB of packed words, b blocks of 16 rows):
-//  * the weight-streaming kernel, which decodes W once per 16 rows: 4.6 + 6 per pass over K beyond the first + b (0.1 +
-//    0.18 W), with groups that are odd multiples of 128 b (0.1 + 0.31 W) (4096 -> 14336, b = 32: 90 and 153; 4096 ->
-//    4096: 32.7 and 48.4; 11008 -> 4096: 91 and 141)
-//  * the plain kernel on the vector ALUs (other groups): 3 + K / 4096 (6.5 + 1.25 per row, up to 16) for every 512
-//    workgroups of 16 x 16 outputs (4096 -> 4096: M = 1 11.3, M = 4 14.6, M = 16 29.8, M = 37 45.8)
+// What the weight-streaming kernel takes (us) for more than 16 rows, W being decoded once per b blocks of 16: t tiles of 16 output rows, s slices
+// of 512 weights, p passes of 8 slices; groups that are odd multiples of 128 need every product twice.  Fitted to 2550 calls over M = 17 ..
+// 2048, N = 512 .. 16384, K = 512 .. 14336: 14 % for nine in ten.
+static double stream_gs_time(int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    const bool whole = group % 256 == 0;
+    const int s = int((K + 511) / 512);
+    const double p = double((s + 7) / 8), b = double((M + 15) / 16), launches = double(((M + 15) / 16 + 31) / 32);
+    const double x = b * double((N + 15) / 16) / 256.0;
+    if (s <= 8) {
+        constexpr double per_whole[9] = {0, 0.132, 0.241, 0.379, 0.443, 0.644, 0.681, 0.712, 0.789};
+        constexpr double per_odd[9] = {0, 0.182, 0.341, 0.615, 0.665, 1.21, 1.29, 1.35, 1.43};
+        return whole ? 4.5 * launches + 0.136 * b + per_whole[s] * x : 4.95 * launches + 0.055 * b + per_odd[s] * x;
+    }
+    return 1.9 + 3.2 * launches * p + 0.1 * b + x * (whole ? 0.0475 * double(s) + 0.71 * p : 0.145 * double(s) + 0.77 * p);
+}
+
+// Tiled kernel or what would take the call without it: the weight-streaming kernel, which never loses up to 16 rows (over the calls of the
+// fit the one chosen is 0.3 % slower than the faster one on average and 17 % in one of a hundred), or, for other groups, the plain kernel on the
+// vector ALUs, 3 + K / 4096 (6.5 + 1.25 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (us; 4096 -> 4096: M = 1
+// 11.3, M = 4 14.6, M = 16 29.8, M = 37 45.8).
 bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
 {
-    if (K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
+    const bool streams = gemv_gs_supports(M, N, K, group);
+    if ((M <= 16 && streams) || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
     double us;
-    pick(M, N, K, group, &us);
-    const double blocks = double((M + 15) / 16);
-    if (gemv_gs_supports(M, N, K, group)) {
-        if (M <= 16) return false;
-        const double w_mb = double(N) * double(K) / 4.0e6;
-        const double passes = double((K + 4095) / 4096);
-        // no band for the streaming kernel: measured at M = 32 to 256 over five layers, groups of 128 and 256, this line loses
-        // nothing, and a band of 8 % kept 4096 -> 14336 at M = 192 (groups of 256) at 39.4 us instead of 32.3, 11008 -> 4096
-        // at M = 64 (groups of 128) at 33.5 instead of 24.4
-        return us < 4.6 + 6.0 * (passes - 1.0) + blocks * (0.1 + (group % 256 == 0 ? 0.18 : 0.31) * w_mb);
+    if (streams) {
+        const double t_stream = stream_gs_time(M, N, K, group);
+        if (tile_at_least(kCost, kShapes, K) >= t_stream) return false;
+        pick(M, N, K, group, &us);
+        return us < t_stream;
     }
-    const double groups = blocks * double((N + 15) / 16) / 512.0;
+    pick(M, N, K, group, &us);
+    const double groups = double((M + 15) / 16) * double((N + 15) / 16) / 512.0;
     return us < 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
 }
 
