@@ -1776,6 +1776,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     bool lean = pol.lean && nb == 1 && gs != 4 && T <= 3;
     int total_groups = 0, kept = 0;
     int64_t w_bytes = 0;                                   // packed words the launch streams
+    bool all_ahead = true;                                 // see below
     for (int j = 0; j < b.count; ++j) {
         lean = lean && b.job[j].slices >= NW && (b.job[j].N & 15) == 0;
         total_groups += wg[j];
@@ -1787,8 +1788,9 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
         // where the last pass has work for half of the waves at most: it skips the others.  Beside that the lean form is (M = 2, 5504 ->
         // 3200 6.9 / 5.9; M = 9, 12224 -> 4992 15.4 / 15.1; M = 1, 11008 -> 4096 8.8 / 7.7).
         const int last = b.job[j].slices % NW;
-        if (gs != 0 && passes(j) > 1 && b.job[j].Mrem <= 4 && r > 1 && last != 0 && 2 * last <= NW) lean = false;
+        if (passes(j) > 1) all_ahead = all_ahead && b.job[j].Mrem <= 4 && r > 1 && last != 0 && 2 * last <= NW;
     }
+    if (gs != 0 && multi_pass && all_ahead) lean = false;
     // The table of records costs the host 0.7 us, which a launch with scales and one pass over K earns back from about 12 MB on (several blocks of rows of a
     // layer, lean over general: below 1 MB 1.09, 2 to 12 MB 1.00 to 1.02, 12 to 16 MB 0.96, beyond 0.93 to 0.95).
     if (gs != 0 && b.count > 1 && !multi_pass && w_bytes < (int64_t(12) << 20)) lean = false;
