@@ -70,11 +70,44 @@ inline double small_m_time(int64_t M, int64_t N, int64_t K)
 // differ by several percent (the same library: 18.3 and 19.6 us for the same launch): beyond 16 rows the small-M kernel keeps a shape
 // unless the models put the tiled kernel ahead by more than 7 %.  Over the calls of the fit the one chosen is 1.0 % slower than the faster one on
 // average and 16 % in one of a hundred; with the constants before 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
-inline bool prefer_small_m(int64_t M, int64_t N, int64_t K)
+inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
 {
-    if (M <= 16) return true;
-    const double t_small = small_m_time(M, N, K);
-    return t_small < 1.07 * tl::mfma_at_least(K) || t_small < 1.07 * tl::mfma_time(M, N, K);
+    KernelChoice c{gemv_supports(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (!c.streams || M <= 16 || !mfma_supports(M, N, K)) return c;
+    c.stream = small_m_time(M, N, K);
+    const bool two_blocks = gemv_two_blocks(M, N, K);
+    const double passes = double((K + 4095) / 4096);
+    if (passes == 1.0) c.launch = two_blocks ? 5.0 : 4.5;
+    else if (!two_blocks && double((M + 15) / 16) * double((N + 15) / 16) >= 512.0) c.launch = 4.5;
+    c.launches = double((M + (two_blocks ? 31 : 15)) / (two_blocks ? 32 : 16)) / 32.0;
+    c.fixed = c.launch * (c.launches > 1.0 ? double(int64_t(c.launches + 0.999)) : 1.0);
+    c.tiled = c.stream;
+    if (1.07 * mfma_at_least(K) <= c.stream) c.tiled = 1.07 * mfma_time(M, N, K);
+    return c;
+}
+
+// Enqueues the jobs of a grouped call, 64 at a time: `fuse` adds one to the shared launches, `flush` sends those, `single` calls one by itself.
+template <class Job, class Choice, class Fuse, class Flush, class Single>
+tl_status run_grouped(const Job* jobs, int64_t count, Choice&& choice, Fuse&& fuse, Flush&& flush, Single&& single)
+{
+    for (int64_t first = 0; first < count; first += 64) {
+        const int n = int(count - first < 64 ? count - first : 64);
+        KernelChoice c[64];
+        bool tiled[64];
+        for (int j = 0; j < n; ++j) c[j] = choice(jobs[first + j]);
+        choose_grouped(c, n, tiled);
+        for (int j = 0; j < n; ++j) {
+            if (c[j].streams && !tiled[j]) {
+                fuse(jobs[first + j]);
+            } else {
+                const tl_status st = single(jobs[first + j]);
+                if (st != TL_OK) return st;
+            }
+        }
+        const tl_status st = flush();
+        if (st != TL_OK) return st;
+    }
+    return TL_OK;
 }
 
 }  // namespace
@@ -100,7 +133,8 @@ tl_status tl_unpack_dev(tl_format fmt, const void* packed, int64_t N, int64_t K,
 tl_path tl_ternary_gemm_which(int64_t M, int64_t N, int64_t K)
 {
     if (!tl::dims_ok(M, N, K)) return TL_PATH_AUTO;
-    if (tl::gemv_supports(M, N, K) && (!tl::mfma_supports(M, N, K) || tl::prefer_small_m(M, N, K))) return TL_PATH_GEMV;
+    const tl::KernelChoice c = tl::choice_2bit(M, N, K);
+    if (c.streams && !(c.tiled < c.stream)) return TL_PATH_GEMV;
     if (tl::mfma_supports(M, N, K)) return TL_PATH_MFMA;
     return TL_PATH_GENERIC;
 }
@@ -155,30 +189,21 @@ tl_status tl_ternary_gemm_grouped(const tl_gemm_job* jobs, int64_t count, void* 
         if (!tl::aligned16(j.x) || !tl::aligned16(j.Wpacked) || !tl::aligned16(j.y)) return TL_ERR_ALIGN;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Jobs the small-M kernel takes are fused; the others go through tl_ternary_gemm one by one.
+    // Jobs the small-M kernel takes share launches; the others go through tl_ternary_gemm one by one.
     tl::GemmDesc fused[64];
     int nf = 0;
-    auto flush = [&]() -> tl_status {
-        if (nf == 0) return TL_OK;
-        const hipError_t e = tl::launch_gemv_jobs(fused, nf, s);
-        nf = 0;
-        return tl::from_hip(e);
-    };
-    for (int64_t i = 0; i < count; ++i) {
-        const tl_gemm_job& j = jobs[i];
-        if (tl_ternary_gemm_which(j.M, j.N, j.K) == TL_PATH_GEMV) {
+    return tl::run_grouped(
+        jobs, count, [](const tl_gemm_job& j) { return tl::choice_2bit(j.M, j.N, j.K); },
+        [&](const tl_gemm_job& j) {
             fused[nf++] = tl::GemmDesc{static_cast<const __half*>(j.x), static_cast<const uint32_t*>(j.Wpacked),
-                                       static_cast<__half*>(j.y), tl::half_bits_to_float(j.gamma_fp16_bits),
-                                       j.M, j.N, j.K};
-            if (nf == 64) { const tl_status st = flush(); if (st != TL_OK) return st; }
-        } else {
-            tl_status st = flush();
-            if (st != TL_OK) return st;
-            st = tl_ternary_gemm(j.x, j.Wpacked, j.gamma_fp16_bits, j.y, j.M, j.N, j.K, stream);
-            if (st != TL_OK) return st;
-        }
-    }
-    return flush();
+                                       static_cast<__half*>(j.y), tl::half_bits_to_float(j.gamma_fp16_bits), j.M, j.N, j.K};
+        },
+        [&] {
+            const hipError_t e = nf ? tl::launch_gemv_jobs(fused, nf, s) : hipSuccess;
+            nf = 0;
+            return tl::from_hip(e);
+        },
+        [&](const tl_gemm_job& j) { return tl_ternary_gemm(j.x, j.Wpacked, j.gamma_fp16_bits, j.y, j.M, j.N, j.K, stream); });
 }
 
 namespace {
@@ -266,25 +291,20 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
     // tiled kernel is faster, go one by one.
     tl::Gemm3Desc fused[64];
     int nf = 0;
-    auto flush = [&]() -> tl_status {
-        if (nf == 0) return TL_OK;
-        const hipError_t e = tl::launch_gemv3_jobs(fused, nf, fx, s);
-        nf = 0;
-        return tl::from_hip(e);
-    };
-    for (int64_t i = 0; i < count; ++i) {
-        const tl_gemm_job& j = jobs[i];
-        if (tl::gemv3_groups(j.M, j.N, j.K) && !tl::tile3_preferred(j.M, j.N, j.K)) {
+    return tl::run_grouped(
+        jobs, count,
+        [](const tl_gemm_job& j) { return j.K % 8 == 0 ? tl::tile3_choice(j.M, j.N, j.K) : tl::KernelChoice{false, 0.0, 0.0, 0.0, 0.0, 0.0}; },
+        [&](const tl_gemm_job& j) {
             fused[nf++] = tl::Gemm3Desc{static_cast<const __half*>(j.x), static_cast<const uint8_t*>(j.Wpacked),
                                         static_cast<__half*>(j.y), tl::half_bits_to_float(j.gamma_fp16_bits),
                                         j.M, j.N, j.K, static_cast<int64_t>(tl_row_stride_bytes(TL_FMT_1P6BIT, j.K))};
-            if (nf == 64) { const tl_status st = flush(); if (st != TL_OK) return st; }
-        } else {
-            const tl_status st = gemm_1p6(j.x, j.Wpacked, j.gamma_fp16_bits, j.y, j.M, j.N, j.K, stream, fx);
-            if (st != TL_OK) return st;
-        }
-    }
-    return flush();
+        },
+        [&] {
+            const hipError_t e = nf ? tl::launch_gemv3_jobs(fused, nf, fx, s) : hipSuccess;
+            nf = 0;
+            return tl::from_hip(e);
+        },
+        [&](const tl_gemm_job& j) { return gemm_1p6(j.x, j.Wpacked, j.gamma_fp16_bits, j.y, j.M, j.N, j.K, stream, fx); });
 }
 
 tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, void* stream)
@@ -304,25 +324,18 @@ tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, 
     // kernel is faster, go one by one.
     tl::GemmGsDesc fused[64];
     int nf = 0;
-    auto flush = [&]() -> tl_status {
-        if (nf == 0) return TL_OK;
-        const hipError_t e = tl::launch_gemv_gs_jobs(fused, nf, s);
-        nf = 0;
-        return tl::from_hip(e);
-    };
-    for (int64_t i = 0; i < count; ++i) {
-        const tl_gemm_gs_job& j = jobs[i];
-        if (tl::gemv_gs_supports(j.M, j.N, j.K, j.group) && !tl::tile_gs_preferred(j.M, j.N, j.K, j.group)) {
+    return tl::run_grouped(
+        jobs, count, [](const tl_gemm_gs_job& j) { return tl::tile_gs_choice(j.M, j.N, j.K, j.group); },
+        [&](const tl_gemm_gs_job& j) {
             fused[nf++] = tl::GemmGsDesc{static_cast<const __half*>(j.x), static_cast<const uint32_t*>(j.Wpacked),
-                                         static_cast<const __half*>(j.scales), static_cast<__half*>(j.y),
-                                         j.M, j.N, j.K, j.group};
-            if (nf == 64) { const tl_status st = flush(); if (st != TL_OK) return st; }
-        } else {
-            const tl_status st = tl_ternary_gemm_gs(j.x, j.Wpacked, j.scales, j.group, j.y, j.M, j.N, j.K, stream);
-            if (st != TL_OK) return st;
-        }
-    }
-    return flush();
+                                         static_cast<const __half*>(j.scales), static_cast<__half*>(j.y), j.M, j.N, j.K, j.group};
+        },
+        [&] {
+            const hipError_t e = nf ? tl::launch_gemv_gs_jobs(fused, nf, s) : hipSuccess;
+            nf = 0;
+            return tl::from_hip(e);
+        },
+        [&](const tl_gemm_gs_job& j) { return tl_ternary_gemm_gs(j.x, j.Wpacked, j.scales, j.group, j.y, j.M, j.N, j.K, stream); });
 }
 
 // For the tests, which assert what they run; not part of the interface.  form: 0 2-bit words, 1 a 1.6-bit code, 2 group scales, 3 2-bit words on
@@ -338,6 +351,20 @@ __attribute__((visibility("default"))) int tl_internal_tile_instance(int form, i
         case 3: return tl::mfma_supports(M, N, K) ? tl::mfma_shape(M, N, K) : -1;
         default: return -1;
     }
+}
+
+// Likewise: which of a grouped call's jobs (M, N, K, group each) the tiled kernel takes where the streaming one could.
+__attribute__((visibility("default"))) void tl_internal_grouped_tiled(int form, const int64_t* jobs, int count, int* out)
+{
+    tl::KernelChoice c[64];
+    bool tiled[64];
+    if (count > 64) count = 64;
+    for (int j = 0; j < count; ++j) {
+        const int64_t M = jobs[4 * j], N = jobs[4 * j + 1], K = jobs[4 * j + 2], group = jobs[4 * j + 3];
+        c[j] = form == 0 ? tl::choice_2bit(M, N, K) : (form == 1 ? tl::tile3_choice(M, N, K) : tl::tile_gs_choice(M, N, K, group));
+    }
+    tl::choose_grouped(c, count, tiled);
+    for (int j = 0; j < count; ++j) out[j] = tiled[j] ? 1 : 0;
 }
 
 tl_status tl_init(void)

@@ -1,5 +1,6 @@
 // Internal declarations shared by the .hip translation units of libtl.so.
 #pragma once
+#include "tl_choice.hpp"
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
@@ -104,11 +105,13 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
 
 // Tiled matrix-core kernel for group scales, and whether it is the faster one for a shape.
 bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group);
+KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group);
 hipError_t launch_tile_gs(const __half* x, const uint32_t* Wp, const __half* scales, int64_t group, __half* y,
                           int64_t M, int64_t N, int64_t K, hipStream_t s);
 
 // Tiled matrix-core kernel for the 1.6-bit formats, and whether it is the faster one for a shape.
 bool tile3_preferred(int64_t M, int64_t N, int64_t K);
+KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K);
 hipError_t launch_tile3(const __half* x, const uint8_t* Wp, int64_t stride, float gamma, __half* y,
                         int64_t M, int64_t N, int64_t K, bool fx, hipStream_t s);
 

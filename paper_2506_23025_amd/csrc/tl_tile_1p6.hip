@@ -85,10 +85,25 @@ bool tile3_preferred(int64_t M, int64_t N, int64_t K)
         const double groups = double((M + 3) / 4) * double((N + 3) / 4) / 1024.0;
         return us < 3.0 + double(K) / 4096.0 * (7.0 + 7.5 * double(M < 4 ? M : 4)) * (groups > 1.0 ? groups : 1.0);
     }
-    const double t_stream = stream3_time(M, N, K) / 1.04;
-    if (tile_at_least(kCost, kShapes, K) >= t_stream) return false;
+    const KernelChoice c = tile3_choice(M, N, K);
+    return c.tiled < c.stream;
+}
+
+// K % 8 == 0
+KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
+{
+    KernelChoice c{gemv3_groups(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (M <= 16 || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return c;
+    c.stream = stream3_time(M, N, K);
+    c.launch = c.streams ? 4.5 : 0.0;
+    c.fixed = c.launch;                                    // of its own it is one launch, however many rows
+    c.launches = double((M + 15) / 16) / 32.0;
+    c.tiled = c.stream;
+    if (1.04 * tile_at_least(kCost, kShapes, K) >= c.stream) return c;
+    double us;
     pick(M, N, K, &us);
-    return us < t_stream;
+    c.tiled = 1.04 * us;
+    return c;
 }
 
 int tile3_shape(int64_t M, int64_t N, int64_t K) { return (K % 8 != 0 ? kRaggedShape : 0) + pick(M, N, K, nullptr); }

@@ -83,16 +83,28 @@ bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
 {
     const bool streams = gemv_gs_supports(M, N, K, group);
     if ((M <= 16 && streams) || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
-    double us;
     if (streams) {
-        const double t_stream = stream_gs_time(M, N, K, group);
-        if (tile_at_least(kCost, kShapes, K) >= t_stream) return false;
-        pick(M, N, K, group, &us);
-        return us < t_stream;
+        const KernelChoice c = tile_gs_choice(M, N, K, group);
+        return c.tiled < c.stream;
     }
+    double us;
     pick(M, N, K, group, &us);
     const double groups = double((M + 15) / 16) * double((N + 15) / 16) / 512.0;
     return us < 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
+}
+
+KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    KernelChoice c{gemv_gs_supports(M, N, K, group), 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (!c.streams || M <= 16) return c;
+    c.stream = stream_gs_time(M, N, K, group);
+    c.launch = 4.5;
+    c.launches = double((M + 15) / 16) / 32.0;
+    c.fixed = c.launch * (c.launches > 1.0 ? double(int64_t(c.launches + 0.999)) : 1.0);
+    c.tiled = c.stream;
+    if (tile_at_least(kCost, kShapes, K) >= c.stream) return c;
+    pick(M, N, K, group, &c.tiled);
+    return c;
 }
 
 int tile_gs_shape(int64_t M, int64_t N, int64_t K, int64_t group) { return (K % 64 != 0 ? kRaggedShape : 0) + pick(M, N, K, group, nullptr); }

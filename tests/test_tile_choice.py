@@ -9,12 +9,23 @@ _instance.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 4
 _instance.restype = ctypes.c_int
 
 TWO_BIT, ONE_POINT_SIX, SCALES, TWO_BIT_FORCED = range(4)
+_grouped = tl.raw().tl_internal_grouped_tiled
+_grouped.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+_grouped.restype = None
 RAGGED = 100                                               # first instance of the forms for odd K
 
 
 def instance(form, M, N, K, group=0):
     """Place of the tiled kernel's instance in the table of its form, or -1 where another kernel takes the call."""
     return _instance(form, M, N, K, group)
+
+
+def grouped(form, jobs):
+    """Per job (M, N, K[, group]) of a grouped call, whether the tiled kernel takes it from the launches the others share."""
+    flat = (ctypes.c_int64 * (4 * len(jobs)))(*[v for j in jobs for v in (tuple(j) + (0,))[:4]])
+    out = (ctypes.c_int * len(jobs))()
+    _grouped(form, flat, len(jobs), out)
+    return [bool(v) for v in out]
 
 
 def test_tile_shapes_reach_every_instance():
@@ -58,3 +69,24 @@ def test_one_point_six_bit_codes_at_many_rows():
         assert instance(ONE_POINT_SIX, M, N, K) == -1, (M, N, K)
     for M, N, K in ((512, 14336, 4096), (64, 4096, 11008), (805, 15020, 704)):
         assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
+
+
+def test_grouped_jobs_share_launches_where_that_is_faster():
+    # measured (us), all streaming / each as if alone: 16 layers at M = 256, 2-bit words 512 x 1024 68.7 / 83.2, 768 x 2048 87.2 / 108.3, 1.6-bit codes
+    # 512 x 1024 102.5 / 119.6
+    for form, M, N, K in ((TWO_BIT, 256, 512, 1024), (TWO_BIT, 256, 768, 2048), (ONE_POINT_SIX, 256, 512, 1024)):
+        assert not any(grouped(form, [(M, N, K)] * 16)), (form, M, N, K)
+
+    def block(M, group=0):
+        return [(M, 12288, 4096, group), (M, 4096, 4096, group), (M, 22016, 4096, group), (M, 4096, 11008, group)]
+
+    assert not any(grouped(SCALES, block(32, 128)))
+    assert all(grouped(SCALES, block(256, 128)))           # 662 / 132
+    assert all(grouped(ONE_POINT_SIX, [(256, n, k) for _, n, k, _ in block(256)][:3]))
+    # a job alone is taken as its single call takes it, and what a group tiles a single call tiles too
+    for form, group in ((TWO_BIT, 0), (ONE_POINT_SIX, 0), (SCALES, 128), (SCALES, 256)):
+        for M in (16, 17, 40, 100, 250, 600, 2000):
+            for N, K in ((512, 512), (1024, 2048), (4096, 4096), (14336, 4096), (768, 4096), (16384, 512)):
+                alone = instance(form, M, N, K, group) >= 0
+                assert grouped(form, [(M, N, K, group)]) == [alone], (form, M, N, K)
+                assert alone or not any(grouped(form, [(M, N, K, group)] * 5)), (form, M, N, K)
