@@ -36,8 +36,8 @@ constexpr int64_t kGemvMaxM = 4096;
 // What the small-M kernel takes (us) for more than 16 rows: t tiles of 16 output rows, b blocks of 16 or 32 activation rows, s slices of
 // 512 weights, p passes of 8 slices.  In one pass a block costs its activations and a share of every tile, which depends on s
 // alone (a workgroup has s waves, and as many more workgroups fit as 8 / s allows), not on the bytes of W.  Fitted with the
-// tiled kernel's times (see TileCost): 10 % for nine in ten calls, 15 % with several passes.  The one line that is older is that of blocks
-// of 32 rows with 8 slices: it is 0.8 of the time for most N, and right where t b is a multiple of 256.
+// tiled kernel's times (see TileCost): 10 % for nine in ten calls, 15 % with several passes.  The one line that is older is that of up to
+// 16 blocks of 32 rows with 8 slices: it is 0.8 of the time for most N, and right where t b is a multiple of 256.
 inline double small_m_time(int64_t M, int64_t N, int64_t K)
 {
     const int s = int((K + 511) / 512);
@@ -51,8 +51,8 @@ inline double small_m_time(int64_t M, int64_t N, int64_t K)
             const int64_t tiles = (N + 15) / 16, cap = tiles >= 4096 ? 1 : 4096 / tiles;
             return 5.16 * p * double((blocks + cap - 1) / cap) + 0.51 * b + b * t / 256.0 * (0.09 * double(s) + 0.49 * p);
         }
-        if (s == 8) return 4.0 + b * (0.31 + 0.2 * double(N) * double(K) / 4.0e6);
-        constexpr double per_tile[8] = {0, 0, 0.334, 0.63, 0.53, 0.82, 0.87, 0.95};
+        if (s == 8 && blocks <= 16) return 4.0 + b * (0.31 + 0.2 * double(N) * double(K) / 4.0e6);
+        constexpr double per_tile[9] = {0, 0, 0.334, 0.63, 0.53, 0.82, 0.87, 0.95, 1.02};
         return 5.8 * double((blocks + 31) / 32) + 0.148 * b + per_tile[s] * b * t / 256.0;
     }
     const int64_t blocks = (M + 15) / 16;
@@ -68,8 +68,8 @@ inline double small_m_time(int64_t M, int64_t N, int64_t K)
 
 // Small-M kernel or tiled matrix-core kernel, when both can run the shape.  A band rather than the bare comparison decides, since machines
 // differ by several percent (the same library: 18.3 and 19.6 us for the same launch): beyond 16 rows the small-M kernel keeps a shape
-// unless the models put the tiled kernel ahead by more than 7 %.  Over the calls of the fit the one chosen is 1.0 % slower than the faster one on
-// average and 16 % in one of a hundred; with the constants before 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
+// unless the models put the tiled kernel ahead by more than 7 %.  Over the calls of the fit the one chosen is 0.5 % slower than the best on
+// average and 12 % in one of a hundred; with the constants before 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
 inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
 {
     KernelChoice c{gemv_supports(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};

@@ -61,18 +61,20 @@ static double stream3_time(int64_t M, int64_t N, int64_t K)
     const double b = double((M + 15) / 16);
     const int64_t s = ((K + 4) / 5 + 127) / 128;
     if (s <= 7) {
-        constexpr double per_tile[8] = {0, 0.226, 0.397, 0.551, 0.856, 0.988, 1.047, 1.162};
-        return 5.0 + per_tile[s] * b * double(tiles) / 256.0;
+        constexpr double start[8] = {0, 4.8, 5.0, 4.9, 4.65, 5.15, 5.3, 5.6};
+        constexpr double per_tile[8] = {0, 0.22, 0.386, 0.542, 0.859, 0.952, 1.0, 1.086};
+        return start[s] + 0.003 * double(s) * b + per_tile[s] * b * double(tiles) / 256.0;
     }
     int64_t groups = tiles < 256 ? tiles : 256, per_group = (tiles + groups - 1) / groups;
     if (per_group > 4) { per_group = 4; groups = (tiles + 3) / 4; }
-    const double rounds = double(((M + 15) / 16 * groups + 255) / 256), k = double(K) / 4096.0;
-    return 1.0 + 0.14 * k + rounds * (4.1 + k * (1.36 + 0.78 * double(per_group)));
+    const double share = b * double(groups) / 256.0, rounds = double(((M + 15) / 16 * groups + 255) / 256);
+    const double k = double(K) / 4096.0, T = double(per_group), passes = double((s + 6) / 7);
+    return 1.25 + 0.08 * k + rounds * (2.2 + 1.85 * passes + k * (0.15 + 0.05 * T)) + (share > 1.0 ? share : 1.0) * k * (0.15 + 0.675 * T);
 }
 
 // Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel, which never
-// loses up to 16 rows and beyond keeps a call unless it is behind by more than 4 %: over the calls of the fit the one chosen is 0.4 % slower
-// than the faster one on average and 11 % in one of a hundred.  (A line through few of them before took narrow layers and 17 to 36 rows of long
+// loses up to 16 rows: over the calls of the fit the one chosen is 0.2 % slower than the best on average and 6 % in one of
+// a hundred.  (A line through few of them before took narrow layers and 17 to 36 rows of long
 // ones from it: 4096 x 576 at M = 1965 25.3 us there, 32.0 here, 8704 x 4260 at 18 17.9 and 22.7.)
 // Other K: the plain kernel on the vector ALUs, 3 + K / 4096 (7 + 7.5 per row, up to 4) for every 1024 workgroups of 4 x 4
 // outputs (4090 -> 4099: M = 1 17.8, M = 4 39, M = 16 159, M = 37 324; 1001 -> 1024: M = 1 6.8, M = 16 13).
@@ -99,10 +101,9 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
     c.fixed = c.launch;                                    // of its own it is one launch, however many rows
     c.launches = double((M + 15) / 16) / 32.0;
     c.tiled = c.stream;
-    if (1.04 * tile_at_least(kCost, kShapes, K) >= c.stream) return c;
-    double us;
-    pick(M, N, K, &us);
-    c.tiled = 1.04 * us;
+    if (tile_at_least(kCost, kShapes, K) >= c.stream) return c;
+    pick(M, N, K, &c.tiled);
+    if ((K + 4) / 5 > 7 * 128) c.tiled *= 1.05;           // several passes: the streaming kernel's time is less certain
     return c;
 }
 

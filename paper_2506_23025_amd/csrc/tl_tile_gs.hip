@@ -60,7 +60,8 @@ int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
 
 // What the weight-streaming kernel takes (us) for more than 16 rows, W being decoded once per b blocks of 16: t tiles of 16 output rows, s slices
 // of 512 weights, p passes of 8 slices; groups that are odd multiples of 128 need every product twice.  Fitted to 2550 calls over M = 17 ..
-// 2048, N = 512 .. 16384, K = 512 .. 14336: 14 % for nine in ten.
+// 2048, N = 512 .. 16384, K = 512 .. 14336: 14 % for nine in ten, 20 % with
+// several passes.
 static double stream_gs_time(int64_t M, int64_t N, int64_t K, int64_t group)
 {
     const bool whole = group % 256 == 0;
@@ -76,7 +77,7 @@ static double stream_gs_time(int64_t M, int64_t N, int64_t K, int64_t group)
 }
 
 // Tiled kernel or what would take the call without it: the weight-streaming kernel, which never loses up to 16 rows (over the calls of the
-// fit the one chosen is 0.3 % slower than the faster one on average and 17 % in one of a hundred), or, for other groups, the plain kernel on the
+// fit the one chosen is 0.2 % slower than the best on average and 6 % in one of a hundred), or, for other groups, the plain kernel on the
 // vector ALUs, 3 + K / 4096 (6.5 + 1.25 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (us; 4096 -> 4096: M = 1
 // 11.3, M = 4 14.6, M = 16 29.8, M = 37 45.8).
 bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
@@ -104,6 +105,7 @@ KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group)
     c.tiled = c.stream;
     if (tile_at_least(kCost, kShapes, K) >= c.stream) return c;
     pick(M, N, K, group, &c.tiled);
+    if (K > 4096) c.tiled *= 1.1;                          // the streaming kernel's time is less certain there: 20 % for nine in ten
     return c;
 }
 

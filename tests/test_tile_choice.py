@@ -62,10 +62,10 @@ def test_two_bit_words_at_many_rows():
 
 
 def test_one_point_six_bit_codes_at_many_rows():
-    # measured (us), streaming / tiled: narrow layers 4096 x 576 at M = 1965 25.6 / 31.8, 4224 x 832 at 1311 25.2 / 33.4, 1024 x 64 at 2048 6.4 /
-    # 7.3; 17 to 36 rows of long ones 8704 x 4260 at 18 17.9 / 22.7, 13184 x 5554 at 19 25.1 / 31.5; and the other way round 4096 x 14336 at 512
-    # 112 / 58, 11008 x 4096 at 64 42 / 27, 704 x 15020 at 805 73 / 47
-    for M, N, K in ((1965, 576, 4096), (1311, 832, 4224), (2048, 64, 1024), (18, 4260, 8704), (19, 5554, 13184)):
+    # measured (us), streaming / best tile: narrow layers 4224 x 832 at M = 1311 25.2 / 27.5, 1024 x 64 at 2048 6.4 / 7.3; 17 to 36 rows of long
+    # ones 8704 x 4260 at 18 17.9 / 22.7, 13184 x 5554 at 19 25.1 / 31.5, 6776 x 4928 at 21 15.5 / 18.4; and the other way round 4096 x 14336
+    # at 512 112 / 58, 11008 x 4096 at 64 42 / 27, 704 x 15020 at 805 73 / 47
+    for M, N, K in ((1311, 832, 4224), (2048, 64, 1024), (18, 4260, 8704), (19, 5554, 13184), (21, 4928, 6776)):
         assert instance(ONE_POINT_SIX, M, N, K) == -1, (M, N, K)
     for M, N, K in ((512, 14336, 4096), (64, 4096, 11008), (805, 15020, 704)):
         assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
