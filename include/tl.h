@@ -58,7 +58,8 @@ typedef enum tl_format {
 /* Kernel choice for tl_ternary_gemm_path.  AUTO is what tl_ternary_gemm uses. */
 typedef enum tl_path {
     TL_PATH_AUTO = 0,
-    TL_PATH_GENERIC = 1, /* plain VALU kernel, any M, N, K                        */
+    TL_PATH_GENERIC = 1, /* any M, N, K: forced, the plain VALU kernel; as the choice named by
+                            tl_ternary_gemm_which, that or the tiled kernel's form for odd K */
     TL_PATH_GEMV = 2,    /* weight-streaming small-M kernel: M <= 16 per pass     */
     TL_PATH_MFMA = 3,    /* tiled fp16 MFMA kernel for many rows                 */
     TL_PATH_INT_RANGE_ = 0x7fffffff /* not a path (see TL_FMT_INT_RANGE_)         */
@@ -188,7 +189,8 @@ tl_status tl_ternary_gemm_path(const void* x, const void* Wpacked, uint16_t gamm
  * of (x, W, gamma, y).  Each job has the contract of tl_ternary_gemm.  No job reads what
  * another writes, and jobs must not alias
  * each other's outputs; they are enqueued in as few kernel launches as possible (jobs that
- * go to the small-M kernel share launches, 16 blocks of 16 activation rows per launch) and
+ * go to the small-M kernel share launches, 32 blocks of 16 or 32 activation rows per launch; a
+ * job of many rows goes to the tiled kernel where that pays for a launch of its own) and
  * may run concurrently.  `jobs` is host memory, read before the call returns.
  */
 typedef struct tl_gemm_job {

@@ -7,11 +7,11 @@
 // WK sets that share the NP 32-k blocks of a step out among them, and WM x WN waves per set, each with
 // FM x FN fragments of v_mfma_f32_16x16x32_f16.
 //
-//  * What bounds it: at full size the chip's power.  A loop of nothing but the matrix instruction on this data gives
-//    1.85 (32x32x16, W as the row operand), 2.0 (32x32x16, X as the row operand) and 2.3 PFLOP/s (16x16x32), so
-//    the 16x16x32 form is used; without the X fragment reads the kernel is 20 % faster, without the decode 6 %.
-//    Small tiles are bound by instruction issue (11 vector operations of decode per FM matrix instructions) and by
-//    the start and end of a launch (5 to 6 us of it in a 20 us call).
+//  * What bounds it: at full size the matrix pipes are busy 0.58 of the time; without the X fragment reads the kernel is
+//    20 % faster, without the decode 6 %, on zero operands, i.e. at the highest clock, 10 %.  Bare loops of the matrix
+//    instruction on this data gave 1.85 (32x32x16, W as the row operand), 2.0 (32x32x16, X as the row operand) and 2.3
+//    PFLOP/s (16x16x32), so the 16x16x32 form is used.  Small tiles are bound by latency: the start and end of a launch (5 to 6 us
+//    of a 20 us call) and the barrier of each step; no unit is busy for more than 0.36 of the time.
 //  * X goes to LDS as it lies in memory, by LDS-DMA (global_load_lds_dwordx4: no registers, no
 //    vector instructions), ST steps ahead.  16-byte pieces of a row are swizzled by row on the way
 //    in so that the fragment reads are free of bank conflicts.
@@ -60,7 +60,7 @@ struct TileParams {
 
 // RAGGED: K (at least 8) is not a multiple of 64 (2-bit) or 8 (1.6-bit): rows of X and W start anywhere, X goes
 // through registers (masked past K) and 2-bit words are fetched one by one.
-// UNIT: blocks per scale unit (kTileGs): NB, or 1 when groups are shorter than a set's part of a step.
+// UNIT: 16-k blocks per scale that is fetched (kTileGs): a set's part of a step, 2 NB of them, or 1, which takes any group.
 template <int FMT_, bool RAGGED_, int FM_, int FN_, int WM_, int WN_, int WK_, int NP_, int ST_, int UNIT_ = 1>
 struct TileCfg {
     static constexpr int FMT = FMT_, FM = FM_, FN = FN_, WM = WM_, WN = WN_, WK = WK_, NP = NP_;
@@ -124,7 +124,7 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
 }
 
-// The transfers are written out by hand (LDS base in M0, lane l lands at base + 16 l or + 4 l): a transfer
+// The transfers are written out by hand (LDS base in M0, lane l lands at base + 16 l, of 2 bytes at base + 4 l): a transfer
 // the compiler knows of makes it drain the memory pipeline before every later LDS access.  Every
 // wait for them is an explicit wait_vm.  gfx950 asks for one wait state between a scalar write of M0 and the transfer that
 // reads it; the compiler adds it for its own transfers and looks into no string, so it stands here (dma16_lanes has
@@ -139,10 +139,6 @@ __device__ __forceinline__ void dma16_lanes(uint32_t voff, const void* sbase, ui
 {
     asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
                  : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)), "s"(mask) : "memory");
-}
-__device__ __forceinline__ void dma4(uint32_t voff, const void* sbase, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 __device__ __forceinline__ void dma2(uint32_t voff, const void* sbase, uint32_t lds)   // zero-extended to a dword
 {
