@@ -44,9 +44,8 @@ __device__ __forceinline__ void digits5(unsigned v, bool fx, unsigned (&d)[5])
 // this 4.1), and where rows are shorter than a piece as many as it takes; the pieces across the ends of the array go
 // weight by weight.
 // FMT: 0 2-bit words, 1 plain base-3 bytes, 2 fixed-point bytes.
-constexpr int kUnpackPieces = 4;             // pieces per thread: their fetches are in flight together
-
-template <int FMT>
+// kUnpackPieces: pieces per thread, whose fetches are in flight together.
+template <int FMT, int kUnpackPieces>
 __global__ void __launch_bounds__(256)
 unpack_kernel(const unsigned char* __restrict__ packed, int64_t K, int64_t stride, int64_t total, int head,
               int8_t* __restrict__ out)
@@ -409,14 +408,22 @@ inline unsigned blocks_for(int64_t items, int per_block)
 
 namespace {
 
-template <int FMT>
+template <int FMT, int PIECES>
 hipError_t launch_unpack(const void* packed, int64_t N, int64_t K, int64_t stride, int8_t* out, hipStream_t s)
 {
     const int64_t total = N * K;
     const int head = int(reinterpret_cast<uintptr_t>(out) & 15u);         // bytes of the first 16-byte piece before the array
-    hipLaunchKernelGGL(unpack_kernel<FMT>, dim3(blocks_for(total + head, 256 * 16 * kUnpackPieces)), dim3(256), 0, s,
+    hipLaunchKernelGGL((unpack_kernel<FMT, PIECES>), dim3(blocks_for(total + head, 256 * 16 * PIECES)), dim3(256), 0, s,
                        static_cast<const unsigned char*>(packed), K, stride, total, head, out);
     return hipGetLastError();
+}
+
+// Four pieces per thread where that leaves a workgroup for every CU; below, one, or most CUs have nothing to do and the others a long chain
+// (from 1.6-bit bytes, us: 4096 x 300 4.03 with four, 3.53 with one; 4096 x 1000 4.11, 3.56).
+template <int FMT>
+hipError_t launch_unpack(const void* packed, int64_t N, int64_t K, int64_t stride, int8_t* out, hipStream_t s)
+{
+    return N * K >= 256 * 256 * 16 * 4 ? launch_unpack<FMT, 4>(packed, N, K, stride, out, s) : launch_unpack<FMT, 1>(packed, N, K, stride, out, s);
 }
 
 }  // namespace

@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 # K below, at and past a piece, many rows to a piece, a piece across rows in every position, more than one block of
 # 16384 weights, K far from and just off multiples of 16 and 5; the output starting at every kind of address.
-@pytest.mark.parametrize("N,K", [(1, 1), (1000, 3), (17, 15), (64, 16), (9, 33), (40, 1000), (5, 16384), (3, 16399), (129, 4095), (16, 4096)])
+@pytest.mark.parametrize("N,K", [(1, 1), (1000, 3), (17, 15), (64, 16), (9, 33), (40, 1000), (5, 16384), (3, 16399), (129, 4095), (16, 4096),
+                                 # four pieces per thread from 2^22 weights on: whole blocks, a last one of a few pieces, rows across pieces
+                                 (1024, 4096), (1100, 4095), (13107, 321)])
 @pytest.mark.parametrize("offset", [0, 1, 7, 15])
 def test_unpack_any_row_and_address(N, K, offset):
     import torch
