@@ -16,10 +16,9 @@
 //    vector instructions), ST steps ahead.  16-byte pieces of a row are swizzled by row on the way
 //    in so that the fragment reads are free of bank conflicts.
 //  * W stays packed in LDS: a 2-bit word holds 16 codes of one column, 1/8 of the bytes of fp16.  A lane
-//    (column i, k quarter g) needs half a word as pairs of neighbours: with t = w >> 2, one byte permute of
-//    (w, t) puts code 2q at bit 4q and code 2q + 1 at bit 4q + 16.  `& mask | 0x64006400` makes an fp16
-//    pair (1024 + 16^q c), one packed fma turns it into (c - 1) exactly: 11 vector operations per 8 weights
-//    and lane, and a decoded operand feeds FM matrix instructions.
+//    (column i, k quarter g) needs half a word as pairs of neighbours: one byte permute, one shift, and per pair one mask and one packed
+//    fma (decode8_codes, decode8_values): 10 vector operations per 8 weights and lane, spread between the matrix instructions of a
+//    fragment, and a decoded operand feeds FM of them.
 //  * 1.6-bit forms are transcoded to 2-bit words once per workgroup and step: a thread looks up the
 //    8 bytes of a column's 40 weights in a 256-entry table of 10-bit entries and writes 80 bits of
 //    codes to LDS two steps before they are used.  A step is then 160 k or a multiple.
@@ -152,17 +151,29 @@ __device__ __forceinline__ uint32_t pkfma(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_bit_cast(uint32_t, r);
 }
 
-// half of a packed word (8 codes, in order) -> fp16 c - 1; sel: the byte selector of this lane's half
-__device__ __forceinline__ u32x4 decode8(uint32_t w, uint32_t sel, uint32_t k1024)
+// Half of a packed word (8 codes, in order) -> fp16 pairs of neighbours, in two parts.  The half word is doubled, so that code 2q stands
+// at bit 4q of the lower half and code 2q + 1 at bit 4q + 2 of the upper half; one packed fma with a factor of its own for each half
+// takes the positions away.  sel: the byte selector of this lane's half.
+//  * UNIT: (c - 1) itself, from 1024 + c 2^p (bits merged into k1024).
+//  * else: (c - 1) 2^-9, from the subnormals c 2^(p - 24), times 2^(15 - p): no merge, the same sum for all; the factor 2^9 is exact and
+//    goes into gamma.  With group scales it would cost the smallest scales bits, so those take the other form.
+// 10 operations where a doubled word with the odd codes moved down took 11; in two halves of a fragment's products instead of one:
+// 128 x 128 tiles 31.1 -> 30.3 us at 1024 x 4096 x 4096, with both 256 x 256 tiles 171.3 -> 169.5 us at 2048 x 14336 x 4096.
+template <bool UNIT>
+__device__ __forceinline__ u32x4 decode8_codes(uint32_t w, uint32_t sel, uint32_t k1024)
 {
-    const uint32_t u = __builtin_amdgcn_perm(w >> 2, w, sel);
+    const uint32_t u = __builtin_amdgcn_perm(w, w, sel);
     const uint32_t v = u >> 8;
-    u32x4 o;
-    o[0] = pkfma((u & 0x00030003u) | k1024, 0x3C003C00u, 0xE401E401u);     // 1024 + c
-    o[1] = pkfma((u & 0x00300030u) | k1024, 0x2C002C00u, 0xD410D410u);     // 1024 + 16 c
-    o[2] = pkfma((v & 0x00030003u) | k1024, 0x3C003C00u, 0xE401E401u);
-    o[3] = pkfma((v & 0x00300030u) | k1024, 0x2C002C00u, 0xD410D410u);
+    u32x4 o = {u & 0x000C0003u, u & 0x00C00030u, v & 0x000C0003u, v & 0x00C00030u};
+    if constexpr (UNIT) o |= k1024;
     return o;
+}
+template <bool UNIT>
+__device__ __forceinline__ u32x4 decode8_values(u32x4 o)
+{
+    constexpr uint32_t m0 = UNIT ? 0x34003C00u : 0x70007800u, m1 = UNIT ? 0x24002C00u : 0x60006800u;      // 2^-p or 2^(15 - p)
+    constexpr uint32_t a0 = UNIT ? 0xDC04E401u : 0x98009800u, a1 = UNIT ? 0xCC40D410u : 0x98009800u;      // -(2^(10 - p) + 1) or -2^-9
+    return u32x4{pkfma(o[0], m0, a0), pkfma(o[1], m1, a1), pkfma(o[2], m0, a0), pkfma(o[3], m1, a1)};
 }
 
 // Piece q of row r of an X stage lies at 16-byte slot r P + slot.  A fragment read takes 4 neighbouring pieces of
@@ -443,8 +454,8 @@ tile_kernel(TileParams p)
 
     // ---- fragments ---------------------------------------------------------------------------------------
     const int fi = lane & 15, fg = lane >> 4;             // row of X / column of W, k quarter of a block
-    const uint32_t sel = (fg & 1) ? 0x07060302u : 0x05040100u;
-    // in a vector register the compiler cannot see through: mask and merge are then one v_and_or_b32
+    const uint32_t sel = (fg & 1) ? 0x03020302u : 0x01000100u;
+    // in a vector register the compiler cannot see through: mask and merge are then one v_and_or_b32 (group scales)
     uint32_t k1024;
     asm volatile("v_mov_b32 %0, 0x64006400" : "=v"(k1024));
     const int xrow = wm * 16 * FM + fi;                   // + 16 a: the swizzle depends on row % 16 alone
@@ -496,9 +507,12 @@ tile_kernel(TileParams p)
             }
         }
     };
-    // one fragment (16 columns x 32 k): 11 vector operations
-    auto decode = [&](int b, uint32_t word, uint32_t scale) {
-        u32x4 o = decode8(word, sel, k1024);
+    // one fragment (16 columns x 32 k): 6 and 4 vector operations
+    constexpr bool kUnit = C::FMT == kTileGs;
+    const float gamma = kUnit ? p.gamma : p.gamma * 512.f;
+    auto decode_codes = [&](int b, uint32_t word) { wf[b] = decode8_codes<kUnit>(word, sel, k1024); };
+    auto decode_values = [&](int b, uint32_t scale) {
+        u32x4 o = decode8_values<kUnit>(wf[b]);
         if constexpr (C::FMT == kTileGs) {
             const _Float16 s1 = __builtin_bit_cast(f16x2, scale)[0];
             const f16x2 s2 = {s1, s1};
@@ -595,7 +609,7 @@ tile_kernel(TileParams p)
     read_x(I0{}, 0, I0{}, I0{}, IFM{});
     read_w(0, 0, I0{}, Any{});
 #pragma unroll
-    for (int b = 0; b + 1 < FN; ++b) decode(b, cw[b][0], sc[b][0]);
+    for (int b = 0; b + 1 < FN; ++b) { decode_codes(b, cw[b][0]); decode_values(b, sc[b][0]); }
 
     // The barrier of step s: behind it all reads of stage s are done and step s + 1 is in LDS.
     auto turn = [&](int s, auto mode) {
@@ -627,6 +641,9 @@ tile_kernel(TileParams p)
     // be none (the last step reads ahead into whatever the ring holds and drops it).
     // st: s mod ST.  An odd number of blocks swaps the two sets of X fragments from step to step: PAR0 is the set of
     // the step's first block; with SWAP = false they are copied, and every step starts from set 0.
+    // The reads of X are kept in front of a half's products; only in the large tiles without the transcoder's registers the compiler may
+    // move them (256 x 256 172.5 -> 170.9 us; 128 x 256 of the 1.6-bit form 56.1 -> 63.9).
+    constexpr bool kLoose = FM * FN == 32 && !C::CODES;
     int st = 0, st_before = ST - 1;
     auto step = [&](int s, auto par0, auto swap, auto mode, auto slot) {
         constexpr int MODE = decltype(mode)::value;
@@ -646,17 +663,18 @@ tile_kernel(TileParams p)
             auto half = [&](auto bt, auto ht) {           // half of fragment b's matrix instructions
                 constexpr int b = decltype(bt)::value, h = decltype(ht)::value;
                 constexpr int from = h * FM / 2, to = (h + 1) * FM / 2;
-                if constexpr (b < 2) {                    // a quarter of the next block's X
-                    constexpr int i = 2 * b + h;
-                    read_x(NextPar{}, END ? st_next : st, Next{}, std::integral_constant<int, i * FM / 4>{}, std::integral_constant<int, (i + 1) * FM / 4>{});
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                constexpr int i = 2 * b + h;              // a share of the next block's X
+                read_x(NextPar{}, END ? st_next : st, Next{}, std::integral_constant<int, i * FM / (2 * FN)>{}, std::integral_constant<int, (i + 1) * FM / (2 * FN)>{});
+                if constexpr (!kLoose) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int a = from; a < to; ++a)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wf[b]), xf[PAR][a], acc[a][b], 0, 0, 0);
-                if constexpr (h == 1) {
-                    if constexpr (b == 0) decode(FN - 1, own, own_sc);
-                    else decode(b - 1, cw[b - 1][NCW == 1 ? 0 : nx], sc[b - 1][NS == 1 ? 0 : nx]);
+                if constexpr (h == 0) {
+                    if constexpr (b == 0) decode_codes(FN - 1, own);
+                    else decode_codes(b - 1, cw[b - 1][NCW == 1 ? 0 : nx]);
+                } else {
+                    if constexpr (b == 0) decode_values(FN - 1, own_sc);
+                    else decode_values(b - 1, sc[b - 1][NS == 1 ? 0 : nx]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (!C::RAGGED) {
@@ -814,7 +832,7 @@ tile_kernel(TileParams p)
             const int m = m_base + row, n = n_base + c4 * 4;
             if (m >= p.M || n >= p.N) continue;
             __half* const dst = p.y + size_t(m) * p.N + n;
-            const f32x4 s = v[0] * p.gamma;
+            const f32x4 s = v[0] * gamma;
             look(s[0]); look(s[1]); look(s[2]); look(s[3]);
             if (n + 4 <= p.N) {
                 const f16x2 lo = {(_Float16)s[0], (_Float16)s[1]}, hi = {(_Float16)s[2], (_Float16)s[3]};
@@ -866,8 +884,8 @@ tile_kernel(TileParams p)
         const int m0 = m_base + wm * 16 * FM + 16 * a;
 #pragma unroll
         for (int b = 0; b < FN; ++b) {
-            const f16x2 lo = {(_Float16)(p.gamma * acc[a][b][0]), (_Float16)(p.gamma * acc[a][b][1])};
-            const f16x2 hi = {(_Float16)(p.gamma * acc[a][b][2]), (_Float16)(p.gamma * acc[a][b][3])};
+            const f16x2 lo = {(_Float16)(gamma * acc[a][b][0]), (_Float16)(gamma * acc[a][b][1])};
+            const f16x2 hi = {(_Float16)(gamma * acc[a][b][2]), (_Float16)(gamma * acc[a][b][3])};
             *reinterpret_cast<u32x2*>(ob + fi * OROW + b * 32 + fg * 8) =
                 u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
         }
