@@ -1,34 +1,30 @@
-// Weight-streaming small-M kernel for the 1.6-bit format (5 trits per byte, plain base 3:
-// byte = sum_i (w_i + 1) 3^i, the block code of Sec. 3.2 without its fixed-point scaling).
+// Weight-streaming small-M kernel for the 1.6-bit formats (5 trits per byte: plain base 3, byte = sum_i (w_i + 1) 3^i, the block code
+// of Sec. 3.2 without its fixed-point scaling, or that code itself).
 //
-// Same organisation as the 2-bit kernel (tl_gemv.hip): a workgroup owns 16-row tiles, wave w
-// owns a K slice and keeps its activations in registers as MFMA B operands, packed rows
-// stream once in full 128-byte lines, the tile slice is turned into MFMA order through
-// wave-private LDS, split-K partial tiles are summed through LDS in a fixed order.
-// What differs is the slice geometry and the decode:
+// Same organisation as the 2-bit kernel (tl_gemv.hip): a workgroup owns 16-row tiles, a wave owns a part of K and keeps its activations
+// in registers as MFMA B operands, packed rows stream once, split-K partial tiles are summed through LDS in a fixed order.
+// What differs is the geometry and the decode:
 //
-//  * A slice is 128 packed bytes = 640 weights per row; a lane's 16 bytes hold 80 weights.
-//  * Decode is a table look-up: a 256-entry table of 8-byte entries in LDS maps a byte to its
-//    five digits c = w + 1 as fp16 (subnormal) pairs: word 0 = c0 << 6 | c2 << 8 | c3 << 22,
-//    word 1 = c1 << 6 | c4 << 22 (every digit at bit 6 or above of its half: the matrix
-//    instruction aligns products by exponent field, and subnormals with only their lowest bits set
-//    lose low-order product bits).  The two words of two neighbouring bytes, with c2 masked out
-//    of the first word of each, are one A operand of v_mfma_f32_16x16x32_f16 as they stand:
-//    (c0, c3) 2^-18, (c1, c4) 2^-18 per byte, against the activation pairs (x[5b], x[5b+3]) and
-//    (x[5b+1], x[5b+4]); the c2 digits of four bytes, masked out the other way, are a third
-//    operand (c2, 0) 2^-16 against (x[5b+2], 0).  Per 5 weights: 1 address operation (a shift
-//    with a byte select), 1 LDS read, 2 ANDs; all sixteen look-ups of a half tile are issued
-//    before the first is used.
-//  * The paper expects the 1.6-bit form to cost more arithmetic per weight than the 2-bit
-//    form (Sec. 3.3 results, "Limitations"); here it is 0.7 VALU operations and 0.2 LDS
-//    look-ups per weight against 0.7 VALU operations for the 2-bit form, for 0.81 of the
-//    bytes, and 24 MFMAs per 640 x 16 weights against 16 per 512 x 16: per weight the SIMD time
-//    is the same, per byte of packed weights it is 1.25 times the 2-bit kernel's.
-//  * Two forms.  gemv3_stream_kernel (K in one pass of at most 7 slices, K <= 4480): a wave
-//    keeps its slice, a workgroup walks a run of tiles in items with the next item's weights in
-//    flight; gemv3_grouped_kernel is the same body fed from one record per workgroup, so that
-//    one launch carries several GEMMs.  gemv3_kernel (longer K): waves loop over slices, one
-//    item per workgroup.
+//  * A wave's part is a half slice of 64 packed bytes = 320 weights per row; a lane's 16 bytes of a tile (row lane % 16, 16-byte chunk
+//    lane / 16) hold 80 weights and lie in its registers as the matrix instruction wants them: no turn through LDS.  Half lines per
+//    request cost the memory a little (a bare load loop 20.0 instead of 16.7 us for 100 MB); the decode takes longer than that.
+//  * Up to 15 waves in a workgroup, one workgroup per CU: four waves per SIMD cover the chain byte -> address -> look-up -> operand
+//    (two LDS round trips and two waves per SIMD, in slices of 128 bytes, took 28 us for the decode sweep where this takes 22.4).
+//  * Decode is a table look-up: a 256-entry table of 8-byte entries in LDS maps a byte to its five digits c = w + 1 as fp16 (subnormal)
+//    pairs: word 0 = c0 << 6 | c2 << 14 | c3 << 22, word 1 = c1 << 6 | c4 << 22 (every digit is used at bit 6 of its half: the matrix
+//    instruction aligns products by exponent field, and subnormals with only their lowest bits set lose low-order product bits).  The
+//    two words of two neighbouring bytes, with c2 masked out of the first word of each, are one A operand of
+//    v_mfma_f32_16x16x32_f16 as they stand: (c0, c3), (c1, c4) per byte, against the activation pairs (x[5b], x[5b+3]) and
+//    (x[5b+1], x[5b+4]); a byte permute brings the c2 of two bytes together, at bit 6, for an operand of eight bytes.  Per 5 weights:
+//    1 address operation (a shift with a byte select), 1 LDS read, 1 AND, 1/2 permute, and 10 products per 320 x 16 weights.
+//  * What bounds it: issue and look-ups.  Decode sweep 22.4 us; without the look-ups 19.5, without them and the products 16.3, without
+//    the weight loads 21.9, with look-ups free of bank conflicts 21.6.  Leaving c2 in the first words and cancelling it by a product of
+//    its own saves the ANDs, adds rounding and gives 22.1: not done.
+//  * The paper expects the 1.6-bit form to cost more arithmetic per weight than the 2-bit form (Sec. 3.3 results, "Limitations").
+//  * Two forms.  gemv3_stream_kernel (K in one pass of at most 15 half slices, K <= 4800): a wave keeps its half slice, a workgroup walks
+//    a run of tiles in items with the next item's weights in flight; gemv3_grouped_kernel is the same body fed from one record per
+//    workgroup, so that one launch carries several GEMMs.  gemv3_kernel (longer K): waves loop over half slices, one item of up to 4
+//    tiles per workgroup.
 #include "tl_internal.hpp"
 #include "tl_deal.hpp"
 
@@ -39,11 +35,12 @@ namespace tl {
 namespace {
 
 constexpr int kT3Max = 4;            // tiles per workgroup
-constexpr int kSlice3 = 640;         // weights per slice (128 packed bytes)
-constexpr int kXRow = 1296;          // bytes per staged activation row (1280 + 16: spreads LDS banks)
-constexpr int kWave3Lds = 16 * kXRow;   // 20736 bytes per wave
-constexpr int kLutBytes = 2048;       // 256 entries of 8 bytes
-constexpr int kNW3Max = 7;           // 7 * 20736 + 2048 bytes of LDS
+constexpr int kHalf3 = 320;          // weights per half slice (64 packed bytes), a wave's share of a pass
+constexpr int kXRowHalf = 656;       // bytes per staged activation row (640 + 16: 16 rows in different banks)
+constexpr int kWaveLds = 16 * kXRowHalf;
+constexpr int kLutBytes = 2048;      // 256 entries of 8 bytes
+constexpr int kWaves3 = 15;
+constexpr int kLds3 = kWaves3 * kWaveLds + kLutBytes;           // 159488 bytes
 
 struct Gemv3Params {
     const __half* x;
@@ -54,7 +51,6 @@ struct Gemv3Params {
     int stride;      // bytes per packed row (multiple of 16)
     int tiles;       // ceil(N / 16)
     int groups;      // gridDim.x
-    int slices;      // ceil(stride / 128)
     int fx;          // bytes hold the fixed-point code of Sec. 3.2 instead of plain base 3
 };
 
@@ -71,6 +67,13 @@ __device__ __forceinline__ void lds_barrier3()
 {
     __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));      // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
+}
+
+// 16 bytes per lane to LDS at `lds` + 16 lane.  Written out by hand (see tl_tile.hpp): the compiler would wait for a transfer it knows of
+// before later LDS accesses.
+__device__ __forceinline__ void dma16(uint32_t voff, const void* sbase, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 
 // 8 * (byte B of w): the offset of that byte's table entry, in one instruction (the shift
@@ -104,233 +107,161 @@ __device__ __forceinline__ void fill_table(u32x2* lut, bool fx)
 #pragma unroll
             for (int i = 0; i < 5; ++i) { c[i] = v % 3u; v /= 3u; }
         }
-        lut[b] = u32x2{(c[0] << 6) | (c[2] << 8) | (c[3] << 22), (c[1] << 6) | (c[4] << 22)};
+        lut[b] = u32x2{(c[0] << 6) | (c[2] << 14) | (c[3] << 22), (c[1] << 6) | (c[4] << 22)};
     }
 }
 
-// The activations as MFMA B operands, grouped as the tile arithmetic uses them.  With
-// p(a, b) = (x[a], x[b]) and k = 5 (4d + j) the first weight of byte 4d + j of the lane's 16 bytes of
-// half h:  bop[h][d][0] = p(k0, k0+3), p(k0+1, k0+4) for bytes j = 0, 1;  bop[h][d][1] the same for
-// j = 2, 3;  bop[h][d][2] = (x[k+2], 0) for j = 0..3.  The lane's 16 bytes of half h cover 80
-// consecutive weights, i.e. 160 consecutive bytes of the staged row: ten 16-byte reads, then one
-// byte permute per pair.
-__device__ __forceinline__ void build_operands(const unsigned char* row, int mg, u32x4 (&bop)[2][4][3])
+// The activations of a half slice (a lane's 16 bytes, 80 weights) as MFMA B operands: with k = 20 d the first weight of dword d,
+// b[2d] = (k, k+3), (k+1, k+4), (k+5, k+8), (k+6, k+9) for its bytes 0 and 1, b[2d + 1] the same ten further on for bytes 2
+// and 3, b[8 + e] = (k+2, k+7), (k+12, k+17) of dwords 2e and 2e + 1.
+__device__ __forceinline__ void build_operands_half(const unsigned char* row, u32x4 (&b)[10])
 {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        u32x4 xv[10];
+    for (int e = 0; e < 2; ++e) {                          // 40 weights, two dwords, at a time: registers
+        __builtin_amdgcn_sched_barrier(0);
+        u32x4 xv[5];
 #pragma unroll
-        for (int i = 0; i < 10; ++i)
-            xv[i] = *reinterpret_cast<const u32x4*>(row + (4 * h + mg) * 160 + 16 * i);
-        auto pair = [&](int a, int b) {                    // (x[a], x[b]) of the 80; b < 0: (x[a], 0)
-            const uint32_t lo = xv[a >> 3][(a >> 1) & 3];
-            const uint32_t hi = b < 0 ? 0u : xv[b >> 3][(b >> 1) & 3];
-            const uint32_t s0 = (a & 1) ? 0x0302u : 0x0100u;
-            const uint32_t s1 = b < 0 ? 0x0c0cu : ((b & 1) ? 0x0706u : 0x0504u);
-            return __builtin_amdgcn_perm(hi, lo, (s1 << 16) | s0);
+        for (int i = 0; i < 5; ++i) xv[i] = *reinterpret_cast<const u32x4*>(row + 80 * e + 16 * i);
+        auto pair = [&](int lo, int hi) {
+            return __builtin_amdgcn_perm(xv[hi >> 3][(hi >> 1) & 3], xv[lo >> 3][(lo >> 1) & 3],
+                                         (((hi & 1) ? 0x0706u : 0x0504u) << 16) | ((lo & 1) ? 0x0302u : 0x0100u));
         };
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const int k = 20 * d;                           // first weight of byte 4d
-            bop[h][d][0] = u32x4{pair(k, k + 3), pair(k + 1, k + 4), pair(k + 5, k + 8), pair(k + 6, k + 9)};
-            bop[h][d][1] = u32x4{pair(k + 10, k + 13), pair(k + 11, k + 14), pair(k + 15, k + 18), pair(k + 16, k + 19)};
-            bop[h][d][2] = u32x4{pair(k + 2, -1), pair(k + 7, -1), pair(k + 12, -1), pair(k + 17, -1)};
+        for (int k = 0; k < 40; k += 20) {
+            const int d = 2 * e + k / 20;
+            b[2 * d] = u32x4{pair(k, k + 3), pair(k + 1, k + 4), pair(k + 5, k + 8), pair(k + 6, k + 9)};
+            b[2 * d + 1] = u32x4{pair(k + 10, k + 13), pair(k + 11, k + 14), pair(k + 15, k + 18), pair(k + 16, k + 19)};
+        }
+        b[8 + e] = u32x4{pair(2, 7), pair(12, 17), pair(22, 27), pair(32, 37)};
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Activation rows of half slice `hs` to LDS at `area`: rows of 40 pieces of 16 bytes, 41 apart (16 rows in different banks), by
+// LDS-DMA; pieces past K are zeros.  Rows from `rows` on stay unwritten (an MFMA column depends on its own column of B alone).
+__device__ __forceinline__ void stage_half(const unsigned char* x, int hs, int rows, int K, unsigned char* area, int lane)
+{
+    const int total = rows * 41;
+    const unsigned char* const src = x + size_t(hs) * (kHalf3 * 2);
+    const uint32_t base = uint32_t(uintptr_t((const __attribute__((address_space(3))) unsigned char*)area));
+#pragma unroll 1
+    for (int i = 0; i < total; i += 64) {
+        const uint32_t piece = uint32_t(i + lane);
+        const uint32_t row = (piece * 1599u) >> 16;        // piece / 41, pieces up to 767
+        const uint32_t col = piece - row * 41u;
+        if (int(piece) < total && col < 40u) {
+            if (hs * kHalf3 + int(col) * 8 < K)
+                dma16(row * (uint32_t(K) * 2u) + col * 16u, src, base + uint32_t(i) * 16u);
+            else
+                *reinterpret_cast<u32x4*>(area + piece * 16u) = u32x4{0u, 0u, 0u, 0u};
         }
     }
 }
 
-// -2^-18 sum_k x over the slice, in accumulator layout (constant 16-row operand)
-__device__ __forceinline__ f32x4 seed_from(const u32x4 (&bop)[2][4][3])
+// the staged rows -> operands, and c0 - 2^-18 sum_k x over the half slice in accumulator layout (constant 16-row operand)
+__device__ __forceinline__ f32x4 operands_and_seed(const unsigned char* area, int rows, int mi, int mg, u32x4 (&bop)[10])
 {
-    f32x4 nsx = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint32_t c = 0x80408040u;
-    const u32x4 a = u32x4{c, c, c, c};
+    int MR = 1;
+    while (MR < rows) MR *= 2;
+    build_operands_half(area + (mi & (MR - 1)) * kXRowHalf + mg * 160, bop);
+    const u32x4 c = {0x80408040u, 0x80408040u, 0x80408040u, 0x80408040u};        // -2^-18
+    f32x4 nsx = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-                nsx = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(a), as_h8(bop[h][d][q]), nsx, 0, 0, 0);
+    for (int q = 0; q < 10; ++q)
+        nsx = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(c), as_h8(bop[q]), nsx, 0, 0, 0);
     return nsx;
 }
 
-// sum_k x_k w_k of one tile slice that lies in MFMA order at reg_t: all sixteen look-ups of a
-// half first, so that their latency runs under the arithmetic of the ones before
-template <class LutAt>
-__device__ __forceinline__ f32x4 tile_sum(const unsigned char* reg_t, uint32_t wr_off0, uint32_t wr_off1,
-                                          const u32x4 (&bop)[2][4][3], f32x4 nsx, LutAt lut_at)
+// table addresses of a lane's 16 bytes
+__device__ __forceinline__ void addresses(u32x4 w, uint32_t (&at)[4][4])
 {
-    f32x4 acc[3] = {nsx, f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const u32x4 wv = *reinterpret_cast<const u32x4*>(reg_t + (h ? wr_off1 : wr_off0));
-        u32x2 e[4][4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            e[d][0] = lut_at(byte_times_8<0>(wv[d]));
-            e[d][1] = lut_at(byte_times_8<1>(wv[d]));
-            e[d][2] = lut_at(byte_times_8<2>(wv[d]));
-            e[d][3] = lut_at(byte_times_8<3>(wv[d]));
-        }
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            // bytes 0,1 and 2,3 of the dword: the two table words of a byte pair are an operand
-            // as they stand once c2 is masked out of the first word of each
-            const u32x4 a2 = u32x4{e[d][0][0] & 0x300u, e[d][1][0] & 0x300u, e[d][2][0] & 0x300u, e[d][3][0] & 0x300u};
-            const u32x4 a01 = u32x4{e[d][0][0] & 0x00c000c0u, e[d][0][1], e[d][1][0] & 0x00c000c0u, e[d][1][1]};
-            const u32x4 a23 = u32x4{e[d][2][0] & 0x00c000c0u, e[d][2][1], e[d][3][0] & 0x00c000c0u, e[d][3][1]};
-            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(a01), as_h8(bop[h][d][0]), acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(a23), as_h8(bop[h][d][1]), acc[1], 0, 0, 0);
-            acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(a2), as_h8(bop[h][d][2]), acc[2], 0, 0, 0);
-        }
+    for (int d = 0; d < 4; ++d) {
+        at[d][0] = byte_times_8<0>(w[d]);
+        at[d][1] = byte_times_8<1>(w[d]);
+        at[d][2] = byte_times_8<2>(w[d]);
+        at[d][3] = byte_times_8<3>(w[d]);
     }
-    return (acc[0] + acc[1]) * 262144.f + acc[2] * 65536.f;
 }
 
-template <int T>
-__global__ void __launch_bounds__(512)
-gemv3_kernel(Gemv3Params p)
+// c0 + 2^-18 sum_k x_k (w_k + 1) of a tile's half slice.  BATCH dwords' look-ups are issued before the first is used, so that their latency
+// runs under the arithmetic of the ones before.  The table starts the LDS: a byte offset into it is an LDS address.
+template <int BATCH>
+__device__ __forceinline__ f32x4 tile_sum_half(const uint32_t (&at)[4][4], const u32x4 (&bop)[10], f32x4 c0)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int NW = blockDim.x >> 6;
-    u32x2* const lut = reinterpret_cast<u32x2*>(lds_raw);
-    unsigned char* const my_lds = lds_raw + kLutBytes + wave * kWave3Lds;
-    // the table starts the LDS: a byte offset into it is an LDS address
     auto lut_at = [](uint32_t off) { return *(const __attribute__((address_space(3))) u32x2*)(uintptr_t(off)); };
-
-    const int m0 = blockIdx.y * 16;
-    const int Mrem = (p.M - m0 < 16) ? (p.M - m0) : 16;
-    int MR = 1;
-    while (MR < Mrem) MR *= 2;
-    const int K = p.K, N = p.N;
-    const uint32_t stride = uint32_t(p.stride);
-    const int chunks = p.stride >> 4;          // 16-byte chunks per packed row
-    const int grp = blockIdx.x, groups = p.groups, tiles = p.tiles, slices = p.slices;
-
-    const int lr = lane >> 3, lc = lane & 7;   // load mapping: row of the half tile, chunk of the slice
-    const int mi = lane & 15, mg = lane >> 4;  // MFMA mapping: row / activation column, k group
-    const int xrow = mi & (MR - 1);
-
-    const uint32_t ww_off = uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
-    const uint32_t wr_off0 = uint32_t(mi) * 128u + (uint32_t((mg) ^ (mi & 7)) << 4);
-    const uint32_t wr_off1 = uint32_t(mi) * 128u + (uint32_t((4 + mg) ^ (mi & 7)) << 4);
-
-    const unsigned char* const Wb = p.W;
-    const unsigned char* const xb = reinterpret_cast<const unsigned char*>(p.x + size_t(m0) * K);
-
-    u32x4 wreg[T][2];
-    const bool ragged_n = (N & 15) != 0;
-    auto issue_w = [&](int t, int slice) {
-        int tile = grp + t * groups;
-        if (tile >= tiles) tile = tiles - 1;
-        int chunk = slice * 8 + lc;
-        if (chunk >= chunks) chunk = 0;                    // past the row: meets zero activations
-        const unsigned char* tb = Wb + size_t(tile) * 16u * stride;
-        uint32_t off0 = uint32_t(lr) * stride + uint32_t(chunk) * 16u;
-        uint32_t off1 = off0 + 8u * stride;
-        if (ragged_n && tile == tiles - 1) {
-            const int last = N - 1 - tile * 16;
-            off0 = uint32_t(lr < last ? lr : last) * stride + uint32_t(chunk) * 16u;
-            off1 = uint32_t(lr + 8 < last ? lr + 8 : last) * stride + uint32_t(chunk) * 16u;
-        }
-        wreg[t][0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(tb + off0));
-        wreg[t][1] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(tb + off1));
-    };
-
-    // Staged activation row r of the slice: 640 halves = 80 pieces of 16 bytes, by LDS-DMA
-    // (two instructions: pieces 0..63, then 64..79).  Pieces past K are stored as zeros.
-    auto issue_x = [&](int slice) {
-        // rows past Mrem stay unwritten: an MFMA column depends on its own column of B alone,
-        // and the outputs of those columns are not stored
-        for (int r = 0; r < Mrem; ++r) {
-            const unsigned char* src = xb + size_t(r) * K * 2;
-            unsigned char* dst = my_lds + r * kXRow;
+    u32x4 e[4][2];                                         // bytes 0 and 1 (2 and 3) of dword d: their table words side by side
+    f32x4 acc[2] = {c0, f32x4{0.f, 0.f, 0.f, 0.f}};
+    u32x4 mid[2];
 #pragma unroll
-            for (int part = 0; part < 2; ++part) {
-                const int piece = part * 64 + lane;
-                const int kx = slice * kSlice3 + piece * 8;
-                if (piece < 80) {
-                    if (kx < K) {
-                        __builtin_amdgcn_global_load_lds(
-                            (const __attribute__((address_space(1))) void*)(src + uint32_t(kx) * 2u),
-                            (__attribute__((address_space(3))) void*)(dst + part * 1024),
-                            16, 0, 0);
-                    } else {
-                        *reinterpret_cast<u32x4*>(dst + piece * 16) = u32x4{0u, 0u, 0u, 0u};
-                    }
+    for (int d = 0; d < 4; ++d) {
+        if (d % BATCH == 0) {
+            if (BATCH < 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = d; q < d + BATCH; ++q)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const u32x2 lo = lut_at(at[q][2 * j]), hi = lut_at(at[q][2 * j + 1]);
+                    e[q][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
                 }
-            }
         }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            // The second byte of a table word is c2 alone, six bits up; without it the words are an operand as they stand.  The mask is
+            // written by hand to stay in these registers (the compiler would keep the words for c2 and copy the others).
+            const uint32_t m = __builtin_amdgcn_perm(e[d][j][2], e[d][j][0], 0x0c050c01u);
+            uint32_t w0 = e[d][j][0], w1 = e[d][j][2];
+            asm("v_and_b32 %0, %2, %0\n\tv_and_b32 %1, %2, %1" : "+v"(w0), "+v"(w1) : "s"(0x00c000c0u), "v"(m));
+            const u32x4 a = {w0, e[d][j][1], w1, e[d][j][3]};
+            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(a), as_h8(bop[2 * d + j]), acc[j], 0, 0, 0);
+            mid[d >> 1][2 * (d & 1) + j] = m;
+        }
+        if (d & 1) acc[d >> 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(mid[d >> 1]), as_h8(bop[8 + (d >> 1)]), acc[d >> 1], 0, 0, 0);
+    }
+    return acc[0] + acc[1];
+}
+
+// Sum of the first `parts` waves' values at `from` (one f32x4, kWaveLds apart), in a fixed order
+__device__ __forceinline__ f32x4 sum_parts(const unsigned char* from, int parts)
+{
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto some = [&](auto count) {
+        constexpr int C = decltype(count)::value;
+        f32x4 v[C];
+#pragma unroll
+        for (int q = 0; q < C; ++q) v[q] = *reinterpret_cast<const f32x4*>(from + q * kWaveLds);
+#pragma unroll
+        for (int step = 1; step < C; step *= 2)
+#pragma unroll
+            for (int q = 0; q < C; q += 2 * step) v[q] += v[q + step];
+        s += v[0];
+        from += C * kWaveLds;
     };
+    if (parts & 8) some(std::integral_constant<int, 8>{});
+    if (parts & 4) some(std::integral_constant<int, 4>{});
+    if (parts & 2) some(std::integral_constant<int, 2>{});
+    if (parts & 1) some(std::integral_constant<int, 1>{});
+    return s;
+}
 
-    f32x4 part_acc[T];
+// four consecutive columns of a row of y, `left` of which exist; `aligned`: as one 8-byte store
+typedef __attribute__((address_space(1))) __half* gh_ptr;
+__device__ __forceinline__ void store_quad(gh_ptr dst, f32x4 s, float gamma, int left, bool aligned)
+{
+    if (left >= 4 && aligned) {
+        const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
+        const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
+        *(__attribute__((address_space(1))) u32x2*)dst = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+    } else {
 #pragma unroll
-    for (int t = 0; t < T; ++t) part_acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    int slice = wave;
-    if (slice < slices) {
-        issue_x(slice);
-#pragma unroll
-        for (int t = 0; t < T; ++t) issue_w(t, slice);
-    }
-
-    fill_table(lut, p.fx != 0);
-    // (the barrier that makes the table visible comes after the operands are built: they need
-    // the wave's own activation transfers only)
-    if (wave < slices) __builtin_amdgcn_s_waitcnt(vmcnt_imm3(2 * T));   // LDS-DMA is not tracked by the compiler
-
-    for (; slice < slices; slice += NW) {
-        const bool more = (slice + NW) < slices;
-        u32x4 bop[2][4][3];
-        build_operands(my_lds + xrow * kXRow, mg, bop);
-        const f32x4 nsx = seed_from(bop);
-        if (slice == wave) lds_barrier3();                 // first pass (every wave runs it): the table is complete
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            unsigned char* const reg_t = my_lds + t * 2048;
-            *reinterpret_cast<u32x4*>(reg_t + ww_off) = wreg[t][0];
-            *reinterpret_cast<u32x4*>(reg_t + 1024 + ww_off) = wreg[t][1];
-            if (more) issue_w(t, slice + NW);
-            if (grp + t * groups < tiles) part_acc[t] += tile_sum(reg_t, wr_off0, wr_off1, bop, nsx, lut_at);
-        }
-        if (more) {
-            issue_x(slice + NW);
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm3(0));
-        }
-    }
-
-    // ---- split-K reduction across the waves, epilogue ----
-    lds_barrier3();
-    f32x4* red = reinterpret_cast<f32x4*>(lds_raw + kLutBytes);
-#pragma unroll
-    for (int t = 0; t < T; ++t) red[(t * NW + wave) * 64 + lane] = part_acc[t];
-    lds_barrier3();
-    for (int item = threadIdx.x; item < T * 64; item += blockDim.x) {
-        const int t = item >> 6;
-        const int l = item & 63;
-        const int tile = grp + t * groups;
-        if (tile >= tiles) continue;
-        f32x4 v[8];
-#pragma unroll
-        for (int w = 0; w < 8; ++w)
-            v[w] = (w < NW) ? red[(t * NW + w) * 64 + l] : f32x4{0.f, 0.f, 0.f, 0.f};
-        const f32x4 s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-        const int n = tile * 16 + 4 * (l >> 4);
-        if ((l & 15) < Mrem) {
-            __half* dst = p.y + size_t(m0 + (l & 15)) * N + n;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (n + r < N) dst[r] = __float2half_rn(p.gamma * s[r]);
-        }
+        for (int r = 0; r < 4; ++r)
+            if (r < left) *(__attribute__((address_space(1))) _Float16*)(dst + r) = (_Float16)(gamma * s[r]);
     }
 }
 
 // ------------------------------------------------------------------------------------------
-// Stream form, for K of at most 7 slices (K <= 4480): wave w owns slice w for the whole kernel,
-// so activations are staged and turned into operands once; a workgroup walks a run of
+// Stream form, for K of at most kWaves3 half slices: wave w owns half slice w (64 packed bytes, 320 weights) for the whole
+// kernel, so activations are staged and turned into operands once; a workgroup walks a run of
 // consecutive tiles, T at a time ("item"), with the next item's weights requested as soon as
 // a tile's registers are free, two alternating sets of partial sums and one LDS-only barrier
 // per item -- the organisation of the 2-bit stream kernel (tl_gemv.hip) with this file's
@@ -346,15 +277,19 @@ struct Run3 {
     int stride;               // bytes per packed row
     int Mrem;                 // activation rows, 1..16
     int tile0, tile_end;      // the run
-    int slices;               // waves with a slice of K (the others idle along)
     int fx;                   // which byte code the table is filled for
+    int pad;
 };
 static_assert(sizeof(Run3) == 64, "one record per 64-byte line");
 
-constexpr int kRec3Max = 256;  // records (workgroups) of a grouped launch: 16 KB of kernel arguments
+// Records (workgroups) of a grouped launch: 16 KB of kernel arguments, or 32 KB where two workgroups fit on a CU (K of up to 7 half
+// slices) and they have 8 tiles each or more: ten layers of K = 1024 13.8 -> 10.3 us, K = 2048 12.4 -> 11.3; two layers of 4.5 tiles per
+// workgroup 6.4 -> 6.8, the larger arguments costing the host 0.5.
+constexpr int kRec3Few = 256, kRec3Many = 512;
 
+template <int R>
 struct Rec3Batch {
-    Run3 rec[kRec3Max];
+    Run3 rec[R];
 };
 
 template <int T>
@@ -365,142 +300,181 @@ __device__ __forceinline__ void gemv3_stream_body(const Run3& p)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int NW = blockDim.x >> 6;
     u32x2* const lut = reinterpret_cast<u32x2*>(lds_raw);
-    unsigned char* const my_lds = lds_raw + kLutBytes + wave * kWave3Lds;
-    auto lut_at = [](uint32_t off) { return *(const __attribute__((address_space(3))) u32x2*)(uintptr_t(off)); };
+    unsigned char* const my_lds = lds_raw + kLutBytes + wave * kWaveLds;
 
-    const int Mrem = p.Mrem;
-    int MR = 1;
-    while (MR < Mrem) MR *= 2;
-    const int K = p.K, N = p.N;
+    const int rows = p.Mrem, K = p.K, N = p.N;
     const uint32_t stride = uint32_t(p.stride);
     const int chunks = p.stride >> 4;
-    const int tiles = (N + 15) >> 4;
-    const int tile0 = p.tile0;
-    const int tile_end = p.tile_end;
-    const int n_items = (tile_end - tile0 + T - 1) / T;
+    const int tile0 = p.tile0, ntiles = p.tile_end - p.tile0;
+    const int mi = lane & 15, mg = lane >> 4;              // row of the tile / activation column, chunk of the slice
+    const bool active = wave * 4 < chunks;
 
-    const int lr = lane >> 3, lc = lane & 7;
-    const int mi = lane & 15, mg = lane >> 4;
-    const int xrow = mi & (MR - 1);
-    const uint32_t ww_off = uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
-    const uint32_t wr_off0 = uint32_t(mi) * 128u + (uint32_t((mg) ^ (mi & 7)) << 4);
-    const uint32_t wr_off1 = uint32_t(mi) * 128u + (uint32_t((4 + mg) ^ (mi & 7)) << 4);
-
-    const unsigned char* const Wb = p.W;
-    const unsigned char* const xb = p.x;
-    const bool active = wave < p.slices;
-    uint32_t col_off;
+    if (active) stage_half(p.x, wave, rows, K, my_lds, lane);
+    // ---- weights: a lane's 16 bytes of a tile lie where the matrix instruction wants them (row mi, k group mg).  The run is a raw buffer
+    // of the rows that exist: rows past N read zeros, and a request costs the vector ALU nothing
+    uint32_t voff;
     {
-        int chunk = wave * 8 + lc;
-        if (chunk >= chunks) chunk = 0;                    // past the row: meets zero activations
-        col_off = uint32_t(chunk) * 16u;
+        const int chunk = wave * 4 + mg;
+        voff = uint32_t(mi) * stride + uint32_t(chunk < chunks ? chunk : 0) * 16u;      // past the row: meets zero activations
     }
-    const bool ragged_n = (N & 15) != 0;
-    typedef const __attribute__((address_space(1))) u32x4* gptr;
-
-    u32x4 wreg[T][2];
-    auto issue_w = [&](int first, int t) {
-        int tile = first + t;
-        if (tile >= tile_end) tile = tile_end - 1;         // past the run: its last tile again, never stored
-        const unsigned char* tb = Wb + size_t(tile) * 16u * stride;
-        const int last = (ragged_n && tile == tiles - 1) ? N - 1 - tile * 16 : 15;
-        const uint32_t off0 = uint32_t(lr < last ? lr : last) * stride + col_off;
-        const uint32_t off1 = uint32_t(lr + 8 < last ? lr + 8 : last) * stride + col_off;
-        wreg[t][0] = __builtin_nontemporal_load((gptr)(tb + off0));
-        wreg[t][1] = __builtin_nontemporal_load((gptr)(tb + off1));
+    const uint32_t tile_bytes = 16u * stride;
+    const int run_rows = N - tile0 * 16 < ntiles * 16 ? N - tile0 * 16 : ntiles * 16;
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char*>(p.W) + size_t(tile0) * tile_bytes, 0, uint32_t(run_rows) * stride, 0x00020000);
+    u32x4 wreg[T];
+    auto issue_w = [&](int idx, int t) {                   // idx: tile of the run; past the run: its last tile again
+        const int c = idx < ntiles ? idx : ntiles - 1;
+        wreg[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, voff, uint32_t(c) * tile_bytes, 0));
     };
-
     if (active) {
-        // activation rows of this wave's slice by LDS-DMA: 640 halves = 80 pieces of 16 bytes per
-        // row (pieces 0..63, then 64..79); pieces past K are stored as zeros; rows past Mrem stay
-        // unwritten (an MFMA column depends on its own column of B alone)
-        for (int r = 0; r < Mrem; ++r) {
-            const unsigned char* src = xb + size_t(r) * K * 2;
-            unsigned char* dst = my_lds + r * kXRow;
 #pragma unroll
-            for (int part = 0; part < 2; ++part) {
-                const int piece = part * 64 + lane;
-                const int kx = wave * kSlice3 + piece * 8;
-                if (piece < 80) {
-                    if (kx < K) {
-                        __builtin_amdgcn_global_load_lds(
-                            (const __attribute__((address_space(1))) void*)(src + uint32_t(kx) * 2u),
-                            (__attribute__((address_space(3))) void*)(dst + part * 1024), 16, 0, 0);
-                    } else {
-                        *reinterpret_cast<u32x4*>(dst + piece * 16) = u32x4{0u, 0u, 0u, 0u};
-                    }
-                }
-            }
+        for (int t = 0; t < T; ++t) {
+            issue_w(t, t);
+            __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int t = 0; t < T; ++t) issue_w(tile0, t);
     }
     fill_table(lut, p.fx != 0);
-    if (active) __builtin_amdgcn_s_waitcnt(vmcnt_imm3(2 * T));   // the activations are in; the weights stay in flight
-
-    u32x4 bop[2][4][3];
+    u32x4 bop[10];
     f32x4 nsx = f32x4{0.f, 0.f, 0.f, 0.f};
     if (active) {
-        build_operands(my_lds + xrow * kXRow, mg, bop);
-        nsx = seed_from(bop);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm3(T));         // the activations are in; the weights stay in flight
+        nsx = operands_and_seed(my_lds, rows, mi, mg, bop);
     }
     lds_barrier3();                                        // the table is complete
 
+    const float gamma = p.gamma * 262144.f;                // times the 2^18 left in the partial sums
+    gh_ptr const ylane = (gh_ptr)(p.y + size_t(mi) * N + size_t(tile0) * 16 + 4 * mg);
+    const int nleft = N - tile0 * 16 - 4 * mg;             // columns from the lane's first one on
+    const bool aligned = (N & 3) == 0;
+    const int parts = (chunks + 3) >> 2;                   // waves with a slice of K
+    int turn = wave;                                       // waves take turns at adding up an item: tile `turn` of it
+    auto finish = [&](int first, int parity) {
+        lds_barrier3();
+        if (turn < T && first + turn < ntiles) {
+            const f32x4 s = sum_parts(lds_raw + kLutBytes + parity * (T * 1024) + turn * 1024 + lane * 16, parts);
+            const int n = (first + turn) * 16;
+            if (mi < rows) store_quad(ylane + n, s, gamma, nleft - n, aligned);
+        }
+        turn -= T;
+        if (turn < 0) turn += NW;
+    };
+    const int n_items = (ntiles + T - 1) / T;
+    if (!active) {
+        for (int i = 0; i < n_items; ++i) finish(i * T, i & 1);
+        return;
+    }
     auto item = [&](auto refill_tag, int first, int parity) {
         constexpr bool REFILL = decltype(refill_tag)::value;
-        f32x4 part[T];
+        unsigned char* const red = my_lds + parity * (T * 1024);
 #pragma unroll
-        for (int t = 0; t < T; ++t) part[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (active) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                unsigned char* const reg_t = my_lds + (t & 1) * 2048;
-                *reinterpret_cast<u32x4*>(reg_t + ww_off) = wreg[t][0];
-                *reinterpret_cast<u32x4*>(reg_t + 1024 + ww_off) = wreg[t][1];
-                if constexpr (REFILL) issue_w(first + T, t);
-                if (REFILL || first + t < tile_end)
-                    part[t] = tile_sum(reg_t, wr_off0, wr_off1, bop, nsx, lut_at);
+        for (int t = 0; t < T; ++t) {
+            if (!REFILL && first + t >= ntiles) break;
+            uint32_t at[4][4];
+            addresses(wreg[t], at);
+            if constexpr (REFILL) {
+                __builtin_amdgcn_sched_barrier(0);
+                issue_w(first + T + t, t);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            reinterpret_cast<f32x4*>(red + t * 1024)[lane] = tile_sum_half<4>(at, bop, nsx);
         }
-        unsigned char* const red = my_lds + 4096 + parity * (T * 1024);
-#pragma unroll
-        for (int t = 0; t < T; ++t) reinterpret_cast<f32x4*>(red + t * 1024)[lane] = part[t];
-        lds_barrier3();
-        if (const int o = threadIdx.x; o < T * 64) {       // T <= waves: one output quad per thread
-            const int t = o >> 6, l = o & 63;
-            const int tile = first + t;
-            f32x4 v[8];
-#pragma unroll
-            for (int w = 0; w < 8; ++w)
-                v[w] = (w < NW) ? reinterpret_cast<const f32x4*>(lds_raw + kLutBytes + w * kWave3Lds + 4096 + parity * (T * 1024) + t * 1024)[l]
-                                : f32x4{0.f, 0.f, 0.f, 0.f};
-            const f32x4 s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-            const int n = tile * 16 + 4 * (l >> 4);
-            if (tile < tile_end && (l & 15) < Mrem) {
-                typedef __attribute__((address_space(1))) __half* gh_ptr;
-                gh_ptr dst = (gh_ptr)(p.y + size_t(l & 15) * N + n);
-                const float gamma = p.gamma;
-                if (n + 3 < N && (N & 3) == 0) {           // four consecutive n: one 8-byte store
-                    const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
-                    const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
-                    *(__attribute__((address_space(1))) u32x2*)dst =
-                        u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (n + r < N) *(__attribute__((address_space(1))) _Float16*)(dst + r) = (_Float16)(gamma * s[r]);
-                }
-            }
-        }
+        finish(first, parity);
     };
     int i = 0;
-    for (; i + 1 < n_items; ++i) item(std::true_type{}, tile0 + i * T, i & 1);
-    item(std::false_type{}, tile0 + i * T, i & 1);
+    for (; i + 1 < n_items; ++i) item(std::true_type{}, i * T, i & 1);
+    item(std::false_type{}, i * T, i & 1);
+}
+
+// ------------------------------------------------------------------------------------------
+// Longer K: wave w owns the half slices w, w + NW, ...; a workgroup's T tiles are its whole work.  Their sums stay in registers over all
+// passes, and a pass's activations and weights are requested while the pass before it is worked on: the activations as soon as the operands
+// are built, each tile's weights as soon as their registers are free.  Against the form with slices of 128 bytes, seven waves and no
+// overlap of the passes: 11008 -> 4096 at M = 1 / 16 6.8 / 11.4 -> 5.8 / 9.2 us, 14336 -> 14336 17.6 / 23.5 -> 14.5 / 18.3.
+template <int T>
+__global__ void __launch_bounds__(1024)
+gemv3_kernel(Gemv3Params p)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int NW = blockDim.x >> 6;
+    unsigned char* const my_lds = lds_raw + kLutBytes + wave * kWaveLds;
+    const int m0 = blockIdx.y * 16;
+    const int rows = (p.M - m0 < 16) ? (p.M - m0) : 16;
+    const int K = p.K, N = p.N, tiles = p.tiles, groups = p.groups, grp = blockIdx.x;
+    const uint32_t stride = uint32_t(p.stride);
+    const int chunks = p.stride >> 4, slices = (chunks + 3) >> 2;
+    const int mi = lane & 15, mg = lane >> 4;
+    const unsigned char* const xb = reinterpret_cast<const unsigned char*>(p.x + size_t(m0) * K);
+
+    u32x4 wreg[T];
+    auto issue_w = [&](int slice, int t) {                 // past the last tile: that tile again
+        int tile = grp + t * groups;
+        if (tile >= tiles) tile = tiles - 1;
+        const int left = N - tile * 16;
+        const int chunk = slice * 4 + mg;
+        const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<unsigned char*>(p.W) + size_t(tile) * (16u * size_t(stride)), 0, uint32_t(left < 16 ? left : 16) * stride, 0x00020000);
+        wreg[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+            res, uint32_t(mi) * stride + uint32_t(chunk < chunks ? chunk : 0) * 16u, 0, 0));
+    };
+    int slice = wave;                                      // slices >= NW: every wave has one
+    stage_half(xb, slice, rows, K, my_lds, lane);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        issue_w(slice, t);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    fill_table(reinterpret_cast<u32x2*>(lds_raw), p.fx != 0);
+    f32x4 part[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) part[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bool first = true;
+    auto pass = [&](auto more_tag) {
+        constexpr bool MORE = decltype(more_tag)::value;
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(T) : "memory");       // the activations, asked for before the weights
+        u32x4 bop[10];
+        const f32x4 nsx = operands_and_seed(my_lds, rows, mi, mg, bop);
+        if (first) lds_barrier3();                         // the table is complete
+        else asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+        first = false;
+        if constexpr (MORE) {
+            // the weights as well, before anything is asked for behind the compiler's back
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm3(0));
+            stage_half(xb, slice + NW, rows, K, my_lds, lane);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            uint32_t at[4][4];
+            addresses(wreg[t], at);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (MORE) issue_w(slice + NW, t);
+            __builtin_amdgcn_sched_barrier(0);
+            part[t] += tile_sum_half<4>(at, bop, nsx);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        slice += NW;
+    };
+    while (slice + NW < slices) pass(std::true_type{});
+    pass(std::false_type{});
+    // ---- sums of the waves
+    unsigned char* const red = my_lds;
+#pragma unroll
+    for (int t = 0; t < T; ++t) reinterpret_cast<f32x4*>(red + t * 1024)[lane] = part[t];
+    lds_barrier3();
+    if (wave < T) {
+        const int tile = grp + wave * groups;
+        if (tile >= tiles) return;
+        const f32x4 s = sum_parts(lds_raw + kLutBytes + wave * 1024 + lane * 16, NW);
+        const int n = tile * 16 + 4 * mg;
+        if (mi < rows) store_quad((gh_ptr)(p.y + size_t(m0 + mi) * N + n), s, p.gamma * 262144.f, N - n, (N & 3) == 0);
+    }
 }
 
 // One GEMM: blockIdx.y is the block of 16 activation rows, the tiles are split evenly over gridDim.x.
 template <int T>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(1024)
 gemv3_stream_kernel(Gemv3Params p)
 {
     const int m0 = blockIdx.y * 16;
@@ -515,15 +489,14 @@ gemv3_stream_kernel(Gemv3Params p)
     r.Mrem = (p.M - m0 < 16) ? (p.M - m0) : 16;
     r.tile0 = g * per + (g < extra ? g : extra);
     r.tile_end = r.tile0 + per + (g < extra ? 1 : 0);
-    r.slices = p.slices;
     r.fx = p.fx;
     gemv3_stream_body<T>(r);
 }
 
 // Several GEMMs: the host has dealt out the workgroups and written one record for each.
-template <int T>
-__global__ void __launch_bounds__(512)
-gemv3_grouped_kernel(Rec3Batch b)
+template <int T, int R>
+__global__ void __launch_bounds__(1024)
+gemv3_grouped_kernel(Rec3Batch<R> b)
 {
     gemv3_stream_body<T>(b.rec[blockIdx.x]);
 }
@@ -549,14 +522,16 @@ Kernel3Fn pick3_stream(int T)
     }
 }
 
-using Grouped3Fn = void (*)(Rec3Batch);
+template <int R>
+using Grouped3Fn = void (*)(Rec3Batch<R>);
 
-Grouped3Fn pick3_grouped(int T)
+template <int R>
+Grouped3Fn<R> pick3_grouped(int T)
 {
     switch (T) {
-        case 1: return gemv3_grouped_kernel<1>;
-        case 2: return gemv3_grouped_kernel<2>;
-        default: return gemv3_grouped_kernel<3>;
+        case 1: return gemv3_grouped_kernel<1, R>;
+        case 2: return gemv3_grouped_kernel<2, R>;
+        default: return gemv3_grouped_kernel<3, R>;
     }
 }
 
@@ -568,14 +543,16 @@ hipError_t gemv3_init()
 {
     for (int T = 1; T <= kT3Max; ++T) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3(T)),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           kNW3Max * kWave3Lds + kLutBytes);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
         if (e == hipSuccess && T <= 3)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3_stream(T)),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kNW3Max * kWave3Lds + kLutBytes);
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
         if (e == hipSuccess && T <= 3)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3_grouped(T)),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kNW3Max * kWave3Lds + kLutBytes);
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3_grouped<kRec3Few>(T)),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
+        if (e == hipSuccess && T <= 3)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3_grouped<kRec3Many>(T)),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -589,8 +566,8 @@ bool gemv3_supports(int64_t M, int64_t N, int64_t K)
 
 bool gemv3_groups(int64_t M, int64_t N, int64_t K)
 {
-    // K in one pass of the stream form: at most kNW3Max slices of 128 packed bytes
-    return gemv3_supports(M, N, K) && (K + 4) / 5 <= int64_t(kNW3Max) * 128;
+    // K in one pass of the stream form
+    return gemv3_supports(M, N, K) && (K + 4) / 5 <= int64_t(kWaves3) * 64;
 }
 
 // Several GEMMs in one launch of the stream form: every block of 16 activation rows of every GEMM
@@ -604,7 +581,7 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
     struct Block { int job; int64_t m0; int rows; };
     Block blk[kMaxBlocks3];
     int nb = 0;
-    static bool lds_raised[kMaxDevices][4];
+    static bool lds_raised[kMaxDevices][2][4];
     auto flush = [&]() -> hipError_t {
         if (nb == 0) return hipSuccess;
         DealJob dj[kMaxBlocks3];
@@ -613,12 +590,13 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
         for (int q = 0; q < nb; ++q) {
             const Gemm3Desc& d = jobs[blk[q].job];
             const int tiles = int((d.N + 15) / 16);
-            const int slices = int((d.stride + 127) / 128);
+            const int slices = int((d.stride + 63) / 64);
             dj[q] = DealJob{tiles, 1, 0.15 * double(blk[q].rows)};
             total_tiles += tiles;
             if (slices > NW) NW = slices;
         }
-        const int G = total_tiles < kRec3Max ? int(total_tiles) : kRec3Max;
+        const int most = NW * 2 <= kWaves3 && total_tiles >= 8 * kRec3Few ? kRec3Many : kRec3Few;
+        const int G = total_tiles < most ? int(total_tiles) : most;
         const DealModel model{3, true, 2.1, 0.43};
         int wg[kMaxBlocks3];
         deal_workgroups(model, dj, nb, G, wg);
@@ -628,40 +606,44 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
             if (r > run) run = r;
             grid += wg[q];
         }
-        if (grid > kRec3Max) return hipErrorInvalidValue;   // more jobs than workgroups: cannot happen with kMaxBlocks3 <= kRec3Max
+        if (grid > most) return hipErrorInvalidValue;       // more jobs than workgroups: cannot happen with kMaxBlocks3 <= kRec3Few
         int T = run <= 3 ? run : (run == 4 ? 2 : 3);
         if (T > NW) T = NW;                                // the epilogue gives every thread at most one output quad
-        Rec3Batch rb;
-        int g = 0;
-        for (int q = 0; q < nb; ++q) {
-            const Gemm3Desc& d = jobs[blk[q].job];
-            const int per = dj[q].tiles / wg[q], plus = dj[q].tiles % wg[q];
-            for (int w = 0; w < wg[q]; ++w) {
-                Run3& r = rb.rec[g++];
-                r.W = d.W;
-                r.x = reinterpret_cast<const unsigned char*>(d.x + blk[q].m0 * d.K);
-                r.y = d.y + blk[q].m0 * d.N;
-                r.gamma = d.gamma;
-                r.K = int(d.K); r.N = int(d.N); r.stride = int(d.stride);
-                r.Mrem = blk[q].rows;
-                r.tile0 = w * per + (w < plus ? w : plus);
-                r.tile_end = r.tile0 + per + (w < plus ? 1 : 0);
-                r.slices = int((d.stride + 127) / 128);
-                r.fx = fx ? 1 : 0;
+        auto send = [&](auto many) -> hipError_t {
+            constexpr int R = decltype(many)::value;
+            Rec3Batch<R> rb;
+            int g = 0;
+            for (int q = 0; q < nb; ++q) {
+                const Gemm3Desc& d = jobs[blk[q].job];
+                const int per = dj[q].tiles / wg[q], plus = dj[q].tiles % wg[q];
+                for (int w = 0; w < wg[q]; ++w) {
+                    Run3& r = rb.rec[g++];
+                    r.W = d.W;
+                    r.x = reinterpret_cast<const unsigned char*>(d.x + blk[q].m0 * d.K);
+                    r.y = d.y + blk[q].m0 * d.N;
+                    r.gamma = d.gamma;
+                    r.K = int(d.K); r.N = int(d.N); r.stride = int(d.stride);
+                    r.Mrem = blk[q].rows;
+                    r.tile0 = w * per + (w < plus ? w : plus);
+                    r.tile_end = r.tile0 + per + (w < plus ? 1 : 0);
+                    r.fx = fx ? 1 : 0;
+                }
             }
-        }
-        Grouped3Fn fn = pick3_grouped(T);
-        const int dev = device_slot();
-        if (dev < 0 || !lds_raised[dev][T]) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     kNW3Max * kWave3Lds + kLutBytes);
-            if (e != hipSuccess) return e;
-            if (dev >= 0) lds_raised[dev][T] = true;
-        }
-        hipLaunchKernelGGL(fn, dim3(grid), dim3(NW * 64), size_t(NW) * kWave3Lds + kLutBytes, s, rb);
+            const Grouped3Fn<R> fn = pick3_grouped<R>(T);
+            const int dev = device_slot();
+            bool& raised = lds_raised[dev < 0 ? 0 : dev][R == kRec3Many][T];
+            if (dev < 0 || !raised) {
+                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
+                if (e != hipSuccess) return e;
+                if (dev >= 0) raised = true;
+            }
+            hipLaunchKernelGGL(fn, dim3(grid), dim3(NW * 64), size_t(NW) * kWaveLds + kLutBytes, s, rb);
+            return hipGetLastError();
+        };
+        const hipError_t e = most == kRec3Many ? send(std::integral_constant<int, kRec3Many>{}) : send(std::integral_constant<int, kRec3Few>{});
         nb = 0;
-        return hipGetLastError();
+        return e;
     };
     for (int i = 0; i < count; ++i) {
         for (int64_t m0 = 0; m0 < jobs[i].M; m0 += 16) {
@@ -684,27 +666,28 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
     p.M = int(M); p.N = int(N); p.K = int(K);
     p.stride = int(stride);
     p.tiles = int((N + 15) / 16);
-    p.slices = int((stride + 127) / 128);
-    const int NW = p.slices < kNW3Max ? p.slices : kNW3Max;
+    const int slices = int((stride + 63) / 64);
     int groups = p.tiles < 256 ? p.tiles : 256;
     static bool lds_raised[kMaxDevices][2][kT3Max + 1];
     const int dev = device_slot();
     auto raise = [&](Kernel3Fn fn, int form, int T) -> hipError_t {
         if (dev >= 0 && lds_raised[dev][form][T]) return hipSuccess;
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 kNW3Max * kWave3Lds + kLutBytes);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
         if (e == hipSuccess && dev >= 0) lds_raised[dev][form][T] = true;
         return e;
     };
     dim3 grid(groups, unsigned((M + 15) / 16));
-    if (p.slices <= kNW3Max) {
+    if (slices <= kWaves3) {
         // every block of 16 activation rows is a set of workgroups of its own (blockIdx.y); they
         // share the CUs, 256 workgroups in all, so that the launch is one round with longer runs
         // (with shorter K, fewer waves per workgroup and as many more workgroups)
         const int mblocks = int((M + 15) / 16);
-        int share = 256 * (kNW3Max / NW) / mblocks;
+        const int NW = slices;
+        int share = 256 * (kWaves3 / NW) / mblocks;
         if (share < 1) share = 1;
+        const int64_t runs = (int64_t(p.tiles) * 16 * stride + (int64_t(1) << 31) - 1) >> 31;     // a run is addressed with 32 bits
+        if (share < runs) share = int(runs);
         groups = p.tiles < share ? p.tiles : share;
         grid.x = unsigned(groups);
         // K in one pass: the stream form.  Tiles per item as for the 2-bit stream kernel: runs
@@ -716,7 +699,7 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
         Kernel3Fn fn = pick3_stream(T);
         const hipError_t e = raise(fn, 1, T);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(fn, grid, dim3(NW * 64), size_t(NW) * kWave3Lds + kLutBytes, s, p);
+        hipLaunchKernelGGL(fn, grid, dim3(NW * 64), size_t(NW) * kWaveLds + kLutBytes, s, p);
         return hipGetLastError();
     }
     int T = (p.tiles + groups - 1) / groups;
@@ -726,7 +709,8 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
     Kernel3Fn fn = pick3(T);
     const hipError_t e = raise(fn, 0, T);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, grid, dim3(NW * 64), size_t(NW) * kWave3Lds + kLutBytes, s, p);
+    const int passes = (slices + kWaves3 - 1) / kWaves3, NW = (slices + passes - 1) / passes;       // as even as they get
+    hipLaunchKernelGGL(fn, grid, dim3(NW * 64), size_t(NW) * kWaveLds + kLutBytes, s, p);
     return hipGetLastError();
 }
 

@@ -1,0 +1,47 @@
+"""The weight-streaming kernel of the 1.6-bit forms at the edges of its geometry: half slices of 320 weights (64 packed bytes, four 16-byte
+chunks), up to 15 waves, items of up to three tiles, several passes beyond, one and two workgroups per CU in a grouped launch."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2506_23025_amd as tl
+import synth_inputs as si
+from parity import assert_close, to_dev
+
+pytestmark = pytest.mark.gpu
+
+FORMS = [(tl.TL_FMT_1P6BIT, tl.tl_pack_1p6bit, tl.tl_ternary_gemm_1p6), (tl.TL_FMT_1P6BIT_FX, tl.tl_pack_1p6bit_fx, tl.tl_ternary_gemm_1p6_fx)]
+
+
+def check(y, x, W, g, what):
+    N = W.shape[0]
+    cols = np.unique(np.r_[0:min(N, 16), max(0, N - 16):N, np.random.default_rng(N).choice(N, min(N, 100), replace=False)])
+    assert_close(y[:, cols], oracle.gemm(x, np.ascontiguousarray(W[cols]), g), x, g, what)
+
+
+# one chunk; a half slice less, full and one group over; 14 and 15 waves full, one weight group over into a second pass; passes of unequal waves;
+# columns: one, a tile less one, full and over, rows of y at odd places, runs of one to four tiles and more
+@pytest.mark.parametrize("fmt,pack,call", FORMS)
+@pytest.mark.parametrize("M,N,K", [(1, 1, 8), (3, 15, 80), (16, 16, 312), (2, 17, 320), (5, 33, 328), (1, 4100, 4480), (16, 1022, 4800),
+                                   (7, 4097, 4808), (16, 48, 9600), (1, 5000, 9608), (9, 8211, 6400), (4, 12304, 4872), (12, 16400, 640)])
+def test_shapes_at_the_edges(M, N, K, fmt, pack, call):
+    x, W, g = si.layer(41000 + M + N + K, M, N, K)
+    xd, wd = to_dev(x.view(np.int16)), to_dev(pack(W))
+    yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
+    call(xd, wd, si.gamma_bits(g), yd, M, N, K)
+    check(yd.cpu().numpy().view(np.float16), x, W, g, f"{M}x{N}x{K}")
+
+
+# K that leaves two workgroups to a CU (up to 2240) and one over, with tiles for both; a wave without a part of a shorter K
+@pytest.mark.parametrize("specs", [[(16, 14336, 1024), (16, 18448, 640)], [(1, 16384, 2240), (9, 16400, 2240)],
+                                   [(2, 16384, 2248), (5, 16384, 2240)], [(3, 32768, 320), (1, 30, 2240)]])
+def test_grouped_launches_of_one_and_two_workgroups_per_cu(specs):
+    jobs, want = [], []
+    for i, (M, N, K) in enumerate(specs):
+        x, W, g = si.layer(42000 + i + M + N + K, M, N, K)
+        yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
+        jobs.append((to_dev(x.view(np.int16)), to_dev(tl.tl_pack_1p6bit(W)), si.gamma_bits(g), yd, M, N, K))
+        want.append((yd, x, W, g))
+    tl.tl_ternary_gemm_1p6_grouped(jobs, tl.TL_FMT_1P6BIT)
+    for yd, x, W, g in want:
+        check(yd.cpu().numpy().view(np.float16), x, W, g, f"{yd.shape}")
