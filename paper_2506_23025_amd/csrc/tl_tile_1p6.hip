@@ -52,30 +52,29 @@ int pick(int64_t M, int64_t N, int64_t K, double* us)
 }  // namespace
 
 // What the weight-streaming kernel (gemv3) takes (us) for more than 16 rows, W being decoded once per b blocks of 16: t tiles of 16 output
-// rows, s slices of 128 packed bytes.  While K is one pass a tile costs what s waves cost; beyond that workgroups of up to 4
-// tiles go in rounds of 256.  Fitted to 8400 calls over M = 17 .. 2048, N = 512 .. 16384, K = 512 .. 14336: 10 % for nine in ten calls,
-// 15 % with several passes.
+// rows, s half slices of 64 packed bytes.  While K is one pass, workgroups of s waves share the CUs and walk runs of tiles, and the fullest
+// CU sets the pace; beyond that workgroups of up to 4 tiles go in rounds of 256.  Fitted to 1100 calls over M = 17 .. 2048, N = 512 .. 16384,
+// K = 512 .. 14336: 13 % for nine in ten calls.  (The fit to slices of 128 bytes and seven waves gave 27 to 33 % more than these calls take,
+// and up to three times as much for K = 4481 .. 4800, which is one pass now.)
 static double stream3_time(int64_t M, int64_t N, int64_t K)
 {
-    const int64_t tiles = (N + 15) / 16;
-    const double b = double((M + 15) / 16);
-    const int64_t s = ((K + 4) / 5 + 127) / 128;
-    if (s <= 7) {
-        constexpr double start[8] = {0, 4.8, 5.0, 4.9, 4.65, 5.15, 5.3, 5.6};
-        constexpr double per_tile[8] = {0, 0.22, 0.386, 0.542, 0.859, 0.952, 1.0, 1.086};
-        return start[s] + 0.003 * double(s) * b + per_tile[s] * b * double(tiles) / 256.0;
+    const int64_t tiles = (N + 15) / 16, b = (M + 15) / 16;
+    const int64_t s = (((K + 4) / 5 + 15) / 16 + 3) / 4;
+    if (s <= 15) {
+        constexpr double start[16] = {0, 4.0, 4.13, 4.23, 3.81, 4.47, 4.14, 4.2, 3.89, 4.13, 4.22, 4.2, 4.17, 4.58, 4.73, 4.66};
+        constexpr double per_tile[16] = {0, 0.13, 0.153, 0.254, 0.258, 0.409, 0.376, 0.43, 0.509, 0.611, 0.642, 0.687, 0.727, 0.83, 0.88, 0.948};
+        const int64_t share = 256 * (15 / s) / b, groups = tiles < share ? tiles : (share < 1 ? 1 : share);
+        return start[s] + per_tile[s] * double((tiles + groups - 1) / groups) * double((b * groups + 255) / 256);
     }
     int64_t groups = tiles < 256 ? tiles : 256, per_group = (tiles + groups - 1) / groups;
     if (per_group > 4) { per_group = 4; groups = (tiles + 3) / 4; }
-    const double share = b * double(groups) / 256.0, rounds = double(((M + 15) / 16 * groups + 255) / 256);
-    const double k = double(K) / 4096.0, T = double(per_group), passes = double((s + 6) / 7);
-    return 1.25 + 0.08 * k + rounds * (2.2 + 1.85 * passes + k * (0.15 + 0.05 * T)) + (share > 1.0 ? share : 1.0) * k * (0.15 + 0.675 * T);
+    const double share = double(b) * double(groups) / 256.0, rounds = double((b * groups + 255) / 256), passes = double((s + 14) / 15);
+    return 1.08 + rounds * (0.85 + 0.8 * passes + 0.8 / 15.0 * double(s * per_group)) + 1.04 * (share > 1.0 ? share : 1.0) * passes;
 }
 
 // Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel, which never
-// loses up to 16 rows: over the calls of the fit the one chosen is 0.2 % slower than the best on average and 6 % in one of
-// a hundred.  (A line through few of them before took narrow layers and 17 to 36 rows of long
-// ones from it: 4096 x 576 at M = 1965 25.3 us there, 32.0 here, 8704 x 4260 at 18 17.9 and 22.7.)
+// loses up to 16 rows: over the calls of the fit the one chosen is 0.4 % slower than the best on average and 11 % in one of
+// a hundred (chosen by what it took with slices of 128 bytes, 3.8 % and 38 %; 4672 -> 4647 at M = 20 7.5 us there, 14.4 here).
 // Other K: the plain kernel on the vector ALUs, 3 + K / 4096 (7 + 7.5 per row, up to 4) for every 1024 workgroups of 4 x 4
 // outputs (4090 -> 4099: M = 1 17.8, M = 4 39, M = 16 159, M = 37 324; 1001 -> 1024: M = 1 6.8, M = 16 13).
 bool tile3_preferred(int64_t M, int64_t N, int64_t K)
@@ -97,13 +96,17 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
     KernelChoice c{gemv3_groups(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (M <= 16 || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return c;
     c.stream = stream3_time(M, N, K);
-    c.launch = c.streams ? 4.5 : 0.0;
+    c.launch = c.streams ? 3.8 : 0.0;
     c.fixed = c.launch;                                    // of its own it is one launch, however many rows
     c.launches = double((M + 15) / 16) / 32.0;
     c.tiled = c.stream;
-    if (tile_at_least(kCost, kShapes, K) >= c.stream) return c;
+    // Short K is mostly start and end on either side, and the streaming kernel's time less certain (0.79 .. 1.18 of the fit): the tiled
+    // kernel keeps what the fit puts less than 16 % behind.  Over the 205 such calls the one chosen is 1.2 % slower than the best without
+    // that line and 1.1 to 1.7 % with it, and fewer of them take longer than with the choice before.
+    const double band = K <= 960 ? 0.84 : 1.0;
+    if (band * tile_at_least(kCost, kShapes, K) >= c.stream) return c;
     pick(M, N, K, &c.tiled);
-    if ((K + 4) / 5 > 7 * 128) c.tiled *= 1.05;           // several passes: the streaming kernel's time is less certain
+    c.tiled *= band;
     return c;
 }
 

@@ -71,6 +71,15 @@ def test_one_point_six_bit_codes_at_many_rows():
         assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
 
 
+def test_one_point_six_bit_codes_in_one_pass():
+    # measured (us), streaming / best tile, K in one pass of 15 half slices: 4672 -> 4647 at M = 20 7.5 / 14.4, 4736 -> 572 at 228 7.3 / 14.6, 4560 -> 2624
+    # at 31 6.5 / 14.5; K past it and wide layers at many rows the other way round: 11008 -> 4096 at 60, 4096 -> 14336 at 512 56
+    for M, N, K in ((20, 4647, 4672), (228, 572, 4736), (31, 2624, 4560), (31, 2624, 4800)):
+        assert instance(ONE_POINT_SIX, M, N, K) == -1, (M, N, K)
+    for M, N, K in ((60, 4096, 11008), (512, 14336, 4096), (2048, 4096, 1024)):
+        assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
+
+
 def test_grouped_jobs_share_launches_where_that_is_faster():
     # measured (us), all streaming / each as if alone: 16 layers at M = 256, 2-bit words 512 x 1024 68.7 / 83.2, 768 x 2048 87.2 / 108.3, 1.6-bit codes
     # 512 x 1024 102.5 / 119.6
