@@ -207,11 +207,15 @@ __device__ __forceinline__ f32x4 tile_sum_half(const uint32_t (&at)[4][4], const
         }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            // The second byte of a table word is c2 alone, six bits up; without it the words are an operand as they stand.  The mask is
-            // written by hand to stay in these registers (the compiler would keep the words for c2 and copy the others).
+            // The second byte of a table word is c2 alone, six bits up; without it the words are an operand as they stand.  The empty
+            // statement makes them new values once c2 is out, so that they are masked where they stand (the compiler would keep the words
+            // for c2 and copy the others).  The mask itself stays visible to it: gfx950 asks for two wait states between a vector
+            // instruction and the matrix instruction that reads its result, and the compiler sees to them for its own only.
             const uint32_t m = __builtin_amdgcn_perm(e[d][j][2], e[d][j][0], 0x0c050c01u);
             uint32_t w0 = e[d][j][0], w1 = e[d][j][2];
-            asm("v_and_b32 %0, %2, %0\n\tv_and_b32 %1, %2, %1" : "+v"(w0), "+v"(w1) : "s"(0x00c000c0u), "v"(m));
+            asm("" : "+v"(w0), "+v"(w1) : "v"(m));
+            w0 &= 0x00c000c0u;
+            w1 &= 0x00c000c0u;
             const u32x4 a = {w0, e[d][j][1], w1, e[d][j][3]};
             acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(a), as_h8(bop[2 * d + j]), acc[j], 0, 0, 0);
             mid[d >> 1][2 * (d & 1) + j] = m;

@@ -4,6 +4,9 @@ The transfers that stand in inline assembly are invisible to the compiler's own 
 before them is checked on what was built: one wait state between a scalar write of M0 and the transfer that takes its LDS
 address from it, and five between a vector instruction that writes a scalar register and a transfer that takes its address
 from that register.
+
+Likewise for matrix instructions: two wait states after a vector instruction that writes one of their operands.  The compiler keeps them
+for the instructions it emits itself, not for those of inline assembly.
 """
 import os
 import re
@@ -91,3 +94,75 @@ def test_transfers_wait_for_their_scalar_operands(tmp_path):
         total += count
         assert not found, f"{len(found)} of {count} transfers unguarded, first: {found[0]}"
     assert total > 0, "no transfer in the library"
+
+
+def vector_registers(operand):
+    m = re.fullmatch(r"v\[(\d+):(\d+)\]", operand)
+    if m:
+        return set(range(int(m[1]), int(m[2]) + 1))
+    m = re.fullmatch(r"v(\d+)", operand)
+    return {int(m[1])} if m else set()
+
+
+def matrix_hazards(lines):
+    """(kernel, instruction, what it follows too closely) of every matrix instruction that reads a vector register too early, and their number."""
+    kernel, before, found, count = None, [], [], 0
+    for line in lines:
+        m = re.match(r"^[0-9a-f]+ <(.+)>:", line)
+        if m:
+            kernel, before = m[1], []
+            continue
+        text = line.split("//")[0].strip()
+        if not text or not re.match(r"^[a-z]", text):
+            continue
+        name, _, rest = text.partition(" ")
+        operands = [o.split()[0] for o in rest.split(",") if o.strip()]
+        if name.startswith("v_mfma"):
+            count += 1
+            reads = set().union(*(vector_registers(o) for o in operands[1:4]))
+            states = 0
+            for name0, ops0 in reversed(before):
+                if states >= 2:
+                    break
+                if name0.startswith("v_") and not name0.startswith("v_mfma") and ops0 and vector_registers(ops0[0]) & reads:
+                    found.append((kernel, text, f"{name0} {', '.join(ops0)}"))
+                states += int(ops0[0], 0) + 1 if name0 == "s_nop" else 1
+        before = [] if name in ("s_branch", "s_endpgm") else (before + [(name, operands)])[-4:]
+    return found, count
+
+
+def test_the_check_sees_matrix_operands_written_too_late():
+    listing = """
+0000000000001000 <k>:
+	v_and_b32_e32 v4, s0, v4   // 0
+	v_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], v[0:3]
+	v_and_b32_e32 v6, s0, v6
+	s_nop 0
+	v_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], v[0:3]
+	v_and_b32_e32 v6, s0, v6
+	s_nop 1
+	v_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], 0
+	v_and_b32_e32 v12, s0, v6
+	v_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], 0
+	v_perm_b32 v9, v1, v2, s3
+	v_mov_b32_e32 v12, 0
+	s_waitcnt lgkmcnt(0)
+	v_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], 0
+"""
+    found, count = matrix_hazards(listing.splitlines())
+    assert count == 5
+    assert [f[2].split()[1] for f in found] == ["v4,", "v6,"]
+
+
+@pytest.mark.skipif(OBJDUMP is None, reason="no llvm-objdump")
+def test_matrix_instructions_wait_for_their_operands(tmp_path):
+    lib = str(tmp_path / "lib.so")
+    shutil.copy(tl.LIB_PATH, lib)
+    subprocess.run([OBJDUMP, "--offloading", lib], cwd=tmp_path, check=True, capture_output=True)
+    total = 0
+    for f in sorted(f for f in os.listdir(tmp_path) if "gfx950" in f):
+        text = subprocess.run([OBJDUMP, "-d", f], cwd=tmp_path, check=True, capture_output=True, text=True).stdout
+        found, count = matrix_hazards(text.splitlines())
+        total += count
+        assert not found, f"{len(found)} of {count} matrix instructions read an operand too early, first: {found[0]}"
+    assert total > 0, "no matrix instruction in the library"
