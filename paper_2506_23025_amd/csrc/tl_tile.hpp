@@ -644,6 +644,11 @@ tile_kernel(TileParams p)
     // The reads of X are kept in front of a half's products; only in the large tiles without the transcoder's registers the compiler may
     // move them (256 x 256 172.5 -> 170.9 us; 128 x 256 of the 1.6-bit form 56.1 -> 63.9).
     constexpr bool kLoose = FM * FN == 32 && !C::CODES;
+    // The half of a fragment's products whose end decodes the codes (the values come at the end of the second): the first, unless the halves
+    // are so short that the words just asked for would be waited for.  All in the second half against both, 64 x 64 / 32 x 64 tiles: group
+    // scales 2.1 / 3.1 % faster (in the first half they had lost 2.1 / 1.5 % to a decode all in the second), 1.6-bit 0.8 / 2.6, 2-bit words
+    // 0.5 / 1.0 (means over calls of M = 17 .. 2048, N = 512 .. 16384, K = 512 .. 14336).
+    constexpr int kCodes = FM <= 4 ? 1 : 0;
     int st = 0, st_before = ST - 1;
     auto step = [&](int s, auto par0, auto swap, auto mode, auto slot) {
         constexpr int MODE = decltype(mode)::value;
@@ -669,10 +674,11 @@ tile_kernel(TileParams p)
 #pragma unroll
                 for (int a = from; a < to; ++a)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wf[b]), xf[PAR][a], acc[a][b], 0, 0, 0);
-                if constexpr (h == 0) {
+                if constexpr (h == kCodes) {
                     if constexpr (b == 0) decode_codes(FN - 1, own);
                     else decode_codes(b - 1, cw[b - 1][NCW == 1 ? 0 : nx]);
-                } else {
+                }
+                if constexpr (h == 1) {
                     if constexpr (b == 0) decode_values(FN - 1, own_sc);
                     else decode_values(b - 1, sc[b - 1][NS == 1 ? 0 : nx]);
                 }
