@@ -154,25 +154,37 @@ __device__ __forceinline__ uint32_t pkfma(uint32_t a, uint32_t b, uint32_t c)
 // Half of a packed word (8 codes, in order) -> fp16 pairs of neighbours, in two parts.  The half word is doubled, so that code 2q stands
 // at bit 4q of the lower half and code 2q + 1 at bit 4q + 2 of the upper half; one packed fma with a factor of its own for each half
 // takes the positions away.  sel: the byte selector of this lane's half.
-//  * UNIT: (c - 1) itself, from 1024 + c 2^p (bits merged into k1024).
-//  * else: (c - 1) 2^-9, from the subnormals c 2^(p - 24), times 2^(15 - p): no merge, the same sum for all; the factor 2^9 is exact and
-//    goes into gamma.  With group scales it would cost the smallest scales bits, so those take the other form.
-// 10 operations where a doubled word with the odd codes moved down took 11; in two halves of a fragment's products instead of one:
-// 128 x 128 tiles 31.1 -> 30.3 us at 1024 x 4096 x 4096, with both 256 x 256 tiles 171.3 -> 169.5 us at 2048 x 14336 x 4096.
-template <bool UNIT>
+//  * kScaled: (c - 1) 2^-9, from the subnormals c 2^(p - 24), times 2^(15 - p): no merge, the same sum for all; the factor 2^9 is exact and
+//    goes into gamma.
+//  * kUnit: (c - 1) itself, from 1024 + c 2^p (bits merged into k1024): group scales, the smallest of which kScaled would cost bits.
+//  * kMoved: as kUnit, with the odd codes moved down by 2 beforehand, one operation more, the same factor for both halves: tiles of 16 rows
+//    (one product per decoded operand), whose calls it keeps 1.5 % (2-bit) and 1.2 % (1.6-bit) faster than kScaled, 2.4 and 0.2 % than
+//    kUnit (means over 167 and 161 calls with odd K, M = 2 .. 300).
+// 10 operations where the odd codes moved down took 11; in two halves of a fragment's products instead of one: 128 x 128 tiles
+// 31.1 -> 30.3 us at 1024 x 4096 x 4096, with both 256 x 256 tiles 171.3 -> 169.5 us at 2048 x 14336 x 4096.
+enum Decode { kScaled, kUnit, kMoved };
+
+template <Decode D>
+__device__ __forceinline__ uint32_t decode_selector(bool upper)
+{
+    if constexpr (D == kMoved) return upper ? 0x07060302u : 0x05040100u;
+    return upper ? 0x03020302u : 0x01000100u;
+}
+template <Decode D>
 __device__ __forceinline__ u32x4 decode8_codes(uint32_t w, uint32_t sel, uint32_t k1024)
 {
-    const uint32_t u = __builtin_amdgcn_perm(w, w, sel);
+    const uint32_t u = __builtin_amdgcn_perm(D == kMoved ? w >> 2 : w, w, sel);
     const uint32_t v = u >> 8;
-    u32x4 o = {u & 0x000C0003u, u & 0x00C00030u, v & 0x000C0003u, v & 0x00C00030u};
-    if constexpr (UNIT) o |= k1024;
-    return o;
+    constexpr uint32_t c0 = D == kMoved ? 0x00030003u : 0x000C0003u, c1 = D == kMoved ? 0x00300030u : 0x00C00030u;
+    if constexpr (D == kScaled) return u32x4{u & c0, u & c1, v & c0, v & c1};
+    return u32x4{(u & c0) | k1024, (u & c1) | k1024, (v & c0) | k1024, (v & c1) | k1024};
 }
-template <bool UNIT>
+template <Decode D>
 __device__ __forceinline__ u32x4 decode8_values(u32x4 o)
 {
-    constexpr uint32_t m0 = UNIT ? 0x34003C00u : 0x70007800u, m1 = UNIT ? 0x24002C00u : 0x60006800u;      // 2^-p or 2^(15 - p)
-    constexpr uint32_t a0 = UNIT ? 0xDC04E401u : 0x98009800u, a1 = UNIT ? 0xCC40D410u : 0x98009800u;      // -(2^(10 - p) + 1) or -2^-9
+    // 2^-p or 2^(15 - p), and -(2^(10 - p) + 1) or -2^-9, for the positions 0 and 4, odd codes 2 further up unless moved
+    constexpr uint32_t m0 = D == kMoved ? 0x3C003C00u : D == kUnit ? 0x34003C00u : 0x70007800u, m1 = D == kMoved ? 0x2C002C00u : D == kUnit ? 0x24002C00u : 0x60006800u;
+    constexpr uint32_t a0 = D == kMoved ? 0xE401E401u : D == kUnit ? 0xDC04E401u : 0x98009800u, a1 = D == kMoved ? 0xD410D410u : D == kUnit ? 0xCC40D410u : 0x98009800u;
     return u32x4{pkfma(o[0], m0, a0), pkfma(o[1], m1, a1), pkfma(o[2], m0, a0), pkfma(o[3], m1, a1)};
 }
 
@@ -454,8 +466,9 @@ tile_kernel(TileParams p)
 
     // ---- fragments ---------------------------------------------------------------------------------------
     const int fi = lane & 15, fg = lane >> 4;             // row of X / column of W, k quarter of a block
-    const uint32_t sel = (fg & 1) ? 0x03020302u : 0x01000100u;
-    // in a vector register the compiler cannot see through: mask and merge are then one v_and_or_b32 (group scales)
+    constexpr Decode kDecode = FM == 1 ? kMoved : C::FMT == kTileGs ? kUnit : kScaled;
+    const uint32_t sel = decode_selector<kDecode>(fg & 1);
+    // in a vector register the compiler cannot see through: mask and merge are then one v_and_or_b32 (not kScaled)
     uint32_t k1024;
     asm volatile("v_mov_b32 %0, 0x64006400" : "=v"(k1024));
     const int xrow = wm * 16 * FM + fi;                   // + 16 a: the swizzle depends on row % 16 alone
@@ -507,12 +520,11 @@ tile_kernel(TileParams p)
             }
         }
     };
-    // one fragment (16 columns x 32 k): 6 and 4 vector operations
-    constexpr bool kUnit = C::FMT == kTileGs;
-    const float gamma = kUnit ? p.gamma : p.gamma * 512.f;
-    auto decode_codes = [&](int b, uint32_t word) { wf[b] = decode8_codes<kUnit>(word, sel, k1024); };
+    // one fragment (16 columns x 32 k): 6 (7 if moved) and 4 vector operations
+    const float gamma = kDecode == kScaled ? p.gamma * 512.f : p.gamma;
+    auto decode_codes = [&](int b, uint32_t word) { wf[b] = decode8_codes<kDecode>(word, sel, k1024); };
     auto decode_values = [&](int b, uint32_t scale) {
-        u32x4 o = decode8_values<kUnit>(wf[b]);
+        u32x4 o = decode8_values<kDecode>(wf[b]);
         if constexpr (C::FMT == kTileGs) {
             const _Float16 s1 = __builtin_bit_cast(f16x2, scale)[0];
             const f16x2 s2 = {s1, s1};
