@@ -367,6 +367,9 @@ __attribute__((visibility("default"))) void tl_internal_grouped_tiled(int form, 
     for (int j = 0; j < count; ++j) out[j] = tiled[j] ? 1 : 0;
 }
 
+// Likewise: workgroups of `waves` waves that a launch of the 1.6-bit streaming kernel puts on a CU, and the LDS that one is given.
+__attribute__((visibility("default"))) int tl_internal_stream3_per_cu(int waves, int* lds) { return tl::gemv3_per_cu(waves, lds); }
+
 tl_status tl_init(void)
 {
     hipError_t e = tl::gemv_init();

@@ -568,6 +568,18 @@ bool gemv3_supports(int64_t M, int64_t N, int64_t K)
            N <= (int64_t(1) << 24) && (M + 15) / 16 <= 65535;
 }
 
+// What a CU holds of the stream form: LDS is handed out in units of 1280 bytes of 160 KB, and one workgroup of 15 waves fills it.  With one
+// wave 12 workgroups would fit and with two 7, but from 8 waves on another one only adds a start (N from 20000 on: one wave 8 workgroups
+// 1.018 times as fast as 12, two waves 4 1.12 times as fast as 7).  Asked for more than fit (3 and 5 waves: 5 and 3 instead of 4 and 2),
+// the last ones ran as a second round: 1.18 to 1.28 times as long.
+int gemv3_per_cu(int waves, int* lds)
+{
+    const int bytes = (waves * kWaveLds + kLutBytes + 1279) / 1280 * 1280;
+    const int by_lds = 160 * 1024 / bytes, by_waves = waves <= 2 ? 8 / waves : kWaves3 / waves;
+    if (lds) *lds = bytes;
+    return by_lds < by_waves ? by_lds : by_waves;
+}
+
 bool gemv3_groups(int64_t M, int64_t N, int64_t K)
 {
     // K in one pass of the stream form
@@ -599,7 +611,7 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
             total_tiles += tiles;
             if (slices > NW) NW = slices;
         }
-        const int most = NW * 2 <= kWaves3 && total_tiles >= 8 * kRec3Few ? kRec3Many : kRec3Few;
+        const int most = gemv3_per_cu(NW) >= 2 && total_tiles >= 8 * kRec3Few ? kRec3Many : kRec3Few;
         const int G = total_tiles < most ? int(total_tiles) : most;
         const DealModel model{3, true, 2.1, 0.43};
         int wg[kMaxBlocks3];
@@ -684,11 +696,11 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
     dim3 grid(groups, unsigned((M + 15) / 16));
     if (slices <= kWaves3) {
         // every block of 16 activation rows is a set of workgroups of its own (blockIdx.y); they
-        // share the CUs, 256 workgroups in all, so that the launch is one round with longer runs
-        // (with shorter K, fewer waves per workgroup and as many more workgroups)
+        // share the CUs, as many workgroups in all as 256 CUs hold, so that the launch is one round
+        // with longer runs
         const int mblocks = int((M + 15) / 16);
         const int NW = slices;
-        int share = 256 * (kWaves3 / NW) / mblocks;
+        int share = 256 * gemv3_per_cu(NW) / mblocks;
         if (share < 1) share = 1;
         const int64_t runs = (int64_t(p.tiles) * 16 * stride + (int64_t(1) << 31) - 1) >> 31;     // a run is addressed with 32 bits
         if (share < runs) share = int(runs);

@@ -101,6 +101,8 @@ struct Gemm3Desc {
     int64_t M, N, K, stride;
 };
 bool gemv3_groups(int64_t M, int64_t N, int64_t K);
+// Workgroups of that many waves (one per half slice of 320 weights, 1..15) of its stream form that a launch puts on a CU, and what LDS each takes.
+int gemv3_per_cu(int waves, int* lds = nullptr);
 hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStream_t s);
 
 // Tiled matrix-core kernel for group scales, and whether it is the faster one for a shape.

@@ -54,16 +54,16 @@ int pick(int64_t M, int64_t N, int64_t K, double* us)
 // What the weight-streaming kernel (gemv3) takes (us) for more than 16 rows, W being decoded once per b blocks of 16: t tiles of 16 output
 // rows, s half slices of 64 packed bytes.  While K is one pass, workgroups of s waves share the CUs and walk runs of tiles, and the fullest
 // CU sets the pace; beyond that workgroups of up to 4 tiles go in rounds of 256.  Fitted to 1100 calls over M = 17 .. 2048, N = 512 .. 16384,
-// K = 512 .. 14336: 13 % for nine in ten calls.  (The fit to slices of 128 bytes and seven waves gave 27 to 33 % more than these calls take,
-// and up to three times as much for K = 4481 .. 4800, which is one pass now.)
+// K = 512 .. 14336, up to 7 half slices to 1700 more with weights out of the caches: 8 % for nine in ten calls.  (The lines of 3 and 5 half
+// slices had been fitted to launches of more workgroups than the CUs held: 13 and 15 % above what the calls take now.)
 static double stream3_time(int64_t M, int64_t N, int64_t K)
 {
     const int64_t tiles = (N + 15) / 16, b = (M + 15) / 16;
     const int64_t s = (((K + 4) / 5 + 15) / 16 + 3) / 4;
     if (s <= 15) {
-        constexpr double start[16] = {0, 4.0, 4.13, 4.23, 3.81, 4.47, 4.14, 4.2, 3.89, 4.13, 4.22, 4.2, 4.17, 4.58, 4.73, 4.66};
-        constexpr double per_tile[16] = {0, 0.13, 0.153, 0.254, 0.258, 0.409, 0.376, 0.43, 0.509, 0.611, 0.642, 0.687, 0.727, 0.83, 0.88, 0.948};
-        const int64_t share = 256 * (15 / s) / b, groups = tiles < share ? tiles : (share < 1 ? 1 : share);
+        constexpr double start[16] = {0, 3.98, 3.94, 3.98, 3.89, 3.98, 4.14, 4.39, 3.89, 4.13, 4.22, 4.2, 4.17, 4.58, 4.73, 4.66};
+        constexpr double per_tile[16] = {0, 0.114, 0.16, 0.2, 0.258, 0.339, 0.393, 0.445, 0.509, 0.611, 0.642, 0.687, 0.727, 0.83, 0.88, 0.948};
+        const int64_t share = 256 * gemv3_per_cu(int(s)) / b, groups = tiles < share ? tiles : (share < 1 ? 1 : share);
         return start[s] + per_tile[s] * double((tiles + groups - 1) / groups) * double((b * groups + 255) / 256);
     }
     int64_t groups = tiles < 256 ? tiles : 256, per_group = (tiles + groups - 1) / groups;

@@ -32,6 +32,17 @@ def test_shapes_at_the_edges(M, N, K, fmt, pack, call):
     check(yd.cpu().numpy().view(np.float16), x, W, g, f"{M}x{N}x{K}")
 
 
+# one to seven half slices, tiles for all workgroups of the chip and for twice as many
+@pytest.mark.parametrize("M,N,K", [(1, 32784, 320), (5, 65552, 264), (16, 16400, 640), (2, 32768, 584), (16, 16399, 960), (3, 33000, 904), (9, 12304, 1280),
+                                   (16, 8208, 1600), (1, 16384, 1320), (7, 24577, 1528), (33, 9000, 1600), (40, 20000, 960), (4, 16400, 2240)])
+def test_several_workgroups_per_cu(M, N, K):
+    x, W, g = si.layer(43000 + M + N + K, M, N, K)
+    xd, wd = to_dev(x.view(np.int16)), to_dev(tl.tl_pack_1p6bit(W))
+    yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
+    tl.tl_ternary_gemm_1p6(xd, wd, si.gamma_bits(g), yd, M, N, K)
+    check(yd.cpu().numpy().view(np.float16), x, W, g, f"{M}x{N}x{K}")
+
+
 # K that leaves two workgroups to a CU (up to 2240) and one over, with tiles for both; a wave without a part of a shorter K
 @pytest.mark.parametrize("specs", [[(16, 14336, 1024), (16, 18448, 640)], [(1, 16384, 2240), (9, 16400, 2240)],
                                    [(2, 16384, 2248), (5, 16384, 2240)], [(3, 32768, 320), (1, 30, 2240)]])

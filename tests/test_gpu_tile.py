@@ -46,6 +46,9 @@ def test_tile_2bit(M, N, K):
 TILE3_SHAPES = [
     (512, 14340, 4096), (2050, 2056, 1288), (500, 4100, 1600), (1030, 2050, 168), (500, 1030, 648), (700, 1100, 952),
     (60, 4096, 11008), (500, 600, 328), (190, 10000, 488),
+    # as those of K = 1600, 168, 648 and 952 above, which the weight-streaming kernel takes since it is the faster one there (500 x 4100 x 1600
+    # 18.0 / 16.3 us, 700 x 1100 x 952 8.0 / 6.8)
+    (2050, 4100, 1600), (1700, 1884, 168), (2500, 1030, 648), (2100, 1430, 952), (82, 7958, 8008), (60, 9004, 5608),
 ]
 
 
