@@ -73,8 +73,8 @@ static double stream3_time(int64_t M, int64_t N, int64_t K)
 }
 
 // Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel, which never
-// loses up to 16 rows: over the calls of the fit the one chosen is 0.4 % slower than the best on average and 11 % in one of
-// a hundred (chosen by what it took with slices of 128 bytes, 3.8 % and 38 %; 4672 -> 4647 at M = 20 7.5 us there, 14.4 here).
+// loses up to 16 rows: over 3200 calls of K up to 4800 the one chosen is 0.15 % slower than the best on average and 6 % in one of
+// a hundred, over 1800 with longer K 0.2 and 8 %.
 // Other K: the plain kernel on the vector ALUs, 3 + K / 4096 (7 + 7.5 per row, up to 4) for every 1024 workgroups of 4 x 4
 // outputs (4090 -> 4099: M = 1 17.8, M = 4 39, M = 16 159, M = 37 324; 1001 -> 1024: M = 1 6.8, M = 16 13).
 bool tile3_preferred(int64_t M, int64_t N, int64_t K)
@@ -100,10 +100,9 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
     c.fixed = c.launch;                                    // of its own it is one launch, however many rows
     c.launches = double((M + 15) / 16) / 32.0;
     c.tiled = c.stream;
-    // Short K is mostly start and end on either side, and the streaming kernel's time less certain (0.79 .. 1.18 of the fit): the tiled
-    // kernel keeps what the fit puts less than 16 % behind.  Over the 205 such calls the one chosen is 1.2 % slower than the best without
-    // that line and 1.1 to 1.7 % with it, and fewer of them take longer than with the choice before.
-    const double band = K <= 960 ? 0.84 : 1.0;
+    // One step of K and less: the tiles' times, fitted from K = 512 on, are 5 to 10 % too long.  Over 1143 such calls the one chosen is 0.4 %
+    // slower than the best (without the factor 1.4 %, with 0.84 for K up to 960 2.6 % here and 5.6 % up to there).
+    const double band = K <= 320 ? 0.92 : 1.0;
     if (band * tile_at_least(kCost, kShapes, K) >= c.stream) return c;
     pick(M, N, K, &c.tiled);
     c.tiled *= band;
