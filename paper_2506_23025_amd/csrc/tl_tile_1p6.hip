@@ -53,9 +53,11 @@ int pick(int64_t M, int64_t N, int64_t K, double* us)
 
 // What the weight-streaming kernel (gemv3) takes (us) for more than 16 rows, W being decoded once per b blocks of 16: t tiles of 16 output
 // rows, s half slices of 64 packed bytes.  While K is one pass, workgroups of s waves share the CUs and walk runs of tiles, and the fullest
-// CU sets the pace; beyond that workgroups of up to 4 tiles go in rounds of 256.  Fitted to 1100 calls over M = 17 .. 2048, N = 512 .. 16384,
-// K = 512 .. 14336, up to 7 half slices to 1700 more with weights out of the caches: 8 % for nine in ten calls.  (The lines of 3 and 5 half
-// slices had been fitted to launches of more workgroups than the CUs held: 13 and 15 % above what the calls take now.)
+// CU sets the pace; beyond that workgroups of up to 4 tiles go in rounds of 256, each staging its rows of x.  Fitted to calls over
+// M = 17 .. 2048, N = 512 .. 16384: 1100 of K = 512 .. 4800, with up to 7 half slices 1700 more and beyond one pass 1400 with weights out
+// of the caches: 8 % for nine in ten calls, 10 % with several passes.  (The lines of 3 and 5 half slices had been fitted to launches of more
+// workgroups than the CUs held: 13 and 15 % above what the calls take now.  Without the rows, which cost a full block 1.6 us per pass of 15
+// waves, calls of 47 and 24 rows lost 13 and 11 %: 9536 -> 10688 and 8320 -> 14080 29.8 and 22.7 us tiled, 34.0 and 25.2 streaming.)
 static double stream3_time(int64_t M, int64_t N, int64_t K)
 {
     const int64_t tiles = (N + 15) / 16, b = (M + 15) / 16;
@@ -68,13 +70,13 @@ static double stream3_time(int64_t M, int64_t N, int64_t K)
     }
     int64_t groups = tiles < 256 ? tiles : 256, per_group = (tiles + groups - 1) / groups;
     if (per_group > 4) { per_group = 4; groups = (tiles + 3) / 4; }
-    const double share = double(b) * double(groups) / 256.0, rounds = double((b * groups + 255) / 256), passes = double((s + 14) / 15);
-    return 1.08 + rounds * (0.85 + 0.8 * passes + 0.8 / 15.0 * double(s * per_group)) + 1.04 * (share > 1.0 ? share : 1.0) * passes;
+    const double rounds = double((b * groups + 255) / 256), passes = double((s + 14) / 15), T = double(per_group);
+    return 1.66 + rounds * (1.53 + 0.35 * passes + double(s) / 15.0 * (T * (0.67 + 0.07 * T) + 1.57 / 16.0 * double(M) / double(b)));
 }
 
 // Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel, which never
 // loses up to 16 rows: over 3200 calls of K up to 4800 the one chosen is 0.15 % slower than the best on average and 6 % in one of
-// a hundred, over 1800 with longer K 0.2 and 8 %.
+// a hundred, over 1800 with longer K 0.1 and 4 %.
 // Other K: the plain kernel on the vector ALUs, 3 + K / 4096 (7 + 7.5 per row, up to 4) for every 1024 workgroups of 4 x 4
 // outputs (4090 -> 4099: M = 1 17.8, M = 4 39, M = 16 159, M = 37 324; 1001 -> 1024: M = 1 6.8, M = 16 13).
 bool tile3_preferred(int64_t M, int64_t N, int64_t K)

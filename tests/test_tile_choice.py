@@ -80,6 +80,24 @@ def test_one_point_six_bit_codes_in_one_pass():
         assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
 
 
+def test_one_point_six_bit_codes_in_several_passes():
+    # measured (us), streaming / best tile: a block of 16 rows costs a pass more than one of few.  9536 -> 10688 at M = 47 34.0 / 29.8, 9536 -> 768 at 258
+    # 26.9 / 25.2, 8320 -> 14080 at 24 25.2 / 22.7; 13248 -> 1920 at 25 10.3 / 31.9, 14208 -> 6592 at 28 24.2 / 34.1
+    for M, N, K in ((47, 10688, 9536), (258, 768, 9536), (24, 14080, 8320)):
+        assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
+    for M, N, K in ((18, 4260, 8704), (25, 1920, 13248), (28, 6592, 14208)):
+        assert instance(ONE_POINT_SIX, M, N, K) == -1, (M, N, K)
+
+
+def test_short_k_of_one_point_six_bit_codes():
+    # measured (us), streaming / best tile: 500 x 4100 x 1600 16.3 / 18.0, 700 x 1100 x 952 6.8 / 8.0; one step of K 33 x 20754 x 64 6.1 / 5.4,
+    # 1279 x 512 x 128 5.7 / 5.2, 846 x 832 x 152 5.8 / 5.3
+    for M, N, K in ((500, 4100, 1600), (700, 1100, 952)):
+        assert instance(ONE_POINT_SIX, M, N, K) == -1, (M, N, K)
+    for M, N, K in ((33, 20754, 64), (1279, 512, 128), (846, 832, 152)):
+        assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
+
+
 def test_workgroups_of_the_streaming_kernel_fit_on_a_compute_unit():
     # 160 KB of LDS in units of 1280 bytes, at most 16 waves; a wave's area (16 rows of 656 bytes) and the table of 2 KB
     fn = tl.raw().tl_internal_stream3_per_cu
