@@ -59,9 +59,11 @@ def _run_1p6_grouped(specs, seed, fmt, check_single=True, sample=None):
 def test_1p6_grouped_mixed_bag(fmt):
     # shapes that share launches (K % 8 == 0, one pass), N not a multiple of 16 or 4, M above 16, a K
     # too long for one pass (runs alone), a K the fast kernel cannot take (plain kernel), the longest
-    # K of one pass with a ragged last slice, a single slice
+    # K of one pass and the first beyond it, a last half slice that is full and one that is not, a single
+    # half slice
     specs = [(1, 4096, 4096), (16, 1000, 1024), (3, 272, 11008), (40, 130, 512), (2, 33, 100),
-             (8, 2050, 4096), (200, 96, 256), (5, 48, 64), (1, 4099, 4480), (7, 17, 4488), (2, 640, 640)]
+             (8, 2050, 4096), (200, 96, 256), (5, 48, 64), (1, 4099, 4480), (7, 17, 4488), (2, 640, 640),
+             (1, 4099, 4800), (7, 17, 4808), (3, 100, 320)]
     _run_1p6_grouped(specs, 11000, fmt)
 
 
