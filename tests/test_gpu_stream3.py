@@ -56,3 +56,26 @@ def test_grouped_launches_of_one_and_two_workgroups_per_cu(specs):
     tl.tl_ternary_gemm_1p6_grouped(jobs, tl.TL_FMT_1P6BIT)
     for yd, x, W, g in want:
         check(yd.cpu().numpy().view(np.float16), x, W, g, f"{yd.shape}")
+
+
+# A NaN and an infinity in two rows of x: every other row is exactly what it is without them.  One pass, several workgroups per CU, several passes;
+# rows that are no power of two and a second block of rows.
+@pytest.mark.parametrize("M,N,K", [(5, 272, 4096), (13, 4100, 960), (7, 1000, 6400), (16, 33, 320), (21, 2000, 11008)])
+@pytest.mark.parametrize("fmt,pack,call", FORMS)
+def test_non_finite_activations_stay_in_their_row(M, N, K, fmt, pack, call):
+    x, W, g = si.layer(44000 + M + N + K, M, N, K)
+    wd = to_dev(pack(W))
+
+    def run(x):
+        yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
+        call(to_dev(x.view(np.int16)), wd, si.gamma_bits(g), yd, M, N, K)
+        return yd.cpu().numpy().view(np.float16)
+
+    clean, bad = run(x), x.copy()
+    bad[1, K - 3] = np.float16(np.nan)
+    bad[3, 7] = np.float16(np.inf)
+    y = run(bad)
+    for m in set(range(M)) - {1, 3}:
+        assert np.array_equal(y[m].view(np.uint16), clean[m].view(np.uint16)), m
+    assert not np.isfinite(y[1].astype(np.float32)).any()
+    assert not np.isfinite(y[3].astype(np.float32)).any()
