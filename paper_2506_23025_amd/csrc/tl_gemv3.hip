@@ -28,6 +28,7 @@
 #include "tl_internal.hpp"
 #include "tl_deal.hpp"
 
+#include <atomic>
 #include <type_traits>
 
 namespace tl {
@@ -184,9 +185,8 @@ __device__ __forceinline__ void addresses(u32x4 w, uint32_t (&at)[4][4])
     }
 }
 
-// c0 + 2^-18 sum_k x_k (w_k + 1) of a tile's half slice.  BATCH dwords' look-ups are issued before the first is used, so that their latency
+// c0 + 2^-18 sum_k x_k (w_k + 1) of a tile's half slice.  All look-ups are issued before the first is used, so that their latency
 // runs under the arithmetic of the ones before.  The table starts the LDS: a byte offset into it is an LDS address.
-template <int BATCH>
 __device__ __forceinline__ f32x4 tile_sum_half(const uint32_t (&at)[4][4], const u32x4 (&bop)[10], f32x4 c0)
 {
     auto lut_at = [](uint32_t off) { return *(const __attribute__((address_space(3))) u32x2*)(uintptr_t(off)); };
@@ -194,17 +194,14 @@ __device__ __forceinline__ f32x4 tile_sum_half(const uint32_t (&at)[4][4], const
     f32x4 acc[2] = {c0, f32x4{0.f, 0.f, 0.f, 0.f}};
     u32x4 mid[2];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        if (d % BATCH == 0) {
-            if (BATCH < 4) __builtin_amdgcn_sched_barrier(0);
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int q = d; q < d + BATCH; ++q)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const u32x2 lo = lut_at(at[q][2 * j]), hi = lut_at(at[q][2 * j + 1]);
-                    e[q][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-                }
+        for (int j = 0; j < 2; ++j) {
+            const u32x2 lo = lut_at(at[q][2 * j]), hi = lut_at(at[q][2 * j + 1]);
+            e[q][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             // The second byte of a table word is c2 alone, six bits up; without it the words are an operand as they stand.  The empty
@@ -287,8 +284,9 @@ struct Run3 {
 static_assert(sizeof(Run3) == 64, "one record per 64-byte line");
 
 // Records (workgroups) of a grouped launch: 16 KB of kernel arguments, or 32 KB where two workgroups fit on a CU (K of up to 7 half
-// slices) and they have 8 tiles each or more: ten layers of K = 1024 13.8 -> 10.3 us, K = 2048 12.4 -> 11.3; two layers of 4.5 tiles per
-// workgroup 6.4 -> 6.8, the larger arguments costing the host 0.5.
+// slices) and the launch holds 2048 tiles or more, which is 4 and more for each of the 512.  Kernel alone / call by call, 512 against 256,
+// means over calls of K = 512 .. 2240: 0.86 .. 0.95 / 1.03 .. 1.07 times as long with 1024 to 2047 tiles (the larger arguments cost the host
+// 0.5 us), 0.82 .. 0.97 / 1.0 with 2048 to 2559, 0.75 .. 0.82 / 0.78 .. 0.84 with 4096 to 6143; ten layers of K = 1024 13.8 -> 10.3 us.
 constexpr int kRec3Few = 256, kRec3Many = 512;
 
 template <int R>
@@ -315,7 +313,9 @@ __device__ __forceinline__ void gemv3_stream_body(const Run3& p)
 
     if (active) stage_half(p.x, wave, rows, K, my_lds, lane);
     // ---- weights: a lane's 16 bytes of a tile lie where the matrix instruction wants them (row mi, k group mg).  The run is a raw buffer
-    // of the rows that exist: rows past N read zeros, and a request costs the vector ALU nothing
+    // of the rows that exist: rows past N read zeros, and a request costs the vector ALU nothing.  Not marked non-temporal, here and in
+    // gemv3_kernel: two requests share a 128-byte line, and so marked calls of K = 1600 .. 14336 took 2 to 5 % longer (up to 14 %), shorter
+    // K and grouped calls 0 to 1 %
     uint32_t voff;
     {
         const int chunk = wave * 4 + mg;
@@ -380,7 +380,7 @@ __device__ __forceinline__ void gemv3_stream_body(const Run3& p)
                 issue_w(first + T + t, t);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            reinterpret_cast<f32x4*>(red + t * 1024)[lane] = tile_sum_half<4>(at, bop, nsx);
+            reinterpret_cast<f32x4*>(red + t * 1024)[lane] = tile_sum_half(at, bop, nsx);
         }
         finish(first, parity);
     };
@@ -455,7 +455,7 @@ gemv3_kernel(Gemv3Params p)
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (MORE) issue_w(slice + NW, t);
             __builtin_amdgcn_sched_barrier(0);
-            part[t] += tile_sum_half<4>(at, bop, nsx);
+            part[t] += tile_sum_half(at, bop, nsx);
             __builtin_amdgcn_sched_barrier(0);
         }
         slice += NW;
@@ -587,9 +587,9 @@ bool gemv3_groups(int64_t M, int64_t N, int64_t K)
 }
 
 // Several GEMMs in one launch of the stream form: every block of 16 activation rows of every GEMM
-// is a job, the 256 workgroups are dealt out to the jobs (tl_deal.hpp; the cost model is the one
-// measured for the 2-bit kernel, whose item structure this kernel shares), and each workgroup
-// gets a record with its run.
+// is a job, the workgroups are dealt out to the jobs (tl_deal.hpp; the constants of the cost model are
+// those measured for the 2-bit kernel: no others were tried for this one), and each workgroup gets a
+// record with its run.
 hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStream_t s)
 {
     for (int i = 0; i < count; ++i)
@@ -597,7 +597,7 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
     struct Block { int job; int64_t m0; int rows; };
     Block blk[kMaxBlocks3];
     int nb = 0;
-    static bool lds_raised[kMaxDevices][2][4];
+    static std::atomic<bool> lds_raised[kMaxDevices][2][4];
     auto flush = [&]() -> hipError_t {
         if (nb == 0) return hipSuccess;
         DealJob dj[kMaxBlocks3];
@@ -647,7 +647,7 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
             }
             const Grouped3Fn<R> fn = pick3_grouped<R>(T);
             const int dev = device_slot();
-            bool& raised = lds_raised[dev < 0 ? 0 : dev][R == kRec3Many][T];
+            std::atomic<bool>& raised = lds_raised[dev < 0 ? 0 : dev][R == kRec3Many][T];
             if (dev < 0 || !raised) {
                 const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
@@ -684,7 +684,7 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
     p.tiles = int((N + 15) / 16);
     const int slices = int((stride + 63) / 64);
     int groups = p.tiles < 256 ? p.tiles : 256;
-    static bool lds_raised[kMaxDevices][2][kT3Max + 1];
+    static std::atomic<bool> lds_raised[kMaxDevices][2][kT3Max + 1];
     const int dev = device_slot();
     auto raise = [&](Kernel3Fn fn, int form, int T) -> hipError_t {
         if (dev >= 0 && lds_raised[dev][form][T]) return hipSuccess;

@@ -544,7 +544,6 @@ tile_kernel(TileParams p)
     typedef std::integral_constant<int, 1> I1;
     typedef std::integral_constant<int, 2> I2;
     typedef std::integral_constant<int, 3> I3;
-    typedef std::true_type Inside;                        // the step lies inside K
     typedef std::false_type Any;
     // The D transfers of a step are spread over its 2 FN NB slots (two per fragment's matrix instructions): all at
     // once, they would hold up the waves at the CU's one address path (16 clocks per transfer) with
