@@ -68,7 +68,8 @@ inline double small_m_time(int64_t M, int64_t N, int64_t K)
 
 // Small-M kernel or tiled matrix-core kernel, when both can run the shape.  A band rather than the bare comparison decides, since machines
 // differ by several percent (the same library: 18.3 and 19.6 us for the same launch): beyond 16 rows the small-M kernel keeps a shape
-// unless the models put the tiled kernel ahead by more than 7 %.  Over the calls of the fit the one chosen is 0.5 % slower than the best on
+// unless the models put the tiled kernel ahead by more than 7 %.  Over the calls of the fit (made before the tiled kernel's present decode,
+// with which it is 1 to 5 % faster than modelled) the one chosen is 0.5 % slower than the best on
 // average and 12 % in one of a hundred; with the constants before 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
 inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
 {

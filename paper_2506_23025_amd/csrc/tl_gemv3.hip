@@ -8,7 +8,7 @@
 //  * A wave's part is a half slice of 64 packed bytes = 320 weights per row; a lane's 16 bytes of a tile (row lane % 16, 16-byte chunk
 //    lane / 16) hold 80 weights and lie in its registers as the matrix instruction wants them: no turn through LDS.  Half lines per
 //    request cost the memory a little (a bare load loop 20.0 instead of 16.7 us for 100 MB); the decode takes longer than that.
-//  * Up to 15 waves in a workgroup, one workgroup per CU: four waves per SIMD cover the chain byte -> address -> look-up -> operand
+//  * Up to 15 waves in a workgroup, one workgroup per CU (more with shorter K, see gemv3_per_cu): four waves per SIMD cover the chain byte -> address -> look-up -> operand
 //    (two LDS round trips and two waves per SIMD, in slices of 128 bytes, took 28 us for the decode sweep where this takes 22.4).
 //  * Decode is a table look-up: a 256-entry table of 8-byte entries in LDS maps a byte to its five digits c = w + 1 as fp16 (subnormal)
 //    pairs: word 0 = c0 << 6 | c2 << 14 | c3 << 22, word 1 = c1 << 6 | c4 << 22 (every digit is used at bit 6 of its half: the matrix

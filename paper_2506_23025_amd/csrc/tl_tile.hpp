@@ -17,8 +17,8 @@
 //    in so that the fragment reads are free of bank conflicts.
 //  * W stays packed in LDS: a 2-bit word holds 16 codes of one column, 1/8 of the bytes of fp16.  A lane
 //    (column i, k quarter g) needs half a word as pairs of neighbours: one byte permute, one shift, and per pair one mask and one packed
-//    fma (decode8_codes, decode8_values): 10 vector operations per 8 weights and lane, spread between the matrix instructions of a
-//    fragment, and a decoded operand feeds FM of them.
+//    fma (decode8_codes, decode8_values): 10 vector operations per 8 weights and lane between the matrix instructions of a fragment, and a
+//    decoded operand feeds FM of them.
 //  * 1.6-bit forms are transcoded to 2-bit words once per workgroup and step: a thread looks up the
 //    8 bytes of a column's 40 weights in a 256-entry table of 10-bit entries and writes 80 bits of
 //    codes to LDS two steps before they are used.  A step is then 160 k or a multiple.
