@@ -7,11 +7,11 @@
 // WK sets that share the NP 32-k blocks of a step out among them, and WM x WN waves per set, each with
 // FM x FN fragments of v_mfma_f32_16x16x32_f16.
 //
-//  * What bounds it: at full size the matrix pipes are busy 0.58 of the time; without the X fragment reads the kernel is
-//    20 % faster, without the decode 6 %, on zero operands, i.e. at the highest clock, 10 %.  Bare loops of the matrix
+//  * What bounds it: at full size the matrix pipes are busy 0.59 of the time; without the X fragment reads the kernel is
+//    20 % faster, without the decode 6 %, on zero operands, i.e. at the highest clock, 13 %.  Bare loops of the matrix
 //    instruction on this data gave 1.85 (32x32x16, W as the row operand), 2.0 (32x32x16, X as the row operand) and 2.3
 //    PFLOP/s (16x16x32), so the 16x16x32 form is used.  Small tiles are bound by latency: the start and end of a launch (5 to 6 us
-//    of a 20 us call) and the barrier of each step; no unit is busy for more than 0.36 of the time.
+//    of a 20 us call) and the barrier of each step; no unit is busy for more than 0.38 of the time.
 //  * X goes to LDS as it lies in memory, by LDS-DMA (global_load_lds_dwordx4: no registers, no
 //    vector instructions), ST steps ahead.  16-byte pieces of a row are swizzled by row on the way
 //    in so that the fragment reads are free of bank conflicts.
