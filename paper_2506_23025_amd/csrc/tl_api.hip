@@ -294,7 +294,7 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
     int nf = 0;
     return tl::run_grouped(
         jobs, count,
-        [](const tl_gemm_job& j) { return j.K % 8 == 0 ? tl::tile3_choice(j.M, j.N, j.K) : tl::KernelChoice{false, 0.0, 0.0, 0.0, 0.0, 0.0}; },
+        [](const tl_gemm_job& j) { return tl::tile3_choice(j.M, j.N, j.K); },
         [&](const tl_gemm_job& j) {
             fused[nf++] = tl::Gemm3Desc{static_cast<const __half*>(j.x), static_cast<const uint8_t*>(j.Wpacked),
                                         static_cast<__half*>(j.y), tl::half_bits_to_float(j.gamma_fp16_bits),

@@ -21,6 +21,10 @@
 //    the weight loads 21.9, with look-ups free of bank conflicts 21.6.  Leaving c2 in the first words and cancelling it by a product of
 //    its own saves the ANDs, adds rounding and gives 22.1: not done.
 //  * The paper expects the 1.6-bit form to cost more arithmetic per weight than the 2-bit form (Sec. 3.3 results, "Limitations").
+//  * K is any number from 8 on.  Rows of packed bytes start at multiples of 16 bytes whatever K is; rows of x at any even address where K is no
+//    multiple of 8, and then their pieces come through registers (ANY_K), which costs 0.3 us and 5 % (10 % with several passes).  Such calls ran
+//    in the tiled kernel's form for odd K: up to 16 rows of 512 .. 16384 x 64 .. 14336 weights this one is 1.6 to 2.1 times as fast on average
+//    (1 x 2577 x 12738 29.0 -> 7.2 us, 7 x 4864 x 3806 12.1 -> 5.7), slower by up to 3 % (0.15 us) in 13 of 1000 calls, K below 290 at 9 rows and more.
 //  * Two forms.  gemv3_stream_kernel (K in one pass of at most 15 half slices, K <= 4800): a wave keeps its half slice, a workgroup walks
 //    a run of tiles in items with the next item's weights in flight; gemv3_grouped_kernel is the same body fed from one record per
 //    workgroup, so that one launch carries several GEMMs.  gemv3_kernel (longer K): waves loop over half slices, one item of up to 4
@@ -159,6 +163,64 @@ __device__ __forceinline__ void stage_half(const unsigned char* x, int hs, int r
     }
 }
 
+// The same for a K that is no multiple of 8, whose rows start at any even address: the pieces come through registers, round i of a wave being
+// the pieces 64 i .. 64 i + 63 of rows of 40.  A piece that reaches past K is fetched from the row's last 16 bytes and shifted down, one past K
+// altogether is zero; pieces past the last row repeat that row.  Rounds I0 .. I0 + R - 1.
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+template <int I0, int R>
+__device__ __forceinline__ void fetch_pieces(const unsigned char* x, int hs, int rows, int K, int lane, u32x4 (&v)[R])
+{
+    asm volatile("" : "+v"(lane));                         // places worked out here, not kept in registers over the passes
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const uint32_t piece = uint32_t((I0 + i) * 64 + lane);
+        uint32_t row = (piece * 1639u) >> 16;              // piece / 40, pieces up to 639
+        uint32_t k = uint32_t(hs) * kHalf3 + (piece - row * 40u) * 8u;
+        if (row >= uint32_t(rows)) row = uint32_t(rows) - 1u;
+        if (k > uint32_t(K) - 8u) k = uint32_t(K) - 8u;
+        v[i] = *(const __attribute__((address_space(1))) u32x4_any*)((const __attribute__((address_space(1))) unsigned char*)x + (row * uint32_t(K) + k) * 2u);
+    }
+}
+template <int I0, int R>
+__device__ __forceinline__ void put_pieces(int hs, int K, unsigned char* area, int lane, const u32x4 (&v)[R])
+{
+    const bool tail = (hs + 1) * kHalf3 > K;
+    asm volatile("" : "+v"(lane));
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const uint32_t piece = uint32_t((I0 + i) * 64 + lane);
+        const uint32_t row = (piece * 1639u) >> 16, col = piece - row * 40u;
+        u32x4 w = v[i];
+        if (tail) {
+            const int past = hs * kHalf3 + int(col) * 8 + 8 - K;              // elements past K, 16 bits each
+            const int n = 16 * (past > 0 ? past : 0);
+            const uint64_t lo = uint64_t(w[0]) | (uint64_t(w[1]) << 32), hi = uint64_t(w[2]) | (uint64_t(w[3]) << 32);
+            uint64_t a = lo, b = hi;
+            if (n >= 128) { a = 0; b = 0; }
+            else if (n >= 64) { a = hi >> (n - 64); b = 0; }
+            else if (n > 0) { a = (lo >> n) | (hi << (64 - n)); b = hi >> n; }
+            w = u32x4{uint32_t(a), uint32_t(a >> 32), uint32_t(b), uint32_t(b >> 32)};
+        }
+        *reinterpret_cast<u32x4*>(area + row * kXRowHalf + col * 16u) = w;
+    }
+}
+// The activations of half slice `hs` so, with `between` (the weights' requests, the table) between asking for them and their way to LDS
+template <class Between>
+__device__ __forceinline__ void stage_pieces(const unsigned char* x, int hs, int rows, int K, unsigned char* area, int lane, Between&& between)
+{
+    auto rounds = [&](auto count) {
+        u32x4 v[decltype(count)::value];
+        fetch_pieces<0>(x, hs, rows, K, lane, v);
+        __builtin_amdgcn_sched_barrier(0);
+        between();
+        put_pieces<0>(hs, K, area, lane, v);
+    };
+    if (rows <= 1) rounds(std::integral_constant<int, 1>{});
+    else if (rows <= 4) rounds(std::integral_constant<int, 3>{});
+    else if (rows <= 8) rounds(std::integral_constant<int, 5>{});
+    else rounds(std::integral_constant<int, 10>{});
+}
+
 // the staged rows -> operands, and c0 - 2^-18 sum_k x over the half slice in accumulator layout (constant 16-row operand)
 __device__ __forceinline__ f32x4 operands_and_seed(const unsigned char* area, int rows, int mi, int mg, u32x4 (&bop)[10])
 {
@@ -294,7 +356,7 @@ struct Rec3Batch {
     Run3 rec[R];
 };
 
-template <int T>
+template <int T, bool ANY_K>
 __device__ __forceinline__ void gemv3_stream_body(const Run3& p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -311,7 +373,8 @@ __device__ __forceinline__ void gemv3_stream_body(const Run3& p)
     const int mi = lane & 15, mg = lane >> 4;              // row of the tile / activation column, chunk of the slice
     const bool active = wave * 4 < chunks;
 
-    if (active) stage_half(p.x, wave, rows, K, my_lds, lane);
+    const bool pieces = ANY_K && (K & 7) != 0;             // rows of x start anywhere
+    if (active && !pieces) stage_half(p.x, wave, rows, K, my_lds, lane);
     // ---- weights: a lane's 16 bytes of a tile lie where the matrix instruction wants them (row mi, k group mg).  The run is a raw buffer
     // of the rows that exist: rows past N read zeros, and a request costs the vector ALU nothing.  Not marked non-temporal, here and in
     // gemv3_kernel: two requests share a 128-byte line, and so marked calls of K = 1600 .. 14336 took 2 to 5 % longer (up to 14 %), shorter
@@ -330,14 +393,18 @@ __device__ __forceinline__ void gemv3_stream_body(const Run3& p)
         const int c = idx < ntiles ? idx : ntiles - 1;
         wreg[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, voff, uint32_t(c) * tile_bytes, 0));
     };
-    if (active) {
+    auto between = [&]() {
+        if (active) {
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            issue_w(t, t);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int t = 0; t < T; ++t) {
+                issue_w(t, t);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-    }
-    fill_table(lut, p.fx != 0);
+        fill_table(lut, p.fx != 0);
+    };
+    if (ANY_K && active && pieces) stage_pieces(p.x, wave, rows, K, my_lds, lane, between);
+    else between();
     u32x4 bop[10];
     f32x4 nsx = f32x4{0.f, 0.f, 0.f, 0.f};
     if (active) {
@@ -394,7 +461,7 @@ __device__ __forceinline__ void gemv3_stream_body(const Run3& p)
 // passes, and a pass's activations and weights are requested while the pass before it is worked on: the activations as soon as the operands
 // are built, each tile's weights as soon as their registers are free.  Against the form with slices of 128 bytes, seven waves and no
 // overlap of the passes: 11008 -> 4096 at M = 1 / 16 6.8 / 11.4 -> 5.8 / 9.2 us, 14336 -> 14336 17.6 / 23.5 -> 14.5 / 18.3.
-template <int T>
+template <int T, bool ANY_K>
 __global__ void __launch_bounds__(1024)
 gemv3_kernel(Gemv3Params p)
 {
@@ -423,26 +490,39 @@ gemv3_kernel(Gemv3Params p)
             res, uint32_t(mi) * stride + uint32_t(chunk < chunks ? chunk : 0) * 16u, 0, 0));
     };
     int slice = wave;                                      // slices >= NW: every wave has one
-    stage_half(xb, slice, rows, K, my_lds, lane);
+    auto between = [&]() {
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        issue_w(slice, t);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < T; ++t) {
+            issue_w(slice, t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        fill_table(reinterpret_cast<u32x2*>(lds_raw), p.fx != 0);
+    };
+    if constexpr (ANY_K) {
+        stage_pieces(xb, slice, rows, K, my_lds, lane, between);
+    } else {
+        stage_half(xb, slice, rows, K, my_lds, lane);
+        between();
     }
-    fill_table(reinterpret_cast<u32x2*>(lds_raw), p.fx != 0);
     f32x4 part[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) part[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     bool first = true;
     auto pass = [&](auto more_tag) {
         constexpr bool MORE = decltype(more_tag)::value;
-        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(T) : "memory");       // the activations, asked for before the weights
+        if constexpr (!ANY_K) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(T) : "memory");       // the activations, asked for before the weights
         u32x4 bop[10];
         const f32x4 nsx = operands_and_seed(my_lds, rows, mi, mg, bop);
         if (first) lds_barrier3();                         // the table is complete
         else asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
         first = false;
-        if constexpr (MORE) {
+        // ANY_K: the next pass's first rounds of pieces (4, 3 or no rows), as many as there are registers for
+        constexpr int AHEAD = T <= 2 ? 3 : (T == 3 ? 2 : 0);
+        u32x4 ahead[AHEAD > 0 ? AHEAD : 1];
+        if constexpr (MORE && ANY_K) {
+            if constexpr (AHEAD > 0) fetch_pieces<0>(xb, slice + NW, rows, K, lane, ahead);
+            __builtin_amdgcn_sched_barrier(0);
+        } else if constexpr (MORE) {
             // the weights as well, before anything is asked for behind the compiler's back
             __builtin_amdgcn_s_waitcnt(vmcnt_imm3(0));
             stage_half(xb, slice + NW, rows, K, my_lds, lane);
@@ -457,6 +537,16 @@ gemv3_kernel(Gemv3Params p)
             __builtin_amdgcn_sched_barrier(0);
             part[t] += tile_sum_half(at, bop, nsx);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (MORE && ANY_K) {
+            if constexpr (AHEAD > 0) put_pieces<0>(slice + NW, K, my_lds, lane, ahead);
+            auto others = [&](auto count) {
+                u32x4 v[decltype(count)::value - AHEAD];
+                fetch_pieces<AHEAD>(xb, slice + NW, rows, K, lane, v);
+                put_pieces<AHEAD>(slice + NW, K, my_lds, lane, v);
+            };
+            if (rows > 8) others(std::integral_constant<int, 10>{});
+            else if (rows * 40 > AHEAD * 64) others(std::integral_constant<int, 5>{});
         }
         slice += NW;
     };
@@ -477,7 +567,7 @@ gemv3_kernel(Gemv3Params p)
 }
 
 // One GEMM: blockIdx.y is the block of 16 activation rows, the tiles are split evenly over gridDim.x.
-template <int T>
+template <int T, bool ANY_K>
 __global__ void __launch_bounds__(1024)
 gemv3_stream_kernel(Gemv3Params p)
 {
@@ -494,48 +584,53 @@ gemv3_stream_kernel(Gemv3Params p)
     r.tile0 = g * per + (g < extra ? g : extra);
     r.tile_end = r.tile0 + per + (g < extra ? 1 : 0);
     r.fx = p.fx;
-    gemv3_stream_body<T>(r);
+    gemv3_stream_body<T, ANY_K>(r);
 }
 
 // Several GEMMs: the host has dealt out the workgroups and written one record for each.
-template <int T, int R>
+template <int T, bool ANY_K, int R>
 __global__ void __launch_bounds__(1024)
 gemv3_grouped_kernel(Rec3Batch<R> b)
 {
-    gemv3_stream_body<T>(b.rec[blockIdx.x]);
+    gemv3_stream_body<T, ANY_K>(b.rec[blockIdx.x]);
 }
 
 using Kernel3Fn = void (*)(Gemv3Params);
 
+// any_k: for a K that is no multiple of 8 (in a grouped launch, that of some job)
+template <bool ANY_K>
 Kernel3Fn pick3(int T)
 {
     switch (T) {
-        case 1: return gemv3_kernel<1>;
-        case 2: return gemv3_kernel<2>;
-        case 3: return gemv3_kernel<3>;
-        default: return gemv3_kernel<4>;
+        case 1: return gemv3_kernel<1, ANY_K>;
+        case 2: return gemv3_kernel<2, ANY_K>;
+        case 3: return gemv3_kernel<3, ANY_K>;
+        default: return gemv3_kernel<4, ANY_K>;
     }
 }
+Kernel3Fn pick3(int T, bool any_k) { return any_k ? pick3<true>(T) : pick3<false>(T); }
 
+template <bool ANY_K>
 Kernel3Fn pick3_stream(int T)
 {
     switch (T) {
-        case 1: return gemv3_stream_kernel<1>;
-        case 2: return gemv3_stream_kernel<2>;
-        default: return gemv3_stream_kernel<3>;
+        case 1: return gemv3_stream_kernel<1, ANY_K>;
+        case 2: return gemv3_stream_kernel<2, ANY_K>;
+        default: return gemv3_stream_kernel<3, ANY_K>;
     }
 }
+Kernel3Fn pick3_stream(int T, bool any_k) { return any_k ? pick3_stream<true>(T) : pick3_stream<false>(T); }
 
 template <int R>
 using Grouped3Fn = void (*)(Rec3Batch<R>);
 
 template <int R>
-Grouped3Fn<R> pick3_grouped(int T)
+Grouped3Fn<R> pick3_grouped(int T, bool any_k)
 {
     switch (T) {
-        case 1: return gemv3_grouped_kernel<1, R>;
-        case 2: return gemv3_grouped_kernel<2, R>;
-        default: return gemv3_grouped_kernel<3, R>;
+        case 1: return any_k ? gemv3_grouped_kernel<1, true, R> : gemv3_grouped_kernel<1, false, R>;
+        case 2: return any_k ? gemv3_grouped_kernel<2, true, R> : gemv3_grouped_kernel<2, false, R>;
+        default: return any_k ? gemv3_grouped_kernel<3, true, R> : gemv3_grouped_kernel<3, false, R>;
     }
 }
 
@@ -545,26 +640,21 @@ constexpr int kMaxBlocks3 = 32;          // blocks of 16 activation rows per gro
 
 hipError_t gemv3_init()
 {
-    for (int T = 1; T <= kT3Max; ++T) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3(T)),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
-        if (e == hipSuccess && T <= 3)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3_stream(T)),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
-        if (e == hipSuccess && T <= 3)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3_grouped<kRec3Few>(T)),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
-        if (e == hipSuccess && T <= 3)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick3_grouped<kRec3Many>(T)),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
-        if (e != hipSuccess) return e;
-    }
+    for (int any_k = 0; any_k < 2; ++any_k)
+        for (int T = 1; T <= kT3Max; ++T) {
+            auto raise = [](const void* fn) { return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLds3); };
+            hipError_t e = raise(reinterpret_cast<const void*>(pick3(T, any_k != 0)));
+            if (e == hipSuccess && T <= 3) e = raise(reinterpret_cast<const void*>(pick3_stream(T, any_k != 0)));
+            if (e == hipSuccess && T <= 3) e = raise(reinterpret_cast<const void*>(pick3_grouped<kRec3Few>(T, any_k != 0)));
+            if (e == hipSuccess && T <= 3) e = raise(reinterpret_cast<const void*>(pick3_grouped<kRec3Many>(T, any_k != 0)));
+            if (e != hipSuccess) return e;
+        }
     return hipSuccess;
 }
 
 bool gemv3_supports(int64_t M, int64_t N, int64_t K)
 {
-    return M >= 1 && N >= 1 && K >= 8 && (K % 8) == 0 && K <= (int64_t(1) << 24) &&
+    return M >= 1 && N >= 1 && K >= 8 && K <= (int64_t(1) << 24) &&
            N <= (int64_t(1) << 24) && (M + 15) / 16 <= 65535;
 }
 
@@ -597,18 +687,20 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
     struct Block { int job; int64_t m0; int rows; };
     Block blk[kMaxBlocks3];
     int nb = 0;
-    static std::atomic<bool> lds_raised[kMaxDevices][2][4];
+    static std::atomic<bool> lds_raised[kMaxDevices][2][2][4];
     auto flush = [&]() -> hipError_t {
         if (nb == 0) return hipSuccess;
         DealJob dj[kMaxBlocks3];
         int NW = 1;
         int64_t total_tiles = 0;
+        bool any_k = false;
         for (int q = 0; q < nb; ++q) {
             const Gemm3Desc& d = jobs[blk[q].job];
             const int tiles = int((d.N + 15) / 16);
             const int slices = int((d.stride + 63) / 64);
             dj[q] = DealJob{tiles, 1, 0.15 * double(blk[q].rows)};
             total_tiles += tiles;
+            any_k = any_k || d.K % 8 != 0;
             if (slices > NW) NW = slices;
         }
         const int most = gemv3_per_cu(NW) >= 2 && total_tiles >= 8 * kRec3Few ? kRec3Many : kRec3Few;
@@ -645,9 +737,9 @@ hipError_t launch_gemv3_jobs(const Gemm3Desc* jobs, int count, bool fx, hipStrea
                     r.fx = fx ? 1 : 0;
                 }
             }
-            const Grouped3Fn<R> fn = pick3_grouped<R>(T);
+            const Grouped3Fn<R> fn = pick3_grouped<R>(T, any_k);
             const int dev = device_slot();
-            std::atomic<bool>& raised = lds_raised[dev < 0 ? 0 : dev][R == kRec3Many][T];
+            std::atomic<bool>& raised = lds_raised[dev < 0 ? 0 : dev][any_k][R == kRec3Many][T];
             if (dev < 0 || !raised) {
                 const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
@@ -684,13 +776,14 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
     p.tiles = int((N + 15) / 16);
     const int slices = int((stride + 63) / 64);
     int groups = p.tiles < 256 ? p.tiles : 256;
-    static std::atomic<bool> lds_raised[kMaxDevices][2][kT3Max + 1];
+    static std::atomic<bool> lds_raised[kMaxDevices][2][2][kT3Max + 1];
+    const bool any_k = K % 8 != 0;
     const int dev = device_slot();
     auto raise = [&](Kernel3Fn fn, int form, int T) -> hipError_t {
-        if (dev >= 0 && lds_raised[dev][form][T]) return hipSuccess;
+        if (dev >= 0 && lds_raised[dev][any_k][form][T]) return hipSuccess;
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLds3);
-        if (e == hipSuccess && dev >= 0) lds_raised[dev][form][T] = true;
+        if (e == hipSuccess && dev >= 0) lds_raised[dev][any_k][form][T] = true;
         return e;
     };
     dim3 grid(groups, unsigned((M + 15) / 16));
@@ -712,7 +805,7 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
         int T = run <= 3 ? run : (run == 4 ? 2 : 3);
         if (T > NW) T = NW;                                // the epilogue gives every thread at most one output quad
         p.groups = groups;
-        Kernel3Fn fn = pick3_stream(T);
+        Kernel3Fn fn = pick3_stream(T, any_k);
         const hipError_t e = raise(fn, 1, T);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(fn, grid, dim3(NW * 64), size_t(NW) * kWaveLds + kLutBytes, s, p);
@@ -722,7 +815,7 @@ hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, floa
     if (T > kT3Max) { T = kT3Max; groups = (p.tiles + T - 1) / T; }
     p.groups = groups;
     grid.x = unsigned(groups);
-    Kernel3Fn fn = pick3(T);
+    Kernel3Fn fn = pick3(T, any_k);
     const hipError_t e = raise(fn, 0, T);
     if (e != hipSuccess) return e;
     const int passes = (slices + kWaves3 - 1) / kWaves3, NW = (slices + passes - 1) / passes;       // as even as they get

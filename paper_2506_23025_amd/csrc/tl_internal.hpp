@@ -87,7 +87,7 @@ hipError_t launch_gemm_generic_gs(const __half* x, const uint32_t* Wp, const __h
                                   int64_t group, __half* y, int64_t M, int64_t N, int64_t K,
                                   hipStream_t s);
 
-// Weight-streaming small-M kernel for the 1.6-bit format.  Needs K % 8 == 0.
+// Weight-streaming small-M kernel for the 1.6-bit format.  Needs K >= 8.
 bool gemv3_supports(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, float gamma, __half* y,
                         int64_t M, int64_t N, int64_t K, bool fx, hipStream_t s);

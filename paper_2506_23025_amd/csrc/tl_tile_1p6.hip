@@ -28,9 +28,9 @@ typedef TileCfg<kTile1p6, true, 1, 2, 1, 2, 4, 10, 2> R16x64;
 
 constexpr int kRagged = 3;
 constexpr TileCost kRaggedCost[kRagged] = {
-    {64, 128, 160, 256, 5.4, 5.4, 0.96, 0.96, 0.96, 0.6, 2.0},
-    {32, 128, 160, 256, 3.7, 3.7, 0.70, 0.70, 0.70, 0.6, 2.0},
-    {16, 64, 320, 256, 3.1, 3.1, 0.63, 0.63, 0.63, 0.6, 2.0},
+    {64, 128, 160, 256, 4.76, 4.76, 0.847, 0.979, 0.979, 0.93, 0.92},
+    {32, 128, 160, 256, 3.53, 3.53, 0.668, 0.729, 0.729, 0.93, 1.07},
+    {16, 64, 320, 256, 2.88, 2.88, 0.662, 0.679, 0.679, 1.0, 1.37},
 };
 
 int pick(int64_t M, int64_t N, int64_t K, double* us)
@@ -74,25 +74,15 @@ static double stream3_time(int64_t M, int64_t N, int64_t K)
     return 1.66 + rounds * (1.53 + 0.35 * passes + double(s) / 15.0 * (T * (0.67 + 0.07 * T) + 1.57 / 16.0 * double(M) / double(b)));
 }
 
-// Tiled kernel or what would take the call without it.  Where K % 8 == 0 that is the weight-streaming kernel, which never
-// loses up to 16 rows: over 3200 calls of K up to 4800 the one chosen is 0.15 % slower than the best on average and 6 % in one of
-// a hundred, over 1800 with longer K 0.1 and 4 %.
-// Other K: the plain kernel on the vector ALUs, 3 + K / 4096 (7 + 7.5 per row, up to 4) for every 1024 workgroups of 4 x 4
-// outputs (4090 -> 4099: M = 1 17.8, M = 4 39, M = 16 159, M = 37 324; 1001 -> 1024: M = 1 6.8, M = 16 13).
+// Tiled or weight-streaming kernel, which never loses up to 16 rows: where K % 8 == 0, over 3200 calls of K up to 4800 the one chosen is 0.15 %
+// slower than the best on average and 6 % in one of a hundred, over 1800 with longer K 0.1 and 4 %.
 bool tile3_preferred(int64_t M, int64_t N, int64_t K)
 {
-    if ((M <= 16 && K % 8 == 0) || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
-    double us;
-    if (K % 8 != 0) {
-        pick(M, N, K, &us);
-        const double groups = double((M + 3) / 4) * double((N + 3) / 4) / 1024.0;
-        return us < 3.0 + double(K) / 4096.0 * (7.0 + 7.5 * double(M < 4 ? M : 4)) * (groups > 1.0 ? groups : 1.0);
-    }
+    if (M <= 16 || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
     const KernelChoice c = tile3_choice(M, N, K);
     return c.tiled < c.stream;
 }
 
-// K % 8 == 0
 KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
 {
     KernelChoice c{gemv3_groups(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -102,6 +92,19 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
     c.fixed = c.launch;                                    // of its own it is one launch, however many rows
     c.launches = double((M + 15) / 16) / 32.0;
     c.tiled = c.stream;
+    if (K % 8 != 0) {
+        if (K < 64) {                                      // below the fit: tiles, as far as anything was measured a third either way
+            c.streams = false;
+            c.tiled = 0.0;
+            return c;
+        }
+        // Rows of x that start anywhere cost the streaming kernel 5 %, 10 with several passes, and 0.3 us.  Fitted with the three tiles' times to 1250
+        // calls over M = 17 .. 2048, N = 512 .. 16384, K = 64 .. 14336; on 1250 others the one chosen is 0.18 % slower than the best and 7 % in
+        // one of a hundred.
+        c.tiled = c.stream = c.stream * (c.streams ? 1.05 : 1.1) + 0.3;
+        if (tile_at_least(kRaggedCost, kRagged, K) < c.stream) pick(M, N, K, &c.tiled);
+        return c;
+    }
     // One step of K and less: the tiles' times, fitted from K = 512 on, are 5 to 10 % too long.  Over 1143 such calls the one chosen is 0.4 %
     // slower than the best (without the factor 1.4 %, with 0.84 for K up to 960 2.6 % here and 5.6 % up to there).
     const double band = K <= 320 ? 0.92 : 1.0;

@@ -79,3 +79,38 @@ def test_non_finite_activations_stay_in_their_row(M, N, K, fmt, pack, call):
         assert np.array_equal(y[m].view(np.uint16), clean[m].view(np.uint16)), m
     assert not np.isfinite(y[1].astype(np.float32)).any()
     assert not np.isfinite(y[3].astype(np.float32)).any()
+
+
+# K that is no multiple of 8, whose rows of x start at any even address: the pieces of one to ten rounds of a wave (1, 4, 8 and 16 rows), the last piece
+# of a row cut at every place, a half slice less one, one over and one piece over, passes with one, two and more rows ahead of their tiles
+@pytest.mark.parametrize("fmt,pack,call", FORMS)
+@pytest.mark.parametrize("M,N,K", [(1, 1, 9), (16, 40, 15), (2, 33, 319), (5, 50, 321), (8, 17, 322), (9, 100, 323), (4, 4099, 2045), (16, 1030, 4799),
+                                   (3, 4099, 644), (1, 300, 4801), (6, 4100, 5002), (16, 4098, 9603), (4, 8211, 9607), (7, 12304, 4873), (2, 16400, 4805),
+                                   (16, 12300, 9611), (40, 700, 1001), (33, 130, 8190), (20, 9000, 1013)])
+def test_any_k(M, N, K, fmt, pack, call):
+    x, W, g = si.layer(45000 + M + N + K, M, N, K)
+    xd, wd = to_dev(x.view(np.int16)), to_dev(pack(W))
+    yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
+    call(xd, wd, si.gamma_bits(g), yd, M, N, K)
+    check(yd.cpu().numpy().view(np.float16), x, W, g, f"{M}x{N}x{K}")
+
+
+# such jobs share a launch with others, bit for bit what they give alone; a NaN in the row that follows a row's last piece stays there
+def test_any_k_in_a_grouped_launch():
+    jobs, alone = [], []
+    for i, (M, N, K) in enumerate([(16, 2050, 1001), (3, 1024, 1024), (9, 515, 641), (16, 300, 4799), (1, 40, 9)]):
+        x, W, g = si.layer(46000 + i, M, N, K)
+        if M > 1:
+            x[1, 0], x[M - 1, K - 1] = np.nan, np.inf
+        xd, wd = to_dev(x.view(np.int16)), to_dev(tl.tl_pack_1p6bit(W))
+        yd, ya = (to_dev(np.full((M, N), -21555, dtype=np.int16)) for _ in range(2))
+        jobs.append((xd, wd, si.gamma_bits(g), yd, M, N, K))
+        tl.tl_ternary_gemm_1p6(xd, wd, si.gamma_bits(g), ya, M, N, K)
+        alone.append((ya, yd, x, W, g))
+    tl.tl_ternary_gemm_1p6_grouped(jobs, tl.TL_FMT_1P6BIT)
+    for ya, yd, x, W, g in alone:
+        assert np.array_equal(ya.cpu().numpy(), yd.cpu().numpy())
+        clean = np.isfinite(x).all(axis=1)
+        y = yd.cpu().numpy().view(np.float16)
+        check(y[clean], np.ascontiguousarray(x[clean]), W, g, f"{x.shape}")
+        assert not np.isfinite(y[~clean].astype(np.float32)).any()

@@ -95,6 +95,7 @@ RAGGED_SHAPES = [
     (1, 1, 9), (3, 40, 33), (16, 333, 1001), (16, 4099, 255), (37, 4099, 4090), (70, 257, 127), (40, 1030, 129), (200, 2050, 257),
     (150, 8200, 641), (900, 2500, 1100), (1030, 4100, 383), (5, 64, 2044), (33, 130, 8190),
     (1024, 4096, 1001), (700, 2050, 127),
+    (79, 4928, 74), (292, 730, 86),                        # 1.6-bit: the smaller tiles, ahead of the streaming kernel for short rows alone
 ]
 
 
