@@ -153,7 +153,7 @@ tl_status tl_unpack_dev(tl_format fmt, const void* packed, int64_t N, int64_t K,
  * because the fast kernels compute sum (w + 1) x - sum x (Sec. 3.1 stores w + 1).
  * Any M, N, K >= 1 is accepted; the library picks the kernel from the shape
  * (small M: weight-streaming kernel; large M: tiled matrix-core kernel; K that is no
- * multiple of 64: the tiled kernel's form for such rows, or the generic kernel where that is faster).  Results are deterministic:
+ * multiple of 64: the streaming or the tiled kernel's form for such rows, or the generic kernel).  Results are deterministic:
  * no atomics, fixed reduction order.  Behaviour on a 2-bit code 3 is memory-safe
  * but otherwise unspecified.
  */
@@ -171,8 +171,8 @@ tl_status tl_init(void);
 
 /*
  * The kernel tl_ternary_gemm (TL_PATH_AUTO) runs for a shape: TL_PATH_GEMV, TL_PATH_MFMA or
- * TL_PATH_GENERIC (K no multiple of 64: the any-shape kernels, i.e. the generic kernel or the tiled
- * kernel's form for odd K); TL_PATH_AUTO (0) if M, N or K is not a valid size.  A pure function of the
+ * TL_PATH_GENERIC (K no multiple of 64: the any-shape kernels, i.e. the generic kernel or the streaming or
+ * tiled kernel's form for odd K); TL_PATH_AUTO (0) if M, N or K is not a valid size.  A pure function of the
  * three numbers (host side, touches no GPU): the library's cost models of its two fast
  * kernels decide between them where both can run the shape.
  */

@@ -73,6 +73,7 @@ inline double small_m_time(int64_t M, int64_t N, int64_t K)
 // average and 12 % in one of a hundred; with the constants before 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
 inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
 {
+    if (K % 64 != 0) return tile_ragged_choice(M, N, K);
     KernelChoice c{gemv_supports(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!c.streams || M <= 16 || !mfma_supports(M, N, K)) return c;
     c.stream = small_m_time(M, N, K);
@@ -134,6 +135,7 @@ tl_status tl_unpack_dev(tl_format fmt, const void* packed, int64_t N, int64_t K,
 tl_path tl_ternary_gemm_which(int64_t M, int64_t N, int64_t K)
 {
     if (!tl::dims_ok(M, N, K)) return TL_PATH_AUTO;
+    if (K % 64 != 0) return TL_PATH_GENERIC;
     const tl::KernelChoice c = tl::choice_2bit(M, N, K);
     if (c.streams && !(c.tiled < c.stream)) return TL_PATH_GEMV;
     if (tl::mfma_supports(M, N, K)) return TL_PATH_MFMA;
@@ -154,9 +156,12 @@ tl_status tl_ternary_gemm_path(const void* x, const void* Wpacked, uint16_t gamm
 
     if (path == TL_PATH_AUTO) {
         path = tl_ternary_gemm_which(M, N, K);
-        // shapes of the any-shape path: the tiled kernel's form for odd K where it is the faster one
-        if (path == TL_PATH_GENERIC && K % 64 != 0 && tl::tile_ragged_preferred(M, N, K))
-            return tl::from_hip(tl::launch_tile_ragged(xh, wp, gamma, yh, M, N, K, s));
+        // shapes of the any-shape path: the streaming or the tiled kernel's form for such K where it is the faster one
+        if (path == TL_PATH_GENERIC && K % 64 != 0) {
+            const tl::KernelChoice c = tl::tile_ragged_choice(M, N, K);
+            if (c.streams && !(c.tiled < c.stream)) return tl::from_hip(tl::launch_gemv(xh, wp, gamma, yh, M, N, K, s));
+            if (c.streams || tl::tile_ragged_preferred(M, N, K)) return tl::from_hip(tl::launch_tile_ragged(xh, wp, gamma, yh, M, N, K, s));
+        }
     }
     switch (path) {
         case TL_PATH_GENERIC:
@@ -344,9 +349,12 @@ tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, 
 __attribute__((visibility("default"))) int tl_internal_tile_instance(int form, int64_t M, int64_t N, int64_t K, int64_t group)
 {
     switch (form) {
-        case 0:
+        case 0: {
             if (tl_ternary_gemm_which(M, N, K) == TL_PATH_MFMA) return tl::mfma_shape(M, N, K);
-            return tl_ternary_gemm_which(M, N, K) == TL_PATH_GENERIC && K % 64 != 0 && tl::tile_ragged_preferred(M, N, K) ? tl::tile_ragged_shape(M, N, K) : -1;
+            if (tl_ternary_gemm_which(M, N, K) != TL_PATH_GENERIC || K % 64 == 0) return -1;
+            const tl::KernelChoice c = tl::tile_ragged_choice(M, N, K);
+            return (c.streams ? c.tiled < c.stream : tl::tile_ragged_preferred(M, N, K)) ? tl::tile_ragged_shape(M, N, K) : -1;
+        }
         case 1: return tl::tile3_preferred(M, N, K) ? tl::tile3_shape(M, N, K) : -1;
         case 2: return tl::tile_gs_preferred(M, N, K, group) ? tl::tile_gs_shape(M, N, K, group) : -1;
         case 3: return tl::mfma_supports(M, N, K) ? tl::mfma_shape(M, N, K) : -1;

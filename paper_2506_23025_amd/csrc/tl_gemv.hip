@@ -874,6 +874,9 @@ gemv_stream_kernel(GemvBatch b)
 // take if the loop is to keep up with HBM), so every instruction that is not decode counts.
 constexpr int kLeanMaxGroups = 256;
 
+// bytes of 16 packed rows
+__host__ __device__ constexpr size_t packed_tile_bytes(int K) { return size_t((unsigned(K) + 15u) >> 4) * 64u; }
+
 struct WgRec {                    // 64 bytes; rec[blockIdx.x] is read with scalar loads
     const unsigned char* W;       // packed row 0 of the first tile of the run
     const unsigned char* x;       // activations of the job, fp16 [Mrem][K]
@@ -920,7 +923,104 @@ struct LeanOne {
         return r;
     }
 };
+
+// The same for any K and N, and any number of rows (`Mrem` of them): blockIdx.y is the block of 16.
+struct LeanAny : LeanOne {
+    __device__ WgRec mine() const
+    {
+        WgRec r = LeanOne::mine();
+        const int m0 = int(blockIdx.y) * 16;
+        r.W = W + size_t(r.tile0) * packed_tile_bytes(K);
+        r.x = x + size_t(m0) * (size_t(2) * size_t(K));
+        r.y = y + size_t(m0) * size_t(N);
+        r.Mrem = Mrem - m0 < 16 ? Mrem - m0 : 16;
+        return r;
+    }
+};
 static_assert(sizeof(LeanOne) == 64, "the arguments of a lone call");
+
+// Activations whose rows start at any even address (K no multiple of 64), to the places the operand set-up reads: through registers, a row to a
+// request.  Lane l takes piece l of the slice, eighth l % 8 of chunk l / 8; a row's last chunk is its last 64 weights (16 packed bytes).  What
+// lies past K or, in the last chunk, before the chunk's own weights becomes zero; the piece across K is fetched from the row's last 16
+// bytes and shifted down.  Rows past the last one repeat it.
+typedef const __attribute__((address_space(1))) unsigned char* global_bytes;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+typedef u32x2 __attribute__((aligned(2))) u32x2_any;
+__device__ __forceinline__ int first_weight(int chunk, int K)
+{
+    const int last = ((K + 15) & ~15) - 64;
+    return chunk * 64 < last ? chunk * 64 : last;
+}
+template <int COUNT>
+__device__ __forceinline__ void fetch_rows(global_bytes x, int rows, int K, int slice, int lane, u32x4 (&v)[COUNT])
+{
+    const int k = first_weight(slice * 8 + (lane >> 3), K) + (lane & 7) * 8;
+    const uint32_t at = uint32_t(k < K - 8 ? k : K - 8) * 2u;
+    uint32_t row = 0;
+#pragma unroll
+    for (int r = 0; r < COUNT; ++r) {
+        v[r] = *(const __attribute__((address_space(1))) u32x4_any*)(x + row + at);
+        row += r + 1 < rows ? uint32_t(K) * 2u : 0u;
+    }
+}
+// the 16 bytes of a piece that ends n / 16 elements past K
+__device__ __forceinline__ u32x4 shifted_down(u32x4 w, int n)
+{
+    uint64_t lo = uint64_t(w[0]) | (uint64_t(w[1]) << 32), hi = uint64_t(w[2]) | (uint64_t(w[3]) << 32);
+    if (n >= 64) { lo = hi; hi = 0; }
+    const int m = n & 63;
+    if (m) { lo = (lo >> m) | (hi << (64 - m)); hi >>= m; }
+    if (n >= 128) lo = 0;
+    return u32x4{uint32_t(lo), uint32_t(lo >> 32), uint32_t(hi), uint32_t(hi >> 32)};
+}
+// At the start of a kernel every line of code is a miss in the instruction cache: many rows are put right in LDS, by little code, since
+// all of them in registers took 16 rows 0.4 to 0.6 us longer; up to four rows in registers, which the LDS's latency made 0.1 to 0.25 us longer.
+template <int COUNT>
+__device__ __forceinline__ void put_rows(unsigned char* area, int rows, int K, int slice, int lane, u32x4 (&v)[COUNT])
+{
+    const bool tail = (slice + 1) * kSliceK > K;
+    const int chunk = slice * 8 + (lane >> 3);
+    const int k = first_weight(chunk, K) + (lane & 7) * 8;
+    const int past = k + 8 - K;                            // elements past K
+    const bool zero = past >= 8 || k < chunk * 64;
+    if (COUNT <= 4 && tail) {
+        const int n = zero ? 128 : 16 * (past > 0 ? past : 0);
+#pragma unroll
+        for (int r = 0; r < COUNT; ++r) v[r] = shifted_down(v[r], n);
+    }
+#pragma unroll
+    for (int r = 0; r < COUNT; ++r) *reinterpret_cast<u32x4*>(area + r * 1024 + (uint32_t(lane ^ (r & 7)) << 4)) = v[r];
+    if (COUNT <= 4 || !tail) return;
+#pragma unroll 1
+    for (int r = 0; r < rows; ++r)
+        if (zero) *reinterpret_cast<u32x4*>(area + r * 1024 + (uint32_t(lane ^ (r & 7)) << 4)) = u32x4{0u, 0u, 0u, 0u};
+    const unsigned long long cut = __builtin_amdgcn_ballot_w64(past > 0 && !zero);
+    if (cut) {                                             // one piece of the slice, lane l's: lane r does row r's
+        const int l = __builtin_ctzll(cut), n = 16 * (first_weight(slice * 8 + (l >> 3), K) + (l & 7) * 8 + 8 - K);
+        if (lane < rows) {
+            u32x4* const p = reinterpret_cast<u32x4*>(area + lane * 1024 + (uint32_t(l ^ (lane & 7)) << 4));
+            *p = shifted_down(*p, n);
+        }
+    }
+}
+// the lane's place in its row of packed words: the row's last chunk, and what lies past it, are its last 16 bytes
+__device__ __forceinline__ uint32_t chunk_place(uint32_t chunk, uint32_t row_bytes)
+{
+    return chunk * 16u < row_bytes - 16u ? chunk * 16u : row_bytes - 16u;
+}
+// four consecutive columns of y from `col` on, as many as there are
+__device__ __forceinline__ void store_quad_any(__attribute__((address_space(1))) __half* row, int col, int N, f32x4 s, float gamma)
+{
+    if (col + 4 <= N) {
+        const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
+        const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
+        *(__attribute__((address_space(1))) u32x2_any*)(row + col) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+    } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            if (col + r < N) *(__attribute__((address_space(1))) _Float16*)(row + col + r) = (_Float16)(gamma * s[r]);
+    }
+}
 
 // PASSES: jobs may have K beyond the waves' slices (the down projection among the linears of a block).  Such a job's run is
 // streamed once per NW slices; between passes the sums of the run wait in LDS (1 KB per tile behind the waves' areas)
@@ -932,7 +1032,12 @@ static_assert(sizeof(LeanOne) == 64, "the arguments of a lone call");
 // other in the same accumulators, each scaled by its group's scales of the lane's four output rows, which are
 // requested with the tile's weights.  Against the general form, groups of 256: block at M = 1 / 4 / 16 16.0 / 17.2 / 24.5 ->
 // 15.8 / 16.6 / 19.5 us, its jobs of one pass 11.7 / 12.3 / 13.7 -> 10.4 / 10.7 / 12.1, 4096 x 11008 alone 8.8 / 10.3 / 15.1 -> 7.7 / 8.2 / 10.9.
-template <int T, bool PASSES, bool GS, class Args>
+// ANY: any K from 64 on and any N (GS: N a multiple of 4), jobs with fewer slices than waves among them.  Packed rows then start at multiples of 4
+// bytes, rows of x and y at any even address.  A row's last 16-byte chunk of weights is its last 16 bytes, wherever they start: no
+// request leaves the row, and what overlaps the chunk before meets zeros.  The activations come through registers.  Calls with K no multiple of 64
+// ran in the tiled kernel's form for those: up to 4 rows of 512 .. 16384 x 64 .. 14336 weights this one is 1.8 times as fast on average
+// (666 calls, none slower), 4099 x 4090 at M = 1 / 16 / 37 8.0 / 8.3 / 10.7 -> 4.3 / 5.7 / 6.8 us.
+template <int T, bool PASSES, bool GS, bool ANY, class Args>
 __global__ void __launch_bounds__(512)
 gemv_lean_kernel(Args b)
 {
@@ -947,7 +1052,7 @@ gemv_lean_kernel(Args b)
     const auto& R = b.mine();
     const int K = R.K, N = R.N, rows = R.Mrem, ntiles = R.ntiles;
     const unsigned char* const Wrun = R.W;
-    const uint32_t row_bytes = uint32_t(K) >> 2;
+    const uint32_t row_bytes = ANY ? ((uint32_t(K) + 15u) >> 4) * 4u : uint32_t(K) >> 2;
     const uint32_t tile_bytes = 16u * row_bytes;
 
     const int lr = lane >> 3, lc = lane & 7;   // load mapping: row of the half tile, chunk of the slice
@@ -981,7 +1086,23 @@ gemv_lean_kernel(Args b)
             }
         }
     };
-    stage_x(wave);
+    auto stage_any = [&](int slice, auto&& between) {      // `between`: what is asked for between the activations and their way to LDS
+        auto with = [&](auto count) {
+            u32x4 v[decltype(count)::value];
+            int k = K;
+            if constexpr (PASSES) asm volatile("" : "+s"(k));  // the rows' addresses worked out here, not kept over the passes
+            fetch_rows((gbytes)R.x, rows, k, slice, lane, v);
+            __builtin_amdgcn_sched_barrier(0);
+            between();
+            put_rows(my_lds, rows, k, slice, lane, v);
+        };
+        if (rows <= 1) with(std::integral_constant<int, 1>{});
+        else if (rows <= 4) with(std::integral_constant<int, 4>{});
+        else if (rows <= 8) with(std::integral_constant<int, 8>{});
+        else with(std::integral_constant<int, 16>{});
+    };
+    bool idle = ANY && wave >= slices;                     // this wave has no slice in this pass
+    if constexpr (!ANY) stage_x(wave);
     constexpr int H = GS ? 2 : 1;
     // GS: the job's scales from the run's first row as a raw buffer, the lane's rows in it, and the units' groups
     const uint32_t last_unit = uint32_t(K - 1) >> 8;
@@ -1003,13 +1124,17 @@ gemv_lean_kernel(Args b)
     // ---- weights: the lane's two 16-byte pieces of a tile, relative to the tile's first row
     auto offset_of = [&](int slice) {
         uint32_t chunk = uint32_t(slice) * 8u + uint32_t(lc);
+        if constexpr (ANY) return uint32_t(lr) * row_bytes + chunk_place(chunk, row_bytes);
         if (chunk >= (uint32_t(K) >> 6)) chunk = 0;        // past K: multiplied by zero activations
         return uint32_t(lr) * row_bytes + chunk * 16u;
     };
     uint32_t voff0 = offset_of(wave);
     uint32_t voff1 = voff0 + 8u * row_bytes;
     // the run as a raw buffer (no stride, byte offsets, size = the run): base in scalar registers
-    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Wrun), 0, uint32_t(ntiles) * tile_bytes, 0x00020000);
+    // (ANY: of the rows that exist; the others read zeros)
+    const int run_rows = ANY && N - R.tile0 * 16 < ntiles * 16 ? N - R.tile0 * 16 : ntiles * 16;
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char*>(Wrun), 0, ANY ? uint32_t(run_rows) * row_bytes : uint32_t(ntiles) * tile_bytes, 0x00020000);
     u32x4 wreg[T][2];
     u32x2 sreg[T][H];
     auto issue_w = [&](int idx, int t) {                   // idx: tile of the run; past the run: its last tile again
@@ -1028,13 +1153,20 @@ gemv_lean_kernel(Args b)
         }
     };
     // in tile order, and kept so: the loop's wait counts are the worse of this order and its own
+    auto first_tiles = [&]() {
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        issue_w(t, t);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < T; ++t) {
+            issue_w(t, t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if constexpr (ANY) {
+        if (!idle) stage_any(wave, first_tiles);
+    } else {
+        first_tiles();
+        // the compiler does not track LDS-DMA: wait until only the weight (and scale) loads are outstanding
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((GS ? 4 : 2) * T));
     }
-    // the compiler does not track LDS-DMA: wait until only the weight (and scale) loads are outstanding
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm((GS ? 4 : 2) * T));
 
     // ---- activations -> MFMA B operands (see gemv_stream_kernel) and the -sum(x) seed ----------
     uint32_t breg[2][4][8];
@@ -1047,7 +1179,7 @@ gemv_lean_kernel(Args b)
         const int xrow = mi & (mr - 1);
         const uint32_t xr_off = uint32_t(xrow) * 1024u + uint32_t(mg) * 128u;
         const uint32_t sw = uint32_t(xrow & 7);
-        const bool live = mi < rows && (!(PASSES && GS) || active);
+        const bool live = mi < rows && (ANY || !(PASSES && GS) || active);
         const uint32_t sel_lo = live ? 0x05040100u : 0x0c0c0c0cu;
         const uint32_t sel_hi = live ? 0x07060302u : 0x0c0c0c0cu;
 #pragma unroll
@@ -1072,7 +1204,7 @@ gemv_lean_kernel(Args b)
                 nsx[GS ? h : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), nsx[GS ? h : 0], 0, 0, 0);
             }
     };
-    build(true);
+    if (!ANY || !idle) build(true);
 
     const uint32_t ww_off = uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
     const uint32_t wr_off0 = uint32_t(mi) * 128u + (uint32_t((mg) ^ (mi & 7)) << 4);
@@ -1088,7 +1220,8 @@ gemv_lean_kernel(Args b)
     // loaded again at once with the tile T further on.
     // REFILL 2 (PASSES): with the first tiles of the next pass, to whose slice the offsets have been moved.
     unsigned char* const ysum = lds_raw + NW * kStride;
-    bool idle = false, next_live = true;                   // this wave has no slice in this pass, has one in the next
+    constexpr bool kSkips = ANY || (PASSES && !GS);        // waves without a slice compute nothing
+    bool next_live = true;                                 // this wave has a slice in the next pass
     auto item = [&](auto nt_tag, auto refill_tag, int first, int parity, bool first_pass, bool last_pass) {
         constexpr int NT = decltype(nt_tag)::value;
         constexpr int REFILL = decltype(refill_tag)::value;
@@ -1097,7 +1230,7 @@ gemv_lean_kernel(Args b)
         for (int t = 0; t < NT; ++t) part[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         // A wave without a slice in the last pass only takes part in the exchange.  (GS: it multiplies zeros as well.  Left out there,
         // the block at M = 4 takes 16.65 instead of 16.42 us, the branch's registers being spilled.)
-        if (!PASSES || GS || !idle) {
+        if (!kSkips || !idle) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             unsigned char* const reg_t = my_lds + (t & 1) * 2048;
@@ -1119,7 +1252,7 @@ gemv_lean_kernel(Args b)
                 }
             }
             if constexpr (REFILL != 0) {
-                if (REFILL == 1 || GS || next_live) issue_w(REFILL == 2 ? t : first + T + t, t);
+                if (REFILL == 1 || !kSkips || next_live) issue_w(REFILL == 2 ? t : first + T + t, t);
                 __builtin_amdgcn_s_setprio(0);
                 // the requests leave here, as soon as the registers are free: left to itself the
                 // scheduler sinks all of an item's loads to its end, which costs two tiles of lead
@@ -1160,7 +1293,7 @@ gemv_lean_kernel(Args b)
         }
         }
         if constexpr (REFILL == 2) {
-            if (GS || next_live) {
+            if (!kSkips || next_live) {
 #pragma unroll
                 for (int t = NT; t < T; ++t) issue_w(t, t);
             }
@@ -1169,7 +1302,7 @@ gemv_lean_kernel(Args b)
         unsigned char* const red = my_lds + 4096 + parity * (T * 1024);
 #pragma unroll
         for (int t = 0; t < NT; ++t)                       // GS: an idle wave's zeros may have met an infinite scale
-            reinterpret_cast<f32x4*>(red + t * 1024)[lane] = (GS && PASSES && idle) ? f32x4{0.f, 0.f, 0.f, 0.f} : part[t];
+            reinterpret_cast<f32x4*>(red + t * 1024)[lane] = (GS && PASSES && !ANY && idle) ? f32x4{0.f, 0.f, 0.f, 0.f} : part[t];
         __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
         __builtin_amdgcn_s_barrier();
         if (ot < NT) {
@@ -1185,10 +1318,14 @@ gemv_lean_kernel(Args b)
                 if (!last_pass) *keep = s;
             }
             if (mi < rows && (!PASSES || last_pass)) {
-                const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
-                const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
-                *(__attribute__((address_space(1))) u32x2*)(yrow + (ycol + 16u * uint32_t(first + ot))) =
-                    u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+                const uint32_t col = ycol + 16u * uint32_t(first + ot);
+                if constexpr (ANY) {
+                    store_quad_any(yrow, int(col), N, s, gamma);
+                } else {
+                    const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
+                    const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
+                    *(__attribute__((address_space(1))) u32x2*)(yrow + col) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+                }
             }
         }
     };
@@ -1228,10 +1365,17 @@ gemv_lean_kernel(Args b)
                 __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
                 __builtin_amdgcn_s_barrier();
                 idle = !next_live;
-                if (!idle) stage_x(slice);
-                if (GS || !idle) {
-                    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
-                    build(!idle);
+                if constexpr (ANY) {
+                    if (!idle) {
+                        stage_any(slice, [] {});
+                        build(true);
+                    }
+                } else {
+                    if (!idle) stage_x(slice);
+                    if (GS || !idle) {
+                        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
+                        build(!idle);
+                    }
                 }
             }
         }
@@ -1256,7 +1400,8 @@ gemv_lean_kernel(Args b)
 constexpr int kLongMaxPasses = 4;
 constexpr int kLongWaveLds = kWaveLds + 2048;     // 16 KB of activation staging + one tile slice
 
-template <int T, class Args>
+// ROWS: 0, or any K and N (see gemv_lean_kernel) and up to ROWS rows, whose next slice waits in registers while a pass is decoded.
+template <int T, int ROWS, class Args>
 __global__ void __launch_bounds__(512)
 gemv_longk_kernel(Args b)
 {
@@ -1272,7 +1417,7 @@ gemv_longk_kernel(Args b)
     const int K = R.K, N = R.N, rows = R.Mrem, ntiles = R.ntiles;
     const int slices = (K + kSliceK - 1) / kSliceK;
     const int P = __builtin_amdgcn_readfirstlane((slices - wave + NW - 1) / NW);   // passes of this wave, >= 1
-    const uint32_t row_bytes = uint32_t(K) >> 2;
+    const uint32_t row_bytes = ROWS ? ((uint32_t(K) + 15u) >> 4) * 4u : uint32_t(K) >> 2;
     const uint32_t tile_bytes = 16u * row_bytes;
 
     const int lr = lane >> 3, lc = lane & 7;   // load mapping: row of the half tile, chunk of the slice
@@ -1285,7 +1430,13 @@ gemv_longk_kernel(Args b)
         // s_nop: the wait state that a transfer needs behind a scalar write of M0
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(base) : "memory");
     };
+    u32x4 xv[ROWS ? ROWS : 1];
     auto stage_x = [&](int p) {
+        if constexpr (ROWS != 0) {
+            fetch_rows((gbytes)R.x, rows, K, wave + NW * p, lane, xv);
+            __builtin_amdgcn_sched_barrier(0);
+            return;
+        }
         const int sl = wave + NW * p;
         const size_t row_stride = size_t(K) * 2;
         gbytes src = (gbytes)(R.x + size_t(sl) * (kSliceK * 2));
@@ -1311,13 +1462,14 @@ gemv_longk_kernel(Args b)
     };
 
     // ---- weights: the T tile slices of a pass into register set `set`
-    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(R.W), 0, uint32_t(ntiles) * tile_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<unsigned char*>(R.W), 0, ROWS ? uint32_t(N - R.tile0 * 16 < ntiles * 16 ? N - R.tile0 * 16 : ntiles * 16) * row_bytes : uint32_t(ntiles) * tile_bytes, 0x00020000);
     u32x4 wreg[2][T][2];
     auto issue_w = [&](auto set_tag, int p) {
         constexpr int SET = decltype(set_tag)::value;
         uint32_t chunk = uint32_t(wave + NW * p) * 8u + uint32_t(lc);
-        if (chunk >= (uint32_t(K) >> 6)) chunk = 0;        // past K: multiplied by zero activations
-        const uint32_t voff0 = uint32_t(lr) * row_bytes + chunk * 16u;
+        if (!ROWS && chunk >= (uint32_t(K) >> 6)) chunk = 0;        // past K: multiplied by zero activations
+        const uint32_t voff0 = uint32_t(lr) * row_bytes + (ROWS ? chunk_place(chunk, row_bytes) : chunk * 16u);
         const uint32_t voff1 = voff0 + 8u * row_bytes;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -1338,7 +1490,8 @@ gemv_longk_kernel(Args b)
     const bool live = mi < rows;
     const uint32_t sel_lo = live ? 0x05040100u : 0x0c0c0c0cu;
     const uint32_t sel_hi = live ? 0x07060302u : 0x0c0c0c0cu;
-    auto build = [&]() {
+    auto build = [&](int p) {
+        if constexpr (ROWS != 0) put_rows(my_lds, rows, K, wave + NW * p, lane, xv);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1406,19 +1559,19 @@ gemv_longk_kernel(Args b)
     if (P > 1) {
         issue_w(Set1{}, 1);
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * T));      // x(0) is in
-        build();
+        build(0);
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * T));      // W(0) is in
         stage_x(1);
     } else {
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * T));
-        build();
+        build(0);
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     }
     for (int p = 0; p < P; p += 2) {
         decode(Set0{});                                    // pass p
         if (p + 1 < P) {
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // x(p + 1) and W(p + 1) are in
-            build();
+            build(p + 1);
             if (p + 2 < P) {
                 issue_w(Set0{}, p + 2);
                 stage_x(p + 2);
@@ -1426,7 +1579,7 @@ gemv_longk_kernel(Args b)
             decode(Set1{});                                // pass p + 1
             if (p + 2 < P) {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-                build();
+                build(p + 2);
                 if (p + 3 < P) {
                     issue_w(Set1{}, p + 3);
                     stage_x(p + 3);
@@ -1457,6 +1610,10 @@ gemv_longk_kernel(Args b)
         if (mi < rows) {
             gh_ptr const yrow = (gh_ptr)(R.y + size_t(mi) * size_t(N));
             const uint32_t ycol = uint32_t(R.tile0 + ot) * 16u + 4u * uint32_t(mg);
+            if constexpr (ROWS != 0) {
+                store_quad_any(yrow, int(ycol), N, s, gamma);
+                return;
+            }
             const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
             const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
             *(__attribute__((address_space(1))) u32x2*)(yrow + ycol) =
@@ -1557,23 +1714,23 @@ constexpr int kStreamMaxRun = 32;       // tiles of a run whose sums fit the 32 
 template <class Args>
 using LeanFn = void (*)(Args);
 
-template <class Args, bool PASSES, bool GS>
+template <class Args, bool PASSES, bool GS, bool ANY>
 LeanFn<Args> pick_lean(int T)
 {
     switch (T) {
-        case 1: return gemv_lean_kernel<1, PASSES, GS, Args>;
-        case 2: return gemv_lean_kernel<2, PASSES, GS, Args>;
-        default: return gemv_lean_kernel<3, PASSES, GS, Args>;
+        case 1: return gemv_lean_kernel<1, PASSES, GS, ANY, Args>;
+        case 2: return gemv_lean_kernel<2, PASSES, GS, ANY, Args>;
+        default: return gemv_lean_kernel<3, PASSES, GS, ANY, Args>;
     }
 }
 
 constexpr int lean_lds(bool passes) { return 8 * stream_wave_lds(3) + (passes ? kStreamMaxRun * 1024 : 0); }
 
 // kept: tiles of the longest run of a job of several passes
-template <bool PASSES, bool GS, class Args>
-hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept, hipStream_t s)
+template <bool PASSES, bool GS, bool ANY, class Args>
+hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept, hipStream_t s)
 {
-    const LeanFn<Args> fn = pick_lean<Args, PASSES, GS>(T);
+    const LeanFn<Args> fn = pick_lean<Args, PASSES, GS, ANY>(T);
     static bool lds_raised[kMaxDevices][4];
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][T]) {
@@ -1582,15 +1739,15 @@ hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept,
         if (e != hipSuccess) return e;
         if (dev >= 0) lds_raised[dev][T] = true;
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(NW * 64), size_t(NW) * stream_wave_lds(T) + size_t(kept) * 1024, s, args);
+    hipLaunchKernelGGL(fn, grid, dim3(NW * 64), size_t(NW) * stream_wave_lds(T) + size_t(kept) * 1024, s, args);
     return hipGetLastError();
 }
 
-template <class Args>
-hipError_t launch_lean_args(const Args& args, int grid, int NW, int T, int kept, bool gs, hipStream_t s)
+template <bool ANY, class Args>
+hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept, bool gs, hipStream_t s)
 {
-    if (gs) return kept ? launch_lean_args<true, true>(args, grid, NW, T, kept, s) : launch_lean_args<false, true>(args, grid, NW, T, 0, s);
-    return kept ? launch_lean_args<true, false>(args, grid, NW, T, kept, s) : launch_lean_args<false, false>(args, grid, NW, T, 0, s);
+    if (gs) return kept ? launch_lean_args<true, true, ANY>(args, grid, NW, T, kept, s) : launch_lean_args<false, true, ANY>(args, grid, NW, T, 0, s);
+    return kept ? launch_lean_args<true, false, ANY>(args, grid, NW, T, kept, s) : launch_lean_args<false, false, ANY>(args, grid, NW, T, 0, s);
 }
 
 // ceil(2^31 / units per group): u * inverse / 2^31 rounded down is u / hpg for every u and hpg up to 2^15 (the error of the
@@ -1613,18 +1770,18 @@ LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int 
 
 // Launch of the lean kernel: wg[j] workgroups for job j, each with a run of consecutive tiles
 // (the first tiles % wg[j] of them one tile longer), written out as one record per workgroup.
-hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, bool gs, hipStream_t s)
+hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, bool gs, bool any, hipStream_t s)
 {
-    if (b.count == 1) {
+    if (b.count == 1 && !any) {
         const GemvJob& J = b.job[0];
-        return launch_lean_args(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0], J.scales, group_inverse(J)), wg[0], NW, T, kept, gs, s);
+        return launch_lean_args<false>(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0], J.scales, group_inverse(J)), dim3(wg[0]), NW, T, kept, gs, s);
     }
     LeanBatch lb;
     int grid = 0;
     for (int j = 0; j < b.count; ++j) {
         const GemvJob& J = b.job[j];
         const int per = J.tiles / wg[j], plus = J.tiles % wg[j];
-        const size_t tile_bytes = size_t(16) * (size_t(J.K) / 4);
+        const size_t tile_bytes = packed_tile_bytes(J.K);
         const uint32_t inv = group_inverse(J);
         for (int g = 0; g < wg[j]; ++g) {
             WgRec& r = lb.rec[grid++];
@@ -1639,29 +1796,64 @@ hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kep
             r.group_inv = inv; r.pad = 0;
         }
     }
-    return launch_lean_args(lb, grid, NW, T, kept, gs, s);
+    return any ? launch_lean_args<true>(lb, dim3(grid), NW, T, kept, gs, s) : launch_lean_args<false>(lb, dim3(grid), NW, T, kept, gs, s);
+}
+
+// Tiles per item of a launch whose longest run is `run` (see launch_stream), at most one output quad per thread
+int tiles_per_item(int run, int NW)
+{
+    const int T = run <= 3 ? run : (run == 4 ? 2 : 3);
+    return T < NW ? T : NW;
+}
+
+// rows: 0, or the rows of a call of any K and N
+template <class Args>
+LeanFn<Args> pick_longk(int T, int rows)
+{
+    if constexpr (std::is_same<Args, LeanAny>::value) {
+        if (rows <= 1) return T == 1 ? gemv_longk_kernel<1, 1, Args> : gemv_longk_kernel<2, 1, Args>;
+        if (rows <= 4) return T == 1 ? gemv_longk_kernel<1, 4, Args> : gemv_longk_kernel<2, 4, Args>;
+        return T == 1 ? gemv_longk_kernel<1, 16, Args> : gemv_longk_kernel<2, 16, Args>;
+    } else {
+        return T == 1 ? gemv_longk_kernel<1, 0, Args> : gemv_longk_kernel<2, 0, Args>;
+    }
 }
 
 template <class Args>
-LeanFn<Args> pick_longk(int T)
+hipError_t launch_longk_args(const Args& args, dim3 grid, int T, int rows, hipStream_t s)
 {
-    return T == 1 ? gemv_longk_kernel<1, Args> : gemv_longk_kernel<2, Args>;
-}
-
-template <class Args>
-hipError_t launch_longk_args(const Args& args, int grid, int T, hipStream_t s)
-{
-    const LeanFn<Args> fn = pick_longk<Args>(T);
-    static bool lds_raised[kMaxDevices][3];
-    const int dev = device_slot();
-    if (dev < 0 || !lds_raised[dev][T]) {
+    const LeanFn<Args> fn = pick_longk<Args>(T, rows);
+    static bool lds_raised[kMaxDevices][3][3];
+    const int dev = device_slot(), kind = rows <= 1 ? 0 : (rows <= 4 ? 1 : 2);
+    if (dev < 0 || !lds_raised[dev][T][kind]) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
         if (e != hipSuccess) return e;
-        if (dev >= 0) lds_raised[dev][T] = true;
+        if (dev >= 0) lds_raised[dev][T][kind] = true;
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kStreamWaves * 64), size_t(kStreamWaves) * kLongWaveLds, s, args);
+    hipLaunchKernelGGL(fn, grid, dim3(kStreamWaves * 64), size_t(kStreamWaves) * kLongWaveLds, s, args);
     return hipGetLastError();
+}
+
+// One product of any K and N: a set of workgroups for every block of 16 rows (blockIdx.y), as many in all as the CUs hold with 8 waves each.
+hipError_t launch_lean_any(const __half* x, const uint32_t* W, float gamma, const __half* scales, uint32_t group_inv, __half* y,
+                           int64_t M, int64_t N, int64_t K, hipStream_t s)
+{
+    const int slices = int((K + kSliceK - 1) / kSliceK), NW = slices < kStreamWaves ? slices : kStreamWaves;
+    const int tiles = int((N + 15) / 16), blocks = int((M + 15) / 16);
+    if (scales == nullptr && slices > kStreamWaves && slices <= kStreamWaves * kLongMaxPasses && int64_t(tiles) * blocks <= 2 * kLeanMaxGroups) {
+        // one or two tiles to a workgroup: the long-K form
+        const int T = tiles * blocks <= kLeanMaxGroups ? 1 : 2, groups = (tiles + T - 1) / T;
+        const LeanAny args{one_job(W, x, y, gamma, int(K), int(N), int(M), tiles, groups)};
+        return launch_longk_args(args, dim3(groups, blocks), T, int(M), s);
+    }
+    int64_t share = int64_t(kLeanMaxGroups) * (kStreamWaves / NW) / blocks;
+    const int64_t longest = slices > NW ? kStreamMaxRun : (int64_t(1) << 31) / int64_t(packed_tile_bytes(int(K)));   // a run's kept sums, its bytes
+    if (share < (tiles + longest - 1) / longest) share = (tiles + longest - 1) / longest;
+    const int groups = share < 1 ? 1 : (tiles < share ? tiles : int(share));
+    const int run = (tiles + groups - 1) / groups, T = tiles_per_item(run, NW);
+    const LeanAny args{one_job(W, x, y, gamma, int(K), int(N), int(M), tiles, groups, scales, group_inv)};
+    return launch_lean_args<true>(args, dim3(groups, blocks), NW, T, slices > NW ? run : 0, scales != nullptr, s);
 }
 
 // Calls in which every GEMM has 4096 < K <= 16384 and N a multiple of 16, and which hold at most two
@@ -1684,7 +1876,7 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
     if (groups > kLeanMaxGroups) return false;
     if (count == 1 && jobs[0].M <= 16) {
         const GemmDesc& d = jobs[0];
-        *err = launch_longk_args(one_job(d.W, d.x, d.y, d.gamma, int(d.K), int(d.N), int(d.M), int(d.N / 16), int(groups)), int(groups), T, s);
+        *err = launch_longk_args(one_job(d.W, d.x, d.y, d.gamma, int(d.K), int(d.N), int(d.M), int(d.N / 16), int(groups)), dim3(unsigned(groups)), T, 0, s);
         return true;
     }
     LeanBatch lb;
@@ -1708,7 +1900,7 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
             }
         }
     }
-    *err = launch_longk_args(lb, grid, T, s);
+    *err = launch_longk_args(lb, dim3(grid), T, 0, s);
     return true;
 }
 
@@ -1716,7 +1908,8 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
 // out to the jobs so that all finish together (see run_cost below); spare ones go to the job
 // with the costliest runs, one by one.  Returns hipErrorInvalidValue without launching if a multi-pass job's
 // runs would not fit the LDS (the caller then uses the general kernel).
-hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, int gs = 0)
+// any: jobs of any K and N among them, for the lean kernel's form for those alone.
+hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, int gs = 0, bool any = false)
 {
     const GemvPolicy pol = g_policy;
     const int NW = max_slices < kStreamWaves ? max_slices : kStreamWaves;
@@ -1729,7 +1922,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     }
     // One workgroup of 8 waves per CU; with shorter K (fewer waves per workgroup) as many more
     // workgroups, so that a CU still runs 8 waves (K = 1024: 1024 workgroups of 2 waves).
-    const int64_t g_max = int64_t(pol.stream_groups) * (kStreamWaves / NW);
+    const int64_t g_max = any ? kLeanMaxGroups : int64_t(pol.stream_groups) * (kStreamWaves / NW);
     const int G = total_tiles < g_max ? int(total_tiles) : int(g_max);
     // Time of a workgroup in tile units: passes x (run time + start-up), see tl_deal.hpp.  The
     // start-up of a pass is fetching the activation slice (1 KB per row and wave through the same
@@ -1759,8 +1952,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // against 8 KB requested per wave at a time; with more in flight the memory system slows
     // down), a run of 4 goes best as 2 + 2 (the second pair loads while the first is decoded),
     // and shorter runs are one item.
-    int T = run <= 3 ? run : (run == 4 ? 2 : 3);
-    if (T > NW) T = NW;                  // the epilogue gives every thread at most one output quad
+    int T = tiles_per_item(run, NW);
     if (pol.t_stream > 0 && T > pol.t_stream) T = pol.t_stream;
     if (gs == 4 && T > 2) T = 2;         // scale units of 128 weights: 12 accumulators per tile (registers)
     if (nb == 2) {                       // two row blocks per job: at most 2 tiles per item (registers)
@@ -1778,7 +1970,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     int64_t w_bytes = 0;                                   // packed words the launch streams
     bool all_ahead = true;                                 // see below
     for (int j = 0; j < b.count; ++j) {
-        lean = lean && b.job[j].slices >= NW && (b.job[j].N & 15) == 0;
+        lean = lean && (any || (b.job[j].slices >= NW && (b.job[j].N & 15) == 0));
         total_groups += wg[j];
         w_bytes += int64_t(b.job[j].tiles) * 4 * b.job[j].K;
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
@@ -1794,7 +1986,8 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // The table of records costs the host 0.7 us, which a launch with scales and one pass over K earns back from about 12 MB on (several blocks of rows of a
     // layer, lean over general: below 1 MB 1.09, 2 to 12 MB 1.00 to 1.02, 12 to 16 MB 0.96, beyond 0.93 to 0.95).
     if (gs != 0 && b.count > 1 && !multi_pass && w_bytes < (int64_t(12) << 20)) lean = false;
-    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs != 0, s);
+    if (any) return launch_lean(b, wg, NW, T, kept, gs != 0, true, s);
+    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs != 0, false, s);
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;
     for (int j = 0; j < b.count; ++j) {
@@ -1912,8 +2105,11 @@ hipError_t gemv_init()
         return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     };
     for (int T = 1; T <= 2; ++T) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_longk<LeanBatch>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
-        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(pick_longk<LeanOne>(T)), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds);
+        auto raise_long = [](const void* fn) { return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kStreamWaves * kLongWaveLds); };
+        hipError_t e = raise_long(reinterpret_cast<const void*>(pick_longk<LeanBatch>(T, 0)));
+        if (e == hipSuccess) e = raise_long(reinterpret_cast<const void*>(pick_longk<LeanOne>(T, 0)));
+        for (int rows : {1, 4, 16})
+            if (e == hipSuccess) e = raise_long(reinterpret_cast<const void*>(pick_longk<LeanAny>(T, rows)));
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= 3; ++T) {
@@ -1923,10 +2119,14 @@ hipError_t gemv_init()
             auto raise_one = [&](const void* fn, bool passes) {
                 if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(passes));
             };
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS>(T)), false);
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS>(T)), true);
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, false, GS>(T)), false);
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, true, GS>(T)), true);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS, false>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS, false>(T)), true);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, false, GS, false>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, true, GS, false>(T)), true);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS, true>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS, true>(T)), true);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanAny, false, GS, true>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanAny, true, GS, true>(T)), true);
         };
         raise_lean(std::false_type{});
         raise_lean(std::true_type{});
@@ -1952,8 +2152,98 @@ bool gemv_supports(int64_t M, int64_t N, int64_t K)
            N <= (int64_t(1) << 24) && M <= (int64_t(1) << 20);
 }
 
+// K that is no multiple of 64: several such jobs, or some among others, share launches of the lean kernel's form for any K.
+bool gemv_any_supports(int64_t M, int64_t N, int64_t K)
+{
+    return M >= 1 && M <= 4096 && N >= 1 && N <= (int64_t(1) << 24) && K >= 64 && K <= int64_t(kStreamWaves) * kStreamMaxPasses * kSliceK;
+}
+
+namespace {
+
+// Jobs (each passing gemv_any_supports, with a group in units of 256 weights or none) in blocks of 16 rows, kMaxJobs of them to a launch
+struct AnyJob {
+    const __half* x;
+    const uint32_t* W;
+    const __half* scales;
+    __half* y;
+    float gamma;
+    int64_t M, N, K, group;
+};
+
+hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s)
+{
+    auto units_per_group = [](const AnyJob& d) {           // a group longer than K is the one group there is
+        const int64_t all = (d.K + 255) / 256;
+        return d.scales == nullptr ? 0 : int(d.group / 256 < all ? d.group / 256 : all);
+    };
+    GemvBatch b;
+    b.count = 0;
+    int max_slices = 1;
+    auto one = [&](const GemvJob& j, int64_t M) {
+        return launch_lean_any(j.x, j.W, j.gamma, j.scales, group_inverse(j), j.y, M, j.N, j.K, s);
+    };
+    auto flush = [&]() -> hipError_t {
+        if (b.count == 0) return hipSuccess;
+        hipError_t e = b.count == 1 ? hipErrorInvalidValue : launch_stream(b, max_slices, 1, s, b.job[0].scales ? 2 : 0, true);
+        if (e == hipErrorInvalidValue) {                   // one job, or runs too long for what a launch keeps of their sums: one launch each
+            e = hipSuccess;
+            for (int q = 0; q < b.count && e == hipSuccess; ++q) e = one(b.job[q], b.job[q].Mrem);
+        }
+        b.count = 0;
+        max_slices = 1;
+        return e;
+    };
+    for (int i = 0; i < count; ++i) {
+        const AnyJob& d = jobs[i];
+        GemvJob j{};
+        j.x = d.x; j.W = d.W; j.y = d.y; j.gamma = d.gamma;
+        j.N = int(d.N); j.K = int(d.K);
+        j.tiles = int((d.N + 15) / 16);
+        j.slices = int((d.K + kSliceK - 1) / kSliceK);
+        j.scales = d.scales; j.hpg = units_per_group(d);
+        if (count == 1) return one(j, d.M);
+        for (int64_t m0 = 0; m0 < d.M; m0 += 16) {
+            GemvJob q = j;
+            q.x = d.x + m0 * d.K;
+            q.y = d.y + m0 * d.N;
+            q.Mrem = int(d.M - m0 < 16 ? d.M - m0 : 16);
+            b.job[b.count++] = q;
+            if (q.slices > max_slices) max_slices = q.slices;
+            if (b.count == kMaxJobs) {
+                const hipError_t e = flush();
+                if (e != hipSuccess) return e;
+            }
+        }
+    }
+    return flush();
+}
+
+}  // namespace
+
 hipError_t launch_gemv_jobs(const GemmDesc* jobs, int count, hipStream_t s)
 {
+    bool any_k = false;
+    for (int i = 0; i < count; ++i) any_k = any_k || jobs[i].K % 64 != 0;
+    if (any_k) {
+        // a job of such a K, and with it those that would share a launch of blocks of 16 rows anyway
+        constexpr int kAtOnce = 64;
+        AnyJob mixed[kAtOnce];
+        GemmDesc rest[kAtOnce];
+        for (int first = 0; first < count; first += kAtOnce) {
+            int m = 0, r = 0;
+            for (int i = first; i < count && i < first + kAtOnce; ++i) {
+                const GemmDesc& d = jobs[i];
+                if (d.K % 64 != 0 || (gemv_any_supports(d.M, d.N, d.K) && !gemv_two_blocks(d.M, d.N, d.K)))
+                    mixed[m++] = AnyJob{d.x, d.W, nullptr, d.y, d.gamma, d.M, d.N, d.K, 0};
+                else
+                    rest[r++] = d;
+            }
+            hipError_t e = m ? launch_any_jobs(mixed, m, s) : hipSuccess;
+            if (e == hipSuccess && r) e = launch_gemv_jobs(rest, r, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     if (g_policy.longk) {
         hipError_t e = hipSuccess;
         if (launch_longk(jobs, count, s, &e)) return e;

@@ -65,7 +65,10 @@ inline bool gemv_two_blocks(int64_t M, int64_t N, int64_t K)
            (M >= 256 && w_bytes >= (int64_t(2) << 20));
 }
 
-// Several independent GEMMs (each passing gemv_supports) in as few launches as possible.
+// Its forms for any K and N: launch_gemv and launch_gemv_jobs take these too (64 <= K <= 32768, M <= 4096).
+bool gemv_any_supports(int64_t M, int64_t N, int64_t K);
+
+// Several independent GEMMs (each passing gemv_supports or gemv_any_supports) in as few launches as possible.
 hipError_t launch_gemv_jobs(const GemmDesc* jobs, int count, hipStream_t s);
 
 // Per-group scales s[K / group][N] in place of gamma (stream form of the small-M kernel; M in
@@ -117,7 +120,8 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K);
 hipError_t launch_tile3(const __half* x, const uint8_t* Wp, int64_t stride, float gamma, __half* y,
                         int64_t M, int64_t N, int64_t K, bool fx, hipStream_t s);
 
-// Tiled matrix-core kernel for 2-bit words and a K that is no multiple of 64, and whether it beats the plain kernel.
+// Tiled matrix-core kernel for 2-bit words and a K that is no multiple of 64, and whether it beats the streaming and the plain kernel.
+KernelChoice tile_ragged_choice(int64_t M, int64_t N, int64_t K);
 bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K);
 hipError_t launch_tile_ragged(const __half* x, const uint32_t* Wp, float gamma, __half* y,
                               int64_t M, int64_t N, int64_t K, hipStream_t s);

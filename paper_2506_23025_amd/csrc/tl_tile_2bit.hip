@@ -47,10 +47,10 @@ typedef TileCfg<kTile2Bit, true, 1, 2, 1, 1, 8, 8, 2> R16x32;       // steps of 
 
 constexpr int kRagged = 4;
 constexpr TileCost kRaggedCost[kRagged] = {
-    {128, 128, 128, 256, 7.8, 7.8, 1.10, 1.10, 1.10, 0.6, 2.0},
-    {64, 128, 128, 256, 3.6, 3.6, 0.60, 0.60, 0.60, 0.6, 2.0},
-    {32, 64, 128, 512, 1.8, 1.8, 0.31, 0.31, 0.45, 0.6, 2.0},
-    {16, 32, 256, 512, 1.5, 1.5, 0.28, 0.28, 0.46, 0.6, 2.0},
+    {128, 128, 128, 256, 4.19, 5.56, 1.064, 1.297, 1.249, 0.82, 2.75},
+    {64, 128, 128, 256, 3.05, 3.47, 0.573, 0.685, 0.643, 0.87, 1.51},
+    {32, 64, 128, 512, 0.94, 2.01, 0.319, 0.356, 0.464, 0.43, 2.14},
+    {16, 32, 256, 512, 0.50, 1.55, 0.323, 0.363, 0.478, 0.50, 2.34},
 };
 
 int pick_ragged(int64_t M, int64_t N, int64_t K, double* us)
@@ -68,7 +68,7 @@ int pick_ragged(int64_t M, int64_t N, int64_t K, double* us)
 
 }  // namespace
 
-// K that is no multiple of 64: tiled kernel or the plain kernel on the vector ALUs, which takes (us) 2.8 + K / 4096
+// Where the streaming kernel cannot run (K below 64, more than 4096 rows): tiled kernel or the plain kernel on the vector ALUs, which takes (us) 2.8 + K / 4096
 // (5.6 + 1.6 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (4090 -> 4099: M = 1 9.6, M = 4 13.0, M = 16
 // 32.3, M = 37 52.8; 1000 -> 1024: M = 1 4.4, M = 16 8.9).  The tiled kernel on the same: 7.4, 7.4, 7.7, 10.8; 4.4, 4.5.
 bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K)
@@ -79,6 +79,39 @@ bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K)
     double us;
     pick_ragged(M, N, K, &us);
     return us < plain;
+}
+
+// What the weight-streaming kernel takes (us) for K that is no multiple of 64: m rows of a block, b blocks of 16, s slices of 512 weights; w workgroups
+// to a CU and xt tiles to a CU.
+static double stream_any_time(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t s = (K + 511) / 512, tiles = (N + 15) / 16, b = (M + 15) / 16;
+    const double m = double(M < 16 ? M : 16);
+    if (s > 8 && s <= 32 && tiles * b <= 512) return 2.77 + 0.019 * m + double(s) * (0.009 + 0.018 * m + 0.124 * (tiles * b <= 256 ? 1.0 : 2.0));
+    int64_t share = 256 * (8 / (s < 8 ? s : 8)) / b;
+    if (s > 8 && share < (tiles + 31) / 32) share = (tiles + 31) / 32;
+    if (share < 1) share = 1;
+    const int64_t groups = tiles < share ? tiles : share;
+    const double w = double((groups * b + 255) / 256), xt = double((tiles + groups - 1) / groups) * w;
+    constexpr double per_tile[9] = {0, 0.139, 0.207, 0.341, 0.368, 0.604, 0.67, 0.724, 0.752};
+    if (s <= 8) return 2.73 + 0.052 * m + 0.013 * m * double(s) * w + per_tile[s] * xt;
+    const double p = double((s + 7) / 8);
+    return 4.33 + w * p * (0.911 + 0.178 * m) + xt * (0.049 * double(s) + 0.344 * p);
+}
+
+// Tiled or weight-streaming kernel for K that is no multiple of 64.  Fitted, with the tiles' times, to 1300 calls of M = 17 .. 2048 and 600 of fewer rows, N = 512
+// .. 16384, K = 64 .. 14336, weights out of the caches; on as many others the one chosen is 0.8 % slower than the best (13 % in one of a
+// hundred) and 0.2 % (6 %).  Up to 4 rows the streaming kernel was the fastest in all.
+KernelChoice tile_ragged_choice(int64_t M, int64_t N, int64_t K)
+{
+    KernelChoice c{gemv_any_supports(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (!c.streams || M <= 4) return c;
+    c.stream = stream_any_time(M, N, K);
+    c.fixed = c.launch = 3.0;
+    c.launches = double((M + 15) / 16) / 32.0;
+    c.tiled = c.stream;
+    if (tile_at_least(kRaggedCost, kRagged, K) < c.stream) pick_ragged(M, N, K, &c.tiled);
+    return c;
 }
 
 hipError_t launch_tile_ragged(const __half* x, const uint32_t* Wp, float gamma, __half* y,
