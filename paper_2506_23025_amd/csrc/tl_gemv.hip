@@ -107,8 +107,6 @@ struct ItemCtx {
     int chunks;                   // 64-weight (16-byte) chunks per row
     int tiles, items, idx;        // tile t of the item is idx + t * items
     int slices;
-    const unsigned char* sc;      // per-group scales [K / group][N] fp16, and 256-weight halves per group
-    int hpg;
 };
 
 // The job table of a launch, one job per lane (lanes 0 .. kMaxJobs - 1), read from the kernel argument
@@ -164,8 +162,6 @@ __device__ __forceinline__ ItemCtx load_item(const JobTable& tb, int g)
     c.tiles = int(f[10]); c.items = int(f[11]); c.idx = g - item0;
     c.slices = int(f[12]);
     c.MR = int(f[13]);
-    c.sc = reinterpret_cast<const unsigned char*>(uintptr_t(f[16]) | (uintptr_t(f[17]) << 32));
-    c.hpg = int(f[18]);
     return c;
 }
 
@@ -461,11 +457,7 @@ constexpr int stream_wave_lds(int T)
 // NB: blocks of 16 activation rows a job may have (1 or 2).  With two, every decoded weight
 // operand feeds two MFMAs, one per block: the decode, which is what limits the kernel, is paid
 // once for 32 rows.  With PASSES the kept sums take 1 KB per tile and row block.
-// GS: per-group scales (Sec. 3.3, CPU inference: one fp16 scale per block along K; App. on the
-// GPU kernel: scales kept in a separate buffer) instead of one gamma: the GS (2 or 4) scale units
-// of a slice, 256 or 128 weights each, are accumulated apart, each multiplied by the scale of its
-// group and output row.  Groups are multiples of 128 weights; the scales lie as [K / group][N].
-template <int T, bool MULTI, bool PASSES, int NB, int GS = 0>
+template <int T, bool MULTI, bool PASSES, int NB>
 __global__ void __launch_bounds__(512)
 gemv_stream_kernel(GemvBatch b)
 {
@@ -475,11 +467,6 @@ gemv_stream_kernel(GemvBatch b)
     const int NW = blockDim.x >> 6;
     // LDS of a wave: activation rows (16 KB) while the operands are built; afterwards two tile
     // regions at 0 and 2 KB, and from 4 KB two sets of T NB partial-sum tiles (1 KB each).
-    // GS: 0, or the number of scale units in a wave's 512-weight slice: 2 (units of 256 weights, an
-    // MFMA's whole k range) or 4 (units of 128: an MFMA's lane groups 0,1 and 2,3 lie in different
-    // units, so every product is issued twice, each time with the other pair's weights masked off)
-    static_assert(GS == 0 || ((GS == 2 || GS == 4) && NB == 1 && MULTI), "per-group scales: one row block, job table");
-    constexpr int H = GS ? GS : 1;            // accumulator sets per tile: one per scale unit
     constexpr int kStride = stream_wave_lds(T * NB);
     unsigned char* const my_lds = lds_raw + wave * kStride;
 
@@ -529,10 +516,6 @@ gemv_stream_kernel(GemvBatch b)
     typedef const __attribute__((address_space(1))) u32x4* gptr;
 
     u32x4 wreg[T][2];
-    f16x4 sreg[T][H];                          // GS: the scales of the lane's four output rows, per unit
-    uint32_t sc_off[H] = {};                   // GS: byte offset of the units' groups in the scales
-    // GS == 4: all ones in the lanes whose k lies in the first (second) unit of an MFMA's range
-    const uint32_t pair_mask[2] = {(lane >> 5) == 0 ? 0xFFFFFFFFu : 0u, (lane >> 5) == 1 ? 0xFFFFFFFFu : 0u};
     auto chunk_offset = [&](int sl) {
         int chunk = sl * 8 + lc;                           // 16-byte chunk of this lane within the row
         if (chunk >= J.chunks) chunk = 0;                  // past K: multiplied by zero activations
@@ -541,7 +524,7 @@ gemv_stream_kernel(GemvBatch b)
     // Several passes, one row block of at most 4 rows: the next pass's activation rows are fetched
     // into registers while the last item of this pass is worked on (plain loads, so the compiler's
     // wait counts stay exact), and that item refills with the next pass's first weights.
-    constexpr bool kAheadOk = PASSES && NB == 1 && GS == 0;
+    constexpr bool kAheadOk = PASSES && NB == 1;
     u32x4 xpre[kAheadOk ? 4 : 1];
     auto issue_w = [&](int first, int t) {
         int tile = first + t;
@@ -553,21 +536,12 @@ gemv_stream_kernel(GemvBatch b)
         const uint32_t off1 = uint32_t(lr + 8 < last ? lr + 8 : last) * J.row_bytes + col_off;
         wreg[t][0] = __builtin_nontemporal_load((gptr)(tb + off0));
         wreg[t][1] = __builtin_nontemporal_load((gptr)(tb + off1));
-        if constexpr (GS) {
-            int n0 = tile * 16 + 4 * mg;                   // the lane's rows of the result: n0 .. n0 + 3
-            if (n0 > J.N - 4) n0 = J.N - 4;                // rows past N (N % 4 == 0): any scale will do
-#pragma unroll
-            for (int hh = 0; hh < H; ++hh)
-                sreg[t][hh] = *(const __attribute__((address_space(1))) f16x4*)(J.sc + sc_off[hh] + uint32_t(n0) * 2u);
-        }
     };
 
     uint32_t breg[NB][2][4][8];                // this wave's activations as MFMA B operands, per row block
-    f32x4 nsx[NB][H];                          // -2^-20 sum_k x[m][k] over the slice (GS: each half), as an accumulator
+    f32x4 nsx[NB];                             // -2^-20 sum_k x[m][k] over the slice, as an accumulator
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int hh = 0; hh < H; ++hh) nsx[nb][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nb = 0; nb < NB; ++nb) nsx[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     // Start of a pass: fetch this wave's activation slice and the first item's weights together,
     // then turn the activations into operand registers.
     // ahead_here: the end of the pass before has requested this pass's activation rows (into xpre)
@@ -577,20 +551,7 @@ gemv_stream_kernel(GemvBatch b)
     active = slice < J.slices;
     if (!ahead_here) col_off = chunk_offset(slice);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int hh = 0; hh < H; ++hh) nsx[nb][hh] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (GS) {
-        // groups of this wave's units (J.hpg units per group); a unit past K (its activations are
-        // zeros) takes the last group
-        const int last_group = (J.K - 1) / ((kSliceK / H) * J.hpg);
-#pragma unroll
-        for (int hh = 0; hh < H; ++hh) {
-            int g = (H * slice + hh) / J.hpg;
-            if (g > last_group) g = last_group;
-            sc_off[hh] = uint32_t(g) * uint32_t(J.N) * 2u;
-        }
-    }
+    for (int nb = 0; nb < NB; ++nb) nsx[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         // rows of this block: block 0 takes the first 16 (or fewer), block 1 what is left
@@ -639,7 +600,7 @@ gemv_stream_kernel(GemvBatch b)
 #pragma unroll
                 for (int t = 0; t < T; ++t) issue_w(tile0, t);
                 // the compiler does not track LDS-DMA: wait until only the 2T weight loads are outstanding
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm((2 + GS) * T));
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * T));
             } else {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
             }
@@ -674,15 +635,7 @@ gemv_stream_kernel(GemvBatch b)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const u32x4 bb = u32x4{breg[nb][h][0][e], breg[nb][h][1][e], breg[nb][h][2][e], breg[nb][h][3][e]};
-                    if constexpr (GS == 4) {
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const u32x4 aq = a & pair_mask[q];
-                            nsx[nb][2 * h + q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(aq), as_f16x8(bb), nsx[nb][2 * h + q], 0, 0, 0);
-                        }
-                    } else {
-                        nsx[nb][GS ? h : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), nsx[nb][GS ? h : 0], 0, 0, 0);
-                    }
+                    nsx[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), nsx[nb], 0, 0, 0);
                 }
             if (NB > 1 && nb == 0) __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));   // staging read before it is refilled
         } else {
@@ -714,20 +667,15 @@ gemv_stream_kernel(GemvBatch b)
                 unsigned char* const reg_t = my_lds + (t & 1) * 2048;
                 *reinterpret_cast<u32x4*>(reg_t + ww_off) = wreg[t][0];
                 *reinterpret_cast<u32x4*>(reg_t + 1024 + ww_off) = wreg[t][1];
-                f16x4 sc_cur[H];                           // this tile's scales, before the refill replaces them
-#pragma unroll
-                for (int hh = 0; hh < H; ++hh) sc_cur[hh] = sreg[t][hh];
                 if constexpr (REFILL) issue_w(refill_first, t);
                 if (REFILL || first + t < tile_end) {      // the last item may be short
-                    f32x4 acc[NB][H][3];
+                    f32x4 acc[NB][3];
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                        for (int hh = 0; hh < H; ++hh) {
-                            acc[nb][hh][0] = nsx[nb][hh];
-                            acc[nb][hh][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-                            acc[nb][hh][2] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        }
+                    for (int nb = 0; nb < NB; ++nb) {
+                        acc[nb][0] = nsx[nb];
+                        acc[nb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        acc[nb][2] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const u32x4 wv = *reinterpret_cast<const u32x4*>(reg_t + (h ? wr_off1 : wr_off0));
@@ -744,33 +692,13 @@ gemv_stream_kernel(GemvBatch b)
 #pragma unroll
                             for (int nb = 0; nb < NB; ++nb) {
                                 const u32x4 bb = u32x4{breg[nb][h][0][e], breg[nb][h][1][e], breg[nb][h][2][e], breg[nb][h][3][e]};
-                                if constexpr (GS == 4) {
-#pragma unroll
-                                    for (int q = 0; q < 2; ++q) {
-                                        const u32x4 aq = sh[src] & (mask & pair_mask[q]);
-                                        acc[nb][2 * h + q][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(aq), as_f16x8(bb), acc[nb][2 * h + q][j], 0, 0, 0);
-                                    }
-                                } else {
-                                    acc[nb][GS ? h : 0][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), acc[nb][GS ? h : 0][j], 0, 0, 0);
-                                }
+                                acc[nb][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), acc[nb][j], 0, 0, 0);
                             }
                         }
                     }
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        if constexpr (GS) {
-                            // register r of the accumulator is output row 4 (lane / 16) + r of the tile
-                            f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                            for (int hh = 0; hh < H; ++hh) {
-                                const f32x4 sc = f32x4{float(sc_cur[hh][0]), float(sc_cur[hh][1]), float(sc_cur[hh][2]), float(sc_cur[hh][3])};
-                                sum += sc * (acc[nb][hh][0] * 1048576.f + acc[nb][hh][1] * 262144.f + acc[nb][hh][2] * 65536.f);
-                            }
-                            part[nb][t] = sum;
-                        } else {
-                            part[nb][t] = acc[nb][0][0] * 1048576.f + acc[nb][0][1] * 262144.f + acc[nb][0][2] * 65536.f;
-                        }
-                    }
+                    for (int nb = 0; nb < NB; ++nb)
+                        part[nb][t] = acc[nb][0] * 1048576.f + acc[nb][1] * 262144.f + acc[nb][2] * 65536.f;
                 }
             }
         }
@@ -805,7 +733,7 @@ gemv_stream_kernel(GemvBatch b)
             if (last_pass && tile < tile_end && row < J.Mrem) {
                 typedef __attribute__((address_space(1))) __half* gh_ptr;
                 gh_ptr dst = (gh_ptr)(J.y + size_t(row) * J.N + n);
-                const float gamma = GS ? 1.f : J.gamma;
+                const float gamma = J.gamma;
                 if (n + 3 < J.N && (J.N & 3) == 0) {       // four consecutive n: one 8-byte store
                     const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
                     const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
@@ -874,6 +802,9 @@ gemv_stream_kernel(GemvBatch b)
 // take if the loop is to keep up with HBM), so every instruction that is not decode counts.
 constexpr int kLeanMaxGroups = 256;
 
+// Group scales in the lean kernel, by what the groups are multiples of: 256, 128, 64 or 32 weights.  Weights per scale that is fetched:
+__host__ __device__ constexpr int lean_scale_unit(int gs) { return gs == 256 ? 256 : gs == 32 ? 32 : 64; }
+
 // bytes of 16 packed rows
 __host__ __device__ constexpr size_t packed_tile_bytes(int K) { return size_t((unsigned(K) + 15u) >> 4) * 64u; }
 
@@ -924,7 +855,7 @@ struct LeanOne {
     }
 };
 
-// The same for any K and N, and any number of rows (`Mrem` of them): blockIdx.y is the block of 16.
+// The same for any number of rows (`Mrem` of them), blockIdx.y being the block of 16, and for any K and N.
 struct LeanAny : LeanOne {
     __device__ WgRec mine() const
     {
@@ -1037,7 +968,8 @@ __device__ __forceinline__ void store_quad_any(__attribute__((address_space(1)))
 // request leaves the row, and what overlaps the chunk before meets zeros.  The activations come through registers.  Calls with K no multiple of 64
 // ran in the tiled kernel's form for those: up to 4 rows of 512 .. 16384 x 64 .. 14336 weights this one is 1.8 times as fast on average
 // (666 calls, none slower), 4099 x 4090 at M = 1 / 16 / 37 8.0 / 8.3 / 10.7 -> 4.3 / 5.7 / 6.8 us.
-template <int T, bool PASSES, bool GS, bool ANY, class Args>
+// GS below 256: see fine_tile.
+template <int T, bool PASSES, int GS, bool ANY, class Args>
 __global__ void __launch_bounds__(512)
 gemv_lean_kernel(Args b)
 {
@@ -1046,6 +978,11 @@ gemv_lean_kernel(Args b)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int NW = blockDim.x >> 6;
     constexpr int kStride = stream_wave_lds(T);
+    constexpr bool FINE = GS != 0 && GS < 256;
+    // LDS of a wave after the operands are built: two tile regions, from `kSums` on two sets of T partial-sum tiles.  FINE: rows of a tile
+    // 144 bytes apart, the tile's scales behind them.
+    constexpr int kScales = 16 * 144, kRegion = FINE ? kScales + 512 : 2048, kSums = 2 * kRegion;
+    static_assert(kSums + 2 * T * 1024 <= kStride, "LDS of a wave");
     unsigned char* const my_lds = lds_raw + wave * kStride;
     typedef const __attribute__((address_space(1))) unsigned char* gbytes;
 
@@ -1062,10 +999,12 @@ gemv_lean_kernel(Args b)
     const int n_pass = PASSES ? (slices + NW - 1) / NW : 1;
     // ---- activations of a slice: LDS-DMA, swizzled (lane l fetches piece l ^ (r & 7) of row r)
     auto stage_x = [&](int slice) {
+        int l = lane;
+        if constexpr (PASSES) asm volatile("" : "+v"(l));  // see exchange
+        const uint32_t lane16 = uint32_t(l) << 4;
         const size_t row_stride = size_t(K) * 2;
         gbytes src = (gbytes)(R.x + size_t(slice) * (kSliceK * 2));
         if ((slice + 1) * kSliceK <= K) {                   // the whole slice lies inside K
-            const uint32_t lane16 = uint32_t(lane) << 4;
 #pragma unroll 1
             for (int r = 0; r < rows; ++r) {
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (lane16 ^ (uint32_t(r & 7) << 4))),
@@ -1075,12 +1014,12 @@ gemv_lean_kernel(Args b)
         } else {
 #pragma unroll 1
             for (int r = 0; r < rows; ++r) {
-                const int kk = (lane ^ (r & 7)) << 3;      // first of this lane's 8 activations within the slice
+                const int kk = (l ^ (r & 7)) << 3;         // first of this lane's 8 activations within the slice
                 if (slice * kSliceK + kk < K) {
                     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + uint32_t(kk) * 2u),
                                                      (__attribute__((address_space(3))) void*)(my_lds + r * 1024), 16, 0, 0);
                 } else {
-                    *reinterpret_cast<u32x4*>(my_lds + r * 1024 + (uint32_t(lane) << 4)) = u32x4{0u, 0u, 0u, 0u};
+                    *reinterpret_cast<u32x4*>(my_lds + r * 1024 + lane16) = u32x4{0u, 0u, 0u, 0u};
                 }
                 src += row_stride;
             }
@@ -1101,21 +1040,30 @@ gemv_lean_kernel(Args b)
         else if (rows <= 8) with(std::integral_constant<int, 8>{});
         else with(std::integral_constant<int, 16>{});
     };
-    bool idle = ANY && wave >= slices;                     // this wave has no slice in this pass
+    const bool idle = ANY && wave >= slices;               // this wave has no slice at all
     if constexpr (!ANY) stage_x(wave);
-    constexpr int H = GS ? 2 : 1;
+    constexpr int H = GS == 256 ? 2 : 1;
     // GS: the job's scales from the run's first row as a raw buffer, the lane's rows in it, and the units' groups
-    const uint32_t last_unit = uint32_t(K - 1) >> 8;
+    constexpr int kUnit = lean_scale_unit(GS);             // weights per scale that is fetched
+    const uint32_t last_unit = uint32_t(K - 1) / uint32_t(kUnit);
     auto group_of = [&](uint32_t u) {                      // a product: two divisions would stand before the first request
         return uint32_t((uint64_t(2u * (u < last_unit ? u : last_unit)) * R.group_inv) >> 32);   // past K: the last one (its activations are zeros)
     };
+    // FINE: one request fetches the scales of a tile and slice: lane l those of unit l / 8 and two rows (kUnit 32: l / 4 and four rows)
+    constexpr int kUnitLanes = kUnit == 32 ? 4 : 8;
+    typedef typename std::conditional<kUnit == 32, u32x2, uint32_t>::type fine_t;
     const __amdgpu_buffer_rsrc_t sres = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<unsigned char*>(R.sc) + size_t(R.tile0) * 32u, 0,
         GS ? (group_of(last_unit) + 1u) * uint32_t(N) * 2u - uint32_t(R.tile0) * 32u : 0u, 0x00020000);
     const uint32_t sc_lane = uint32_t(mg) * 8u;
     uint32_t sc_unit[H] = {};
+    uint32_t sc_fine = 0;
     auto scales_of = [&](int slice) {
-        if constexpr (GS) {
+        if constexpr (FINE) {
+            // past K: outside the buffer, which reads as zero
+            const uint32_t unit = uint32_t(slice) * (kSliceK / kUnit) + uint32_t(lane / kUnitLanes);
+            sc_fine = unit <= last_unit ? group_of(unit) * uint32_t(N) * 2u + uint32_t(lane % kUnitLanes) * uint32_t(sizeof(fine_t)) : 0x80000000u;
+        } else if constexpr (GS != 0) {
 #pragma unroll
             for (int h = 0; h < H; ++h) sc_unit[h] = group_of(uint32_t(2 * slice + h)) * uint32_t(N) * 2u;
         }
@@ -1137,6 +1085,7 @@ gemv_lean_kernel(Args b)
         const_cast<unsigned char*>(Wrun), 0, ANY ? uint32_t(run_rows) * row_bytes : uint32_t(ntiles) * tile_bytes, 0x00020000);
     u32x4 wreg[T][2];
     u32x2 sreg[T][H];
+    fine_t freg[T];
     auto issue_w = [&](int idx, int t) {                   // idx: tile of the run; past the run: its last tile again
         const int c = idx < ntiles ? idx : ntiles - 1;
         // Buffer loads: descriptor and tile offset are scalar, the lane offset is a register that
@@ -1146,7 +1095,11 @@ gemv_lean_kernel(Args b)
         const uint32_t so = uint32_t(c) * tile_bytes;
         wreg[t][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, voff0, so, 2));   // 2: nt
         wreg[t][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, voff1, so, 2));
-        if constexpr (GS) {
+        if constexpr (FINE && kUnit == 32) {
+            freg[t] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(sres, sc_fine, uint32_t(c) * 32u, 0));
+        } else if constexpr (FINE) {
+            freg[t] = __builtin_amdgcn_raw_buffer_load_b32(sres, sc_fine, uint32_t(c) * 32u, 0);
+        } else if constexpr (GS != 0) {
 #pragma unroll
             for (int h = 0; h < H; ++h)
                 sreg[t][h] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(sres, sc_lane, __builtin_amdgcn_readfirstlane(sc_unit[h] + uint32_t(c) * 32u), 0));
@@ -1165,23 +1118,57 @@ gemv_lean_kernel(Args b)
     } else {
         first_tiles();
         // the compiler does not track LDS-DMA: wait until only the weight (and scale) loads are outstanding
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((GS ? 4 : 2) * T));
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((FINE ? 3 : GS ? 4 : 2) * T));
     }
 
     // ---- activations -> MFMA B operands (see gemv_stream_kernel) and the -sum(x) seed ----------
-    uint32_t breg[2][4][8];
-    f32x4 nsx[H];
-    auto build = [&](bool active) {
+    u32x4 breg[16];
+    constexpr int kSeeds = GS == 64 ? 8 : GS == 128 ? 4 : H;
+    f32x4 nsx[kSeeds];
+    auto build = [&] {
+        int l = lane;
+        if constexpr (PASSES) asm volatile("" : "+v"(l));  // see exchange
+        const int mi = l & 15, mg = l >> 4;
 #pragma unroll
-        for (int h = 0; h < H; ++h) nsx[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int h = 0; h < kSeeds; ++h) nsx[h] = f32x4{0.f, 0.f, 0.f, 0.f};
         int mr = 1;
         while (mr < rows) mr *= 2;
         const int xrow = mi & (mr - 1);
-        const uint32_t xr_off = uint32_t(xrow) * 1024u + uint32_t(mg) * 128u;
+        const uint32_t xr_off = uint32_t(xrow) * 1024u + (FINE ? 0u : uint32_t(mg) * 128u);
         const uint32_t sw = uint32_t(xrow & 7);
-        const bool live = mi < rows && (ANY || !(PASSES && GS) || active);
+        const bool live = mi < rows;
         const uint32_t sel_lo = live ? 0x05040100u : 0x0c0c0c0cu;
         const uint32_t sel_hi = live ? 0x07060302u : 0x0c0c0c0cu;
+        const uint32_t c = 0x80108010u;                   // fp16 pair of -2^-20
+        const u32x4 a = u32x4{c, c, c, c};
+        if constexpr (GS == 32) {
+            // breg[v]: unit v's eight activations of this lane, in order
+            const uint32_t keep = live ? ~0u : 0u;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const u32x4 q = *reinterpret_cast<const u32x4*>(my_lds + xr_off + (v >> 1) * 128 + ((uint32_t(4 * (v & 1) + mg) ^ sw) << 4));
+#pragma unroll
+                for (int r = 0; r < 4; ++r) breg[v][r] = q[r] & keep;
+            }
+            return;
+        } else if constexpr (FINE) {
+            // breg[2 c], [2 c + 1]: of chunk c the lane's 16 activations x[16 g + j], as pairs (j, j + 8) of even and of odd j
+            const uint32_t at = (uint32_t(2 * mg) ^ sw) << 4;
+#pragma unroll
+            for (int ch = 0; ch < 8; ++ch) {
+                const u32x4 lo = *reinterpret_cast<const u32x4*>(my_lds + xr_off + ch * 128 + at);
+                const u32x4 hi = *reinterpret_cast<const u32x4*>(my_lds + xr_off + ch * 128 + (at ^ 16u));
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    breg[2 * ch][r] = __builtin_amdgcn_perm(hi[r], lo[r], sel_lo);
+                    breg[2 * ch + 1][r] = __builtin_amdgcn_perm(hi[r], lo[r], sel_hi);
+                }
+                const int u = ch * kSeeds / 8;
+                nsx[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(breg[2 * ch]), nsx[u], 0, 0, 0);
+                nsx[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(breg[2 * ch + 1]), nsx[u], 0, 0, 0);
+            }
+            return;
+        } else {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1190,58 +1177,129 @@ gemv_lean_kernel(Args b)
                 const u32x4 hi = *reinterpret_cast<const u32x4*>(my_lds + xr_off + h * 512 + ((uint32_t(2 * wd + 1) ^ sw) << 4));
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    breg[h][wd][2 * r] = __builtin_amdgcn_perm(hi[r], lo[r], sel_lo);
-                    breg[h][wd][2 * r + 1] = __builtin_amdgcn_perm(hi[r], lo[r], sel_hi);
+                    breg[h * 8 + 2 * r][wd] = __builtin_amdgcn_perm(hi[r], lo[r], sel_lo);
+                    breg[h * 8 + 2 * r + 1][wd] = __builtin_amdgcn_perm(hi[r], lo[r], sel_hi);
                 }
             }
-        const uint32_t c = 0x80108010u;                   // fp16 pair of -2^-20
-        const u32x4 a = u32x4{c, c, c, c};
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const u32x4 bb = u32x4{breg[h][0][e], breg[h][1][e], breg[h][2][e], breg[h][3][e]};
-                nsx[GS ? h : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), nsx[GS ? h : 0], 0, 0, 0);
-            }
+            for (int e = 0; e < 8; ++e)
+                nsx[GS ? h : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(breg[h * 8 + e]), nsx[GS ? h : 0], 0, 0, 0);
+        }
     };
-    if (!ANY || !idle) build(true);
+    if (!ANY || !idle) build();
 
-    const uint32_t ww_off = uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
+    const uint32_t ww_off = FINE ? uint32_t(lr) * 144u + (uint32_t(lc) << 4) : uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
+    constexpr uint32_t kUpperRows = FINE ? 8 * 144 : 1024;
+    // FINE: the lane's word of the first chunk (kUnit 32: of its first half), its scales' places: [4 rows][unit], 8 bytes each
+    const uint32_t wr_fine = uint32_t(mi) * 144u + uint32_t(kUnit == 32 ? mg >> 1 : mg) * 4u;
+    constexpr uint32_t kQuad = 8 * kSliceK / kUnit;
+    const uint32_t sw_off = kScales + (kUnit == 32 ? uint32_t(lane & 3) * kQuad + uint32_t(lane >> 2) * 8u
+                                                  : uint32_t((lane & 7) >> 1) * kQuad + uint32_t(lane >> 3) * 8u + uint32_t(lane & 1) * 4u);
+    const uint32_t sr_off = kScales + uint32_t(mg) * kQuad;
+    const uint32_t half_sel = mg & 1 ? 0x07060302u : 0x05040100u;
     const uint32_t wr_off0 = uint32_t(mi) * 128u + (uint32_t((mg) ^ (mi & 7)) << 4);
     const uint32_t wr_off1 = uint32_t(mi) * 128u + (uint32_t((4 + mg) ^ (mi & 7)) << 4);
-    const float gamma = GS ? 65536.f : R.gamma * 65536.f;               // times the 2^16 left in the partial sums
+    // times the 2^16 (2^18, 2^20) left in the partial sums
+    const float gamma = GS == 32 ? 1048576.f : FINE ? 262144.f : GS ? 65536.f : R.gamma * 65536.f;
     typedef __attribute__((address_space(1))) __half* gh_ptr;
-    // the output quad this thread owns in an item's epilogue: tile t = threadIdx.x / 64 of the item
-    const int ot = int(threadIdx.x) >> 6;
-    const uint32_t ycol = uint32_t(R.tile0) * 16u + 4u * uint32_t(mg);       // + 16 (first + ot)
-    gh_ptr const yrow = (gh_ptr)(R.y + size_t(mi) * size_t(N));
+
+    // FINE: the tile in LDS region `reg`.  A unit's sum is complete in its accumulators and then scaled.
+    auto fine_tile = [&](const unsigned char* reg) {
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (FINE) {
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            auto scaled = [&](int u, f32x4 v) {            // u: unit of kUnit weights
+                const f16x4 s = reinterpret_cast<const f16x4*>(reg + sr_off)[u];
+                const f32x4 f = {float(s[0]), float(s[1]), float(s[2]), float(s[3])};
+                sum = __builtin_elementwise_fma(f, v, sum);
+            };
+            if constexpr (kUnit == 32) {
+                // Lane (i, g) of unit v takes the eight codes 8 g ..: the half word is spread so that code 2q stands at bit 4q of the lower half and 2q + 1
+                // at bit 4q of the upper one; each pair is brought to bit 4 and loses its offset there, (c - 1) 2^-20, exact.
+                const f16x2 one = __builtin_bit_cast(f16x2, 0x00100010u);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const uint32_t w = *reinterpret_cast<const uint32_t*>(reg + wr_fine + (v >> 1) * 16 + (v & 1) * 8);
+                    const uint32_t p = __builtin_amdgcn_perm(w >> 2, w, half_sel);
+                    u32x4 a = {(p << 4) & 0x00300030u, p & 0x00300030u, (p >> 4) & 0x00300030u, (p >> 8) & 0x00300030u};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) a[r] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, uint32_t(a[r])) - one);
+                    scaled(v, __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(breg[v]), zero, 0, 0, 0));
+                }
+            } else {
+                // Lane (i, g) takes word g of a chunk, codes j and j + 8 as a pair: even j at bit 4, odd ones at bit 6, an accumulator for each
+                f32x4 even, odd;
+#pragma unroll
+                for (int ch = 0; ch < 8; ++ch) {
+                    const uint32_t w = *reinterpret_cast<const uint32_t*>(reg + wr_fine + ch * 16);
+                    const u32x4 sh = {w << 4, w, w >> 4, w >> 8};
+                    const bool first = GS == 64 || (ch & 1) == 0;
+                    even = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(sh & 0x00300030u), as_f16x8(breg[2 * ch]), first ? nsx[ch * kSeeds / 8] : even, 0, 0, 0);
+                    odd = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(sh & 0x00C000C0u), as_f16x8(breg[2 * ch + 1]), first ? zero : odd, 0, 0, 0);
+                    if (GS == 64 || (ch & 1)) scaled(GS == 64 ? ch : ch - 1, __builtin_elementwise_fma(even, f32x4{4.f, 4.f, 4.f, 4.f}, odd));
+                }
+            }
+        }
+        return sum;
+    };
+
+    // split-K: each wave's partial sums of nt tiles are in its set `parity`; one LDS-only barrier, fixed-order sum
+    unsigned char* const ysum = lds_raw + NW * kStride;
+    auto exchange = [&](int nt, int first, int parity, bool first_pass, bool last_pass) {
+        __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
+        __builtin_amdgcn_s_barrier();
+        if (wave < nt) {                                   // a thread owns an output quad of tile `wave` of the item
+            // PASSES: its places are worked out here.  Kept over the loop they took registers that others were spilled for, and a
+            // reload waits for every weight on its way.
+            int l = lane;
+            if constexpr (PASSES) asm volatile("" : "+v"(l));
+            f32x4 v[8];
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                v[w] = (w < NW) ? reinterpret_cast<const f32x4*>(lds_raw + w * kStride + kSums + parity * (T * 1024) + wave * 1024)[l]
+                                : f32x4{0.f, 0.f, 0.f, 0.f};
+            f32x4 s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+            if constexpr (PASSES) {
+                f32x4* const keep = reinterpret_cast<f32x4*>(ysum + (first + wave) * 1024) + l;
+                if (!first_pass) s += *keep;
+                if (!last_pass) *keep = s;
+            }
+            const int row = l & 15;
+            if (row < rows && (!PASSES || last_pass)) {
+                gh_ptr const yrow = (gh_ptr)(R.y + size_t(row) * size_t(N));
+                const uint32_t col = uint32_t(R.tile0 + first + wave) * 16u + 4u * uint32_t(l >> 4);
+                if constexpr (ANY) {
+                    store_quad_any(yrow, int(col), N, s, gamma);
+                } else {
+                    const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
+                    const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
+                    *(__attribute__((address_space(1))) u32x2*)(yrow + col) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+                }
+            }
+        }
+    };
 
     // One item of NT tiles starting at tile `first` of the run.  REFILL: each tile's registers are
     // loaded again at once with the tile T further on.
     // REFILL 2 (PASSES): with the first tiles of the next pass, to whose slice the offsets have been moved.
-    unsigned char* const ysum = lds_raw + NW * kStride;
-    constexpr bool kSkips = ANY || (PASSES && !GS);        // waves without a slice compute nothing
-    bool next_live = true;                                 // this wave has a slice in the next pass
     auto item = [&](auto nt_tag, auto refill_tag, int first, int parity, bool first_pass, bool last_pass) {
         constexpr int NT = decltype(nt_tag)::value;
         constexpr int REFILL = decltype(refill_tag)::value;
         f32x4 part[NT];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) part[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // A wave without a slice in the last pass only takes part in the exchange.  (GS: it multiplies zeros as well.  Left out there,
-        // the block at M = 4 takes 16.65 instead of 16.42 us, the branch's registers being spilled.)
-        if (!kSkips || !idle) {
-#pragma unroll
         for (int t = 0; t < NT; ++t) {
-            unsigned char* const reg_t = my_lds + (t & 1) * 2048;
+            unsigned char* const reg_t = my_lds + (t & 1) * kRegion;
             // Writing a tile to LDS and asking for the tile that takes its registers is a handful
             // of LDS, scalar and memory instructions; they run at raised priority so that they do
             // not queue behind the other wave's decode (measured: decode sweep 17.55 -> 17.2 us).
             if constexpr (REFILL != 0) __builtin_amdgcn_s_setprio(3);
             *reinterpret_cast<u32x4*>(reg_t + ww_off) = wreg[t][0];
-            *reinterpret_cast<u32x4*>(reg_t + 1024 + ww_off) = wreg[t][1];
+            *reinterpret_cast<u32x4*>(reg_t + kUpperRows + ww_off) = wreg[t][1];
+            if constexpr (FINE) *reinterpret_cast<fine_t*>(reg_t + sw_off) = freg[t];
             u32x2 sc_cur[H];
-            if constexpr (GS) {
+            if constexpr (GS == 256) {
 #pragma unroll
                 for (int h = 0; h < H; ++h) {
                     // This tile's scales are taken over here, before the refill replaces them: left to itself the compiler
@@ -1252,12 +1310,15 @@ gemv_lean_kernel(Args b)
                 }
             }
             if constexpr (REFILL != 0) {
-                if (REFILL == 1 || !kSkips || next_live) issue_w(REFILL == 2 ? t : first + T + t, t);
+                issue_w(REFILL == 2 ? t : first + T + t, t);
                 __builtin_amdgcn_s_setprio(0);
                 // the requests leave here, as soon as the registers are free: left to itself the
                 // scheduler sinks all of an item's loads to its end, which costs two tiles of lead
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (FINE) {
+                part[t] = fine_tile(reg_t);
+            } else {
             f32x4 acc[3];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -1271,12 +1332,11 @@ gemv_lean_kernel(Args b)
                     const int j = e < 2 ? e : (e < 5 ? e - 2 : e - 5);
                     const uint32_t mask = 0x00300030u << (2 * j);
                     const u32x4 a = sh[src] & mask;
-                    const u32x4 bb = u32x4{breg[h][0][e], breg[h][1][e], breg[h][2][e], breg[h][3][e]};
                     // first product of an accumulator: class 0 starts from the -sum(x) seed, the others from zero
                     const f32x4 c0 = ((GS || h == 0) && (e == 0 || e == 1 || e == 4)) ? (j == 0 ? nsx[GS ? h : 0] : f32x4{0.f, 0.f, 0.f, 0.f}) : acc[j];
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(bb), c0, 0, 0, 0);
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(breg[h * 8 + e]), c0, 0, 0, 0);
                 }
-                if constexpr (GS) {
+                if constexpr (GS != 0) {
                     // register r of the accumulator is output row 4 (lane / 16) + r of the tile
                     const f16x4 sh4 = __builtin_bit_cast(f16x4, sc_cur[h]);
                     const f32x4 sc = {float(sh4[0]), float(sh4[1]), float(sh4[2]), float(sh4[3])};
@@ -1287,49 +1347,19 @@ gemv_lean_kernel(Args b)
             }
             // the three classes carry 2^-20, 2^-18 and 2^-16: two fused multiply-adds leave the sum at
             // 2^-16, and that power of two goes into the scale of the epilogue (exact, same roundings)
-            if constexpr (!GS)
+            if constexpr (GS == 0)
                 part[t] = __builtin_elementwise_fma(__builtin_elementwise_fma(acc[0], f32x4{4.f, 4.f, 4.f, 4.f}, acc[1]),
                                                     f32x4{4.f, 4.f, 4.f, 4.f}, acc[2]);
-        }
+            }
         }
         if constexpr (REFILL == 2) {
-            if (!kSkips || next_live) {
 #pragma unroll
-                for (int t = NT; t < T; ++t) issue_w(t, t);
-            }
+            for (int t = NT; t < T; ++t) issue_w(t, t);
         }
-        // split-K: partial sums into this wave's set `parity`, one LDS-only barrier, fixed-order sum
-        unsigned char* const red = my_lds + 4096 + parity * (T * 1024);
 #pragma unroll
-        for (int t = 0; t < NT; ++t)                       // GS: an idle wave's zeros may have met an infinite scale
-            reinterpret_cast<f32x4*>(red + t * 1024)[lane] = (GS && PASSES && !ANY && idle) ? f32x4{0.f, 0.f, 0.f, 0.f} : part[t];
-        __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
-        __builtin_amdgcn_s_barrier();
-        if (ot < NT) {
-            f32x4 v[8];
-#pragma unroll
-            for (int w = 0; w < 8; ++w)
-                v[w] = (w < NW) ? reinterpret_cast<const f32x4*>(lds_raw + w * kStride + 4096 + parity * (T * 1024) + ot * 1024)[lane]
-                                : f32x4{0.f, 0.f, 0.f, 0.f};
-            f32x4 s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-            if constexpr (PASSES) {
-                f32x4* const keep = reinterpret_cast<f32x4*>(ysum + (first + ot) * 1024) + lane;
-                if (!first_pass) s += *keep;
-                if (!last_pass) *keep = s;
-            }
-            if (mi < rows && (!PASSES || last_pass)) {
-                const uint32_t col = ycol + 16u * uint32_t(first + ot);
-                if constexpr (ANY) {
-                    store_quad_any(yrow, int(col), N, s, gamma);
-                } else {
-                    const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
-                    const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
-                    *(__attribute__((address_space(1))) u32x2*)(yrow + col) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-                }
-            }
-        }
+        for (int t = 0; t < NT; ++t) reinterpret_cast<f32x4*>(my_lds + kSums + parity * (T * 1024) + t * 1024)[lane] = part[t];
+        exchange(NT, first, parity, first_pass, last_pass);
     };
-
     const int n_items = (ntiles + T - 1) / T;
     typedef std::integral_constant<int, 0> None;
     typedef std::integral_constant<int, 1> Refill;
@@ -1343,6 +1373,18 @@ gemv_lean_kernel(Args b)
         else if (T == 2 || rem == 2) item(N2{}, refill, i * T, i & 1, first_pass, last_pass);
         else item(NT{}, refill, i * T, i & 1, first_pass, last_pass);
     };
+    // The items of a wave without a slice, which it can only be in the last pass: it takes part in the exchange alone.
+    auto idle_items = [&](bool first_pass) {
+        for (int i = 0; i < n_items; ++i) {
+            const int left = ntiles - i * T;
+#pragma unroll
+            for (int t = 0; t < T; ++t) reinterpret_cast<f32x4*>(my_lds + kSums + (i & 1) * (T * 1024) + t * 1024)[lane] = f32x4{0.f, 0.f, 0.f, 0.f};
+            exchange(left < T ? left : T, i * T, i & 1, first_pass, true);
+        }
+    };
+    if constexpr (ANY) {
+        if (idle) { idle_items(true); return; }
+    }
     if constexpr (!PASSES) {
         int i = 0;
         for (; i + 1 < n_items; ++i) item(NT{}, Refill{}, i * T, i & 1, true, true);
@@ -1356,27 +1398,22 @@ gemv_lean_kernel(Args b)
                 last_item(None{}, i, first_pass, true);
             } else {
                 const int slice = (pass + 1) * NW + wave;
-                voff0 = offset_of(slice);
+                // no slice: outside the buffers, which read as zero without a request to memory
+                voff0 = slice < slices ? offset_of(slice) : 0x80000000u;
                 voff1 = voff0 + 8u * row_bytes;
                 scales_of(slice);
-                next_live = slice < slices;
                 last_item(NextPass{}, i, first_pass, false);
                 // the activations land where other waves may still be reading this item's sums
                 __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
                 __builtin_amdgcn_s_barrier();
-                idle = !next_live;
+                if (slice >= slices) { idle_items(false); return; }
                 if constexpr (ANY) {
-                    if (!idle) {
-                        stage_any(slice, [] {});
-                        build(true);
-                    }
+                    stage_any(slice, [] {});
                 } else {
-                    if (!idle) stage_x(slice);
-                    if (GS || !idle) {
-                        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
-                        build(!idle);
-                    }
+                    stage_x(slice);
+                    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // requested after the weights: wait for all
                 }
+                build();
             }
         }
     }
@@ -1651,20 +1688,6 @@ KernelFn pick_stream_t(int T)
     }
 }
 
-// units: scale units per 512-weight slice, 2 (256 weights each) or 4 (128 each, at most 2 tiles per item)
-KernelFn pick_stream_gs(int T, bool passes, int units)
-{
-    if (units == 4) {
-        if (T == 1) return passes ? gemv_stream_kernel<1, true, true, 1, 4> : gemv_stream_kernel<1, true, false, 1, 4>;
-        return passes ? gemv_stream_kernel<2, true, true, 1, 4> : gemv_stream_kernel<2, true, false, 1, 4>;
-    }
-    switch (T) {
-        case 1: return passes ? gemv_stream_kernel<1, true, true, 1, 2> : gemv_stream_kernel<1, true, false, 1, 2>;
-        case 2: return passes ? gemv_stream_kernel<2, true, true, 1, 2> : gemv_stream_kernel<2, true, false, 1, 2>;
-        default: return passes ? gemv_stream_kernel<3, true, true, 1, 2> : gemv_stream_kernel<3, true, false, 1, 2>;
-    }
-}
-
 KernelFn pick_stream(int T, bool multi, bool passes, int nb)
 {
     if (nb == 2) {                                         // two row blocks: T <= 2
@@ -1714,7 +1737,7 @@ constexpr int kStreamMaxRun = 32;       // tiles of a run whose sums fit the 32 
 template <class Args>
 using LeanFn = void (*)(Args);
 
-template <class Args, bool PASSES, bool GS, bool ANY>
+template <class Args, bool PASSES, int GS, bool ANY>
 LeanFn<Args> pick_lean(int T)
 {
     switch (T) {
@@ -1727,7 +1750,7 @@ LeanFn<Args> pick_lean(int T)
 constexpr int lean_lds(bool passes) { return 8 * stream_wave_lds(3) + (passes ? kStreamMaxRun * 1024 : 0); }
 
 // kept: tiles of the longest run of a job of several passes
-template <bool PASSES, bool GS, bool ANY, class Args>
+template <bool PASSES, int GS, bool ANY, class Args>
 hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept, hipStream_t s)
 {
     const LeanFn<Args> fn = pick_lean<Args, PASSES, GS, ANY>(T);
@@ -1744,11 +1767,25 @@ hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept
 }
 
 template <bool ANY, class Args>
-hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept, bool gs, hipStream_t s)
+hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept, int gs, hipStream_t s)
 {
-    if (gs) return kept ? launch_lean_args<true, true, ANY>(args, grid, NW, T, kept, s) : launch_lean_args<false, true, ANY>(args, grid, NW, T, 0, s);
-    return kept ? launch_lean_args<true, false, ANY>(args, grid, NW, T, kept, s) : launch_lean_args<false, false, ANY>(args, grid, NW, T, 0, s);
+    auto with = [&](auto tag) {
+        constexpr int GS = decltype(tag)::value;
+        return kept ? launch_lean_args<true, GS, ANY>(args, grid, NW, T, kept, s) : launch_lean_args<false, GS, ANY>(args, grid, NW, T, 0, s);
+    };
+    switch (gs) {
+        case 0:
+            if constexpr (ANY || std::is_same<Args, LeanBatch>::value) return with(std::integral_constant<int, 0>{});
+            else return hipErrorInvalidValue;
+        case 32: return with(std::integral_constant<int, 32>{});
+        case 64: return with(std::integral_constant<int, 64>{});
+        case 128: return with(std::integral_constant<int, 128>{});
+        default: return with(std::integral_constant<int, 256>{});
+    }
 }
+
+// What the groups of a scale are multiples of, of the kinds the lean kernel knows; 0: of none
+int lean_scale_kind(int64_t group) { return group % 256 == 0 ? 256 : group % 128 == 0 ? 128 : group % 64 == 0 ? 64 : group % 32 == 0 ? 32 : 0; }
 
 // ceil(2^31 / units per group): u * inverse / 2^31 rounded down is u / hpg for every u and hpg up to 2^15 (the error of the
 // inverse, below 2^-31, times u stays below the 1 / hpg that is missing to the next whole number), and K holds at most
@@ -1759,7 +1796,7 @@ uint32_t group_inverse(const GemvJob& J)
     const uint32_t hpg = uint32_t(J.hpg);
     return uint32_t(((uint64_t(1) << 31) + hpg - 1) / hpg);
 }
-static_assert(2 * kStreamWaves * kStreamMaxPasses <= 1 << 15, "group_inverse");
+static_assert(kSliceK / 32 * kStreamWaves * kStreamMaxPasses <= 1 << 15, "group_inverse");
 
 LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int K, int N, int rows, int tiles, int grid,
                 const __half* scales = nullptr, uint32_t group_inv = 0)
@@ -1770,11 +1807,12 @@ LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int 
 
 // Launch of the lean kernel: wg[j] workgroups for job j, each with a run of consecutive tiles
 // (the first tiles % wg[j] of them one tile longer), written out as one record per workgroup.
-hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, bool gs, bool any, hipStream_t s)
+hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, int gs, bool any, hipStream_t s)
 {
-    if (b.count == 1 && !any) {
+    if (b.count == 1 && gs == 0 && !any) {
         const GemvJob& J = b.job[0];
-        return launch_lean_args<false>(one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0], J.scales, group_inverse(J)), dim3(wg[0]), NW, T, kept, gs, s);
+        const LeanOne args = one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0]);
+        return kept ? launch_lean_args<true, 0, false>(args, dim3(wg[0]), NW, T, kept, s) : launch_lean_args<false, 0, false>(args, dim3(wg[0]), NW, T, 0, s);
     }
     LeanBatch lb;
     int grid = 0;
@@ -1806,6 +1844,10 @@ int tiles_per_item(int run, int NW)
     return T < NW ? T : NW;
 }
 
+// Groups of 64s hold a seed for each of a slice's eight units: with several passes and 3 tiles 20 registers spill (block at M = 1 / 4 / 16 22.0 / 22.0 / 24.7
+// us, with 2 tiles 18.9 / 18.5 / 21.9).
+int lean_passes_tiles(int T, int gs) { return gs == 64 && T > 2 ? 2 : T; }
+
 // rows: 0, or the rows of a call of any K and N
 template <class Args>
 LeanFn<Args> pick_longk(int T, int rows)
@@ -1835,9 +1877,10 @@ hipError_t launch_longk_args(const Args& args, dim3 grid, int T, int rows, hipSt
     return hipGetLastError();
 }
 
-// One product of any K and N: a set of workgroups for every block of 16 rows (blockIdx.y), as many in all as the CUs hold with 8 waves each.
-hipError_t launch_lean_any(const __half* x, const uint32_t* W, float gamma, const __half* scales, uint32_t group_inv, __half* y,
-                           int64_t M, int64_t N, int64_t K, hipStream_t s)
+// One product: a set of workgroups for every block of 16 rows (blockIdx.y), as many in all as the CUs hold with 8 waves each.
+// any: of any K and N; else K is a multiple of 64, N of 16, and there are scales.
+hipError_t launch_lean_rows(const __half* x, const uint32_t* W, float gamma, const __half* scales, uint32_t group_inv, __half* y,
+                            int64_t M, int64_t N, int64_t K, int gs, bool any, hipStream_t s)
 {
     const int slices = int((K + kSliceK - 1) / kSliceK), NW = slices < kStreamWaves ? slices : kStreamWaves;
     const int tiles = int((N + 15) / 16), blocks = int((M + 15) / 16);
@@ -1851,9 +1894,10 @@ hipError_t launch_lean_any(const __half* x, const uint32_t* W, float gamma, cons
     const int64_t longest = slices > NW ? kStreamMaxRun : (int64_t(1) << 31) / int64_t(packed_tile_bytes(int(K)));   // a run's kept sums, its bytes
     if (share < (tiles + longest - 1) / longest) share = (tiles + longest - 1) / longest;
     const int groups = share < 1 ? 1 : (tiles < share ? tiles : int(share));
-    const int run = (tiles + groups - 1) / groups, T = tiles_per_item(run, NW);
+    const int run = (tiles + groups - 1) / groups, t = tiles_per_item(run, NW), T = slices > NW ? lean_passes_tiles(t, gs) : t;
     const LeanAny args{one_job(W, x, y, gamma, int(K), int(N), int(M), tiles, groups, scales, group_inv)};
-    return launch_lean_args<true>(args, dim3(groups, blocks), NW, T, slices > NW ? run : 0, scales != nullptr, s);
+    const int kept = slices > NW ? run : 0;
+    return any ? launch_lean_args<true>(args, dim3(groups, blocks), NW, T, kept, gs, s) : launch_lean_args<false>(args, dim3(groups, blocks), NW, T, kept, gs, s);
 }
 
 // Calls in which every GEMM has 4096 < K <= 16384 and N a multiple of 16, and which hold at most two
@@ -1909,6 +1953,7 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
 // with the costliest runs, one by one.  Returns hipErrorInvalidValue without launching if a multi-pass job's
 // runs would not fit the LDS (the caller then uses the general kernel).
 // any: jobs of any K and N among them, for the lean kernel's form for those alone.
+// gs: 0, or the kind of scales (see lean_scale_kind); below 256 the lean kernel takes them in one of its forms.
 hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, int gs = 0, bool any = false)
 {
     const GemvPolicy pol = g_policy;
@@ -1932,7 +1977,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // costs its latency and barrier once: measured (block launch, runs of 15 ... 19 tiles) 1.0 us
     // for the first tile of an item and 0.2 us for each further one, i.e. 2.1 and 0.43 in units
     // of an average tile.
-    const DealModel model{(nb == 2 || gs == 4) ? 2 : 3, pol.item_cost != 0, pol.item_first, pol.tile_extra};
+    const DealModel model{nb == 2 ? 2 : 3, pol.item_cost != 0, pol.item_first, pol.tile_extra};
     DealJob dj[kMaxJobs];
     for (int j = 0; j < b.count; ++j) {
         const int rows = b.job[j].Mrem < 16 * nb ? b.job[j].Mrem : 16 * nb;
@@ -1954,40 +1999,27 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // and shorter runs are one item.
     int T = tiles_per_item(run, NW);
     if (pol.t_stream > 0 && T > pol.t_stream) T = pol.t_stream;
-    if (gs == 4 && T > 2) T = 2;         // scale units of 128 weights: 12 accumulators per tile (registers)
     if (nb == 2) {                       // two row blocks per job: at most 2 tiles per item (registers)
         if (T > 2) T = 2;
         if (2 * T > NW) T = NW / 2;
         if (T < 1) return hipErrorInvalidValue;
     }
     if (T < 1) T = 1;
+    if (multi_pass) T = lean_passes_tiles(T, gs);
     // The lean kernel takes the launch when every job has at least one slice per wave (more: several passes), N is a
-    // multiple of 16 throughout, scales if any for groups of whole 256s (units of 128 would need every product twice and the
-    // registers of twice the sums) and the workgroups fit its record table.  (The linears of a block, K = 4096 three times
+    // multiple of 16 throughout and the workgroups fit its record table; with scales else its form for any K and N.  (The linears of a block, K = 4096 three times
     // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
-    bool lean = pol.lean && nb == 1 && gs != 4 && T <= 3;
+    bool lean = pol.lean && nb == 1 && T <= 3;
     int total_groups = 0, kept = 0;
-    int64_t w_bytes = 0;                                   // packed words the launch streams
-    bool all_ahead = true;                                 // see below
     for (int j = 0; j < b.count; ++j) {
         lean = lean && (any || (b.job[j].slices >= NW && (b.job[j].N & 15) == 0));
         total_groups += wg[j];
-        w_bytes += int64_t(b.job[j].tiles) * 4 * b.job[j].K;
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
         if (passes(j) > 1 && r > kept) kept = r;
-        // With scales the general form is ahead (M = 2, 5760 -> 5376 7.3 against 8.9 us, -> 11584 9.0 / 10.8; M = 4, 4224 -> 8960 9.1 / 10.6;
-        // M = 1, 12928 -> 6784 13.0 / 15.3) up to 4 rows, whose activations it asks for a pass ahead, on runs of more than a tile,
-        // where the last pass has work for half of the waves at most: it skips the others.  Beside that the lean form is (M = 2, 5504 ->
-        // 3200 6.9 / 5.9; M = 9, 12224 -> 4992 15.4 / 15.1; M = 1, 11008 -> 4096 8.8 / 7.7).
-        const int last = b.job[j].slices % NW;
-        if (passes(j) > 1) all_ahead = all_ahead && b.job[j].Mrem <= 4 && r > 1 && last != 0 && 2 * last <= NW;
     }
-    if (gs != 0 && multi_pass && all_ahead) lean = false;
-    // The table of records costs the host 0.7 us, which a launch with scales and one pass over K earns back from about 12 MB on (several blocks of rows of a
-    // layer, lean over general: below 1 MB 1.09, 2 to 12 MB 1.00 to 1.02, 12 to 16 MB 0.96, beyond 0.93 to 0.95).
-    if (gs != 0 && b.count > 1 && !multi_pass && w_bytes < (int64_t(12) << 20)) lean = false;
-    if (any) return launch_lean(b, wg, NW, T, kept, gs != 0, true, s);
-    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs != 0, false, s);
+    if (any) return launch_lean(b, wg, NW, T, kept, gs, true, s);
+    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs, false, s);
+    if (gs != 0) return launch_stream(b, max_slices, nb, s, gs, true);
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;
     for (int j = 0; j < b.count; ++j) {
@@ -2001,11 +2033,10 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     b.total_items = 0;                                 // the stream form has no item queue
     b.red_off = 0;
     b.pad = 0;
-    const bool multi = gs != 0 || b.count > 1;         // the scaled form always reads the job table
-    KernelFn fn = gs ? pick_stream_gs(T, multi_pass, gs) : pick_stream(T, multi, multi_pass, nb);
-    static bool lds_raised[kMaxDevices][8][2][kTMax + 1];
-    const int variant = gs == 4 ? (multi_pass ? 7 : 6)
-                                : (gs ? (multi_pass ? 4 : 3) : (nb == 2 ? (multi_pass ? 5 : 2) : (multi_pass ? 1 : 0)));
+    const bool multi = b.count > 1;
+    KernelFn fn = pick_stream(T, multi, multi_pass, nb);
+    static bool lds_raised[kMaxDevices][4][2][kTMax + 1];
+    const int variant = nb == 2 ? (multi_pass ? 3 : 2) : (multi_pass ? 1 : 0);
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][variant][multi][T]) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
@@ -2115,21 +2146,25 @@ hipError_t gemv_init()
     for (int T = 1; T <= 3; ++T) {
         hipError_t e = hipSuccess;
         auto raise_lean = [&](auto gs_tag) {
-            constexpr bool GS = decltype(gs_tag)::value;
+            constexpr int GS = decltype(gs_tag)::value;
             auto raise_one = [&](const void* fn, bool passes) {
                 if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lean_lds(passes));
             };
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS, false>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS, false>(T)), true);
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, false, GS, false>(T)), false);
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanOne, true, GS, false>(T)), true);
+            typedef typename std::conditional<GS == 0, LeanOne, LeanAny>::type Alone;
+            raise_one(reinterpret_cast<const void*>(pick_lean<Alone, false, GS, false>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<Alone, true, GS, false>(T)), true);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS, true>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS, true>(T)), true);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanAny, false, GS, true>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanAny, true, GS, true>(T)), true);
         };
-        raise_lean(std::false_type{});
-        raise_lean(std::true_type{});
+        raise_lean(std::integral_constant<int, 0>{});
+        raise_lean(std::integral_constant<int, 32>{});
+        raise_lean(std::integral_constant<int, 64>{});
+        raise_lean(std::integral_constant<int, 128>{});
+        raise_lean(std::integral_constant<int, 256>{});
         if (e != hipSuccess) return e;
     }
     for (int T = 1; T <= kTMax; ++T)
@@ -2138,8 +2173,6 @@ hipError_t gemv_init()
             for (int passes = 0; passes < 2 && e == hipSuccess; ++passes) {
                 e = raise(pick_stream(T, multi != 0, passes != 0, 1), stream_lds);
                 if (e == hipSuccess && T <= 2) e = raise(pick_stream(T, multi != 0, passes != 0, 2), stream_lds);
-                if (e == hipSuccess && T <= 3) e = raise(pick_stream_gs(T, passes != 0, 2), stream_lds);
-                if (e == hipSuccess && T <= 2) e = raise(pick_stream_gs(T, passes != 0, 4), stream_lds);
             }
             if (e != hipSuccess) return e;
         }
@@ -2160,7 +2193,7 @@ bool gemv_any_supports(int64_t M, int64_t N, int64_t K)
 
 namespace {
 
-// Jobs (each passing gemv_any_supports, with a group in units of 256 weights or none) in blocks of 16 rows, kMaxJobs of them to a launch
+// Jobs (each passing gemv_any_supports; all with groups of one kind, or none) in blocks of 16 rows, kMaxJobs of them to a launch
 struct AnyJob {
     const __half* x;
     const uint32_t* W;
@@ -2170,21 +2203,24 @@ struct AnyJob {
     int64_t M, N, K, group;
 };
 
-hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s)
+// Scale units of a group; a group longer than K is the one group there is (the quotient itself need not fit 32 bits)
+int units_per_group(int64_t K, int64_t group, int kind)
 {
-    auto units_per_group = [](const AnyJob& d) {           // a group longer than K is the one group there is
-        const int64_t all = (d.K + 255) / 256;
-        return d.scales == nullptr ? 0 : int(d.group / 256 < all ? d.group / 256 : all);
-    };
+    const int64_t unit = lean_scale_unit(kind), all = (K + unit - 1) / unit;
+    return int(group / unit < all ? group / unit : all);
+}
+
+hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s, int gs = 0)
+{
     GemvBatch b;
     b.count = 0;
     int max_slices = 1;
     auto one = [&](const GemvJob& j, int64_t M) {
-        return launch_lean_any(j.x, j.W, j.gamma, j.scales, group_inverse(j), j.y, M, j.N, j.K, s);
+        return launch_lean_rows(j.x, j.W, j.gamma, j.scales, group_inverse(j), j.y, M, j.N, j.K, gs, true, s);
     };
     auto flush = [&]() -> hipError_t {
         if (b.count == 0) return hipSuccess;
-        hipError_t e = b.count == 1 ? hipErrorInvalidValue : launch_stream(b, max_slices, 1, s, b.job[0].scales ? 2 : 0, true);
+        hipError_t e = b.count == 1 ? hipErrorInvalidValue : launch_stream(b, max_slices, 1, s, gs, true);
         if (e == hipErrorInvalidValue) {                   // one job, or runs too long for what a launch keeps of their sums: one launch each
             e = hipSuccess;
             for (int q = 0; q < b.count && e == hipSuccess; ++q) e = one(b.job[q], b.job[q].Mrem);
@@ -2200,7 +2236,7 @@ hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s)
         j.N = int(d.N); j.K = int(d.K);
         j.tiles = int((d.N + 15) / 16);
         j.slices = int((d.K + kSliceK - 1) / kSliceK);
-        j.scales = d.scales; j.hpg = units_per_group(d);
+        j.scales = d.scales; j.hpg = gs ? units_per_group(d.K, d.group, gs) : 0;
         if (count == 1) return one(j, d.M);
         for (int64_t m0 = 0; m0 < d.M; m0 += 16) {
             GemvJob q = j;
@@ -2329,8 +2365,11 @@ bool gemv_gs_supports(int64_t M, int64_t N, int64_t K, int64_t group)
     const int64_t slices = (K + kSliceK - 1) / kSliceK;
     // (the kernel addresses the scales with 32-bit byte offsets)
     if (((K - 1) / group + 1) * N * 2 >= (int64_t(1) << 31)) return false;
-    return gemv_supports(M, N, K) && group >= 128 && group % 128 == 0 && N >= 4 && N % 4 == 0 &&
-           slices <= kStreamWaves * kStreamMaxPasses &&
+    if (N < 4 || N % 4 != 0 || lean_scale_kind(group) == 0) return false;
+    // Other K: a row's last chunk of packed words starts anywhere in units of 16 weights and meets zeros up to its own, which are a unit of 64 or part
+    // of one; units of 32 would lie across its halves.
+    if (K % 64 != 0) return group % 64 == 0 && gemv_any_supports(M, N, K);
+    return gemv_supports(M, N, K) && slices <= kStreamWaves * kStreamMaxPasses &&
            (slices <= kStreamWaves || (N + 15) / 16 <= int64_t(256) * kStreamMaxRun);
 }
 
@@ -2338,17 +2377,30 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
 {
     for (int i = 0; i < count; ++i)
         if (!gemv_gs_supports(jobs[i].M, jobs[i].N, jobs[i].K, jobs[i].group)) return hipErrorInvalidValue;
-    // Jobs whose groups are multiples of 256 weights and jobs with odd multiples of 128 run in
-    // different instances of the kernel; each kind shares launches, kMaxJobs blocks of 16
-    // activation rows per launch.  A launch whose runs would not fit the LDS of a multi-pass
-    // workgroup (launch_stream says so without launching) goes out as one launch per job.
-    for (int units = 2; units <= 4; units += 2) {
+    if (count == 1) {
+        const GemmGsDesc& d = jobs[0];
+        const int kind = lean_scale_kind(d.group);
+        GemvJob j{};
+        j.scales = d.scales;
+        j.hpg = units_per_group(d.K, d.group, kind);
+        constexpr int64_t kAtOnce = 4096;                  // rows of a launch, which bounds its grid
+        for (int64_t m0 = 0; m0 < d.M; m0 += kAtOnce) {
+            const hipError_t e = launch_lean_rows(d.x + m0 * d.K, d.W, 1.f, d.scales, group_inverse(j), d.y + m0 * d.N, d.M - m0 < kAtOnce ? d.M - m0 : kAtOnce,
+                                                  d.N, d.K, kind, d.K % 64 != 0 || d.N % 16 != 0, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    // Each kind of groups has instances of its own and shares launches, kMaxJobs blocks of 16 activation rows per launch; so do, kind
+    // by kind, jobs of other K.  A launch whose runs would not fit the LDS of a multi-pass workgroup (launch_stream says so
+    // without launching) goes out as one launch per job.
+    for (int kind = 32; kind <= 256; kind *= 2) {
         GemvBatch b;
         b.count = 0;
         int max_slices = 1;
         auto flush = [&]() -> hipError_t {
             if (b.count == 0) return hipSuccess;
-            hipError_t e = launch_stream(b, max_slices, 1, s, units);
+            hipError_t e = launch_stream(b, max_slices, 1, s, kind);
             if (e == hipErrorInvalidValue && b.count > 1) {
                 // one launch per row block; a block alone fits by gemv_gs_supports
                 e = hipSuccess;
@@ -2356,20 +2408,30 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
                     GemvBatch one;
                     one.count = 1;
                     one.job[0] = b.job[q];
-                    e = launch_stream(one, one.job[0].slices, 1, s, units);
+                    e = launch_stream(one, one.job[0].slices, 1, s, kind);
                 }
             }
             b.count = 0;
             max_slices = 1;
             return e;
         };
+        constexpr int kAtOnce = 64;
+        AnyJob other[kAtOnce];
+        int others = 0;
         for (int i = 0; i < count; ++i) {
             const GemmGsDesc& d = jobs[i];
-            if ((d.group % 256 == 0 ? 2 : 4) != units) continue;
+            if (lean_scale_kind(d.group) != kind) continue;
+            if (d.K % 64 != 0) {
+                other[others++] = AnyJob{d.x, d.W, d.scales, d.y, 1.f, d.M, d.N, d.K, d.group};
+                if (others == kAtOnce) {
+                    const hipError_t e = launch_any_jobs(other, others, s, kind);
+                    if (e != hipSuccess) return e;
+                    others = 0;
+                }
+                continue;
+            }
             const int slices = int((d.K + kSliceK - 1) / kSliceK);
-            // units per group: a group longer than K is the one group there is (the quotient itself need not fit 32 bits)
-            const int64_t unit = kSliceK / units, all = (d.K + unit - 1) / unit;
-            const int hpg = int(d.group / unit < all ? d.group / unit : all);
+            const int hpg = units_per_group(d.K, d.group, kind);
             for (int64_t m0 = 0; m0 < d.M; m0 += 16) {
                 GemvJob j;
                 j.x = d.x + m0 * d.K;
@@ -2392,7 +2454,8 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
                 }
             }
         }
-        const hipError_t e = flush();
+        hipError_t e = flush();
+        if (e == hipSuccess && others) e = launch_any_jobs(other, others, s, kind);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

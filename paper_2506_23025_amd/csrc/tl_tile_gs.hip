@@ -19,13 +19,13 @@ typedef TileCfg<kTileGs, false, 2, 2, 1, 2, 4, 4, 4, 1> T32x64any;
 
 constexpr int kShapes = 7, kFirstAny = 3;     // from kFirstAny on any group that is a multiple of 16
 constexpr TileCost kCost[kShapes] = {
-    {256, 256, 64, 256, 6.3, 6.3, 1.205, 1.454, 1.454, 0.93, 0.5},
-    {128, 256, 128, 256, 7.85, 7.85, 1.29, 1.525, 1.525, 0.91, 0.75},
-    {128, 128, 128, 256, 5.6, 5.6, 0.73, 0.863, 0.863, 0.90, 1.2},
-    {128, 128, 128, 256, 5.45, 5.45, 0.815, 0.932, 0.932, 0.91, 1.1},
-    {128, 64, 128, 256, 4.45, 4.45, 0.415, 0.49, 0.49, 0.91, 0.95},
-    {64, 64, 128, 512, 2.0, 3.8, 0.28, 0.321, 0.542, 0.42, 2.85},
-    {32, 64, 128, 512, 1.4, 3.2, 0.236, 0.258, 0.407, 0.39, 2.9},
+    {256, 256, 64, 256, 6.8, 6.8, 0.955, 1.444, 1.444, 0.743, 2.24},
+    {128, 256, 128, 256, 7.29, 7.29, 1.089, 1.505, 1.505, 0.838, 3.37},
+    {128, 128, 128, 256, 5.31, 5.31, 0.632, 0.861, 0.861, 0.826, 2.76},
+    {128, 128, 128, 256, 5.32, 5.32, 0.617, 0.842, 0.842, 0.865, 2.88},
+    {128, 64, 128, 256, 4.43, 4.43, 0.379, 0.475, 0.475, 0.909, 1.9},
+    {64, 64, 128, 512, 1.61, 3.79, 0.282, 0.343, 0.545, 0.432, 3.76},
+    {32, 64, 128, 512, 1.13, 3.29, 0.227, 0.265, 0.398, 0.375, 3.68},
 };
 
 // K that is no multiple of 64
@@ -35,9 +35,9 @@ typedef TileCfg<kTileGs, true, 1, 2, 1, 2, 4, 4, 2, 1> R16x64;      // two workg
 
 constexpr int kRagged = 3;
 constexpr TileCost kRaggedCost[kRagged] = {
-    {64, 128, 128, 256, 4.2, 4.2, 0.83, 0.83, 0.83, 0.6, 2.0},
-    {32, 64, 128, 512, 2.4, 2.4, 0.38, 0.38, 0.54, 0.6, 2.0},
-    {16, 64, 128, 512, 2.1, 2.1, 0.36, 0.36, 0.53, 0.6, 2.0},
+    {64, 128, 128, 256, 4.6, 4.6, 0.734, 0.951, 0.951, 0.807, 1.38},
+    {32, 64, 128, 512, 1.45, 2.96, 0.363, 0.42, 0.58, 0.429, 2.69},
+    {16, 64, 128, 512, 0.96, 2.32, 0.349, 0.398, 0.531, 0.434, 3.1},
 };
 
 int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
@@ -58,26 +58,35 @@ int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
 
 }  // namespace
 
-// What the weight-streaming kernel takes (us) for more than 16 rows, W being decoded once per b blocks of 16: t tiles of 16 output rows, s slices
-// of 512 weights, p passes of 8 slices; groups that are odd multiples of 128 need every product twice.  Fitted to 2550 calls over M = 17 ..
-// 2048, N = 512 .. 16384, K = 512 .. 14336: 14 % for nine in ten, 20 % with
-// several passes.
+// What the weight-streaming kernel takes (us) for more than 16 rows in one launch: m rows of a block, b blocks of 16, s slices of 512 weights, p passes of 8
+// slices; w workgroups to a CU and xt tiles to a CU (as in launch_lean_rows).  A line each for groups of 256s, 128s, 64s and 32s.  Fitted, with
+// the tiles' times, to 2500 calls over M = 1 .. 2048, N = 512 .. 16384, K = 512 .. 14336 and 1500 with K no multiple of 64, weights out of the caches:
+// 14 % for nine in ten, and the one chosen is 0.3 % slower than the best on average, 10 % in one of a hundred.
 static double stream_gs_time(int64_t M, int64_t N, int64_t K, int64_t group)
 {
-    const bool whole = group % 256 == 0;
-    const int s = int((K + 511) / 512);
-    const double p = double((s + 7) / 8), b = double((M + 15) / 16), launches = double(((M + 15) / 16 + 31) / 32);
-    const double x = b * double((N + 15) / 16) / 256.0;
-    if (s <= 8) {
-        constexpr double per_whole[9] = {0, 0.132, 0.241, 0.379, 0.443, 0.644, 0.681, 0.712, 0.789};
-        constexpr double per_odd[9] = {0, 0.182, 0.341, 0.615, 0.665, 1.21, 1.29, 1.35, 1.43};
-        return whole ? 4.5 * launches + 0.136 * b + per_whole[s] * x : 4.95 * launches + 0.055 * b + per_odd[s] * x;
-    }
-    return 1.9 + 3.2 * launches * p + 0.1 * b + x * (whole ? 0.0475 * double(s) + 0.71 * p : 0.145 * double(s) + 0.77 * p);
+    struct Line { double start, row, row_slice, per_tile[9], start_p, pass, pass_row, tile_slice, tile_pass; };
+    static constexpr Line lines[4] = {
+        {3.19, 0.042, 0.006, {0, 0.14, 0.225, 0.368, 0.448, 0.711, 0.748, 0.757, 0.843}, 2.74, 0.933, 0.102, 0.062, 0.386},
+        {3.23, 0.053, 0.004, {0, 0.147, 0.244, 0.399, 0.462, 0.759, 0.792, 0.841, 0.929}, 2.91, 0.873, 0.106, 0.052, 0.459},
+        {3.2, 0.051, 0.004, {0, 0.164, 0.273, 0.452, 0.538, 0.88, 0.927, 1.014, 1.074}, 3.42, 0.536, 0.131, 0.102, 0.473},
+        {3.42, 0.061, 0.0, {0, 0.24, 0.399, 0.69, 0.756, 1.35, 1.405, 1.505, 1.473}, 2.59, 1.093, 0.07, 0.1, 0.803},
+    };
+    const Line& c = lines[group % 256 == 0 ? 0 : group % 128 == 0 ? 1 : group % 64 == 0 ? 2 : 3];
+    const int64_t s = (K + 511) / 512, tiles = (N + 15) / 16, b = (M + 15) / 16;
+    const double m = double(M < 16 ? M : 16);
+    int64_t share = 256 * (8 / (s < 8 ? s : 8)) / b;
+    if (s > 8 && share < (tiles + 31) / 32) share = (tiles + 31) / 32;
+    if (share < 1) share = 1;
+    const int64_t groups = tiles < share ? tiles : share;
+    const double w = double((groups * b + 255) / 256), xt = double((tiles + groups - 1) / groups) * w;
+    const double p = double((s + 7) / 8);
+    const double t = s <= 8 ? c.start + c.row * m + c.row_slice * m * double(s) * w + c.per_tile[s] * xt
+                            : c.start_p + w * p * (c.pass + c.pass_row * m) + xt * (c.tile_slice * double(s) + c.tile_pass * p);
+    return K % 64 != 0 ? 1.1 * t + 0.35 : t;
 }
 
-// Tiled kernel or what would take the call without it: the weight-streaming kernel, which never loses up to 16 rows (over the calls of the
-// fit the one chosen is 0.2 % slower than the best on average and 6 % in one of a hundred), or, for other groups, the plain kernel on the
+// Tiled kernel or what would take the call without it: the weight-streaming kernel, which up to 16 rows was the fastest in all calls of the fit but a
+// few of groups of 64s and 32s (by up to 7 and 15 %), or, for other groups, the plain kernel on the
 // vector ALUs, 3 + K / 4096 (6.5 + 1.25 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (us; 4096 -> 4096: M = 1
 // 11.3, M = 4 14.6, M = 16 29.8, M = 37 45.8).
 bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
@@ -99,13 +108,15 @@ KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group)
     KernelChoice c{gemv_gs_supports(M, N, K, group), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!c.streams || M <= 16) return c;
     c.stream = stream_gs_time(M, N, K, group);
-    c.launch = 4.5;
-    c.launches = double((M + 15) / 16) / 32.0;
-    c.fixed = c.launch * (c.launches > 1.0 ? double(int64_t(c.launches + 0.999)) : 1.0);
+    c.launch = 3.2;
+    c.fixed = c.launch;                                    // of its own it is one launch, however many rows
+    // In a shared launch it has a part of 256 workgroups, which for K of up to four slices leave wavefronts out: 1.15 to 1.2 times as long up
+    // to 64 rows, 1.2 to 1.5 times up to 512 (250 calls both ways).
+    const double blocks = double((M + 15) / 16), crowd = K > 2048 ? 0.0 : blocks > 4.0 ? 0.3 : 0.15;
+    c.launches = blocks / 32.0 + crowd * (c.stream - c.fixed) / c.launch;
     c.tiled = c.stream;
-    if (tile_at_least(kCost, kShapes, K) >= c.stream) return c;
+    if (K % 64 != 0 ? tile_at_least(kRaggedCost, kRagged, K) >= c.stream : tile_at_least(kCost, kShapes, K) >= c.stream) return c;
     pick(M, N, K, group, &c.tiled);
-    if (K > 4096) c.tiled *= 1.1;                          // the streaming kernel's time is less certain there: 20 % for nine in ten
     return c;
 }
 
