@@ -841,9 +841,9 @@ struct LeanOne {
     int per, plus;
     uint32_t group_inv;           // see WgRec
     const unsigned char* sc;
-    __device__ WgRec mine() const
+    __device__ WgRec mine() const { return at(int(blockIdx.x)); }
+    __device__ WgRec at(int g) const
     {
-        const int g = int(blockIdx.x);
         WgRec r;
         r.tile0 = g * per + (g < plus ? g : plus);
         r.ntiles = per + (g < plus ? 1 : 0);
@@ -869,6 +869,29 @@ struct LeanAny : LeanOne {
     }
 };
 static_assert(sizeof(LeanOne) == 64, "the arguments of a lone call");
+
+// A few jobs in a small launch: 1 KB of arguments, and a workgroup finds its job by two scalar look-ups in turn.  The records' 16 KB cost the host
+// 1.1 us, which is what a small call waits for; the look-ups cost the device 0.2 to 0.4 us (two layers of 2048 x 2048 called in a loop 5.4
+// -> 4.3 us, replayed from a graph 3.1 -> 3.3; 4096 x 4096 5.6 -> 4.8 and 4.6 -> 5.0; two of 5504 x 4096, 11 MB, 5.7 -> 5.9 and 5.65 -> 6.2).
+constexpr int kLeanTableJobs = 16;
+struct LeanJobs {
+    int first[kLeanTableJobs];    // first workgroup of job j; INT_MAX for unused entries
+    LeanOne job[kLeanTableJobs];
+    __device__ WgRec mine() const
+    {
+        int j = 0;
+#pragma unroll
+        for (int i = 1; i < 8; ++i) j += int(blockIdx.x) >= first[i] ? 1 : 0;
+        if (j == 7) {
+#pragma unroll
+            for (int i = 8; i < kLeanTableJobs; ++i) j += int(blockIdx.x) >= first[i] ? 1 : 0;
+        }
+        const LeanOne& J = job[j];
+        WgRec r = J.at(int(blockIdx.x) - first[j]);
+        r.W = J.W + size_t(r.tile0) * packed_tile_bytes(J.K);
+        return r;
+    }
+};
 
 // Activations whose rows start at any even address (K no multiple of 64), to the places the operand set-up reads: through registers, a row to a
 // request.  Lane l takes piece l of the slice, eighth l % 8 of chunk l / 8; a row's last chunk is its last 64 weights (16 packed bytes).  What
@@ -1040,8 +1063,12 @@ gemv_lean_kernel(Args b)
         else if (rows <= 8) with(std::integral_constant<int, 8>{});
         else with(std::integral_constant<int, 16>{});
     };
-    const bool idle = ANY && wave >= slices;               // this wave has no slice at all
-    if constexpr (!ANY) stage_x(wave);
+    // A job with fewer slices than waves, which the table of records does not hold: looking for it there cost the decode sweep 18.2 -> 20.0 us.
+    constexpr bool kIdle = ANY || std::is_same<Args, LeanJobs>::value;
+    const bool idle = kIdle && wave >= slices;             // this wave has no slice at all
+    if constexpr (!ANY) {
+        if (!idle) stage_x(wave);
+    }
     constexpr int H = GS == 256 ? 2 : 1;
     // GS: the job's scales from the run's first row as a raw buffer, the lane's rows in it, and the units' groups
     constexpr int kUnit = lean_scale_unit(GS);             // weights per scale that is fetched
@@ -1116,9 +1143,11 @@ gemv_lean_kernel(Args b)
     if constexpr (ANY) {
         if (!idle) stage_any(wave, first_tiles);
     } else {
-        first_tiles();
-        // the compiler does not track LDS-DMA: wait until only the weight (and scale) loads are outstanding
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((FINE ? 3 : GS ? 4 : 2) * T));
+        if (!idle) {
+            first_tiles();
+            // the compiler does not track LDS-DMA: wait until only the weight (and scale) loads are outstanding
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm((FINE ? 3 : GS ? 4 : 2) * T));
+        }
     }
 
     // ---- activations -> MFMA B operands (see gemv_stream_kernel) and the -sum(x) seed ----------
@@ -1188,7 +1217,7 @@ gemv_lean_kernel(Args b)
                 nsx[GS ? h : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(breg[h * 8 + e]), nsx[GS ? h : 0], 0, 0, 0);
         }
     };
-    if (!ANY || !idle) build();
+    if (!idle) build();
 
     const uint32_t ww_off = FINE ? uint32_t(lr) * 144u + (uint32_t(lc) << 4) : uint32_t(lr) * 128u + (uint32_t(lc ^ lr) << 4);
     constexpr uint32_t kUpperRows = FINE ? 8 * 144 : 1024;
@@ -1245,39 +1274,48 @@ gemv_lean_kernel(Args b)
         return sum;
     };
 
-    // split-K: each wave's partial sums of nt tiles are in its set `parity`; one LDS-only barrier, fixed-order sum
+    // split-K: each wave's partial sums of nt tiles are in its set `parity`; one LDS-only barrier, fixed-order sum.  A thread owns an output
+    // quad of tile threadIdx.x / 64 of the item.
+    const int ot = int(threadIdx.x) >> 6;
+    const uint32_t ycol = uint32_t(R.tile0) * 16u + 4u * uint32_t(mg);       // + 16 (first + ot)
+    gh_ptr const yrow = (gh_ptr)(R.y + size_t(mi) * size_t(N));
     unsigned char* const ysum = lds_raw + NW * kStride;
+    auto sum_of = [&](int t, int l, int parity) {
+        f32x4 v[8];
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+            v[w] = (w < NW) ? reinterpret_cast<const f32x4*>(lds_raw + w * kStride + kSums + parity * (T * 1024) + t * 1024)[l]
+                            : f32x4{0.f, 0.f, 0.f, 0.f};
+        return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    };
+    auto put = [&](gh_ptr row, uint32_t col, f32x4 s) {
+        if constexpr (ANY) {
+            store_quad_any(row, int(col), N, s, gamma);
+        } else {
+            const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
+            const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
+            *(__attribute__((address_space(1))) u32x2*)(row + col) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+        }
+    };
     auto exchange = [&](int nt, int first, int parity, bool first_pass, bool last_pass) {
         __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
         __builtin_amdgcn_s_barrier();
-        if (wave < nt) {                                   // a thread owns an output quad of tile `wave` of the item
-            // PASSES: its places are worked out here.  Kept over the loop they took registers that others were spilled for, and a
-            // reload waits for every weight on its way.
+        if constexpr (!PASSES) {
+            if (ot < nt) {
+                const f32x4 s = sum_of(ot, lane, parity);
+                if (mi < rows) put(yrow, ycol + 16u * uint32_t(first + ot), s);
+            }
+        } else if (wave < nt) {
+            // The thread's places are worked out here.  Kept over the loop they took registers that others were spilled for, and a
+            // reload waits for every weight on its way (block with groups of 256 at M = 1 / 4 / 16 16.5 / 16.8 / 19.0 -> 15.0 / 15.5 / 18.0 us).
             int l = lane;
-            if constexpr (PASSES) asm volatile("" : "+v"(l));
-            f32x4 v[8];
-#pragma unroll
-            for (int w = 0; w < 8; ++w)
-                v[w] = (w < NW) ? reinterpret_cast<const f32x4*>(lds_raw + w * kStride + kSums + parity * (T * 1024) + wave * 1024)[l]
-                                : f32x4{0.f, 0.f, 0.f, 0.f};
-            f32x4 s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-            if constexpr (PASSES) {
-                f32x4* const keep = reinterpret_cast<f32x4*>(ysum + (first + wave) * 1024) + l;
-                if (!first_pass) s += *keep;
-                if (!last_pass) *keep = s;
-            }
-            const int row = l & 15;
-            if (row < rows && (!PASSES || last_pass)) {
-                gh_ptr const yrow = (gh_ptr)(R.y + size_t(row) * size_t(N));
-                const uint32_t col = uint32_t(R.tile0 + first + wave) * 16u + 4u * uint32_t(l >> 4);
-                if constexpr (ANY) {
-                    store_quad_any(yrow, int(col), N, s, gamma);
-                } else {
-                    const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
-                    const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
-                    *(__attribute__((address_space(1))) u32x2*)(yrow + col) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-                }
-            }
+            asm volatile("" : "+v"(l));
+            f32x4 s = sum_of(wave, l, parity);
+            f32x4* const keep = reinterpret_cast<f32x4*>(ysum + (first + wave) * 1024) + l;
+            if (!first_pass) s += *keep;
+            if (!last_pass) *keep = s;
+            if (last_pass && (l & 15) < rows)
+                put((gh_ptr)(R.y + size_t(l & 15) * size_t(N)), uint32_t(R.tile0 + first + wave) * 16u + 4u * uint32_t(l >> 4), s);
         }
     };
 
@@ -1382,7 +1420,7 @@ gemv_lean_kernel(Args b)
             exchange(left < T ? left : T, i * T, i & 1, first_pass, true);
         }
     };
-    if constexpr (ANY) {
+    if constexpr (kIdle) {
         if (idle) { idle_items(true); return; }
     }
     if constexpr (!PASSES) {
@@ -1747,6 +1785,8 @@ LeanFn<Args> pick_lean(int T)
     }
 }
 
+constexpr int64_t kLeanTableBytes = int64_t(10) << 20;       // of packed words in a launch, see LeanJobs
+
 constexpr int lean_lds(bool passes) { return 8 * stream_wave_lds(3) + (passes ? kStreamMaxRun * 1024 : 0); }
 
 // kept: tiles of the longest run of a job of several passes
@@ -1771,11 +1811,13 @@ hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept
 {
     auto with = [&](auto tag) {
         constexpr int GS = decltype(tag)::value;
-        return kept ? launch_lean_args<true, GS, ANY>(args, grid, NW, T, kept, s) : launch_lean_args<false, GS, ANY>(args, grid, NW, T, 0, s);
+        if constexpr (!std::is_same<Args, LeanJobs>::value)
+            if (kept) return launch_lean_args<true, GS, ANY>(args, grid, NW, T, kept, s);
+        return launch_lean_args<false, GS, ANY>(args, grid, NW, T, 0, s);
     };
     switch (gs) {
         case 0:
-            if constexpr (ANY || std::is_same<Args, LeanBatch>::value) return with(std::integral_constant<int, 0>{});
+            if constexpr (ANY || !std::is_same<Args, LeanAny>::value) return with(std::integral_constant<int, 0>{});
             else return hipErrorInvalidValue;
         case 32: return with(std::integral_constant<int, 32>{});
         case 64: return with(std::integral_constant<int, 64>{});
@@ -1807,12 +1849,29 @@ LeanOne one_job(const uint32_t* W, const __half* x, __half* y, float gamma, int 
 
 // Launch of the lean kernel: wg[j] workgroups for job j, each with a run of consecutive tiles
 // (the first tiles % wg[j] of them one tile longer), written out as one record per workgroup.
-hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, int gs, bool any, hipStream_t s)
+hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kept, int gs, bool any, bool table, hipStream_t s)
 {
     if (b.count == 1 && gs == 0 && !any) {
         const GemvJob& J = b.job[0];
         const LeanOne args = one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0]);
         return kept ? launch_lean_args<true, 0, false>(args, dim3(wg[0]), NW, T, kept, s) : launch_lean_args<false, 0, false>(args, dim3(wg[0]), NW, T, 0, s);
+    }
+    if (b.count == 1 && !any) {
+        const GemvJob& J = b.job[0];
+        const LeanAny args{one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0], J.scales, group_inverse(J))};
+        return launch_lean_args<false>(args, dim3(wg[0]), NW, T, kept, gs, s);
+    }
+    if (table) {
+        LeanJobs lj;
+        int grid = 0;
+        for (int j = 0; j < kLeanTableJobs; ++j) {
+            lj.first[j] = j < b.count ? grid : 0x7fffffff;
+            if (j >= b.count) continue;
+            const GemvJob& J = b.job[j];
+            lj.job[j] = one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[j], J.scales, group_inverse(J));
+            grid += wg[j];
+        }
+        return any ? launch_lean_args<true>(lj, dim3(grid), NW, T, 0, gs, s) : launch_lean_args<false>(lj, dim3(grid), NW, T, 0, gs, s);
     }
     LeanBatch lb;
     int grid = 0;
@@ -1959,15 +2018,22 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     const GemvPolicy pol = g_policy;
     const int NW = max_slices < kStreamWaves ? max_slices : kStreamWaves;
     auto passes = [&](int j) { return (b.job[j].slices + NW - 1) / NW; };
-    int64_t total_tiles = 0;
-    bool multi_pass = false;
+    int64_t total_tiles = 0, w_bytes = 0;
+    bool multi_pass = false, short_jobs = false;           // short: fewer slices than waves
     for (int j = 0; j < b.count; ++j) {
         total_tiles += b.job[j].tiles;
+        w_bytes += int64_t(b.job[j].tiles) * int64_t(packed_tile_bytes(b.job[j].K));
+        short_jobs |= b.job[j].slices < NW;
         multi_pass |= passes(j) > 1;
     }
     // One workgroup of 8 waves per CU; with shorter K (fewer waves per workgroup) as many more
     // workgroups, so that a CU still runs 8 waves (K = 1024: 1024 workgroups of 2 waves).
-    const int64_t g_max = any ? kLeanMaxGroups : int64_t(pol.stream_groups) * (kStreamWaves / NW);
+    const int64_t g_all = int64_t(pol.stream_groups) * (kStreamWaves / NW);
+    // With scales the table of jobs also takes what no records hold, more than 256 workgroups or jobs with fewer slices than waves.
+    const bool no_records = gs != 0 && (short_jobs || (total_tiles > kLeanMaxGroups && g_all > kLeanMaxGroups));
+    const bool table = nb == 1 && !multi_pass && b.count > 1 && b.count <= kLeanTableJobs &&
+                       (no_records || (w_bytes < kLeanTableBytes && !short_jobs));
+    const int64_t g_max = any && !table ? kLeanMaxGroups : g_all;
     const int G = total_tiles < g_max ? int(total_tiles) : int(g_max);
     // Time of a workgroup in tile units: passes x (run time + start-up), see tl_deal.hpp.  The
     // start-up of a pass is fetching the activation slice (1 KB per row and wave through the same
@@ -2009,16 +2075,16 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // The lean kernel takes the launch when every job has at least one slice per wave (more: several passes), N is a
     // multiple of 16 throughout and the workgroups fit its record table; with scales else its form for any K and N.  (The linears of a block, K = 4096 three times
     // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
-    bool lean = pol.lean && nb == 1 && T <= 3;
+    bool lean = pol.lean && nb == 1 && T <= 3 && (!short_jobs || table || any);
     int total_groups = 0, kept = 0;
     for (int j = 0; j < b.count; ++j) {
-        lean = lean && (any || (b.job[j].slices >= NW && (b.job[j].N & 15) == 0));
+        lean = lean && (any || (b.job[j].N & 15) == 0);
         total_groups += wg[j];
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
         if (passes(j) > 1 && r > kept) kept = r;
     }
-    if (any) return launch_lean(b, wg, NW, T, kept, gs, true, s);
-    if (lean && total_groups <= kLeanMaxGroups) return launch_lean(b, wg, NW, T, kept, gs, false, s);
+    if (any) return launch_lean(b, wg, NW, T, kept, gs, true, table, s);
+    if (lean && (total_groups <= kLeanMaxGroups || table || b.count == 1)) return launch_lean(b, wg, NW, T, kept, gs, false, table, s);
     if (gs != 0) return launch_stream(b, max_slices, nb, s, gs, true);
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;
@@ -2155,6 +2221,8 @@ hipError_t gemv_init()
             typedef typename std::conditional<GS == 0, LeanOne, LeanAny>::type Alone;
             raise_one(reinterpret_cast<const void*>(pick_lean<Alone, false, GS, false>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<Alone, true, GS, false>(T)), true);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs, false, GS, false>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs, false, GS, true>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS, true>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS, true>(T)), true);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanAny, false, GS, true>(T)), false);
@@ -2398,9 +2466,10 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
         GemvBatch b;
         b.count = 0;
         int max_slices = 1;
+        bool quads = false;                                // an N that is no multiple of 16
         auto flush = [&]() -> hipError_t {
             if (b.count == 0) return hipSuccess;
-            hipError_t e = launch_stream(b, max_slices, 1, s, kind);
+            hipError_t e = launch_stream(b, max_slices, 1, s, kind, quads);
             if (e == hipErrorInvalidValue && b.count > 1) {
                 // one launch per row block; a block alone fits by gemv_gs_supports
                 e = hipSuccess;
@@ -2408,11 +2477,12 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
                     GemvBatch one;
                     one.count = 1;
                     one.job[0] = b.job[q];
-                    e = launch_stream(one, one.job[0].slices, 1, s, kind);
+                    e = launch_stream(one, one.job[0].slices, 1, s, kind, one.job[0].N % 16 != 0);
                 }
             }
             b.count = 0;
             max_slices = 1;
+            quads = false;
             return e;
         };
         constexpr int kAtOnce = 64;
@@ -2447,6 +2517,7 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
                 j.run = j.plus = 0;
                 j.scales = d.scales; j.hpg = hpg; j.reserved = 0;
                 b.job[b.count++] = j;
+                quads = quads || d.N % 16 != 0;
                 if (slices > max_slices) max_slices = slices;
                 if (b.count == kMaxJobs) {
                     const hipError_t e = flush();

@@ -77,6 +77,23 @@ def test_groups_in_one_call(specs):
     assert not any(grouped(SCALES, [s for s in specs if s[0] <= 16]))
 
 
+# a few small jobs, which find their place in a table of jobs: of 2 to 16 jobs, of equal and of different numbers of slices, N of quads, more
+# workgroups than 256, one gamma or scales; one job more than the table holds
+@pytest.mark.parametrize("group", [0, 64, 256])
+@pytest.mark.parametrize("specs", [[(1, 512, 512)] * 2, [(3, 528, 1024)] * 8, [(2, 64, 2048), (16, 4096, 2048), (1, 16, 2048)] * 3, [(i + 1, 512, 1024) for i in range(16)], [(1, 256, 512)] * 17,
+                                   [(4, 1024, 512), (4, 20, 1024), (4, 1000, 4096)], [(1, 12288, 1024), (2, 12288, 1024)], [(1, 16, 64), (1, 16, 4096)]])
+def test_small_jobs_in_one_call(specs, group):
+    host = [inputs(M, N, K, group or 1 << 20, 66000 + i + M + N + K) for i, (M, N, K) in enumerate(specs)]
+    dev = [on_device(x, W, sc, M, N) for (x, W, sc), (M, N, K) in zip(host, specs)]
+    if group:
+        tl.tl_ternary_gemm_gs_grouped([(xd, wd, sd, group, yd, M, N, K) for (xd, wd, sd, yd), (M, N, K) in zip(dev, specs)])
+    else:
+        tl.tl_ternary_gemm_grouped([(xd, wd, si.gamma_bits(np.float16(0.02)), yd, M, N, K) for (xd, wd, sd, yd), (M, N, K) in zip(dev, specs)])
+    for (x, W, sc), (_, _, _, yd), (M, N, K) in zip(host, dev, specs):
+        sc = sc if group else np.full((1, N), 0.02, dtype=np.float16)
+        check(result(yd, M, N), x, W, sc, group or 1 << 20, f"{M}x{N}x{K} group {group}")
+
+
 # An infinite scale makes the outputs of its column infinite, with the sign of scale times the group's sum, and leaves the others alone; K that
 # ends within a unit, a slice and a pass.  A NaN or an infinity in x stays in its row.
 @pytest.mark.parametrize("M,N,K,group", [(4, 64, 448, 64), (4, 64, 4032, 32), (16, 96, 4096, 128), (3, 48, 5056, 64), (5, 64, 8256, 128), (4, 64, 1003, 64), (2, 64, 4800, 32)])
