@@ -2,8 +2,12 @@
 // Pure C++ (no HIP calls); compiled into libtl.so together with the kernels.
 #include "tl.h"
 
+#include <sched.h>
+
+#include <atomic>
 #include <cmath>
 #include <cstring>
+#include <thread>
 
 namespace {
 
@@ -54,6 +58,44 @@ inline bool has_avx2() { return __builtin_cpu_supports("avx2"); }
 uint64_t pack_words_avx2(const int8_t* row, uint32_t* dst, int64_t whole) { return pack_words(row, dst, whole); }
 inline bool has_avx2() { return false; }
 #endif
+
+// CPUs this process may run on
+inline int cpus() {
+    cpu_set_t set;
+    return sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1;
+}
+
+// The packers' rows 0 .. N - 1, in pieces that threads take as they come: rows(n0, n1) packs some and returns nonzero for a value that is no
+// weight.  A thread for every `share` weights, what one packs in about 50 us, a few times what it costs to start it; at most 8.  They end before
+// the call returns; where one cannot be started the others do its work.  One thread and up to 8 on a server, us: 4096 x 4096 to 2-bit words 764
+// and 206, to the 1.6-bit codes 2789 and 553, 4625 and 708; 1024 x 1024 50 and 51, 186 and 84, 299 and 105; 512 x 512 runs in one.
+template <class Rows>
+unsigned over_rows(int64_t N, int64_t K, double share, const Rows& rows) {
+    constexpr int kMost = 8;
+    const double want = static_cast<double>(N) * static_cast<double>(K) / share;
+    int threads = want < kMost ? static_cast<int>(want) : kMost;
+    if (threads > N) threads = static_cast<int>(N);
+    if (threads >= 2 && threads > cpus()) threads = cpus();
+    if (threads < 2) return rows(int64_t(0), N);
+    const int64_t piece = ceil_div(N, int64_t(4) * threads);
+    std::atomic<int64_t> next{0};
+    std::atomic<unsigned> bad{0};
+    auto work = [&] {
+        unsigned b = 0;
+        for (int64_t n0 = next.fetch_add(piece); n0 < N; n0 = next.fetch_add(piece)) b |= rows(n0, n0 + piece < N ? n0 + piece : N);
+        bad |= b;
+    };
+    std::thread others[kMost - 1];
+    int started = 0;
+    try {
+        for (; started < threads - 1; ++started) others[started] = std::thread(work);
+    } catch (...) {
+    }
+    work();
+    for (int i = 0; i < started; ++i) others[i].join();
+    return bad;
+}
+constexpr double kShare2Bit = 1e6, kShare1p6 = 1.5e5;
 
 // Base-3 byte -> its five digits, least significant first (digits of v mod 243 for v > 242).
 struct Base3Table {
@@ -163,25 +205,28 @@ tl_status tl_pack_2bit(const int8_t* W, int64_t N, int64_t K, uint32_t* out) {
     if (!shape_ok(N, K)) return TL_ERR_SHAPE;
     const int64_t words = ceil_div(K, 16);
     const bool avx2 = has_avx2();
-    unsigned bad = 0;
-    for (int64_t n = 0; n < N; ++n) {
-        const int8_t* row = W + n * K;
-        uint32_t* dst = out + n * words;
-        const int64_t whole = K / 16;
-        bad |= ((avx2 ? pack_words_avx2(row, dst, whole) : pack_words_any(row, dst, whole)) != 0);
-        for (int64_t i = whole; i < words; ++i) {
-            const int64_t base = 16 * i;
-            const int len = static_cast<int>(K - base < 16 ? K - base : 16);
-            uint32_t word = 0;
-            for (int j = 15; j >= 0; --j) {
-                const unsigned dgt = (j < len) ? digit_of(row[base + j]) : 1u;
-                bad |= (dgt > 2u);
-                word = (word << 2) | (dgt & 3u);
+    const unsigned any_bad = over_rows(N, K, kShare2Bit, [=](int64_t n0, int64_t n1) {
+        unsigned bad = 0;
+        for (int64_t n = n0; n < n1; ++n) {
+            const int8_t* row = W + n * K;
+            uint32_t* dst = out + n * words;
+            const int64_t whole = K / 16;
+            bad |= ((avx2 ? pack_words_avx2(row, dst, whole) : pack_words_any(row, dst, whole)) != 0);
+            for (int64_t i = whole; i < words; ++i) {
+                const int64_t base = 16 * i;
+                const int len = static_cast<int>(K - base < 16 ? K - base : 16);
+                uint32_t word = 0;
+                for (int j = 15; j >= 0; --j) {
+                    const unsigned dgt = (j < len) ? digit_of(row[base + j]) : 1u;
+                    bad |= (dgt > 2u);
+                    word = (word << 2) | (dgt & 3u);
+                }
+                dst[i] = word;
             }
-            dst[i] = word;
         }
-    }
-    return bad ? TL_ERR_VALUE : TL_OK;
+        return bad;
+    });
+    return any_bad ? TL_ERR_VALUE : TL_OK;
 }
 
 // Plain base-3 byte, digit i of the byte = weight 5b+i (Horner from the top digit).
@@ -190,34 +235,37 @@ tl_status tl_pack_1p6bit(const int8_t* W, int64_t N, int64_t K, uint8_t* out) {
     if (!shape_ok(N, K)) return TL_ERR_SHAPE;
     const int64_t stride = static_cast<int64_t>(tl_row_stride_bytes(TL_FMT_1P6BIT, K));
     const int64_t nbytes = ceil_div(K, kTritsPerByte);
-    unsigned bad = 0;
-    for (int64_t n = 0; n < N; ++n) {
-        const int8_t* row = W + n * K;
-        uint8_t* dst = out + n * stride;
-        // bytes whose weights are followed by three more: five digits of an 8-byte load, gathered by one product
-        // (each byte of it up to the fifth is a sum of digits times distinct powers of 3, below 256: no carries)
-        constexpr uint64_t kGather = (1ull << 32) | (3ull << 24) | (9ull << 16) | (27ull << 8) | 81ull;
-        uint64_t off = 0;
-        const int64_t whole = K >= 8 ? (K - 8) / kTritsPerByte + 1 : 0;
-        for (int64_t b = 0; b < whole; ++b) {
-            const uint64_t d = digits8(load8(row + kTritsPerByte * b)) & 0xFFFFFFFFFFull;
-            off |= not_digits(d);
-            dst[b] = static_cast<uint8_t>((d * kGather) >> 32);
-        }
-        bad |= (off != 0);
-        for (int64_t b = whole; b < nbytes; ++b) {
-            const int64_t base = kTritsPerByte * b;
-            unsigned v = 0;
-            for (int i = kTritsPerByte - 1; i >= 0; --i) {
-                const unsigned dgt = (base + i < K) ? digit_of(row[base + i]) : 1u;
-                bad |= (dgt > 2u);
-                v = v * 3u + (dgt > 2u ? 0u : dgt);
+    const unsigned any_bad = over_rows(N, K, kShare1p6, [=](int64_t n0, int64_t n1) {
+        unsigned bad = 0;
+        for (int64_t n = n0; n < n1; ++n) {
+            const int8_t* row = W + n * K;
+            uint8_t* dst = out + n * stride;
+            // bytes whose weights are followed by three more: five digits of an 8-byte load, gathered by one product
+            // (each byte of it up to the fifth is a sum of digits times distinct powers of 3, below 256: no carries)
+            constexpr uint64_t kGather = (1ull << 32) | (3ull << 24) | (9ull << 16) | (27ull << 8) | 81ull;
+            uint64_t off = 0;
+            const int64_t whole = K >= 8 ? (K - 8) / kTritsPerByte + 1 : 0;
+            for (int64_t b = 0; b < whole; ++b) {
+                const uint64_t d = digits8(load8(row + kTritsPerByte * b)) & 0xFFFFFFFFFFull;
+                off |= not_digits(d);
+                dst[b] = static_cast<uint8_t>((d * kGather) >> 32);
             }
-            dst[b] = static_cast<uint8_t>(v);
+            bad |= (off != 0);
+            for (int64_t b = whole; b < nbytes; ++b) {
+                const int64_t base = kTritsPerByte * b;
+                unsigned v = 0;
+                for (int i = kTritsPerByte - 1; i >= 0; --i) {
+                    const unsigned dgt = (base + i < K) ? digit_of(row[base + i]) : 1u;
+                    bad |= (dgt > 2u);
+                    v = v * 3u + (dgt > 2u ? 0u : dgt);
+                }
+                dst[b] = static_cast<uint8_t>(v);
+            }
+            std::memset(dst + nbytes, 0, static_cast<size_t>(stride - nbytes));
         }
-        std::memset(dst + nbytes, 0, static_cast<size_t>(stride - nbytes));
-    }
-    return bad ? TL_ERR_VALUE : TL_OK;
+        return bad;
+    });
+    return any_bad ? TL_ERR_VALUE : TL_OK;
 }
 
 // Sec. 3.2 / App. E with k = 5, p = 8: digits big-endian, byte = floor((256 Nval + 242) / 243).
@@ -226,34 +274,37 @@ tl_status tl_pack_1p6bit_fx(const int8_t* W, int64_t N, int64_t K, uint8_t* out)
     if (!shape_ok(N, K)) return TL_ERR_SHAPE;
     const int64_t stride = static_cast<int64_t>(tl_row_stride_bytes(TL_FMT_1P6BIT, K));
     const int64_t nbytes = ceil_div(K, kTritsPerByte);
-    unsigned bad = 0;
-    for (int64_t n = 0; n < N; ++n) {
-        const int8_t* row = W + n * K;
-        uint8_t* dst = out + n * stride;
-        // as in tl_pack_1p6bit, the powers of 3 the other way round
-        constexpr uint64_t kGather = (81ull << 32) | (27ull << 24) | (9ull << 16) | (3ull << 8) | 1ull;
-        uint64_t off = 0;
-        const int64_t whole = K >= 8 ? (K - 8) / kTritsPerByte + 1 : 0;
-        for (int64_t b = 0; b < whole; ++b) {
-            const uint64_t d = digits8(load8(row + kTritsPerByte * b)) & 0xFFFFFFFFFFull;
-            off |= not_digits(d);
-            const uint32_t nval = static_cast<uint32_t>((d * kGather) >> 32) & 255u;
-            dst[b] = static_cast<uint8_t>((nval * 256u + 242u) / 243u);
-        }
-        bad |= (off != 0);
-        for (int64_t b = whole; b < nbytes; ++b) {
-            const int64_t base = kTritsPerByte * b;
-            unsigned nval = 0;
-            for (int j = 0; j < kTritsPerByte; ++j) {
-                const unsigned dgt = (base + j < K) ? digit_of(row[base + j]) : 1u;
-                bad |= (dgt > 2u);
-                nval = nval * 3u + (dgt > 2u ? 0u : dgt);
+    const unsigned any_bad = over_rows(N, K, kShare1p6, [=](int64_t n0, int64_t n1) {
+        unsigned bad = 0;
+        for (int64_t n = n0; n < n1; ++n) {
+            const int8_t* row = W + n * K;
+            uint8_t* dst = out + n * stride;
+            // as in tl_pack_1p6bit, the powers of 3 the other way round
+            constexpr uint64_t kGather = (81ull << 32) | (27ull << 24) | (9ull << 16) | (3ull << 8) | 1ull;
+            uint64_t off = 0;
+            const int64_t whole = K >= 8 ? (K - 8) / kTritsPerByte + 1 : 0;
+            for (int64_t b = 0; b < whole; ++b) {
+                const uint64_t d = digits8(load8(row + kTritsPerByte * b)) & 0xFFFFFFFFFFull;
+                off |= not_digits(d);
+                const uint32_t nval = static_cast<uint32_t>((d * kGather) >> 32) & 255u;
+                dst[b] = static_cast<uint8_t>((nval * 256u + 242u) / 243u);
             }
-            dst[b] = static_cast<uint8_t>((nval * 256u + 242u) / 243u);
+            bad |= (off != 0);
+            for (int64_t b = whole; b < nbytes; ++b) {
+                const int64_t base = kTritsPerByte * b;
+                unsigned nval = 0;
+                for (int j = 0; j < kTritsPerByte; ++j) {
+                    const unsigned dgt = (base + j < K) ? digit_of(row[base + j]) : 1u;
+                    bad |= (dgt > 2u);
+                    nval = nval * 3u + (dgt > 2u ? 0u : dgt);
+                }
+                dst[b] = static_cast<uint8_t>((nval * 256u + 242u) / 243u);
+            }
+            std::memset(dst + nbytes, 0, static_cast<size_t>(stride - nbytes));
         }
-        std::memset(dst + nbytes, 0, static_cast<size_t>(stride - nbytes));
-    }
-    return bad ? TL_ERR_VALUE : TL_OK;
+        return bad;
+    });
+    return any_bad ? TL_ERR_VALUE : TL_OK;
 }
 
 // Decode of the fixed-point code: b = ceil(256 V / 243) is inverted by V = floor(243 b / 256),
