@@ -66,11 +66,24 @@ inline double small_m_time(int64_t M, int64_t N, int64_t K)
     return 1.7 + 3.2 * p + 0.06 * b + 0.166 * double(s) * b * t / 256.0;
 }
 
+// The same for a call that is one launch of the lean kernel (gemv_rows_form): b blocks of 16 rows, w workgroups and xt tiles to a CU (as in launch_lean_rows).
+// Fitted to 860 calls over M = 17 .. 2048, N = 512 .. 16384, K = 512 .. 2048 with every alternative timed, weights out of the caches; of those the one
+// chosen is 0.6 % slower than the best on average (before that launch was there 1.8 % slower than the best of the others).
+inline double rows_form_time(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t s = (K + 511) / 512, tiles = N / 16, b = (M + 15) / 16;
+    int64_t share = 256 * (8 / s) / b;
+    if (share < 1) share = 1;
+    const int64_t groups = tiles < share ? tiles : share;
+    const double w = double((groups * b + 255) / 256), xt = double((tiles + groups - 1) / groups) * w;
+    constexpr double per_tile[5] = {0, 0.141, 0.21, 0.343, 0.385};
+    return 3.86 + 0.048 * double(s) * w + per_tile[s] * xt;
+}
+
 // Small-M kernel or tiled matrix-core kernel, when both can run the shape.  A band rather than the bare comparison decides, since machines
 // differ by several percent (the same library: 18.3 and 19.6 us for the same launch): beyond 16 rows the small-M kernel keeps a shape
-// unless the models put the tiled kernel ahead by more than 7 %.  Over the calls of the fit (made before the tiled kernel's present decode,
-// with which it is 1 to 5 % faster than modelled) the one chosen is 0.5 % slower than the best on
-// average and 12 % in one of a hundred; with the constants before 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
+// unless the models put the tiled kernel ahead by more than 7 %.  Over 1740 calls of K beyond 2048 the one chosen is 1.3 % slower than the best on
+// average and 20 % in one of a hundred; with the constants before these fits 4.6 to 6.5 % and a factor of 2 (14701 x 2304 at M = 1295 141 us for 93).
 inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
 {
     if (K % 64 != 0) return tile_ragged_choice(M, N, K);
@@ -83,8 +96,16 @@ inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
     else if (!two_blocks && double((M + 15) / 16) * double((N + 15) / 16) >= 512.0) c.launch = 4.5;
     c.launches = double((M + (two_blocks ? 31 : 15)) / (two_blocks ? 32 : 16)) / 32.0;
     c.fixed = c.launch * (c.launches > 1.0 ? double(int64_t(c.launches + 0.999)) : 1.0);
+    if (gemv_rows_form(M, N, K)) {
+        // a call of its own; in a shared launch it costs what it did: its part of one, and the rest of its time there
+        const double shared = c.stream - c.fixed + c.launch * c.launches;
+        c.stream = rows_form_time(M, N, K);
+        c.fixed = 3.0;
+        c.launches = shared > c.stream - c.fixed ? (shared - (c.stream - c.fixed)) / c.launch : 0.0;
+    }
     c.tiled = c.stream;
-    if (1.07 * mfma_at_least(K) <= c.stream) c.tiled = 1.07 * mfma_time(M, N, K);
+    const double band = gemv_rows_form(M, N, K) ? 1.03 : 1.07;       // (the one launch's time is the better known)
+    if (band * mfma_at_least(K) <= c.stream) c.tiled = band * mfma_time(M, N, K);
     return c;
 }
 

@@ -1811,14 +1811,12 @@ hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept
 {
     auto with = [&](auto tag) {
         constexpr int GS = decltype(tag)::value;
-        if constexpr (!std::is_same<Args, LeanJobs>::value)
+        if constexpr (!std::is_same<Args, LeanJobs>::value && !(std::is_same<Args, LeanAny>::value && GS == 0 && !ANY))   // which are one pass over K
             if (kept) return launch_lean_args<true, GS, ANY>(args, grid, NW, T, kept, s);
         return launch_lean_args<false, GS, ANY>(args, grid, NW, T, 0, s);
     };
     switch (gs) {
-        case 0:
-            if constexpr (ANY || !std::is_same<Args, LeanAny>::value) return with(std::integral_constant<int, 0>{});
-            else return hipErrorInvalidValue;
+        case 0: return with(std::integral_constant<int, 0>{});
         case 32: return with(std::integral_constant<int, 32>{});
         case 64: return with(std::integral_constant<int, 64>{});
         case 128: return with(std::integral_constant<int, 128>{});
@@ -1937,7 +1935,7 @@ hipError_t launch_longk_args(const Args& args, dim3 grid, int T, int rows, hipSt
 }
 
 // One product: a set of workgroups for every block of 16 rows (blockIdx.y), as many in all as the CUs hold with 8 waves each.
-// any: of any K and N; else K is a multiple of 64, N of 16, and there are scales.
+// any: of any K and N; else K is a multiple of 64 and N of 16, and there are scales or K is one pass.
 hipError_t launch_lean_rows(const __half* x, const uint32_t* W, float gamma, const __half* scales, uint32_t group_inv, __half* y,
                             int64_t M, int64_t N, int64_t K, int gs, bool any, hipStream_t s)
 {
@@ -2219,6 +2217,7 @@ hipError_t gemv_init()
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS, false>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS, false>(T)), true);
             typedef typename std::conditional<GS == 0, LeanOne, LeanAny>::type Alone;
+            if constexpr (GS == 0) raise_one(reinterpret_cast<const void*>(pick_lean<LeanAny, false, 0, false>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<Alone, false, GS, false>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<Alone, true, GS, false>(T)), true);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs, false, GS, false>(T)), false);
@@ -2347,6 +2346,10 @@ hipError_t launch_gemv_jobs(const GemmDesc* jobs, int count, hipStream_t s)
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
+    }
+    if (count == 1 && gemv_rows_form(jobs[0].M, jobs[0].N, jobs[0].K)) {
+        const GemmDesc& d = jobs[0];
+        return launch_lean_rows(d.x, d.W, d.gamma, nullptr, 0, d.y, d.M, d.N, d.K, 0, false, s);
     }
     if (g_policy.longk) {
         hipError_t e = hipSuccess;

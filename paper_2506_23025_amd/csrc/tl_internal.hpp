@@ -65,6 +65,14 @@ inline bool gemv_two_blocks(int64_t M, int64_t N, int64_t K)
            (M >= 256 && w_bytes >= (int64_t(2) << 20));
 }
 
+// Whether a call of more than 16 rows is one launch of the lean kernel, blocks of 16 rows in the grid's second dimension: up to K = 2048, where blocks of
+// 32 rows and launches of 32 blocks take 1.06 times as long on average (M = 17 .. 512; beyond, 1.37 times), in none of 860 calls much less.  Of longer K
+// some calls win and some lose by as much (14336 x 4096 at M = 48 12.0 -> 13.8 us).
+inline bool gemv_rows_form(int64_t M, int64_t N, int64_t K)
+{
+    return M > 16 && M <= 4096 && K % 64 == 0 && K >= 64 && K <= 2048 && N % 16 == 0 && N <= (int64_t(1) << 24);
+}
+
 // Its forms for any K and N: launch_gemv and launch_gemv_jobs take these too (64 <= K <= 32768, M <= 4096).
 bool gemv_any_supports(int64_t M, int64_t N, int64_t K);
 

@@ -82,3 +82,15 @@ def test_the_forced_path_still_refuses_it():
         with pytest.raises(RuntimeError):
             tl.tl_ternary_gemm_path(xd, wd, si.gamma_bits(g), yd, 2, 64, 100, path=path)
     assert tl.tl_ternary_gemm_which(2, 64, 100) == tl.TL_PATH_GENERIC
+
+
+# K a multiple of 64 up to 2048 and more than 16 rows: one launch with the blocks of rows in the grid's second dimension.  One wave to four per
+# workgroup, a last block of one row, several tiles per workgroup, the most blocks that a launch has
+@pytest.mark.parametrize("M,N,K", [(17, 16, 64), (33, 48, 512), (64, 2048, 1024), (37, 4096, 2048), (100, 1040, 1600), (20, 14336, 2048), (300, 528, 512), (47, 2064, 1472), (4096, 16, 64)])
+def test_blocks_of_rows_in_one_launch(M, N, K):
+    x, W, g = si.layer(49000 + M + N + K, M, N, K)
+    yd = to_dev(np.full(M * N + 64, -21555, dtype=np.int16))
+    tl.tl_ternary_gemm_path(to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), si.gamma_bits(g), yd, M, N, K, path=tl.TL_PATH_GEMV)
+    y = yd.cpu().numpy()
+    assert (y[M * N:] == -21555).all()
+    check(y[:M * N].view(np.float16).reshape(M, N), x, W, g, f"{M}x{N}x{K}")
