@@ -227,11 +227,10 @@ tl_status tl_ternary_gemm_1p6_fx(const void* x, const void* Wpacked, uint16_t ga
  * format), y, stream, accumulation and rounding as for tl_ternary_gemm.  `group` must be a
  * multiple of 16 (TL_ERR_SHAPE otherwise).  Scales are expected to be finite: an infinite one makes
  * the outputs of its column infinite or NaN, a NaN makes them NaN, and neither shows in another column.
- * K % 64 == 0: few activation
- * rows, group % 128 == 0 and N % 4 == 0 in the weight-streaming small-M kernel (M in blocks of 16
- * rows; multiples of 256 a little faster than odd multiples of 128), the rest in the tiled kernel,
- * except where so few rows make the generic kernel the faster one; other K likewise in the tiled or
- * the generic kernel.
+ * Few activation rows, N % 4 == 0 and group % 64 == 0, or % 32 where K % 64 == 0, run in the
+ * weight-streaming small-M kernel (M in blocks of 16 rows; the larger the power of two in `group`, up to
+ * 256, the faster), the rest in the tiled kernel, except where so few rows make the generic kernel the
+ * faster one.
  * Nothing is allocated; the call is asynchronous on `stream`.
  */
 tl_status tl_ternary_gemm_gs(const void* x, const void* Wpacked, const void* scales, int64_t group,
@@ -255,8 +254,8 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
 /*
  * tl_ternary_gemm_gs_grouped: 2-bit weights with per-group scales (Sec. 3.3; App. G), one group
  * size per job.  Jobs that tl_ternary_gemm_gs would run in the weight-streaming kernel share
- * launches (groups that are multiples of 256 weights among themselves, odd multiples of 128
- * among themselves); the others run one by one.
+ * launches (groups that are multiples of 256 weights among themselves, and so other multiples of 128, of
+ * 64 and of 32); the others run one by one.
  */
 typedef struct tl_gemm_gs_job {
     const void* x;            /* device, fp16 [M][K]                         */

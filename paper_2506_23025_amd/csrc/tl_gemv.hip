@@ -35,7 +35,8 @@
 //    activations are staged once and only weights move afterwards.  The lean form
 //    (gemv_lean_kernel) is the stream form cut down to the decode shapes (K the same number of
 //    slices in every job or, in a second copy, several passes over K; one block of 16 rows, one
-//    gamma or scales of groups of 256s, N a multiple of 16) and is what those launches run.  The
+//    gamma, N a multiple of 16) and is what those launches run; its further copies take group
+//    scales, any K and N, and many rows of short K.  The
 //    long-K form (gemv_longk_kernel) takes lone calls with 4096 < K <= 16384 whose workgroups
 //    get one or two tiles each: a wave walks its up to four slices with the next one's data
 //    already in flight.  The general form (gemv_kernel) loops a wave over slices and a
@@ -786,7 +787,7 @@ gemv_stream_kernel(GemvBatch b)
 // ------------------------------------------------------------------------------------------
 // Lean stream kernel: the stream form for launches in which every job has as many 512-weight
 // slices as the workgroup has waves, or (PASSES) more, one block of at most 16 activation
-// rows, one gamma or (GS) scales for groups of 256s, and N a multiple of 16 -- the decode shapes.  What differs from
+// rows, one gamma or (GS) group scales, and N a multiple of 16 -- the decode shapes.  What differs from
 // gemv_stream_kernel is the way in and the loop, not the arithmetic:
 //  * Every workgroup has a 64-byte record of its own in the kernel arguments (pointers of its job,
 //    first tile and length of its run), read with one scalar load at an address that depends on
@@ -981,17 +982,21 @@ __device__ __forceinline__ void store_quad_any(__attribute__((address_space(1)))
 // with the thread that owns the output quad.  The last item of a pass asks for the next pass's first weights; the
 // activations follow once every wave has left the sums of that item, which share LDS with them.  Waves past the last
 // slice take no part in the last pass but for the exchange (multiplying zeros instead, 7936 x 5248 at M = 18, two slices in the last of
-// two passes, took 12.5 us and the general form 11.1; now 11.3; 65 rows of 11648 x 4480 25.3, 23.6 and 22.3); GS multiplies zeros.
-// GS: group scales, groups of whole units of 256 weights (half a slice).  The halves of a tile are summed one after the
+// two passes, took 12.5 us and the general form 11.1; now 11.3; 65 rows of 11648 x 4480 25.3, 23.6 and 22.3).
+// GS = 256: group scales, groups of whole units of 256 weights (half a slice).  The halves of a tile are summed one after the
 // other in the same accumulators, each scaled by its group's scales of the lane's four output rows, which are
-// requested with the tile's weights.  Against the general form, groups of 256: block at M = 1 / 4 / 16 16.0 / 17.2 / 24.5 ->
-// 15.8 / 16.6 / 19.5 us, its jobs of one pass 11.7 / 12.3 / 13.7 -> 10.4 / 10.7 / 12.1, 4096 x 11008 alone 8.8 / 10.3 / 15.1 -> 7.7 / 8.2 / 10.9.
+// requested with the tile's weights (block at M = 1 / 4 / 16 15.0 / 15.5 / 18.0 us).
+// GS = 128, 64, 32: groups of multiples of as many.  In the order above a product's 32 weights come from four chunks of 64, so a unit's sum
+// would never stand alone in an accumulator; here a lane takes a word of every chunk (32: half a word), and 64 (32) weights are two products (one).
+// What bounds them is the scaling of every unit's sum on the vector ALU, 4 operations for 16 x 16 outputs beside the 11 (32: 13) of the decode per
+// product pair (product): block at M = 4 15.6 / 18.5 / 24.5 us with groups of 128 / 64 / 32, decode sweep 21.5 / 24.6 / 36.2.  Groups of 128 took
+// 25.8 and 36.5 in the general form, every product issued twice with other lanes masked off; the others went to the tiled kernel one by one, 68
+// and 131 us.
 // ANY: any K from 64 on and any N (GS: N a multiple of 4), jobs with fewer slices than waves among them.  Packed rows then start at multiples of 4
 // bytes, rows of x and y at any even address.  A row's last 16-byte chunk of weights is its last 16 bytes, wherever they start: no
 // request leaves the row, and what overlaps the chunk before meets zeros.  The activations come through registers.  Calls with K no multiple of 64
 // ran in the tiled kernel's form for those: up to 4 rows of 512 .. 16384 x 64 .. 14336 weights this one is 1.8 times as fast on average
 // (666 calls, none slower), 4099 x 4090 at M = 1 / 16 / 37 8.0 / 8.3 / 10.7 -> 4.3 / 5.7 / 6.8 us.
-// GS below 256: see fine_tile.
 template <int T, bool PASSES, int GS, bool ANY, class Args>
 __global__ void __launch_bounds__(512)
 gemv_lean_kernel(Args b)
@@ -1024,10 +1029,10 @@ gemv_lean_kernel(Args b)
     auto stage_x = [&](int slice) {
         int l = lane;
         if constexpr (PASSES) asm volatile("" : "+v"(l));  // see exchange
-        const uint32_t lane16 = uint32_t(l) << 4;
         const size_t row_stride = size_t(K) * 2;
         gbytes src = (gbytes)(R.x + size_t(slice) * (kSliceK * 2));
         if ((slice + 1) * kSliceK <= K) {                   // the whole slice lies inside K
+            const uint32_t lane16 = uint32_t(l) << 4;
 #pragma unroll 1
             for (int r = 0; r < rows; ++r) {
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (lane16 ^ (uint32_t(r & 7) << 4))),
@@ -1042,7 +1047,7 @@ gemv_lean_kernel(Args b)
                     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + uint32_t(kk) * 2u),
                                                      (__attribute__((address_space(3))) void*)(my_lds + r * 1024), 16, 0, 0);
                 } else {
-                    *reinterpret_cast<u32x4*>(my_lds + r * 1024 + lane16) = u32x4{0u, 0u, 0u, 0u};
+                    *reinterpret_cast<u32x4*>(my_lds + r * 1024 + (uint32_t(l) << 4)) = u32x4{0u, 0u, 0u, 0u};
                 }
                 src += row_stride;
             }
@@ -1781,7 +1786,7 @@ LeanFn<Args> pick_lean(int T)
     switch (T) {
         case 1: return gemv_lean_kernel<1, PASSES, GS, ANY, Args>;
         case 2: return gemv_lean_kernel<2, PASSES, GS, ANY, Args>;
-        default: return gemv_lean_kernel<3, PASSES, GS, ANY, Args>;
+        default: return gemv_lean_kernel<PASSES && GS == 64 ? 2 : 3, PASSES, GS, ANY, Args>;   // see lean_passes_tiles
     }
 }
 
