@@ -85,10 +85,19 @@ static double stream_gs_time(int64_t M, int64_t N, int64_t K, int64_t group)
     return K % 64 != 0 ? 1.1 * t + 0.35 : t;
 }
 
+// What the plain kernel on the vector ALUs takes (us) for up to 4 rows: chunks of 1024 weights, of which a part costs as much as a whole one, in as many
+// rounds as there are 200 workgroups of 16 columns; one or two columns leave wavefronts out.
+static double plain_gs_time(int64_t M, int64_t N, int64_t K)
+{
+    const double chunks = double((K + 1023) / 1024), groups = double((N + 15) / 16);
+    return 2.6 + chunks * (N <= 2 ? 1.2 + 0.3 * double(M) : 2.5) * (groups > 200.0 ? groups / 200.0 : 1.0);
+}
+
 // Tiled kernel or what would take the call without it: the weight-streaming kernel, which up to 16 rows was the fastest in all calls of the fit but a
-// few of groups of 64s and 32s (by up to 7 and 15 %), or, for other groups, the plain kernel on the
-// vector ALUs, 3 + K / 4096 (6.5 + 1.25 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (us; 4096 -> 4096: M = 1
-// 11.3, M = 4 14.6, M = 16 29.8, M = 37 45.8).
+// few of groups of 64s and 32s (by up to 7 and 15 %), or, for other groups and N, the plain kernel.  That one wins in calls of up to 4 rows alone (in none
+// of 1050 calls of more; in 51 of 350 others, 1 x 1 x 5344 17.7 us tiled and 11.5, 2 x 64 x 960 5.8 and 5.2), where the tiled kernel takes 0.9 us
+// less than the fit of larger calls says.  Over those 1400 calls of M = 1 .. 8192, N = 1 .. 16384, K = 16 .. 14336 the one chosen is 0.4 % slower than
+// the best on average and 15 % in one of a hundred.
 bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
 {
     const bool streams = gemv_gs_supports(M, N, K, group);
@@ -97,10 +106,10 @@ bool tile_gs_preferred(int64_t M, int64_t N, int64_t K, int64_t group)
         const KernelChoice c = tile_gs_choice(M, N, K, group);
         return c.tiled < c.stream;
     }
+    if (M > 4) return true;
     double us;
     pick(M, N, K, group, &us);
-    const double groups = double((M + 15) / 16) * double((N + 15) / 16) / 512.0;
-    return us < 3.0 + double(K) / 4096.0 * (6.5 + 1.25 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
+    return us - 0.9 < plain_gs_time(M, N, K);
 }
 
 KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group)

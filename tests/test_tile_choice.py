@@ -98,6 +98,16 @@ def test_short_k_of_one_point_six_bit_codes():
         assert instance(ONE_POINT_SIX, M, N, K) >= 0, (M, N, K)
 
 
+def test_scales_that_do_not_stream():
+    # measured (us), plain / tiled: groups or N that the streaming kernel does not take, short K and many rows above all, whose chunks of 1024 weights cost the plain
+    # kernel as much as whole ones; and the other way round one or two rows of few columns
+    for M, N, K, group in ((3, 12363, 1088, 32), (1566, 433, 85, 16), (5042, 209, 64, 256), (52, 4032, 128, 80), (730, 261, 192, 256), (229, 320, 384, 16),   # 19.8 / 6.9, 57 / 5.1, 80 / 5.4, 19 / 3.4, 20 / 3.9, 12 / 4.3
+                           (490, 9, 384, 16), (5, 695, 1344, 384), (3, 1721, 2304, 64), (3, 8003, 2496, 128), (6, 6, 1088, 32), (2, 64, 16, 80)):            # 9.4 / 4.2, 10.4 / 6.8, 12.0 / 8.2, 15.6 / 9.7, 9.6 / 6.0, 5.3 / 3.2
+        assert instance(SCALES, M, N, K, group) >= 0, (M, N, K, group)
+    for M, N, K, group in ((1, 1, 5344, 128), (2, 2, 13292, 16), (2, 4, 3041, 48), (1, 22, 1888, 256)):                                                      # 11.5 / 17.7, 27 / 39, 9.4 / 12.1, 6.7 / 8.2
+        assert instance(SCALES, M, N, K, group) == -1, (M, N, K, group)
+
+
 def test_workgroups_of_the_streaming_kernel_fit_on_a_compute_unit():
     # 160 KB of LDS in units of 1280 bytes, at most 16 waves; a wave's area (16 rows of 656 bytes) and the table of 2 KB
     fn = tl.raw().tl_internal_stream3_per_cu
