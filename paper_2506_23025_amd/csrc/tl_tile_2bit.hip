@@ -68,17 +68,12 @@ int pick_ragged(int64_t M, int64_t N, int64_t K, double* us)
 
 }  // namespace
 
-// Where the streaming kernel cannot run (K below 64, more than 4096 rows): tiled kernel or the plain kernel on the vector ALUs, which takes (us) 2.8 + K / 4096
-// (5.6 + 1.6 per row, up to 16) for every 512 workgroups of 16 x 16 outputs (4090 -> 4099: M = 1 9.6, M = 4 13.0, M = 16
-// 32.3, M = 37 52.8; 1000 -> 1024: M = 1 4.4, M = 16 8.9).  The tiled kernel on the same: 7.4, 7.4, 7.7, 10.8; 4.4, 4.5.
+// Where the streaming kernel cannot run (K below 64, more than 4096 rows): in none of 249 calls of K = 8 .. 63, M = 1 .. 20000 and of longer K, M = 4097 .. 20000, over
+// N = 1 .. 16384, was the plain kernel on the vector ALUs ahead (at K = 8 .. 63 it takes 1.25 to 1.5 times as long up to 4 rows, 2 to 16 times
+// beyond): what it pays for is whole chunks of 1024 weights.
 bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K)
 {
-    if (K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return false;
-    const double groups = double((M + 15) / 16) * double((N + 15) / 16) / 512.0;
-    const double plain = 2.8 + double(K) / 4096.0 * (5.6 + 1.6 * double(M < 16 ? M : 16)) * (groups > 1.0 ? groups : 1.0);
-    double us;
-    pick_ragged(M, N, K, &us);
-    return us < plain;
+    return K >= 8 && K <= (int64_t(1) << 24) && M <= (int64_t(1) << 24) && N <= (int64_t(1) << 24);
 }
 
 // What the weight-streaming kernel takes (us) for K that is no multiple of 64: m rows of a block, b blocks of 16, s slices of 512 weights; w workgroups

@@ -108,6 +108,13 @@ def test_scales_that_do_not_stream():
         assert instance(SCALES, M, N, K, group) == -1, (M, N, K, group)
 
 
+def test_two_bit_words_that_do_not_stream():
+    # measured (us), plain / tiled: K below 64 or more than 4096 rows: 42 / 5.2, 18 / 4.9, 16 / 4.5, 183 / 11.4, 388 / 25
+    for M, N, K in ((19384, 25, 84), (8760, 3, 235), (8496, 1, 308), (1844, 1406, 51), (13509, 179, 1427), (1, 16, 8), (4, 20, 63)):
+        assert instance(TWO_BIT, M, N, K) >= RAGGED, (M, N, K)
+    assert instance(TWO_BIT, 4, 20, 7) == -1               # K of less than a piece
+
+
 def test_workgroups_of_the_streaming_kernel_fit_on_a_compute_unit():
     # 160 KB of LDS in units of 1280 bytes, at most 16 waves; a wave's area (16 rows of 656 bytes) and the table of 2 KB
     fn = tl.raw().tl_internal_stream3_per_cu
