@@ -2459,9 +2459,8 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
         GemvJob j{};
         j.scales = d.scales;
         j.hpg = units_per_group(d.K, d.group, kind);
-        constexpr int64_t kAtOnce = 4096;                  // rows of a launch, which bounds its grid
-        for (int64_t m0 = 0; m0 < d.M; m0 += kAtOnce) {
-            const hipError_t e = launch_lean_rows(d.x + m0 * d.K, d.W, 1.f, d.scales, group_inverse(j), d.y + m0 * d.N, d.M - m0 < kAtOnce ? d.M - m0 : kAtOnce,
+        for (int64_t m0 = 0; m0 < d.M; m0 += kStreamRows) {
+            const hipError_t e = launch_lean_rows(d.x + m0 * d.K, d.W, 1.f, d.scales, group_inverse(j), d.y + m0 * d.N, d.M - m0 < kStreamRows ? d.M - m0 : kStreamRows,
                                                   d.N, d.K, kind, d.K % 64 != 0 || d.N % 16 != 0, s);
             if (e != hipSuccess) return e;
         }

@@ -98,6 +98,17 @@ hipError_t launch_gemm_generic_gs(const __half* x, const uint32_t* Wp, const __h
                                   int64_t group, __half* y, int64_t M, int64_t N, int64_t K,
                                   hipStream_t s);
 
+// Most activation rows of one launch of a weight-streaming kernel for a call of its own; more rows take several launches.
+constexpr int64_t kStreamRows = 4096;
+
+// What such a call of M rows takes: time(m) for each launch of m rows.
+template <class Time>
+double over_stream_launches(int64_t M, Time&& time)
+{
+    const int64_t full = M / kStreamRows, rest = M % kStreamRows;
+    return (full ? double(full) * time(kStreamRows) : 0.0) + (rest ? time(rest) : 0.0);
+}
+
 // Weight-streaming small-M kernel for the 1.6-bit format.  Needs K >= 8.
 bool gemv3_supports(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemv3(const __half* x, const uint8_t* Wp, int64_t stride, float gamma, __half* y,

@@ -116,9 +116,9 @@ KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group)
 {
     KernelChoice c{gemv_gs_supports(M, N, K, group), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!c.streams || M <= 16) return c;
-    c.stream = stream_gs_time(M, N, K, group);
+    c.stream = over_stream_launches(M, [&](int64_t m) { return stream_gs_time(m, N, K, group); });
     c.launch = 3.2;
-    c.fixed = c.launch;                                    // of its own it is one launch, however many rows
+    c.fixed = c.launch * double((M + kStreamRows - 1) / kStreamRows);
     // In a shared launch it has a part of 256 workgroups, which for K of up to four slices leave wavefronts out: 1.15 to 1.2 times as long up
     // to 64 rows, 1.2 to 1.5 times up to 512 (250 calls both ways).
     const double blocks = double((M + 15) / 16), crowd = K > 2048 ? 0.0 : blocks > 4.0 ? 0.3 : 0.15;

@@ -115,6 +115,13 @@ def test_two_bit_words_that_do_not_stream():
     assert instance(TWO_BIT, 4, 20, 7) == -1               # K of less than a piece
 
 
+def test_scales_of_more_rows_than_one_launch_streams():
+    # measured (us), streaming, 4096 rows to a launch / tiled
+    for M, N, K, group in ((21027, 36, 192, 128), (14334, 8, 128, 256), (27651, 16, 448, 128), (18991, 64, 832, 256)):    # 27 / 6.2, 15 / 3.9, 28 / 7.6, 33 / 9.5
+        assert instance(SCALES, M, N, K, group) >= 0, (M, N, K, group)
+    assert instance(SCALES, 1311, 832, 512, 256) == -1
+
+
 def test_workgroups_of_the_streaming_kernel_fit_on_a_compute_unit():
     # 160 KB of LDS in units of 1280 bytes, at most 16 waves; a wave's area (16 rows of 656 bytes) and the table of 2 KB
     fn = tl.raw().tl_internal_stream3_per_cu
