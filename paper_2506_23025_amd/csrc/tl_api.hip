@@ -30,9 +30,6 @@ inline bool dims_ok(int64_t M, int64_t N, int64_t K)
 
 inline tl_status from_hip(hipError_t e) { return e == hipSuccess ? TL_OK : TL_ERR_HIP; }
 
-// Most activation rows one launch of the 1.6-bit weight-streaming kernel takes.
-constexpr int64_t kGemvMaxM = 4096;
-
 // What the small-M kernel takes (us) for more than 16 rows: t tiles of 16 output rows, b blocks of 16 or 32 activation rows, s slices of
 // 512 weights, p passes of 8 slices.  In one pass a block costs its activations and a share of every tile, which depends on s
 // alone (a workgroup has s waves, and as many more workgroups fit as 8 / s allows), not on the bytes of W.  Fitted with the
@@ -247,12 +244,12 @@ tl_status gemm_1p6(const void* x, const void* Wpacked, uint16_t gamma_fp16_bits,
     if (tl::tile3_preferred(M, N, K))
         return tl::from_hip(tl::launch_tile3(static_cast<const __half*>(x), static_cast<const uint8_t*>(Wpacked), stride,
                                              gamma, static_cast<__half*>(y), M, N, K, fx, s));
-    if (tl::gemv3_supports(M < tl::kGemvMaxM ? M : tl::kGemvMaxM, N, K)) {
-        // more rows than one launch takes: one launch per kGemvMaxM rows
+    if (tl::gemv3_supports(M < tl::kStreamRows ? M : tl::kStreamRows, N, K)) {
+        // more rows than one launch takes: one launch per kStreamRows rows
         const __half* xh = static_cast<const __half*>(x);
         __half* yh = static_cast<__half*>(y);
-        for (int64_t m0 = 0; m0 < M; m0 += tl::kGemvMaxM) {
-            const int64_t rows = M - m0 < tl::kGemvMaxM ? M - m0 : tl::kGemvMaxM;
+        for (int64_t m0 = 0; m0 < M; m0 += tl::kStreamRows) {
+            const int64_t rows = M - m0 < tl::kStreamRows ? M - m0 : tl::kStreamRows;
             const hipError_t e = tl::launch_gemv3(xh + m0 * K, static_cast<const uint8_t*>(Wpacked), stride, gamma,
                                                   yh + m0 * N, rows, N, K, fx, s);
             if (e != hipSuccess) return tl::from_hip(e);

@@ -87,9 +87,9 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
 {
     KernelChoice c{gemv3_groups(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (M <= 16 || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return c;
-    c.stream = stream3_time(M, N, K);
+    c.stream = over_stream_launches(M, [&](int64_t m) { return stream3_time(m, N, K); });
     c.launch = c.streams ? 3.8 : 0.0;
-    c.fixed = c.launch;                                    // of its own it is one launch, however many rows
+    c.fixed = c.launch * double((M + kStreamRows - 1) / kStreamRows);
     c.launches = double((M + 15) / 16) / 32.0;
     c.tiled = c.stream;
     if (K % 8 != 0) {
@@ -101,7 +101,7 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
         // Rows of x that start anywhere cost the streaming kernel 5 %, 10 with several passes, and 0.3 us.  Fitted with the three tiles' times to 1250
         // calls over M = 17 .. 2048, N = 512 .. 16384, K = 64 .. 14336; on 1250 others the one chosen is 0.18 % slower than the best and 7 % in
         // one of a hundred.
-        c.tiled = c.stream = c.stream * (c.streams ? 1.05 : 1.1) + 0.3;
+        c.tiled = c.stream = c.stream * (c.streams ? 1.05 : 1.1) + 0.3 * double((M + kStreamRows - 1) / kStreamRows);
         if (tile_at_least(kRaggedCost, kRagged, K) < c.stream) pick(M, N, K, &c.tiled);
         return c;
     }

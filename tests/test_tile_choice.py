@@ -122,6 +122,12 @@ def test_scales_of_more_rows_than_one_launch_streams():
     assert instance(SCALES, 1311, 832, 512, 256) == -1
 
 
+def test_one_point_six_bit_codes_of_more_rows_than_one_launch_streams():
+    # measured (us), streaming, 4096 rows to a launch / tiled
+    for M, N, K in ((29569, 20, 171), (14561, 37, 703), (10488, 62, 743), (24042, 62, 1251), (5936, 144, 107), (4872, 8, 354)):    # 36 / 16, 24 / 12, 21 / 12, 50 / 29, 12 / 7, 8 / 6
+        assert instance(ONE_POINT_SIX, M, N, K) >= RAGGED, (M, N, K)
+
+
 def test_workgroups_of_the_streaming_kernel_fit_on_a_compute_unit():
     # 160 KB of LDS in units of 1280 bytes, at most 16 waves; a wave's area (16 rows of 656 bytes) and the table of 2 KB
     fn = tl.raw().tl_internal_stream3_per_cu
