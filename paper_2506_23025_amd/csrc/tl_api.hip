@@ -101,7 +101,10 @@ inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
         c.launches = shared > c.stream - c.fixed ? (shared - (c.stream - c.fixed)) / c.launch : 0.0;
     }
     c.tiled = c.stream;
-    const double band = gemv_rows_form(M, N, K) ? 1.03 : 1.07;       // (the one launch's time is the better known)
+    // The one launch's time is the better known.  Below its fit, K < 512, both times are too long, the tiled kernel's the more (24 x 128 x 128 2.7 us
+    // against 3.9, the one launch 3.4 against 4.05): over 253 such calls the one chosen is 0.2 % slower than the best, 6 % in one of a
+    // hundred (with 1.03 2.2 and 23 %, with 0.9 0.4 and 11 %).
+    const double band = !gemv_rows_form(M, N, K) ? 1.07 : K < 512 ? 0.95 : 1.03;
     if (band * mfma_at_least(K) <= c.stream) c.tiled = band * mfma_time(M, N, K);
     return c;
 }

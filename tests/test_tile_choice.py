@@ -61,6 +61,15 @@ def test_two_bit_words_at_many_rows():
         assert tl.tl_ternary_gemm_which(M, N, K) == tl.TL_PATH_GEMV, (M, N, K)
 
 
+def test_two_bit_words_of_short_k_at_more_than_16_rows():
+    # measured (us), streaming / tiled: 3.40 / 2.69, 3.55 / 2.91, 4.19 / 3.49, 3.53 / 2.98, 3.64 / 3.31, 4.59 / 3.89; the other way round
+    # 3.62 / 4.25, 3.58 / 4.20
+    for M, N, K in ((24, 128, 128), (75, 576, 128), (46, 1696, 192), (81, 576, 64), (128, 768, 256), (113, 1072, 320)):
+        assert tl.tl_ternary_gemm_which(M, N, K) == tl.TL_PATH_MFMA, (M, N, K)
+    for M, N, K in ((26, 1344, 448), (66, 1024, 448)):
+        assert tl.tl_ternary_gemm_which(M, N, K) == tl.TL_PATH_GEMV, (M, N, K)
+
+
 def test_one_point_six_bit_codes_at_many_rows():
     # measured (us), streaming / best tile: narrow layers 4224 x 832 at M = 1311 25.2 / 27.5, 1024 x 64 at 2048 6.4 / 7.3; 17 to 36 rows of long
     # ones 8704 x 4260 at 18 17.9 / 22.7, 13184 x 5554 at 19 25.1 / 31.5, 6776 x 4928 at 21 15.5 / 18.4; and the other way round 4096 x 14336
