@@ -397,6 +397,12 @@ __attribute__((visibility("default"))) void tl_internal_grouped_tiled(int form, 
     for (int j = 0; j < count; ++j) out[j] = tiled[j] ? 1 : 0;
 }
 
+// Likewise: jobs_by_table.
+__attribute__((visibility("default"))) int tl_internal_jobs_by_table(int count, int one_pass, int records, int several, int64_t w_bytes, int captured)
+{
+    return tl::jobs_by_table(count, one_pass != 0, records != 0, several != 0, w_bytes, captured != 0) ? 1 : 0;
+}
+
 // Likewise: workgroups of `waves` waves that a launch of the 1.6-bit streaming kernel puts on a CU, and the LDS that one is given.
 __attribute__((visibility("default"))) int tl_internal_stream3_per_cu(int waves, int* lds) { return tl::gemv3_per_cu(waves, lds); }
 

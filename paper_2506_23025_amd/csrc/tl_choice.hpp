@@ -1,5 +1,7 @@
-// Which jobs of a grouped call go through the tiled kernel (host side; plain C++).
+// Which jobs of a grouped call go through the tiled kernel, and how a shared launch hands its jobs out (host side; plain C++).
 #pragma once
+
+#include <cstdint>
 
 namespace tl {
 
@@ -37,6 +39,20 @@ inline void choose_grouped(const KernelChoice* c, int n, bool* tiled)
     }
     if (!any || !can || all >= rest + launch * (launches > 1.0 ? launches : 1.0)) return;
     for (int j = 0; j < n; ++j) tiled[j] = c[j].streams;
+}
+
+// How the workgroups of a shared launch of the 2-bit streaming kernel find their jobs, when K is one pass: in a table of jobs (1 KB of arguments, two
+// scalar look-ups in turn) or each in a record of its own (16 KB).  records: whether the launch can do without the table; several: more workgroups
+// than CUs; w_bytes: its packed words; captured: it becomes part of a graph.
+// The records cost the host 1.1 us, which is what a small call waits for.  The look-ups cost the device 0.2 to 0.5 us where a CU holds one workgroup,
+// nothing where it holds several.  So the table takes launches below 8 MB (two layers of 2048 x 2048 called in a loop 5.4 -> 4.3 us, 4096 x 4096 5.6 ->
+// 4.8; 18 x 4672 x 4096, 9.1 MB, 5.6 and by the table 5.9), but not under capture, since a replay pays nothing for arguments (the three 3.1, 4.6 and
+// 5.1 us, by the table 3.3, 5.0 and 5.5), unless there are several workgroups to a CU.
+constexpr int kTableJobs = 16;
+inline bool jobs_by_table(int count, bool one_pass, bool records, bool several, int64_t w_bytes, bool captured)
+{
+    if (!one_pass || count < 2 || count > kTableJobs) return false;
+    return !records || (w_bytes < (int64_t(8) << 20) && (several || !captured));
 }
 
 }  // namespace tl

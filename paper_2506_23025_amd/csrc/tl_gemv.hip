@@ -871,10 +871,8 @@ struct LeanAny : LeanOne {
 };
 static_assert(sizeof(LeanOne) == 64, "the arguments of a lone call");
 
-// A few jobs in a small launch: 1 KB of arguments, and a workgroup finds its job by two scalar look-ups in turn.  The records' 16 KB cost the host
-// 1.1 us, which is what a small call waits for; the look-ups cost the device 0.2 to 0.4 us (two layers of 2048 x 2048 called in a loop 5.4
-// -> 4.3 us, replayed from a graph 3.1 -> 3.3; 4096 x 4096 5.6 -> 4.8 and 4.6 -> 5.0; two of 5504 x 4096, 11 MB, 5.7 -> 5.9 and 5.65 -> 6.2).
-constexpr int kLeanTableJobs = 16;
+// A few jobs in a small launch: 1 KB of arguments, and a workgroup finds its job by two scalar look-ups in turn (see jobs_by_table).
+constexpr int kLeanTableJobs = kTableJobs;
 struct LeanJobs {
     int first[kLeanTableJobs];    // first workgroup of job j; INT_MAX for unused entries
     LeanOne job[kLeanTableJobs];
@@ -1790,8 +1788,6 @@ LeanFn<Args> pick_lean(int T)
     }
 }
 
-constexpr int64_t kLeanTableBytes = int64_t(10) << 20;       // of packed words in a launch, see LeanJobs
-
 constexpr int lean_lds(bool passes) { return 8 * stream_wave_lds(3) + (passes ? kStreamMaxRun * 1024 : 0); }
 
 // kept: tiles of the longest run of a job of several passes
@@ -2010,6 +2006,16 @@ bool launch_longk(const GemmDesc* jobs, int count, hipStream_t s, hipError_t* er
     return true;
 }
 
+// Whether what is enqueued now becomes part of a graph.  (The null stream cannot be captured, and asking about it while another stream is fails.)
+bool being_captured(hipStream_t s)
+{
+    if (s == nullptr) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Stream form: one job per workgroup, a run of consecutive tiles each.  Workgroups are dealt
 // out to the jobs so that all finish together (see run_cost below); spare ones go to the job
 // with the costliest runs, one by one.  Returns hipErrorInvalidValue without launching if a multi-pass job's
@@ -2032,10 +2038,12 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // One workgroup of 8 waves per CU; with shorter K (fewer waves per workgroup) as many more
     // workgroups, so that a CU still runs 8 waves (K = 1024: 1024 workgroups of 2 waves).
     const int64_t g_all = int64_t(pol.stream_groups) * (kStreamWaves / NW);
-    // With scales the table of jobs also takes what no records hold, more than 256 workgroups or jobs with fewer slices than waves.
-    const bool no_records = gs != 0 && (short_jobs || (total_tiles > kLeanMaxGroups && g_all > kLeanMaxGroups));
-    const bool table = nb == 1 && !multi_pass && b.count > 1 && b.count <= kLeanTableJobs &&
-                       (no_records || (w_bytes < kLeanTableBytes && !short_jobs));
+    // With scales the table of jobs also takes what no records hold, more than 256 workgroups or jobs with fewer slices than waves; without, the latter
+    // are left to the general form.
+    const bool beyond = (total_tiles < g_all ? total_tiles : g_all) > kLeanMaxGroups;
+    const bool records = gs == 0 || !(short_jobs || beyond);
+    bool table = nb == 1 && !(gs == 0 && short_jobs) && jobs_by_table(b.count, !multi_pass, records, beyond, w_bytes, false);
+    if (table && records && !beyond) table = !being_captured(s);
     const int64_t g_max = any && !table ? kLeanMaxGroups : g_all;
     const int G = total_tiles < g_max ? int(total_tiles) : int(g_max);
     // Time of a workgroup in tile units: passes x (run time + start-up), see tl_deal.hpp.  The

@@ -94,6 +94,35 @@ def test_small_jobs_in_one_call(specs, group):
         check(result(yd, M, N), x, W, sc, group or 1 << 20, f"{M}x{N}x{K} group {group}")
 
 
+# The same calls in a graph, whose launches carry records where the table's look-ups cost more: every replay gives what the call gives
+@pytest.mark.parametrize("group", [0, 64, 256])
+@pytest.mark.parametrize("specs", [[(1, 2048, 2048)] * 2, [(3, 4096, 4096), (16, 528, 4096)], [(2, 64, 2048), (5, 8192, 2048)], [(18, 512, 512), (1, 512, 512)]])
+def test_small_jobs_in_a_graph(specs, group):
+    import torch
+    host = [inputs(M, N, K, group or 1 << 20, 67000 + i + M + N + K) for i, (M, N, K) in enumerate(specs)]
+    dev = [on_device(x, W, sc, M, N) for (x, W, sc), (M, N, K) in zip(host, specs)]
+    if group:
+        jobs = tl.make_gs_jobs([(xd, wd, sd, group, yd, M, N, K) for (xd, wd, sd, yd), (M, N, K) in zip(dev, specs)])
+        call = lambda: tl.tl_ternary_gemm_gs_grouped(jobs)
+    else:
+        jobs = tl.make_jobs([(xd, wd, si.gamma_bits(np.float16(0.02)), yd, M, N, K) for (xd, wd, _, yd), (M, N, K) in zip(dev, specs)])
+        call = lambda: tl.tl_ternary_gemm_grouped(jobs)
+    tl.tl_init()
+    call()
+    want = [yd.clone() for _, _, _, yd in dev]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(4):
+        for _, _, _, yd in dev:
+            yd.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        for w, (_, _, _, yd), (M, N, K) in zip(want, dev, specs):
+            assert torch.equal(w[:M * N], yd[:M * N])
+        call()
+
+
 # An infinite scale makes the outputs of its column infinite, with the sign of scale times the group's sum, and leaves the others alone; K that
 # ends within a unit, a slice and a pass.  A NaN or an infinity in x stays in its row.
 @pytest.mark.parametrize("M,N,K,group", [(4, 64, 448, 64), (4, 64, 4032, 32), (16, 96, 4096, 128), (3, 48, 5056, 64), (5, 64, 8256, 128), (4, 64, 1003, 64), (2, 64, 4800, 32)])

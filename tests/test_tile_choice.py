@@ -148,6 +148,20 @@ def test_workgroups_of_the_streaming_kernel_fit_on_a_compute_unit():
         assert count >= 1 and count * lds.value <= 160 * 1024 and count * waves <= 16, waves
 
 
+def test_small_launches_find_their_jobs_in_a_table_unless_captured():
+    # measured (us), records / table: 2 x 2048 x 2048 in a loop 5.4 / 4.3, replayed 3.1 / 3.3; 18 x 4672 x 4096 (two blocks of rows, 9.1 MB) 5.6 / 5.9
+    fn = tl.raw().tl_internal_jobs_by_table
+    fn.argtypes = [ctypes.c_int] * 4 + [ctypes.c_int64, ctypes.c_int]
+    mb = 1 << 20
+    for captured in (0, 1):
+        assert fn(2, 1, 1, 0, 2 * mb, captured) == 1 - captured
+        assert fn(16, 1, 1, 0, 8 * mb - 1, captured) == 1 - captured
+        assert not fn(2, 1, 1, 0, 9 * mb, captured) and not fn(2, 1, 1, 1, 9 * mb, captured)
+        assert fn(2, 1, 1, 1, 2 * mb, captured)            # several workgroups to a CU: equal on the device, cheaper on the host
+        assert fn(2, 1, 0, 0, 90 * mb, captured)           # nothing else takes it
+        assert not fn(1, 1, 1, 0, mb, captured) and not fn(17, 1, 0, 0, mb, captured) and not fn(2, 0, 0, 0, mb, captured)
+
+
 def test_grouped_jobs_share_launches_where_that_is_faster():
     # measured (us), all streaming / each as if alone: 16 layers at M = 256, 2-bit words 512 x 1024 68.7 / 83.2, 768 x 2048 87.2 / 108.3, 1.6-bit codes
     # 512 x 1024 102.5 / 119.6
