@@ -2044,6 +2044,12 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     const bool records = gs == 0 || !(short_jobs || beyond);
     bool table = nb == 1 && !(gs == 0 && short_jobs) && jobs_by_table(b.count, !multi_pass, records, beyond, w_bytes, false);
     if (table && records && !beyond) table = !being_captured(s);
+    // What has scales and neither the plain records nor the table take goes to the form for any K and N, for which the workgroups are dealt out once: dealing
+    // them out twice cost the host as much again (blocks of 33 to 64 rows 8 us of 23 in a loop).
+    bool odd_n = false;
+    for (int j = 0; j < b.count; ++j) odd_n = odd_n || (b.job[j].N & 15) != 0;
+    if (gs != 0 && !table && b.count > 1 && !records) any = true;
+    if (gs != 0 && odd_n) any = true;
     const int64_t g_max = any && !table ? kLeanMaxGroups : g_all;
     const int G = total_tiles < g_max ? int(total_tiles) : int(g_max);
     // Time of a workgroup in tile units: passes x (run time + start-up), see tl_deal.hpp.  The
@@ -2086,17 +2092,16 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // The lean kernel takes the launch when every job has at least one slice per wave (more: several passes), N is a
     // multiple of 16 throughout and the workgroups fit its record table; with scales else its form for any K and N.  (The linears of a block, K = 4096 three times
     // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
-    bool lean = pol.lean && nb == 1 && T <= 3 && (!short_jobs || table || any);
+    const bool lean = nb == 1 && T <= 3 && (gs != 0 || (pol.lean && !odd_n && (!short_jobs || table)));
     int total_groups = 0, kept = 0;
     for (int j = 0; j < b.count; ++j) {
-        lean = lean && (any || (b.job[j].N & 15) == 0);
         total_groups += wg[j];
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
         if (passes(j) > 1 && r > kept) kept = r;
     }
     if (any) return launch_lean(b, wg, NW, T, kept, gs, true, table, s);
     if (lean && (total_groups <= kLeanMaxGroups || table || b.count == 1)) return launch_lean(b, wg, NW, T, kept, gs, false, table, s);
-    if (gs != 0) return launch_stream(b, max_slices, nb, s, gs, true);
+    if (gs != 0) return hipErrorInvalidValue;              // not reached: nothing else reads scales
     for (int j = 0; j < kMaxJobs; ++j) b.item0[j] = 0x7fffffff;
     int grid = 0;
     for (int j = 0; j < b.count; ++j) {
