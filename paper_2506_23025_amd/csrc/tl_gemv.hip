@@ -990,6 +990,8 @@ __device__ __forceinline__ void store_quad_any(__attribute__((address_space(1)))
 // product pair (product): block at M = 4 15.6 / 18.5 / 24.5 us with groups of 128 / 64 / 32, decode sweep 21.5 / 24.6 / 36.2.  Groups of 128 took
 // 25.8 and 36.5 in the general form, every product issued twice with other lanes masked off; the others went to the tiled kernel one by one, 68
 // and 131 us.
+// GS, several jobs: an N that is a multiple of 4 as well; through ANY such a launch, its x in registers, took up to 13 % longer (block of 8 rows, 1088 wide,
+// one N no multiple of 16, 6.5 -> 6.0 us).  Lone calls go without, which would cost them 0.05 to 0.2 us.
 // ANY: any K from 64 on and any N (GS: N a multiple of 4), jobs with fewer slices than waves among them.  Packed rows then start at multiples of 4
 // bytes, rows of x and y at any even address.  A row's last 16-byte chunk of weights is its last 16 bytes, wherever they start: no
 // request leaves the row, and what overlaps the chunk before meets zeros.  The activations come through registers.  Calls with K no multiple of 64
@@ -1109,10 +1111,11 @@ gemv_lean_kernel(Args b)
     uint32_t voff0 = offset_of(wave);
     uint32_t voff1 = voff0 + 8u * row_bytes;
     // the run as a raw buffer (no stride, byte offsets, size = the run): base in scalar registers
-    // (ANY: of the rows that exist; the others read zeros)
-    const int run_rows = ANY && N - R.tile0 * 16 < ntiles * 16 ? N - R.tile0 * 16 : ntiles * 16;
+    // (with an N that need not be a multiple of 16, of the rows that exist; the others read zeros)
+    constexpr bool kPartTile = ANY || (GS != 0 && !std::is_base_of<LeanOne, Args>::value);
+    const int run_rows = kPartTile && N - R.tile0 * 16 < ntiles * 16 ? N - R.tile0 * 16 : ntiles * 16;
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<unsigned char*>(Wrun), 0, ANY ? uint32_t(run_rows) * row_bytes : uint32_t(ntiles) * tile_bytes, 0x00020000);
+        const_cast<unsigned char*>(Wrun), 0, kPartTile ? uint32_t(run_rows) * row_bytes : uint32_t(ntiles) * tile_bytes, 0x00020000);
     u32x4 wreg[T][2];
     u32x2 sreg[T][H];
     fine_t freg[T];
@@ -1295,6 +1298,7 @@ gemv_lean_kernel(Args b)
         if constexpr (ANY) {
             store_quad_any(row, int(col), N, s, gamma);
         } else {
+            if (kPartTile && col >= uint32_t(N)) return;   // N is a multiple of 4
             const f16x2 lo = {(_Float16)(gamma * s[0]), (_Float16)(gamma * s[1])};
             const f16x2 hi = {(_Float16)(gamma * s[2]), (_Float16)(gamma * s[3])};
             *(__attribute__((address_space(1))) u32x2*)(row + col) = u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
@@ -2046,10 +2050,8 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     if (table && records && !beyond) table = !being_captured(s);
     // What has scales and neither the plain records nor the table take goes to the form for any K and N, for which the workgroups are dealt out once: dealing
     // them out twice cost the host as much again (blocks of 33 to 64 rows 8 us of 23 in a loop).
-    bool odd_n = false;
-    for (int j = 0; j < b.count; ++j) odd_n = odd_n || (b.job[j].N & 15) != 0;
     if (gs != 0 && !table && b.count > 1 && !records) any = true;
-    if (gs != 0 && odd_n) any = true;
+    if (gs != 0 && b.count == 1 && b.job[0].N % 16 != 0) any = true;       // one job's arguments are for whole tiles
     const int64_t g_max = any && !table ? kLeanMaxGroups : g_all;
     const int G = total_tiles < g_max ? int(total_tiles) : int(g_max);
     // Time of a workgroup in tile units: passes x (run time + start-up), see tl_deal.hpp.  The
@@ -2092,9 +2094,10 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     // The lean kernel takes the launch when every job has at least one slice per wave (more: several passes), N is a
     // multiple of 16 throughout and the workgroups fit its record table; with scales else its form for any K and N.  (The linears of a block, K = 4096 three times
     // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
-    const bool lean = nb == 1 && T <= 3 && (gs != 0 || (pol.lean && !odd_n && (!short_jobs || table)));
+    bool lean = nb == 1 && T <= 3 && (gs != 0 || (pol.lean && (!short_jobs || table)));
     int total_groups = 0, kept = 0;
     for (int j = 0; j < b.count; ++j) {
+        lean = lean && (gs != 0 || (b.job[j].N & 15) == 0);
         total_groups += wg[j];
         const int r = (b.job[j].tiles + wg[j] - 1) / wg[j];
         if (passes(j) > 1 && r > kept) kept = r;
@@ -2486,10 +2489,9 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
         GemvBatch b;
         b.count = 0;
         int max_slices = 1;
-        bool quads = false;                                // an N that is no multiple of 16
         auto flush = [&]() -> hipError_t {
             if (b.count == 0) return hipSuccess;
-            hipError_t e = launch_stream(b, max_slices, 1, s, kind, quads);
+            hipError_t e = launch_stream(b, max_slices, 1, s, kind);
             if (e == hipErrorInvalidValue && b.count > 1) {
                 // one launch per row block; a block alone fits by gemv_gs_supports
                 e = hipSuccess;
@@ -2497,12 +2499,11 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
                     GemvBatch one;
                     one.count = 1;
                     one.job[0] = b.job[q];
-                    e = launch_stream(one, one.job[0].slices, 1, s, kind, one.job[0].N % 16 != 0);
+                    e = launch_stream(one, one.job[0].slices, 1, s, kind);
                 }
             }
             b.count = 0;
             max_slices = 1;
-            quads = false;
             return e;
         };
         constexpr int kAtOnce = 64;
@@ -2537,7 +2538,6 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
                 j.run = j.plus = 0;
                 j.scales = d.scales; j.hpg = hpg; j.reserved = 0;
                 b.job[b.count++] = j;
-                quads = quads || d.N % 16 != 0;
                 if (slices > max_slices) max_slices = slices;
                 if (b.count == kMaxJobs) {
                     const hipError_t e = flush();
