@@ -46,6 +46,7 @@
 #include "tl_internal.hpp"
 #include "tl_deal.hpp"
 
+#include <atomic>
 #include <cstddef>
 #include <type_traits>
 
@@ -1799,7 +1800,7 @@ template <bool PASSES, int GS, bool ANY, class Args>
 hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept, hipStream_t s)
 {
     const LeanFn<Args> fn = pick_lean<Args, PASSES, GS, ANY>(T);
-    static bool lds_raised[kMaxDevices][4];
+    static std::atomic<bool> lds_raised[kMaxDevices][4];
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][T]) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
@@ -1927,7 +1928,7 @@ template <class Args>
 hipError_t launch_longk_args(const Args& args, dim3 grid, int T, int rows, hipStream_t s)
 {
     const LeanFn<Args> fn = pick_longk<Args>(T, rows);
-    static bool lds_raised[kMaxDevices][3][3];
+    static std::atomic<bool> lds_raised[kMaxDevices][3][3];
     const int dev = device_slot(), kind = rows <= 1 ? 0 : (rows <= 4 ? 1 : 2);
     if (dev < 0 || !lds_raised[dev][T][kind]) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
@@ -2120,7 +2121,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     b.pad = 0;
     const bool multi = b.count > 1;
     KernelFn fn = pick_stream(T, multi, multi_pass, nb);
-    static bool lds_raised[kMaxDevices][4][2][kTMax + 1];
+    static std::atomic<bool> lds_raised[kMaxDevices][4][2][kTMax + 1];
     const int variant = nb == 2 ? (multi_pass ? 3 : 2) : (multi_pass ? 1 : 0);
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][variant][multi][T]) {
@@ -2197,8 +2198,8 @@ hipError_t launch_batch(GemvBatch& b, bool grouped, bool stream_form, int nb, hi
     const bool multi = b.count > 1;
     KernelFn fn = pick_kernel(T, multi);
     // More than the default 64 KB of dynamic LDS needs the attribute; it is set once per
-    // kernel instance and device (idempotent, so a race only repeats it).
-    static bool lds_raised[kMaxDevices][2][kTMax + 1];
+    // kernel instance and device (idempotent, so threads that meet only repeat it).
+    static std::atomic<bool> lds_raised[kMaxDevices][2][kTMax + 1];
     const int dev = device_slot();
     if (dev < 0 || !lds_raised[dev][multi][T]) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),

@@ -315,6 +315,14 @@ print("ok")
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr[-500:])
 
 
+def test_flags_that_threads_share_are_atomic():
+    # "this kernel's LDS limit is raised on this device", read and written by whichever threads make the first calls
+    src = os.path.join(ROOT, "paper_2506_23025_amd", "csrc")
+    flags = [(f, line.strip()) for f in sorted(os.listdir(src)) for line in open(os.path.join(src, f)) if re.search(r"^\s*static\b.*\[kMaxDevices\]", line)]
+    assert len(flags) >= 7
+    assert [x for x in flags if "static std::atomic<bool>" not in x[1]] == []
+
+
 def test_kernel_choice_is_a_pure_function_of_the_shape():
     # decode batch sizes stream the weights; the prefill sizes of the workloads use the tiled MFMA
     # kernel; shapes neither fast kernel takes fall back; invalid sizes give no path
