@@ -2,11 +2,19 @@
 // Pure C++ (no HIP calls); compiled into libtl.so together with the kernels.
 #include "tl.h"
 
+#include <pthread.h>
 #include <sched.h>
+#include <signal.h>
+#include <unistd.h>
 
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
+#include <cstdio>
 #include <cstring>
+#include <memory>
+#include <mutex>
+#include <new>
 #include <thread>
 
 namespace {
@@ -59,41 +67,170 @@ uint64_t pack_words_avx2(const int8_t* row, uint32_t* dst, int64_t whole) { retu
 inline bool has_avx2() { return false; }
 #endif
 
-// CPUs this process may run on
-inline int cpus() {
-    cpu_set_t set;
-    return sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1;
+// CPUs this thread may run on
+struct Cpus {
+    unsigned long mask[16384 / (8 * sizeof(unsigned long))] = {};
+    Cpus() { if (sched_getaffinity(0, sizeof mask, reinterpret_cast<cpu_set_t*>(mask)) != 0) mask[0] = 1; }
+    int count() const { return CPU_COUNT_S(sizeof mask, reinterpret_cast<const cpu_set_t*>(mask)); }
+    bool operator==(const Cpus& o) const { return std::memcmp(mask, o.mask, sizeof mask) == 0; }
+};
+
+// CPUs that the process's control group is given time for (cgroup v2 "quota period" or v1's two files), or a large number
+int cpu_quota() {
+    long long quota = -1, period = 0;
+    if (FILE* f = std::fopen("/sys/fs/cgroup/cpu.max", "re")) {
+        if (std::fscanf(f, "%lld %lld", &quota, &period) != 2) quota = -1;       // "max 100000": no quota
+        std::fclose(f);
+    } else if (FILE* q = std::fopen("/sys/fs/cgroup/cpu/cpu.cfs_quota_us", "re")) {
+        if (std::fscanf(q, "%lld", &quota) != 1) quota = -1;
+        std::fclose(q);
+        if (FILE* p = std::fopen("/sys/fs/cgroup/cpu/cpu.cfs_period_us", "re")) {
+            if (std::fscanf(p, "%lld", &period) != 1) period = 0;
+            std::fclose(p);
+        }
+    }
+    if (quota <= 0 || period <= 0) return 1 << 20;
+    return quota < period ? 1 : static_cast<int>(quota / period < (1 << 20) ? quota / period : 1 << 20);
 }
 
-// The packers' rows 0 .. N - 1, in pieces that threads take as they come: rows(n0, n1) packs some and returns nonzero for a value that is no
-// weight.  A thread for every `share` weights, what one packs in about 50 us, a few times what it costs to start it; at most 8.  They end before
-// the call returns; where one cannot be started the others do its work.  One thread and up to 8 on a server, us: 4096 x 4096 to 2-bit words 764
-// and 206, to the 1.6-bit codes 2789 and 553, 4625 and 708; 1024 x 1024 50 and 51, 186 and 84, 299 and 105; 512 x 512 runs in one.
+// The work of one call of a packer: rows 0 .. N - 1 in pieces, which the caller and helpers take as they come.
+struct Pieces {
+    int64_t N, rows_each, count;
+    unsigned (*pack)(const void* rows, int64_t n0, int64_t n1);
+    const void* rows;                                      // the caller's: read for a piece that was taken, and the caller waits for those
+    int helpers;                                           // that may still join (under Helpers::m)
+    std::atomic<int64_t> next{0}, done{0};
+    std::atomic<unsigned> bad{0};
+    void work() {
+        for (int64_t p = next.fetch_add(1); p < count; p = next.fetch_add(1)) {
+            const int64_t n0 = p * rows_each;
+            if (pack(rows, n0, n0 + rows_each < N ? n0 + rows_each : N)) bad.store(1);
+            done.fetch_add(1);
+        }
+    }
+};
+
+// Up to 7 threads that wait for calls of the packers: started by the first call that wants them, one call's at a time (another one meanwhile works
+// alone), ended with the library.  Nothing waits for a helper that has not begun: a call ends when the pieces that were taken are done.  Threads
+// started and joined in every call waited for cores on which a program's own workers still spun.  us on 8 cores, 2-bit words, right after the tensor operation
+// that made the weights / repeated, one thread -> such threads -> these: 2048 x 1024 354 / 209 -> 1296 / 175 -> 348 / 155, 2048 x 2048 586 / 426 -> 2357 / 201 ->
+// 395 / 226, 4096 x 4096 2423 / 2107 -> 2969 / 528 -> 1381 / 347; 1.6-bit codes, 1024 x 1024 400 / 351 -> 3191 / 225 -> 235 / 129, 4096 x 4096 5469 /
+// 5439 -> 3133 / 1051 -> 2587 / 932.  A forked child has none of its parent's threads and starts its own.
+class Helpers {
+public:
+    static constexpr int kMost = 7;
+    const pid_t pid = getpid();
+    const Cpus cpus;
+    const int quota = cpu_quota();
+
+    void run(const std::shared_ptr<Pieces>& p) {
+        if (!busy.exchange(true)) {
+            {
+                std::lock_guard<std::mutex> hold(m);
+                if (!stop && started < p->helpers) start(p->helpers);
+                current = p;
+            }
+            wake.notify_one();
+            p->work();
+            {
+                std::lock_guard<std::mutex> hold(m);
+                current.reset();
+            }
+            busy.store(false);
+        } else {
+            p->work();
+        }
+        for (int spins = 0; p->done.load() < p->count; ++spins) {
+            if (spins >= 200) sched_yield();
+        }
+    }
+    void end() {
+        {
+            std::lock_guard<std::mutex> hold(m);
+            stop = true;
+        }
+        wake.notify_all();
+        for (int i = 0; i < started; ++i) threads[i].join();
+    }
+
+private:
+    // under m; the program's signals stay with its own threads
+    void start(int count) {
+        sigset_t all, before;
+        sigfillset(&all);
+        pthread_sigmask(SIG_SETMASK, &all, &before);
+        try {
+            for (; started < count && started < kMost; ++started) threads[started] = std::thread([this] { serve(); });
+        } catch (...) {                                    // no thread to be had: those there are
+        }
+        pthread_sigmask(SIG_SETMASK, &before, nullptr);
+    }
+    void serve() {
+        std::shared_ptr<Pieces> last;
+        for (;;) {
+            {
+                std::unique_lock<std::mutex> hold(m);
+                wake.wait(hold, [&] { return stop || (current && current != last && current->helpers > 0); });
+                if (stop) return;
+                last = current;
+                if (--last->helpers > 0) wake.notify_one();
+            }
+            last->work();
+        }
+    }
+    std::mutex m;
+    std::condition_variable wake;
+    std::shared_ptr<Pieces> current;
+    std::thread threads[kMost];
+    int started = 0;
+    bool stop = false;
+    std::atomic<bool> busy{false};
+};
+
+// This process's helpers.  The object itself is never freed: a thread may still be in a call when the library ends.
+std::atomic<Helpers*> g_helpers{nullptr};
+Helpers* helpers() {
+    Helpers* h = g_helpers.load();
+    if (h && h->pid == getpid()) return h;
+    Helpers* mine = new (std::nothrow) Helpers;
+    if (mine == nullptr) return nullptr;
+    if (g_helpers.compare_exchange_strong(h, mine)) return mine;
+    delete mine;
+    return h;
+}
+struct EndHelpers {
+    ~EndHelpers() {
+        Helpers* h = g_helpers.load();
+        if (h && h->pid == getpid()) h->end();
+    }
+} g_end_helpers;
+
+// The packers' rows 0 .. N - 1: rows(n0, n1) packs some and returns nonzero for a value that is no weight.  A thread for every `share` weights, which one
+// packs in 45 us (2-bit words), 25 and 40 us (the two 1.6-bit codes) on a server, at most 8.
 template <class Rows>
 unsigned over_rows(int64_t N, int64_t K, double share, const Rows& rows) {
-    constexpr int kMost = 8;
     const double want = static_cast<double>(N) * static_cast<double>(K) / share;
-    int threads = want < kMost ? static_cast<int>(want) : kMost;
-    if (threads > N) threads = static_cast<int>(N);
-    if (threads >= 2 && threads > cpus()) threads = cpus();
-    if (threads < 2) return rows(int64_t(0), N);
-    const int64_t piece = ceil_div(N, int64_t(4) * threads);
-    std::atomic<int64_t> next{0};
-    std::atomic<unsigned> bad{0};
-    auto work = [&] {
-        unsigned b = 0;
-        for (int64_t n0 = next.fetch_add(piece); n0 < N; n0 = next.fetch_add(piece)) b |= rows(n0, n0 + piece < N ? n0 + piece : N);
-        bad |= b;
-    };
-    std::thread others[kMost - 1];
-    int started = 0;
+    if (want < 2.0 || N < 2) return rows(int64_t(0), N);
+    const Cpus here;
+    int threads = want < Helpers::kMost + 1 ? static_cast<int>(want) : Helpers::kMost + 1;
+    if (threads > here.count()) threads = here.count();
+    Helpers* const h = threads > 1 ? helpers() : nullptr;
+    if (h != nullptr && threads > h->quota) threads = h->quota;
+    if (h == nullptr || threads < 2 || !(h->cpus == here)) return rows(int64_t(0), N);
+    std::shared_ptr<Pieces> p;
     try {
-        for (; started < threads - 1; ++started) others[started] = std::thread(work);
+        p = std::make_shared<Pieces>();
     } catch (...) {
+        return rows(int64_t(0), N);
     }
-    work();
-    for (int i = 0; i < started; ++i) others[i].join();
-    return bad;
+    p->N = N;
+    p->rows_each = ceil_div(N, int64_t(8) * threads);
+    p->count = ceil_div(N, p->rows_each);
+    p->pack = [](const void* r, int64_t n0, int64_t n1) -> unsigned { return (*static_cast<const Rows*>(r))(n0, n1); };
+    p->rows = &rows;
+    p->helpers = threads - 1;
+    h->run(p);
+    return p->bad.load();
 }
 constexpr double kShare2Bit = 1e6, kShare1p6 = 1.5e5;
 
