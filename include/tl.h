@@ -246,7 +246,8 @@ tl_status tl_ternary_gemm_gs(const void* x, const void* Wpacked, const void* sca
  * tl_ternary_gemm_1p6_grouped: weights in the 1.6-bit layout (Sec. 3.2), all jobs in the same
  * byte code: `format` is TL_FMT_1P6BIT (tl_pack_1p6bit) or TL_FMT_1P6BIT_FX (tl_pack_1p6bit_fx),
  * anything else is TL_ERR_VALUE.  Jobs with 8 <= K <= 4800 share launches (32 blocks
- * of 16 activation rows per launch); the others run as tl_ternary_gemm_1p6 / _fx would run them.
+ * of 16 activation rows per launch) unless they have so many rows that the tiled kernel is faster, or more
+ * than 16 and a K below 64 that is no multiple of 8; the others run as tl_ternary_gemm_1p6 / _fx would run them.
  */
 tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl_format format,
                                       void* stream);

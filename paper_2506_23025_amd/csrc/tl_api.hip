@@ -109,6 +109,29 @@ inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
     return c;
 }
 
+// Which kernel takes a call of its own.
+enum class Runs { plain, streams, tiled };
+
+inline Runs runs_2bit(int64_t M, int64_t N, int64_t K)
+{
+    const KernelChoice c = choice_2bit(M, N, K);
+    if (c.streams && !(c.tiled < c.stream)) return Runs::streams;
+    if (K % 64 != 0) return c.streams || tile_ragged_preferred(M, N, K) ? Runs::tiled : Runs::plain;
+    return mfma_supports(M, N, K) ? Runs::tiled : Runs::plain;
+}
+
+inline Runs runs_1p6(int64_t M, int64_t N, int64_t K)
+{
+    if (tile3_preferred(M, N, K)) return Runs::tiled;
+    return gemv3_supports(M < kStreamRows ? M : kStreamRows, N, K) ? Runs::streams : Runs::plain;
+}
+
+inline Runs runs_gs(int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    if (tile_gs_preferred(M, N, K, group)) return Runs::tiled;
+    return gemv_gs_supports(M, N, K, group) ? Runs::streams : Runs::plain;
+}
+
 // Enqueues the jobs of a grouped call, 64 at a time: `fuse` adds one to the shared launches, `flush` sends those, `single` calls one by itself.
 template <class Job, class Choice, class Fuse, class Flush, class Single>
 tl_status run_grouped(const Job* jobs, int64_t count, Choice&& choice, Fuse&& fuse, Flush&& flush, Single&& single)
@@ -157,10 +180,11 @@ tl_path tl_ternary_gemm_which(int64_t M, int64_t N, int64_t K)
 {
     if (!tl::dims_ok(M, N, K)) return TL_PATH_AUTO;
     if (K % 64 != 0) return TL_PATH_GENERIC;
-    const tl::KernelChoice c = tl::choice_2bit(M, N, K);
-    if (c.streams && !(c.tiled < c.stream)) return TL_PATH_GEMV;
-    if (tl::mfma_supports(M, N, K)) return TL_PATH_MFMA;
-    return TL_PATH_GENERIC;
+    switch (tl::runs_2bit(M, N, K)) {
+        case tl::Runs::streams: return TL_PATH_GEMV;
+        case tl::Runs::tiled: return TL_PATH_MFMA;
+        default: return TL_PATH_GENERIC;
+    }
 }
 
 tl_status tl_ternary_gemm_path(const void* x, const void* Wpacked, uint16_t gamma_fp16_bits, void* y,
@@ -177,11 +201,11 @@ tl_status tl_ternary_gemm_path(const void* x, const void* Wpacked, uint16_t gamm
 
     if (path == TL_PATH_AUTO) {
         path = tl_ternary_gemm_which(M, N, K);
-        // shapes of the any-shape path: the streaming or the tiled kernel's form for such K where it is the faster one
+        // shapes of the any-shape path: the streaming or the tiled kernel's form for such K
         if (path == TL_PATH_GENERIC && K % 64 != 0) {
-            const tl::KernelChoice c = tl::tile_ragged_choice(M, N, K);
-            if (c.streams && !(c.tiled < c.stream)) return tl::from_hip(tl::launch_gemv(xh, wp, gamma, yh, M, N, K, s));
-            if (c.streams || tl::tile_ragged_preferred(M, N, K)) return tl::from_hip(tl::launch_tile_ragged(xh, wp, gamma, yh, M, N, K, s));
+            const tl::Runs r = tl::runs_2bit(M, N, K);
+            if (r == tl::Runs::streams) return tl::from_hip(tl::launch_gemv(xh, wp, gamma, yh, M, N, K, s));
+            if (r == tl::Runs::tiled) return tl::from_hip(tl::launch_tile_ragged(xh, wp, gamma, yh, M, N, K, s));
         }
     }
     switch (path) {
@@ -244,10 +268,11 @@ tl_status gemm_1p6(const void* x, const void* Wpacked, uint16_t gamma_fp16_bits,
     const float gamma = tl::half_bits_to_float(gamma_fp16_bits);
     const int64_t stride = static_cast<int64_t>(tl_row_stride_bytes(TL_FMT_1P6BIT, K));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (tl::tile3_preferred(M, N, K))
+    const tl::Runs r = tl::runs_1p6(M, N, K);
+    if (r == tl::Runs::tiled)
         return tl::from_hip(tl::launch_tile3(static_cast<const __half*>(x), static_cast<const uint8_t*>(Wpacked), stride,
                                              gamma, static_cast<__half*>(y), M, N, K, fx, s));
-    if (tl::gemv3_supports(M < tl::kStreamRows ? M : tl::kStreamRows, N, K)) {
+    if (r == tl::Runs::streams) {
         // more rows than one launch takes: one launch per kStreamRows rows
         const __half* xh = static_cast<const __half*>(x);
         __half* yh = static_cast<__half*>(y);
@@ -290,9 +315,9 @@ tl_status tl_ternary_gemm_gs(const void* x, const void* Wpacked, const void* sca
     const uint32_t* wp = static_cast<const uint32_t*>(Wpacked);
     const __half* sh = static_cast<const __half*>(scales);
     __half* yh = static_cast<__half*>(y);
-    if (tl::tile_gs_preferred(M, N, K, group))
-        return tl::from_hip(tl::launch_tile_gs(xh, wp, sh, group, yh, M, N, K, s));
-    if (tl::gemv_gs_supports(M, N, K, group)) {
+    const tl::Runs r = tl::runs_gs(M, N, K, group);
+    if (r == tl::Runs::tiled) return tl::from_hip(tl::launch_tile_gs(xh, wp, sh, group, yh, M, N, K, s));
+    if (r == tl::Runs::streams) {
         const hipError_t e = tl::launch_gemv_gs(xh, wp, sh, group, yh, M, N, K, s);
         if (e != hipErrorInvalidValue) return tl::from_hip(e);
         (void)hipGetLastError();                 // nothing was launched: the plain kernel takes it
@@ -366,24 +391,31 @@ tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, 
 }
 
 // For the tests, which assert what they run; not part of the interface.  form: 0 2-bit words, 1 a 1.6-bit code, 2 group scales, 3 2-bit words on
-// TL_PATH_MFMA.  The tiled kernel's instance for a call of its own, or -1 where another kernel takes it.
-__attribute__((visibility("default"))) int tl_internal_tile_instance(int form, int64_t M, int64_t N, int64_t K, int64_t group)
+// TL_PATH_MFMA.  The kernel that a call of its own runs in: 0 plain, 1 streaming, 2 tiled.
+__attribute__((visibility("default"))) int tl_internal_runs(int form, int64_t M, int64_t N, int64_t K, int64_t group)
 {
     switch (form) {
-        case 0: {
-            if (tl_ternary_gemm_which(M, N, K) == TL_PATH_MFMA) return tl::mfma_shape(M, N, K);
-            if (tl_ternary_gemm_which(M, N, K) != TL_PATH_GENERIC || K % 64 == 0) return -1;
-            const tl::KernelChoice c = tl::tile_ragged_choice(M, N, K);
-            return (c.streams ? c.tiled < c.stream : tl::tile_ragged_preferred(M, N, K)) ? tl::tile_ragged_shape(M, N, K) : -1;
-        }
-        case 1: return tl::tile3_preferred(M, N, K) ? tl::tile3_shape(M, N, K) : -1;
-        case 2: return tl::tile_gs_preferred(M, N, K, group) ? tl::tile_gs_shape(M, N, K, group) : -1;
-        case 3: return tl::mfma_supports(M, N, K) ? tl::mfma_shape(M, N, K) : -1;
+        case 0: return int(tl::runs_2bit(M, N, K));
+        case 1: return int(tl::runs_1p6(M, N, K));
+        case 2: return int(tl::runs_gs(M, N, K, group));
+        case 3: return tl::mfma_supports(M, N, K) ? 2 : -1;
         default: return -1;
     }
 }
 
-// Likewise: which of a grouped call's jobs (M, N, K, group each) the tiled kernel takes where the streaming one could.
+// Likewise: the tiled kernel's instance for such a call, or -1 where another kernel takes it.
+__attribute__((visibility("default"))) int tl_internal_tile_instance(int form, int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    if (tl_internal_runs(form, M, N, K, group) != int(tl::Runs::tiled)) return -1;
+    switch (form) {
+        case 1: return tl::tile3_shape(M, N, K);
+        case 2: return tl::tile_gs_shape(M, N, K, group);
+        default: return K % 64 != 0 ? tl::tile_ragged_shape(M, N, K) : tl::mfma_shape(M, N, K);
+    }
+}
+
+// Likewise: per job of a grouped call (M, N, K, group each) 1 where the tiled kernel takes it though the streaming one could, 0 where it shares the
+// streaming kernel's launches, and -1 where that kernel cannot take it and it runs as a call of its own.
 __attribute__((visibility("default"))) void tl_internal_grouped_tiled(int form, const int64_t* jobs, int count, int* out)
 {
     tl::KernelChoice c[64];
@@ -394,7 +426,7 @@ __attribute__((visibility("default"))) void tl_internal_grouped_tiled(int form, 
         c[j] = form == 0 ? tl::choice_2bit(M, N, K) : (form == 1 ? tl::tile3_choice(M, N, K) : tl::tile_gs_choice(M, N, K, group));
     }
     tl::choose_grouped(c, count, tiled);
-    for (int j = 0; j < count; ++j) out[j] = tiled[j] ? 1 : 0;
+    for (int j = 0; j < count; ++j) out[j] = c[j].streams ? (tiled[j] ? 1 : 0) : -1;
 }
 
 // Likewise: jobs_by_table.

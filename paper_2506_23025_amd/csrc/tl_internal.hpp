@@ -43,7 +43,8 @@ struct GemmDesc {
     int64_t M, N, K;
 };
 
-// Weight-streaming small-M kernel (2-bit).  Needs K % 64 == 0; handles M in chunks of 16.
+// Weight-streaming small-M kernel (2-bit), M in blocks of 16 or 32 rows.  gemv_supports: its forms for K % 64 == 0; launch_gemv also takes what
+// gemv_any_supports does.
 bool gemv_supports(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemv(const __half* x, const uint32_t* Wp, float gamma, __half* y,
                        int64_t M, int64_t N, int64_t K, hipStream_t s);
@@ -73,14 +74,14 @@ inline bool gemv_rows_form(int64_t M, int64_t N, int64_t K)
     return M > 16 && M <= 4096 && K % 64 == 0 && K >= 64 && K <= 2048 && N % 16 == 0 && N <= (int64_t(1) << 24);
 }
 
-// Its forms for any K and N: launch_gemv and launch_gemv_jobs take these too (64 <= K <= 32768, M <= 4096).
+// The forms for any K and N (64 <= K <= 32768, M <= 4096), which launch_gemv and launch_gemv_jobs use where K % 64 != 0.
 bool gemv_any_supports(int64_t M, int64_t N, int64_t K);
 
 // Several independent GEMMs (each passing gemv_supports or gemv_any_supports) in as few launches as possible.
 hipError_t launch_gemv_jobs(const GemmDesc* jobs, int count, hipStream_t s);
 
-// Per-group scales s[K / group][N] in place of gamma (stream form of the small-M kernel; M in
-// blocks of 16).  Needs what gemv_supports needs and group % 128 == 0, N % 4 == 0.
+// Per-group scales s[K / group][N] in place of gamma (lean form of the small-M kernel; M in blocks of 16).  Needs N % 4 == 0 and
+// group % 64 == 0, or % 32 where K % 64 == 0; K from 64 to 32768, and where K % 64 != 0 at most 4096 rows.
 bool gemv_gs_supports(int64_t M, int64_t N, int64_t K, int64_t group);
 hipError_t launch_gemv_gs(const __half* x, const uint32_t* Wp, const __half* scales, int64_t group,
                           __half* y, int64_t M, int64_t N, int64_t K, hipStream_t s);

@@ -7,7 +7,7 @@ import oracle
 import paper_2506_23025_amd as tl
 import synth_inputs as si
 from parity import assert_close, dev_u32, to_dev
-from test_tile_choice import TWO_BIT, instance
+from test_tile_choice import STREAMS, TWO_BIT, runs, shares
 
 pytestmark = pytest.mark.gpu
 
@@ -38,7 +38,7 @@ def check(y, x, W, g, what):
                                    (2, 600, 16385), (16, 1030, 32767), (13, 30, 16383), (64, 515, 4111)])
 def test_any_k(M, N, K):
     y, x, W, g = product(M, N, K, 47000 + M + N + K)
-    assert instance(TWO_BIT, M, N, K) == -1, "the tiled kernel takes it"
+    assert runs(TWO_BIT, M, N, K) == STREAMS
     check(y, x, W, g, f"{M}x{N}x{K}")
 
 
@@ -48,7 +48,7 @@ def test_rows_stay_apart(M, N, K):
     x, W, g = si.layer(48000 + K, M, N, K)
     x[1, 0], x[2, K - 1], x[M - 1, 5] = np.inf, np.nan, -np.inf
     y, x, W, g = product(M, N, K, 48000 + K, x)
-    assert instance(TWO_BIT, M, N, K) == -1
+    assert runs(TWO_BIT, M, N, K) == STREAMS
     clean = np.setdiff1d(np.arange(M), [1, 2, M - 1])
     check(y[clean], np.ascontiguousarray(x[clean]), W, g, "rows beside a NaN")
     assert np.isnan(y[2]).all() and not np.isfinite(y[[1, M - 1]].astype(np.float32)).any()
@@ -61,6 +61,7 @@ def test_rows_stay_apart(M, N, K):
                                    [(200, 512, 999), (8, 512, 999), (300, 4096, 4096)], [(4, 300, 77)],
                                    [(1, 60000, 4100), (1, 60000, 4100), (1, 60000, 4100)], [(3, 100, 30), (3, 100, 100)]])
 def test_grouped(specs):
+    assert shares(TWO_BIT, specs) == [K >= 64 for M, N, K in specs]
     jobs, want = [], []
     for i, (M, N, K) in enumerate(specs):
         x, W, g = si.layer(49000 + i + M + N + K, M, N, K)

@@ -6,7 +6,7 @@ import oracle
 import paper_2506_23025_amd as tl
 import synth_inputs as si
 from parity import assert_close, dev_u32, to_dev
-from test_tile_choice import SCALES, grouped, instance
+from test_tile_choice import SCALES, STREAMS, TILED, TWO_BIT, runs, shares
 
 pytestmark = pytest.mark.gpu
 
@@ -50,7 +50,7 @@ SHAPES = [(1, 4, 64), (3, 20, 128), (2, 16, 192), (4, 64, 512), (16, 1000, 576),
 @pytest.mark.parametrize("group", [32, 64, 96, 128, 192, 256, 384, 1 << 20])
 @pytest.mark.parametrize("M,N,K", SHAPES)
 def test_groups(M, N, K, group):
-    assert M > 16 or instance(SCALES, M, N, K, group) == -1, "the tiled kernel takes it"
+    assert runs(SCALES, M, N, K, group) == STREAMS
     y, x, W, sc = product(M, N, K, group, 61000 + M + N + K)
     check(y, x, W, sc, group, f"{M}x{N}x{K} group {group}")
 
@@ -59,7 +59,7 @@ def test_groups(M, N, K, group):
 @pytest.mark.parametrize("group", [64, 128, 192, 256])
 @pytest.mark.parametrize("M,N,K", [(1, 4, 65), (4, 20, 127), (3, 64, 513), (16, 1000, 1003), (4, 4096, 4090), (16, 2048, 4104), (8, 20000, 2049), (5, 9000, 6001), (37, 516, 3000), (1, 100, 32760)])
 def test_groups_of_any_k(M, N, K, group):
-    assert M > 16 or instance(SCALES, M, N, K, group) == -1
+    assert runs(SCALES, M, N, K, group) == STREAMS
     y, x, W, sc = product(M, N, K, group, 62000 + M + N + K)
     check(y, x, W, sc, group, f"{M}x{N}x{K} group {group}")
 
@@ -74,7 +74,8 @@ def test_groups_in_one_call(specs):
     tl.tl_ternary_gemm_gs_grouped([(xd, wd, sd, group, yd, M, N, K) for (xd, wd, sd, yd), (M, N, K, group) in zip(dev, specs)])
     for (x, W, sc), (_, _, _, yd), (M, N, K, group) in zip(host, dev, specs):
         check(result(yd, M, N), x, W, sc, group, f"{M}x{N}x{K} group {group}")
-    assert not any(grouped(SCALES, [s for s in specs if s[0] <= 16]))
+    # all but groups of 32 with a K that is no multiple of 64, which the streaming kernel does not take
+    assert shares(SCALES, specs) == [group != 32 or K % 64 == 0 for M, N, K, group in specs]
 
 
 # a few small jobs, which find their place in a table of jobs: of 2 to 16 jobs, of equal and of different numbers of slices, N of quads, more
@@ -83,6 +84,7 @@ def test_groups_in_one_call(specs):
 @pytest.mark.parametrize("specs", [[(1, 512, 512)] * 2, [(3, 528, 1024)] * 8, [(2, 64, 2048), (16, 4096, 2048), (1, 16, 2048)] * 3, [(i + 1, 512, 1024) for i in range(16)], [(1, 256, 512)] * 17,
                                    [(4, 1024, 512), (4, 20, 1024), (4, 1000, 4096)], [(1, 12288, 1024), (2, 12288, 1024)], [(1, 16, 64), (1, 16, 4096)]])
 def test_small_jobs_in_one_call(specs, group):
+    assert all(shares(SCALES if group else TWO_BIT, [(*s, group) for s in specs]))
     host = [inputs(M, N, K, group or 1 << 20, 66000 + i + M + N + K) for i, (M, N, K) in enumerate(specs)]
     dev = [on_device(x, W, sc, M, N) for (x, W, sc), (M, N, K) in zip(host, specs)]
     if group:
@@ -99,6 +101,7 @@ def test_small_jobs_in_one_call(specs, group):
 @pytest.mark.parametrize("specs", [[(1, 2048, 2048)] * 2, [(3, 4096, 4096), (16, 528, 4096)], [(2, 64, 2048), (5, 8192, 2048)], [(18, 512, 512), (1, 512, 512)]])
 def test_small_jobs_in_a_graph(specs, group):
     import torch
+    assert all(shares(SCALES if group else TWO_BIT, [(*s, group) for s in specs]))
     host = [inputs(M, N, K, group or 1 << 20, 67000 + i + M + N + K) for i, (M, N, K) in enumerate(specs)]
     dev = [on_device(x, W, sc, M, N) for (x, W, sc), (M, N, K) in zip(host, specs)]
     if group:
@@ -152,8 +155,9 @@ def test_infinite_scales_and_activations(M, N, K, group):
         check(y2[2:], x2[2:], W, sc2, group, "rows beside a NaN")
 
 
-def test_rows_of_several_launches():
-    M, N, K, group = 4096 + 17, 16, 512, 64
+@pytest.mark.parametrize("M,N,K,group,kernel", [(4096 + 17, 16, 512, 64, TILED), (4096 + 17, 4, 12288, 256, STREAMS)])
+def test_rows_of_several_launches(M, N, K, group, kernel):
+    assert runs(SCALES, M, N, K, group) == kernel
     x, W, sc = inputs(M, N, K, group, 65000)
     y, _, _, _ = product(M, N, K, group, 65000, x, sc)
     rows = np.r_[0:20, 4080:M]

@@ -7,6 +7,7 @@ import oracle
 import paper_2506_23025_amd as tl
 import synth_inputs as si
 from parity import assert_close, to_dev
+from test_tile_choice import ONE_POINT_SIX, STREAMS, runs, shares
 
 pytestmark = pytest.mark.gpu
 
@@ -25,6 +26,7 @@ def check(y, x, W, g, what):
 @pytest.mark.parametrize("M,N,K", [(1, 1, 8), (3, 15, 80), (16, 16, 312), (2, 17, 320), (5, 33, 328), (1, 4100, 4480), (16, 1022, 4800),
                                    (7, 4097, 4808), (16, 48, 9600), (1, 5000, 9608), (9, 8211, 6400), (4, 12304, 4872), (12, 16400, 640)])
 def test_shapes_at_the_edges(M, N, K, fmt, pack, call):
+    assert runs(ONE_POINT_SIX, M, N, K) == STREAMS
     x, W, g = si.layer(41000 + M + N + K, M, N, K)
     xd, wd = to_dev(x.view(np.int16)), to_dev(pack(W))
     yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
@@ -36,6 +38,7 @@ def test_shapes_at_the_edges(M, N, K, fmt, pack, call):
 @pytest.mark.parametrize("M,N,K", [(1, 32784, 320), (5, 65552, 264), (16, 16400, 640), (2, 32768, 584), (16, 16399, 960), (3, 33000, 904), (9, 12304, 1280),
                                    (16, 8208, 1600), (1, 16384, 1320), (7, 24577, 1528), (33, 9000, 1600), (40, 20000, 960), (4, 16400, 2240)])
 def test_several_workgroups_per_cu(M, N, K):
+    assert runs(ONE_POINT_SIX, M, N, K) == STREAMS
     x, W, g = si.layer(43000 + M + N + K, M, N, K)
     xd, wd = to_dev(x.view(np.int16)), to_dev(tl.tl_pack_1p6bit(W))
     yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
@@ -47,6 +50,7 @@ def test_several_workgroups_per_cu(M, N, K):
 @pytest.mark.parametrize("specs", [[(16, 14336, 1024), (16, 18448, 640)], [(1, 16384, 2240), (9, 16400, 2240)],
                                    [(2, 16384, 2248), (5, 16384, 2240)], [(3, 32768, 320), (1, 30, 2240)]])
 def test_grouped_launches_of_one_and_two_workgroups_per_cu(specs):
+    assert all(shares(ONE_POINT_SIX, specs))
     jobs, want = [], []
     for i, (M, N, K) in enumerate(specs):
         x, W, g = si.layer(42000 + i + M + N + K, M, N, K)
@@ -63,6 +67,7 @@ def test_grouped_launches_of_one_and_two_workgroups_per_cu(specs):
 @pytest.mark.parametrize("M,N,K", [(5, 272, 4096), (13, 4100, 960), (7, 1000, 6400), (16, 33, 320), (21, 2000, 11008)])
 @pytest.mark.parametrize("fmt,pack,call", FORMS)
 def test_non_finite_activations_stay_in_their_row(M, N, K, fmt, pack, call):
+    assert runs(ONE_POINT_SIX, M, N, K) == STREAMS
     x, W, g = si.layer(44000 + M + N + K, M, N, K)
     wd = to_dev(pack(W))
 
@@ -88,6 +93,7 @@ def test_non_finite_activations_stay_in_their_row(M, N, K, fmt, pack, call):
                                    (3, 4099, 644), (1, 300, 4801), (6, 4100, 5002), (16, 4098, 9603), (4, 8211, 9607), (7, 12304, 4873), (2, 16400, 4805),
                                    (16, 12300, 9611), (40, 700, 1001), (33, 130, 8190), (20, 9000, 1013)])
 def test_any_k(M, N, K, fmt, pack, call):
+    assert runs(ONE_POINT_SIX, M, N, K) == STREAMS
     x, W, g = si.layer(45000 + M + N + K, M, N, K)
     xd, wd = to_dev(x.view(np.int16)), to_dev(pack(W))
     yd = to_dev(np.full((M, N), -21555, dtype=np.int16))
@@ -97,8 +103,10 @@ def test_any_k(M, N, K, fmt, pack, call):
 
 # such jobs share a launch with others, bit for bit what they give alone; a NaN in the row that follows a row's last piece stays there
 def test_any_k_in_a_grouped_launch():
+    specs = [(16, 2050, 1001), (3, 1024, 1024), (9, 515, 641), (16, 300, 4799), (1, 40, 9)]
+    assert all(shares(ONE_POINT_SIX, specs))
     jobs, alone = [], []
-    for i, (M, N, K) in enumerate([(16, 2050, 1001), (3, 1024, 1024), (9, 515, 641), (16, 300, 4799), (1, 40, 9)]):
+    for i, (M, N, K) in enumerate(specs):
         x, W, g = si.layer(46000 + i, M, N, K)
         if M > 1:
             x[1, 0], x[M - 1, K - 1] = np.nan, np.inf

@@ -9,6 +9,10 @@ _instance.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 4
 _instance.restype = ctypes.c_int
 
 TWO_BIT, ONE_POINT_SIX, SCALES, TWO_BIT_FORCED = range(4)
+_runs = tl.raw().tl_internal_runs
+_runs.argtypes = _instance.argtypes
+_runs.restype = ctypes.c_int
+PLAIN, STREAMS, TILED = range(3)
 _grouped = tl.raw().tl_internal_grouped_tiled
 _grouped.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
 _grouped.restype = None
@@ -20,12 +24,26 @@ def instance(form, M, N, K, group=0):
     return _instance(form, M, N, K, group)
 
 
-def grouped(form, jobs):
-    """Per job (M, N, K[, group]) of a grouped call, whether the tiled kernel takes it from the launches the others share."""
+def runs(form, M, N, K, group=0):
+    """The kernel that a call of its own runs in: PLAIN, STREAMS or TILED."""
+    return _runs(form, M, N, K, group)
+
+
+def _of_jobs(form, jobs):
     flat = (ctypes.c_int64 * (4 * len(jobs)))(*[v for j in jobs for v in (tuple(j) + (0,))[:4]])
     out = (ctypes.c_int * len(jobs))()
     _grouped(form, flat, len(jobs), out)
-    return [bool(v) for v in out]
+    return list(out)
+
+
+def grouped(form, jobs):
+    """Per job (M, N, K[, group]) of a grouped call, whether the tiled kernel takes it from the launches the others share."""
+    return [v == 1 for v in _of_jobs(form, jobs)]
+
+
+def shares(form, jobs):
+    """Per job of a grouped call, whether it shares the streaming kernel's launches."""
+    return [v == 0 for v in _of_jobs(form, jobs)]
 
 
 def test_tile_shapes_reach_every_instance():
@@ -48,6 +66,15 @@ def test_shapes_beyond_the_form_are_left_to_others():
     for form in (TWO_BIT, ONE_POINT_SIX, SCALES):
         assert instance(form, 1024, 4096, 7, 16) == -1     # K of less than a piece
         assert instance(form, 1 << 25, 16, 100, 16) == -1  # rows past 2^24
+
+
+def test_a_call_is_told_from_those_of_other_kernels():
+    assert runs(SCALES, 16, 4096, 4096, 128) == STREAMS and runs(SCALES, 16, 4096, 4096, 16) == TILED and runs(SCALES, 1, 1, 5344, 128) == PLAIN
+    assert shares(SCALES, [(16, 4096, 4096, 128), (16, 4096, 4096, 16), (16, 4099, 4096, 128), (2, 300, 777, 32)]) == [True, False, False, False]
+    assert runs(TWO_BIT, 16, 4099, 4090) == STREAMS and runs(TWO_BIT, 2000, 2050, 33) == TILED and runs(TWO_BIT, 1, 16, 7) == PLAIN
+    assert shares(TWO_BIT, [(16, 4099, 4090), (16, 4099, 63)]) == [True, False]
+    assert runs(ONE_POINT_SIX, 16, 4096, 4096) == STREAMS and runs(ONE_POINT_SIX, 512, 14336, 4096) == TILED and runs(ONE_POINT_SIX, 1, 16, 7) == PLAIN
+    assert shares(ONE_POINT_SIX, [(16, 4096, 4800), (16, 4096, 4801), (16, 4096, 63), (17, 4096, 63)]) == [True, False, True, False]
 
 
 def test_two_bit_words_at_many_rows():
