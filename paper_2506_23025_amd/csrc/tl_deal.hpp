@@ -29,7 +29,7 @@ inline double deal_run_time(const DealModel& m, int run)
 {
     if (!m.item_cost) return double(run);
     // a run of 4 goes as 2 + 2 when items hold 3
-    const int items = run <= m.t_max ? 1 : ((m.t_max == 3 && run == 4) ? 2 : (run + m.t_max - 1) / m.t_max);
+    const int items = run <= m.t_max ? 1 : (m.t_max == 3 ? (run == 4 ? 2 : (run + 2) / 3) : (m.t_max == 2 ? (run + 1) / 2 : (run + m.t_max - 1) / m.t_max));
     return m.item_first * double(items) + m.tile_extra * double(run - items);
 }
 
@@ -54,6 +54,20 @@ inline int deal_groups_for(const DealModel& m, const DealJob& j, double tau)
     return w < 1 ? 1 : (w > j.tiles ? j.tiles : w);
 }
 
+// Of every job the fewest workgroups that finish it by tau, and their sum.  The blocks of rows of one matrix follow each other and are alike but for the
+// last, so they are worked out once: 24 blocks of six matrices 26 -> 9 us of the host.
+inline int deal_groups_of_all(const DealModel& m, const DealJob* jobs, int count, double tau, int* wg)
+{
+    int need = 0;
+    for (int j = 0; j < count; ++j) {
+        const DealJob& a = jobs[j];
+        const bool alike = j > 0 && a.tiles == jobs[j - 1].tiles && a.passes == jobs[j - 1].passes && a.start_up == jobs[j - 1].start_up;
+        wg[j] = alike ? wg[j - 1] : deal_groups_for(m, a, tau);
+        need += wg[j];
+    }
+    return need;
+}
+
 // wg[j] >= 1 workgroups for job j, G in all when the jobs hold at least G tiles (fewer jobs than G)
 inline void deal_workgroups(const DealModel& m, const DealJob* jobs, int count, int G, int* wg)
 {
@@ -61,12 +75,9 @@ inline void deal_workgroups(const DealModel& m, const DealJob* jobs, int count, 
     for (int j = 0; j < count; ++j) { const double c = deal_run_cost(m, jobs[j], 1); if (c > hi) hi = c; }
     for (int it = 0; it < 24; ++it) {
         const double mid = 0.5 * (lo + hi);
-        int need = 0;
-        for (int j = 0; j < count; ++j) need += deal_groups_for(m, jobs[j], mid);
-        if (need <= G) hi = mid; else lo = mid;
+        if (deal_groups_of_all(m, jobs, count, mid, wg) <= G) hi = mid; else lo = mid;
     }
-    int used = 0;
-    for (int j = 0; j < count; ++j) { wg[j] = deal_groups_for(m, jobs[j], hi); used += wg[j]; }
+    int used = deal_groups_of_all(m, jobs, count, hi, wg);
     // Spare groups, one by one to the job with the costliest run (the first of equals).  A job keeps getting them until its run is
     // a tile shorter, so all of those are handed over at once: hundreds of spare groups cost the host more than the kernel
     // takes otherwise (12 jobs of 1024 tiles on 2048 groups: 52 us one at a time, 4.3 like this).
