@@ -2299,23 +2299,36 @@ int units_per_group(int64_t K, int64_t group, int kind)
     return int(group / unit < all ? group / unit : all);
 }
 
+hipError_t launch_any_rows(const GemvJob& j, int64_t M, int gs, hipStream_t s)
+{
+    return launch_lean_rows(j.x, j.W, j.gamma, j.scales, group_inverse(j), j.y, M, j.N, j.K, gs, true, s);
+}
+
+// Blocks of 16 rows in one launch, or, where their runs are too long for what a launch keeps of their sums, half of them in each of two: one launch per
+// block took 26 jobs of 33 rows and K up to 11008 418 us (the general kernel 216), halves take 174.
+hipError_t launch_any_blocks(const GemvJob* blocks, int count, int gs, hipStream_t s)
+{
+    if (count == 1) return launch_any_rows(blocks[0], blocks[0].Mrem, gs, s);
+    GemvBatch b;
+    b.count = count;
+    int max_slices = 1;
+    for (int q = 0; q < count; ++q) {
+        b.job[q] = blocks[q];
+        if (blocks[q].slices > max_slices) max_slices = blocks[q].slices;
+    }
+    const hipError_t e = launch_stream(b, max_slices, 1, s, gs, true);
+    if (e != hipErrorInvalidValue) return e;
+    const hipError_t first = launch_any_blocks(blocks, count / 2, gs, s);
+    return first == hipSuccess ? launch_any_blocks(blocks + count / 2, count - count / 2, gs, s) : first;
+}
+
 hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s, int gs = 0)
 {
-    GemvBatch b;
-    b.count = 0;
-    int max_slices = 1;
-    auto one = [&](const GemvJob& j, int64_t M) {
-        return launch_lean_rows(j.x, j.W, j.gamma, j.scales, group_inverse(j), j.y, M, j.N, j.K, gs, true, s);
-    };
+    GemvJob blocks[kMaxJobs];
+    int held = 0;
     auto flush = [&]() -> hipError_t {
-        if (b.count == 0) return hipSuccess;
-        hipError_t e = b.count == 1 ? hipErrorInvalidValue : launch_stream(b, max_slices, 1, s, gs, true);
-        if (e == hipErrorInvalidValue) {                   // one job, or runs too long for what a launch keeps of their sums: one launch each
-            e = hipSuccess;
-            for (int q = 0; q < b.count && e == hipSuccess; ++q) e = one(b.job[q], b.job[q].Mrem);
-        }
-        b.count = 0;
-        max_slices = 1;
+        const hipError_t e = held ? launch_any_blocks(blocks, held, gs, s) : hipSuccess;
+        held = 0;
         return e;
     };
     for (int i = 0; i < count; ++i) {
@@ -2326,15 +2339,14 @@ hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s, int gs 
         j.tiles = int((d.N + 15) / 16);
         j.slices = int((d.K + kSliceK - 1) / kSliceK);
         j.scales = d.scales; j.hpg = gs ? units_per_group(d.K, d.group, gs) : 0;
-        if (count == 1) return one(j, d.M);
+        if (count == 1) return launch_any_rows(j, d.M, gs, s);
         for (int64_t m0 = 0; m0 < d.M; m0 += 16) {
             GemvJob q = j;
             q.x = d.x + m0 * d.K;
             q.y = d.y + m0 * d.N;
             q.Mrem = int(d.M - m0 < 16 ? d.M - m0 : 16);
-            b.job[b.count++] = q;
-            if (q.slices > max_slices) max_slices = q.slices;
-            if (b.count == kMaxJobs) {
+            blocks[held++] = q;
+            if (held == kMaxJobs) {
                 const hipError_t e = flush();
                 if (e != hipSuccess) return e;
             }
@@ -2350,7 +2362,9 @@ hipError_t launch_gemv_jobs(const GemmDesc* jobs, int count, hipStream_t s)
     bool any_k = false;
     for (int i = 0; i < count; ++i) any_k = any_k || jobs[i].K % 64 != 0;
     if (any_k) {
-        // a job of such a K, and with it those that would share a launch of blocks of 16 rows anyway
+        // a job of such a K, and with it those that would share a launch of blocks of 16 rows anyway: a launch of its own costs it more than the form for
+        // any K costs its neighbours.  Over 120 calls of 1 to 50 aligned jobs (M = 1 .. 64, K = 512 .. 11008) and one or two of such K 0.68 of the time
+        // of the aligned jobs' own launches and the tiled kernel's for the others up to 40 jobs, 0.87 at 8 to 50; the slowest two 1.007 (215 and 156 us).
         constexpr int kAtOnce = 64;
         AnyJob mixed[kAtOnce];
         GemmDesc rest[kAtOnce];

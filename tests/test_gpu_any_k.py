@@ -95,3 +95,38 @@ def test_blocks_of_rows_in_one_launch(M, N, K):
     y = yd.cpu().numpy()
     assert (y[M * N:] == -21555).all()
     check(y[:M * N].view(np.float16).reshape(M, N), x, W, g, f"{M}x{N}x{K}")
+
+
+def launches(call):
+    """Kernels that a call enqueues: the nodes of its graph."""
+    import ctypes
+    import torch
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    stream, graph, nodes = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
+    handle = ctypes.c_void_p(stream.cuda_stream)
+    assert hip.hipStreamBeginCapture(handle, 2) == 0       # relaxed
+    call(stream)
+    assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return nodes.value
+
+
+# what one launch keeps of the sums of several passes is 32 tiles a workgroup, 8192 in all: jobs beyond that are two launches, not one for each block of 16 rows
+@pytest.mark.parametrize("specs,most", [([(2, 14336, 4608 + 8)] * 12, 2), ([(17, 14336, 4608), (17, 100, 999)] * 6, 3), ([(1, 60000, 4100)] * 3, 2), ([(3, 640, 4099), (16, 4096, 1024)], 1)])
+def test_launches_of_long_runs(specs, most):
+    tl.tl_init()
+    jobs, want, layers = [], [], {}
+    for M, N, K in specs:
+        if (M, N, K) not in layers:
+            x, W, g = si.layer(51000 + M + N + K, M, N, K)
+            layers[M, N, K] = (x, W, g, to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)))
+        x, W, g, xd, wd = layers[M, N, K]
+        yd = to_dev(np.full(M * N, -21555, dtype=np.int16))
+        jobs.append((xd, wd, si.gamma_bits(g), yd, M, N, K))
+        want.append((yd, x, W, g))
+    assert all(shares(TWO_BIT, specs))
+    assert launches(lambda stream: tl.tl_ternary_gemm_grouped(jobs, stream)) <= most
+    tl.tl_ternary_gemm_grouped(jobs)
+    for (yd, x, W, g), (M, N, K) in zip(want, specs):
+        check(yd.cpu().numpy().view(np.float16).reshape(M, N), x, W, g, f"{M}x{N}x{K}")
