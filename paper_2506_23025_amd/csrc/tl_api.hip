@@ -340,21 +340,26 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
     const bool fx = format == TL_FMT_1P6BIT_FX;
     hipStream_t s = static_cast<hipStream_t>(stream);
     // Jobs whose K fits one pass of the stream form share launches; the others, and those with so many rows that the
-    // tiled kernel is faster, go one by one.
+    // tiled kernel is faster, go one by one.  So does one that shares with nobody and would fill several launches: a call of its own is one, however many
+    // rows (1080 x 62 x 274 13.0 us in three, 4.7 tiled).  Of fewer rows the shared launch's records are the faster way in (376 x 192 x 2112
+    // replayed 4.7 us and 5.5 as a call of its own).
     tl::Gemm3Desc fused[64];
+    const tl_gemm_job* last = nullptr;
     int nf = 0;
     return tl::run_grouped(
         jobs, count,
         [](const tl_gemm_job& j) { return tl::tile3_choice(j.M, j.N, j.K); },
         [&](const tl_gemm_job& j) {
+            last = &j;
             fused[nf++] = tl::Gemm3Desc{static_cast<const __half*>(j.x), static_cast<const uint8_t*>(j.Wpacked),
                                         static_cast<__half*>(j.y), tl::half_bits_to_float(j.gamma_fp16_bits),
                                         j.M, j.N, j.K, static_cast<int64_t>(tl_row_stride_bytes(TL_FMT_1P6BIT, j.K))};
         },
         [&] {
-            const hipError_t e = nf ? tl::launch_gemv3_jobs(fused, nf, fx, s) : hipSuccess;
+            const int n = nf;
             nf = 0;
-            return tl::from_hip(e);
+            if (n == 1 && last->M > tl::kMaxBlocks3 * 16) return gemm_1p6(last->x, last->Wpacked, last->gamma_fp16_bits, last->y, last->M, last->N, last->K, stream, fx);
+            return tl::from_hip(n ? tl::launch_gemv3_jobs(fused, n, fx, s) : hipSuccess);
         },
         [&](const tl_gemm_job& j) { return gemm_1p6(j.x, j.Wpacked, j.gamma_fp16_bits, j.y, j.M, j.N, j.K, stream, fx); });
 }

@@ -634,8 +634,6 @@ Grouped3Fn<R> pick3_grouped(int T, bool any_k)
     }
 }
 
-constexpr int kMaxBlocks3 = 32;          // blocks of 16 activation rows per grouped launch
-
 }  // namespace
 
 hipError_t gemv3_init()

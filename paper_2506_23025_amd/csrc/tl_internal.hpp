@@ -123,6 +123,7 @@ struct Gemm3Desc {
     float gamma;
     int64_t M, N, K, stride;
 };
+constexpr int kMaxBlocks3 = 32;          // blocks of 16 activation rows per grouped launch
 bool gemv3_groups(int64_t M, int64_t N, int64_t K);
 // Workgroups of that many waves (one per half slice of 320 weights, 1..15) of its stream form that a launch puts on a CU, and what LDS each takes.
 int gemv3_per_cu(int waves, int* lds = nullptr);

@@ -48,3 +48,18 @@ def dev_u32(a):
     """uint32 numpy -> device tensor (torch has no uint32 arithmetic; int32 view carries the bits)."""
     import torch
     return torch.from_numpy(np.ascontiguousarray(a).view(np.int32)).cuda()
+
+
+def launches(call):
+    """Kernels that a call enqueues: the nodes of its graph."""
+    import ctypes
+    import torch
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    stream, graph, nodes = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
+    handle = ctypes.c_void_p(stream.cuda_stream)
+    assert hip.hipStreamBeginCapture(handle, 2) == 0       # relaxed
+    call(stream)
+    assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return nodes.value

@@ -6,7 +6,7 @@ import pytest
 import oracle
 import paper_2506_23025_amd as tl
 import synth_inputs as si
-from parity import assert_close, dev_u32, to_dev
+from parity import assert_close, dev_u32, launches, to_dev
 from test_tile_choice import STREAMS, TWO_BIT, runs, shares
 
 pytestmark = pytest.mark.gpu
@@ -95,21 +95,6 @@ def test_blocks_of_rows_in_one_launch(M, N, K):
     y = yd.cpu().numpy()
     assert (y[M * N:] == -21555).all()
     check(y[:M * N].view(np.float16).reshape(M, N), x, W, g, f"{M}x{N}x{K}")
-
-
-def launches(call):
-    """Kernels that a call enqueues: the nodes of its graph."""
-    import ctypes
-    import torch
-    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
-    stream, graph, nodes = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
-    handle = ctypes.c_void_p(stream.cuda_stream)
-    assert hip.hipStreamBeginCapture(handle, 2) == 0       # relaxed
-    call(stream)
-    assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
-    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0
-    assert hip.hipGraphDestroy(graph) == 0
-    return nodes.value
 
 
 # what one launch keeps of the sums of several passes is 32 tiles a workgroup, 8192 in all: jobs beyond that are two launches, not one for each block of 16 rows

@@ -6,7 +6,7 @@ import pytest
 import oracle
 import paper_2506_23025_amd as tl
 import synth_inputs as si
-from parity import assert_close, to_dev
+from parity import assert_close, launches, to_dev
 from test_tile_choice import ONE_POINT_SIX, STREAMS, runs, shares
 
 pytestmark = pytest.mark.gpu
@@ -122,3 +122,18 @@ def test_any_k_in_a_grouped_launch():
         y = yd.cpu().numpy().view(np.float16)
         check(y[clean], np.ascontiguousarray(x[clean]), W, g, f"{x.shape}")
         assert not np.isfinite(y[~clean].astype(np.float32)).any()
+
+
+# a grouped call of one job is one launch however many rows, and gives the bits of the call of its own; so is the one of several that the others leave alone
+@pytest.mark.parametrize("M,N,K,others", [(1080, 62, 274, []), (905, 16, 108, []), (1311, 832, 512, []), (600, 48, 1280, []), (600, 48, 1280, [(512, 14336, 4096)]), (512, 62, 273, []), (3, 100, 40, [])])
+def test_one_job(M, N, K, others):
+    tl.tl_init()
+    jobs = []
+    for m, n, k in [(M, N, K), *others]:
+        x, W, g = si.layer(47000 + m, m, n, k)
+        jobs.append((to_dev(x.view(np.int16)), to_dev(tl.tl_pack_1p6bit(W)), si.gamma_bits(g), to_dev(np.full((m, n), -21555, dtype=np.int16)), m, n, k))
+    ya = to_dev(np.full((M, N), -21555, dtype=np.int16))
+    tl.tl_ternary_gemm_1p6(*jobs[0][:3], ya, M, N, K)
+    tl.tl_ternary_gemm_1p6_grouped(jobs, tl.TL_FMT_1P6BIT)
+    assert np.array_equal(ya.cpu().numpy(), jobs[0][3].cpu().numpy())
+    assert launches(lambda stream: tl.tl_ternary_gemm_1p6_grouped(jobs, tl.TL_FMT_1P6BIT, stream)) == len(jobs)
