@@ -158,6 +158,14 @@ def test_scales_of_more_rows_than_one_launch_streams():
     assert instance(SCALES, 1311, 832, 512, 256) == -1
 
 
+def test_scales_of_short_k_at_more_than_16_rows():
+    # measured (us), streaming / tiled: 4.7 / 3.7, 4.7 / 3.7, 4.6 / 3.7, 4.3 / 3.6, 4.3 / 3.6, 4.2 / 3.5, 4.5 / 4.0; the other way round 4.0 / 4.6, 3.8 / 4.9, 3.8 / 5.0
+    for M, N, K, group in ((96, 2912, 64, 256), (305, 896, 64, 256), (30, 5948, 64, 256), (1572, 96, 128, 128), (493, 352, 128, 128), (641, 36, 128, 128), (29, 320, 256, 32)):
+        assert runs(SCALES, M, N, K, group) == TILED, (M, N, K, group)
+    for M, N, K, group in ((98, 112, 320, 128), (19, 1408, 448, 256), (64, 272, 448, 256)):
+        assert runs(SCALES, M, N, K, group) == STREAMS, (M, N, K, group)
+
+
 def test_one_point_six_bit_codes_of_more_rows_than_one_launch_streams():
     # measured (us), streaming, 4096 rows to a launch / tiled
     for M, N, K in ((29569, 20, 171), (14561, 37, 703), (10488, 62, 743), (24042, 62, 1251), (5936, 144, 107), (4872, 8, 354)):    # 36 / 16, 24 / 12, 21 / 12, 50 / 29, 12 / 7, 8 / 6
