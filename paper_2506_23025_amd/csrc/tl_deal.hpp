@@ -38,34 +38,38 @@ inline double deal_run_cost(const DealModel& m, const DealJob& j, int w)
     return double(j.passes) * (deal_run_time(m, (j.tiles + w - 1) / w) + j.start_up);
 }
 
-// fewest workgroups that finish job j by tau
-inline int deal_groups_for(const DealModel& m, const DealJob& j, double tau)
+// longest run that takes no more than `per`; 0 if one tile takes longer
+inline int deal_longest_run(const DealModel& m, double per)
 {
-    const double per = tau / double(j.passes) - j.start_up;
-    // longest run that fits: from the estimate with whole items, a few steps up or down
+    // from the estimate with whole items, a few steps up or down
     const double per_tile = m.item_cost ? (m.item_first + m.tile_extra * double(m.t_max - 1)) / double(m.t_max) : 1.0;
     int run = int(per / per_tile);
     if (run < 1) run = 1;
-    if (run > j.tiles) run = j.tiles;
     while (run > 1 && deal_run_time(m, run) > per) --run;
-    while (run < j.tiles && deal_run_time(m, run + 1) <= per) ++run;
-    if (deal_run_time(m, run) > per) return j.tiles;
-    const int w = (j.tiles + run - 1) / run;
-    return w < 1 ? 1 : (w > j.tiles ? j.tiles : w);
+    while (deal_run_time(m, run + 1) <= per) ++run;
+    return deal_run_time(m, run) > per ? 0 : run;
 }
 
-// Of every job the fewest workgroups that finish it by tau, and their sum.  The blocks of rows of one matrix follow each other and are alike but for the
-// last, so they are worked out once: 24 blocks of six matrices 26 -> 9 us of the host.
+// Of every job the fewest workgroups that finish it by tau, and their sum.  The longest run depends on a job's passes and start-up alone, in which the jobs
+// of a call are mostly alike: 24 blocks of six matrices 26 -> 2.2 us of the host, 16 matrices 8.2 -> 2.0.
 inline int deal_groups_of_all(const DealModel& m, const DealJob* jobs, int count, double tau, int* wg)
 {
-    int need = 0;
+    int need = 0, longest = 0;
     for (int j = 0; j < count; ++j) {
         const DealJob& a = jobs[j];
-        const bool alike = j > 0 && a.tiles == jobs[j - 1].tiles && a.passes == jobs[j - 1].passes && a.start_up == jobs[j - 1].start_up;
-        wg[j] = alike ? wg[j - 1] : deal_groups_for(m, a, tau);
+        if (j == 0 || a.passes != jobs[j - 1].passes || a.start_up != jobs[j - 1].start_up) longest = deal_longest_run(m, tau / double(a.passes) - a.start_up);
+        const int run = longest < a.tiles ? longest : a.tiles;
+        wg[j] = run < 1 ? a.tiles : (a.tiles + run - 1) / run;
         need += wg[j];
     }
     return need;
+}
+
+inline int deal_groups_for(const DealModel& m, const DealJob& j, double tau)
+{
+    int w;
+    deal_groups_of_all(m, &j, 1, tau, &w);
+    return w;
 }
 
 // wg[j] >= 1 workgroups for job j, G in all when the jobs hold at least G tiles (fewer jobs than G)
