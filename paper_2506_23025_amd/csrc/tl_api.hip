@@ -86,26 +86,33 @@ inline KernelChoice choice_2bit(int64_t M, int64_t N, int64_t K)
     if (K % 64 != 0) return tile_ragged_choice(M, N, K);
     KernelChoice c{gemv_supports(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!c.streams || M <= 16 || !mfma_supports(M, N, K)) return c;
-    c.stream = small_m_time(M, N, K);
+    const double apart = small_m_time(M, N, K);
     const bool two_blocks = gemv_two_blocks(M, N, K);
     const double passes = double((K + 4095) / 4096);
     if (passes == 1.0) c.launch = two_blocks ? 5.0 : 4.5;
     else if (!two_blocks && double((M + 15) / 16) * double((N + 15) / 16) >= 512.0) c.launch = 4.5;
     c.launches = double((M + (two_blocks ? 31 : 15)) / (two_blocks ? 32 : 16)) / 32.0;
-    c.fixed = c.launch * (c.launches > 1.0 ? double(int64_t(c.launches + 0.999)) : 1.0);
-    if (gemv_rows_form(M, N, K)) {
-        // a call of its own; in a shared launch it costs what it did: its part of one, and the rest of its time there
-        const double shared = c.stream - c.fixed + c.launch * c.launches;
-        c.stream = rows_form_time(M, N, K);
-        c.fixed = 3.0;
-        c.launches = shared > c.stream - c.fixed ? (shared - (c.stream - c.fixed)) / c.launch : 0.0;
-    }
+    // Less 1 us, by which a call of its own between others is longer than alone (ties went wrong by 2 us of 29 and 4 of 58 without; over 160 groups of 2 to 8
+    // alike jobs of M = 17 .. 1500 and K up to 8192 the way chosen takes 0.5 % longer than the better one, without 1.6 %).
+    c.own = apart - c.launch * (c.launches > 1.0 ? double(int64_t(c.launches + 0.999)) : 1.0) - 1.0;
+    c.stream = gemv_rows_form(M, N, K) ? rows_form_time(M, N, K) : apart;
     c.tiled = c.stream;
     // The one launch's time is the better known.  Below its fit, K < 512, both times are too long, the tiled kernel's the more (24 x 128 x 128 2.7 us
     // against 3.9, the one launch 3.4 against 4.05): over 253 such calls the one chosen is 0.2 % slower than the best, 6 % in one of a
     // hundred (with 1.03 2.2 and 23 %, with 0.9 0.4 and 11 %).
     const double band = !gemv_rows_form(M, N, K) ? 1.07 : K < 512 ? 0.95 : 1.03;
     if (band * mfma_at_least(K) <= c.stream) c.tiled = band * mfma_time(M, N, K);
+    return c;
+}
+
+// The same for a job of a call in which some K is no multiple of 64 (any_k), and which shares those jobs' launches.
+inline KernelChoice choice_2bit_among(int64_t M, int64_t N, int64_t K, bool any_k)
+{
+    KernelChoice c = choice_2bit(M, N, K);
+    if (any_k && K % 64 == 0 && c.stream > 0.0 && gemv_any_supports(M, N, K) && !gemv_two_blocks(M, N, K)) {
+        const double share = stream_any_share(M, N, K);
+        if (share > c.own) c.own = share;
+    }
     return c;
 }
 
@@ -139,11 +146,11 @@ tl_status run_grouped(const Job* jobs, int64_t count, Choice&& choice, Fuse&& fu
     for (int64_t first = 0; first < count; first += 64) {
         const int n = int(count - first < 64 ? count - first : 64);
         KernelChoice c[64];
-        bool tiled[64];
+        bool alone[64];
         for (int j = 0; j < n; ++j) c[j] = choice(jobs[first + j]);
-        choose_grouped(c, n, tiled);
+        choose_grouped(c, n, alone);
         for (int j = 0; j < n; ++j) {
-            if (c[j].streams && !tiled[j]) {
+            if (c[j].streams && !alone[j]) {
                 fuse(jobs[first + j]);
             } else {
                 const tl_status st = single(jobs[first + j]);
@@ -240,11 +247,13 @@ tl_status tl_ternary_gemm_grouped(const tl_gemm_job* jobs, int64_t count, void* 
         if (!tl::aligned16(j.x) || !tl::aligned16(j.Wpacked) || !tl::aligned16(j.y)) return TL_ERR_ALIGN;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Jobs the small-M kernel takes share launches; the others go through tl_ternary_gemm one by one.
+    // Jobs the small-M kernel takes share launches; the others, and those with so many rows that a call of their own is faster, go one by one.
     tl::GemmDesc fused[64];
     int nf = 0;
+    bool any_k = false;
+    for (int64_t i = 0; i < count; ++i) any_k = any_k || jobs[i].K % 64 != 0;
     return tl::run_grouped(
-        jobs, count, [](const tl_gemm_job& j) { return tl::choice_2bit(j.M, j.N, j.K); },
+        jobs, count, [any_k](const tl_gemm_job& j) { return tl::choice_2bit_among(j.M, j.N, j.K, any_k); },
         [&](const tl_gemm_job& j) {
             fused[nf++] = tl::GemmDesc{static_cast<const __half*>(j.x), static_cast<const uint32_t*>(j.Wpacked),
                                        static_cast<__half*>(j.y), tl::half_bits_to_float(j.gamma_fp16_bits), j.M, j.N, j.K};
@@ -339,8 +348,8 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
     }
     const bool fx = format == TL_FMT_1P6BIT_FX;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Jobs whose K fits one pass of the stream form share launches; the others, and those with so many rows that the
-    // tiled kernel is faster, go one by one.  So does one that shares with nobody and would fill several launches: a call of its own is one, however many
+    // Jobs whose K fits one pass of the stream form share launches; the others, and those with so many rows that a call of
+    // their own is faster, go one by one.  So does one that shares with nobody and would fill several launches: a call of its own is one, however many
     // rows (1080 x 62 x 274 13.0 us in three, 4.7 tiled).  Of fewer rows the shared launch's records are the faster way in (376 x 192 x 2112
     // replayed 4.7 us and 5.5 as a call of its own).
     tl::Gemm3Desc fused[64];
@@ -377,8 +386,8 @@ tl_status tl_ternary_gemm_gs_grouped(const tl_gemm_gs_job* jobs, int64_t count, 
         if (!tl::aligned16(j.x) || !tl::aligned16(j.Wpacked) || !tl::aligned16(j.scales) || !tl::aligned16(j.y)) return TL_ERR_ALIGN;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Jobs the weight-streaming kernel takes share launches; the others, and those with so many rows that the tiled
-    // kernel is faster, go one by one.
+    // Jobs the weight-streaming kernel takes share launches; the others, and those with so many rows that a call of
+    // their own is faster, go one by one.
     tl::GemmGsDesc fused[64];
     int nf = 0;
     return tl::run_grouped(
@@ -419,19 +428,21 @@ __attribute__((visibility("default"))) int tl_internal_tile_instance(int form, i
     }
 }
 
-// Likewise: per job of a grouped call (M, N, K, group each) 1 where the tiled kernel takes it though the streaming one could, 0 where it shares the
-// streaming kernel's launches, and -1 where that kernel cannot take it and it runs as a call of its own.
+// Likewise: per job of a grouped call (M, N, K, group each) 0 where it shares the streaming kernel's launches, 1 and 2 where it runs as a call of its own
+// though it could, tiled and streaming, and -1 where that kernel cannot take it.
 __attribute__((visibility("default"))) void tl_internal_grouped_tiled(int form, const int64_t* jobs, int count, int* out)
 {
     tl::KernelChoice c[64];
-    bool tiled[64];
+    bool alone[64];
     if (count > 64) count = 64;
+    bool any_k = false;
+    for (int j = 0; j < count; ++j) any_k = any_k || jobs[4 * j + 2] % 64 != 0;
     for (int j = 0; j < count; ++j) {
         const int64_t M = jobs[4 * j], N = jobs[4 * j + 1], K = jobs[4 * j + 2], group = jobs[4 * j + 3];
-        c[j] = form == 0 ? tl::choice_2bit(M, N, K) : (form == 1 ? tl::tile3_choice(M, N, K) : tl::tile_gs_choice(M, N, K, group));
+        c[j] = form == 0 ? tl::choice_2bit_among(M, N, K, any_k) : (form == 1 ? tl::tile3_choice(M, N, K) : tl::tile_gs_choice(M, N, K, group));
     }
-    tl::choose_grouped(c, count, tiled);
-    for (int j = 0; j < count; ++j) out[j] = c[j].streams ? (tiled[j] ? 1 : 0) : -1;
+    tl::choose_grouped(c, count, alone);
+    for (int j = 0; j < count; ++j) out[j] = !c[j].streams ? -1 : !alone[j] ? 0 : c[j].tiled < c[j].stream ? 1 : 2;
 }
 
 // Likewise: jobs_by_table.

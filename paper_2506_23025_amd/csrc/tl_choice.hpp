@@ -1,44 +1,47 @@
-// Which jobs of a grouped call go through the tiled kernel, and how a shared launch hands its jobs out (host side; plain C++).
+// Which jobs of a grouped call share launches, and how a shared launch hands its jobs out (host side; plain C++).
 #pragma once
 
 #include <cstdint>
 
 namespace tl {
 
-// A job's alternatives.  Times in us, of a call of its own.
+// A job's alternatives.  Times in us; 0 throughout where the streaming kernel is the one whatever the others take (few rows).
 struct KernelChoice {
     bool streams;          // the weight-streaming kernel can take it and shares its launches with other jobs
-    double stream;         // time there
-    double fixed;          // what of that its launches cost whatever they hold
-    double launch;         // the same of one launch shared with others
-    double launches;       // how many of those it would fill (blocks of rows over blocks per launch)
-    double tiled;          // time in the tiled kernel, the caller's band included; as much as `stream` or more where it cannot win
+    double stream;         // a call of its own there
+    double tiled;          // a call of its own in the tiled kernel, the caller's band included; as much as `stream` or more where it cannot win
+    double own;            // what it adds to the launches that it shares, beside its part of
+    double launch;         // what one of those costs whatever it holds
+    double launches;       // how many of them it would fill (blocks of rows over blocks per launch)
 };
 
-// A job of a shared launch pays only for the part of the launch that it fills, while a launch of the tiled kernel serves one job.  So a job
-// is tiled if that beats its streaming time less the launch it shares (16 layers of 512 x 1024 at M = 256, choosing as if alone 83 us, like this
-// 65; the linears of a block at M = 48 with groups of 128 72 and 65); and what is left streams, unless it is so little that it would
-// not pay for its launch.  tiled[j] implies that job j alone would be tiled too; with one job it is just that.
-constexpr double kBetween = 1.0;                           // a launch of its own between others, us (ties went wrong by 2 us of 29 and 4 of 58 without)
-
-inline void choose_grouped(const KernelChoice* c, int n, bool* tiled)
+// Which jobs of a grouped call run as calls of their own though they could share launches.  A job that shares pays only for the part of the launch that
+// it fills, which is what makes small ones cheap (16 layers of 512 x 1024 at M = 256, choosing as if alone 83 us, sharing 65; the linears of a block
+// at M = 48 with groups of 128 72 and 65); but shared launches hold 512 rows and mostly one workgroup per CU, where a call of its own is one launch of as many
+// as fit, or the tiled kernel's.  So a job leaves if its call is shorter than what it adds; and what is left shares, unless it is so little
+// that it would not pay for its launch.  A job alone is a call of its own, tiled or not.
+inline void choose_grouped(const KernelChoice* c, int n, bool* alone)
 {
-    double rest = 0.0, all = 0.0, launch = 0.0, launches = 0.0;
+    if (n == 1) { alone[0] = c[0].streams && c[0].tiled < c[0].stream; return; }
+    double rest = 0.0, all = 0.0, launch = 0.0, launches = 0.0, total = 0.0;
     bool any = false, can = true;
+    for (int j = 0; j < n; ++j) total += c[j].launches;
+    const double spared = total > 1.0 ? 1.0 - 1.0 / total : 0.0;       // the first launch is not
     for (int j = 0; j < n; ++j) {
-        if (!c[j].streams) { tiled[j] = false; continue; }
-        const double own = c[j].stream - c[j].fixed, shared = own + c[j].launch * c[j].launches;
-        tiled[j] = n > 1 ? c[j].tiled + kBetween < shared && c[j].tiled < c[j].stream : c[j].tiled < c[j].stream;
-        if (tiled[j]) continue;
+        alone[j] = false;
+        if (!c[j].streams) continue;
+        const double call = c[j].tiled < c[j].stream ? c[j].tiled : c[j].stream;
+        alone[j] = call < c[j].own + spared * c[j].launch * c[j].launches;
+        if (alone[j]) continue;
         any = true;
-        can = can && c[j].tiled < c[j].stream;
-        rest += own;
-        all += c[j].tiled;
+        can = can && c[j].stream > 0.0;
+        rest += c[j].own;
+        all += call;
         launches += c[j].launches;
         if (c[j].launch > launch) launch = c[j].launch;
     }
     if (!any || !can || all >= rest + launch * (launches > 1.0 ? launches : 1.0)) return;
-    for (int j = 0; j < n; ++j) tiled[j] = c[j].streams;
+    for (int j = 0; j < n; ++j) alone[j] = c[j].streams;
 }
 
 // How the workgroups of a shared launch of the 2-bit streaming kernel find their jobs, when K is one pass: in a table of jobs (1 KB of arguments, two

@@ -143,6 +143,7 @@ hipError_t launch_tile3(const __half* x, const uint8_t* Wp, int64_t stride, floa
 
 // Tiled matrix-core kernel for 2-bit words and a K that is no multiple of 64, and whether it beats the streaming and the plain kernel.
 KernelChoice tile_ragged_choice(int64_t M, int64_t N, int64_t K);
+double stream_any_share(int64_t M, int64_t N, int64_t K);
 bool tile_ragged_preferred(int64_t M, int64_t N, int64_t K);
 hipError_t launch_tile_ragged(const __half* x, const uint32_t* Wp, float gamma, __half* y,
                               int64_t M, int64_t N, int64_t K, hipStream_t s);

@@ -88,9 +88,15 @@ KernelChoice tile3_choice(int64_t M, int64_t N, int64_t K)
     KernelChoice c{gemv3_groups(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (M <= 16 || K < 8 || K > (int64_t(1) << 24) || M > (int64_t(1) << 24) || N > (int64_t(1) << 24)) return c;
     c.stream = over_stream_launches(M, [&](int64_t m) { return stream3_time(m, N, K); });
-    c.launch = c.streams ? 3.8 : 0.0;
-    c.fixed = c.launch * double((M + kStreamRows - 1) / kStreamRows);
-    c.launches = double((M + 15) / 16) / 32.0;
+    if (c.streams) {
+        // In shared launches: fitted to 480 groups of 2 to 8 alike jobs of M = 17 .. 1500, N = 64 .. 8192, K = 64 .. 4800, 7 % on average.  The way chosen there takes
+        // 0.7 % longer than the better one; counted as in a launch of its own 13 %, up to 2.8 times.
+        constexpr double per_tile[16] = {0, 0.304, 0.242, 0.24, 0.263, 0.336, 0.395, 0.444, 0.543, 0.647, 0.74, 0.76, 0.8, 0.929, 0.974, 1.161};
+        const double blocks = double((M + 15) / 16);
+        c.launch = 4.63;
+        c.launches = blocks / 32.0;
+        c.own = blocks * double((N + 15) / 16) / 256.0 * per_tile[(((K + 4) / 5 + 15) / 16 + 3) / 4];
+    }
     c.tiled = c.stream;
     if (K % 8 != 0) {
         if (K < 64) {                                      // below the fit: tiles, as far as anything was measured a third either way

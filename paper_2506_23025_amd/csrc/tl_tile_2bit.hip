@@ -94,6 +94,17 @@ static double stream_any_time(int64_t M, int64_t N, int64_t K)
     return 4.33 + w * p * (0.911 + 0.178 * m) + xt * (0.049 * double(s) + 0.344 * p);
 }
 
+// What a job of more than 16 rows adds to shared launches of that form, which have one workgroup per CU: fitted to 320 groups of 2 to 8 alike jobs of
+// M = 17 .. 1500, N = 64 .. 8192, K = 64 .. 8192, 10 % on average.  The way chosen there takes 1.0 % longer than the better one; counted as in a
+// launch of its own 9 %, up to 2.8 times.
+double stream_any_share(int64_t M, int64_t N, int64_t K)
+{
+    constexpr double per_tile[9] = {0, 0.58, 0.51, 0.55, 0.585, 0.72, 0.9, 0.865, 0.97};
+    const int64_t s = (K + 511) / 512, p = (s + 7) / 8;
+    const double blocks = double((M + 15) / 16), x = blocks * double((N + 15) / 16) / 256.0;
+    return s <= 8 ? per_tile[s] * x : 0.133 * double(s) * x + 3.08 * double(p) * blocks / 32.0;
+}
+
 // Tiled or weight-streaming kernel for K that is no multiple of 64.  Fitted, with the tiles' times, to 1300 calls of M = 17 .. 2048 and 600 of fewer rows, N = 512
 // .. 16384, K = 64 .. 14336, weights out of the caches; on as many others the one chosen is 0.8 % slower than the best (13 % in one of a
 // hundred) and 0.2 % (6 %).  Up to 4 rows the streaming kernel was the fastest in all.
@@ -102,8 +113,9 @@ KernelChoice tile_ragged_choice(int64_t M, int64_t N, int64_t K)
     KernelChoice c{gemv_any_supports(M, N, K), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!c.streams || M <= 4) return c;
     c.stream = stream_any_time(M, N, K);
-    c.fixed = c.launch = 3.0;
+    c.launch = 4.2;
     c.launches = double((M + 15) / 16) / 32.0;
+    c.own = M <= 16 ? c.stream - 3.0 : stream_any_share(M, N, K);
     c.tiled = c.stream;
     if (tile_at_least(kRaggedCost, kRagged, K) < c.stream) pick_ragged(M, N, K, &c.tiled);
     return c;

@@ -62,16 +62,20 @@ int pick(int64_t M, int64_t N, int64_t K, int64_t group, double* us)
 // slices; w workgroups to a CU and xt tiles to a CU (as in launch_lean_rows).  A line each for groups of 256s, 128s, 64s and 32s.  Fitted, with
 // the tiles' times, to 2500 calls over M = 1 .. 2048, N = 512 .. 16384, K = 512 .. 14336 and 1500 with K no multiple of 64, weights out of the caches:
 // 14 % for nine in ten, and the one chosen is 0.3 % slower than the best on average, 10 % in one of a hundred.
-static double stream_gs_time(int64_t M, int64_t N, int64_t K, int64_t group)
+struct StreamLine { double start, row, row_slice, per_tile[9], start_p, pass, pass_row, tile_slice, tile_pass; };
+static const StreamLine& stream_line(int64_t group)
 {
-    struct Line { double start, row, row_slice, per_tile[9], start_p, pass, pass_row, tile_slice, tile_pass; };
-    static constexpr Line lines[4] = {
+    static constexpr StreamLine lines[4] = {
         {3.19, 0.042, 0.006, {0, 0.14, 0.225, 0.368, 0.448, 0.711, 0.748, 0.757, 0.843}, 2.74, 0.933, 0.102, 0.062, 0.386},
         {3.23, 0.053, 0.004, {0, 0.147, 0.244, 0.399, 0.462, 0.759, 0.792, 0.841, 0.929}, 2.91, 0.873, 0.106, 0.052, 0.459},
         {3.2, 0.051, 0.004, {0, 0.164, 0.273, 0.452, 0.538, 0.88, 0.927, 1.014, 1.074}, 3.42, 0.536, 0.131, 0.102, 0.473},
         {3.42, 0.061, 0.0, {0, 0.24, 0.399, 0.69, 0.756, 1.35, 1.405, 1.505, 1.473}, 2.59, 1.093, 0.07, 0.1, 0.803},
     };
-    const Line& c = lines[group % 256 == 0 ? 0 : group % 128 == 0 ? 1 : group % 64 == 0 ? 2 : 3];
+    return lines[group % 256 == 0 ? 0 : group % 128 == 0 ? 1 : group % 64 == 0 ? 2 : 3];
+}
+static double stream_gs_time(int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    const StreamLine& c = stream_line(group);
     const int64_t s = (K + 511) / 512, tiles = (N + 15) / 16, b = (M + 15) / 16;
     const double m = double(M < 16 ? M : 16);
     int64_t share = 256 * (8 / (s < 8 ? s : 8)) / b;
@@ -117,12 +121,17 @@ KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group)
     KernelChoice c{gemv_gs_supports(M, N, K, group), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!c.streams || M <= 16) return c;
     c.stream = over_stream_launches(M, [&](int64_t m) { return stream_gs_time(m, N, K, group); });
-    c.launch = 3.2;
-    c.fixed = c.launch * double((M + kStreamRows - 1) / kStreamRows);
-    // In a shared launch it has a part of 256 workgroups, which for K of up to four slices leave wavefronts out: 1.15 to 1.2 times as long up
-    // to 64 rows, 1.2 to 1.5 times up to 512 (250 calls both ways).
-    const double blocks = double((M + 15) / 16), crowd = K > 2048 ? 0.0 : blocks > 4.0 ? 0.3 : 0.15;
-    c.launches = blocks / 32.0 + crowd * (c.stream - c.fixed) / c.launch;
+    // In shared launches, which mostly have one workgroup per CU, so that with few slices of K wavefronts are left out: fitted to 600 groups of 2 to 8 alike
+    // jobs of M = 17 .. 1500, N = 64 .. 8192, K = 64 .. 8192, 11 % on average.  The way chosen there takes 1.5 % longer than the better one;
+    // counted as 1.15 to 1.3 times as long as in a launch of its own 9 %, up to 3.7 times.
+    const StreamLine& line = stream_line(group);
+    const int64_t s = (K + 511) / 512, p = (s + 7) / 8;
+    constexpr double crowd[9] = {0, 4.31, 2.62, 1.6, 1.56, 1.12, 1.24, 1.1, 1.1};
+    const double blocks = double((M + 15) / 16);
+    c.launch = 4.16;
+    c.launches = blocks / 32.0;
+    const double x = blocks * double((N + 15) / 16) / 256.0;
+    c.own = s <= 8 ? crowd[s] * line.per_tile[s] * x : 1.18 * (line.tile_slice * double(s) + line.tile_pass * double(p)) * x + 2.84 * double(p) * c.launches;
     c.tiled = c.stream;
     // Below the fit, K < 512, both times are too long, the tiled kernel's by 36 % at K = 64 and 10 % at 448 (96 x 64 x 2912 3.7 us, streaming 4.7; 1572 x 128 x
     // 96 3.6 and 4.3).  Over 384 such calls the one chosen is 0.2 % slower than the best, 7 % in one of a hundred (without the factors 6.7 and 31 %).

@@ -37,7 +37,7 @@ def _of_jobs(form, jobs):
 
 
 def grouped(form, jobs):
-    """Per job (M, N, K[, group]) of a grouped call, whether the tiled kernel takes it from the launches the others share."""
+    """Per job (M, N, K[, group]) of a grouped call, whether the tiled kernel takes it from the launches that others share."""
     return [v == 1 for v in _of_jobs(form, jobs)]
 
 
@@ -72,7 +72,7 @@ def test_a_call_is_told_from_those_of_other_kernels():
     assert runs(SCALES, 16, 4096, 4096, 128) == STREAMS and runs(SCALES, 16, 4096, 4096, 16) == TILED and runs(SCALES, 1, 1, 5344, 128) == PLAIN
     assert shares(SCALES, [(16, 4096, 4096, 128), (16, 4096, 4096, 16), (16, 4099, 4096, 128), (2, 300, 777, 32)]) == [True, False, False, False]
     assert runs(TWO_BIT, 16, 4099, 4090) == STREAMS and runs(TWO_BIT, 2000, 2050, 33) == TILED and runs(TWO_BIT, 1, 16, 7) == PLAIN
-    assert shares(TWO_BIT, [(16, 4099, 4090), (16, 4099, 63)]) == [True, False]
+    assert shares(TWO_BIT, [(16, 4099, 4090), (9, 4099, 4090), (16, 4099, 63)]) == [True, True, False]
     assert runs(ONE_POINT_SIX, 16, 4096, 4096) == STREAMS and runs(ONE_POINT_SIX, 512, 14336, 4096) == TILED and runs(ONE_POINT_SIX, 1, 16, 7) == PLAIN
     assert shares(ONE_POINT_SIX, [(16, 4096, 4800), (16, 4096, 4801), (16, 4096, 63), (17, 4096, 63)]) == [True, False, True, False]
 
@@ -216,3 +216,16 @@ def test_grouped_jobs_share_launches_where_that_is_faster():
                 alone = instance(form, M, N, K, group) >= 0
                 assert grouped(form, [(M, N, K, group)]) == [alone], (form, M, N, K)
                 assert alone or not any(grouped(form, [(M, N, K, group)] * 5)), (form, M, N, K)
+
+
+def test_jobs_of_many_rows_leave_the_shared_launches():
+    # measured (us), 2 to 8 alike jobs that share launches / as calls of their own: 2-bit words 43.4 / 16.5, 16.0 / 13.9; scales 64.4 / 36.0, 20.1 / 12.0; 1.6-bit
+    # codes 75.4 / 65.7 and 30.6 / 25.4 (two of several); and the other way round 5.1 / 13.4, 8.2 / 9.5, 8.0 / 16.4, and of different ones 22.4 / 27.9
+    assert not any(shares(TWO_BIT, [(834, 2624, 128), (834, 6054, 488)]))
+    assert not shares(TWO_BIT, [(57, 96, 208), (302, 3520, 64)])[1]                    # K = 64 in the form for any K: 15.7 / 8.1
+    for form, n, job in ((TWO_BIT, 4, (1479, 80, 512)), (TWO_BIT, 2, (506, 272, 453)), (SCALES, 2, (787, 4128, 273, 64)),
+                         (SCALES, 2, (131, 4672, 164, 128)), (ONE_POINT_SIX, 4, (835, 2432, 80)), (ONE_POINT_SIX, 2, (1197, 272, 1071))):
+        assert not any(shares(form, [job] * n)), (form, job)
+    assert all(shares(SCALES, [(33, 8032, 640, 256), (33, 10312, 8064, 256)])) and all(shares(ONE_POINT_SIX, [(2, 3200, 136), (445, 208, 384)]))
+    for form, n, job in ((TWO_BIT, 4, (99, 272, 318)), (SCALES, 2, (70, 2176, 576, 32)), (ONE_POINT_SIX, 4, (129, 350, 400))):
+        assert all(shares(form, [job] * n)), (form, job)
