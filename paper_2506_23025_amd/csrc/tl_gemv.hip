@@ -2362,17 +2362,23 @@ hipError_t launch_gemv_jobs(const GemmDesc* jobs, int count, hipStream_t s)
     bool any_k = false;
     for (int i = 0; i < count; ++i) any_k = any_k || jobs[i].K % 64 != 0;
     if (any_k) {
-        // a job of such a K, and with it those that would share a launch of blocks of 16 rows anyway: a launch of its own costs it more than the form for
-        // any K costs its neighbours.  Over 120 calls of 1 to 50 aligned jobs (M = 1 .. 64, K = 512 .. 11008) and one or two of such K 0.68 of the time
-        // of the aligned jobs' own launches and the tiled kernel's for the others up to 40 jobs, 0.87 at 8 to 50; the slowest two 1.007 (215 and 156 us).
+        // A job of such a K, and with it those that would share a launch of blocks of 16 rows anyway: a launch of its own costs it more than the form for any K
+        // costs its neighbours (270 calls of 1 to 50 aligned jobs, M = 1 .. 64, K = 512 .. 11008, with one or two of such K 0.72 of the time of the aligned
+        // jobs' own launches and the tiled kernel's for the others, the slowest 1.03).  But not those of K up to 2048 if all do not fit one launch, since launches of their own hold more
+        // workgroups than that form's records: 38 jobs of 64 rows, K = 512, with one of K = 1296 182 us apart, 214 together.
         constexpr int kAtOnce = 64;
         AnyJob mixed[kAtOnce];
         GemmDesc rest[kAtOnce];
         for (int first = 0; first < count; first += kAtOnce) {
+            const int last = count - first < kAtOnce ? count : first + kAtOnce;
+            auto with_them = [](const GemmDesc& d) { return d.K % 64 != 0 || (gemv_any_supports(d.M, d.N, d.K) && !gemv_two_blocks(d.M, d.N, d.K)); };
+            int64_t blocks = 0;
+            for (int i = first; i < last; ++i)
+                if (with_them(jobs[i])) blocks += (jobs[i].M + 15) / 16;
             int m = 0, r = 0;
-            for (int i = first; i < count && i < first + kAtOnce; ++i) {
+            for (int i = first; i < last; ++i) {
                 const GemmDesc& d = jobs[i];
-                if (d.K % 64 != 0 || (gemv_any_supports(d.M, d.N, d.K) && !gemv_two_blocks(d.M, d.N, d.K)))
+                if (d.K % 64 != 0 || ((d.K > 2048 || blocks <= kMaxJobs) && with_them(d)))
                     mixed[m++] = AnyJob{d.x, d.W, nullptr, d.y, d.gamma, d.M, d.N, d.K, 0};
                 else
                     rest[r++] = d;

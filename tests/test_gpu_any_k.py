@@ -115,3 +115,20 @@ def test_launches_of_long_runs(specs, most):
     tl.tl_ternary_gemm_grouped(jobs)
     for (yd, x, W, g), (M, N, K) in zip(want, specs):
         check(yd.cpu().numpy().view(np.float16).reshape(M, N), x, W, g, f"{M}x{N}x{K}")
+
+
+# Aligned jobs of short K that fill launches of their own leave those to them, since the form for any K has fewer workgroups there; others share its launches
+@pytest.mark.parametrize("specs,count", [([(64, 32, 512)] * 9 + [(64, 15, 1296 + 1)], 3), ([(64, 32, 512)] * 7 + [(64, 15, 1296 + 1)], 1), ([(16, 48, 4096)] * 40 + [(16, 15, 1001)], 2)])
+def test_launches_beside_aligned_jobs(specs, count):
+    tl.tl_init()
+    jobs, want = [], []
+    for i, (M, N, K) in enumerate(specs):
+        x, W, g = si.layer(52000 + i, M, N, K)
+        yd = to_dev(np.full(M * N, -21555, dtype=np.int16))
+        jobs.append((to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), si.gamma_bits(g), yd, M, N, K))
+        want.append((yd, x, W, g))
+    assert all(shares(TWO_BIT, specs))
+    assert launches(lambda stream: tl.tl_ternary_gemm_grouped(jobs, stream)) == count
+    tl.tl_ternary_gemm_grouped(jobs)
+    for (yd, x, W, g), (M, N, K) in zip(want, specs):
+        check(yd.cpu().numpy().view(np.float16).reshape(M, N), x, W, g, f"{M}x{N}x{K}")
