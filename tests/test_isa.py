@@ -166,3 +166,24 @@ def test_matrix_instructions_wait_for_their_operands(tmp_path):
         total += count
         assert not found, f"{len(found)} of {count} matrix instructions read an operand too early, first: {found[0]}"
     assert total > 0, "no matrix instruction in the library"
+
+
+@pytest.mark.skipif(OBJDUMP is None, reason="no llvm-objdump")
+def test_operands_of_a_pass_are_built_in_one_place(tmp_path):
+    # the streaming kernel of several passes, items of one tile: three copies of an item, 16 products each, and 16 for the sums over x.  Built in two places
+    # (32), the operands were copied from one to the other in every pass
+    lib = str(tmp_path / "lib.so")
+    shutil.copy(tl.LIB_PATH, lib)
+    subprocess.run([OBJDUMP, "--offloading", lib], cwd=tmp_path, check=True, capture_output=True)
+    counts = {}
+    for f in sorted(f for f in os.listdir(tmp_path) if "gfx950" in f):
+        kernel = None
+        for line in subprocess.run([OBJDUMP, "-d", f], cwd=tmp_path, check=True, capture_output=True, text=True).stdout.splitlines():
+            m = re.match(r"^[0-9a-f]+ <(.+)>:", line)
+            if m:
+                kernel = m[1] if re.search(r"gemv_lean_kernelILi1ELb1ELi(0|256)E", m[1]) else None
+                if kernel:
+                    counts[kernel] = 0
+            elif kernel and "v_mfma" in line:
+                counts[kernel] += 1
+    assert len(counts) >= 8 and set(counts.values()) == {64}, counts
