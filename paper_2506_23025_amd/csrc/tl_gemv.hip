@@ -984,11 +984,11 @@ __device__ __forceinline__ void store_quad_any(__attribute__((address_space(1)))
 // two passes, took 12.5 us and the general form 11.1; now 11.3; 65 rows of 11648 x 4480 25.3, 23.6 and 22.3).
 // GS = 256: group scales, groups of whole units of 256 weights (half a slice).  The halves of a tile are summed one after the
 // other in the same accumulators, each scaled by its group's scales of the lane's four output rows, which are
-// requested with the tile's weights (block at M = 1 / 4 / 16 15.0 / 15.5 / 18.0 us).
+// requested with the tile's weights (block at M = 1 / 4 / 16 14.5 / 14.3 / 17.1 us).
 // GS = 128, 64, 32: groups of multiples of as many.  In the order above a product's 32 weights come from four chunks of 64, so a unit's sum
 // would never stand alone in an accumulator; here a lane takes a word of every chunk (32: half a word), and 64 (32) weights are two products (one).
 // What bounds them is the scaling of every unit's sum on the vector ALU, 4 operations for 16 x 16 outputs beside the 11 (32: 13) of the decode per
-// product pair (product): block at M = 4 15.6 / 18.5 / 24.5 us with groups of 128 / 64 / 32, decode sweep 21.5 / 24.6 / 36.2.  Groups of 128 took
+// product pair (product): block at M = 4 15.2 / 17.3 / 24.7 us with groups of 128 / 64 / 32, decode sweep 21.0 / 24.3 / 36.5.  Groups of 128 took
 // 25.8 and 36.5 in the general form, every product issued twice with other lanes masked off; the others went to the tiled kernel one by one, 68
 // and 131 us.
 // GS, several jobs: an N that is a multiple of 4 as well; through ANY such a launch, its x in registers, took up to 13 % longer (block of 8 rows, 1088 wide,
@@ -1794,7 +1794,7 @@ LeanFn<Args> pick_lean(int T)
     switch (T) {
         case 1: return gemv_lean_kernel<1, PASSES, GS, ANY, Args>;
         case 2: return gemv_lean_kernel<2, PASSES, GS, ANY, Args>;
-        default: return gemv_lean_kernel<PASSES && GS == 64 ? 2 : 3, PASSES, GS, ANY, Args>;   // see lean_passes_tiles
+        default: return gemv_lean_kernel<3, PASSES, GS, ANY, Args>;
     }
 }
 
@@ -1912,10 +1912,6 @@ int tiles_per_item(int run, int NW)
     return T < NW ? T : NW;
 }
 
-// Groups of 64s hold a seed for each of a slice's eight units: with several passes and 3 tiles 20 registers spill (block at M = 1 / 4 / 16 22.0 / 22.0 / 24.7
-// us, with 2 tiles 18.9 / 18.5 / 21.9).
-int lean_passes_tiles(int T, int gs) { return gs == 64 && T > 2 ? 2 : T; }
-
 // rows: 0, or the rows of a call of any K and N
 template <class Args>
 LeanFn<Args> pick_longk(int T, int rows)
@@ -1962,7 +1958,7 @@ hipError_t launch_lean_rows(const __half* x, const uint32_t* W, float gamma, con
     const int64_t longest = slices > NW ? kStreamMaxRun : (int64_t(1) << 31) / int64_t(packed_tile_bytes(int(K)));   // a run's kept sums, its bytes
     if (share < (tiles + longest - 1) / longest) share = (tiles + longest - 1) / longest;
     const int groups = share < 1 ? 1 : (tiles < share ? tiles : int(share));
-    const int run = (tiles + groups - 1) / groups, t = tiles_per_item(run, NW), T = slices > NW ? lean_passes_tiles(t, gs) : t;
+    const int run = (tiles + groups - 1) / groups, T = tiles_per_item(run, NW);
     const LeanAny args{one_job(W, x, y, gamma, int(K), int(N), int(M), tiles, groups, scales, group_inv)};
     const int kept = slices > NW ? run : 0;
     if (!any && gs == 256 && blocks == 1) {                // spares 0.1 us of working out which block
@@ -2100,7 +2096,6 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
         if (T < 1) return hipErrorInvalidValue;
     }
     if (T < 1) T = 1;
-    if (multi_pass) T = lean_passes_tiles(T, gs);
     // The lean kernel takes the launch when every job has at least one slice per wave (more: several passes), N is a
     // multiple of 16 throughout and the workgroups fit its record table; with scales else its form for any K and N.  (The linears of a block, K = 4096 three times
     // and 11008, against the general form: M = 1 14.05 -> 13.2, M = 4 14.2 -> 13.9, M = 16 17.6 -> 16.2-16.7 us.)
