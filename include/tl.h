@@ -190,7 +190,7 @@ tl_status tl_ternary_gemm_path(const void* x, const void* Wpacked, uint16_t gamm
  * another writes, and jobs must not alias
  * each other's outputs; they are enqueued in as few kernel launches as possible (jobs that
  * go to the small-M kernel share launches, 32 blocks of 16 or 32 activation rows per launch; a
- * job of many rows goes to the tiled kernel where that pays for a launch of its own) and
+ * job of many rows runs as tl_ternary_gemm would run it where that is faster) and
  * may run concurrently.  `jobs` is host memory, read before the call returns.
  */
 typedef struct tl_gemm_job {
@@ -246,7 +246,7 @@ tl_status tl_ternary_gemm_gs(const void* x, const void* Wpacked, const void* sca
  * tl_ternary_gemm_1p6_grouped: weights in the 1.6-bit layout (Sec. 3.2), all jobs in the same
  * byte code: `format` is TL_FMT_1P6BIT (tl_pack_1p6bit) or TL_FMT_1P6BIT_FX (tl_pack_1p6bit_fx),
  * anything else is TL_ERR_VALUE.  Jobs with 8 <= K <= 4800 share launches (32 blocks
- * of 16 activation rows per launch) unless they have so many rows that the tiled kernel is faster, or more
+ * of 16 activation rows per launch) unless they have so many rows that a call of their own is faster, or more
  * than 16 and a K below 64 that is no multiple of 8; the others run as tl_ternary_gemm_1p6 / _fx would run them.
  */
 tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl_format format,
@@ -256,7 +256,7 @@ tl_status tl_ternary_gemm_1p6_grouped(const tl_gemm_job* jobs, int64_t count, tl
  * tl_ternary_gemm_gs_grouped: 2-bit weights with per-group scales (Sec. 3.3; App. G), one group
  * size per job.  Jobs that tl_ternary_gemm_gs would run in the weight-streaming kernel share
  * launches (groups that are multiples of 256 weights among themselves, and so other multiples of 128, of
- * 64 and of 32); the others run one by one.
+ * 64 and of 32) unless they have so many rows that a call of their own is faster; the others run one by one.
  */
 typedef struct tl_gemm_gs_job {
     const void* x;            /* device, fp16 [M][K]                         */
