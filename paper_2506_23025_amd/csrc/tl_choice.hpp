@@ -44,17 +44,19 @@ inline void choose_grouped(const KernelChoice* c, int n, bool* alone)
     for (int j = 0; j < n; ++j) alone[j] = c[j].streams;
 }
 
-// How the workgroups of a shared launch of the 2-bit streaming kernel find their jobs, when K is one pass: in a table of jobs (1 KB of arguments, two
+// How the workgroups of a shared launch of the 2-bit streaming kernel find their jobs, when K is one pass: in a table of jobs (68 bytes of arguments each, two
 // scalar look-ups in turn) or each in a record of its own (16 KB).  records: whether the launch can do without the table; several: more workgroups
 // than CUs; w_bytes: its packed words; captured: it becomes part of a graph.
 // The records cost the host 1.1 us, which is what a small call waits for.  The look-ups cost the device 0.2 to 0.5 us where a CU holds one workgroup,
 // nothing where it holds several.  So the table takes launches below 8 MB (two layers of 2048 x 2048 called in a loop 5.4 -> 4.3 us, 4096 x 4096 5.6 ->
 // 4.8; 18 x 4672 x 4096, 9.1 MB, 5.6 and by the table 5.9), but not under capture, since a replay pays nothing for arguments (the three 3.1, 4.6 and
 // 5.1 us, by the table 3.3, 5.0 and 5.5), unless there are several workgroups to a CU.
-constexpr int kTableJobs = 16;
+// A launch that cannot do without it, of group scales and more than 256 workgroups, has as many jobs as a launch holds: the form for any K and N, with
+// records for 256, leaves wavefronts out (block of 174 rows, 1024 wide with groups of 256, 17.7 -> 22.0 us).
+constexpr int kTableJobs = 16, kTableMost = 32;
 inline bool jobs_by_table(int count, bool one_pass, bool records, bool several, int64_t w_bytes, bool captured)
 {
-    if (!one_pass || count < 2 || count > kTableJobs) return false;
+    if (!one_pass || count < 2 || count > (records ? kTableJobs : kTableMost)) return false;
     return !records || (w_bytes < (int64_t(8) << 20) && (several || !captured));
 }
 

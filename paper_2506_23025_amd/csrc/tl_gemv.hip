@@ -871,12 +871,14 @@ struct LeanAny : LeanOne {
     }
 };
 static_assert(sizeof(LeanOne) == 64, "the arguments of a lone call");
+static_assert(kMaxJobs <= kTableMost, "a table holds the jobs of a launch");
 
-// A few jobs in a small launch: 1 KB of arguments, and a workgroup finds its job by two scalar look-ups in turn (see jobs_by_table).
-constexpr int kLeanTableJobs = kTableJobs;
+// Up to R jobs: 68 bytes of arguments each, and a workgroup finds its job by two scalar look-ups in turn (see jobs_by_table).
+template <int R>
 struct LeanJobs {
-    int first[kLeanTableJobs];    // first workgroup of job j; INT_MAX for unused entries
-    LeanOne job[kLeanTableJobs];
+    static constexpr int kJobs = R;
+    int first[R];                 // first workgroup of job j; INT_MAX for unused entries
+    LeanOne job[R];
     __device__ WgRec mine() const
     {
         int j = 0;
@@ -884,7 +886,13 @@ struct LeanJobs {
         for (int i = 1; i < 8; ++i) j += int(blockIdx.x) >= first[i] ? 1 : 0;
         if (j == 7) {
 #pragma unroll
-            for (int i = 8; i < kLeanTableJobs; ++i) j += int(blockIdx.x) >= first[i] ? 1 : 0;
+            for (int i = 8; i < 16; ++i) j += int(blockIdx.x) >= first[i] ? 1 : 0;
+        }
+        if constexpr (R > 16) {
+            if (j == 15) {
+#pragma unroll
+                for (int i = 16; i < R; ++i) j += int(blockIdx.x) >= first[i] ? 1 : 0;
+            }
         }
         const LeanOne& J = job[j];
         WgRec r = J.at(int(blockIdx.x) - first[j]);
@@ -892,6 +900,11 @@ struct LeanJobs {
         return r;
     }
 };
+
+template <class Args>
+constexpr bool kIsTable = false;
+template <int R>
+constexpr bool kIsTable<LeanJobs<R>> = true;
 
 // Activations whose rows start at any even address (K no multiple of 64), to the places the operand set-up reads: through registers, a row to a
 // request.  Lane l takes piece l of the slice, eighth l % 8 of chunk l / 8; a row's last chunk is its last 64 weights (16 packed bytes).  What
@@ -1070,7 +1083,7 @@ gemv_lean_kernel(Args b)
         else with(std::integral_constant<int, 16>{});
     };
     // A job with fewer slices than waves, which the table of records does not hold: looking for it there cost the decode sweep 18.2 -> 20.0 us.
-    constexpr bool kIdle = ANY || std::is_same<Args, LeanJobs>::value;
+    constexpr bool kIdle = ANY || kIsTable<Args>;
     const bool idle = kIdle && wave >= slices;             // this wave has no slice at all
     if constexpr (!ANY) {
         if (!idle) stage_x(wave);
@@ -1822,7 +1835,7 @@ hipError_t launch_lean_args(const Args& args, dim3 grid, int NW, int T, int kept
 {
     auto with = [&](auto tag) {
         constexpr int GS = decltype(tag)::value;
-        if constexpr (!std::is_same<Args, LeanJobs>::value && !(std::is_same<Args, LeanAny>::value && GS == 0 && !ANY))   // which are one pass over K
+        if constexpr (!(std::is_same<Args, LeanAny>::value && GS == 0 && !ANY))   // which is one pass over K
             if (kept) return launch_lean_args<true, GS, ANY>(args, grid, NW, T, kept, s);
         return launch_lean_args<false, GS, ANY>(args, grid, NW, T, 0, s);
     };
@@ -1865,22 +1878,33 @@ hipError_t launch_lean(const GemvBatch& b, const int* wg, int NW, int T, int kep
         const LeanOne args = one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0]);
         return kept ? launch_lean_args<true, 0, false>(args, dim3(wg[0]), NW, T, kept, s) : launch_lean_args<false, 0, false>(args, dim3(wg[0]), NW, T, 0, s);
     }
-    if (b.count == 1 && !any) {
-        const GemvJob& J = b.job[0];
-        const LeanAny args{one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[0], J.scales, group_inverse(J))};
-        return launch_lean_args<false>(args, dim3(wg[0]), NW, T, kept, gs, s);
-    }
     if (table) {
-        LeanJobs lj;
-        int grid = 0;
-        for (int j = 0; j < kLeanTableJobs; ++j) {
-            lj.first[j] = j < b.count ? grid : 0x7fffffff;
-            if (j >= b.count) continue;
-            const GemvJob& J = b.job[j];
-            lj.job[j] = one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[j], J.scales, group_inverse(J));
-            grid += wg[j];
+        auto fill = [&](auto gs_tag, auto jobs_tag) {
+            constexpr int GS = decltype(gs_tag)::value;
+            LeanJobs<decltype(jobs_tag)::value> lj;
+            int grid = 0;
+            for (int j = 0; j < lj.kJobs; ++j) {
+                lj.first[j] = j < b.count ? grid : 0x7fffffff;
+                if (j >= b.count) continue;
+                const GemvJob& J = b.job[j];
+                lj.job[j] = one_job(J.W, J.x, J.y, J.gamma, J.K, J.N, J.Mrem, J.tiles, wg[j], J.scales, group_inverse(J));
+                grid += wg[j];
+            }
+            return any ? launch_lean_args<false, GS, true>(lj, dim3(grid), NW, T, 0, s) : launch_lean_args<false, GS, false>(lj, dim3(grid), NW, T, 0, s);
+        };
+        // the larger table takes small launches 0.1 us longer
+        auto with = [&](auto gs_tag) {
+            if constexpr (decltype(gs_tag)::value != 0)
+                if (b.count > kTableJobs) return fill(gs_tag, std::integral_constant<int, kTableMost>{});
+            return fill(gs_tag, std::integral_constant<int, kTableJobs>{});
+        };
+        switch (gs) {
+            case 0: return with(std::integral_constant<int, 0>{});
+            case 32: return with(std::integral_constant<int, 32>{});
+            case 64: return with(std::integral_constant<int, 64>{});
+            case 128: return with(std::integral_constant<int, 128>{});
+            default: return with(std::integral_constant<int, 256>{});
         }
-        return any ? launch_lean_args<true>(lj, dim3(grid), NW, T, 0, gs, s) : launch_lean_args<false>(lj, dim3(grid), NW, T, 0, gs, s);
     }
     LeanBatch lb;
     int grid = 0;
@@ -2056,8 +2080,7 @@ hipError_t launch_stream(GemvBatch& b, int max_slices, int nb, hipStream_t s, in
     if (table && records && !beyond) table = !being_captured(s);
     // What has scales and neither the plain records nor the table take goes to the form for any K and N, for which the workgroups are dealt out once: dealing
     // them out twice cost the host as much again (blocks of 33 to 64 rows 8 us of 23 in a loop).
-    if (gs != 0 && !table && b.count > 1 && !records) any = true;
-    if (gs != 0 && b.count == 1 && b.job[0].N % 16 != 0) any = true;       // one job's arguments are for whole tiles
+    if (gs != 0 && !table && !records) any = true;
     const int64_t g_max = any && !table ? kLeanMaxGroups : g_all;
     const int G = total_tiles < g_max ? int(total_tiles) : int(g_max);
     // Time of a workgroup in tile units: passes x (run time + start-up), see tl_deal.hpp.  The
@@ -2250,8 +2273,12 @@ hipError_t gemv_init()
             }
             raise_one(reinterpret_cast<const void*>(pick_lean<Alone, false, GS, false>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<Alone, true, GS, false>(T)), true);
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs, false, GS, false>(T)), false);
-            raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs, false, GS, true>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs<kTableJobs>, false, GS, false>(T)), false);
+            raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs<kTableJobs>, false, GS, true>(T)), false);
+            if constexpr (GS != 0) {
+                raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs<kTableMost>, false, GS, false>(T)), false);
+                raise_one(reinterpret_cast<const void*>(pick_lean<LeanJobs<kTableMost>, false, GS, true>(T)), false);
+            }
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, false, GS, true>(T)), false);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanBatch, true, GS, true>(T)), true);
             raise_one(reinterpret_cast<const void*>(pick_lean<LeanAny, false, GS, true>(T)), false);
@@ -2307,16 +2334,16 @@ int units_per_group(int64_t K, int64_t group, int kind)
     return int(group / unit < all ? group / unit : all);
 }
 
-hipError_t launch_any_rows(const GemvJob& j, int64_t M, int gs, hipStream_t s)
+hipError_t launch_rows(const GemvJob& j, int64_t M, int gs, bool any, hipStream_t s)
 {
-    return launch_lean_rows(j.x, j.W, j.gamma, j.scales, group_inverse(j), j.y, M, j.N, j.K, gs, true, s);
+    return launch_lean_rows(j.x, j.W, j.gamma, j.scales, group_inverse(j), j.y, M, j.N, j.K, gs, any || j.N % 16 != 0, s);
 }
 
 // Blocks of 16 rows in one launch, or, where their runs are too long for what a launch keeps of their sums, half of them in each of two: one launch per
 // block took 26 jobs of 33 rows and K up to 11008 418 us (the general kernel 216), halves take 174.
-hipError_t launch_any_blocks(const GemvJob* blocks, int count, int gs, hipStream_t s)
+hipError_t launch_blocks(const GemvJob* blocks, int count, int gs, bool any, hipStream_t s)
 {
-    if (count == 1) return launch_any_rows(blocks[0], blocks[0].Mrem, gs, s);
+    if (count == 1) return launch_rows(blocks[0], blocks[0].Mrem, gs, any, s);
     GemvBatch b;
     b.count = count;
     int max_slices = 1;
@@ -2324,10 +2351,10 @@ hipError_t launch_any_blocks(const GemvJob* blocks, int count, int gs, hipStream
         b.job[q] = blocks[q];
         if (blocks[q].slices > max_slices) max_slices = blocks[q].slices;
     }
-    const hipError_t e = launch_stream(b, max_slices, 1, s, gs, true);
+    const hipError_t e = launch_stream(b, max_slices, 1, s, gs, any);
     if (e != hipErrorInvalidValue) return e;
-    const hipError_t first = launch_any_blocks(blocks, count / 2, gs, s);
-    return first == hipSuccess ? launch_any_blocks(blocks + count / 2, count - count / 2, gs, s) : first;
+    const hipError_t first = launch_blocks(blocks, count / 2, gs, any, s);
+    return first == hipSuccess ? launch_blocks(blocks + count / 2, count - count / 2, gs, any, s) : first;
 }
 
 hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s, int gs = 0)
@@ -2335,7 +2362,7 @@ hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s, int gs 
     GemvJob blocks[kMaxJobs];
     int held = 0;
     auto flush = [&]() -> hipError_t {
-        const hipError_t e = held ? launch_any_blocks(blocks, held, gs, s) : hipSuccess;
+        const hipError_t e = held ? launch_blocks(blocks, held, gs, true, s) : hipSuccess;
         held = 0;
         return e;
     };
@@ -2347,7 +2374,7 @@ hipError_t launch_any_jobs(const AnyJob* jobs, int count, hipStream_t s, int gs 
         j.tiles = int((d.N + 15) / 16);
         j.slices = int((d.K + kSliceK - 1) / kSliceK);
         j.scales = d.scales; j.hpg = gs ? units_per_group(d.K, d.group, gs) : 0;
-        if (count == 1) return launch_any_rows(j, d.M, gs, s);
+        if (count == 1) return launch_rows(j, d.M, gs, true, s);
         for (int64_t m0 = 0; m0 < d.M; m0 += 16) {
             GemvJob q = j;
             q.x = d.x + m0 * d.K;
@@ -2512,27 +2539,13 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
         return hipSuccess;
     }
     // Each kind of groups has instances of its own and shares launches, kMaxJobs blocks of 16 activation rows per launch; so do, kind
-    // by kind, jobs of other K.  A launch whose runs would not fit the LDS of a multi-pass workgroup (launch_stream says so
-    // without launching) goes out as one launch per job.
+    // by kind, jobs of other K.
     for (int kind = 32; kind <= 256; kind *= 2) {
-        GemvBatch b;
-        b.count = 0;
-        int max_slices = 1;
+        GemvJob blocks[kMaxJobs];
+        int held = 0;
         auto flush = [&]() -> hipError_t {
-            if (b.count == 0) return hipSuccess;
-            hipError_t e = launch_stream(b, max_slices, 1, s, kind);
-            if (e == hipErrorInvalidValue && b.count > 1) {
-                // one launch per row block; a block alone fits by gemv_gs_supports
-                e = hipSuccess;
-                for (int q = 0; q < b.count && e == hipSuccess; ++q) {
-                    GemvBatch one;
-                    one.count = 1;
-                    one.job[0] = b.job[q];
-                    e = launch_stream(one, one.job[0].slices, 1, s, kind);
-                }
-            }
-            b.count = 0;
-            max_slices = 1;
+            const hipError_t e = held ? launch_blocks(blocks, held, kind, false, s) : hipSuccess;
+            held = 0;
             return e;
         };
         constexpr int kAtOnce = 64;
@@ -2566,9 +2579,8 @@ hipError_t launch_gemv_gs_jobs(const GemmGsDesc* jobs, int count, hipStream_t s)
                 j.mr = pow2_at_least(j.Mrem);
                 j.run = j.plus = 0;
                 j.scales = d.scales; j.hpg = hpg; j.reserved = 0;
-                b.job[b.count++] = j;
-                if (slices > max_slices) max_slices = slices;
-                if (b.count == kMaxJobs) {
+                blocks[held++] = j;
+                if (held == kMaxJobs) {
                     const hipError_t e = flush();
                     if (e != hipSuccess) return e;
                 }

@@ -121,17 +121,16 @@ KernelChoice tile_gs_choice(int64_t M, int64_t N, int64_t K, int64_t group)
     KernelChoice c{gemv_gs_supports(M, N, K, group), 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!c.streams || M <= 16) return c;
     c.stream = over_stream_launches(M, [&](int64_t m) { return stream_gs_time(m, N, K, group); });
-    // In shared launches, which mostly have one workgroup per CU, so that with few slices of K wavefronts are left out: fitted to 600 groups of 2 to 8 alike
-    // jobs of M = 17 .. 1500, N = 64 .. 8192, K = 64 .. 8192, 11 % on average.  The way chosen there takes 1.5 % longer than the better one;
-    // counted as 1.15 to 1.3 times as long as in a launch of its own 9 %, up to 3.7 times.
+    // In shared launches: fitted to 600 groups of 2 to 8 alike jobs of M = 17 .. 1500, N = 64 .. 8192, K = 64 .. 8192, 10 % on average.  The way chosen there
+    // takes 1.1 % longer than the better one (1.6 % without the 1 us); counted as 1.15 to 1.3 times as long as in a launch of its own 9 %, up to 3.7 times.
     const StreamLine& line = stream_line(group);
     const int64_t s = (K + 511) / 512, p = (s + 7) / 8;
-    constexpr double crowd[9] = {0, 4.31, 2.62, 1.6, 1.56, 1.12, 1.24, 1.1, 1.1};
+    constexpr double crowd[9] = {0, 1.42, 1.37, 1.19, 1.24, 1.07, 1.18, 1.06, 1.07};
     const double blocks = double((M + 15) / 16);
-    c.launch = 4.16;
+    c.launch = 4.42;
     c.launches = blocks / 32.0;
     const double x = blocks * double((N + 15) / 16) / 256.0;
-    c.own = s <= 8 ? crowd[s] * line.per_tile[s] * x : 1.18 * (line.tile_slice * double(s) + line.tile_pass * double(p)) * x + 2.84 * double(p) * c.launches;
+    c.own = 1.0 + (s <= 8 ? crowd[s] * line.per_tile[s] * x : 1.08 * (line.tile_slice * double(s) + line.tile_pass * double(p)) * x + 2.44 * double(p) * c.launches);
     c.tiled = c.stream;
     // Below the fit, K < 512, both times are too long, the tiled kernel's by 36 % at K = 64 and 10 % at 448 (96 x 64 x 2912 3.7 us, streaming 4.7; 1572 x 128 x
     // 96 3.6 and 4.3).  Over 384 such calls the one chosen is 0.2 % slower than the best, 7 % in one of a hundred (without the factors 6.7 and 31 %).

@@ -5,7 +5,7 @@ import pytest
 import oracle
 import paper_2506_23025_amd as tl
 import synth_inputs as si
-from parity import assert_close, dev_u32, to_dev
+from parity import assert_close, dev_u32, launches, to_dev
 from test_tile_choice import SCALES, STREAMS, TILED, TWO_BIT, runs, shares
 
 pytestmark = pytest.mark.gpu
@@ -162,3 +162,25 @@ def test_rows_of_several_launches(M, N, K, group, kernel):
     y, _, _, _ = product(M, N, K, group, 65000, x, sc)
     rows = np.r_[0:20, 4080:M]
     check(y[rows], x[rows], W, sc, group, "many rows")
+
+
+# Shared launches: as many jobs as a launch holds find their place in a table where 256 records do not do (more workgroups, jobs with fewer slices than waves);
+# runs too long for what one launch keeps of their sums are two launches
+@pytest.mark.parametrize("specs,count", [([(16, 1024, 512, 256)] * 32, 1), ([(5, 528, 1024, 64), (16, 300, 512, 64), (1, 20, 2048, 64)] * 10, 1), ([(9, 516, 1000, 128)] * 24, 1),
+                                         ([(70, 1024, 1024, 32)] * 6, 1), ([(70, 1024, 1024, 32)] * 7, 2), ([(2, 14336, 4608, 64)] * 12, 2), ([(2, 14336, 4600, 64)] * 12, 2)])
+def test_launches_of_many_jobs(specs, count):
+    tl.tl_init()
+    assert all(shares(SCALES, specs))
+    made, jobs, want = {}, [], []
+    for i, (M, N, K, group) in enumerate(specs):
+        if (M, N, K, group) not in made:
+            x, W, sc = inputs(M, N, K, group, 68000 + M + N + K)
+            made[M, N, K, group] = (x, W, sc, to_dev(x.view(np.int16)), dev_u32(tl.tl_pack_2bit(W)), to_dev(sc.view(np.int16)))
+        x, W, sc, xd, wd, sd = made[M, N, K, group]
+        yd = to_dev(np.full(M * N + 64, -21555, dtype=np.int16))
+        jobs.append((xd, wd, sd, group, yd, M, N, K))
+        want.append((x, W, sc, yd))
+    assert launches(lambda stream: tl.tl_ternary_gemm_gs_grouped(jobs, stream)) == count
+    tl.tl_ternary_gemm_gs_grouped(jobs)
+    for (x, W, sc, yd), (M, N, K, group) in zip(want, specs):
+        check(result(yd, M, N), x, W, sc, group, f"{M}x{N}x{K} group {group}")

@@ -194,7 +194,8 @@ def test_small_launches_find_their_jobs_in_a_table_unless_captured():
         assert not fn(2, 1, 1, 0, 9 * mb, captured) and not fn(2, 1, 1, 1, 9 * mb, captured)
         assert fn(2, 1, 1, 1, 2 * mb, captured)            # several workgroups to a CU: equal on the device, cheaper on the host
         assert fn(2, 1, 0, 0, 90 * mb, captured)           # nothing else takes it
-        assert not fn(1, 1, 1, 0, mb, captured) and not fn(17, 1, 0, 0, mb, captured) and not fn(2, 0, 0, 0, mb, captured)
+        assert not fn(1, 1, 1, 0, mb, captured) and not fn(17, 1, 1, 0, mb, captured) and not fn(2, 0, 0, 0, mb, captured)
+        assert fn(32, 1, 0, 1, mb, captured) and not fn(33, 1, 0, 1, mb, captured)
 
 
 def test_grouped_jobs_share_launches_where_that_is_faster():
@@ -219,12 +220,12 @@ def test_grouped_jobs_share_launches_where_that_is_faster():
 
 
 def test_jobs_of_many_rows_leave_the_shared_launches():
-    # measured (us), 2 to 8 alike jobs that share launches / as calls of their own: 2-bit words 43.4 / 16.5, 16.0 / 13.9; scales 64.4 / 36.0, 20.1 / 12.0; 1.6-bit
+    # measured (us), 2 to 8 alike jobs that share launches / as calls of their own: 2-bit words 43.4 / 16.5, 16.0 / 13.9; scales 64.4 / 36.0, 27.6 / 21.6; 1.6-bit
     # codes 75.4 / 65.7 and 30.6 / 25.4 (two of several); and the other way round 5.1 / 13.4, 8.2 / 9.5, 8.0 / 16.4, and of different ones 22.4 / 27.9
     assert not any(shares(TWO_BIT, [(834, 2624, 128), (834, 6054, 488)]))
     assert not shares(TWO_BIT, [(57, 96, 208), (302, 3520, 64)])[1]                    # K = 64 in the form for any K: 15.7 / 8.1
     for form, n, job in ((TWO_BIT, 4, (1479, 80, 512)), (TWO_BIT, 2, (506, 272, 453)), (SCALES, 2, (787, 4128, 273, 64)),
-                         (SCALES, 2, (131, 4672, 164, 128)), (ONE_POINT_SIX, 4, (835, 2432, 80)), (ONE_POINT_SIX, 2, (1197, 272, 1071))):
+                         (SCALES, 4, (482, 328, 621, 64)), (ONE_POINT_SIX, 4, (835, 2432, 80)), (ONE_POINT_SIX, 2, (1197, 272, 1071))):
         assert not any(shares(form, [job] * n)), (form, job)
     assert all(shares(SCALES, [(33, 8032, 640, 256), (33, 10312, 8064, 256)])) and all(shares(ONE_POINT_SIX, [(2, 3200, 136), (445, 208, 384)]))
     for form, n, job in ((TWO_BIT, 4, (99, 272, 318)), (SCALES, 2, (70, 2176, 576, 32)), (ONE_POINT_SIX, 4, (129, 350, 400))):
